@@ -10,17 +10,19 @@
 // coalesced 1 KiB read straight into registers.  V is transposed on the way (the value product
 // contracts over keys, which are the strided axis of the cache).
 //
-// attn_prefill_kernel: a wavefront owns kTok consecutive query tokens of one key-value head and
-// works alone -- no LDS, no barriers.  The G (<=16) query heads of a token fill the 16 columns of
-// one MFMA tile, so per-token block sets cost no padded matrix work when G = 16.  The wavefront
-// walks the union of its tokens' block lists in ascending order; each fragment it loads is used
-// for every one of its tokens that selected the block.  Both contractions are computed
+// attn_prefill_kernel: a wavefront owns the kTok consecutive query tokens of kTiles MFMA tiles of one
+// key-value head; the 16 columns of a tile are the G query heads of 16 / G tokens, so no column is
+// padding.  The wavefront walks the union of its tokens' block lists in ascending order; each
+// fragment it loads is used for every tile with a token that selected the block (inside a tile the
+// columns of the other tokens get probability zero).  Either every wavefront works alone, or the
+// four of a workgroup own the same tokens, take every fourth block of the union and merge their
+// partial results at the end.  Both contractions are computed
 // transposed so that no register shuffles are needed:
-//   S^T[key, head] = K[key, :] . Q[head, :]            A = K fragment,   B = Q (registers)
+//   S^T[key, head] = K[key, :] . Q[head, :]            A = K fragment,   B = Q (registers or LDS)
 //   O^T[c,  head] += V^T[c, key] . P^T[key, head]       A = V^T fragment, B = P^T taken straight
 // from the accumulator layout of S^T (lane = head column, 4 consecutive keys per 16-lane group),
 // with the key order inside the packed V^T rows permuted to match.
-#include "common.h"
+#include "token_union.h"
 
 namespace infllmv2 {
 
@@ -32,15 +34,6 @@ constexpr int kPackedBlockU4 = 2 * kFragsPerOperand * 64; // uint4 per packed (K
 __device__ inline uint32_t xcd_contiguous_id(uint32_t bid, uint32_t n) {
     const uint32_t per = n >> 3, rem = n & 7u, x = bid & 7u, slot = bid >> 3;
     return x * per + (x < rem ? x : rem) + slot;
-}
-
-__device__ inline int wave_min_i32(int v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int w = __shfl_xor(v, o);
-        v = w < v ? w : v;
-    }
-    return v;
 }
 
 // ---- re-layout of one 64-token block per workgroup -------------------------------------------------
@@ -108,13 +101,17 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
 // of the wavefront's list) is issued into the same registers, so loads stay in flight under the
 // wavefront's own arithmetic.
 //
+// What bounds it: the L2 -> register path (64 bytes per clock and compute unit).  At 32K tokens (2 heads, G = 16,
+// top-k 16) the union of two tokens has 24 blocks, of four 33: four tokens per wavefront, their queries in LDS so that
+// the accumulators (128 registers) and a ring of four units fit 256 registers, move 15.9 GB instead of 22.5 GB through
+// that path: 1.00 -> 0.78 ms.  Without misses (32 blocks in all) it would take 0.75 ms, without the softmax 0.76 ms.
+//
 // The softmax keeps a per-head reference exponent taken from the data and re-bases it only when
 // a partial sum leaves the safe range (or on first use, when it is still NaN): the common path is
 // one fma, one exp2 and one add per probability, with no running maximum.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr float kPsumLimit = 0x1p40f;
 constexpr int kNone = 0x7fffffff;
-constexpr int kBlkBits = 27, kBlkMask = (1 << kBlkBits) - 1;
 
 // probabilities 2^(s*c + ne) of 32 keys (two key tiles) of one token in MFMA B layout, and their sum
 __device__ __forceinline__ float half_probs(const f32x4 (&s)[2], float c, float ne, bf16x8 &p8) {
@@ -130,130 +127,119 @@ __device__ __forceinline__ float half_probs(const f32x4 (&s)[2], float c, float 
     return sum;
 }
 
-template <int kTok, int kNU, int kWavesPerSimd>
-__global__ __launch_bounds__(256, kWavesPerSimd) void attn_prefill_kernel(Dims dm, Tensor q, const uint4 *__restrict__ kvp,
+constexpr int kRun = 4;                                  // tiles of a sequence that go to one XCD together
+
+template <int kG, int kTiles, int kSplit>
+struct AttnCfg {
+    static constexpr bool kQLds = kTiles > 2;             // queries in LDS: registers hold the accumulators of four tiles
+    static constexpr int kTokPerTile = 16 / kG;           // tokens in the 16 columns of one MFMA tile
+    static constexpr int kTok = kTiles * kTokPerTile;     // tokens of a wavefront (of the workgroup when its waves split the blocks)
+    static constexpr int kTokPerWg = kSplit > 1 ? kTok : 4 * kTok;
+    static constexpr int kCopies = kSplit > 1 ? 1 : 4;    // of the list and the queries: one per wavefront, or shared
+    __host__ __device__ static size_t queries_at(int topk) { return kCopies * UnionLds::bytes(kTok, topk); }
+    __host__ __device__ static size_t merge_at(int topk) {
+        return queries_at(topk) + (kQLds ? (size_t)kCopies * kTiles * 4 * 64 * sizeof(uint4) : 0);
+    }
+    static size_t lds_bytes(int topk) {                   // merge area: one tile of every wavefront at a time
+        return merge_at(topk) + (kSplit > 1 ? (size_t)4 * 64 * (8 * sizeof(float4) + sizeof(float2)) : 0);
+    }
+};
+
+template <int kG, int kTiles, int kSplit>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q, const uint4 *__restrict__ kvp,
                                                             int32_t nb_cap,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
                                                             Tensor out, float *__restrict__ lse,
-                                                            int32_t n_tiles) {
-    static_assert(kNU == 4 || kNU == 8, "ring of 4 or 8 units");
-    static_assert(kTok <= 4 && 64 % kTok == 0, "membership bits / one own block per wavefront");
-    // a workgroup is 4 independent wavefronts covering 4*kTok consecutive tokens
-    const uint32_t vid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-    const int tile = vid % n_tiles;
-    const int h = (vid / n_tiles) % dm.Hkv;
-    const int b = vid / (n_tiles * dm.Hkv);
-    int32_t L = seqlens[b];
+                                                            int32_t slots) {
+    using C = AttnCfg<kG, kTiles, kSplit>;
+    constexpr int kNU = 4, kTPT = C::kTokPerTile, kTok = C::kTok;
+    static_assert(64 % kTok == 0 && kTok <= 32, "one own block per wavefront; member bits in one word");
+    extern __shared__ __align__(16) unsigned char attn_smem[];
+    // grid: 8 XCDs x slots x (sequence, key-value head); see launch_attn_variant
+    const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
+    const int h = bh % dm.Hkv, b = bh / dm.Hkv;
+    int32_t L = __builtin_amdgcn_readfirstlane(seqlens[b]);
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = (tile * 4 + wave) * kTok;             // this wavefront's first token
-    if (t0 >= L) return;
+    const int tile = (L + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = kSplit > 1 ? tile * kTok : (tile * 4 + wave) * kTok;   // this wavefront's first token
+    if (tile < 0 || t0 >= L) return;                     // (uniform over the workgroup when it splits the blocks)
     const int b_own = t0 / kBlock;                       // kTok divides 64: one own block per wavefront
-    const int n = lane & 15, g = lane >> 4;              // MFMA column (query head) and 16-lane group
-    const int G = dm.G;
+    const int n = lane & 15, g = lane >> 4;              // MFMA column (token, query head) and 16-lane group
+    const int tn = n / kG;                               // token of the column inside its tile
     const float c = dm.scale_log2;
 
-    bf16x8 qf[kTok][4];
-    f32x4 o[kTok][8];
-    float neg_m[kTok], l_run[kTok];
-    int own[kTok];                                       // lane e < topk holds entry e of the block list
+    bf16x8 qf[C::kQLds ? 1 : kTiles][4];
+    bf16x8 *ql = reinterpret_cast<bf16x8 *>(attn_smem + C::queries_at(dm.topk)) +                // [tile][ks][lane]
+                 (kSplit > 1 ? 0 : wave * kTiles * 4 * 64) + lane;
+    f32x4 o[kTiles][8];
+    float neg_m[kTiles], l_run[kTiles];
 #pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        const int tok = t0 + u;
-        const bool live = tok < L;
+    for (int u = 0; u < kTiles; ++u) {
+        const int tok = t0 + u * kTPT + tn;
+        const __bf16 *qr = q.ptr + b * q.sb + (int64_t)tok * q.st + (int64_t)(h * kG + n % kG) * q.sh + 8 * g;
+        if (!C::kQLds || kSplit == 1 || wave == u) {     // (the waves that share their tokens load a tile each)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            qf[u][ks] = zero8();
-            if (live && n < G)
-                qf[u][ks] = load8(q.ptr + b * q.sb + (int64_t)tok * q.st + (int64_t)(h * G + n) * q.sh +
-                                  32 * ks + 8 * g);
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 x = tok < L ? load8(qr + 32 * ks) : zero8();
+                if constexpr (C::kQLds) ql[(u * 4 + ks) * 64] = x;
+                else qf[u][ks] = x;
+            }
         }
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) o[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         neg_m[u] = __builtin_nanf("");
         l_run[u] = 0.f;
-        int e = kNone;
-        if (live && lane < dm.topk) {
-            int x = block_idx[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + tok) * dm.topk + lane];
-            if (x >= 0 && x <= b_own) e = x;
-        }
-        own[u] = e;
     }
-
-    // Ascending union of the tokens' block lists, by counting instead of sorting: an entry's place
-    // is the number of distinct smaller entries.  A token's own list holds no duplicates, so an
-    // entry is a duplicate exactly when a lower-numbered token of the wavefront lists the same
-    // block.  Entry i of the union ends up in lane i%64 of ul[i/64] as block | member bits << 27.
-    // (A caller's row that lists a block twice, against the contract, is attended once: the copy in the
-    // higher lane counts as a duplicate too, so every rank below is taken by exactly one entry.)
-    int w[kTok];                                         // own[u] with duplicates removed
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        bool dup = false;
-        for (int j = 0; j < dm.topk; ++j) dup |= j < lane && __builtin_amdgcn_readlane(own[u], j) == own[u];
-#pragma unroll
-        for (int u2 = 0; u2 < u; ++u2)
-            for (int j = 0; j < dm.topk; ++j) dup |= __builtin_amdgcn_readlane(own[u2], j) == own[u];
-        w[u] = dup ? kNone : own[u];
-    }
-    int rank[kTok], bits[kTok];
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) rank[u] = bits[u] = 0;
-#pragma unroll
-    for (int u2 = 0; u2 < kTok; ++u2)
-        for (int j = 0; j < dm.topk; ++j) {
-            const int wj = __builtin_amdgcn_readlane(w[u2], j), xj = __builtin_amdgcn_readlane(own[u2], j);
-#pragma unroll
-            for (int u = 0; u < kTok; ++u) {
-                rank[u] += wj < w[u] ? 1 : 0;            // kNone (absent or duplicate) is never smaller
-                bits[u] |= xj == w[u] ? 1 << u2 : 0;
-            }
-        }
-    __shared__ int ulist[4][64 * kTok];
+    const UnionLds ul(attn_smem + (kSplit > 1 ? 0 : wave * UnionLds::bytes(kTok, dm.topk)));
     int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        const bool have = w[u] != kNone;
-        if (have) ulist[wave][rank[u]] = w[u] | (bits[u] << kBlkBits);
-        cnt += __popcll(__ballot(have));
+    if (kSplit == 1 || wave == 0)
+        cnt = build_union<kTok>(block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk, dm.topk,
+                                min(kTok, (int)L - t0), b_own, ul, lane);
+    if constexpr (kSplit > 1) {
+        __shared__ int cnt_s;
+        if (threadIdx.x == 0) cnt_s = cnt;
+        __syncthreads();
+        cnt = __builtin_amdgcn_readfirstlane(cnt_s);
     }
-    int ul[kTok];
-#pragma unroll
-    for (int r = 0; r < kTok; ++r) ul[r] = ulist[wave][64 * r + lane];   // same wavefront: LDS keeps the order
-    auto union_entry = [&](int i) __attribute__((always_inline)) {
-        int e = __builtin_amdgcn_readlane(ul[0], i & 63);
-#pragma unroll
-        for (int r = 1; r < kTok; ++r)
-            if ((i >> 6) == r) e = __builtin_amdgcn_readlane(ul[r], i & 63);
-        return e;
-    };
+    auto union_entry = [&](int i) __attribute__((always_inline)) { return ul.list[min(i, cnt - 1)]; };
 
-    const u32x4 *kv_lane = reinterpret_cast<const u32x4 *>(kvp) +
-                           ((int64_t)b * dm.Hkv + h) * nb_cap * kPackedBlockU4 + lane;
+    // A block's address is uniform: fragments come by buffer loads (scalar base and offset, one vector register of lane
+    // offsets), so that fetching them costs no vector instructions.
+    const char *kv_head = reinterpret_cast<const char *>(kvp) + ((int64_t)b * dm.Hkv + h) * nb_cap * (kPackedBlockU4 * 16);
+    const uint32_t lane16 = 16u * lane;
     u32x4 ring[kNU][4];
-    auto issue = [&](int unit, const u32x4 *bp) __attribute__((always_inline)) {
+    auto block_rsrc = [&](uint32_t blk) __attribute__((always_inline)) {
+        const int64_t at = (int64_t)(int)__builtin_amdgcn_readfirstlane(blk) * (kPackedBlockU4 * 16);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kv_head) + at, 0, kPackedBlockU4 * 16, 0x00027000);
+    };
+    auto fragment = [&](__amdgpu_buffer_rsrc_t bp, int f) __attribute__((always_inline)) {
+        return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bp, lane16, f * 1024, 0));
+    };
+    auto issue = [&](int unit, __amdgpu_buffer_rsrc_t bp) __attribute__((always_inline)) {
         const int hs = unit >> 2, r = unit & 3;
         if (r < 2) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) ring[unit % kNU][ks] = bp[(ks * 4 + 2 * hs + r) * 64];
+            for (int ks = 0; ks < 4; ++ks) ring[unit % kNU][ks] = fragment(bp, ks * 4 + 2 * hs + r);
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                ring[unit % kNU][i] = bp[(kFragsPerOperand + (4 * (r - 2) + i) * 2 + hs) * 64];
+                ring[unit % kNU][i] = fragment(bp, kFragsPerOperand + (4 * (r - 2) + i) * 2 + hs);
         }
     };
 
-    // softmax of one member token on 32 keys: pf = P^T in bf16; re-bases the reference when needed
-    auto softmax = [&](f32x4 (&s)[2], int u, bf16x8 &pf) __attribute__((always_inline)) {
-        float ps = half_probs(s, c, neg_m[u], pf);
+    // softmax of one tile on 32 keys: pf = P^T in bf16; re-bases the reference when needed.  `member`: this column's
+    // token selected the block (always true for one token per tile)
+    auto softmax = [&](f32x4 (&s)[2], int u, bool member, bf16x8 &pf) __attribute__((always_inline)) {
+        float ps = half_probs(s, c, member ? neg_m[u] : -INFINITY, pf);
         if (__any(!(ps <= kPsumLimit))) {                 // rare: too large, inf, or NaN (no reference yet)
             float tmax = -INFINITY;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) tmax = fmaxf(tmax, s[t][j]);
-            tmax = xgroup_max(tmax) * c;                  // per head, same in the four lane groups
+            tmax = member ? xgroup_max(tmax) * c : -INFINITY;   // per column, same in the four lane groups
             const float old = neg_m[u];                   // NaN = no reference yet
             const float m_new = (old != old) ? tmax : fmaxf(-old, tmax);
             if (m_new > -INFINITY) {
@@ -262,8 +248,8 @@ __global__ __launch_bounds__(256, kWavesPerSimd) void attn_prefill_kernel(Dims d
 #pragma unroll
                 for (int dt = 0; dt < 8; ++dt) o[u][dt] *= f;
                 neg_m[u] = -m_new;
-                ps = half_probs(s, c, -m_new, pf);
-            } else {                                      // every key of this head masked so far
+                ps = half_probs(s, c, member ? -m_new : -INFINITY, pf);
+            } else {                                      // every key of this column masked so far
                 ps = 0.f;
                 pf = zero8();
             }
@@ -275,80 +261,152 @@ __global__ __launch_bounds__(256, kWavesPerSimd) void attn_prefill_kernel(Dims d
     // compiler's wait-count bookkeeping otherwise merges those pending loads into the loop and
     // waits for ALL outstanding loads at the top of every iteration, which defeats the ring.
     __builtin_amdgcn_s_waitcnt(0);
-    if (cnt > 0) {
-        const u32x4 *bp = kv_lane + (int64_t)(union_entry(0) & kBlkMask) * kPackedBlockU4;
+    constexpr int kStep = kSplit;                        // the waves of a splitting workgroup take every kSplit-th block
+    const int first = kSplit > 1 ? wave : 0;
+    uint2 e_cur = {0u, 0u}, e_nxt = {0u, 0u};
+    if (first < cnt) {
+        e_cur = union_entry(first);
+        e_nxt = union_entry(first + kStep);
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
 #pragma unroll
         for (int unit = 0; unit < kNU; ++unit) issue(unit, bp);
     }
-    for (int ci = 0; ci < cnt; ++ci) {
-        const int e = union_entry(ci);
-        const int blk = e & kBlkMask, bits = e >> kBlkBits;
-        const bool has_next = ci + 1 < cnt;
-        const int en = union_entry(has_next ? ci + 1 : ci);
-        const u32x4 *bp = kv_lane + (int64_t)blk * kPackedBlockU4;
-        const u32x4 *bn = kv_lane + (int64_t)(en & kBlkMask) * kPackedBlockU4;
+    for (int ci = first; ci < cnt; ci += kStep) {
+        const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
+        const uint32_t bits = __builtin_amdgcn_readfirstlane(e_cur.y);
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x), bn = block_rsrc(e_nxt.x);
+        e_cur = e_nxt;
+        e_nxt = union_entry(ci + 2 * kStep);
         const int key0 = blk * kBlock;
-        const bool edge = (blk == b_own) || (key0 + kBlock > L);
+        const bool edge = blk == b_own;                  // the last, partial block of a sequence is its last tokens' own
+        uint32_t tb[kTiles];                             // member bits of the tile's tokens
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) tb[u] = (bits >> (u * kTPT)) & ((1u << kTPT) - 1u);
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
             // ---- S^T = K . Q^T for 32 keys, one key tile per unit ------------------------------
-            f32x4 s[kTok][2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int unit = 4 * hs + r;
-#pragma unroll
-                for (int u = 0; u < kTok; ++u) {
-                    if (!((bits >> u) & 1)) continue;
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        acc = mfma16(__builtin_bit_cast(bf16x8, ring[unit % kNU][ks]), qf[u][ks], acc);
-                    s[u][r] = acc;
-                }
+            auto refill = [&](int unit) __attribute__((always_inline)) {
                 if (unit + kNU < 8) issue(unit + kNU, bp);
                 else issue(unit + kNU - 8, bn);      // (a harmless re-read of this block at the tail)
+            };
+            auto scores = [&](int r, const bf16x8 (&qu)[4]) __attribute__((always_inline)) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    acc = mfma16(__builtin_bit_cast(bf16x8, ring[(4 * hs + r) % kNU][ks]), qu[ks], acc);
+                return acc;
+            };
+            f32x4 s[kTiles][2];
+            if constexpr (!C::kQLds) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+#pragma unroll
+                    for (int u = 0; u < kTiles; ++u)
+                        if (tb[u]) s[u][r] = scores(r, qf[u]);
+                    refill(4 * hs + r);
+                }
             }
             // ---- probabilities, P^T packed to bf16 in MFMA B layout ---------------------------
-            bf16x8 pf[kTok];
+            bf16x8 pf[kTiles];
 #pragma unroll
-            for (int u = 0; u < kTok; ++u) {
-                if (!((bits >> u) & 1)) continue;
+            for (int u = 0; u < kTiles; ++u) {
+                if (!tb[u]) continue;
+                if constexpr (C::kQLds) {                // a tile at a time: its queries come from LDS once per half
+                    bf16x8 qu[4];
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) qu[ks] = ql[(u * 4 + ks) * 64];
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) s[u][r] = scores(r, qu);
+                }
                 if (edge) {
-                    const int tok = t0 + u;
+                    const int tok = t0 + u * kTPT + tn;
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             if (key0 + 32 * hs + 16 * t + 4 * g + j > tok) s[u][t][j] = -INFINITY;
                 }
-                softmax(s[u], u, pf[u]);
+                softmax(s[u], u, kTPT == 1 || ((tb[u] >> tn) & 1u), pf[u]);
+            }
+            if constexpr (C::kQLds) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) refill(4 * hs + r);
             }
             // ---- O^T += V^T . P^T, four channel tiles per unit --------------------------------
 #pragma unroll
             for (int r = 2; r < 4; ++r) {
                 const int unit = 4 * hs + r, dh = r - 2;
 #pragma unroll
-                for (int u = 0; u < kTok; ++u) {
-                    if (!((bits >> u) & 1)) continue;
+                for (int u = 0; u < kTiles; ++u) {
+                    if (!tb[u]) continue;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         o[u][4 * dh + i] =
                             mfma16(__builtin_bit_cast(bf16x8, ring[unit % kNU][i]), pf[u], o[u][4 * dh + i]);
                 }
-                if (unit + kNU < 8) issue(unit + kNU, bp);
-                else issue(unit + kNU - 8, bn);      // (a harmless re-read of this block at the tail)
+                refill(unit);
             }
         }
     }
 
-    // ---- normalise and write: lane holds channels 16*dt + 4*g .. +3 of head n ------------------
+    if constexpr (kSplit > 1) {
+        // ---- merge the four waves, a tile at a time: every wave leaves (o, reference, sum) of its blocks in LDS, then
+        // wave w combines channel tiles 2w, 2w+1 of every column --------------------------------------------------
+        float4 *po = reinterpret_cast<float4 *>(attn_smem + C::merge_at(dm.topk));   // [wave][dt][lane]
+        float2 *pm = reinterpret_cast<float2 *>(po + 4 * 8 * 64);                    // [wave][lane]
 #pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        const int tok = t0 + u;
-        if (tok >= L || n >= G) continue;
+        for (int u = 0; u < kTiles; ++u) {
+            if (u) __syncthreads();
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt)
+                po[(wave * 8 + dt) * 64 + lane] = float4{o[u][dt][0], o[u][dt][1], o[u][dt][2], o[u][dt][3]};
+            pm[wave * 64 + lane] = float2{(neg_m[u] != neg_m[u]) ? -INFINITY : -neg_m[u], xgroup_sum(l_run[u])};
+            __syncthreads();
+            const int tok = t0 + u * kTPT + tn;
+            float2 m4[4];
+            float M = -INFINITY, l_tot = 0.f, f[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                m4[w] = pm[w * 64 + lane];
+                M = fmaxf(M, m4[w].x);
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                f[w] = m4[w].x > -INFINITY ? fast_exp2(m4[w].x - M) : 0.f;
+                l_tot += f[w] * m4[w].y;
+            }
+            if (tok < L) {
+                const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+                __bf16 *op = out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)(h * kG + n % kG) * out.sh + 4 * g;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int dt = 2 * wave + i;
+                    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const float4 y = po[(w * 8 + dt) * 64 + lane];
+                        x += f32x4{y.x, y.y, y.z, y.w} * f[w];
+                    }
+                    bf16x4 r;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) r[j] = (__bf16)(x[j] * inv);
+                    *reinterpret_cast<uint2 *>(op + 16 * dt) = __builtin_bit_cast(uint2, r);
+                }
+                if (g == 0 && wave == 0)
+                    lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * kG + n % kG] =
+                        l_tot > 0.f ? (fast_log2(l_tot) + M) * kLn2 : -INFINITY;
+            }
+        }
+        return;
+    }
+    // ---- normalise and write: lane holds channels 16*dt + 4*g .. +3 of column n -----------------
+#pragma unroll
+    for (int u = 0; u < kTiles; ++u) {
+        const int tok = t0 + u * kTPT + tn;
+        if (tok >= L) continue;
         const float l_tot = xgroup_sum(l_run[u]);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        __bf16 *op = out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)(h * G + n) * out.sh + 4 * g;
+        __bf16 *op = out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)(h * kG + n % kG) * out.sh + 4 * g;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) {
             bf16x4 r;
@@ -357,7 +415,7 @@ __global__ __launch_bounds__(256, kWavesPerSimd) void attn_prefill_kernel(Dims d
             *reinterpret_cast<uint2 *>(op + 16 * dt) = __builtin_bit_cast(uint2, r);
         }
         if (g == 0)
-            lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * G + n] =
+            lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * kG + n % kG] =
                 l_tot > 0.f ? (fast_log2(l_tot) - neg_m[u]) * kLn2 : -INFINITY;
     }
 }
@@ -530,13 +588,49 @@ size_t attn_prefill_ws_bytes(const Dims &dm) {
     return (size_t)dm.batch * dm.Hkv * nb_cap * kPackedBlockU4 * sizeof(uint4);
 }
 
-template <int kTok, int kNU, int kWavesPerSimd>
-static void launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
-                                const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
-    const int32_t n_tiles = (dm.max_seqlen + 4 * kTok - 1) / (4 * kTok);
-    const int64_t n_wg = (int64_t)n_tiles * dm.Hkv * dm.batch;
-    hipLaunchKernelGGL((attn_prefill_kernel<kTok, kNU, kWavesPerSimd>), dim3((uint32_t)n_wg), dim3(256), 0, stream,
-                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, n_tiles);
+// Workgroups go to the XCDs round-robin by their id.  A sequence's tiles are dealt to the XCDs in runs of kRun, last
+// tile first, counted from the sequence's own length: every XCD gets the same share of every sequence (a batch of
+// unequal lengths leaves no XCD idle: 12289 + 8693 + 5096 + 1500 tokens 1256 -> 700 us from this alone), neighbours,
+// which share blocks, still meet in one L2, and the long rows start first.
+
+template <int kG, int kTiles, int kSplit>
+static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
+                               const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
+    using C = AttnCfg<kG, kTiles, kSplit>;
+    const int32_t n_tiles = (dm.max_seqlen + C::kTokPerWg - 1) / C::kTokPerWg;
+    const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
+    const int64_t n_wg = (int64_t)slots * 8 * dm.Hkv * dm.batch;
+    const size_t lds = C::lds_bytes(dm.topk);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)attn_prefill_kernel<kG, kTiles, kSplit>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return (int)e;
+    }
+    hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
+                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
+    return 0;
+}
+
+// How many tiles a wavefront takes and whether the waves of a workgroup share their tokens, by how many workgroups the
+// call fills (two fit a compute unit: 512 fill the chip).  More tiles per wavefront mean fewer bytes per token, since
+// a fetched block serves every token that selected it; splitting the blocks over four waves makes four times as many
+// waves out of few tokens.  Measured over 150 .. 32768 tokens, 2 key-value heads, top-k 16 (us, start -> now):
+//   G = 16: 150 17 -> 9, 1500 56 -> 37, 4096 128 -> 100, 32768 1024 -> 777;  G = 4: 777 31 -> 15, 4096 123 -> 57,
+//   32768 1148 -> 755;  G = 1: 777 31 -> 12, 4096 124 -> 38, 32768 1339 -> 534
+// The lines: four tiles, split, from 512 workgroups on (at 390 .. 750 it meets two tiles for every G); two tiles, split,
+// from 192 (at 190 it meets one tile); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
+// only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
+template <int kG>
+static int launch_attn_group(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
+                             const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
+    const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
+    constexpr int kTPT = 16 / kG;
+    if constexpr (kG == 16)
+        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    if constexpr (kG > 1)                                // (member bits of at most 32 tokens)
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
 }
 
 int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int32_t *seqlens,
@@ -556,10 +650,16 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
         timing_end(stream);
         return (int)hipGetLastError();
     }
-    // 2 tokens per wavefront, ring of 4 units, 2 wavefronts per SIMD: the configuration that keeps
-    // the most loads in flight per compute unit within 256 registers per lane
     timing_begin("attn_prefill_kernel", stream);
-    launch_attn_variant<2, 4, 2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    int err = (int)hipErrorInvalidValue;
+    switch (dm.G) {
+        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+    }
+    if (err) return err;
     timing_end(stream);
     return (int)hipGetLastError();
 }

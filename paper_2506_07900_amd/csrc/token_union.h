@@ -1,0 +1,86 @@
+// Union of the block lists of a few consecutive query tokens, built by one wavefront in its own piece of LDS.
+// Shared by the prefill attention and its backward: a wavefront that owns several tokens fetches every block
+// that any of them selected once.
+#pragma once
+#include "common.h"
+
+namespace infllmv2 {
+
+// Inclusive prefix sum over the 64 lanes (row shifts, then the row totals broadcast: no LDS round trips).
+__device__ inline int wave_inclusive_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// LDS of one wavefront: a bitmap of 2048 blocks with the rank of every word, then the list itself.
+struct UnionLds {
+    uint32_t *words, *prefix;                            // [64] each
+    uint2 *list;                                         // [cap]: {block, member bits: bit t = token t selected it}
+    __host__ __device__ static int cap(int n_tok, int topk) { return (n_tok * topk + 63) & ~63; }
+    __host__ __device__ static size_t bytes(int n_tok, int topk) { return 512 + (size_t)cap(n_tok, topk) * sizeof(uint2); }
+    __device__ explicit UnionLds(unsigned char *p)
+        : words(reinterpret_cast<uint32_t *>(p)), prefix(words + 64), list(reinterpret_cast<uint2 *>(p + 512)) {}
+};
+
+// Ascending union of the lists of n_tok <= NT <= 32 consecutive tokens.  rows: their n_tok * topk entries, contiguous;
+// entries < 0 or > b_own are dropped, a block that a row lists twice counts once.  Returns the number of distinct
+// blocks.  An entry's place is the number of set bits before its own in the bitmap, so nothing is sorted and the
+// order of the rows' entries does not matter; sequences of more than 2048 blocks take several rounds.
+template <int NT>
+__device__ inline int build_union(const int32_t *__restrict__ rows, int topk, int n_tok, int b_own, const UnionLds &u,
+                                  int lane) {
+    constexpr int kE = NT >= 4 ? NT / 4 : 1;             // entries per lane kept in registers: top-k 16; more are re-read
+    const int n_ent = n_tok * topk;
+    const uint32_t inv = (1u << 20) / (uint32_t)topk + 1u;   // entry i belongs to token i / topk (exact for i < 2048)
+    int ent[kE];
+#pragma unroll
+    for (int i = 0; i < kE; ++i) {
+        const int at = lane + 64 * i;
+        int x = -1;
+        if (at < n_ent) x = rows[at];
+        ent[i] = x > b_own ? -1 : x;
+    }
+    auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kE; ++i)
+            if (ent[i] >= 0) f(ent[i], (int)(((uint32_t)(lane + 64 * i) * inv) >> 20));
+        for (int at = lane + 64 * kE; at < n_ent; at += 64) {
+            const int x = rows[at];
+            if (x >= 0 && x <= b_own) f(x, (int)(((uint32_t)at * inv) >> 20));
+        }
+    };
+    const int cap = UnionLds::cap(NT, topk);
+    for (int i = lane; i < cap; i += 64) u.list[i] = uint2{0u, 0u};
+    int cnt = 0;
+    for (int base = 0; base <= b_own; base += 2048) {
+        u.words[lane] = 0u;
+        __builtin_amdgcn_wave_barrier();                 // same wavefront throughout: LDS keeps the order
+        each([&](int x, int) {
+            const uint32_t r = (uint32_t)(x - base);
+            if (r < 2048u) atomicOr(&u.words[r >> 5], 1u << (r & 31u));
+        });
+        __builtin_amdgcn_wave_barrier();
+        const int mine = __popc(u.words[lane]);
+        const int incl = wave_inclusive_sum(mine);
+        u.prefix[lane] = (uint32_t)(cnt + incl - mine);
+        __builtin_amdgcn_wave_barrier();
+        each([&](int x, int t) {
+            const uint32_t r = (uint32_t)(x - base);
+            if (r < 2048u) {
+                const uint32_t at = u.prefix[r >> 5] + __popc(u.words[r >> 5] & ((1u << (r & 31u)) - 1u));
+                u.list[at].x = (uint32_t)x;
+                atomicOr(&u.list[at].y, 1u << t);
+            }
+        });
+        cnt += __builtin_amdgcn_readlane(incl, 63);
+        __builtin_amdgcn_wave_barrier();
+    }
+    return cnt;
+}
+
+}  // namespace infllmv2

@@ -317,6 +317,46 @@ def test_sparse_attn_prefill(seqlens, Hq, Hkv, topk, planted):
         assert np.all(o[b, l:] == 3.0) and np.all(ls[b, l:] == 5.0)     # padding rows untouched
 
 
+# One case on each side of every line of the attention's dispatch (tiles per wavefront, split over the waves or not,
+# by tokens x key-value heads), per group size; ragged batches, odd lengths, a sequence shorter than a tile, and more
+# than 2048 blocks (the union's bitmap takes two rounds there).
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [
+    ([383], 16, 1, 16), ([385], 16, 1, 16), ([1023], 32, 2, 5), ([1025, 3], 32, 2, 16), ([8191], 32, 2, 8), ([8193, 700], 32, 2, 24),
+    ([300], 16, 2, 16), ([771, 1], 16, 2, 16), ([2049], 16, 2, 64), ([700, 40], 8, 2, 16), ([1600], 8, 2, 33), ([4101, 65], 8, 2, 16),
+    ([1500], 4, 2, 16), ([1601], 4, 2, 48), ([8201, 15], 4, 2, 16), ([3000], 2, 2, 16), ([3090, 31], 2, 2, 16), ([6500], 1, 1, 64),
+    ([139333], 16, 1, 16), ([132001], 4, 1, 16)])
+def test_sparse_attn_prefill_dispatch(seqlens, Hq, Hkv, topk):
+    print("case attn prefill dispatch", seqlens, Hq, Hkv, topk, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    oprm = oracle_params(prm)
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    B, T = len(seqlens), max(seqlens)
+    q = torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16()
+    k = torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16()
+    v = torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16()
+    # lists in no particular order: neighbours share most of their blocks, a few entries are their own, some are empty
+    own = (torch.arange(T, device="cuda") // 64)[None, None, :, None]
+    i = torch.arange(topk, device="cuda")[None, None, None, :]
+    shift = torch.randint(0, 3, (B, Hkv, T, 1), device="cuda", generator=gen) * 3
+    idx = (own + 1 - 7 * i - torch.where(i % 4 == 3, shift, torch.zeros_like(shift)))
+    idx = torch.where((i % 5 == 4) | (idx < 0), torch.full_like(idx, -1), torch.where(i == 0, own.expand_as(idx), idx))
+    idx = idx.flip(-1).to(torch.int32).contiguous()
+    out, lse = torch.full_like(q, 3.0), torch.full((B, T, Hq), 5.0, dtype=torch.float32, device="cuda")
+    binding.sparse_attn_prefill(prm, q, k, v, dev_i32(seqlens), T, idx, out=out, lse=lse)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(3)
+    for b, l in enumerate(seqlens):
+        pos = np.array(sorted(set(rng.integers(0, l, 60).tolist()) | set(range(max(0, l - 35), l)) | set(range(min(l, 5)))), np.int32)
+        at = torch.from_numpy(pos).long().cuda()
+        want_o, want_l = ref.sparse_attn(to_bits(q[b, at]), to_bits(k[b, :, :l]), to_bits(v[b, :, :l]), pos,
+                                         idx[b, :, at].cpu().numpy(), oprm)
+        eo = np.abs(out[b, at].double().cpu().numpy() - want_o).max()
+        el = lse_err(lse[b, at].double().cpu().numpy(), want_l)
+        print("len %d: max|dO| %.3e LSE err/tol %.3f" % (l, eo, el), flush=True)
+        assert eo <= OUT_TOL and el <= 1.0
+        assert bool((out[b, l:] == 3.0).all()) and bool((lse[b, l:] == 5.0).all())
+
+
 def test_sparse_attn_prefill_row_that_repeats_a_block():
     # the contract asks for duplicate-free rows; a row that repeats a block all the same must stay inside
     # the caches and attend that block once: same output as the clean row, bit for bit
