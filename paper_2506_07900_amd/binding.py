@@ -3,6 +3,8 @@
 Argument marshalling only: every function here has the name of the C entry point it calls
 (minus the `infllmv2_` prefix), turns torch tensors into pointers + element strides, and
 passes the current torch stream.  torch is used for device memory and streams, nothing else.
+The marshalling of the path's own calls is native (csrc/marshal.cpp, `_marshal.so`); the
+comparison variant, the inspection calls and the probes go through ctypes.
 A missing library is an error: there is no fallback path.
 
 Tensor layouts (bf16, CUDA/HIP device, head_dim contiguous):
@@ -12,6 +14,7 @@ Tensor layouts (bf16, CUDA/HIP device, head_dim contiguous):
   block_idx         int32 [B, Hkv, Tq, topk]
 """
 import ctypes
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -19,6 +22,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libinfllmv2.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 BENCH_LIB_PATH = os.path.join(_HERE, "libinfllmv2_bench.so")   # + per-kernel timing and probes (include/infllmv2_bench.h)
 
 OK = 0
@@ -71,6 +75,17 @@ class Params:
         if self.softmax_scale is None:
             self.softmax_scale = float(self.head_dim) ** -0.5
 
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        self.__dict__.pop("_packed", None)
+
+    def packed(self):
+        """The C parameter block as bytes (kept until a field changes)."""
+        p = self.__dict__.get("_packed")
+        if p is None:
+            p = self.__dict__["_packed"] = bytes(self.c())
+        return p
+
     def c(self):
         return CParams(self.head_dim, self.n_q_heads, self.n_kv_heads, self.block_size,
                        self.kernel_size, self.kernel_stride, self.topk, self.n_init_blocks,
@@ -82,11 +97,12 @@ class InfLLMv2Error(RuntimeError):
 
 
 _lib = None
+_marshal = None
 
 
 def load_library(path=None):
     """Load libinfllmv2.so (built by paper_2506_07900_amd.build); raises if it is missing."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None and path is None:
         return _lib
     path = path or os.environ.get("INFLLMV2_LIB") or LIB_PATH     # INFLLMV2_LIB: use another build of the library
@@ -140,8 +156,28 @@ def load_library(path=None):
         lib.infllmv2_timing_enable.argtypes = [i32]
         lib.infllmv2_timing_read.restype = i32
         lib.infllmv2_timing_read.argtypes = [i32, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_float)]
-    _lib = lib
+    marshal = _load_marshal()
+    marshal.bind(os.path.abspath(path), InfLLMv2Error)
+    _lib, _marshal = lib, marshal
     return lib
+
+
+def _load_marshal():
+    """The Python extension next to this file (built with the library)."""
+    if _marshal is not None:
+        return _marshal
+    if not os.path.exists(MARSHAL_PATH):
+        raise InfLLMv2Error("Python extension not built: %s is missing (run python -m paper_2506_07900_amd.build)" % MARSHAL_PATH)
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+def _native():
+    if _marshal is None:
+        load_library()
+    return _marshal
 
 
 def load_bench_library():
@@ -226,28 +262,13 @@ def _workspace(op, prm, batch, max_seqlen, workspace, device):
 
 def compress_keys(prm, k, seqlens, max_seqlen, ck=None, n_new_tokens=0):
     """k [B, Hkv, T, d] -> ck [B, Hkv, n_c(max_seqlen) (or more), d] (allocated if not given)."""
-    lib = load_library()
-    B, Hkv = k.shape[0], k.shape[1]
-    if ck is None:
-        ck = torch.zeros((B, Hkv, max(num_kernels(max_seqlen, prm), 1), k.shape[3]),
-                         dtype=torch.bfloat16, device=k.device)
-    kd, cd = _cache_desc(k, "k"), _cache_desc(ck, "ck")
-    _check(lib.infllmv2_compress_keys(ctypes.byref(prm.c()), ctypes.byref(kd), _i32(seqlens, "seqlens").data_ptr(),
-                                      B, max_seqlen, n_new_tokens, ctypes.byref(cd), _stream()),
-           "infllmv2_compress_keys")
-    return ck
+    return _native().compress_keys(prm.packed(), k, seqlens, max_seqlen, ck, n_new_tokens)
 
 
 def append_kv(prm, k_new, v_new, k, v, seqlens, max_seqlen, ck=None):
     """k_new, v_new [B, Hkv, 1, d] are written at cache position seqlens[b]-1; with ck the
     compressed key that the new token completes (if any) is written in the same launch."""
-    lib = load_library()
-    d = [_cache_desc(k_new, "k_new"), _cache_desc(v_new, "v_new"), _cache_desc(k, "k"), _cache_desc(v, "v")]
-    ckd = ctypes.byref(_cache_desc(ck, "ck")) if ck is not None else None
-    _check(lib.infllmv2_append_kv(ctypes.byref(prm.c()), ctypes.byref(d[0]), ctypes.byref(d[1]),
-                                  ctypes.byref(d[2]), ctypes.byref(d[3]), ckd,
-                                  _i32(seqlens, "seqlens").data_ptr(), k.shape[0], max_seqlen, _stream()),
-           "infllmv2_append_kv")
+    _native().append_kv(prm.packed(), k_new, v_new, k, v, seqlens, max_seqlen, ck)
 
 
 def probe_peaks(buf):
@@ -288,55 +309,17 @@ def probe_detail(buf):
 
 def select_blocks(prm, mode, q, ck, seqlens, max_seqlen, block_idx=None, workspace=None):
     """-> block_idx int32 [B, Hkv, Tq, topk] (Tq = max_seqlen in prefill, 1 in decode)."""
-    lib = load_library()
-    B = q.shape[0]
-    n_q = max_seqlen if mode == MODE_PREFILL else 1
-    if block_idx is None:
-        block_idx = torch.full((B, prm.n_kv_heads, n_q, prm.topk), -1, dtype=torch.int32, device=q.device)
-    op = OP_SELECT_PREFILL if mode == MODE_PREFILL else OP_SELECT_DECODE
-    workspace, ws_bytes = _workspace(op, prm, B, max_seqlen, workspace, q.device)
-    qd, cd = _query_desc(q, "q"), _cache_desc(ck, "ck")
-    _check(lib.infllmv2_select_blocks(ctypes.byref(prm.c()), mode, ctypes.byref(qd), ctypes.byref(cd),
-                                      _i32(seqlens, "seqlens").data_ptr(), B, max_seqlen,
-                                      _i32(block_idx, "block_idx").data_ptr(), workspace.data_ptr(),
-                                      ws_bytes, _stream()), "infllmv2_select_blocks")
-    return block_idx
+    return _native().select_blocks(prm.packed(), mode, q, ck, seqlens, max_seqlen, block_idx, workspace)
 
 
 def sparse_attn_prefill(prm, q, k, v, seqlens, max_seqlen, block_idx, out=None, lse=None, workspace=None):
     """-> out bf16 [B, T, Hq, d], lse fp32 [B, T, Hq]."""
-    lib = load_library()
-    B = q.shape[0]
-    if out is None:
-        out = torch.zeros_like(q)
-    if lse is None:
-        lse = torch.zeros((B, max_seqlen, prm.n_q_heads), dtype=torch.float32, device=q.device)
-    workspace, ws_bytes = _workspace(OP_ATTN_PREFILL, prm, B, max_seqlen, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k, "k"), _cache_desc(v, "v"), _query_desc(out, "out")]
-    _check(lib.infllmv2_sparse_attn_prefill(ctypes.byref(prm.c()), ctypes.byref(d[0]), ctypes.byref(d[1]),
-                                            ctypes.byref(d[2]), _i32(seqlens, "seqlens").data_ptr(), B,
-                                            max_seqlen, _i32(block_idx, "block_idx").data_ptr(),
-                                            ctypes.byref(d[3]), lse.data_ptr(), workspace.data_ptr(),
-                                            ws_bytes, _stream()), "infllmv2_sparse_attn_prefill")
-    return out, lse
+    return _native().sparse_attn_prefill(prm.packed(), q, k, v, seqlens, max_seqlen, block_idx, out, lse, workspace)
 
 
 def sparse_attn_decode(prm, q, k, v, seqlens, max_seqlen, block_idx, out=None, lse=None, workspace=None):
     """q [B, 1, Hq, d] -> out bf16 [B, 1, Hq, d], lse fp32 [B, Hq]."""
-    lib = load_library()
-    B = q.shape[0]
-    if out is None:
-        out = torch.zeros_like(q)
-    if lse is None:
-        lse = torch.zeros((B, prm.n_q_heads), dtype=torch.float32, device=q.device)
-    workspace, ws_bytes = _workspace(OP_ATTN_DECODE, prm, B, max_seqlen, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k, "k"), _cache_desc(v, "v"), _query_desc(out, "out")]
-    _check(lib.infllmv2_sparse_attn_decode(ctypes.byref(prm.c()), ctypes.byref(d[0]), ctypes.byref(d[1]),
-                                           ctypes.byref(d[2]), _i32(seqlens, "seqlens").data_ptr(), B,
-                                           max_seqlen, _i32(block_idx, "block_idx").data_ptr(),
-                                           ctypes.byref(d[3]), lse.data_ptr(), workspace.data_ptr(),
-                                           ws_bytes, _stream()), "infllmv2_sparse_attn_decode")
-    return out, lse
+    return _native().sparse_attn_decode(prm.packed(), q, k, v, seqlens, max_seqlen, block_idx, out, lse, workspace)
 
 
 def sparse_attn_decode_noalloc(prm, q, k, v, seqlens, max_seqlen, block_idx, out, lse):
@@ -358,134 +341,46 @@ def verify_workspace_bytes(op, prm, batch, max_seqlen, n_draft):
     return int(load_library().infllmv2_verify_workspace_bytes(op, ctypes.byref(prm.c()), batch, max_seqlen, n_draft))
 
 
-def _verify_workspace(op, prm, batch, max_seqlen, n_draft, workspace, device):
-    need = verify_workspace_bytes(op, prm, batch, max_seqlen, n_draft)
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-    return workspace, workspace.numel() * workspace.element_size()
-
-
 def append_kv_verify(prm, k_new, v_new, k, v, seqlens, max_seqlen, ck=None):
     """k_new, v_new [B, Hkv, n_draft, d] are written at cache rows seqlens[b]-n_draft .. seqlens[b]-1;
     with ck the compressed keys those rows complete are written too."""
-    lib = load_library()
-    d = [_cache_desc(k_new, "k_new"), _cache_desc(v_new, "v_new"), _cache_desc(k, "k"), _cache_desc(v, "v")]
-    ckd = ctypes.byref(_cache_desc(ck, "ck")) if ck is not None else None
-    _check(lib.infllmv2_append_kv_verify(ctypes.byref(prm.c()), ctypes.byref(d[0]), ctypes.byref(d[1]),
-                                         ctypes.byref(d[2]), ctypes.byref(d[3]), ckd,
-                                         _i32(seqlens, "seqlens").data_ptr(), k.shape[0], max_seqlen,
-                                         k_new.shape[2], _stream()), "infllmv2_append_kv_verify")
+    _native().append_kv_verify(prm.packed(), k_new, v_new, k, v, seqlens, max_seqlen, ck)
 
 
 def select_blocks_verify(prm, q, ck, seqlens, max_seqlen, block_idx=None, workspace=None):
     """q [B, n_draft, Hq, d] -> block_idx int32 [B, Hkv, n_draft, topk]."""
-    lib = load_library()
-    B, n = q.shape[0], q.shape[1]
-    if block_idx is None:
-        block_idx = torch.full((B, prm.n_kv_heads, n, prm.topk), -1, dtype=torch.int32, device=q.device)
-    workspace, ws_bytes = _verify_workspace(OP_SELECT_VERIFY, prm, B, max_seqlen, n, workspace, q.device)
-    qd, cd = _query_desc(q, "q"), _cache_desc(ck, "ck")
-    _check(lib.infllmv2_select_blocks_verify(ctypes.byref(prm.c()), ctypes.byref(qd), ctypes.byref(cd),
-                                             _i32(seqlens, "seqlens").data_ptr(), B, max_seqlen, n,
-                                             _i32(block_idx, "block_idx").data_ptr(), workspace.data_ptr(),
-                                             ws_bytes, _stream()), "infllmv2_select_blocks_verify")
-    return block_idx
+    return _native().select_blocks_verify(prm.packed(), q, ck, seqlens, max_seqlen, block_idx, workspace)
 
 
 def sparse_attn_verify(prm, q, k, v, seqlens, max_seqlen, block_idx, tree_mask=None, out=None, lse=None,
                        workspace=None):
     """q [B, n_draft, Hq, d]; tree_mask int64 device tensor [B, n_draft] holding the uint64 mask words
     (None = causal chain) -> out bf16 [B, n_draft, Hq, d], lse fp32 [B, n_draft, Hq]."""
-    lib = load_library()
-    B, n = q.shape[0], q.shape[1]
-    if out is None:
-        out = torch.zeros_like(q)
-    if lse is None:
-        lse = torch.zeros((B, n, prm.n_q_heads), dtype=torch.float32, device=q.device)
-    mask_ptr = None
-    if tree_mask is not None:
-        if not (tree_mask.is_cuda and tree_mask.dtype == torch.int64 and tree_mask.is_contiguous()
-                and tuple(tree_mask.shape) == (B, n)):
-            raise InfLLMv2Error("tree_mask must be a contiguous int64 device tensor [B, n_draft]")
-        mask_ptr = tree_mask.data_ptr()
-    workspace, ws_bytes = _verify_workspace(OP_ATTN_VERIFY, prm, B, max_seqlen, n, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k, "k"), _cache_desc(v, "v"), _query_desc(out, "out")]
-    _check(lib.infllmv2_sparse_attn_verify(ctypes.byref(prm.c()), ctypes.byref(d[0]), ctypes.byref(d[1]),
-                                           ctypes.byref(d[2]), _i32(seqlens, "seqlens").data_ptr(), B,
-                                           max_seqlen, n, mask_ptr, _i32(block_idx, "block_idx").data_ptr(),
-                                           ctypes.byref(d[3]), lse.data_ptr(), workspace.data_ptr(),
-                                           ws_bytes, _stream()), "infllmv2_sparse_attn_verify")
-    return out, lse
+    return _native().sparse_attn_verify(prm.packed(), q, k, v, seqlens, max_seqlen, block_idx, tree_mask, out, lse,
+                                        workspace)
 
 
 def verify_step(prm, q, k_new, v_new, k, v, ck, seqlens, max_seqlen, tree_mask=None, block_idx=None, out=None,
                 lse=None, workspace=None):
     """One verification step in one call: append_kv_verify (with ck) + select_blocks_verify + sparse_attn_verify.
     q [B, n_draft, Hq, d]; k_new, v_new [B, Hkv, n_draft, d] -> block_idx [B, Hkv, n_draft, topk], out, lse."""
-    lib = load_library()
-    B, n = q.shape[0], q.shape[1]
-    if block_idx is None:
-        block_idx = torch.full((B, prm.n_kv_heads, n, prm.topk), -1, dtype=torch.int32, device=q.device)
-    if out is None:
-        out = torch.zeros_like(q)
-    if lse is None:
-        lse = torch.zeros((B, n, prm.n_q_heads), dtype=torch.float32, device=q.device)
-    mask_ptr = None
-    if tree_mask is not None:
-        if not (tree_mask.is_cuda and tree_mask.dtype == torch.int64 and tree_mask.is_contiguous()
-                and tuple(tree_mask.shape) == (B, n)):
-            raise InfLLMv2Error("tree_mask must be a contiguous int64 device tensor [B, n_draft]")
-        mask_ptr = tree_mask.data_ptr()
-    workspace, ws_bytes = _verify_workspace(OP_VERIFY_STEP, prm, B, max_seqlen, n, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k_new, "k_new"), _cache_desc(v_new, "v_new"), _cache_desc(k, "k"),
-         _cache_desc(v, "v"), _cache_desc(ck, "ck"), _query_desc(out, "out")]
-    _check(lib.infllmv2_verify_step(ctypes.byref(prm.c()), *[ctypes.byref(x) for x in d[:6]],
-                                    _i32(seqlens, "seqlens").data_ptr(), B, max_seqlen, n, mask_ptr,
-                                    _i32(block_idx, "block_idx").data_ptr(), ctypes.byref(d[6]), lse.data_ptr(),
-                                    workspace.data_ptr(), ws_bytes, _stream()), "infllmv2_verify_step")
-    return block_idx, out, lse
+    return _native().verify_step(prm.packed(), q, k_new, v_new, k, v, ck, seqlens, max_seqlen, tree_mask, block_idx, out,
+                                 lse, workspace)
 
 
 def sparse_attn_bwd(prm, q, k, v, out, dout, lse, seqlens, max_seqlen, block_idx, dq=None, dk=None, dv=None,
                     workspace=None):
     """Backward of sparse_attn_prefill with the block sets fixed -> dq [B, T, Hq, d], dk, dv [B, Hkv, T, d] (bf16)."""
-    lib = load_library()
-    B = q.shape[0]
-    dq = torch.zeros_like(q) if dq is None else dq
-    dk = torch.zeros_like(k) if dk is None else dk
-    dv = torch.zeros_like(v) if dv is None else dv
-    workspace, ws_bytes = _workspace(OP_ATTN_BWD, prm, B, max_seqlen, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k, "k"), _cache_desc(v, "v"), _query_desc(out, "out"),
-         _query_desc(dout, "dout"), _query_desc(dq, "dq"), _cache_desc(dk, "dk"), _cache_desc(dv, "dv")]
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous()):
-        raise InfLLMv2Error("lse must be a contiguous fp32 device tensor")
-    _check(lib.infllmv2_sparse_attn_bwd(ctypes.byref(prm.c()), *[ctypes.byref(x) for x in d[:5]], lse.data_ptr(),
-                                        _i32(seqlens, "seqlens").data_ptr(), B, max_seqlen,
-                                        _i32(block_idx, "block_idx").data_ptr(), *[ctypes.byref(x) for x in d[5:]],
-                                        workspace.data_ptr(), ws_bytes, _stream()), "infllmv2_sparse_attn_bwd")
-    return dq, dk, dv
+    return _native().sparse_attn_bwd(prm.packed(), q, k, v, out, dout, lse, seqlens, max_seqlen, block_idx, dq, dk, dv,
+                                     workspace)
 
 
 def decode_step(prm, q, k_new, v_new, k, v, ck, seqlens, max_seqlen, block_idx=None, out=None, lse=None,
                 workspace=None):
-    """append_kv (with ck) + select_blocks(MODE_DECODE) + sparse_attn_decode in one call, five launches.
+    """append_kv (with ck) + select_blocks(MODE_DECODE) + sparse_attn_decode in one call.
     -> block_idx [B, Hkv, 1, topk], out [B, 1, Hq, d], lse [B, Hq]."""
-    lib = load_library()
-    B = q.shape[0]
-    if block_idx is None:
-        block_idx = torch.full((B, prm.n_kv_heads, 1, prm.topk), -1, dtype=torch.int32, device=q.device)
-    if out is None:
-        out = torch.zeros_like(q)
-    if lse is None:
-        lse = torch.zeros((B, prm.n_q_heads), dtype=torch.float32, device=q.device)
-    workspace, ws_bytes = _workspace(OP_DECODE_STEP, prm, B, max_seqlen, workspace, q.device)
-    d = [_query_desc(q, "q"), _cache_desc(k_new, "k_new"), _cache_desc(v_new, "v_new"), _cache_desc(k, "k"),
-         _cache_desc(v, "v"), _cache_desc(ck, "ck"), _query_desc(out, "out")]
-    _check(lib.infllmv2_decode_step(ctypes.byref(prm.c()), *[ctypes.byref(x) for x in d[:6]],
-                                    _i32(seqlens, "seqlens").data_ptr(), B, max_seqlen,
-                                    _i32(block_idx, "block_idx").data_ptr(), ctypes.byref(d[6]), lse.data_ptr(),
-                                    workspace.data_ptr(), ws_bytes, _stream()), "infllmv2_decode_step")
-    return block_idx, out, lse
+    return _native().decode_step(prm.packed(), q, k_new, v_new, k, v, ck, seqlens, max_seqlen, block_idx, out, lse,
+                                 workspace)
 
 
 def select_blocks_shared(prm, q, ck, seqlens, max_seqlen, block_idx=None, workspace=None):

@@ -1,6 +1,7 @@
 // C ABI of the library: argument validation (host only, before any HIP call) and dispatch to
 // the kernel launchers.  See include/infllmv2.h for the contract of every entry point.
 #include "common.h"
+#include "internal.h"
 
 using namespace infllmv2;
 
@@ -56,7 +57,7 @@ int32_t check_tensor(const infllmv2_tensor *t) {
     return INFLLMV2_OK;
 }
 
-Dims make_dims(const infllmv2_params *p, int32_t batch, int32_t max_seqlen, int32_t n_q = 1) {
+Dims make_dims(const infllmv2_params *p, int32_t batch, int32_t max_seqlen, int32_t n_q = 1, int32_t fill = 0) {
     Dims d;
     d.Hq = p->n_q_heads;
     d.Hkv = p->n_kv_heads;
@@ -70,6 +71,7 @@ Dims make_dims(const infllmv2_params *p, int32_t batch, int32_t max_seqlen, int3
     d.rho = p->lse_coarse_ratio > 1 ? p->lse_coarse_ratio : 1;
     d.n_q = n_q;
     d.shared_q = 0;
+    d.fill = fill;
     return d;
 }
 
@@ -164,17 +166,23 @@ size_t infllmv2_verify_workspace_bytes(int32_t op, const infllmv2_params *prm, i
     return 0;
 }
 
-int32_t infllmv2_compress_keys(const infllmv2_params *prm, const infllmv2_tensor *k,
-                               const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
-                               int32_t n_new_tokens, const infllmv2_tensor *ck, void *stream) {
+int32_t infllmv2i_compress_keys(const infllmv2_params *prm, const infllmv2_tensor *k,
+                                const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
+                                int32_t n_new_tokens, const infllmv2_tensor *ck, void *stream, int32_t fill) {
     RETURN_IF_ERR(check_params(prm));
     RETURN_IF_ERR(check_sizes(batch, max_seqlen));
     RETURN_IF_ERR(check_tensor(k));
     RETURN_IF_ERR(check_tensor(ck));
     if (!seqlens) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    const Dims dm = make_dims(prm, batch, max_seqlen);
+    const Dims dm = make_dims(prm, batch, max_seqlen, 1, fill);
     return hip_status(launch_compress_keys(dm, make_tensor(k), make_tensor(ck), seqlens, n_new_tokens,
                                            reinterpret_cast<hipStream_t>(stream)));
+}
+
+int32_t infllmv2_compress_keys(const infllmv2_params *prm, const infllmv2_tensor *k,
+                               const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
+                               int32_t n_new_tokens, const infllmv2_tensor *ck, void *stream) {
+    return infllmv2i_compress_keys(prm, k, seqlens, batch, max_seqlen, n_new_tokens, ck, stream, 0);
 }
 
 int32_t infllmv2_append_kv(const infllmv2_params *prm, const infllmv2_tensor *k_new,
@@ -311,10 +319,10 @@ int32_t infllmv2_decode_step(const infllmv2_params *prm, const infllmv2_tensor *
                                          lse, workspace, reinterpret_cast<char *>(workspace) + sel, st));
 }
 
-int32_t infllmv2_select_blocks(const infllmv2_params *prm, int32_t mode, const infllmv2_tensor *q,
+int32_t infllmv2i_select_blocks(const infllmv2_params *prm, int32_t mode, const infllmv2_tensor *q,
                                const infllmv2_tensor *ck, const int32_t *seqlens, int32_t batch,
                                int32_t max_seqlen, int32_t *block_idx, void *workspace,
-                               size_t workspace_bytes, void *stream) {
+                               size_t workspace_bytes, void *stream, int32_t fill) {
     RETURN_IF_ERR(check_params(prm));
     RETURN_IF_ERR(check_sizes(batch, max_seqlen));
     if (mode != INFLLMV2_MODE_PREFILL && mode != INFLLMV2_MODE_DECODE) return INFLLMV2_ERR_INVALID_ARGUMENT;
@@ -322,7 +330,7 @@ int32_t infllmv2_select_blocks(const infllmv2_params *prm, int32_t mode, const i
     RETURN_IF_ERR(check_tensor(ck));
     if (!seqlens || !block_idx) return INFLLMV2_ERR_INVALID_ARGUMENT;
     if (mode == INFLLMV2_MODE_DECODE && max_seqlen > kMaxDecodeSeqlen) return INFLLMV2_ERR_UNSUPPORTED;
-    const Dims dm = make_dims(prm, batch, max_seqlen);
+    const Dims dm = make_dims(prm, batch, max_seqlen, 1, fill);
     const size_t need = mode == INFLLMV2_MODE_PREFILL ? select_prefill_ws_bytes(dm) : select_decode_ws_bytes(dm);
     if (need > 0 && (!workspace || workspace_bytes < need ||
                      (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0))
@@ -333,6 +341,13 @@ int32_t infllmv2_select_blocks(const infllmv2_params *prm, int32_t mode, const i
                                                 workspace, st));
     return hip_status(launch_select_decode(dm, make_tensor(q), make_tensor(ck), seqlens, block_idx,
                                            workspace, st));
+}
+
+int32_t infllmv2_select_blocks(const infllmv2_params *prm, int32_t mode, const infllmv2_tensor *q,
+                               const infllmv2_tensor *ck, const int32_t *seqlens, int32_t batch,
+                               int32_t max_seqlen, int32_t *block_idx, void *workspace,
+                               size_t workspace_bytes, void *stream) {
+    return infllmv2i_select_blocks(prm, mode, q, ck, seqlens, batch, max_seqlen, block_idx, workspace, workspace_bytes, stream, 0);
 }
 
 int32_t infllmv2_block_scores(const infllmv2_params *prm, const infllmv2_tensor *q, const infllmv2_tensor *ck,
@@ -372,11 +387,11 @@ int32_t infllmv2_select_blocks_shared(const infllmv2_params *prm, const infllmv2
                                             reinterpret_cast<hipStream_t>(stream)));
 }
 
-int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_tensor *q,
+int32_t infllmv2i_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_tensor *q,
                                      const infllmv2_tensor *k, const infllmv2_tensor *v,
                                      const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
                                      const int32_t *block_idx, const infllmv2_tensor *out, float *lse,
-                                     void *workspace, size_t workspace_bytes, void *stream) {
+                                     void *workspace, size_t workspace_bytes, void *stream, int32_t fill) {
     RETURN_IF_ERR(check_params(prm));
     RETURN_IF_ERR(check_sizes(batch, max_seqlen));
     RETURN_IF_ERR(check_tensor(q));
@@ -384,7 +399,7 @@ int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_
     RETURN_IF_ERR(check_tensor(v));
     RETURN_IF_ERR(check_tensor(out));
     if (!seqlens || !block_idx || !lse) return INFLLMV2_ERR_INVALID_ARGUMENT;
-    const Dims dm = make_dims(prm, batch, max_seqlen);
+    const Dims dm = make_dims(prm, batch, max_seqlen, 1, fill);
     const size_t need = attn_prefill_ws_bytes(dm);
     if (need > 0 && (!workspace || workspace_bytes < need ||
                      (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0))
@@ -392,6 +407,15 @@ int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_
     return hip_status(launch_attn_prefill(dm, make_tensor(q), make_tensor(k), make_tensor(v), seqlens,
                                           block_idx, make_tensor(out), lse, workspace,
                                           reinterpret_cast<hipStream_t>(stream)));
+}
+
+int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_tensor *q,
+                                     const infllmv2_tensor *k, const infllmv2_tensor *v,
+                                     const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
+                                     const int32_t *block_idx, const infllmv2_tensor *out, float *lse,
+                                     void *workspace, size_t workspace_bytes, void *stream) {
+    return infllmv2i_sparse_attn_prefill(prm, q, k, v, seqlens, batch, max_seqlen, block_idx, out, lse, workspace,
+                                         workspace_bytes, stream, 0);
 }
 
 int32_t infllmv2_sparse_attn_prefill_shared(const infllmv2_params *prm, const infllmv2_tensor *q,
@@ -417,13 +441,13 @@ int32_t infllmv2_sparse_attn_prefill_shared(const infllmv2_params *prm, const in
                                           reinterpret_cast<hipStream_t>(stream)));
 }
 
-int32_t infllmv2_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tensor *q,
+int32_t infllmv2i_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tensor *q,
                                  const infllmv2_tensor *k, const infllmv2_tensor *v,
                                  const infllmv2_tensor *out, const infllmv2_tensor *dout, const float *lse,
                                  const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
                                  const int32_t *block_idx, const infllmv2_tensor *dq,
                                  const infllmv2_tensor *dk, const infllmv2_tensor *dv, void *workspace,
-                                 size_t workspace_bytes, void *stream) {
+                                 size_t workspace_bytes, void *stream, int32_t fill) {
     RETURN_IF_ERR(check_params(prm));
     RETURN_IF_ERR(check_sizes(batch, max_seqlen));
     const infllmv2_tensor *ts[8] = {q, k, v, out, dout, dq, dk, dv};
@@ -432,7 +456,7 @@ int32_t infllmv2_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tens
     // the dk/dv kernel addresses the heads of a group with 32-bit element offsets from the group's first head
     const int64_t head_span = (int64_t)(prm->n_q_heads / prm->n_kv_heads) * (q->stride_h > dout->stride_h ? q->stride_h : dout->stride_h);
     if (head_span > (int64_t)1 << 30) return INFLLMV2_ERR_UNSUPPORTED;
-    const Dims dm = make_dims(prm, batch, max_seqlen);
+    const Dims dm = make_dims(prm, batch, max_seqlen, 1, fill);
     const size_t need = attn_bwd_ws_bytes(dm);
     if (need > 0 && (!workspace || workspace_bytes < need ||
                      (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0))
@@ -440,6 +464,17 @@ int32_t infllmv2_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tens
     return hip_status(launch_attn_bwd(dm, make_tensor(q), make_tensor(k), make_tensor(v), make_tensor(out),
                                       make_tensor(dout), lse, seqlens, block_idx, make_tensor(dq), make_tensor(dk),
                                       make_tensor(dv), workspace, reinterpret_cast<hipStream_t>(stream)));
+}
+
+int32_t infllmv2_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tensor *q,
+                                 const infllmv2_tensor *k, const infllmv2_tensor *v,
+                                 const infllmv2_tensor *out, const infllmv2_tensor *dout, const float *lse,
+                                 const int32_t *seqlens, int32_t batch, int32_t max_seqlen,
+                                 const int32_t *block_idx, const infllmv2_tensor *dq,
+                                 const infllmv2_tensor *dk, const infllmv2_tensor *dv, void *workspace,
+                                 size_t workspace_bytes, void *stream) {
+    return infllmv2i_sparse_attn_bwd(prm, q, k, v, out, dout, lse, seqlens, batch, max_seqlen, block_idx, dq, dk, dv,
+                                     workspace, workspace_bytes, stream, 0);
 }
 
 int32_t infllmv2_sparse_attn_decode(const infllmv2_params *prm, const infllmv2_tensor *q,

@@ -79,13 +79,19 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(Dims dm, Tensor out, Tens
                                                         const int32_t *__restrict__ block_idx,
                                                         const float *__restrict__ lse, float *__restrict__ delta,
                                                         float *__restrict__ rowc, uint32_t *__restrict__ bitmap,
-                                                        int32_t nb_cap, int32_t words) {
+                                                        int32_t nb_cap, int32_t words, Tensor dq) {
     const int h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tok = blockIdx.x * 4 + wave;
     const int L = seq_len(dm, seqlens, b);
-    if (tok >= L) return;
     const int G = dm.G;
+    if (tok >= L) {
+        if (dm.fill && tok < dm.max_seqlen)
+            for (int i = lane; i < G * 16; i += 64)
+                *reinterpret_cast<uint4 *>(dq.ptr + b * dq.sb + (int64_t)tok * dq.st + (int64_t)(h * G + (i >> 4)) * dq.sh +
+                                           8 * (i & 15)) = uint4{0u, 0u, 0u, 0u};
+        return;
+    }
     const int row = lane >> 2, quarter = lane & 3;        // head of the group, 32 channels
     const int64_t ooff = b * out.sb + (int64_t)tok * out.st + (int64_t)(h * G + min(row, G - 1)) * out.sh + 32 * quarter;
     const int64_t goff = b * dout.sb + (int64_t)tok * dout.st + (int64_t)(h * G + min(row, G - 1)) * dout.sh + 32 * quarter;
@@ -644,7 +650,13 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Dims dm, const int32_t 
     const int b = blockIdx.z, h = blockIdx.y;
     const int L = seq_len(dm, seqlens, b);
     const int t = blockIdx.x * 16 + (threadIdx.x >> 4), c8 = (threadIdx.x & 15) * 8;
-    if (t >= L) return;
+    if (t >= L) {
+        if (dm.fill && t < dm.max_seqlen) {
+            *reinterpret_cast<uint4 *>(dk.ptr + b * dk.sb + h * dk.sh + (int64_t)t * dk.st + c8) = uint4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<uint4 *>(dv.ptr + b * dv.sb + h * dv.sh + (int64_t)t * dv.st + c8) = uint4{0u, 0u, 0u, 0u};
+        }
+        return;
+    }
     const float scale = dm.scale_log2 * kLn2;
     const int64_t src = (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t) * kHeadDim + c8;
     const float4 k0 = *reinterpret_cast<const float4 *>(acc_dk + src), k1 = *reinterpret_cast<const float4 *>(acc_dk + src + 4);
@@ -679,7 +691,7 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     timing_end(stream);
     timing_begin("bwd_prep_kernel", stream);
     hipLaunchKernelGGL(bwd_prep_kernel, dim3((T + 3) / 4, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, out, dout,
-                       seqlens, block_idx, lse, delta, rowc, bitmap, l.nb_cap, l.words);
+                       seqlens, block_idx, lse, delta, rowc, bitmap, l.nb_cap, l.words, dq);
     timing_end(stream);
     timing_begin("pack_bwd_kernel", stream);
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,

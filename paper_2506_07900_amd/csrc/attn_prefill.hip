@@ -41,14 +41,22 @@ __device__ inline uint32_t xcd_contiguous_id(uint32_t bid, uint32_t n) {
 // V fragment (dt, kk), lane (g, m), element e:  V[64j + 32kk + (e<4 ? 4g+e : 16+4g+e-4)][16dt + m]
 __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor v,
                                                        const int32_t *__restrict__ seqlens,
-                                                       uint4 *__restrict__ kvp, int32_t nb_cap) {
+                                                       uint4 *__restrict__ kvp, int32_t nb_cap, Tensor out,
+                                                       float *__restrict__ lse) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     int32_t L = seqlens[b];
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    if (j * kBlock >= L) return;
     const int tid = threadIdx.x;
+    if (dm.fill)                                         // this head's rows of the block's tokens past the end: out = 0, lse = 0
+        for (int t = max(j * kBlock, (int)L) + (tid >> 4); t < min((j + 1) * kBlock, dm.max_seqlen); t += 16)
+            for (int hq = h * dm.G; hq < (h + 1) * dm.G; ++hq) {
+                *reinterpret_cast<uint4 *>(out.ptr + b * out.sb + (int64_t)t * out.st + (int64_t)hq * out.sh + 8 * (tid & 15)) =
+                    uint4{0u, 0u, 0u, 0u};
+                if ((tid & 15) == 0) lse[((int64_t)b * dm.max_seqlen + t) * dm.Hq + hq] = 0.f;
+            }
+    if (j * kBlock >= L) return;
     const int sc = tid & 15, sr = tid >> 4;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
     const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
@@ -640,7 +648,7 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
     uint4 *kvp = reinterpret_cast<uint4 *>(ws);
     timing_begin("pack_kv_kernel", stream);
     hipLaunchKernelGGL(pack_kv_kernel, dim3(nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v,
-                       seqlens, kvp, nb_cap);
+                       seqlens, kvp, nb_cap, out, lse);
     timing_end(stream);
     if (dm.shared_q) {                                   // one block list per query block (comparison variant)
         const int32_t n_tiles = (dm.max_seqlen + 7) / 8;

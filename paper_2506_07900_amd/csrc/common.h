@@ -31,6 +31,7 @@ struct Dims {
     int32_t rho;        // coarse / fine kernel stride of the approximate log-sum-exp; 1 = exact
     int32_t n_q;        // decode-side kernels: query tokens per sequence (1 = plain decode, n = draft verification)
     int32_t shared_q;   // prefill selection: 1 = one block set per 64-token query block (comparison variant)
+    int32_t fill;       // 1 = also clear the rows of sequences shorter than max_seqlen (see internal.h)
 };
 
 struct Tensor {          // strides in elements
@@ -207,6 +208,14 @@ __device__ inline void write_block_row(int picked, int n_pick, int n_sel, int n_
     for (int e = 0; e < n_sel; ++e) rank += __builtin_amdgcn_readlane(mine, e) < mine ? 1 : 0;
     if (lane < n_sel) o[rank] = mine;
     else if (lane < topk) o[lane] = -1;
+}
+
+// Rows max(t0, L) .. t0 + n_tok - 1 of a block-list tensor (below max_seqlen) set to -1 by one wavefront.
+__device__ inline void fill_block_rows(const Dims &dm, int b, int h, int t0, int n_tok, int L, int32_t *__restrict__ block_idx,
+                                       int lane) {
+    const int t1 = min(t0 + n_tok, dm.max_seqlen);
+    for (int t = max(t0, L); t < t1; ++t)
+        if (lane < dm.topk) block_idx[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t) * dm.topk + lane] = -1;
 }
 
 // Per-kernel timing of the bench-only build (INFLLMV2_TIMING, see timing.hip): every launch is bracketed

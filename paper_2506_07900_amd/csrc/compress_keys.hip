@@ -20,7 +20,12 @@ __global__ __launch_bounds__(256) void compress_keys_kernel(Dims dm, Tensor k, T
     const int c = (threadIdx.x & 15) * 8;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh + c;
     __bf16 *ob = ck.ptr + b * ck.sb + h * ck.sh + c;
-    for (int32_t jh = first + blockIdx.x * 16 + (threadIdx.x >> 4); jh < n_c; jh += gridDim.x * 16) {
+    const int32_t n_rows = dm.fill ? num_kernels(dm.max_seqlen) : n_c;
+    for (int32_t jh = first + blockIdx.x * 16 + (threadIdx.x >> 4); jh < n_rows; jh += gridDim.x * 16) {
+        if (jh >= n_c) {
+            *reinterpret_cast<uint4 *>(ob + (int64_t)jh * ck.st) = uint4{0u, 0u, 0u, 0u};
+            continue;
+        }
         double acc[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.0;

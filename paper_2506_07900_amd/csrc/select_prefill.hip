@@ -186,6 +186,8 @@ __global__ __launch_bounds__(256) void select_score_kernel(Dims dm, Tensor q, Te
     int32_t L = seqlens[b];
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
     const int t0 = tile * C::kTokPerWg;
+    if (kFused && dm.fill)
+        fill_block_rows(dm, b, h, t0 + (threadIdx.x >> 6) * C::kTokPerWave, C::kTokPerWave, L, block_idx, threadIdx.x & 63);
     if (t0 >= L) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;

@@ -293,6 +293,7 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = tile * kTokPerWg16 + wave * kMT;
+    if (kFused && dm.fill) fill_block_rows(dm, b, h, t0, kMT, L, block_idx, lane);
     if (t0 >= L) return;
     const int n = lane & 15, g = lane >> 4;
     const float c = dm.scale_log2;

@@ -357,6 +357,48 @@ def test_sparse_attn_prefill_dispatch(seqlens, Hq, Hkv, topk):
         assert bool((out[b, l:] == 3.0).all()) and bool((lse[b, l:] == 5.0).all())
 
 
+@pytest.mark.parametrize("seqlens,T,Hq,Hkv", [([130, 0, 31, 77], 130, 32, 2), ([65, 200], 257, 4, 1), ([20, 3], 31, 8, 2)])
+def test_results_made_by_the_call_are_clear_past_the_end(seqlens, T, Hq, Hkv):
+    # tensors the binding allocates: rows of shorter sequences read 0 (block lists -1), whatever the memory held before
+    print("case padding", seqlens, T, Hq, Hkv, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=8)
+    B = len(seqlens)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q = torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16()
+    k, v = (torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    dout = torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16()
+    sl = dev_i32(seqlens)
+
+    def poison():                                        # the allocator hands these bytes out again
+        junk = [torch.full((n,), 0x41, dtype=torch.uint8, device="cuda") for n in (1 << 14, 1 << 17, 1 << 20, 1 << 22, 1 << 24) for _ in range(4)]
+        torch.cuda.synchronize()
+        del junk
+
+    poison()
+    ck = binding.compress_keys(prm, k, sl, T)
+    poison()
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)
+    poison()
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    poison()
+    dq, dk, dv = binding.sparse_attn_bwd(prm, q, k, v, out, dout, lse, sl, T, idx)
+    torch.cuda.synchronize()
+    assert ck.shape == (B, Hkv, max(1, binding.num_kernels(T, prm)), 128) and idx.shape == (B, Hkv, T, 8)
+    for b, l in enumerate(seqlens):
+        assert bool((ck[b, :, binding.num_kernels(l, prm):] == 0).all())
+        assert bool((idx[b, :, l:] == -1).all()) and bool((idx[b, :, :l, 0] >= 0).all())
+        for t in (out[b, l:], lse[b, l:], dq[b, l:], dk[b, :, l:], dv[b, :, l:]):
+            assert bool((t == 0).all())
+    # and the same values as in the caller's own buffers
+    out2, lse2 = torch.zeros_like(q), torch.zeros_like(lse)
+    binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx, out=out2, lse=lse2)
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16)) and torch.equal(lse, lse2)
+    with pytest.raises(binding.InfLLMv2Error, match="bf16"):
+        binding.compress_keys(prm, k.float(), sl, T)
+    with pytest.raises(binding.InfLLMv2Error, match="workspace"):
+        binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx, workspace=torch.empty(8, dtype=torch.uint8, device="cuda"))
+
+
 def test_sparse_attn_prefill_row_that_repeats_a_block():
     # the contract asks for duplicate-free rows; a row that repeats a block all the same must stay inside
     # the caches and attend that block once: same output as the clean row, bit for bit
