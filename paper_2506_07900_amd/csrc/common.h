@@ -95,16 +95,34 @@ __device__ inline bf16x8 zero8() {
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ inline float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
-// Reduce over the four 16-lane groups of a wavefront (lanes l, l^16, l^32, l^48).
+// Reduce over the four 16-lane groups of a wavefront (lanes l, l^16, l^32, l^48): two lane swaps, each of which puts
+// the two halves to be combined side by side in every lane (a shuffle would be an LDS round trip of 60 to 70 ns).
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+template <typename F>
+__device__ inline float xgroup_reduce(float v, F f) {
+    const u32x2_t a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const u32x2_t b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 __device__ inline float xgroup_max(float v) {
-    v = fmaxf(v, __shfl_xor(v, 16));
-    v = fmaxf(v, __shfl_xor(v, 32));
-    return v;
+    return xgroup_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ inline float xgroup_sum(float v) {
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    return xgroup_reduce(v, [](float a, float b) { return a + b; });
+}
+
+// Reduce over the 16 lanes of a group (a DPP row): four rotations, every lane ends with the result.
+template <int kCtrl>
+__device__ inline float dpp_rotate(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
+}
+template <typename F>
+__device__ inline float row_reduce(float v, F f) {
+    v = f(v, dpp_rotate<0x128>(v));
+    v = f(v, dpp_rotate<0x124>(v));
+    v = f(v, dpp_rotate<0x122>(v));
+    return f(v, dpp_rotate<0x121>(v));
 }
 
 // Top-k by counting (used by the pick kernels).  An element is the 64-bit word

@@ -75,6 +75,19 @@ __device__ inline void load_query_operands(const Dims &dm, const Tensor &q, int 
     }
 }
 
+// Candidates and counts of a query at cache row L - 1 (L >= 1).
+struct RowRange {
+    int n_sel, n_init, lo_local, jc_max, n_pick;
+    __device__ RowRange(const Dims &dm, int L) {
+        const int b_own = (L - 1) / kBlock, n_blk = b_own + 1;
+        n_sel = dm.topk < n_blk ? dm.topk : n_blk;
+        n_init = dm.n_init < n_blk ? dm.n_init : n_blk;                       // forced leading blocks
+        lo_local = max(n_init, b_own - dm.n_local + 1);                       // forced trailing: lo_local..b_own
+        jc_max = lo_local - 1;                                                // candidates: n_init..jc_max
+        n_pick = n_sel - (n_init + (b_own - lo_local + 1));                   // at most topk - n_init - n_local
+    }
+};
+
 // ---- selection, parts 1 and 2 -------------------------------------------------------------------
 // Both parts score semantic kernels against kQT consecutive query tokens of one sequence on the
 // matrix cores.  kQT = 1 is plain decode; verification uses kQT = kVerifyQT.  A workgroup of part 1
@@ -475,28 +488,34 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
 // ---- part 2, plain decode: block scores from the logits part 1 kept ---------------------------------
 // (One query per sequence: its logits are a quarter of the bytes of the compressed keys, so reading
 // them back is cheaper than computing them again; with several queries per sequence the balance tips.)
-// grid (nb_cap/64, Hkv, B), 320 threads.  Thread t <= 256 scores kernel 256*bx - 1 + t
-// (one halo kernel to the left); threads 0..63 then pool blocks 64*bx + t.
+// grid (n_lists, Hkv, B), 576 threads.  Thread t <= 512 scores kernel 512*bx - 1 + t (one halo kernel to the left);
+// waves 0 and 1 then pool blocks 128*bx + t and leave the list_len best of the 128 as a descending list of pick words:
+// the top-k that follows merges nb/128 short lists, at most one word per thread up to 150K tokens, instead of ranking a
+// row of nb scores -- which each of its topk workgroups per row would do again.
 constexpr int kMaxParts = 128;                        // partials per head (of >= 128 kernels): contexts up to 262144 tokens
-__global__ __launch_bounds__(320) void decode_scores_z_kernel(Dims dm, const int32_t *__restrict__ seqlens,
+constexpr int kListBlocks = 128;                      // blocks per list
+__global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int32_t *__restrict__ seqlens,
                                                              const float *__restrict__ zbuf,
                                                              const float2 *__restrict__ part,
                                                              int32_t n_c_cap, int32_t n_part, int32_t part_kernels,
-                                                             float *__restrict__ R, int32_t nb_cap) {
+                                                             uint64_t *__restrict__ lists, int32_t list_len) {
     __shared__ float lse_h[16];
-    __shared__ float rs[260];
+    __shared__ float rs[4 * kListBlocks + 4];
+    __shared__ __align__(16) uint64_t words[2][64], best[2][64];
     const int h = blockIdx.y, bv = blockIdx.z;
     const int tid = threadIdx.x;
     const int G = dm.G;
-    const int base = blockIdx.x * 256;
+    const int base = blockIdx.x * 4 * kListBlocks;
     // Everything this thread reads lies in the workspace at places that do not depend on the sequence
     // length, so the loads go out before the length is known (one memory round trip less on the
     // critical path of the step); what turns out to be past the end is masked afterwards.
     const int head = min(tid >> 4, G - 1), sub = tid & 15;
     float2 v[kMaxParts / 16];
+    if (tid < 256) {
 #pragma unroll
-    for (int i = 0; i < kMaxParts / 16; ++i)
-        v[i] = part[(((int64_t)bv * dm.Hkv + h) * G + head) * n_part + min(sub + 16 * i, n_part - 1)];
+        for (int i = 0; i < kMaxParts / 16; ++i)
+            v[i] = part[(((int64_t)bv * dm.Hkv + h) * G + head) * n_part + min(sub + 16 * i, n_part - 1)];
+    }
     const int jh = base - 1 + tid;
     const int jh_c = min(max(jh, 0), n_c_cap - 1);
     float zz[16];
@@ -505,7 +524,7 @@ __global__ __launch_bounds__(320) void decode_scores_z_kernel(Dims dm, const int
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     const int n_vis = num_kernels(L);
-    if (L < 1 || (int)blockIdx.x * 64 > (L - 1) / kBlock) return;            // no block of this chunk exists
+    if (L < 1 || (int)blockIdx.x * kListBlocks > (L - 1) / kBlock) return;   // no block of this chunk exists
     const int np = (n_vis + part_kernels - 1) / part_kernels;   // valid partials
     // log-sum-exp per head: 16 lanes per head
     if (tid < 256) {
@@ -515,22 +534,20 @@ __global__ __launch_bounds__(320) void decode_scores_z_kernel(Dims dm, const int
         float m = -INFINITY;
 #pragma unroll
         for (int i = 0; i < kMaxParts / 16; ++i) m = fmaxf(m, v[i].x);
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        m = row_reduce(m, [](float a, float c) { return fmaxf(a, c); });
         const float mu = m == -INFINITY ? 0.f : m;
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < kMaxParts / 16; ++i) s += v[i].y * fast_exp2(v[i].x - mu);
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o);
+        s = row_reduce(s, [](float a, float c) { return a + c; });
         if (sub == 0 && (tid >> 4) < G)   // approximate mode: rho times fewer kernels were summed; 0 when none is visible
             lse_h[tid >> 4] = dm.rho > 1 ? (m == -INFINITY ? 0.f : m + fast_log2(s) + (float)(31 - __clz(dm.rho)))
                                          : m + fast_log2(s);
     }
     // logits of this thread's kernel, all heads
-    const bool have = tid <= 256 && jh >= 0 && jh < n_vis;
+    const bool have = tid <= 4 * kListBlocks && jh >= 0 && jh < n_vis;
     __syncthreads();
-    if (tid <= 256) {
+    if (tid <= 4 * kListBlocks) {
         float acc = 0.f;
 #pragma unroll
         for (int gq = 0; gq < 16; ++gq)
@@ -538,14 +555,26 @@ __global__ __launch_bounds__(320) void decode_scores_z_kernel(Dims dm, const int
         rs[tid] = have ? fminf(fmaxf(acc * (1.f / G), kScoreFloor), kScoreCeil) : -INFINITY;
     }
     __syncthreads();
-    if (tid < 64) {
-        const int j = blockIdx.x * 64 + tid;          // kernels 4j-1 .. 4j+3 = rs[4*tid .. 4*tid+4]
-        if (j <= (L - 1) / kBlock) {
-            float v = rs[4 * tid];
+    const int wave = tid >> 6, lane = tid & 63;
+    uint64_t e = 0ull;
+    int rank = 64;
+    if (wave < 2) {
+        const int j = blockIdx.x * kListBlocks + tid;     // kernels 4j-1 .. 4j+3 = rs[4*tid .. 4*tid+4]
+        float r = rs[4 * tid];
 #pragma unroll
-            for (int x = 1; x < 5; ++x) v = fmaxf(v, rs[4 * tid + x]);
-            R[((int64_t)bv * dm.Hkv + h) * nb_cap + j] = v;
-        }
+        for (int x = 1; x < 5; ++x) r = fmaxf(r, rs[4 * tid + x]);
+        const RowRange rr(dm, L);
+        e = pick_element(r, j, rr.n_init, rr.jc_max);
+        words[wave][lane] = e;
+        best[wave][lane] = 0ull;
+        __builtin_amdgcn_wave_barrier();                  // same wavefront: LDS keeps the order
+        rank = count_larger(words[wave], 64, e);          // no two words are equal
+        if (rank < list_len) best[wave][rank] = e;
+    }
+    __syncthreads();
+    if (wave < 2 && rank < list_len) {
+        rank += count_larger(best[wave ^ 1], (list_len + 3) & ~3, e);
+        if (rank < list_len) lists[(((int64_t)bv * dm.Hkv + h) * gridDim.x + blockIdx.x) * list_len + rank] = e;
     }
 }
 
@@ -566,162 +595,219 @@ __global__ __launch_bounds__(320) void decode_scores_z_kernel(Dims dm, const int
 //   1a. rank of `best` inside its wavefront; the n_pick best of each wavefront survive
 //   1b. rank of the survivors among all survivors = rank among all thread maxima; gives tau
 //   2.  the n_pick best threads publish their elements >= tau; rank by counting among those
-constexpr int kPickThreads = 256, kPickMaxVPT = 16;
+//   3.  every wavefront repeats the ranking of the survivors of all of them and orders the selected blocks
+//
+// Plain decode: the elements are the nb / 64 sorted lists the scoring kernel left.  Verification: a row of nb scores.
+constexpr int kPickThreads = 256, kPickWaves = kPickThreads / 64, kPickMaxVPT = 16;
 // LDS of the top-k, carved out of the kernel's dynamic shared memory (16-byte aligned) so that its size
 // follows the call's top-k instead of the largest one supported.
-template <int kThreads>
 struct PickShared {
-    uint64_t *tmax;                                       // [kThreads] thread maxima, 64 per wavefront
-    uint64_t *top;                                        // [kWaves * topk + 4] per wavefront: its n_pick best (0 = none)
-    uint64_t *cand;                                       // [kWaves][cand_cap] per wavefront: elements that can still make it
-    int *picked;                                          // [topk]
+    uint64_t *tmax;                                       // [kPickThreads] thread maxima, 64 per wavefront
+    uint64_t *top;                                        // [kPickWaves][n_pick rounded up to 4] per wavefront: its best (0 = none)
+    uint64_t *cand;                                       // [kPickWaves][cand_cap] per wavefront: elements that can still make it
     int cand_cap;
     __device__ PickShared(unsigned char *smem, int topk, int vpt) {
         tmax = reinterpret_cast<uint64_t *>(smem);
-        top = tmax + kThreads;
-        cand = top + ((kThreads / 64 * topk + 4 + 1) & ~1);
+        top = tmax + kPickThreads;
+        cand = top + kPickWaves * ((topk + 3) & ~3);
         cand_cap = (topk * vpt + 3) & ~3;
-        picked = reinterpret_cast<int *>(cand + kThreads / 64 * cand_cap);
     }
 };
-static inline size_t pick_shared_bytes(int threads, int topk, int vpt) {
-    const size_t words = (size_t)threads + (((size_t)threads / 64 * topk + 4 + 1) & ~(size_t)1) +
-                         (size_t)threads / 64 * (((size_t)topk * vpt + 3) & ~(size_t)3);
-    return words * sizeof(uint64_t) + (size_t)topk * sizeof(int);
+static inline size_t pick_shared_bytes(int topk, int vpt) {
+    const size_t words = (size_t)kPickThreads + (size_t)kPickWaves * ((topk + 3) & ~3) +
+                         (vpt > 1 ? (size_t)kPickWaves * (((size_t)topk * vpt + 3) & ~(size_t)3) : 0);
+    return words * sizeof(uint64_t);
 }
 
-// Top-k of one row of block scores for a query at cache row L - 1 (L >= 1), by a whole workgroup of
-// kThreads threads; thread t passes the scores of blocks t, t + kThreads, ... in r.  The selected
-// blocks, ascending, go to `o` (a row of the block_idx output, padded with -1; may be null) and to
-// `sel` (LDS, may be null).  Returns their number.  Contains barriers: every thread calls it.
+// This thread's kVPT elements of row `row` of the top-k's input: words of the lists (kLists) or scores of a row.  Every
+// load goes out before the sequence length is known; what lies past the end is dropped afterwards.
+struct PickInput {
+    const void *base;                                     // lists: uint64 [rows][n_lists][list_len]; scores: float [rows][pitch]
+    int32_t n_lists, list_len, inv;                       // inv: i / n_lists = (i * inv) >> 20 for i < 4096
+    int32_t pitch;
+};
+template <bool kLists, int kVPT>
+struct PickLoad {
+    uint64_t w[kLists ? kVPT : 1];
+    float r[kLists ? 1 : kVPT];
+    __device__ PickLoad(const PickInput &in, int64_t row) {
+#pragma unroll
+        for (int s = 0; s < kVPT; ++s) {
+            const int i = threadIdx.x + kPickThreads * s;
+            if constexpr (kLists) {                       // element i = entry i / n_lists of list i % n_lists
+                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
+                w[s] = reinterpret_cast<const uint64_t *>(in.base)[(row * in.n_lists + list) * in.list_len + min(rank, in.list_len - 1)];
+            } else {
+                r[s] = reinterpret_cast<const float *>(in.base)[row * in.pitch + min(i, in.pitch - 1)];
+            }
+        }
+    }
+    __device__ void elements(const PickInput &in, const RowRange &rr, int L, uint64_t (&el)[kVPT]) const {
+#pragma unroll
+        for (int s = 0; s < kVPT; ++s) {
+            const int i = threadIdx.x + kPickThreads * s;
+            if constexpr (kLists) {
+                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
+                el[s] = (rank < in.list_len && list * kListBlocks <= (L - 1) / kBlock) ? w[s] : 0ull;   // (later lists were not written)
+            } else {
+                el[s] = pick_element(r[s], i, rr.n_init, rr.jc_max);
+            }
+        }
+    }
+};
+
+// Top-k of one row for a query at cache row L - 1 (L >= 1), by a whole workgroup of kPickThreads threads; a thread
+// brings kVPT elements.  Leaves the selected blocks in this wavefront's `mine` (LDS, [64]): the picked ones, best first,
+// then the forced ones; every wavefront gets its own copy.  Contains barriers: every thread calls it.
 //
 // Two levels.  Every wavefront finds the n_pick best of its own share on its own, synchronising with
 // nobody: rank its 64 thread maxima by counting; an element of its top n_pick can only sit in a
 // thread whose maximum is among the n_pick largest, and is at least tau, the n_pick-th largest
 // maximum; those threads publish their elements >= tau (a handful) and the wavefront ranks them by
-// counting.  After one workgroup barrier the (at most) kWaves * n_pick finalists are ranked the same
-// way.  A step that waits for the slowest wavefront costs more here than the arithmetic between two
-// of them, hence as few of those as possible.
-template <int kThreads, int kVPT>
-__device__ inline int pick_row(const Dims &dm, int L, const float (&r)[kVPT], const PickShared<kThreads> &sh,
-                               int32_t *__restrict__ o, int *sel) {
-    constexpr int kWaves = kThreads / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b_own = (L - 1) / kBlock, n_blk = b_own + 1;
-    const int n_sel = dm.topk < n_blk ? dm.topk : n_blk;
-    const int n_init = dm.n_init < n_blk ? dm.n_init : n_blk;                 // forced leading blocks
-    const int lo_local = max(n_init, b_own - dm.n_local + 1);                 // forced trailing: lo_local..b_own
-    const int jc_max = lo_local - 1;                                          // candidates: n_init..jc_max
-    const int n_pick = n_sel - (n_init + (b_own - lo_local + 1));
+// counting (with one element per thread the first ranking is the answer).  Then every finalist is counted against the
+// four short lists, one list per wavefront, and the counts are added.
+// Clock stamps at 128K context, one sequence: 0.4 us first ranking, 0.1 barrier, 0.3 second; a row of 2048 scores cost
+// 4.4 us in all.
+template <int kVPT>
+__device__ inline void pick_row(const RowRange &rr, const uint64_t (&el)[kVPT], const PickShared &sh, int *mine) {
+    __shared__ int counts[kPickWaves][kPickWaves * kMaxTopk];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n_pick = rr.n_pick;
     if (n_pick > 0) {                                                         // uniform over the workgroup
-        const int n_top = (kWaves * n_pick + 3) & ~3;
-        uint64_t *wtop = sh.top + wave * n_pick, *wcand = sh.cand + wave * sh.cand_cap, *wmax = sh.tmax + 64 * wave;
-        if (lane < n_pick) wtop[lane] = 0ull;
-        if (wave == kWaves - 1 && lane < n_top - kWaves * n_pick) sh.top[kWaves * n_pick + lane] = 0ull;
-        uint64_t el[kVPT], best = 0ull;
+        const int pitch = (n_pick + 3) & ~3, n_fin = kPickWaves * pitch;
+        uint64_t *wtop = sh.top + wave * pitch, *wmax = sh.tmax + 64 * wave;
+        if (lane < pitch) wtop[lane] = 0ull;
+        uint64_t best = 0ull;
 #pragma unroll
-        for (int s = 0; s < kVPT; ++s) {
-            const int j = tid + kThreads * s;
-            const uint32_t kj = r[s] == -INFINITY ? 1u : __float_as_uint(r[s]);
-            const uint32_t key = (j >= n_init && j <= jc_max) ? kj : 0u;
-            el[s] = ((uint64_t)key << 32) | (uint32_t)~j;
-            best = el[s] > best ? el[s] : best;
-        }
+        for (int s = 0; s < kVPT; ++s) best = el[s] > best ? el[s] : best;
         const bool real = best >= kPickValid;
         wmax[lane] = best;
         __builtin_amdgcn_wave_barrier();                  // same wavefront: LDS keeps the order
         const int lrank = count_larger(wmax, 64, best);
-        const bool finalist = real && lrank < n_pick;
-        uint64_t tau = kPickValid;                        // the n_pick-th largest maximum, if there are that many real ones
-        const uint64_t who = __ballot(real && lrank == n_pick - 1);
-        if (who) {
-            const int src = __builtin_ctzll(who);
-            tau = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(best >> 32), src) << 32) |
-                  (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, src);
-        }
-        int n_cand = 0;                                   // <= n_pick * kVPT <= cand_cap
-        const uint64_t below = (1ull << lane) - 1ull;
+        if constexpr (kVPT == 1) {
+            if (real && lrank < n_pick) wtop[lrank] = best;
+        } else {
+            uint64_t *wcand = sh.cand + wave * sh.cand_cap;
+            const bool finalist = real && lrank < n_pick;
+            uint64_t tau = kPickValid;                    // the n_pick-th largest maximum, if there are that many real ones
+            const uint64_t who = __ballot(real && lrank == n_pick - 1);
+            if (who) {
+                const int src = __builtin_ctzll(who);
+                tau = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(best >> 32), src) << 32) |
+                      (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, src);
+            }
+            int n_cand = 0;                               // <= n_pick * kVPT <= cand_cap
+            const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
-        for (int s = 0; s < kVPT; ++s) {
-            const bool pub = finalist && el[s] >= tau;
-            const uint64_t m = __ballot(pub);
-            if (pub) wcand[n_cand + __popcll(m & below)] = el[s];
-            n_cand += __popcll(m);
-        }
-        const int n_cand4 = (n_cand + 3) & ~3;
-        if (lane < n_cand4 - n_cand) wcand[n_cand + lane] = 0ull;
-        __builtin_amdgcn_wave_barrier();
-        for (int i = lane; i < n_cand; i += 64) {
-            const uint64_t e = wcand[i];
-            const int beaten = count_larger(wcand, n_cand4, e);
-            if (beaten < n_pick) wtop[beaten] = e;
-        }
-        __syncthreads();
-        if (tid < kWaves * n_pick) {                      // kWaves * n_pick <= kThreads: n_pick <= 64
-            const uint64_t e = sh.top[tid];
-            if (e >= kPickValid) {
-                const int beaten = count_larger(sh.top, n_top, e);
-                if (beaten < n_pick) sh.picked[beaten] = (int)~(uint32_t)e;
+            for (int s = 0; s < kVPT; ++s) {
+                const bool pub = finalist && el[s] >= tau;
+                const uint64_t m = __ballot(pub);
+                if (pub) wcand[n_cand + __popcll(m & below)] = el[s];
+                n_cand += __popcll(m);
+            }
+            const int n_cand4 = (n_cand + 3) & ~3;
+            if (lane < n_cand4 - n_cand) wcand[n_cand + lane] = 0ull;
+            __builtin_amdgcn_wave_barrier();
+            for (int i = lane; i < n_cand; i += 64) {
+                const uint64_t e = wcand[i];
+                const int beaten = count_larger(wcand, n_cand4, e);
+                if (beaten < n_pick) wtop[beaten] = e;
             }
         }
         __syncthreads();
-    }
-    if (wave == 0) {
-        int mine = 0x7fffffff;
-        if (lane < n_pick) mine = sh.picked[lane];
-        else if (lane < n_sel) {
-            const int f = lane - n_pick;
-            mine = f < n_init ? f : lo_local + (f - n_init);
-        }
-        // ascending order: rank = number of selected blocks below mine
-        int rank = 0;
-        for (int e = 0; e < n_sel; ++e) rank += __builtin_amdgcn_readlane(mine, e) < mine ? 1 : 0;
-        if (lane < n_sel) {
-            if (o) o[rank] = mine;
-            if (sel) sel[rank] = mine;
-        } else if (o && lane < dm.topk) {
-            o[lane] = -1;
+        for (int i = lane; i < n_fin; i += 64) counts[wave][i] = count_larger(wtop, pitch, sh.top[i]);
+        __syncthreads();
+        for (int i = lane; i < n_fin; i += 64) {
+            const uint64_t e = sh.top[i];
+            const int beaten = (counts[0][i] + counts[1][i]) + (counts[2][i] + counts[3][i]);
+            if (e >= kPickValid && beaten < n_pick) mine[beaten] = (int)~(uint32_t)e;
         }
     }
-    return n_sel;
+    if (lane >= max(n_pick, 0) && lane < rr.n_sel) {      // the forced blocks
+        const int f = lane - max(n_pick, 0);
+        mine[lane] = f < rr.n_init ? f : rr.lo_local + (f - rr.n_init);
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
-template <int kVPT>
-__global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, const int32_t *__restrict__ seqlens,
-                                                                    const float *__restrict__ R, int32_t nb_cap,
-                                                                    int32_t *__restrict__ block_idx) {
-    extern __shared__ __align__(16) unsigned char pick_smem[];
-    const PickShared<kPickThreads> sh(pick_smem, dm.topk, kVPT);
-    const int row = blockIdx.x, bv = row / dm.Hkv, h = row - bv * dm.Hkv;
-    const int tid = threadIdx.x;
-    const float *Rr = R + (int64_t)row * nb_cap;
-    float r[kVPT];                                        // every load issued before any use
+// Puts a wavefront's n_sel selected blocks (`mine`, LDS) in ascending order: returns the place of this lane's block
+// (lane < n_sel) and, if `o` is given, writes the row of the block_idx output, padded with -1.
+__device__ inline int order_row(int *mine, int n_sel, int topk, int32_t *__restrict__ o) {
+    const int lane = threadIdx.x & 63;
+    const int x = lane < n_sel ? mine[lane] : 0x7fffffff;
+    mine[lane] = x;
+    __builtin_amdgcn_wave_barrier();
+    int rank = 0;                                         // number of selected blocks below x
+    for (int e = 0; e < n_sel; e += 16) {
+        int4 y[4];
 #pragma unroll
-    for (int s = 0; s < kVPT; ++s) r[s] = Rr[min(tid + kPickThreads * s, nb_cap - 1)];
+        for (int i = 0; i < 4; ++i) y[i] = *reinterpret_cast<const int4 *>(mine + e + 4 * i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            rank += (y[i].x < x ? 1 : 0) + (y[i].y < x ? 1 : 0) + (y[i].z < x ? 1 : 0) + (y[i].w < x ? 1 : 0);
+    }
+    if (o) {
+        if (lane < n_sel) o[rank] = x;
+        else if (lane < topk) o[lane] = -1;
+    }
+    return rank;
+}
+
+template <bool kLists, int kVPT>
+__global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, const int32_t *__restrict__ seqlens,
+                                                                    PickInput in, int32_t *__restrict__ block_idx) {
+    extern __shared__ __align__(16) unsigned char pick_smem[];
+    const PickShared sh(pick_smem, dm.topk, kVPT);
+    const int row = blockIdx.x, bv = row / dm.Hkv, h = row - bv * dm.Hkv;
+    const PickLoad<kLists, kVPT> load(in, row);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     int32_t *o = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
     if (L < 1) {
-        if (tid < dm.topk) o[tid] = -1;
+        if ((int)threadIdx.x < dm.topk) o[threadIdx.x] = -1;
         return;
     }
-    pick_row<kPickThreads, kVPT>(dm, L, r, sh, o, nullptr);
+    const RowRange rr(dm, L);
+    uint64_t el[kVPT];
+    load.elements(in, rr, L, el);
+    __shared__ __align__(16) int mine[kPickWaves][64];
+    pick_row<kVPT>(rr, el, sh, mine[threadIdx.x >> 6]);
+    if (threadIdx.x < 64) order_row(mine[0], rr.n_sel, dm.topk, o);
 }
 
 // ---- attention, part 1: one workgroup per selected block --------------------------------------
 // grid (topk, Hkv, B), 256 threads.  Every load of the block (64 key rows as MFMA operands, 64
 // value rows for LDS, the query) is issued before anything is used.  Wave w: S^T = K . Q^T for
-// keys 16w..16w+15; the probabilities go to LDS as P[key][head]; then wave w owns value channels
-// 32w..32w+31 and computes O^T = V^T . P^T on the matrix cores, gathering the V^T fragments
-// (8 keys of one channel per lane) from the row-major value tile in LDS.
-constexpr int kVsPitch = kHeadDim + 4;               // bf16 elements per LDS value row: conflict-free column reads
+// keys 16w..16w+15; the probabilities go to LDS in bf16 as the B operand of the value product; then
+// wave w owns value channels 32w..32w+31 and computes O^T = V^T . P^T on the matrix cores, reading
+// V^T through the transposing LDS load from the row-major value tile.
+constexpr int kVsPitch = kHeadDim + 4;               // bf16 elements per LDS value row: 4 rows of a transposing load in 4 bank groups
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+
+// The rows of a block this thread loads, as offsets from the block's first row: value rows tid/16 + 16i (channels
+// 8(tid%16) ..), key row 16 wave + n (channels 32ks + 8g ..).  Worked out before the block is known, so that a uniform
+// base is all that is added afterwards (a lone wavefront spends 0.4 us on the address arithmetic otherwise).
+struct BlockRows {
+    int64_t v[4], k;
+    __device__ BlockRows(const Tensor &kt, const Tensor &vt, int last) {
+        const int tid = threadIdx.x, lane = tid & 63;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (int64_t)min((tid >> 4) + 16 * i, last) * vt.st + 8 * (tid & 15);
+        k = (int64_t)min(16 * (tid >> 6) + (lane & 15), last) * kt.st + 8 * (lane >> 4);
+    }
+};
+
 // Partial attention of query row bv = (b, qi), L cache rows up to and including the query, over
-// selected block `blk` (entry cidx of the row's list; < 0: none).  Whole workgroup of 256 threads.
-__device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tensor &k, const Tensor &v, int bv, int b,
-                                    int qi, int h, int cidx, int L, int blk, const uint64_t *__restrict__ tree_mask,
-                                    float *__restrict__ o_part, float2 *__restrict__ ml_part) {
+// selected block `blk` (< 0: none; uniform).  Whole workgroup of 256 threads.  `place()` returns the block's entry in
+// the row's ascending list, where the partial result goes; it is called while the block's rows are on their way.
+// kFresh: row fresh_row of the caches (-1: none) is being written by this very launch: it is taken from fresh.k_new / v_new.
+template <bool kFresh, typename Place>
+__device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tensor &k, const Tensor &v, const BlockRows &rows,
+                                    int bv, int b, int qi, int h, int L, int blk, const uint64_t *__restrict__ tree_mask,
+                                    float *__restrict__ o_part, float2 *__restrict__ ml_part, Place place,
+                                    const AppendArgs *fresh = nullptr, int fresh_row = -1) {
     __shared__ __align__(16) uint16_t Vs[kBlock * kVsPitch];
-    __shared__ float Ps[kBlock][17];
+    __shared__ __align__(16) uint4 Pb[2 * 4 * 16];       // [key half kk][key group g][head]: keys 32kk + 8g .. +7 in bf16
     __shared__ float wmax[4][16], wsum[4][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
@@ -732,6 +818,7 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
     // a tree mask may let a query attend drafted tokens that lie after it in the cache
     const bool valid = L >= 1 && blk >= 0 && (int64_t)blk * kBlock < (tree_mask ? L_all : L);
     if (!valid) {                                        // uniform over the workgroup
+        const int cidx = place();
         const int head = tid & 15, chunk = tid >> 4;
         if (head < G) {
             const int64_t pbase = (((int64_t)bv * dm.Hq + h * G + head) * dm.topk + cidx);
@@ -744,27 +831,30 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
         return;
     }
     const int key0 = blk * kBlock;
-    const int last_row = dm.max_seqlen - 1;              // rows the query may not see are read (in bounds) and masked
     // ---- all loads --------------------------------------------------------------------------------
+    // (rows the query may not see are read, in bounds, and masked)
     const int c8 = tid & 15, vr = tid >> 4;
     uint4 vrow[4];
-    {
-        const __bf16 *vb = v.ptr + b * v.sb + h * v.sh + 8 * c8;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            vrow[i] = *reinterpret_cast<const uint4 *>(vb + (int64_t)min(key0 + vr + 16 * i, last_row) * v.st);
-    }
     bf16x8 a[4], bq[4];
     {
-        const int key = min(key0 + 16 * wave + n, last_row);
-        const __bf16 *kr = k.ptr + b * k.sb + h * k.sh + (int64_t)key * k.st + 8 * g;
+        const __bf16 *kb = k.ptr + b * k.sb + h * k.sh + (int64_t)key0 * k.st;
+        const __bf16 *vb = v.ptr + b * v.sb + h * v.sh + (int64_t)key0 * v.st;
+        const BlockRows r = key0 + kBlock <= dm.max_seqlen ? rows : BlockRows(k, v, dm.max_seqlen - 1 - key0);
+        const __bf16 *kr = kb + r.k;
+        if (kFresh && key0 + 16 * wave + n == fresh_row) kr = fresh->k_new.ptr + b * fresh->k_new.sb + h * fresh->k_new.sh + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) a[ks] = load8(kr + 32 * ks);
         const __bf16 *qr = q.ptr + b * q.sb + qi * q.st + (int64_t)(h * G + min(n, G - 1)) * q.sh + 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            a[ks] = load8(kr + 32 * ks);
-            bq[ks] = load8(qr + 32 * ks);
+        for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const __bf16 *vp = vb + r.v[i];
+            if (kFresh && key0 + vr + 16 * i == fresh_row) vp = fresh->v_new.ptr + b * fresh->v_new.sb + h * fresh->v_new.sh + 8 * c8;
+            vrow[i] = *reinterpret_cast<const uint4 *>(vp);
         }
     }
+    const int cidx = place();
     // ---- which of the block's 64 keys the query attends: bit r = key key0 + r ------------------------
     // Causal: keys up to the query's own position.  Tree mask: every context key (before the drafted
     // tokens), and drafted token j iff bit j of the query's mask word is set.
@@ -779,15 +869,6 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
         if (sh >= 0) allow = sh < 64 ? mw >> sh : 0ull;
         else allow = sh > -64 ? (mw << -sh) | ((1ull << -sh) - 1ull) : ~0ull;
     }
-    // ---- value tile to LDS (masked rows as zeros: 0 * garbage must stay 0) ----------------------------
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = vr + 16 * i;
-        uint4 x = vrow[i];
-        if (!((allow >> r) & 1ull)) x = uint4{0u, 0u, 0u, 0u};
-        *reinterpret_cast<uint2 *>(&Vs[r * kVsPitch + 8 * c8]) = uint2{x.x, x.y};
-        *reinterpret_cast<uint2 *>(&Vs[r * kVsPitch + 8 * c8 + 4]) = uint2{x.z, x.w};
-    }
     // ---- scores of this wave's 16 keys ---------------------------------------------------------------
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -800,16 +881,28 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
     }
     mx = xgroup_max(mx);
     if (g == 0) wmax[wave][n] = mx;
+    // ---- value tile to LDS (masked rows as zeros: 0 * garbage must stay 0) ----------------------------
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = vr + 16 * i;
+        uint4 y = vrow[i];
+        if (!((allow >> r) & 1ull)) y = uint4{0u, 0u, 0u, 0u};
+        *reinterpret_cast<uint2 *>(&Vs[r * kVsPitch + 8 * c8]) = uint2{y.x, y.y};
+        *reinterpret_cast<uint2 *>(&Vs[r * kVsPitch + 8 * c8 + 4]) = uint2{y.z, y.w};
+    }
     __syncthreads();
     const float m = fmaxf(fmaxf(wmax[0][n], wmax[1][n]), fmaxf(wmax[2][n], wmax[3][n]));
     const float m_sub = m == -INFINITY ? 0.f : m;       // -inf only when a tree mask hides the whole block
     float ps = 0.f;
+    bf16x4 pv;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float p = fast_exp2(x[j] - m_sub);
         ps += p;
-        Ps[16 * wave + 4 * g + j][n] = p;
+        pv[j] = (__bf16)p;
     }
+    // keys 16 wave + 4g + j: half wave/2, group 2 (wave%2) + g/2, elements 4 (g%2) + j
+    reinterpret_cast<uint2 *>(Pb)[2 * (((wave >> 1) * 4 + 2 * (wave & 1) + (g >> 1)) * 16 + n) + (g & 1)] = __builtin_bit_cast(uint2, pv);
     ps = xgroup_sum(ps);
     if (g == 0) wsum[wave][n] = ps;
     __syncthreads();
@@ -818,18 +911,13 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
     o[0] = o[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 pb;                                       // B: head n, keys 32kk + 8g .. +7
+        const bf16x8 pb = __builtin_bit_cast(bf16x8, Pb[(kk * 4 + g) * 16 + n]);       // B: head n, keys 32kk + 8g .. +7
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pb[e] = (__bf16)Ps[32 * kk + 8 * g + e][n];
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            const uint16_t *vc = &Vs[(32 * kk + 8 * g) * kVsPitch + 32 * wave + 16 * ct + n];   // A: channel row n
-            uint32_t w[4];
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2)
-                w[e2] = (uint32_t)vc[(2 * e2) * kVsPitch] | ((uint32_t)vc[(2 * e2 + 1) * kVsPitch] << 16);
-            const uint4 av = {w[0], w[1], w[2], w[3]};
-            o[ct] = mfma16(__builtin_bit_cast(bf16x8, av), pb, o[ct]);
+        for (int ct = 0; ct < 2; ++ct) {                 // A: channel 32 wave + 16ct + n, the same keys: 4 rows x 16 channels per read
+            const uint16_t *vp = &Vs[(32 * kk + 8 * g + (n >> 2)) * kVsPitch + 32 * wave + 16 * ct + 4 * (n & 3)];
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)vp);
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)(vp + 4 * kVsPitch));
+            o[ct] = mfma16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)), pb, o[ct]);
         }
     }
     if (n < G) {                                         // lane: head n, channels 32w + 16ct + 4g .. +3
@@ -853,72 +941,79 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     const int blk = block_idx[(((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk + cidx];
-    attend_block(dm, q, k, v, bv, b, qi, h, cidx, L, blk, tree_mask, o_part, ml_part);
+    const BlockRows rows(k, v, kBlock - 1);
+    attend_block<false>(dm, q, k, v, rows, bv, b, qi, h, L, __builtin_amdgcn_readfirstlane(blk), tree_mask, o_part, ml_part,
+                        [cidx] { return cidx; });
 }
 
 // Top-k and partial attention in one launch (the one-call decode and verification steps): a step is
 // a chain of dependent launches, each costing a launch gap and a memory round trip, and the block
 // list is the only thing the attention waits for.  Every one of the k workgroups of a (query row,
-// key-value head) repeats the top-k on the same row of block scores (same result; workgroup 0 writes
-// it out) and goes on with its own entry of the list.
-template <int kVPT>
+// key-value head) repeats the top-k on the same input (same result; workgroup 0 writes it out) and goes on with one
+// entry of the result as it stands, best first; the list's ascending order, which decides where the partial result goes,
+// is worked out while the block's rows are on their way.
+template <bool kLists, int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                                             const int32_t *__restrict__ seqlens,
-                                                                            const float *__restrict__ R, int32_t nb_cap,
+                                                                            PickInput in,
                                                                             const uint64_t *__restrict__ tree_mask,
                                                                             int32_t *__restrict__ block_idx,
                                                                             float *__restrict__ o_part,
                                                                             float2 *__restrict__ ml_part) {
     extern __shared__ __align__(16) unsigned char pick_smem[];
-    const PickShared<kPickThreads> sh(pick_smem, dm.topk, kVPT);
-    __shared__ int sel[kMaxTopk];
+    const PickShared sh(pick_smem, dm.topk, kVPT);
     const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
-    const int tid = threadIdx.x;
-    const float *Rr = R + ((int64_t)bv * dm.Hkv + h) * nb_cap;
-    float r[kVPT];                                        // every load issued before any use
-#pragma unroll
-    for (int s = 0; s < kVPT; ++s) r[s] = Rr[min(tid + kPickThreads * s, nb_cap - 1)];
+    const PickLoad<kLists, kVPT> load(in, (int64_t)bv * dm.Hkv + h);
+    const BlockRows rows(k, v, kBlock - 1);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     int32_t *orow = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
-    int blk = -1;
+    __shared__ __align__(16) int mine[kPickWaves][64];
+    const int wave = threadIdx.x >> 6;
+    int blk = -1, n_sel = 0;
     if (L < 1) {                                          // uniform over the workgroup
-        if (cidx == 0 && tid < dm.topk) orow[tid] = -1;
+        if (cidx == 0 && (int)threadIdx.x < dm.topk) orow[threadIdx.x] = -1;
     } else {
-        const int n_sel = pick_row<kPickThreads, kVPT>(dm, L, r, sh, cidx == 0 ? orow : nullptr, sel);
-        __syncthreads();
-        if (cidx < n_sel) blk = sel[cidx];
+        const RowRange rr(dm, L);
+        uint64_t el[kVPT];
+        load.elements(in, rr, L, el);
+        pick_row<kVPT>(rr, el, sh, mine[wave]);
+        n_sel = rr.n_sel;
+        if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
     }
-    attend_block(dm, q, k, v, bv, b, qi, h, cidx, L, blk, tree_mask, o_part, ml_part);
+    attend_block<false>(dm, q, k, v, rows, bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
+        if (n_sel == 0) return cidx;
+        const int rank = order_row(mine[wave], n_sel, dm.topk, cidx == 0 && wave == 0 ? orow : nullptr);
+        return cidx < n_sel ? __builtin_amdgcn_readlane(rank, cidx) : cidx;
+    });
 }
 
 // ---- attention, part 2: merge the k partials of every query head ---------------------------------
-// grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge.
+// grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge, unconditionally
+// (entries past the top-k re-read the last one and get weight zero): kTop is the top-k rounded up.
+template <int kTop>
 __global__ __launch_bounds__(128) void decode_merge_kernel(Dims dm, const float *__restrict__ o_part,
                                                             const float2 *__restrict__ ml_part, Tensor out,
                                                             float *__restrict__ lse) {
     const int hq = blockIdx.x, bv = blockIdx.y, cch = threadIdx.x;
-    const int b = bv / dm.n_q, qi = bv - b * dm.n_q;
     const int64_t pbase = ((int64_t)bv * dm.Hq + hq) * dm.topk;
-    float2 ml[kMaxTopk];
-    float ov[kMaxTopk];
+    float2 ml[kTop];
+    float ov[kTop];
 #pragma unroll
-    for (int c = 0; c < kMaxTopk; ++c) {
-        ml[c] = float2{-INFINITY, 0.f};
-        ov[c] = 0.f;
-        if (c < dm.topk) {
-            ml[c] = ml_part[pbase + c];
-            ov[c] = o_part[(pbase + c) * kHeadDim + cch];
-        }
+    for (int c = 0; c < kTop; ++c) {
+        const int64_t at = pbase + min(c, dm.topk - 1);
+        ml[c] = ml_part[at];
+        ov[c] = o_part[at * kHeadDim + cch];
     }
+    const int b = bv / dm.n_q, qi = bv - b * dm.n_q;
     float M = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < kMaxTopk; ++c) M = fmaxf(M, ml[c].x);
+    for (int c = 0; c < kTop; ++c) M = fmaxf(M, ml[c].x);
     float num = 0.f, den = 0.f;
     if (M > -INFINITY) {
 #pragma unroll
-        for (int c = 0; c < kMaxTopk; ++c) {
-            const float w = fast_exp2(ml[c].x - M);
+        for (int c = 0; c < kTop; ++c) {
+            const float w = c < dm.topk ? fast_exp2(ml[c].x - M) : 0.f;
             den += w * ml[c].y;
             num += w * ov[c];
         }
@@ -933,7 +1028,8 @@ static inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodeSelLayout {
     int32_t n_c_cap, n_part, nb_cap;
-    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only
+    int32_t n_lists, list_len;                        // plain decode: sorted lists of pick words, one per 64 blocks
+    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists, or rows of scores
 };
 static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     DecodeSelLayout l;
@@ -945,7 +1041,9 @@ static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     const size_t rows = (size_t)dm.batch * dm.n_q;
     l.z_bytes = dm.n_q == 1 ? align256(rows * dm.Hq * l.n_c_cap * sizeof(float)) : 0;
     l.part_bytes = align256(rows * dm.Hq * l.n_part * sizeof(float2));
-    l.r_bytes = align256(rows * dm.Hkv * l.nb_cap * sizeof(float));
+    l.n_lists = max(1, (dm.max_seqlen + kBlock * kListBlocks - 1) / (kBlock * kListBlocks));
+    l.list_len = max(1, dm.topk - dm.n_init - dm.n_local);
+    l.r_bytes = align256(rows * dm.Hkv * (dm.n_q == 1 ? (size_t)l.n_lists * l.list_len * sizeof(uint64_t) : l.nb_cap * sizeof(float)));
     return l;
 }
 
@@ -964,7 +1062,7 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     float *zbuf = reinterpret_cast<float *>(wsb);
     float2 *part = reinterpret_cast<float2 *>(wsb + l.z_bytes);
     float2 *part_c = reinterpret_cast<float2 *>(wsb + l.z_bytes + l.part_bytes);
-    float *R = reinterpret_cast<float *>(wsb + l.z_bytes + 2 * l.part_bytes);
+    void *R = wsb + l.z_bytes + 2 * l.part_bytes;
     const int rows = dm.batch * dm.n_q;                              // <= 65535, checked by the C ABI
     const int n_qt = (dm.n_q + kVerifyQT - 1) / kVerifyQT;
     const float2 *part_lse = dm.rho > 1 ? part_c : part;
@@ -990,48 +1088,47 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     timing_end(stream);
     timing_begin("decode_scores_kernel", stream);
     if (dm.n_q == 1)
-        hipLaunchKernelGGL(decode_scores_z_kernel, dim3(l.nb_cap / 64, dm.Hkv, dm.batch), dim3(320), 0, stream,
-                           dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm), R, l.nb_cap);
+        hipLaunchKernelGGL(decode_scores_z_kernel, dim3(l.n_lists, dm.Hkv, dm.batch), dim3(576), 0, stream,
+                           dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm),
+                           reinterpret_cast<uint64_t *>(R), l.list_len);
     else
         hipLaunchKernelGGL(decode_scores_kernel<kVerifyQT>,
                            dim3(l.nb_cap / (16 * tiles_per_wave2(kVerifyQT)), dm.Hkv, dm.batch * n_qt), dim3(256), 0,
-                           stream, dm, q, ck, seqlens, part_lse, l.n_part, R, l.nb_cap);
+                           stream, dm, q, ck, seqlens, part_lse, l.n_part, reinterpret_cast<float *>(R), l.nb_cap);
     timing_end(stream);
-    const int n_blocks = (dm.max_seqlen + kBlock - 1) / kBlock;
-    if (n_blocks > kPickThreads * kPickMaxVPT) return (int)hipErrorInvalidValue;   // rejected earlier by the C ABI
+    const bool lists = dm.n_q == 1;
+    const int n_elements = lists ? l.n_lists * l.list_len : (dm.max_seqlen + kBlock - 1) / kBlock;
+    const int vpt = (n_elements + kPickThreads - 1) / kPickThreads;
+    if (vpt > kPickMaxVPT) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
+    const PickInput in = {R, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.nb_cap};
     // Top-k and partial attention in one launch: every workgroup of the attention repeats the top-k of its
     // row, which is free while compute units idle and costs throughput once the launch fills the machine.
     constexpr int64_t kMaxFusedUnits = 1024;                         // (row, key-value head, block) workgroups
     if (attend) attend->fused = (int64_t)rows * dm.Hkv * dm.topk <= kMaxFusedUnits;
-    if (attend && attend->fused) {
-        const dim3 grid(dm.topk, dm.Hkv, rows), block(kPickThreads);
-        timing_begin("decode_pick_partial_kernel", stream);
-#define INFLLMV2_PICK_PARTIAL(VPT)                                                                                  \
-    hipLaunchKernelGGL(decode_pick_partial_kernel<VPT>, grid, block, pick_shared_bytes(kPickThreads, dm.topk, VPT), \
-                       stream, dm, q, attend->k, attend->v, seqlens, R, l.nb_cap, attend->tree_mask, block_idx,     \
-                       attend->o_part, attend->ml_part)
-        if (n_blocks <= kPickThreads * 4) INFLLMV2_PICK_PARTIAL(4);
-        else if (n_blocks <= kPickThreads * 8) INFLLMV2_PICK_PARTIAL(8);
-        else if (n_blocks <= kPickThreads * 12) INFLLMV2_PICK_PARTIAL(12);
-        else INFLLMV2_PICK_PARTIAL(16);
-#undef INFLLMV2_PICK_PARTIAL
-        timing_end(stream);
-        return (int)hipGetLastError();
+    const bool fused = attend && attend->fused;
+    timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
+#define INFLLMV2_PICK(LISTS, VPT)                                                                                       \
+    do {                                                                                                                \
+        if (fused)                                                                                                      \
+            hipLaunchKernelGGL((decode_pick_partial_kernel<LISTS, VPT>), dim3(dm.topk, dm.Hkv, rows),                   \
+                               dim3(kPickThreads), pick_shared_bytes(dm.topk, VPT), stream, dm, q, attend->k,           \
+                               attend->v, seqlens, in, attend->tree_mask, block_idx, attend->o_part, attend->ml_part);  \
+        else                                                                                                            \
+            hipLaunchKernelGGL((decode_pick_kernel<LISTS, VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),               \
+                               pick_shared_bytes(dm.topk, VPT), stream, dm, seqlens, in, block_idx);                    \
+    } while (0)
+    if (lists) {
+        if (vpt <= 1) INFLLMV2_PICK(true, 1);
+        else if (vpt <= 2) INFLLMV2_PICK(true, 2);
+        else if (vpt <= 4) INFLLMV2_PICK(true, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(true, 8);
+        else INFLLMV2_PICK(true, 16);
+    } else {
+        if (vpt <= 4) INFLLMV2_PICK(false, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(false, 8);
+        else INFLLMV2_PICK(false, 16);
     }
-    const dim3 grid(rows * dm.Hkv), block(kPickThreads);
-    timing_begin("decode_pick_kernel", stream);
-    if (n_blocks <= kPickThreads * 4)
-        hipLaunchKernelGGL(decode_pick_kernel<4>, grid, block, pick_shared_bytes(kPickThreads, dm.topk, 4), stream, dm,
-                           seqlens, R, l.nb_cap, block_idx);
-    else if (n_blocks <= kPickThreads * 8)
-        hipLaunchKernelGGL(decode_pick_kernel<8>, grid, block, pick_shared_bytes(kPickThreads, dm.topk, 8), stream, dm,
-                           seqlens, R, l.nb_cap, block_idx);
-    else if (n_blocks <= kPickThreads * 12)
-        hipLaunchKernelGGL(decode_pick_kernel<12>, grid, block, pick_shared_bytes(kPickThreads, dm.topk, 12), stream, dm,
-                           seqlens, R, l.nb_cap, block_idx);
-    else
-        hipLaunchKernelGGL(decode_pick_kernel<16>, grid, block, pick_shared_bytes(kPickThreads, dm.topk, 16), stream, dm,
-                           seqlens, R, l.nb_cap, block_idx);
+#undef INFLLMV2_PICK
     timing_end(stream);
     return (int)hipGetLastError();
 }
@@ -1060,8 +1157,11 @@ static void launch_decode_partial(const Dims &dm, Tensor q, Tensor k, Tensor v, 
 static int launch_decode_merge(const Dims &dm, const float *o_part, const float2 *ml_part, Tensor out, float *lse,
                                hipStream_t stream) {
     timing_begin("decode_merge_kernel", stream);
-    hipLaunchKernelGGL(decode_merge_kernel, dim3(dm.Hq, dm.batch * dm.n_q), dim3(128), 0, stream, dm, o_part,
-                       ml_part, out, lse);
+    const dim3 grid(dm.Hq, dm.batch * dm.n_q), block(128);
+    if (dm.topk <= 8) hipLaunchKernelGGL(decode_merge_kernel<8>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
+    else if (dm.topk <= 16) hipLaunchKernelGGL(decode_merge_kernel<16>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
+    else if (dm.topk <= 32) hipLaunchKernelGGL(decode_merge_kernel<32>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
+    else hipLaunchKernelGGL(decode_merge_kernel<64>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
     timing_end(stream);
     return (int)hipGetLastError();
 }
