@@ -988,6 +988,204 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     });
 }
 
+// ---- short caches: selection, append and partial attention in one kernel -----------------------------------
+// Up to kShortTokens cached tokens a row has at most 512 semantic kernels and 128 blocks: one workgroup scores them all
+// in registers, so nothing of the selection has to pass through memory and the step is two launches, this one and the
+// merge, instead of four -- each of which costs 1.3 to 1.9 us between kernels and a round trip to memory before it does
+// anything.  Every one of the k workgroups of a (sequence, key-value head) repeats the selection (128 KB of compressed
+// keys at most, from L2) and attends its own entry of the result; workgroup 0 writes the row and, in a step, the caches.
+// In a graph, us per step, four launches -> two: 2K G = 4 13.5 -> 8.3, one sequence of 4000 tokens 16.1 -> 11.5, 8000
+// 16.1 -> 14.4; 32 sequences of 8000, three launches: 25.8 -> 23.9.
+//   mode 0: block list only (infllmv2_select_blocks)       grid (1, Hkv, B)
+//   mode 1: append + block list (steps with many rows)      grid (1, Hkv, B)
+//   mode 2: append + block list + partial attention         grid (topk, Hkv, B)
+// Wave w scores kernels 16 kTW w .. +16 kTW - 1, Z = Q . CK^T: lane = kernel, accumulator entries = heads 4g .. 4g+3.
+constexpr int kShortTokens = 8192;
+template <int kTW, int kMode>
+__global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Tensor ck, const int32_t *__restrict__ seqlens,
+                                                            AppendArgs ap, int32_t *__restrict__ block_idx,
+                                                            float *__restrict__ o_part, float2 *__restrict__ ml_part) {
+    constexpr int kKernels = 64 * kTW, kWords = kTW > 4 ? 128 : 64;
+    static_assert(16 * kTW <= kWords, "one word per block");
+    __shared__ __align__(16) float2 wpart[4][16];
+    __shared__ float rs[kKernels + 4];                    // slot 1 + jh: score of kernel jh; slot 0: no kernel
+    __shared__ __align__(16) uint64_t words[kWords];
+    __shared__ int counts[4][kWords];
+    __shared__ int sel[4][64];                            // per wavefront: the selected blocks, ascending
+    __shared__ __align__(16) uint32_t newrow[kMode > 0 ? 64 : 4];
+    const int cidx = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int G = dm.G;
+    const int32_t L_raw = __builtin_amdgcn_readfirstlane(seqlens[b]);
+    const int L = clamp_len(L_raw, dm.max_seqlen);
+    const bool live = kMode > 0 && L_raw >= 1 && L_raw <= dm.max_seqlen;      // as the stand-alone append: others are skipped
+    int32_t *orow = block_idx + ((int64_t)b * dm.Hkv + h) * dm.topk;
+    int blk = -1;
+    const BlockRows rows(ap.k, ap.v, kBlock - 1);
+    if (live && cidx == 0 && tid < 32) {
+        const int c8 = (tid & 15) * 8;
+        const Tensor &src = tid < 16 ? ap.k_new : ap.v_new;
+        const Tensor &dst = tid < 16 ? ap.k : ap.v;
+        *reinterpret_cast<uint4 *>(dst.ptr + b * dst.sb + h * dst.sh + (int64_t)(L_raw - 1) * dst.st + c8) =
+            *reinterpret_cast<const uint4 *>(src.ptr + b * src.sb + h * src.sh + c8);
+    }
+    if (L < 1) {                                          // uniform over the workgroup
+        if (cidx == 0 && tid < dm.topk) orow[tid] = -1;
+    } else {
+        const int n_vis = num_kernels(L);
+        const RowRange rr(dm, L);
+        bf16x8 a[kTW][4], bq[4];
+        const int jw = 16 * kTW * wave;
+        if (rr.n_pick > 0) {                              // (otherwise every block is forced: nothing to score)
+            const __bf16 *ckh = ck.ptr + b * ck.sb + h * ck.sh + 8 * g;
+#pragma unroll
+            for (int i = 0; i < kTW; ++i) {               // rows past the last kernel repeat it and are masked below
+                const __bf16 *ckr = ckh + (int64_t)max(min(jw + 16 * i + n, n_vis - 1), 0) * ck.st;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) a[i][ks] = jw + 16 * i < n_vis ? load8(ckr + 32 * ks) : zero8();
+            }
+            const __bf16 *qr = q.ptr + b * q.sb + (int64_t)(h * G + min(n, G - 1)) * q.sh + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
+        }
+        if constexpr (kMode > 0) {
+            // the semantic kernel the new token completes: rows L-32 .. L-2 from the cache, row L-1 from k_new, fp64 sum in
+            // token order, one rounding (the bits of compress_keys_kernel); lane = channels 2*lane, 2*lane+1
+            const int jh_new = n_vis - 1;
+            const bool closes = live && L >= kKernel && (L - kKernel) % kStride == 0;
+            if (closes && jh_new >= jw && jh_new < jw + 16 * kTW && (rr.n_pick > 0 || cidx == 0)) {   // uniform over the wave
+                const __bf16 *kc = ap.k.ptr + b * ap.k.sb + h * ap.k.sh + 2 * lane;
+                uint32_t rowv[kKernel];
+#pragma unroll
+                for (int t = 0; t < kKernel - 1; ++t)
+                    rowv[t] = *reinterpret_cast<const uint32_t *>(kc + (int64_t)(L - kKernel + t) * ap.k.st);
+                rowv[kKernel - 1] = *reinterpret_cast<const uint32_t *>(ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + 2 * lane);
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int t = 0; t < kKernel; ++t) {
+                    s0 += (double)__uint_as_float(rowv[t] << 16);
+                    s1 += (double)__uint_as_float(rowv[t] & 0xffff0000u);
+                }
+                const uint32_t packed = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) |
+                                        ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+                newrow[lane] = packed;
+                if (cidx == 0) *reinterpret_cast<uint32_t *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh_new * ck.st + 2 * lane) = packed;
+                __builtin_amdgcn_wave_barrier();          // same wavefront: LDS keeps the order
+                // (the row's place in ck may or may not hold it yet: workgroup 0 is storing it)
+#pragma unroll
+                for (int i = 0; i < kTW; ++i)
+                    if (jw + 16 * i + n >= jh_new) {
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks)
+                            a[i][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&newrow[16 * ks + 4 * g]));
+                    }
+            }
+        }
+        uint64_t chosen[kWords / 64];                     // picked blocks as bits, 64 per word
+#pragma unroll
+        for (int i = 0; i < kWords / 64; ++i) chosen[i] = 0ull;
+        if (rr.n_pick > 0) {
+            f32x4 x[kTW];
+            float m[4], s[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m[j] = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < kTW; ++i) {
+                f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) z = mfma16(bq[ks], a[i][ks], z);
+                const bool vis = jw + 16 * i + n < n_vis;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    x[i][j] = vis ? z[j] * dm.scale_log2 : -INFINITY;
+                    m[j] = fmaxf(m[j], x[i][j]);
+                }
+            }
+            // log-sum-exp per head: over the wave's kernels, then over the waves
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                m[j] = row_reduce(m[j], [](float u, float w) { return fmaxf(u, w); });
+                const float mu = m[j] == -INFINITY ? 0.f : m[j];
+                float t = 0.f;
+#pragma unroll
+                for (int i = 0; i < kTW; ++i) t += fast_exp2(x[i][j] - mu);
+                s[j] = row_reduce(t, [](float u, float w) { return u + w; });
+            }
+            if (n == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) wpart[wave][4 * g + j] = float2{m[j], s[j]};
+            }
+            if (tid == 0) rs[0] = -INFINITY;
+            __syncthreads();
+            float lse_j[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float2 p[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) p[w] = wpart[w][4 * g + j];
+                const float M = fmaxf(fmaxf(p[0].x, p[1].x), fmaxf(p[2].x, p[3].x)), mu = M == -INFINITY ? 0.f : M;
+                float S = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) S += p[w].y * fast_exp2(p[w].x - mu);
+                lse_j[j] = M + fast_log2(S);
+            }
+            // group mean of the kernel scores; 16-lane group i % 4 keeps tile i
+#pragma unroll
+            for (int i = 0; i < kTW; ++i) {
+                float acc = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * g + j < G) acc += fast_exp2(x[i][j] - lse_j[j]);
+                acc = xgroup_sum(acc);
+                const int jh = jw + 16 * i + n;
+                if (g == (i & 3)) rs[1 + jh] = jh < n_vis ? fminf(fmaxf(acc * (1.f / G), kScoreFloor), kScoreCeil) : -INFINITY;
+            }
+            __syncthreads();
+            if (tid < kWords) {                           // 5/4 max-pool: kernels 4j-1 .. 4j+3 = rs[4j .. 4j+4]
+                uint64_t e = 0ull;
+                if (tid < 16 * kTW) {
+                    float r = rs[4 * tid];
+#pragma unroll
+                    for (int y = 1; y < 5; ++y) r = fmaxf(r, rs[4 * tid + y]);
+                    e = pick_element(r, tid, rr.n_init, rr.jc_max);
+                }
+                words[tid] = e;
+            }
+            __syncthreads();
+            // top-k by counting: every word against a quarter of the words on each wave; the words are in block order, so
+            // the picked blocks come out ascending
+#pragma unroll
+            for (int i = 0; i < kWords / 64; ++i)
+                counts[wave][64 * i + lane] = count_larger(words + wave * (kWords / 4), kWords / 4, words[64 * i + lane]);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kWords / 64; ++i) {
+                const int at = 64 * i + lane;
+                const int beaten = (counts[0][at] + counts[1][at]) + (counts[2][at] + counts[3][at]);
+                chosen[i] = __ballot(words[at] >= kPickValid && beaten < rr.n_pick);
+            }
+        }
+        // the row: forced leading blocks, picked blocks, forced trailing blocks -- ascending as they stand
+        const uint64_t below = (1ull << lane) - 1ull;
+        int *mine = sel[wave];
+        int at = rr.n_init;
+#pragma unroll
+        for (int i = 0; i < kWords / 64; ++i) {
+            if ((chosen[i] >> lane) & 1ull) mine[at + __popcll(chosen[i] & below)] = 64 * i + lane;
+            at += __popcll(chosen[i]);
+        }
+        if (lane < rr.n_init) mine[lane] = lane;
+        if (lane >= at && lane < rr.n_sel) mine[lane] = rr.lo_local + (lane - at);
+        __builtin_amdgcn_wave_barrier();
+        if (cidx == 0 && wave == 0 && lane < dm.topk) orow[lane] = lane < rr.n_sel ? mine[lane] : -1;
+        if (cidx < rr.n_sel) blk = __builtin_amdgcn_readfirstlane(mine[cidx]);
+    }
+    if constexpr (kMode == 2)
+        attend_block<true>(dm, q, ap.k, ap.v, rows, b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
+                           live ? L_raw - 1 : -1);
+}
+
 // ---- attention, part 2: merge the k partials of every query head ---------------------------------
 // grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge, unconditionally
 // (entries past the top-k re-read the last one and get weight zero): kTop is the top-k rounded up.
@@ -1052,10 +1250,53 @@ size_t select_decode_ws_bytes(const Dims &dm) {
     return l.z_bytes + 2 * l.part_bytes + l.r_bytes;
 }
 
+// One workgroup per row can score it all (see decode_short_kernel); the approximate log-sum-exp keeps the long path.
+static bool short_cache(const Dims &dm) { return dm.n_q == 1 && dm.rho == 1 && dm.max_seqlen <= kShortTokens; }
+// Fused top-k and attention: every workgroup repeats the top-k of its row, which is free while compute units idle and
+// costs throughput once the launch fills the machine.
+constexpr int64_t kMaxFusedUnits = 1024;              // (row, key-value head, block) workgroups
+static bool fuse_units(const Dims &dm) { return (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk <= kMaxFusedUnits; }
+
+static int short_tiles(const Dims &dm) {              // tiles of 16 kernels (16 blocks) per wave
+    const int n_blocks = (dm.max_seqlen + kBlock - 1) / kBlock;
+    return n_blocks <= 16 ? 1 : n_blocks <= 32 ? 2 : n_blocks <= 64 ? 4 : 8;
+}
+// Repeating the whole selection in every attention workgroup beats a launch for it while the workgroups fit the chip a
+// few times over; the more kernels there are to score, the earlier that ends.  Measured (us, fused / apart): 900 tokens
+// 1024 units 16.6 / 18.6, 2048 30.9 / 28.0; 2000 tokens 512 15.1 / 16.7, 1024 19.4 / 19.6 and 16.9 / 16.3; 4000 tokens
+// 256 13.7 / 15.0, 512 17.3 / 17.7 and 16.2 / 15.0; 8000 tokens 256 16.6 / 18.2, 512 21.7 / 20.8.
+static bool fuse_short(const Dims &dm) {
+    const int64_t units = (int64_t)dm.batch * dm.Hkv * dm.topk;
+    const int t = short_tiles(dm);
+    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? 384 : 256);
+}
+
+template <int kMode>
+static int launch_short(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap, const int32_t *seqlens, int32_t *block_idx,
+                        float *o_part, float2 *ml_part, hipStream_t stream) {
+    const dim3 grid(kMode == 2 ? dm.topk : 1, dm.Hkv, dm.batch), block(256);
+    timing_begin("decode_short_kernel", stream);
+#define INFLLMV2_SHORT(TW) \
+    hipLaunchKernelGGL((decode_short_kernel<TW, kMode>), grid, block, 0, stream, dm, q, ck, seqlens, ap, block_idx, o_part, ml_part)
+    switch (short_tiles(dm)) {
+        case 1: INFLLMV2_SHORT(1); break;
+        case 2: INFLLMV2_SHORT(2); break;
+        case 4: INFLLMV2_SHORT(4); break;
+        default: INFLLMV2_SHORT(8); break;
+    }
+#undef INFLLMV2_SHORT
+    timing_end(stream);
+    return (int)hipGetLastError();
+}
+
 int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens,
                          int32_t *block_idx, void *ws, hipStream_t stream, const AppendArgs *append,
                          AttendArgs *attend) {
     if (dm.batch <= 0) return 0;
+    if (short_cache(dm) && !append) {
+        const AppendArgs none = {q, q, q, q};                        // unused placeholders
+        return launch_short<0>(dm, q, ck, none, seqlens, block_idx, nullptr, nullptr, stream);
+    }
     DecodeSelLayout l = decode_sel_layout(dm);
     if (l.n_c_cap > 16384) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
     char *wsb = reinterpret_cast<char *>(ws);
@@ -1101,10 +1342,7 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     const int vpt = (n_elements + kPickThreads - 1) / kPickThreads;
     if (vpt > kPickMaxVPT) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
     const PickInput in = {R, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.nb_cap};
-    // Top-k and partial attention in one launch: every workgroup of the attention repeats the top-k of its
-    // row, which is free while compute units idle and costs throughput once the launch fills the machine.
-    constexpr int64_t kMaxFusedUnits = 1024;                         // (row, key-value head, block) workgroups
-    if (attend) attend->fused = (int64_t)rows * dm.Hkv * dm.topk <= kMaxFusedUnits;
+    if (attend) attend->fused = fuse_units(dm);
     const bool fused = attend && attend->fused;
     timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
 #define INFLLMV2_PICK(LISTS, VPT)                                                                                       \
@@ -1184,6 +1422,14 @@ int launch_decode_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap
     if (dm.batch <= 0) return 0;
     AttendArgs at = {append.k, append.v, nullptr, false, nullptr, nullptr};
     attn_decode_ws(dm, ws_attn, at.o_part, at.ml_part);
+    if (short_cache(dm)) {
+        const bool fused = fuse_short(dm);
+        const int err = fused ? launch_short<2>(dm, q, ck, append, seqlens, block_idx, at.o_part, at.ml_part, stream)
+                                       : launch_short<1>(dm, q, ck, append, seqlens, block_idx, nullptr, nullptr, stream);
+        if (err) return err;
+        if (!fused) launch_decode_partial(dm, q, append.k, append.v, seqlens, block_idx, nullptr, at.o_part, at.ml_part, stream);
+        return launch_decode_merge(dm, at.o_part, at.ml_part, out, lse, stream);
+    }
     const int err = launch_select_decode(dm, q, ck, seqlens, block_idx, ws_select, stream, &append, &at);
     if (err) return err;
     if (!at.fused) launch_decode_partial(dm, q, append.k, append.v, seqlens, block_idx, nullptr, at.o_part, at.ml_part, stream);

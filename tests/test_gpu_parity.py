@@ -925,6 +925,55 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# Caches of up to 8192 tokens take the one-kernel selection: both sides of each of its lines (16, 32, 64, 128 blocks), the
+# three-launch form for many rows, the long path from 8193 tokens on and around a list of 128 blocks, lengths that complete
+# a kernel, are shorter than one, or select everything.
+@pytest.mark.parametrize("cap,lens,Hq,Hkv,topk,forced", [
+    (64, [1, 31, 32, 64], 32, 2, 16, (1, 2)), (1024, [1024, 1008, 1023], 32, 2, 8, (1, 2)), (1025, [1025, 48], 4, 2, 16, (0, 0)),
+    (2048, [2048, 1040, 600], 8, 1, 12, (1, 2)), (2049, [2049, 2000], 16, 1, 64, (2, 3)), (4096, [4096, 4095, 3000], 2, 2, 16, (1, 2)),
+    (4097, [4097, 100], 32, 2, 16, (0, 1)), (8192, [8192, 8191, 8176], 32, 2, 16, (1, 2)), (8192, [8192, 5008], 16, 2, 33, (1, 0)),
+    (8193, [8193, 8192, 65], 32, 2, 16, (1, 2)), (16384, [16384, 8208], 4, 1, 64, (0, 0)), (16500, [16448, 16500], 32, 2, 16, (1, 2)),
+    (2048, [33 + 49 * b for b in range(41)], 32, 2, 16, (1, 2)), (8192, [8192 - 176 * b for b in range(20)], 16, 1, 16, (1, 2))])
+def test_decode_step_short_caches(cap, lens, Hq, Hkv, topk, forced):
+    print("case short decode", cap, len(lens), Hq, Hkv, topk, forced, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk, n_init_blocks=forced[0], n_local_blocks=forced[1])
+    oprm = oracle_params(prm)
+    B = len(lens)
+    gen = torch.Generator(device="cuda").manual_seed(cap + B)
+    q = torch.randn((B, 1, Hq, 128), device="cuda", generator=gen).bfloat16()
+    k, v = (torch.randn((B, Hkv, cap, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k[:, :, ::5] += 3 * q.float().mean(2)[:, 0, None, None, :].bfloat16()        # scores well apart
+    sl = dev_i32(lens)
+    at = (torch.tensor(lens, device="cuda") - 1)
+    rows = torch.arange(B, device="cuda")
+    kn, vn = k[rows, :, at][:, :, None].contiguous(), v[rows, :, at][:, :, None].contiguous()
+    ck = binding.compress_keys(prm, k, sl - 1, cap)
+    kc, vc = k.clone(), v.clone()
+    for b, l in enumerate(lens):                            # what this step is about to write: a stale read shows
+        kc[b, :, l - 1], vc[b, :, l - 1] = 90.0, 90.0
+        if l >= 32 and (l - 32) % 16 == 0:
+            ck[b, :, (l - 32) // 16] = 90.0
+    kc2, vc2, ck2 = kc.clone(), vc.clone(), ck.clone()
+    idx, out, lse = binding.decode_step(prm, q, kn, vn, kc, vc, ck, sl, cap)
+    binding.append_kv(prm, kn, vn, kc2, vc2, sl, cap, ck=ck2)
+    idx2 = binding.select_blocks(prm, binding.MODE_DECODE, q, ck2, sl, cap)
+    out2, lse2 = binding.sparse_attn_decode(prm, q, kc2, vc2, sl, cap, idx2)
+    torch.cuda.synchronize()
+    for x, y in ((kc, k), (vc, v), (kc2, k), (ck, ck2), (idx, idx2), (out, out2), (lse, lse2)):
+        assert torch.equal(x, y)
+    for b in sorted(set(range(B)) if B < 5 else {0, 1, B // 2, B - 1}):
+        l = lens[b]
+        pos = np.array([l - 1], np.int32)
+        kb, vb, qb = to_bits(k[b, :, :l]), to_bits(v[b, :, :l]), to_bits(q[b])
+        _, ck_ref = ref.compress_keys(kb, oprm)
+        assert np.array_equal(to_bits(ck[b])[:, :ck_ref.shape[1]], ck_ref), b
+        want, margins, R = ref.select_blocks(qb, ck_ref, pos, oprm, want_scores=True)
+        n, e, nt, hard = compare_selection(idx[b].cpu().numpy(), want, margins, R)
+        assert not hard, (b, hard)
+        wo, wl = ref.sparse_attn(qb, kb, vb, pos, idx[b].cpu().numpy(), oprm)
+        assert out_err(out[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(lse[b].double().cpu().numpy(), wl[0]) <= 1.0
+
+
 @pytest.mark.parametrize("B", [1, 4])
 @pytest.mark.parametrize("rho", [2, 4])
 def test_decode_step_approximate_lse_when_the_new_kernel_feeds_another_workgroup(rho, B):
