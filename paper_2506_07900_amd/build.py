@@ -16,7 +16,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libinfllmv2.so")
 BENCH_LIB = os.path.join(HERE, "libinfllmv2_bench.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
-SOURCES = ["api.hip", "compress_keys.hip", "select_prefill.hip", "select_prefill16.hip", "attn_prefill.hip",
+SOURCES = ["api.hip", "compress_keys.hip", "select_prefill.hip", "select_prefill16.hip", "select_short.hip", "attn_prefill.hip",
            "attn_bwd.hip", "decode.hip", "noalloc.hip"]
 BENCH_SOURCES = SOURCES + ["timing.hip", "probes.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

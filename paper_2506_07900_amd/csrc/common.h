@@ -211,6 +211,52 @@ __device__ inline uint64_t wave_topk(const uint64_t (&el)[NE], int n, uint64_t *
     return res;
 }
 
+// Largest value over a wavefront (uniform).
+__device__ inline uint32_t wave_max_u32(uint32_t x) {
+    auto step = [&](uint32_t y) { x = y > x ? y : x; };
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));   // rotations inside the 16-lane rows
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false));
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false));
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 16);
+    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
+    return max(max(r0, r1), max(r2, r3));
+}
+
+// The n largest of the keys a wavefront holds (kN per lane; 0 = not a candidate, at least n candidates, n >= 1), as bit
+// masks per register; ties go to the lower register, then the lower lane.  top: the largest key.  Bisection on the key:
+// a step is kN vector compares and scalar counting, and it ends early once a threshold splits off exactly n keys.  The
+// first threshold lies a factor of 8 below the largest key, which in practice leaves 2^25 patterns instead of 2^30: about
+// ten steps on scores that differ in the second digit, 32 at most.
+template <int kN>
+__device__ inline void pick_by_bisection(const uint32_t (&key)[kN], uint32_t top, int n, uint64_t (&chosen)[kN]) {
+    uint32_t lo = 1u, hi = top + 1u;                      // count(key >= lo) >= n > count(key >= hi)
+    int n_hi = 0;
+    uint32_t mid = top > (3u << 23) + 1u ? top - (3u << 23) : lo + ((hi - lo) >> 1);
+    for (; hi - lo > 1u; mid = lo + ((hi - lo) >> 1)) {
+        int cnt = 0;
+#pragma unroll
+        for (int s = 0; s < kN; ++s) {
+            chosen[s] = __ballot(key[s] >= mid);
+            cnt += __popcll(chosen[s]);
+        }
+        if (cnt == n) return;
+        if (cnt > n) lo = mid;
+        else {
+            hi = mid;
+            n_hi = cnt;
+        }
+    }
+    int need = n - n_hi;                                  // the keys above lo, and the first `need` of those equal to it
+#pragma unroll
+    for (int s = 0; s < kN; ++s) {
+        const uint64_t eq = __ballot(key[s] == lo);
+        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
+        chosen[s] = __ballot(key[s] > lo || (key[s] == lo && before < need));
+        need -= min(need, (int)__popcll(eq));
+    }
+}
+
 // The row of selected blocks of one query: lane c < n_pick brings a picked candidate block, the forced
 // blocks (the first n_init and lo_local .. b_own) are added, and the n_sel blocks are written in
 // ascending order, padded with -1 up to topk.
@@ -260,6 +306,9 @@ int launch_select_prefill16(const Dims &dm, Tensor q, Tensor ck, const int32_t *
                             int32_t *block_idx, void *ws, hipStream_t stream, float *scores_out = nullptr,
                             int32_t scores_pitch = 0);
 size_t select_prefill16_ws_bytes(const Dims &dm);
+constexpr int kShortPrefill = 8192;                        // tokens: up to 512 semantic kernels (select_short.hip)
+bool select_short_fits(const Dims &dm);
+int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream);
 int32_t select_scores_pitch(const Dims &dm);
 size_t select_scores_bytes(const Dims &dm);
 size_t select_shared_scores_bytes(const Dims &dm);

@@ -539,6 +539,7 @@ static int launch_select_prefill_g(const Dims &dm, Tensor q, Tensor ck, const in
 int launch_select_prefill(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens,
                           int32_t *block_idx, void *ws, hipStream_t stream, float *scores_out,
                           int32_t scores_pitch) {
+    if (!scores_out && select_short_fits(dm)) return launch_select_short(dm, q, ck, seqlens, block_idx, stream);
     switch (dm.G) {
         case 1: return launch_select_prefill_g<1>(dm, q, ck, seqlens, block_idx, ws, stream, scores_out, scores_pitch);
         case 2: return launch_select_prefill_g<2>(dm, q, ck, seqlens, block_idx, ws, stream, scores_out, scores_pitch);

@@ -137,6 +137,48 @@ def test_select_blocks_prefill(seqlens, Hq, Hkv, topk, planted):
     assert near <= max(2, tot // 200)
 
 
+# Up to 8192 tokens the selection is one pass in one kernel: both sides of each of its sizes (32, 64, 128 blocks) for every
+# group size, forced counts including none, batches, tokens that need no scores, few tiles (wavefronts share a tile) and
+# many (wavefronts take several), and the first length of the two-pass kernels.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk,forced", [
+    ([2047, 31], 32, 2, 16, (1, 2)), ([2048], 16, 2, 8, (0, 0)), ([2049, 2048, 1], 4, 1, 16, (1, 2)), ([1100], 2, 2, 6, (0, 1)),
+    ([4096], 2, 1, 16, (2, 1)), ([4097, 100], 32, 2, 8, (0, 0)), ([4095, 3000], 4, 2, 64, (1, 2)), ([3001], 1, 1, 3, (1, 2)),
+    ([8192, 8177, 33], 16, 1, 16, (1, 2)), ([8191], 32, 2, 24, (1, 2)), ([8192], 4, 4, 16, (0, 3)), ([8190, 5000], 2, 2, 16, (1, 0)),
+    ([8193, 64], 32, 2, 16, (1, 2)), ([8193], 4, 1, 8, (0, 0))])
+def test_select_blocks_prefill_short(seqlens, Hq, Hkv, topk, forced):
+    print("case short select", seqlens, Hq, Hkv, topk, forced, flush=True)
+    prm, (q, k, v, T), dev, ck, idx = run_prefill(seqlens, Hq, Hkv, topk, 5, seed=33, forced=forced)
+    oprm = oracle_params(prm)
+    ckb = to_bits(ck)
+    tot = near = 0
+    rng = np.random.default_rng(8)
+    for b, l in enumerate(seqlens):
+        pos = np.array(sorted(set(rng.integers(0, l, 150).tolist()) | set(range(max(0, l - 70), l)) | set(range(min(l, 40)))), np.int32)
+        want, margins, R = ref.select_blocks(q[b, pos], ckb[b, :, :ref.num_kernels(l, 32, 16)], pos, oprm, want_scores=True)
+        got = idx[b][:, torch.from_numpy(pos).long().cuda()].cpu().numpy()
+        n, e, nt, hard = compare_selection(got, want, margins, R)
+        assert not hard, hard[:3]
+        tot, near = tot + n, near + nt
+        assert bool((idx[b, :, l:] == -1).all())
+    print("rows %d near-tie %d" % (tot, near), flush=True)
+    assert near <= max(2, tot // 200)
+
+
+def test_select_blocks_prefill_ties_go_to_the_lower_block():
+    # keys of all zeros: every visible kernel of a row scores the same, the tie rule alone decides (one-pass kernel, more
+    # than 64 candidate blocks)
+    Hq, Hkv, topk, T = 32, 2, 8, 5000
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    q = torch.randn((1, T, Hq, 128), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).bfloat16()
+    ck = torch.zeros((1, Hkv, binding.num_kernels(T, prm), 128), dtype=torch.bfloat16, device="cuda")
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, dev_i32([T]), T)[0].cpu()
+    own = torch.arange(T) // 64
+    for t in list(range(0, T, 37)) + [T - 1]:
+        o = int(own[t])
+        want = list(range(min(o + 1, topk - 2))) + [j for j in (o - 1, o) if j >= min(o + 1, topk - 2)]
+        assert idx[0, t].tolist() == (want + [-1] * topk)[:topk], t
+
+
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([1077, 333], 32, 2, 16), ([700, 65], 4, 1, 6), ([450], 2, 2, 5)])
 def test_block_scores_against_the_oracle(seqlens, Hq, Hkv, topk):
     # the scores the selection ranks (Eq. 1 after the group mean and the max over intersecting kernels),
