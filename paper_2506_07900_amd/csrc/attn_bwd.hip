@@ -11,7 +11,7 @@
 // in registers:
 //   bwd_prep_kernel     D, the exponent offsets -lse log2(e), and the membership bits of every token
 //   pack_bwd_kernel     fragment-major copies of every block: K rows, V rows, K transposed
-//   attn_bwd_dq_kernel  wavefront = 2 tokens, walks the union of their block lists:
+//   attn_bwd_dq_kernel  workgroup = 1 to 4 MFMA tiles of 16 (token, head) columns, walks the union of the tokens' block lists:
 //                       S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T
 //   attn_bwd_dkdv_kernel  wavefront = 32 keys x 64 channels of a block, walks the member tokens of one
 //                       segment in pairs: S = Q.K^T, dP = dO.V^T, dV^T += dO^T.P, dK^T += Q^T.dS
@@ -20,7 +20,7 @@
 //   bwd_finish_kernel   fp32 accumulators -> bf16 dk (times scale), dv
 // As in the forward, every second contraction takes its B operand straight from the accumulator
 // layout of the first, with the contraction index of the A fragments permuted to match.
-#include "common.h"
+#include "token_union.h"
 
 namespace infllmv2 {
 
@@ -32,8 +32,6 @@ constexpr int kBwdBlockU4 = 3 * 16 * 64;              // uint4 per packed block:
 // more workgroups (better balance at 32K tokens), long ones fewer prologues and merges per block
 // (at 128K tokens most (block, segment) units hold a handful of members).
 static inline int bwd_seg_tokens(const Dims &dm) { return dm.max_seqlen > 65536 ? 8192 : 2048; }
-constexpr int kBwdNone = 0x7fffffff;
-constexpr int kBwdBlkBits = 27, kBwdBlkMask = (1 << kBwdBlkBits) - 1;
 
 struct BwdLayout {
     int32_t nb_cap, words;                            // blocks per sequence; bitmap words per block row (multiple of 64)
@@ -185,198 +183,279 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
     }
 }
 
-__device__ inline uint32_t bwd_xcd_contiguous_id(uint32_t bid, uint32_t n) {
-    const uint32_t per = n >> 3, rem = n & 7u, x = bid & 7u, slot = bid >> 3;
-    return x * per + (x < rem ? x : rem) + slot;
-}
-
-// ---- dq: a wavefront owns 2 consecutive tokens of one key-value head ---------------------------------
+// ---- dq: a workgroup owns the tokens of kTiles MFMA tiles of one key-value head ---------------------------
+// As in the forward: the 16 columns of a tile are the G query heads of 16 / G tokens, the union of the tokens' block
+// lists is walked once, every fragment serves every tile with a token that selected the block; the four wavefronts take
+// every fourth block of the union and their sums are added at the end.
 // A block is processed as two halves of 32 keys; per half six units of 4 fragments (4 KiB each) are
-// consumed in this order and rotate through a ring of 4 register buffers (12 units per block):
+// consumed in this order and rotate through a ring of register buffers (12 units per block):
 //   K rows of key tile 2hs, of key tile 2hs+1      -> S^T  = K . Q^T
 //   V rows of key tile 2hs, of key tile 2hs+1      -> dP^T = V . dO^T
 //   K^T of the half for channel tiles 0..3, 4..7   -> dQ^T += K^T . dS^T
-constexpr int kDqTok = 2, kDqRing = 3, kDqUnits = 12;
+// Bound by the L2 -> register path (48 KiB per block and union); with four tiles the queries and upstream gradients sit
+// in LDS and a tile's scores and dP are formed together, which needs four units in registers; with one or two tiles they
+// sit in registers and the units are used one at a time.  Against two whole tokens per wavefront: 32K tokens, G = 16
+// 1590 -> 1360 us; 4096 tokens, two sequences, G = 8 332 -> 173; 8192 tokens, G = 1 (16 tokens a tile) ~480 -> 107.
+constexpr int kDqUnits = 12;
+template <int kG, int kTiles>
+struct DqCfg {
+    static constexpr bool kLds = kTiles > 2;
+    static constexpr int kRing = kLds ? 4 : 3;
+    static constexpr int kTPT = 16 / kG, kTok = kTiles * kTPT;
+    // LDS: union list, then the rows [q | dout][tile][ks][lane] (kLds); the merge area lies over both
+    static size_t lds_bytes(int topk) {
+        const size_t work = UnionLds::bytes(kTok, topk) + (kLds ? (size_t)2 * kTiles * 4 * 64 * sizeof(uint4) : 0);
+        const size_t merge = (size_t)4 * 8 * 64 * sizeof(float4);
+        return work > merge ? work : merge;
+    }
+};
+
+template <int kG, int kTiles>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
                                                               int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                               const int32_t *__restrict__ block_idx,
                                                               const float *__restrict__ lse,
                                                               const float *__restrict__ delta, Tensor dq,
-                                                              int32_t n_tiles) {
-    const uint32_t vid = bwd_xcd_contiguous_id(blockIdx.x, gridDim.x);
-    const int tile = vid % n_tiles;
-    const int h = (vid / n_tiles) % dm.Hkv;
-    const int b = vid / (n_tiles * dm.Hkv);
-    const int L = seq_len(dm, seqlens, b);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = (tile * 4 + wave) * kDqTok;            // this wavefront's first token
-    if (t0 >= L) return;
+                                                              int32_t slots) {
+    using C = DqCfg<kG, kTiles>;
+    constexpr int kRing = C::kRing, kTPT = C::kTPT, kTok = C::kTok;
+    static_assert(64 % kTok == 0 && kTok <= 32, "one own block per workgroup; member bits in one word");
+    extern __shared__ __align__(16) unsigned char dq_smem[];
+    __shared__ int cnt_s;
+    __shared__ float2 row_s[kTiles][16];                  // per column: exponent offset -lse log2(e), D
+    const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
+    const int h = bh % dm.Hkv, b = bh / dm.Hkv;
+    const int L = __builtin_amdgcn_readfirstlane(seq_len(dm, seqlens, b));
+    const int tile = (L + kTok - 1) / kTok - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);   // (see the forward's launch)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = tile * kTok;
+    if (tile < 0 || t0 >= L) return;                      // uniform over the workgroup
     const int b_own = t0 / kBlock;
-    const int n = lane & 15, g = lane >> 4;               // MFMA column (query head) and 16-lane group
-    const int G = dm.G;
+    const int n = lane & 15, g = lane >> 4;               // MFMA column (token, query head) and 16-lane group
+    const int tn = n / kG;
     const float c = dm.scale_log2;
 
-    bf16x8 qf[kDqTok][4], gf[kDqTok][4];
-    f32x4 acc[kDqTok][8];
-    float neg_lse2[kDqTok], dlt[kDqTok];                  // per lane: its head's -lse*log2(e) and D
-    int own[kDqTok];
+    bf16x8 qf[C::kLds ? 1 : kTiles][4], gf[C::kLds ? 1 : kTiles][4];
+    bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + UnionLds::bytes(kTok, dm.topk)) + lane;   // [q | dout][tile][ks][lane]
+    f32x4 acc[kTiles][8];
 #pragma unroll
-    for (int u = 0; u < kDqTok; ++u) {
-        const int tok = t0 + u;
-        const bool live = tok < L && n < G;
-        const int64_t row = (int64_t)(h * G + min(n, G - 1));
-        const int tk = min(tok, L - 1);
+    for (int u = 0; u < kTiles; ++u) {
+        const int tok = t0 + u * kTPT + tn, tk = min(tok, L - 1);
+        const int64_t row = (int64_t)(h * kG + n % kG);
+        if (!C::kLds || wave == u) {
+            const __bf16 *qr = q.ptr + b * q.sb + (int64_t)tk * q.st + row * q.sh + 8 * g;
+            const __bf16 *gr = dout.ptr + b * dout.sb + (int64_t)tk * dout.st + row * dout.sh + 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            qf[u][ks] = load8(q.ptr + b * q.sb + (int64_t)tk * q.st + row * q.sh + 32 * ks + 8 * g);
-            gf[u][ks] = load8(dout.ptr + b * dout.sb + (int64_t)tk * dout.st + row * dout.sh + 32 * ks + 8 * g);
-        }
-        const float ls = lse[((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row];
-        dlt[u] = delta[((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row];
-        // p = 2^(s*c - lse*log2e); a dead column (no such token or head, or a row that attended nothing) gets p = 0
-        neg_lse2[u] = (live && ls > -INFINITY) ? -ls * kLog2e : -INFINITY;
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        int e = kBwdNone;
-        if (tok < L && lane < dm.topk) {
-            const int x = block_idx[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + tok) * dm.topk + lane];
-            if (x >= 0 && x <= b_own) e = x;
-        }
-        own[u] = e;
-    }
-    // ascending union of the two block lists by counting (an entry's place = number of distinct smaller entries)
-    // (a block listed twice in one row, against the contract, counts once: the copy in the higher lane is dropped)
-    int w[kDqTok];
-#pragma unroll
-    for (int u = 0; u < kDqTok; ++u) {
-        bool dup = false;
-        for (int j = 0; j < dm.topk; ++j) dup |= j < lane && __builtin_amdgcn_readlane(own[u], j) == own[u];
-        if (u == 1)
-            for (int j = 0; j < dm.topk; ++j) dup |= __builtin_amdgcn_readlane(own[0], j) == own[1];
-        w[u] = dup ? kBwdNone : own[u];
-    }
-    int rank[kDqTok] = {0, 0}, bits[kDqTok] = {0, 0};
-#pragma unroll
-    for (int u2 = 0; u2 < kDqTok; ++u2)
-        for (int j = 0; j < dm.topk; ++j) {
-            const int wj = __builtin_amdgcn_readlane(w[u2], j), xj = __builtin_amdgcn_readlane(own[u2], j);
-#pragma unroll
-            for (int u = 0; u < kDqTok; ++u) {
-                rank[u] += wj < w[u] ? 1 : 0;
-                bits[u] |= xj == w[u] ? 1 << u2 : 0;
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16x8 xq = load8(qr + 32 * ks), xg = load8(gr + 32 * ks);
+                if constexpr (C::kLds) {
+                    ql[(u * 4 + ks) * 64] = xq;
+                    ql[((kTiles + u) * 4 + ks) * 64] = xg;
+                } else {
+                    qf[u][ks] = xq;
+                    gf[u][ks] = xg;
+                }
             }
         }
-    __shared__ int ulist[4][64 * kDqTok];
-    int cnt = 0;
+        if (wave == u && g == 0) {
+            const int64_t at = ((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row;
+            const float ls = lse[at];
+            // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
+            row_s[u][n] = float2{(tok < L && ls > -INFINITY) ? -ls * kLog2e : -INFINITY, delta[at]};
+        }
 #pragma unroll
-    for (int u = 0; u < kDqTok; ++u) {
-        const bool have = w[u] != kBwdNone;
-        if (have) ulist[wave][rank[u]] = w[u] | (bits[u] << kBwdBlkBits);
-        cnt += __popcll(__ballot(have));
+        for (int dt = 0; dt < 8; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    int ul[kDqTok];
-#pragma unroll
-    for (int r = 0; r < kDqTok; ++r) ul[r] = ulist[wave][64 * r + lane];
-    auto union_entry = [&](int i) __attribute__((always_inline)) {
-        int e = __builtin_amdgcn_readlane(ul[0], i & 63);
-        if ((i >> 6) == 1) e = __builtin_amdgcn_readlane(ul[1], i & 63);
-        return e;
-    };
+    const UnionLds ul(dq_smem);
+    if (wave == 0) {
+        const int x = build_union<kTok>(block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk, dm.topk,
+                                        min(kTok, L - t0), b_own, ul, lane);
+        if (lane == 0) cnt_s = x;
+    }
+    __syncthreads();
+    const int cnt = __builtin_amdgcn_readfirstlane(cnt_s);
+    auto union_entry = [&](int i) __attribute__((always_inline)) { return ul.list[min(i, cnt - 1)]; };
 
-    const u32x4 *kv_lane = reinterpret_cast<const u32x4 *>(kvb) + ((int64_t)b * dm.Hkv + h) * nb_cap * kBwdBlockU4 + lane;
-    u32x4 ring[kDqRing][4];
-    auto issue = [&](int unit, const u32x4 *bp) __attribute__((always_inline)) {
+    // block addresses are uniform: buffer loads, no vector address arithmetic
+    const char *kv_head = reinterpret_cast<const char *>(kvb) + ((int64_t)b * dm.Hkv + h) * nb_cap * (kBwdBlockU4 * 16);
+    const uint32_t lane16 = 16u * lane;
+    u32x4 ring[kRing][4];
+    auto block_rsrc = [&](uint32_t blk) __attribute__((always_inline)) {
+        const int64_t at = (int64_t)(int)__builtin_amdgcn_readfirstlane(blk) * (kBwdBlockU4 * 16);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kv_head) + at, 0, kBwdBlockU4 * 16, 0x00027000);
+    };
+    auto fragment = [&](__amdgpu_buffer_rsrc_t bp, int f) __attribute__((always_inline)) {
+        return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bp, lane16, f * 1024, 0));
+    };
+    auto issue = [&](int unit, __amdgpu_buffer_rsrc_t bp) __attribute__((always_inline)) {
         const int hs = unit / 6, r = unit % 6;
         if (r < 4) {                                      // K rows (section 0) or V rows (section 1), key tile 2hs + r%2
             const int sec = r >> 1, mt = 2 * hs + (r & 1);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) ring[unit % kDqRing][ks] = bp[(sec * 16 + ks * 4 + mt) * 64];
+            for (int ks = 0; ks < 4; ++ks) ring[unit % kRing][ks] = fragment(bp, sec * 16 + ks * 4 + mt);
         } else {                                          // K^T (section 2), channel tiles 4(r-4) .. +3 of half hs
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ring[unit % kDqRing][i] = bp[(32 + (4 * (r - 4) + i) * 2 + hs) * 64];
+            for (int i = 0; i < 4; ++i) ring[unit % kRing][i] = fragment(bp, 32 + (4 * (r - 4) + i) * 2 + hs);
         }
     };
 
     __builtin_amdgcn_s_waitcnt(0);                        // nothing of the prologue may still be pending inside the ring loop
-    if (cnt > 0) {
-        const u32x4 *bp = kv_lane + (int64_t)(union_entry(0) & kBwdBlkMask) * kBwdBlockU4;
+    uint2 e_cur = {0u, 0u}, e_nxt = {0u, 0u};
+    if (wave < cnt) {
+        e_cur = union_entry(wave);
+        e_nxt = union_entry(wave + 4);
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
 #pragma unroll
-        for (int unit = 0; unit < kDqRing; ++unit) issue(unit, bp);
+        for (int unit = 0; unit < kRing; ++unit) issue(unit, bp);
     }
-    for (int ci = 0; ci < cnt; ++ci) {
-        const int e = union_entry(ci);
-        const int blk = e & kBwdBlkMask, mem = e >> kBwdBlkBits;
-        const int en = union_entry(ci + 1 < cnt ? ci + 1 : ci);
-        const u32x4 *bp = kv_lane + (int64_t)blk * kBwdBlockU4;
-        const u32x4 *bn = kv_lane + (int64_t)(en & kBwdBlkMask) * kBwdBlockU4;
+    for (int ci = wave; ci < cnt; ci += 4) {
+        const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
+        const uint32_t bits = __builtin_amdgcn_readfirstlane(e_cur.y);
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x), bn = block_rsrc(e_nxt.x);
+        e_cur = e_nxt;
+        e_nxt = union_entry(ci + 8);
         const int key0 = blk * kBlock;
         const bool edge = blk == b_own;
+        uint32_t tb[kTiles];                              // member bits of the tile's tokens
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) tb[u] = (bits >> (u * kTPT)) & ((1u << kTPT) - 1u);
         auto refill = [&](int unit) __attribute__((always_inline)) {
-            if (unit + kDqRing < kDqUnits) issue(unit + kDqRing, bp);
-            else issue(unit + kDqRing - kDqUnits, bn);    // (a harmless re-read of this block at the tail)
+            if (unit + kRing < kDqUnits) issue(unit + kRing, bp);
+            else issue(unit + kRing - kDqUnits, bn);      // (a harmless re-read of this block at the tail)
+        };
+        auto product = [&](int unit, const bf16x8 (&x)[4]) __attribute__((always_inline)) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a = mfma16(__builtin_bit_cast(bf16x8, ring[unit % kRing][ks]), x[ks], a);
+            return a;
+        };
+        auto grad = [&](int u, int hs, const f32x4 (&s)[2], const f32x4 (&dp)[2], bf16x8 &dsf) __attribute__((always_inline)) {
+            const float2 r = row_s[u][n];
+            const float ne = (kTPT == 1 || ((tb[u] >> tn) & 1u)) ? r.x : -INFINITY;
+            const int tok = t0 + u * kTPT + tn;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float p = fast_exp2(__builtin_fmaf(s[t][j], c, ne));
+                    if (edge && key0 + 32 * hs + 16 * t + 4 * g + j > tok) p = 0.f;
+                    dsf[4 * t + j] = (__bf16)(p * (dp[t][j] - r.y));
+                }
         };
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
-            f32x4 s[kDqTok][2], dp[kDqTok][2];
+            bf16x8 dsf[kTiles];
+            if constexpr (C::kLds) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int unit = 6 * hs + r;
+                for (int u = 0; u < kTiles; ++u) {
+                    if (!tb[u]) continue;
+                    f32x4 s[2], dp[2];
+                    bf16x8 x[4];
 #pragma unroll
-                for (int u = 0; u < kDqTok; ++u) {
-                    if (!((mem >> u) & 1)) continue;
-                    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+                    for (int ks = 0; ks < 4; ++ks) x[ks] = ql[(u * 4 + ks) * 64];
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        a = mfma16(__builtin_bit_cast(bf16x8, ring[unit % kDqRing][ks]), r < 2 ? qf[u][ks] : gf[u][ks], a);
-                    if (r < 2) s[u][r] = a;
-                    else dp[u][r - 2] = a;
+                    for (int r = 0; r < 2; ++r) s[r] = product(6 * hs + r, x);
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) x[ks] = ql[((kTiles + u) * 4 + ks) * 64];
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) dp[r] = product(6 * hs + 2 + r, x);
+                    grad(u, hs, s, dp, dsf[u]);
                 }
-                refill(unit);
-            }
-            bf16x8 dsf[kDqTok];
 #pragma unroll
-            for (int u = 0; u < kDqTok; ++u) {
-                if (!((mem >> u) & 1)) continue;
-                const int tok = t0 + u;
+                for (int r = 0; r < 4; ++r) refill(6 * hs + r);
+            } else {
+                f32x4 s[kTiles][2], dp[kTiles][2];
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int r = 0; r < 4; ++r) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        float p = fast_exp2(__builtin_fmaf(s[u][t][j], c, neg_lse2[u]));
-                        if (edge && key0 + 32 * hs + 16 * t + 4 * g + j > tok) p = 0.f;
-                        dsf[u][4 * t + j] = (__bf16)(p * (dp[u][t][j] - dlt[u]));
+                    for (int u = 0; u < kTiles; ++u) {
+                        if (!tb[u]) continue;
+                        if (r < 2) s[u][r] = product(6 * hs + r, qf[u]);
+                        else dp[u][r - 2] = product(6 * hs + r, gf[u]);
                     }
+                    refill(6 * hs + r);
+                }
+#pragma unroll
+                for (int u = 0; u < kTiles; ++u)
+                    if (tb[u]) grad(u, hs, s[u], dp[u], dsf[u]);
             }
 #pragma unroll
             for (int r = 4; r < 6; ++r) {
                 const int unit = 6 * hs + r;
 #pragma unroll
-                for (int u = 0; u < kDqTok; ++u) {
-                    if (!((mem >> u) & 1)) continue;
+                for (int u = 0; u < kTiles; ++u) {
+                    if (!tb[u]) continue;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         acc[u][4 * (r - 4) + i] =
-                            mfma16(__builtin_bit_cast(bf16x8, ring[unit % kDqRing][i]), dsf[u], acc[u][4 * (r - 4) + i]);
+                            mfma16(__builtin_bit_cast(bf16x8, ring[unit % kRing][i]), dsf[u], acc[u][4 * (r - 4) + i]);
                 }
                 refill(unit);
             }
         }
     }
-    // ---- write: lane holds channels 16*dt + 4*g .. +3 of head n ------------------------------------------
+    // ---- add the four wavefronts' sums, a tile at a time, and write: lane holds channels 16*dt + 4*g .. +3 of column n ----
     const float scale = c * kLn2;
+    float4 *po = reinterpret_cast<float4 *>(dq_smem);     // [wave][dt][lane]
 #pragma unroll
-    for (int u = 0; u < kDqTok; ++u) {
-        const int tok = t0 + u;
-        if (tok >= L || n >= G) continue;
-        __bf16 *op = dq.ptr + b * dq.sb + (int64_t)tok * dq.st + (int64_t)(h * G + n) * dq.sh + 4 * g;
+    for (int u = 0; u < kTiles; ++u) {
+        __syncthreads();
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-            bf16x4 r;
+        for (int dt = 0; dt < 8; ++dt)
+            po[(wave * 8 + dt) * 64 + lane] = float4{acc[u][dt][0], acc[u][dt][1], acc[u][dt][2], acc[u][dt][3]};
+        __syncthreads();
+        const int tok = t0 + u * kTPT + tn;
+        if (tok < L) {
+            __bf16 *op = dq.ptr + b * dq.sb + (int64_t)tok * dq.st + (int64_t)(h * kG + n % kG) * dq.sh + 4 * g;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) r[j] = (__bf16)(acc[u][dt][j] * scale);
-            *reinterpret_cast<uint2 *>(op + 16 * dt) = __builtin_bit_cast(uint2, r);
+            for (int i = 0; i < 2; ++i) {
+                const int dt = 2 * wave + i;
+                f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float4 y = po[(w * 8 + dt) * 64 + lane];
+                    x += f32x4{y.x, y.y, y.z, y.w};
+                }
+                bf16x4 r;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) r[j] = (__bf16)(x[j] * scale);
+                *reinterpret_cast<uint2 *>(op + 16 * dt) = __builtin_bit_cast(uint2, r);
+            }
         }
     }
+}
+
+template <int kG, int kTiles>
+static int launch_dq_variant(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
+                             const int32_t *block_idx, const float *lse, const float *delta, Tensor dq, hipStream_t stream) {
+    using C = DqCfg<kG, kTiles>;
+    const int32_t n_tiles = (dm.max_seqlen + C::kTok - 1) / C::kTok;
+    const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
+    const size_t lds = C::lds_bytes(dm.topk);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<kG, kTiles>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return (int)e;
+    }
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<kG, kTiles>), dim3((uint32_t)((int64_t)slots * 8 * dm.Hkv * dm.batch)), dim3(256), lds,
+                       stream, dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, slots);
+    return 0;
+}
+
+// Tiles per workgroup, by (token, key-value head) rows: four as soon as that still gives every CU its two workgroups
+// (the more tokens share a walk, the fewer bytes per token), two while that gives at least three workgroups to four CUs, else
+// one.  Past those lines the fewer, longer workgroups lose more to an idle chip than the walk saves (1000 tokens, G = 4:
+// 13 / 16 / 27 us with 1 / 2 / 4; 8192 x 2, G = 1: 123 / 107 with 1 / 2; 4096 x 2 x 2, G = 8: 258 / 189 / 173).  A tile of
+// G = 1 is 16 tokens and four would not fit the 32 member bits.
+template <int kG>
+static int launch_dq_group(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
+                           const int32_t *block_idx, const float *lse, const float *delta, Tensor dq, hipStream_t stream) {
+    const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
+    constexpr int kTPT = 16 / kG;
+    if constexpr (kG > 1)
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
+    return launch_dq_variant<kG, 1>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
 }
 
 // ---- dk, dv of one block from the tokens that selected it ------------------------------------------------------
@@ -697,10 +776,16 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,
                        l.nb_cap);
     timing_end(stream);
-    const int32_t n_tiles = (T + 4 * kDqTok - 1) / (4 * kDqTok);
     timing_begin("attn_bwd_dq_kernel", stream);
-    hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3((uint32_t)((int64_t)n_tiles * dm.Hkv * dm.batch)), dim3(256), 0, stream,
-                       dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, n_tiles);
+    int err = (int)hipErrorInvalidValue;
+    switch (dm.G) {
+        case 1: err = launch_dq_group<1>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+        case 2: err = launch_dq_group<2>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+        case 4: err = launch_dq_group<4>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+        case 8: err = launch_dq_group<8>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+        case 16: err = launch_dq_group<16>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+    }
+    if (err) return err;
     timing_end(stream);
     timing_begin("attn_bwd_dkdv_kernel", stream);
     if (bwd_seg_tokens(dm) == 8192)

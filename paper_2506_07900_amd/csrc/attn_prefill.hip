@@ -135,8 +135,6 @@ __device__ __forceinline__ float half_probs(const f32x4 (&s)[2], float c, float 
     return sum;
 }
 
-constexpr int kRun = 4;                                  // tiles of a sequence that go to one XCD together
-
 template <int kG, int kTiles, int kSplit>
 struct AttnCfg {
     static constexpr bool kQLds = kTiles > 2;             // queries in LDS: registers hold the accumulators of four tiles

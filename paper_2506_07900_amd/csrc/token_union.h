@@ -6,6 +6,8 @@
 
 namespace infllmv2 {
 
+constexpr int kRun = 4;                                  // tiles of a sequence that go to one XCD together
+
 // Inclusive prefix sum over the 64 lanes (row shifts, then the row totals broadcast: no LDS round trips).
 __device__ inline int wave_inclusive_sum(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);

@@ -830,6 +830,43 @@ def test_sparse_attn_backward(seqlens, Hq, Hkv, topk, planted):
         assert eq <= 1.0 and ek <= 1.0 and ev <= 1.0
 
 
+# Lists in no particular order with holes, most with the first block: each side of the lines of the backward's dispatch (tiles per workgroup by
+# tokens x key-value heads), per group size.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [
+    ([383], 16, 1, 16), ([385], 16, 1, 8), ([1025, 3], 32, 2, 16), ([770, 65], 8, 1, 16), ([2050], 16, 2, 24), ([1537], 4, 1, 64),
+    ([4100], 8, 2, 8), ([3080, 31], 2, 1, 16), ([8200], 4, 2, 5), ([3080, 1], 2, 2, 33)])
+def test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk):
+    print("case attn backward dispatch", seqlens, Hq, Hkv, topk, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    oprm = oracle_params(prm)
+    gen = torch.Generator(device="cuda").manual_seed(78)
+    B, T = len(seqlens), max(seqlens)
+    q, do = (torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    own = (torch.arange(T, device="cuda") // 64)[None, None, :, None]
+    i = torch.arange(topk, device="cuda")[None, None, None, :]
+    shift = torch.randint(0, 3, (B, Hkv, T, 1), device="cuda", generator=gen) * 3
+    idx = (own + 1 - 7 * i - torch.where(i % 4 == 3, shift, torch.zeros_like(shift)))
+    idx = torch.where((i % 5 == 4) | (idx < 0), torch.full_like(idx, -1), torch.where(i == 0, own.expand_as(idx), idx))
+    idx = torch.where((own > 0) & (idx <= 0), torch.where((i == topk - 1).expand_as(idx), torch.zeros_like(idx), torch.full_like(idx, -1)), idx)
+    idx = idx.flip(-1).to(torch.int32).contiguous()
+    sl = dev_i32(seqlens)
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    dq, dk, dv = torch.full_like(q, 3.0), torch.full_like(k, 3.0), torch.full_like(v, 3.0)
+    binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, sl, T, idx, dq=dq, dk=dk, dv=dv)
+    torch.cuda.synchronize()
+    for b, l in enumerate(seqlens):
+        pos = np.arange(l, dtype=np.int32)
+        wq, wk, wv, mq, mk, mv = ref.sparse_attn_bwd(to_bits(q[b, :l]), to_bits(k[b, :, :l]), to_bits(v[b, :, :l]), to_bits(do[b, :l]),
+                                                     pos, idx[b, :, :l].cpu().numpy(), oprm, want_mag=True)
+        eq = grad_err(dq[b, :l].double().cpu().numpy(), wq, mq)
+        ek = grad_err(dk[b, :, :l].double().cpu().numpy(), wk, mk)
+        ev = grad_err(dv[b, :, :l].double().cpu().numpy(), wv, mv)
+        print("seq %d len %d: err/tol dq %.3f dk %.3f dv %.3f" % (b, l, eq, ek, ev), flush=True)
+        assert eq <= 1.0 and ek <= 1.0 and ev <= 1.0
+        assert bool((dq[b, l:] == 3.0).all()) and bool((dk[b, :, l:] == 3.0).all()) and bool((dv[b, :, l:] == 3.0).all())
+
+
 def test_sparse_attn_backward_long_capacity():
     # buffers sized for more than 65536 tokens make the dk/dv kernel work on 8192-token segments
     # (2048 below that); a sequence that crosses a segment boundary and one that does not, the rest
