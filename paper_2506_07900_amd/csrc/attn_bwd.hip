@@ -7,53 +7,72 @@
 //
 // Per-token block sets make dq a gather (a token walks its blocks, like the forward) and dk/dv a
 // scatter (a block collects from every token that selected it).  The scatter is turned around with
-// a membership bitmap (block x token) built from the block lists, so both big kernels accumulate
+// membership words (word of 32 tokens x block) built from the block lists, so both big kernels accumulate
 // in registers:
-//   bwd_prep_kernel     D, the exponent offsets -lse log2(e), and the membership bits of every token
-//   pack_bwd_kernel     fragment-major copies of every block: K rows, V rows, K transposed
+//   pack_bwd_kernel     fragment-major copies of every block (K rows, V rows), its tokens' membership bits, its cleared sums
+//   bwd_items_kernel    the members of every block, cut into work items, queued per XCD
 //   attn_bwd_dq_kernel  workgroup = 1 to 4 MFMA tiles of 16 (token, head) columns, walks the union of the tokens' block lists:
-//                       S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T
-//   attn_bwd_dkdv_kernel  wavefront = 32 keys x 64 channels of a block, walks the member tokens of one
-//                       segment in pairs: S = Q.K^T, dP = dO.V^T, dV^T += dO^T.P, dK^T += Q^T.dS
+//                       D, then S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T
+//   attn_bwd_dkdv_kernel  workgroup = one item of a block after the other, wavefront = 32 keys x 128 channels:
+//                       S = Q.K^T, dP = dO.V^T, dV += P^T.dO, dK += dS^T.Q over steps of 32 (token, head) rows
 //                       (32x32x16 MFMAs; q and dout rows copied from memory straight into LDS);
-//                       fp32 atomics merge the segments
+//                       fp32 atomics add up the items of a block
 //   bwd_finish_kernel   fp32 accumulators -> bf16 dk (times scale), dv
-// As in the forward, every second contraction takes its B operand straight from the accumulator
-// layout of the first, with the contraction index of the A fragments permuted to match.
+// As in the forward, every second contraction takes an operand straight from the accumulator
+// layout of the first, with the contraction index of the other operand permuted to match.
 #include "token_union.h"
+#include <type_traits>
 
 namespace infllmv2 {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBwdBlockU4 = 3 * 16 * 64;              // uint4 per packed block: K rows, V rows, K^T (48 KiB)
-// Member tokens of one dk/dv workgroup come from one segment of the sequence.  Short segments give
-// more workgroups (better balance at 32K tokens), long ones fewer prologues and merges per block
-// (at 128K tokens most (block, segment) units hold a handful of members).
-static inline int bwd_seg_tokens(const Dims &dm) { return dm.max_seqlen > 65536 ? 8192 : 2048; }
+constexpr int kBwdBlockU4 = 2 * 16 * 64;              // uint4 per packed block: K rows, V rows (32 KiB)
+// The scatter's work items (see bwd_items_kernel): a block with the tokens of at most kSegWords words of 32 tokens.
+constexpr int kSegWords = 64;
+constexpr int kQueues = 8;                            // one per XCD
+constexpr int kQueueStride = 64;                      // words between two queues' counters: {length, ..., head, ...} on lines of their own
+
+// Members of an item, in steps of 32 (token, head) rows: an equal share for each of the chip's kDkdvGroups workgroups, within
+// 12 .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us
+// with at least 8 / 16 / 32 steps; 1000 tokens, G = 4 would take 31 / 43 / 62); above, the last items keep the others
+// waiting (32K tokens, G = 16: 1190 / 1310 us with at most 64 / 256).
+constexpr int kDkdvGroups = 256 * 4;
+constexpr int kMaxMembers = 1024;
+static inline int32_t bwd_item_members(const Dims &dm) {
+    const int64_t all = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv * dm.topk;
+    const int64_t steps = all * dm.G / 32 / kDkdvGroups;             // of 32 rows
+    const int64_t m = (steps < 12 ? 12 : steps > 64 ? 64 : steps) * 32 / dm.G;
+    return (int32_t)(m > kMaxMembers ? kMaxMembers : m);
+}
 
 struct BwdLayout {
-    int32_t nb_cap, words;                            // blocks per sequence; bitmap words per block row (multiple of 64)
-    size_t kvb, delta, rowc, bitmap, acc_dk, acc_dv, total; // byte offsets into the workspace
-    size_t zero_begin, zero_bytes;                    // the part that has to start at zero (bitmap and accumulators)
+    int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
+    int32_t members, item_cap;                        // most members of an item (unless one word has more); items per queue
+    size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
 static inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 static BwdLayout bwd_layout(const Dims &dm) {
     BwdLayout l;
     const size_t T = (size_t)dm.max_seqlen, BH = (size_t)dm.batch * dm.Hkv;
     l.nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
-    const int seg_tokens = bwd_seg_tokens(dm);
-    l.words = ((dm.max_seqlen + seg_tokens - 1) / seg_tokens) * (seg_tokens / 32);
+    l.words = 2 * l.nb_cap;
+    l.n_seg = (l.words + kSegWords - 1) / kSegWords;
+    l.members = bwd_item_members(dm);
+    // a segment's items: one per block with a member and one more for the own tokens, and two neighbours of one block together
+    // exceed `members`
+    const size_t ent = (size_t)kSegWords * 32 * dm.topk;
+    const size_t per_seg = (ent < (size_t)l.nb_cap ? ent : (size_t)l.nb_cap) + 2 * ent / l.members + kSegWords / 2 + 1;
+    l.item_cap = (int32_t)((BH * l.n_seg + kQueues - 1) / kQueues * per_seg);
     size_t o = 0;
-    l.kvb = o;    o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
-    l.delta = o;  o += al256((size_t)dm.batch * T * dm.Hq * sizeof(float));
-    l.rowc = o;   o += al256((size_t)dm.batch * T * dm.Hkv * 32 * sizeof(float));
-    l.zero_begin = o;
-    l.bitmap = o; o += al256(BH * l.nb_cap * l.words * sizeof(uint32_t));
-    l.acc_dk = o; o += al256(BH * T * kHeadDim * sizeof(float));
-    l.acc_dv = o; o += al256(BH * T * kHeadDim * sizeof(float));
-    l.zero_bytes = o - l.zero_begin;
+    l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
+    l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
+    l.bits = o;     o += al256(BH * l.words * l.nb_cap * sizeof(uint32_t));
+    l.acc_dk = o;   o += al256(BH * T * kHeadDim * sizeof(float));
+    l.acc_dv = o;   o += al256(BH * T * kHeadDim * sizeof(float));
+    l.counters = o; o += al256((size_t)kQueues * kQueueStride * sizeof(uint32_t));
+    l.items = o;    o += al256((size_t)kQueues * l.item_cap * sizeof(uint4));
     l.total = o;
     return l;
 }
@@ -65,83 +84,26 @@ __device__ inline int seq_len(const Dims &dm, const int32_t *__restrict__ seqlen
     return L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
 }
 
-__global__ __launch_bounds__(256) void bwd_zero_kernel(uint4 *__restrict__ p, size_t n) {
-    const uint4 z = {0u, 0u, 0u, 0u};
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = z;
-}
-
-// ---- per token: D and membership bits -----------------------------------------------------------------
-// grid (ceil(T/4), Hkv, B); wave w handles token 4*bx + w for key-value head h.
-__global__ __launch_bounds__(256) void bwd_prep_kernel(Dims dm, Tensor out, Tensor dout,
-                                                        const int32_t *__restrict__ seqlens,
-                                                        const int32_t *__restrict__ block_idx,
-                                                        const float *__restrict__ lse, float *__restrict__ delta,
-                                                        float *__restrict__ rowc, uint32_t *__restrict__ bitmap,
-                                                        int32_t nb_cap, int32_t words, Tensor dq) {
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int tok = blockIdx.x * 4 + wave;
-    const int L = seq_len(dm, seqlens, b);
-    const int G = dm.G;
-    if (tok >= L) {
-        if (dm.fill && tok < dm.max_seqlen)
-            for (int i = lane; i < G * 16; i += 64)
-                *reinterpret_cast<uint4 *>(dq.ptr + b * dq.sb + (int64_t)tok * dq.st + (int64_t)(h * G + (i >> 4)) * dq.sh +
-                                           8 * (i & 15)) = uint4{0u, 0u, 0u, 0u};
-        return;
-    }
-    const int row = lane >> 2, quarter = lane & 3;        // head of the group, 32 channels
-    const int64_t ooff = b * out.sb + (int64_t)tok * out.st + (int64_t)(h * G + min(row, G - 1)) * out.sh + 32 * quarter;
-    const int64_t goff = b * dout.sb + (int64_t)tok * dout.st + (int64_t)(h * G + min(row, G - 1)) * dout.sh + 32 * quarter;
-    uint4 xo[4], xg[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        xo[i] = *reinterpret_cast<const uint4 *>(out.ptr + ooff + 8 * i);
-        xg[i] = *reinterpret_cast<const uint4 *>(dout.ptr + goff + 8 * i);
-    }
-    int blk = -1;
-    if (lane < dm.topk) blk = block_idx[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + tok) * dm.topk + lane];
-    float dsum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const bf16x8 o8 = __builtin_bit_cast(bf16x8, xo[i]), g8 = __builtin_bit_cast(bf16x8, xg[i]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dsum += (float)o8[e] * (float)g8[e];
-    }
-    dsum += __shfl_xor(dsum, 1);
-    dsum += __shfl_xor(dsum, 2);
-    if (quarter == 0 && row < G) delta[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * G + row] = dsum;
-    // the same per (token, key-value head) as one 128-byte record for the dk/dv kernel: the exponent offsets
-    // -lse log2(e) of the 16 head slots (-inf for slots past the group and for rows without a finite lse, whose
-    // probabilities are then zero), then D
-    if (quarter == 0) {
-        float *rec = rowc + (((int64_t)b * dm.max_seqlen + tok) * dm.Hkv + h) * 32;
-        float ne = -INFINITY;
-        if (row < G) {
-            const float ls = lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * G + row];
-            if (ls > -INFINITY && ls < INFINITY) ne = -ls * kLog2e;
-        }
-        rec[row] = ne;
-        rec[16 + row] = row < G ? dsum : 0.f;
-    }
-    if (blk >= 0 && blk <= tok / kBlock)
-        atomicOr(&bitmap[(((int64_t)b * dm.Hkv + h) * nb_cap + blk) * words + (tok >> 5)], 1u << (tok & 31));
-}
-
-// ---- re-layout of one 64-token block per workgroup ---------------------------------------------------
+// ---- everything per 64-token block, one workgroup each: its fragments, the membership bits of its tokens, its cleared
+// accumulators (the memory is touched anyway and a launch is saved) --------------------------------------------------
 // section 0, K rows:  fragment (ks, mt), lane (g, m):  K[64j + 16mt + m][32ks + 8g .. +7]
 // section 1, V rows:  the same of V
-// section 2, K^T:     fragment (dt, kk), lane (g, m), element e:
-//                     K[64j + 32kk + (e<4 ? 4g+e : 16+4g+e-4)][16dt + m]
 __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor v,
                                                         const int32_t *__restrict__ seqlens,
-                                                        uint4 *__restrict__ kvb, int32_t nb_cap) {
+                                                        uint4 *__restrict__ kvb, int32_t nb_cap,
+                                                        const int32_t *__restrict__ block_idx, uint32_t *__restrict__ bits,
+                                                        float *__restrict__ acc_dk, float *__restrict__ acc_dv,
+                                                        uint32_t *__restrict__ counters, float *__restrict__ null_row) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int L = seq_len(dm, seqlens, b);
-    if (j * kBlock >= L) return;
     const int tid = threadIdx.x;
+    if ((j | h | b) == 0) {
+        for (int i = tid; i < kQueues * kQueueStride; i += 256) counters[i] = 0u;
+        if (tid < 32) null_row[tid] = tid < 16 ? -INFINITY : 0.f;       // the constants of a row that is not there: p = 0
+    }
+    if (j * kBlock >= L) return;
     const int sc = tid & 15, sr = tid >> 4;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
     const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
@@ -166,59 +128,141 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
         dst[c] = *reinterpret_cast<const uint4 *>(&Ks[(16 * mt + m) * 136 + 32 * ks + 8 * g]);
         dst[1024 + c] = *reinterpret_cast<const uint4 *>(&Vs[(16 * mt + m) * 136 + 32 * ks + 8 * g]);
     }
-    const uint16_t *Ku = reinterpret_cast<const uint16_t *>(Ks);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + 256 * i;
-        const int f = c >> 6, lane = c & 63, m = lane & 15, g = lane >> 4;
-        const int dt = f >> 1, kk = f & 1;
-        uint32_t w[4];
-#pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-            const int e = 2 * e2;                        // elements e, e+1 are consecutive keys
-            const int key = 32 * kk + (e < 4 ? 4 * g + e : 16 + 4 * g + e - 4);
-            w[e2] = (uint32_t)Ku[key * 136 + 16 * dt + m] | ((uint32_t)Ku[(key + 1) * 136 + 16 * dt + m] << 16);
-        }
-        dst[2048 + c] = uint4{w[0], w[1], w[2], w[3]};
+    const int64_t bh = (int64_t)b * dm.Hkv + h;
+    const int n_tok = min(kBlock, L - j * kBlock);
+    const int64_t a0 = (bh * dm.max_seqlen + (int64_t)j * kBlock) * kHeadDim;
+    for (int i = tid; i < n_tok * (kHeadDim / 4); i += 256) {
+        *reinterpret_cast<float4 *>(acc_dk + a0 + 4 * i) = float4{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<float4 *>(acc_dv + a0 + 4 * i) = float4{0.f, 0.f, 0.f, 0.f};
     }
+    // membership: bit t % 32 of word [t / 32][block] = token t selected the block (blocks 0 .. j, 2048 at a time)
+    uint32_t *w = reinterpret_cast<uint32_t *>(Ks);
+    static_assert(2 * 2048 * sizeof(uint32_t) <= sizeof(Ks), "two words of 2048 blocks");
+    const int32_t *rows = block_idx + (bh * dm.max_seqlen + (int64_t)j * kBlock) * dm.topk;
+    for (int base = 0; base <= j; base += 2048) {
+        const int n = min(2048, j + 1 - base);
+        __syncthreads();
+        for (int i = tid; i < n; i += 256) w[i] = w[2048 + i] = 0u;
+        __syncthreads();
+        for (int e = tid; e < n_tok * dm.topk; e += 256) {
+            const uint32_t r = (uint32_t)(rows[e] - base);
+            const int tok = e / dm.topk;
+            if (r < (uint32_t)n) atomicOr(&w[2048 * (tok >> 5) + r], 1u << (tok & 31));
+        }
+        __syncthreads();
+        uint32_t *o = bits + (bh * 2 * nb_cap + 2 * j) * nb_cap + base;
+        for (int i = tid; i < n; i += 256) {
+            o[i] = w[i];
+            o[nb_cap + i] = w[2048 + i];
+        }
+    }
+}
+
+// ---- the scatter's work items --------------------------------------------------------------------------------------
+// A thread per (segment, block): the block's members in the segment, cut at word borders into items of about `members`
+// tokens (those inside the block itself, which alone meet the causal edge, apart from the others); item = {sequence and head, block, first word, words | members << 16}.  The items of a segment go to one XCD's queue, so
+// that the q and dout rows that its blocks share are fetched into one L2.
+__global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
+                                                         int32_t nb_cap, int32_t n_seg, int32_t members, uint32_t *__restrict__ counters,
+                                                         uint4 *__restrict__ items, int32_t item_cap) {
+    const int seg = blockIdx.x % n_seg, j = (int)(blockIdx.x / n_seg) * 256 + threadIdx.x;
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int64_t bh = (int64_t)b * dm.Hkv + h;
+    const int L = seq_len(dm, seqlens, b);
+    const int w0 = seg * kSegWords, w1 = min(w0 + kSegWords, (L + 31) / 32);   // block j's tokens start at word 2j
+    if (w0 >= w1 || 2 * (int)(blockIdx.x / n_seg) * 256 >= w1) return;         // uniform
+    const uint32_t *src = bits + bh * 2 * nb_cap * nb_cap + min(j, nb_cap - 1);
+    uint32_t count[kSegWords / 4];                       // members per word, a byte each
+#pragma unroll
+    for (int i = 0; i < kSegWords / 4; ++i) {
+        count[i] = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int w = w0 + 4 * i + e;
+            const uint32_t x = src[(int64_t)min(w, w1 - 1) * nb_cap];
+            count[i] |= (w < w1 && w >= 2 * j ? (uint32_t)__popc(x) : 0u) << (8 * e);
+        }
+    }
+    auto cut = [&](auto emit) __attribute__((always_inline)) {
+        uint32_t sum = 0;
+        int first = 0, last = 0;
+#pragma unroll
+        for (int i = 0; i < kSegWords; ++i) {
+            const uint32_t x = (count[i / 4] >> (8 * (i % 4))) & 255u;
+            if (sum && (sum + x > (uint32_t)members || w0 + i == 2 * j + 2)) {
+                emit(first, last, sum);
+                sum = 0;
+            }
+            if (x) {
+                if (!sum) first = i;
+                last = i;
+                sum += x;
+            }
+        }
+        if (sum) emit(first, last, sum);
+    };
+    int n = 0;
+    cut([&](int, int, uint32_t) { ++n; });
+    const int incl = wave_inclusive_sum(n), all = __builtin_amdgcn_readlane(incl, 63);
+    if (all == 0) return;
+    const int q = (int)((bh * n_seg + seg) % kQueues);
+    int at = 0;
+    if ((threadIdx.x & 63) == 0) at = (int)atomicAdd(&counters[q * kQueueStride], (uint32_t)all);
+    at = __builtin_amdgcn_readfirstlane(at) + incl - n;
+    uint4 *dst = items + (int64_t)q * item_cap;
+    cut([&](int first, int last, uint32_t sum) {
+        dst[at++] = uint4{(uint32_t)bh, (uint32_t)j, (uint32_t)(w0 + first), (uint32_t)(last - first + 1) | (sum << 16)};
+    });
+}
+
+// Rows of 128 channels in LDS: a row's sixteen 16-byte pieces are stored XOR-swizzled with the row's two bit pairs exchanged.  An
+// operand load takes one piece from each of 16 or 32 rows, a transposing load 32 bytes from each of 4 consecutive rows, and
+// both then touch every bank once.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int bwd_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// 4 rows x 16 channels per 16-lane group, transposed: lane i of the group gets channel i of the four rows its
+// group addressed (source lane s: row s/4, channels 4(s%4) .. +3)
+__device__ __forceinline__ s16x4 lds_read_tr16(const char *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
 }
 
 // ---- dq: a workgroup owns the tokens of kTiles MFMA tiles of one key-value head ---------------------------
 // As in the forward: the 16 columns of a tile are the G query heads of 16 / G tokens, the union of the tokens' block
 // lists is walked once, every fragment serves every tile with a token that selected the block; the four wavefronts take
 // every fourth block of the union and their sums are added at the end.
-// A block is processed as two halves of 32 keys; per half six units of 4 fragments (4 KiB each) are
-// consumed in this order and rotate through a ring of register buffers (12 units per block):
+// A block is processed as two halves of 32 keys; per half four units of 4 fragments (4 KiB each) rotate through a ring
+// of register buffers (8 units per block):
 //   K rows of key tile 2hs, of key tile 2hs+1      -> S^T  = K . Q^T
 //   V rows of key tile 2hs, of key tile 2hs+1      -> dP^T = V . dO^T
-//   K^T of the half for channel tiles 0..3, 4..7   -> dQ^T += K^T . dS^T
-// Bound by the L2 -> register path (48 KiB per block and union); with four tiles the queries and upstream gradients sit
-// in LDS and a tile's scores and dP are formed together, which needs four units in registers; with one or two tiles they
-// sit in registers and the units are used one at a time.  Against two whole tokens per wavefront: 32K tokens, G = 16
-// 1590 -> 1360 us; 4096 tokens, two sequences, G = 8 332 -> 173; 8192 tokens, G = 1 (16 tokens a tile) ~480 -> 107.
-constexpr int kDqUnits = 12;
+// and the K rows also go to 8 KiB of LDS, from which the transposing load makes the A fragments of dQ^T += K^T . dS^T.
+// No single bound at 32K tokens, G = 16: matrix cores 30 %, vector issue 43 %, L2 -> register 32 KiB per block and
+// union, 35 % of the wavefronts' time in waits.  With several tiles the queries and upstream gradients sit in LDS and a
+// tile's scores and dP are formed together; with one tile they sit in registers and the units are used one at a time.
+// Against two whole tokens per wavefront: 2 x 4096 tokens, G = 8 332 -> 171; 8192 tokens, G = 1 (16 tokens a tile) ~480 -> 96; 32K
+// tokens, G = 16 1590 -> 1350 (1415 with a third, transposed copy of K read from memory in place of the LDS turn), D included.
+constexpr int kDqUnits = 8, kDqRing = 4;
 template <int kG, int kTiles>
 struct DqCfg {
-    static constexpr bool kLds = kTiles > 2;
-    static constexpr int kRing = kLds ? 4 : 3;
+    static constexpr bool kLds = kTiles > 1;
     static constexpr int kTPT = 16 / kG, kTok = kTiles * kTPT;
-    // LDS: union list, then the rows [q | dout][tile][ks][lane] (kLds); the merge area lies over both
+    // LDS: union list, each wave's 32 K rows, then [q | dout][tile][ks][lane] (kLds); the merge area lies over the front
+    static constexpr int kRowBytes = 4 * 32 * kHeadDim * 2;
     static size_t lds_bytes(int topk) {
-        const size_t work = UnionLds::bytes(kTok, topk) + (kLds ? (size_t)2 * kTiles * 4 * 64 * sizeof(uint4) : 0);
+        const size_t work = UnionLds::bytes(kTok, topk) + kRowBytes + (kLds ? (size_t)2 * kTiles * 4 * 64 * sizeof(uint4) : 0);
         const size_t merge = (size_t)4 * 8 * 64 * sizeof(float4);
         return work > merge ? work : merge;
     }
 };
 
 template <int kG, int kTiles>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, Tensor out, Tensor dout,
+                                                              const uint4 *__restrict__ kvb,
                                                               int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                               const int32_t *__restrict__ block_idx,
                                                               const float *__restrict__ lse,
-                                                              const float *__restrict__ delta, Tensor dq,
-                                                              int32_t slots) {
+                                                              float *__restrict__ rowc, Tensor dq, int32_t slots) {
     using C = DqCfg<kG, kTiles>;
-    constexpr int kRing = C::kRing, kTPT = C::kTPT, kTok = C::kTok;
+    constexpr int kRing = kDqRing, kTPT = C::kTPT, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per workgroup; member bits in one word");
     extern __shared__ __align__(16) unsigned char dq_smem[];
     __shared__ int cnt_s;
@@ -229,14 +273,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     const int tile = (L + kTok - 1) / kTok - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);   // (see the forward's launch)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t0 = tile * kTok;
-    if (tile < 0 || t0 >= L) return;                      // uniform over the workgroup
+    if (dm.fill) {                                        // rows past the end: this tile's, or one of those behind the last
+        const int f0 = tile >= 0 ? t0 : ((L + kTok - 1) / kTok - 1 - tile) * kTok;
+        for (int i = threadIdx.x; i < kTok * kG * 16; i += 256) {
+            const int tok = f0 + i / (kG * 16);
+            if (tok >= L && tok < dm.max_seqlen)
+                *reinterpret_cast<uint4 *>(dq.ptr + b * dq.sb + (int64_t)tok * dq.st +
+                                           (int64_t)(h * kG + i / 16 % kG) * dq.sh + 8 * (i & 15)) = uint4{0u, 0u, 0u, 0u};
+        }
+    }
+    if (tile < 0) return;                                 // uniform over the workgroup
     const int b_own = t0 / kBlock;
     const int n = lane & 15, g = lane >> 4;               // MFMA column (token, query head) and 16-lane group
     const int tn = n / kG;
     const float c = dm.scale_log2;
 
     bf16x8 qf[C::kLds ? 1 : kTiles][4], gf[C::kLds ? 1 : kTiles][4];
-    bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + UnionLds::bytes(kTok, dm.topk)) + lane;   // [q | dout][tile][ks][lane]
+    bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + UnionLds::bytes(kTok, dm.topk) + C::kRowBytes) + lane;   // [q | dout][tile][ks][lane]
     f32x4 acc[kTiles][8];
 #pragma unroll
     for (int u = 0; u < kTiles; ++u) {
@@ -245,9 +298,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
         if (!C::kLds || wave == u) {
             const __bf16 *qr = q.ptr + b * q.sb + (int64_t)tk * q.st + row * q.sh + 8 * g;
             const __bf16 *gr = dout.ptr + b * dout.sb + (int64_t)tk * dout.st + row * dout.sh + 8 * g;
+            const __bf16 *orow = out.ptr + b * out.sb + (int64_t)tk * out.st + row * out.sh + 8 * g;
+            float d = 0.f;                                // D = <dout, out> of the row
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 const bf16x8 xq = load8(qr + 32 * ks), xg = load8(gr + 32 * ks);
+                if (wave == u) {
+                    const bf16x8 xo = load8(orow + 32 * ks);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) d = __builtin_fmaf((float)xo[e], (float)xg[e], d);
+                }
                 if constexpr (C::kLds) {
                     ql[(u * 4 + ks) * 64] = xq;
                     ql[((kTiles + u) * 4 + ks) * 64] = xg;
@@ -256,12 +316,21 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                     gf[u][ks] = xg;
                 }
             }
-        }
-        if (wave == u && g == 0) {
-            const int64_t at = ((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row;
-            const float ls = lse[at];
-            // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
-            row_s[u][n] = float2{(tok < L && ls > -INFINITY) ? -ls * kLog2e : -INFINITY, delta[at]};
+            if (wave == u) {
+                d = xgroup_sum(d);
+                const float ls = lse[((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row];
+                // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
+                const float ne = (ls > -INFINITY && ls < INFINITY) ? -ls * kLog2e : -INFINITY;
+                if (g == 0) {
+                    row_s[u][n] = float2{tok < L ? ne : -INFINITY, d};
+                    // the same for dk and dv, per (token, key-value head): G exponent offsets, then G times D
+                    float *rec = rowc + (((int64_t)b * dm.max_seqlen + tk) * dm.Hkv + h) * (2 * kG) + n % kG;
+                    if (tok < L) {
+                        rec[0] = ne;
+                        rec[kG] = d;
+                    }
+                }
+            }
         }
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -288,15 +357,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
         return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bp, lane16, f * 1024, 0));
     };
     auto issue = [&](int unit, __amdgpu_buffer_rsrc_t bp) __attribute__((always_inline)) {
-        const int hs = unit / 6, r = unit % 6;
-        if (r < 4) {                                      // K rows (section 0) or V rows (section 1), key tile 2hs + r%2
-            const int sec = r >> 1, mt = 2 * hs + (r & 1);
+        const int hs = unit / 4, sec = (unit >> 1) & 1, mt = 2 * hs + (unit & 1);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) ring[unit % kRing][ks] = fragment(bp, sec * 16 + ks * 4 + mt);
-        } else {                                          // K^T (section 2), channel tiles 4(r-4) .. +3 of half hs
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ring[unit % kRing][i] = fragment(bp, 32 + (4 * (r - 4) + i) * 2 + hs);
-        }
+        for (int ks = 0; ks < 4; ++ks) ring[unit % kRing][ks] = fragment(bp, sec * 16 + ks * 4 + mt);
+    };
+    // this wave's K rows of the half in LDS: where the lane's piece of key 16t + n goes, and where its four rows for the
+    // transposing load begin (keys 16t + 4g .. +3, channels 16dt ..: ^ (dt << 5))
+    char *kt = reinterpret_cast<char *>(dq_smem + UnionLds::bytes(kTok, dm.topk)) + wave * (C::kRowBytes / 4);
+    // (both formed anew where they are used: with four tiles the registers are all taken)
+    auto kt_put = [&]() __attribute__((always_inline)) {       // ^ (ks << 6)
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));
+        return (ln & 15) * 256u + (((ln >> 4) ^ (uint32_t)bwd_swizzle((int)(ln & 15))) << 4);
+    };
+    auto kt_get = [&]() __attribute__((always_inline)) {
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));
+        const uint32_t row = 4u * (ln >> 4) + ((ln & 15) >> 2);
+        return row * 256u + ((((ln & 3) >> 1) ^ (uint32_t)bwd_swizzle((int)row)) << 4) + 8u * (ln & 1);
     };
 
     __builtin_amdgcn_s_waitcnt(0);                        // nothing of the prologue may still be pending inside the ring loop
@@ -345,7 +423,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
             bf16x8 dsf[kTiles];
+            auto keep = [&](int r) __attribute__((always_inline)) {
+                const uint32_t put = kt_put();
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    *reinterpret_cast<u32x4 *>(kt + (put ^ (uint32_t)(ks << 6)) + r * 4096) = ring[(4 * hs + r) % kRing][ks];
+            };
             if constexpr (C::kLds) {
+                keep(0);
+                keep(1);
 #pragma unroll
                 for (int u = 0; u < kTiles; ++u) {
                     if (!tb[u]) continue;
@@ -354,43 +440,48 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) x[ks] = ql[(u * 4 + ks) * 64];
 #pragma unroll
-                    for (int r = 0; r < 2; ++r) s[r] = product(6 * hs + r, x);
+                    for (int r = 0; r < 2; ++r) s[r] = product(4 * hs + r, x);
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) x[ks] = ql[((kTiles + u) * 4 + ks) * 64];
 #pragma unroll
-                    for (int r = 0; r < 2; ++r) dp[r] = product(6 * hs + 2 + r, x);
+                    for (int r = 0; r < 2; ++r) dp[r] = product(4 * hs + 2 + r, x);
                     grad(u, hs, s, dp, dsf[u]);
                 }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) refill(6 * hs + r);
+                for (int r = 0; r < 4; ++r) refill(4 * hs + r);
             } else {
                 f32x4 s[kTiles][2], dp[kTiles][2];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
+                    if (r < 2) keep(r);
 #pragma unroll
                     for (int u = 0; u < kTiles; ++u) {
                         if (!tb[u]) continue;
-                        if (r < 2) s[u][r] = product(6 * hs + r, qf[u]);
-                        else dp[u][r - 2] = product(6 * hs + r, gf[u]);
+                        if (r < 2) s[u][r] = product(4 * hs + r, qf[u]);
+                        else dp[u][r - 2] = product(4 * hs + r, gf[u]);
                     }
-                    refill(6 * hs + r);
+                    refill(4 * hs + r);
                 }
 #pragma unroll
                 for (int u = 0; u < kTiles; ++u)
                     if (tb[u]) grad(u, hs, s[u], dp[u], dsf[u]);
             }
 #pragma unroll
-            for (int r = 4; r < 6; ++r) {
-                const int unit = 6 * hs + r;
+            for (int d4 = 0; d4 < 8; d4 += 4) {
+                bf16x8 kf[4];
+                const uint32_t get = kt_get();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t at = get ^ (uint32_t)((d4 + i) << 5);
+                    const s16x4 x0 = lds_read_tr16(kt + at), x1 = lds_read_tr16(kt + at + 4096);
+                    kf[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
 #pragma unroll
                 for (int u = 0; u < kTiles; ++u) {
                     if (!tb[u]) continue;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        acc[u][4 * (r - 4) + i] =
-                            mfma16(__builtin_bit_cast(bf16x8, ring[unit % kRing][i]), dsf[u], acc[u][4 * (r - 4) + i]);
+                    for (int i = 0; i < 4; ++i) acc[u][d4 + i] = mfma16(kf[i], dsf[u], acc[u][d4 + i]);
                 }
-                refill(unit);
             }
         }
     }
@@ -426,8 +517,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 }
 
 template <int kG, int kTiles>
-static int launch_dq_variant(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                             const int32_t *block_idx, const float *lse, const float *delta, Tensor dq, hipStream_t stream) {
+static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
+                             const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
     using C = DqCfg<kG, kTiles>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTok - 1) / C::kTok;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
@@ -438,7 +529,7 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor dout, const uint4 
         if (e != hipSuccess) return (int)e;
     }
     hipLaunchKernelGGL((attn_bwd_dq_kernel<kG, kTiles>), dim3((uint32_t)((int64_t)slots * 8 * dm.Hkv * dm.batch)), dim3(256), lds,
-                       stream, dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, slots);
+                       stream, dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, slots);
     return 0;
 }
 
@@ -448,278 +539,279 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor dout, const uint4 
 // 13 / 16 / 27 us with 1 / 2 / 4; 8192 x 2, G = 1: 123 / 107 with 1 / 2; 4096 x 2 x 2, G = 8: 258 / 189 / 173).  A tile of
 // G = 1 is 16 tokens and four would not fit the 32 member bits.
 template <int kG>
-static int launch_dq_group(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                           const int32_t *block_idx, const float *lse, const float *delta, Tensor dq, hipStream_t stream) {
+static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
+                           const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG > 1)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
-    return launch_dq_variant<kG, 1>(dm, q, dout, kvb, nb_cap, seqlens, block_idx, lse, delta, dq, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
+    return launch_dq_variant<kG, 1>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
 }
 
 // ---- dk, dv of one block from the tokens that selected it ------------------------------------------------------
-// 256 threads: a workgroup handles member tokens of block j that lie in one segment of the sequence (all of
-// them, or one slice of the list when there are many).  The member tokens are compacted from the bitmap into a
-// list and walked in pairs; rows = (token of the pair, head).  Every pair has two phases with a barrier between:
-//   phase 1, wave = (token u, key half kh), 16x16x32 MFMAs: S = Q.K^T and dP = dO.V^T for the token's 16 heads
-//            and the half's 32 keys (A = the token's q / dout rows from LDS, B = K / V rows of the keys, held
-//            in registers), then P = exp(S - lse) and dS = P (dP - D), left in LDS as bf16 in the layout of a
-//            32x32x16 B operand (lane = key, 8 heads of one token per lane);
-//   phase 2, wave = channel quarter cq, 32x32x16 MFMAs: dV^T[c, key] += dO^T[c, row] . P[row, key] and
-//            dK^T[c, key] += Q^T[c, row] . dS[row, key] for channels 32cq .. +31 and all 64 keys: A = the same
-//            staged rows read through the transposing LDS load (each fragment feeds both key halves), B = P / dS.
-// Nothing is computed twice, and a wavefront keeps 64 accumulator registers next to the 64 of its K and V operands.
-// Staging: the 16 KiB of q and dout rows of a pair (and its 64 scalars) go from memory straight into LDS (no
-// registers, no vector instructions) two pairs ahead; three slots rotate.  The slots are three objects and the
-// loop is unrolled by three, so that the compiler's wait counts let reads of one slot run under the copies into
-// another.  A row is 256 bytes; its sixteen 16-byte pieces are stored XOR-swizzled with the head's two bit
-// pairs exchanged: an operand load of phase 1 takes one piece from each of 16 rows, a transposing load 32 bytes
+// 128 threads, persistent: a workgroup takes items from its XCD's queue, then from the others', until all are empty.  An item's
+// member tokens are expanded from the membership words into a list and walked in steps of 32 rows = (token, head), 32 / G
+// tokens; wave = 32 keys of the block through the whole step, in registers from the scores to the sums (32x32x16 MFMAs):
+//   S[row, key] = Q.K^T and dP = dO.V^T       A = rows from LDS, B = the keys' K and V rows, held in registers
+//   P = exp(S - lse), dS = P (dP - D)         lane = key, 16 rows: as bf16 they are the next products' A operands
+//   dV[key, c] += P^T.dO, dK += dS^T.Q        B = the same rows through the transposing LDS load, contraction index permuted to match
+// Nothing passes between the two waves but the staged rows: one barrier per step.
+// Bound by the matrix cores (half of their time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (9.4 GB, L2
+// hit 17 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
+// keys the LDS reads double.  Against a workgroup per (block, 2048-token segment) with P and dS exchanged through LDS, rows
+// of two whole tokens a step, and blocks dealt to the XCDs by their number (the first block, which every token selects, kept
+// one XCD busy while the others waited: CUs 55 % busy): 32K tokens, G = 16 3440 -> 1190 us; 2 x 4096 tokens, G = 8
+// 690 -> 160; 8192 tokens, G = 1 770 -> 75; 777 tokens, G = 16, top-k 8 204 -> 47.
+// Staging: the 16 KiB of q and dout rows of a step (and its 64 scalars) go from memory straight into LDS one step ahead.
+// The two slots are two objects and the loop is unrolled by two, so that the compiler's wait counts let reads of one slot run
+// under the copies into the other.  A row is 256 bytes; its sixteen 16-byte pieces are stored XOR-swizzled with the
+// row's two bit pairs exchanged: an operand load takes one piece from each of 32 rows, a transposing load 32 bytes
 // from each of 4 consecutive rows, and both then touch every bank once.
-constexpr int kBwdSlices = 4;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 struct __align__(16) BwdSlot {
     uint16_t rows[2][32][kHeadDim];                       // [q | dout][(token, head)][channel]: 16 KiB
-    float ld[64];                                         // [exponent offset of token a, of b | D of token a, of b][head]
+    float ld[64];                                         // [exponent offset | D][(token, head)]
 };
-struct __align__(16) BwdExchange {
-    uint4 frag[2][2][2][2][64];                           // [buffer][P | dS][token][key half][lane = (key, head group)]: 16 KiB
-};
-__device__ __forceinline__ int bwd_swizzle(int head) { return ((head & 3) << 2) | ((head >> 2) & 3); }
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-// 4 rows x 16 channels per 16-lane group, transposed: lane i of the group gets channel i of the four rows its
-// group addressed (source lane s: row s/4, channels 4(s%4) .. +3)
-__device__ __forceinline__ s16x4 lds_read_tr16(const char *p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-}
-
-template <int kSegTokens>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
+template <int kG>
+__global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
                                                                 int32_t nb_cap, const int32_t *__restrict__ seqlens,
-                                                                const float *__restrict__ rowc,
-                                                                const uint32_t *__restrict__ bitmap, int32_t words,
+                                                                const float *__restrict__ rowc, const float *__restrict__ null_row,
+                                                                const uint32_t *__restrict__ bits, uint32_t *__restrict__ counters,
+                                                                const uint4 *__restrict__ items, int32_t item_cap,
                                                                 float *__restrict__ acc_dk, float *__restrict__ acc_dv) {
-    constexpr int kSegWords = kSegTokens / 32;
-    constexpr int kSegWordsPerLane = kSegWords / 64;      // the member list is compacted by one wavefront
-    static_assert(kSegWords % 64 == 0 && kSegTokens <= 65536, "whole words per lane; 16-bit offsets in the member list");
-    __shared__ uint16_t list[kSegTokens / kBwdSlices];   // this workgroup's member tokens as offsets into the segment
-    __shared__ BwdSlot slot0, slot1, slot2;
-    __shared__ BwdExchange ex;
-    __shared__ int total_s;
-    // grid (blocks, segments x slices, B*Hkv): workgroups that run at the same time work on neighbouring blocks
-    // of one segment and find its tokens' rows in the caches; a (block, segment) unit with many members is
-    // shared by up to kBwdSlices workgroups, each taking kSliceTokens consecutive members
-    constexpr int kSliceTokens = kSegTokens / kBwdSlices;
-    const int j = blockIdx.x, seg = blockIdx.y / kBwdSlices, slice = blockIdx.y - seg * kBwdSlices;
-    const int b = blockIdx.z / dm.Hkv, h = blockIdx.z - b * dm.Hkv;
-    const int L = seq_len(dm, seqlens, b);
-    if ((seg + 1) * kSegTokens <= j * kBlock || seg * kSegTokens >= L || j * kBlock >= L) return;   // no member can be here
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = dm.G;
+    constexpr int kTPS = 32 / kG;                         // tokens per step
+    __shared__ uint16_t list[kMaxMembers];                // the item's member tokens as offsets from its first word's first token
+    __shared__ BwdSlot slot0, slot1;
+    __shared__ uint4 item_s;
+    __shared__ int tries_s;
+    const int tid = threadIdx.x, lane = tid & 63;
+    int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    asm volatile("" : "+s"(wave));                        // (a scalar, also after the compiler's own rewriting)
+    const int c32 = lane & 31, hf = lane >> 5;
+    const int kh = wave;                                  // key half
     const float c = dm.scale_log2;
-    const int64_t bh = (int64_t)b * dm.Hkv + h;
-    // ---- member tokens of this segment, ascending (wave 0) ----------------------------------------------
-    uint32_t word[kSegWordsPerLane];                      // consecutive words per lane: the list comes out ascending
-    int before = 0, mine = 0;
-    if (wave == 0) {
-#pragma unroll
-        for (int i = 0; i < kSegWordsPerLane; ++i) {
-            word[i] = bitmap[(bh * nb_cap + j) * words + seg * kSegWords + lane * kSegWordsPerLane + i];
-            mine += __popc(word[i]);
-        }
-        before = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int x = __shfl_up(before, o);
-            if (lane >= o) before += x;
-        }
-        if (lane == 63) total_s = before;
-        before -= mine;
+    const __bf16 *const s_ptr = wave == 0 ? q.ptr : dout.ptr;
+    const int64_t s_sb = wave == 0 ? q.sb : dout.sb, s_sh = wave == 0 ? q.sh : dout.sh, s_st = wave == 0 ? q.st : dout.st;
+    const uint32_t s_head = (uint32_t)(s_sh * 2);         // bytes from head to head
+    auto draw = [&](int x) __attribute__((always_inline)) {
+        return atomicAdd(&counters[((blockIdx.x + x) % kQueues) * kQueueStride + kQueueStride / 2], 1u);
+    };
+    uint32_t ticket = 0;                                  // thread 0: place in queue `tries` behind the own one
+    if (tid == 0) {
+        tries_s = 0;
+        ticket = draw(0);
     }
-    __syncthreads();
-    const int first = slice * kSliceTokens;               // this workgroup's members: first .. first + total - 1 of the unit
-    const int total = min(total_s - first, kSliceTokens);
-    if (total <= 0) return;                               // uniform
-    if (wave == 0) {
+    for (;;) {
+        // ---- next item ----------------------------------------------------------------------------------------------
+        if (tid == 0) {
+            uint4 it = {0u, 0u, 0u, 0u};
+            for (int x = tries_s; x < kQueues; ticket = draw(x)) {      // ends: a queue that is found empty stays empty
+                const int at = (int)((blockIdx.x + x) % kQueues);
+                if (ticket < counters[at * kQueueStride]) {
+                    it = items[(int64_t)at * item_cap + ticket];
+                    break;
+                }
+                tries_s = ++x;
+                if (x == kQueues) break;
+            }
+            item_s = it;
+        }
+        __syncthreads();                                  // (also: everyone is past the last item's reads of the list and the slots)
+        const int bh = (int)__builtin_amdgcn_readfirstlane(item_s.x), j = (int)__builtin_amdgcn_readfirstlane(item_s.y);
+        const int tok0 = 32 * (int)__builtin_amdgcn_readfirstlane(item_s.z);
+        const uint32_t nw = __builtin_amdgcn_readfirstlane(item_s.w);
+        const int total = (int)(nw >> 16);
+        if (total == 0) return;                           // uniform: every queue is empty
+        const int b = bh / dm.Hkv, h = bh - b * dm.Hkv;
+        const int L = seq_len(dm, seqlens, b);
+        // ---- B operands: K and V rows of keys 32kh + c32, channels 16ks + 8hf .. +7 -------------------------------------
+        const u32x4 *blk = reinterpret_cast<const u32x4 *>(kvb) + ((int64_t)bh * nb_cap + j) * kBwdBlockU4 +
+                           (2 * kh + ((lane >> 4) & 1)) * 64 + hf * 16 + (lane & 15);
+        bf16x8 kB[8], vB[8];
 #pragma unroll
-        for (int i = 0; i < kSegWordsPerLane; ++i) {
-            uint32_t w = word[i];
+        for (int ks = 0; ks < 8; ++ks) {
+            const int at = (ks >> 1) * 4 * 64 + (ks & 1) * 32;
+            kB[ks] = __builtin_bit_cast(bf16x8, blk[at]);
+            vB[ks] = __builtin_bit_cast(bf16x8, blk[16 * 64 + at]);
+        }
+        // ---- member tokens, ascending -----------------------------------------------------------------------------------
+        if (wave == 0) {
+            uint32_t w = 0u;
+            if (lane < (int)(nw & 0xffffu)) w = bits[((int64_t)bh * 2 * nb_cap + (tok0 >> 5) + lane) * nb_cap + j];
+            const int mine = __popc(w);
+            int at = wave_inclusive_sum(mine) - mine;
             while (w) {
                 const int bit = __ffs(w) - 1;
                 w &= w - 1;
-                const int at = before++ - first;
-                if (at >= 0 && at < kSliceTokens) list[at] = (uint16_t)((lane * kSegWordsPerLane + i) * 32 + bit);
+                list[at++] = (uint16_t)(lane * 32 + bit);
             }
         }
-    }
-    __syncthreads();
-    const int n_pairs = (total + 1) >> 1;
-    const int n = lane & 15, g = lane >> 4;               // 16x16x32 roles: row / column, k group
-    const int c32 = lane & 31, hf = lane >> 5;            // 32x32x16 roles
-    const int u = wave >> 1, kh = wave & 1;               // phase 1: token of the pair, key half
-    const int cq = wave;                                  // phase 2: channel quarter
-    // ---- phase 1 B operands: K and V rows of keys 32kh + 16t + n, channels 32ks + 8g .. +7 ---------------------
-    const u32x4 *blk = reinterpret_cast<const u32x4 *>(kvb) + (bh * nb_cap + j) * kBwdBlockU4 + lane;
-    bf16x8 kB[2][4], vB[2][4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            kB[t][ks] = __builtin_bit_cast(bf16x8, blk[(ks * 4 + 2 * kh + t) * 64]);
-            vB[t][ks] = __builtin_bit_cast(bf16x8, blk[(16 + ks * 4 + 2 * kh + t) * 64]);
-        }
-    f32x16 dkT[2], dvT[2];                                // [key half]: channels 32cq .. +31 x 32 keys
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) dkT[i][v] = dvT[i][v] = 0.f;
+        __syncthreads();
+        const int steps = (total + kTPS - 1) / kTPS;
 
-    // staging: wave w copies one token's 16 rows of one tensor (token w&1 of the pair, q for w < 2, dout else): four
-    // 1 KiB copies of four heads each, all from one token offset; lane = (head 4i + lane/16, piece lane%16 of the
-    // LDS row = piece (lane%16) ^ swizzle(head) of the row in memory)
-    const Tensor &s_t = wave < 2 ? q : dout;
-    const __bf16 *s_base = s_t.ptr + b * s_t.sb + (int64_t)(h * G) * s_t.sh;
-    int32_t s_off[4];                                     // elements from the token's first head of the group
+        const __bf16 *s_base = s_ptr + b * s_sb + (int64_t)(h * kG) * s_sh + (int64_t)tok0 * s_st;
+        asm volatile("" : "+s"(s_base));
+        const char *s_rec = reinterpret_cast<const char *>(rowc + (((int64_t)b * dm.max_seqlen + tok0) * dm.Hkv + h) * (2 * kG));
+        auto stage = [&](BwdSlot &dst, int p) __attribute__((always_inline)) {
+            // wave 0 copies q, wave 1 dout: 1 KiB copies of rows 4i + lane/16 (what depends on the lane only is formed anew each
+            // time: registers are what this kernel has least of)
+            uint32_t ln = lane;
+            asm volatile("" : "+v"(ln));
+            const uint32_t s_row = ((ln >> 4) % kG) * s_head, s_piece = ((ln & 15) ^ ((ln >> 4) << 2)) << 4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int head = 4 * i + (lane >> 4);
-        s_off[i] = (int32_t)(min(head, G - 1) * s_t.sh) + 8 * ((lane & 15) ^ bwd_swizzle(head));
-    }
-    const float *s_f = rowc + ((int64_t)b * dm.max_seqlen * dm.Hkv + h) * 32 + 16 * (lane >> 5) + (lane & 15);   // + 32 Hkv tok
-    auto stage = [&](BwdSlot &dst, int p) __attribute__((always_inline)) {
-        const int tok = seg * kSegTokens + list[min(2 * p + (wave & 1), total - 1)];
-        const __bf16 *src = s_base + (int64_t)tok * s_t.st;
+            for (int i = 0; i < 8; ++i) {
+                auto to = (__attribute__((address_space(3))) void *)&dst.rows[wave][4 * i][0];
+                if constexpr (kG >= 4) {
+                    const int tok = __builtin_amdgcn_readfirstlane((int)list[min(p * kTPS + 4 * i / kG, total - 1)]);
+                    const __amdgpu_buffer_rsrc_t src =
+                        __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(s_base + (int64_t)tok * s_st), 0, 0xffffffffu, 0x00027000);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, to, 16, (int)((s_piece ^ ((i & 3) << 4)) + s_row), (int)(4 * i % kG * s_head), 0, 0);
+                } else {
+                    const int tok = list[min(p * kTPS + (int)(4 * i + (ln >> 4)) / kG, total - 1)];
+                    const char *src = reinterpret_cast<const char *>(s_base + (int64_t)tok * s_st) + (s_piece ^ ((i & 3) << 4)) + s_row;
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, to, 16, 0, 0);
+                }
+            }
+            if (wave == 1) {
+                const int at = p * kTPS + (int)(ln & 31) / kG;
+                const uint32_t off = list[min(at, total - 1)] * (uint32_t)(dm.Hkv * 2 * kG * 4) + 4u * ((ln >> 5) * kG + ln % kG);
+                const char *src = at < total ? s_rec + off : reinterpret_cast<const char *>(null_row) + 4u * (16 * (ln >> 5));
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                                 (__attribute__((address_space(3))) void *)&dst.ld[0], 4, 0, 0);
+            }
+        };
+        // an item's walk; `edge`: the members lie inside the block itself (apart: the others have no registers for it)
+        auto walk = [&](auto edge) __attribute__((always_inline)) {
+        f32x16 dk[4], dv[4];                              // [channel tile]: keys 8(v/4) + 4hf + v%4 of the half, channel 32ct + c32
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + s_off[i]),
-                                             (__attribute__((address_space(3))) void *)&dst.rows[wave >> 1][16 * (wave & 1) + 4 * i][0],
-                                             16, 0, 0);
-        if (wave == 0) {
-            const int tb = seg * kSegTokens + list[min(2 * p + 1, total - 1)];
-            const int tk = ((lane >> 4) & 1) ? tb : tok;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(s_f + (int64_t)tk * dm.Hkv * 32),
-                                             (__attribute__((address_space(3))) void *)&dst.ld[0], 4, 0, 0);
-        }
-    };
-    // LDS addresses of the operand loads, the parts that depend on the lane
-    const uint32_t a_row = (uint32_t)(16 * u + n) * 256u + (uint32_t)((g ^ bwd_swizzle(n)) << 4);   // piece 4ks + g of the row: ^ (ks << 6)
-    const uint32_t t_r = 4u * hf + ((lane & 15) >> 2), t_c = 2u * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    // (channel quarter cq starts at piece 4cq; rows 8rd + t_r have swizzle 2rd ^ swizzle(t_r))
-    const uint32_t a_tr = t_r * 256u + ((t_c ^ (uint32_t)bwd_swizzle((int)t_r) ^ (4u * cq)) << 4) + 8u * (lane & 1);   // ^ (2rd << 4), + (16 s2 + 8 rd) rows
-    // where this lane's four probabilities of a key go in the exchange: consumer lane (key 16t + n, head group g & 1),
-    // elements 4 (g >> 1) .. +3
-    const uint32_t x_put = (uint32_t)((n + 32 * (g & 1)) * 16 + 8 * (g >> 1));   // + 256 t bytes
-
-    auto phase1 = [&](const BwdSlot &cur, int p) __attribute__((always_inline)) {
-        const int tk = seg * kSegTokens + list[min(2 * p + u, total - 1)];
-        const bool valid = 2 * p + u < total;
-        const char *xq = reinterpret_cast<const char *>(&cur.rows[0][0][0]);
-        const char *xg = reinterpret_cast<const char *>(&cur.rows[1][0][0]);
-        f32x4 sacc[2], dp[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) sacc[t] = dp[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int v = 0; v < 16; ++v) dk[i][v] = dv[i][v] = 0.f;
+        auto step = [&](const BwdSlot &cur, BwdSlot &next, int p) __attribute__((always_inline)) {
+            __builtin_amdgcn_s_waitcnt(0);                // this wavefront's copies for step p have landed
+            __syncthreads();                              // everyone's have, and everyone is past step p - 1
+            stage(next, p + 1);                           // (past the end: copies of the last token, never used)
+            const char *xq = reinterpret_cast<const char *>(&cur.rows[0][0][0]);
+            const char *xg = reinterpret_cast<const char *>(&cur.rows[1][0][0]);
+            uint32_t ln = lane;
+            asm volatile("" : "+v"(ln));
+            const uint32_t hf = ln >> 5;
+            // operand loads: piece 2ks + hf of row lane % 32; transposed: rows 16s + 8rd + 4hf + 0..3 at channel tile ct, whose pieces
+            // start at 4ct and have swizzle 2rd ^ that of row 4hf + 0..3
+            const uint32_t ar = (ln & 31) * 256u + ((hf ^ (uint32_t)bwd_swizzle((int)(ln & 15))) << 4);
+            const uint32_t t_r = 4u * hf + ((ln & 15) >> 2), t_c = 2u * ((ln >> 4) & 1) + ((ln & 3) >> 1);
+            const uint32_t at = t_r * 256u + ((t_c ^ (uint32_t)bwd_swizzle((int)t_r)) << 4) + 8u * (ln & 1);
+            auto rows_of = [&](const char *x, int ks) __attribute__((always_inline)) {
+                return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(x + (ar ^ (uint32_t)(ks << 5))));
+            };
+            auto columns_of = [&](const char *x, int i) __attribute__((always_inline)) {       // i = 4 s2 + ct
+                const uint32_t s2 = i >> 2, ct = i & 3;
+                const s16x4 x0 = lds_read_tr16(x + ((at ^ (ct << 6)) + 16 * s2 * 256u));
+                const s16x4 x1 = lds_read_tr16(x + ((at ^ ((ct << 6) | (2 << 4))) + (16 * s2 + 8) * 256u));
+                return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
+            };
+            f32x16 s, dp;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 qa = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(xq + (a_row ^ (uint32_t)(ks << 6))));
-            const bf16x8 ga = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(xg + (a_row ^ (uint32_t)(ks << 6))));
+            for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
+            bf16x8 xa[2], xb[2];                          // the next operands are under way while the matrix cores work
+            xa[0] = rows_of(xq, 0);
+            xb[0] = rows_of(xg, 0);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                sacc[t] = mfma16(qa, kB[t][ks], sacc[t]);
-                dp[t] = mfma16(ga, vB[t][ks], dp[t]);
+            for (int ks = 0; ks < 8; ++ks) {
+                if (ks < 7) {
+                    xa[(ks + 1) & 1] = rows_of(xq, ks + 1);
+                    xb[(ks + 1) & 1] = rows_of(xg, ks + 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                s = mfma32(xa[ks & 1], kB[ks], s);
+                dp = mfma32(xb[ks & 1], vB[ks], dp);
             }
-        }
-        // accumulator entry r of tile t: head 4g + r (row), key 32kh + 16t + n (column)
-        const float4 n4 = *reinterpret_cast<const float4 *>(&cur.ld[16 * u + 4 * g]);
-        const float4 d4 = *reinterpret_cast<const float4 *>(&cur.ld[32 + 16 * u + 4 * g]);
-        const float nl[4] = {n4.x, n4.y, n4.z, n4.w}, dl[4] = {d4.x, d4.y, d4.z, d4.w};
-        char *xp = reinterpret_cast<char *>(&ex.frag[p & 1][0][u][kh][0]) + x_put;
-        char *xs = reinterpret_cast<char *>(&ex.frag[p & 1][1][u][kh][0]) + x_put;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            // padding of the list and the causal edge inside the own block: the exponent's offset becomes -inf
-            const float bias = (!valid | (j * kBlock + 32 * kh + 16 * t + n > tk)) ? -INFINITY : 0.f;
-            bf16x4 pb, sb;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float pr = fast_exp2(__builtin_fmaf(sacc[t][r], c, nl[r] + bias));
-                pb[r] = (__bf16)pr;
-                sb[r] = (__bf16)(pr * (dp[t][r] - dl[r]));
-            }
-            *reinterpret_cast<uint2 *>(xp + 256 * t) = __builtin_bit_cast(uint2, pb);
-            *reinterpret_cast<uint2 *>(xs + 256 * t) = __builtin_bit_cast(uint2, sb);
-        }
-    };
-    auto phase2 = [&](const BwdSlot &cur, int p) __attribute__((always_inline)) {
-        const char *xq = reinterpret_cast<const char *>(&cur.rows[0][0][0]);
-        const char *xg = reinterpret_cast<const char *>(&cur.rows[1][0][0]);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const uint32_t o0 = a_tr + (uint32_t)(16 * s2) * 256u;
-            const uint32_t o1 = (a_tr ^ (uint32_t)(2 << 4)) + (uint32_t)(16 * s2 + 8) * 256u;
-            const s16x4 g0 = lds_read_tr16(xg + o0), g1 = lds_read_tr16(xg + o1);
-            const s16x4 q0 = lds_read_tr16(xq + o0), q1 = lds_read_tr16(xq + o1);
-            const bf16x8 ag = __builtin_bit_cast(bf16x8, __builtin_shufflevector(g0, g1, 0, 1, 2, 3, 4, 5, 6, 7));
-            const bf16x8 aq = __builtin_bit_cast(bf16x8, __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-            for (int k2 = 0; k2 < 2; ++k2) {
-                const bf16x8 pf = __builtin_bit_cast(bf16x8, ex.frag[p & 1][0][s2][k2][lane]);
-                const bf16x8 sf = __builtin_bit_cast(bf16x8, ex.frag[p & 1][1][s2][k2][lane]);
-                dvT[k2] = mfma32(ag, pf, dvT[k2]);
-                dkT[k2] = mfma32(aq, sf, dkT[k2]);
-            }
-        }
-    };
-    // pair p: phase 1, barrier, phase 2; the copies for pair p + 2 go out right after the barrier, into the slot
-    // whose last reads (phase 2 of pair p - 1) everyone has finished by then, and have a whole pair's time to land.
-    // The trip count is rounded up to a multiple of three and nothing in the loop is conditional (pairs past the
-    // end are copies of the last token with every probability zero): at a join of two paths the compiler would
-    // wait for every copy in flight.
-    auto pair_step = [&](const BwdSlot &cur, BwdSlot &third, int p) __attribute__((always_inline)) {
-        phase1(cur, p);
-        __builtin_amdgcn_s_waitcnt(0);                    // this wavefront's copies for pair p + 1 have landed
-        __syncthreads();                                  // everyone's have; P and dS of pair p are in place
-        stage(third, p + 2);
-        phase2(cur, p);
-    };
-    stage(slot0, 0);
-    stage(slot1, 1);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int p = 0; p < n_pairs; p += 3) {
-        pair_step(slot0, slot2, p);
-        pair_step(slot1, slot0, p + 1);
-        pair_step(slot2, slot1, p + 2);
-    }
-    __builtin_amdgcn_s_waitcnt(0);                        // the last copies (never used) have landed: the slots are reused below
-    // ---- merge: a lane holds channels 32cq + 8(v/4) + 4hf + v%4 of key 32kh' + c32.  The tiles are turned through
-    // LDS (the staging slots, 8 KiB per wavefront) so that one atomic instruction covers the 32 channels of two
-    // keys: two cache lines instead of 64. --------------------------------------------------------------------
-    __syncthreads();                                      // every wavefront is past its last read of the staging slots
-    float *tile = reinterpret_cast<float *>(wave < 2 ? &slot0.rows[0][0][0] : &slot1.rows[0][0][0]) + (wave & 1) * 2048;
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        // [key 0 .. 63][16-byte piece ^ (key & 7)][4 channels]
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
+            // entry v: row 8(v/4) + 4hf + v%4, key 32kh + lane % 32
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
-                const f32x16 &t = which ? dvT[k2] : dkT[k2];
-                const int key = 32 * k2 + c32, piece = 2 * v4 + hf;   // channels 4 piece .. +3 of the wave's 32
-                *reinterpret_cast<float4 *>(tile + key * 32 + ((piece ^ (key & 7)) << 2)) =
-                    float4{t[4 * v4], t[4 * v4 + 1], t[4 * v4 + 2], t[4 * v4 + 3]};
+                if (v4 & 1) __builtin_amdgcn_sched_barrier(0);
+                const float4 n4 = *reinterpret_cast<const float4 *>(&cur.ld[8 * v4 + 4 * hf]);
+                const float ne[4] = {n4.x, n4.y, n4.z, n4.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[4 * v4 + r] = fast_exp2(__builtin_fmaf(s[4 * v4 + r], c, ne[r]));
             }
-        // (same wavefront wrote and reads: LDS keeps the order)
-        float *acc = (which ? acc_dv : acc_dk) + (bh * dm.max_seqlen + (int64_t)j * kBlock + hf) * kHeadDim + 32 * cq + c32;
-#pragma unroll 8
-        for (int i = 0; i < 32; ++i) {
-            const int key = 2 * i + hf;
-            const float x = tile[key * 32 + ((((c32 >> 2) ^ (key & 7)) << 2) | (c32 & 3))];
-            if (j * kBlock + key < L) unsafeAtomicAdd(acc + (int64_t)(2 * i) * kHeadDim, x);
+            if constexpr (decltype(edge)::value) {
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int m = p * kTPS + (int)(8 * v4 + 4 * hf + (kG < 4 ? r : 0)) / kG;
+                        const int tok = tok0 + list[min(m, total - 1)];
+                        s[4 * v4 + r] = j * kBlock + 32 * kh + (int)(ln & 31) > tok ? 0.f : s[4 * v4 + r];
+                    }
+            }
+            bf16x8 pf[2], sf[2];
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                if (v4 & 1) __builtin_amdgcn_sched_barrier(0);
+                const float4 d4 = *reinterpret_cast<const float4 *>(&cur.ld[32 + 8 * v4 + 4 * hf]);
+                const float dl[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    pf[v4 >> 1][4 * (v4 & 1) + r] = (__bf16)s[4 * v4 + r];
+                    sf[v4 >> 1][4 * (v4 & 1) + r] = (__bf16)(s[4 * v4 + r] * (dp[4 * v4 + r] - dl[r]));
+                }
+            }
+            xa[0] = columns_of(xg, 0);
+            xb[0] = columns_of(xq, 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (i < 7) {
+                    xa[(i + 1) & 1] = columns_of(xg, i + 1);
+                    xb[(i + 1) & 1] = columns_of(xq, i + 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                dv[i & 3] = mfma32(pf[i >> 2], xa[i & 1], dv[i & 3]);
+                dk[i & 3] = mfma32(sf[i >> 2], xb[i & 1], dk[i & 3]);
+            }
+        };
+        stage(slot0, 0);
+        for (int p = 0;;) {
+            step(slot0, slot1, p);
+            if (++p >= steps) break;
+            step(slot1, slot0, p);
+            if (++p >= steps) break;
         }
+        // ---- add to the block's sums: an instruction covers 32 channels of two keys, two cache lines ------------------------
+        if (tid == 0) ticket = draw(tries_s);             // the next item's place, under way meanwhile
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int64_t o = ((int64_t)bh * dm.max_seqlen + (int64_t)j * kBlock + 32 * kh + 4 * (ln >> 5)) * kHeadDim + (ln & 31);
+        const int left = L - (j * kBlock + 32 * kh + 4 * (ln >> 5));
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int key = 8 * (v >> 2) + (v & 3);
+            if (key < left) {
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) {
+                    unsafeAtomicAdd(acc_dk + o + key * kHeadDim + 32 * ct, dk[ct][v]);
+                    unsafeAtomicAdd(acc_dv + o + key * kHeadDim + 32 * ct, dv[ct][v]);
+                }
+            }
+        }
+        };
+        if (tok0 >= (j + 1) * kBlock) walk(std::false_type{});
+        else walk(std::true_type{});
+        __builtin_amdgcn_s_waitcnt(0);                    // the copies past the end have landed: the slots may be filled anew
+        __syncthreads();
     }
+}
+
+template <int kG>
+static void launch_dkdv(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, const BwdLayout &l, const int32_t *seqlens,
+                        const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint4 *items,
+                        float *acc_dk, float *acc_dv, hipStream_t stream) {
+    hipLaunchKernelGGL(attn_bwd_dkdv_kernel<kG>, dim3(kDkdvGroups), dim3(128), 0, stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc,
+                       null_row, bits, counters, items, l.item_cap, acc_dk, acc_dv);
 }
 
 // ---- fp32 accumulators -> bf16 gradients ------------------------------------------------------------------
@@ -759,41 +851,39 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     const BwdLayout l = bwd_layout(dm);
     char *base = reinterpret_cast<char *>(ws);
     uint4 *kvb = reinterpret_cast<uint4 *>(base + l.kvb);
-    float *delta = reinterpret_cast<float *>(base + l.delta);
     float *rowc = reinterpret_cast<float *>(base + l.rowc);
-    uint32_t *bitmap = reinterpret_cast<uint32_t *>(base + l.bitmap);
+    float *null_row = rowc + (size_t)dm.batch * dm.max_seqlen * dm.Hq * 2;
+    uint32_t *bits = reinterpret_cast<uint32_t *>(base + l.bits), *counters = reinterpret_cast<uint32_t *>(base + l.counters);
+    uint4 *items = reinterpret_cast<uint4 *>(base + l.items);
     float *acc_dk = reinterpret_cast<float *>(base + l.acc_dk), *acc_dv = reinterpret_cast<float *>(base + l.acc_dv);
     const int T = dm.max_seqlen;
-    timing_begin("bwd_zero_kernel", stream);
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3(2048), dim3(256), 0, stream, reinterpret_cast<uint4 *>(base + l.zero_begin),
-                       l.zero_bytes / sizeof(uint4));
-    timing_end(stream);
-    timing_begin("bwd_prep_kernel", stream);
-    hipLaunchKernelGGL(bwd_prep_kernel, dim3((T + 3) / 4, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, out, dout,
-                       seqlens, block_idx, lse, delta, rowc, bitmap, l.nb_cap, l.words, dq);
-    timing_end(stream);
     timing_begin("pack_bwd_kernel", stream);
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,
-                       l.nb_cap);
+                       l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, null_row);
+    timing_end(stream);
+    timing_begin("bwd_items_kernel", stream);
+    hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)l.n_seg * ((l.nb_cap + 255) / 256), dm.Hkv, dm.batch), dim3(256), 0, stream, dm,
+                       seqlens, bits, l.nb_cap, l.n_seg, l.members, counters, items, l.item_cap);
     timing_end(stream);
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_dq_group<1>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
-        case 2: err = launch_dq_group<2>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
-        case 4: err = launch_dq_group<4>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
-        case 8: err = launch_dq_group<8>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
-        case 16: err = launch_dq_group<16>(dm, q, dout, kvb, l.nb_cap, seqlens, block_idx, lse, delta, dq, stream); break;
+        case 1: err = launch_dq_group<1>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 2: err = launch_dq_group<2>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 4: err = launch_dq_group<4>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 8: err = launch_dq_group<8>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 16: err = launch_dq_group<16>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
     }
     if (err) return err;
     timing_end(stream);
     timing_begin("attn_bwd_dkdv_kernel", stream);
-    if (bwd_seg_tokens(dm) == 8192)
-        hipLaunchKernelGGL(attn_bwd_dkdv_kernel<8192>, dim3(l.nb_cap, l.words / 256 * kBwdSlices, dm.batch * dm.Hkv), dim3(256), 0,
-                           stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc, bitmap, l.words, acc_dk, acc_dv);
-    else
-        hipLaunchKernelGGL(attn_bwd_dkdv_kernel<2048>, dim3(l.nb_cap, l.words / 64 * kBwdSlices, dm.batch * dm.Hkv), dim3(256), 0,
-                           stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc, bitmap, l.words, acc_dk, acc_dv);
+    switch (dm.G) {
+        case 1: launch_dkdv<1>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream); break;
+        case 2: launch_dkdv<2>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream); break;
+        case 4: launch_dkdv<4>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream); break;
+        case 8: launch_dkdv<8>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream); break;
+        case 16: launch_dkdv<16>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream); break;
+    }
     timing_end(stream);
     timing_begin("bwd_finish_kernel", stream);
     hipLaunchKernelGGL(bwd_finish_kernel, dim3((T + 15) / 16, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, seqlens,

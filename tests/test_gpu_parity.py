@@ -831,10 +831,10 @@ def test_sparse_attn_backward(seqlens, Hq, Hkv, topk, planted):
 
 
 # Lists in no particular order with holes, most with the first block: each side of the lines of the backward's dispatch (tiles per workgroup by
-# tokens x key-value heads), per group size.
+# tokens x key-value heads), per group size; more than 2048 blocks (the membership words are built in rounds).
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [
     ([383], 16, 1, 16), ([385], 16, 1, 8), ([1025, 3], 32, 2, 16), ([770, 65], 8, 1, 16), ([2050], 16, 2, 24), ([1537], 4, 1, 64),
-    ([4100], 8, 2, 8), ([3080, 31], 2, 1, 16), ([8200], 4, 2, 5), ([3080, 1], 2, 2, 33)])
+    ([4100], 8, 2, 8), ([3080, 31], 2, 1, 16), ([8200], 4, 2, 5), ([3080, 1], 2, 2, 33), ([132001], 1, 1, 3)])
 def test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk):
     print("case attn backward dispatch", seqlens, Hq, Hkv, topk, flush=True)
     prm = binding.Params(Hq, Hkv, topk=topk)
