@@ -245,13 +245,14 @@ template <int kG, int kTiles>
 struct DqCfg {
     static constexpr bool kLds = kTiles > 1;
     static constexpr int kTPT = 16 / kG, kTok = kTiles * kTPT;
-    // LDS: union list, each wave's 32 K rows, then [q | dout][tile][ks][lane] (kLds); the merge area lies over the front
+    // LDS: each wave's 32 K rows, [q | dout][tile][ks][lane] (kLds), per column {exponent offset, D}, union list; the merge area
+    // lies over the front
     static constexpr int kRowBytes = 4 * 32 * kHeadDim * 2;
-    static size_t lds_bytes(int topk) {
-        const size_t work = UnionLds::bytes(kTok, topk) + kRowBytes + (kLds ? (size_t)2 * kTiles * 4 * 64 * sizeof(uint4) : 0);
-        const size_t merge = (size_t)4 * 8 * 64 * sizeof(float4);
-        return work > merge ? work : merge;
-    }
+    static constexpr int kQueryBytes = kLds ? 2 * kTiles * 4 * 64 * (int)sizeof(uint4) : 0;
+    static constexpr int kColumnBytes = kTiles * 16 * (int)sizeof(float2);
+    static constexpr int kUnionAt = kRowBytes + kQueryBytes + kColumnBytes;
+    static_assert(4 * 8 * 64 * sizeof(float4) <= kRowBytes, "the merge area");
+    static size_t lds_bytes(int topk) { return kUnionAt + UnionLds::bytes(kTok, topk) + 16; }
 };
 
 template <int kG, int kTiles>
@@ -265,8 +266,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     constexpr int kRing = kDqRing, kTPT = C::kTPT, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per workgroup; member bits in one word");
     extern __shared__ __align__(16) unsigned char dq_smem[];
-    __shared__ int cnt_s;
-    __shared__ float2 row_s[kTiles][16];                  // per column: exponent offset -lse log2(e), D
+    float2 *row_s = reinterpret_cast<float2 *>(dq_smem + C::kRowBytes + C::kQueryBytes);   // [tile][column]: -lse log2(e), D
+    int &cnt_s = *reinterpret_cast<int *>(dq_smem + C::kUnionAt + UnionLds::bytes(kTok, dm.topk));
     const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
     const int h = bh % dm.Hkv, b = bh / dm.Hkv;
     const int L = __builtin_amdgcn_readfirstlane(seq_len(dm, seqlens, b));
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     const float c = dm.scale_log2;
 
     bf16x8 qf[C::kLds ? 1 : kTiles][4], gf[C::kLds ? 1 : kTiles][4];
-    bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + UnionLds::bytes(kTok, dm.topk) + C::kRowBytes) + lane;   // [q | dout][tile][ks][lane]
+    bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + C::kRowBytes) + lane;   // [q | dout][tile][ks][lane]
     f32x4 acc[kTiles][8];
 #pragma unroll
     for (int u = 0; u < kTiles; ++u) {
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                 // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
                 const float ne = (ls > -INFINITY && ls < INFINITY) ? -ls * kLog2e : -INFINITY;
                 if (g == 0) {
-                    row_s[u][n] = float2{tok < L ? ne : -INFINITY, d};
+                    row_s[u * 16 + n] = float2{tok < L ? ne : -INFINITY, d};
                     // the same for dk and dv, per (token, key-value head): G exponent offsets, then G times D
                     float *rec = rowc + (((int64_t)b * dm.max_seqlen + tk) * dm.Hkv + h) * (2 * kG) + n % kG;
                     if (tok < L) {
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const UnionLds ul(dq_smem);
+    const UnionLds ul(dq_smem + C::kUnionAt);
     if (wave == 0) {
         const int x = build_union<kTok>(block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk, dm.topk,
                                         min(kTok, L - t0), b_own, ul, lane);
@@ -363,40 +364,32 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     };
     // this wave's K rows of the half in LDS: where the lane's piece of key 16t + n goes, and where its four rows for the
     // transposing load begin (keys 16t + 4g .. +3, channels 16dt ..: ^ (dt << 5))
-    char *kt = reinterpret_cast<char *>(dq_smem + UnionLds::bytes(kTok, dm.topk)) + wave * (C::kRowBytes / 4);
-    // (both formed anew where they are used: with four tiles the registers are all taken)
-    auto kt_put = [&]() __attribute__((always_inline)) {       // ^ (ks << 6)
-        uint32_t ln = lane;
-        asm volatile("" : "+v"(ln));
-        return (ln & 15) * 256u + (((ln >> 4) ^ (uint32_t)bwd_swizzle((int)(ln & 15))) << 4);
-    };
-    auto kt_get = [&]() __attribute__((always_inline)) {
-        uint32_t ln = lane;
-        asm volatile("" : "+v"(ln));
-        const uint32_t row = 4u * (ln >> 4) + ((ln & 15) >> 2);
-        return row * 256u + ((((ln & 3) >> 1) ^ (uint32_t)bwd_swizzle((int)row)) << 4) + 8u * (ln & 1);
-    };
+    char *kt = reinterpret_cast<char *>(dq_smem) + wave * (C::kRowBytes / 4);
+    const uint32_t kt_put = (uint32_t)n * 256u + (uint32_t)((g ^ bwd_swizzle(n)) << 4);     // ^ (ks << 6)
+    const uint32_t kt_row = 4u * g + (n >> 2);
+    const uint32_t kt_get = kt_row * 256u + ((((n & 3) >> 1) ^ (uint32_t)bwd_swizzle((int)kt_row)) << 4) + 8u * (n & 1);
 
     __builtin_amdgcn_s_waitcnt(0);                        // nothing of the prologue may still be pending inside the ring loop
-    uint2 e_cur = {0u, 0u}, e_nxt = {0u, 0u};
+    uint32_t blk = 0u, bits = 0u;                         // the block at hand and its member bits
     if (wave < cnt) {
-        e_cur = union_entry(wave);
-        e_nxt = union_entry(wave + 4);
-        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
+        const uint2 e = union_entry(wave);
+        blk = __builtin_amdgcn_readfirstlane(e.x);
+        bits = __builtin_amdgcn_readfirstlane(e.y);
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(blk);
 #pragma unroll
         for (int unit = 0; unit < kRing; ++unit) issue(unit, bp);
     }
-    for (int ci = wave; ci < cnt; ci += 4) {
-        const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
-        const uint32_t bits = __builtin_amdgcn_readfirstlane(e_cur.y);
-        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x), bn = block_rsrc(e_nxt.x);
-        e_cur = e_nxt;
-        e_nxt = union_entry(ci + 8);
-        const int key0 = blk * kBlock;
-        const bool edge = blk == b_own;
+    // `edge`: the tokens' own block, the last of the union: the only one with the causal edge
+    auto block = [&](auto edge, int ci) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t bp = block_rsrc(blk);
+        __amdgpu_buffer_rsrc_t bn = bp;                   // the next block's, known from the second half on
+        const int key0 = (int)blk * kBlock;
         uint32_t tb[kTiles];                              // member bits of the tile's tokens
 #pragma unroll
-        for (int u = 0; u < kTiles; ++u) tb[u] = (bits >> (u * kTPT)) & ((1u << kTPT) - 1u);
+        for (int u = 0; u < kTiles; ++u) {
+            tb[u] = (bits >> (u * kTPT)) & ((1u << kTPT) - 1u);
+            asm volatile("" : "+s"(tb[u]));               // (its tests stay scalar)
+        }
         auto refill = [&](int unit) __attribute__((always_inline)) {
             if (unit + kRing < kDqUnits) issue(unit + kRing, bp);
             else issue(unit + kRing - kDqUnits, bn);      // (a harmless re-read of this block at the tail)
@@ -408,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
             return a;
         };
         auto grad = [&](int u, int hs, const f32x4 (&s)[2], const f32x4 (&dp)[2], bf16x8 &dsf) __attribute__((always_inline)) {
-            const float2 r = row_s[u][n];
+            const float2 r = row_s[u * 16 + n];
             const float ne = (kTPT == 1 || ((tb[u] >> tn) & 1u)) ? r.x : -INFINITY;
             const int tok = t0 + u * kTPT + tn;
 #pragma unroll
@@ -416,18 +409,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     float p = fast_exp2(__builtin_fmaf(s[t][j], c, ne));
-                    if (edge && key0 + 32 * hs + 16 * t + 4 * g + j > tok) p = 0.f;
+                    if (decltype(edge)::value && key0 + 32 * hs + 16 * t + 4 * g + j > tok) p = 0.f;
                     dsf[4 * t + j] = (__bf16)(p * (dp[t][j] - r.y));
                 }
         };
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
+            if (hs == 1) {
+                const uint2 e = union_entry(ci + 4);
+                blk = __builtin_amdgcn_readfirstlane(e.x);
+                bits = __builtin_amdgcn_readfirstlane(e.y);
+                bn = block_rsrc(blk);
+            }
             bf16x8 dsf[kTiles];
             auto keep = [&](int r) __attribute__((always_inline)) {
-                const uint32_t put = kt_put();
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
-                    *reinterpret_cast<u32x4 *>(kt + (put ^ (uint32_t)(ks << 6)) + r * 4096) = ring[(4 * hs + r) % kRing][ks];
+                    *reinterpret_cast<u32x4 *>(kt + (kt_put ^ (uint32_t)(ks << 6)) + r * 4096) = ring[(4 * hs + r) % kRing][ks];
             };
             if constexpr (C::kLds) {
                 keep(0);
@@ -441,6 +439,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                     for (int ks = 0; ks < 4; ++ks) x[ks] = ql[(u * 4 + ks) * 64];
 #pragma unroll
                     for (int r = 0; r < 2; ++r) s[r] = product(4 * hs + r, x);
+                    if constexpr (kTiles > 2) __builtin_amdgcn_sched_barrier(0);   // (the next loads reuse x: no register to spare)
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) x[ks] = ql[((kTiles + u) * 4 + ks) * 64];
 #pragma unroll
@@ -469,10 +468,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 #pragma unroll
             for (int d4 = 0; d4 < 8; d4 += 4) {
                 bf16x8 kf[4];
-                const uint32_t get = kt_get();
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const uint32_t at = get ^ (uint32_t)((d4 + i) << 5);
+                    const uint32_t at = kt_get ^ (uint32_t)((d4 + i) << 5);
                     const s16x4 x0 = lds_read_tr16(kt + at), x1 = lds_read_tr16(kt + at + 4096);
                     kf[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
@@ -484,7 +482,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                 }
             }
         }
-    }
+    };
+    const int own_at = cnt > 0 && ul.list[max(cnt - 1, 0)].x == (uint32_t)b_own ? cnt - 1 : cnt;
+    for (int ci = wave; ci < own_at; ci += 4) block(std::false_type{}, ci);
+    if (own_at < cnt && (own_at & 3) == wave) block(std::true_type{}, own_at);
     // ---- add the four wavefronts' sums, a tile at a time, and write: lane holds channels 16*dt + 4*g .. +3 of column n ----
     const float scale = c * kLn2;
     float4 *po = reinterpret_cast<float4 *>(dq_smem);     // [wave][dt][lane]
