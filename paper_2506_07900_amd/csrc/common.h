@@ -111,6 +111,14 @@ __device__ inline float xgroup_max(float v) {
 __device__ inline float xgroup_sum(float v) {
     return xgroup_reduce(v, [](float a, float b) { return a + b; });
 }
+// Sum of x w over the four groups, in the first of them only: one product of each pair unrounded (an fma).
+__device__ inline float xgroup_dot(float x, float w) {
+    const float p = x * w;
+    const u32x2_t a = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    const float v = __builtin_fmaf(x, w, __uint_as_float(a[1]));              // even groups: with the next one's product
+    const u32x2_t b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
 // Reduce over the 16 lanes of a group (a DPP row): four rotations, every lane ends with the result.
 template <int kCtrl>

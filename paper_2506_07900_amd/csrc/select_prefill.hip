@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void select_lse_kernel(Dims dm, Tensor q, Tens
     for (int mt = 0; mt < C::kTiles; ++mt) {
         const float M = xgroup_max(m_run[mt]);
         const float m_use = M == -INFINITY ? 0.f : M;
-        const float S = xgroup_sum(s_run[mt] * fast_exp2(m_run[mt] - m_use));
+        const float S = xgroup_dot(s_run[mt], fast_exp2(m_run[mt] - m_use));
         const int tok = tok_wave0 + mt * C::kTokPerTile + n / G;
         if (g == 0 && tok < L)
             lse2[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * G + n % G] = M + fast_log2(S);

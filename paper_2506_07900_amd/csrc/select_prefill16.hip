@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void select_lse16_kernel(Dims dm, Tensor q,
         const float m_lane = (neg_m[mt] != neg_m[mt]) ? -INFINITY : -neg_m[mt];
         const float M = xgroup_max(m_lane);
         const float m_use = M == -INFINITY ? 0.f : M;
-        const float S = xgroup_sum(s_run[mt] * fast_exp2(m_lane - m_use));
+        const float S = xgroup_dot(s_run[mt], fast_exp2(m_lane - m_use));
         const int tok = t0 + mt;
         float lse = M + fast_log2(S);
         // approximate mode: rho times fewer kernels were summed (log2 rho is an integer); a query
