@@ -42,7 +42,7 @@ __device__ inline uint32_t xcd_contiguous_id(uint32_t bid, uint32_t n) {
 __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor v,
                                                        const int32_t *__restrict__ seqlens,
                                                        uint4 *__restrict__ kvp, int32_t nb_cap, Tensor out,
-                                                       float *__restrict__ lse) {
+                                                       float *__restrict__ lse, uint32_t *__restrict__ marks) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -60,6 +60,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
     const int sc = tid & 15, sr = tid >> 4;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
     const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
+    uint32_t top = 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = sr + 16 * i, t = j * kBlock + r;
@@ -70,7 +71,10 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
         }
         *reinterpret_cast<uint4 *>(&Ks[r * 136 + 8 * sc]) = xk;
         *reinterpret_cast<uint4 *>(&Vs[r * 136 + 8 * sc]) = xv;
+        if (dm.G < 16) top = fold_magnitude(fold_magnitude(top, xk), xv);
     }
+    const uint64_t marked = __ballot(is_nonfinite(top));  // (see union_mark; with one token per tile nobody asks)
+    if (dm.G < 16 && (tid & 63) == 0) marks[(((int64_t)b * dm.Hkv + h) * nb_cap + j) * 4 + (tid >> 6)] = marked != 0ull;
     __syncthreads();
     uint4 *dst = kvp + ((((int64_t)b * dm.Hkv + h) * nb_cap + j) * kPackedBlockU4);
 #pragma unroll
@@ -157,7 +161,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
                                                             Tensor out, float *__restrict__ lse,
-                                                            int32_t slots) {
+                                                            int32_t slots, const uint4 *__restrict__ marks) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     constexpr int kNU = 4, kTPT = C::kTokPerTile, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per wavefront; member bits in one word");
@@ -193,10 +197,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                 else qf[u][ks] = x;
             }
         }
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) o[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        neg_m[u] = __builtin_nanf("");
-        l_run[u] = 0.f;
     }
     const UnionLds ul(attn_smem + (kSplit > 1 ? 0 : wave * UnionLds::bytes(kTok, dm.topk)));
     int cnt = 0;
@@ -263,6 +263,19 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         l_run[u] += ps;
     };
 
+    // One walk; if it met a marked block (see union_mark), another for each token of a tile.  (A wavefront that works alone
+    // has one token per tile.)
+    static_assert(kSplit > 1 || kTPT == 1, "the flag of the workgroup's waves is exchanged in the merge");
+    __shared__ int careful_s[4];
+    for (int pass = 0;; ++pass) {
+    const uint32_t slot_mask = pass ? 1u << (pass - 1) : (1u << kTPT) - 1u;
+#pragma unroll
+    for (int u = 0; u < kTiles; ++u) {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) o[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        neg_m[u] = __builtin_nanf("");
+        l_run[u] = 0.f;
+    }
     // Everything loaded so far (queries, block lists) has to land before the ring starts: the
     // compiler's wait-count bookkeeping otherwise merges those pending loads into the loop and
     // waits for ALL outstanding loads at the top of every iteration, which defeats the ring.
@@ -270,12 +283,18 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
     constexpr int kStep = kSplit;                        // the waves of a splitting workgroup take every kSplit-th block
     const int first = kSplit > 1 ? wave : 0;
     uint2 e_cur = {0u, 0u}, e_nxt = {0u, 0u};
+    bool careful = false;                                // a block of this wavefront's is marked
     if (first < cnt) {
+        const uint4 *mk = marks + ((int64_t)b * dm.Hkv + h) * nb_cap;
+        uint4 m = {0u, 0u, 0u, 0u};
+        if constexpr (kTPT > 1) m = union_mark(mk, ul, first, kStep, cnt, lane);
+        __builtin_amdgcn_sched_barrier(0);
         e_cur = union_entry(first);
         e_nxt = union_entry(first + kStep);
         const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
 #pragma unroll
         for (int unit = 0; unit < kNU; ++unit) issue(unit, bp);
+        if constexpr (kTPT > 1) careful = union_marked(m, mk, ul, first, kStep, cnt, lane);
     }
     for (int ci = first; ci < cnt; ci += kStep) {
         const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
@@ -287,7 +306,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         const bool edge = blk == b_own;                  // the last, partial block of a sequence is its last tokens' own
         uint32_t tb[kTiles];                             // member bits of the tile's tokens
 #pragma unroll
-        for (int u = 0; u < kTiles; ++u) tb[u] = (bits >> (u * kTPT)) & ((1u << kTPT) - 1u);
+        for (int u = 0; u < kTiles; ++u) tb[u] = (bits >> (u * kTPT)) & slot_mask;
 #pragma unroll
         for (int hs = 0; hs < 2; ++hs) {
             // ---- S^T = K . Q^T for 32 keys, one key tile per unit ------------------------------
@@ -360,6 +379,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         // wave w combines channel tiles 2w, 2w+1 of every column --------------------------------------------------
         float4 *po = reinterpret_cast<float4 *>(attn_smem + C::merge_at(dm.topk));   // [wave][dt][lane]
         float2 *pm = reinterpret_cast<float2 *>(po + 4 * 8 * 64);                    // [wave][lane]
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                      // (what follows is not formed ahead of the walk: no register to spare there)
+        const int lane = ln, n = ln & 15, g = ln >> 4, tn = n / kG;
+        const bool writes = pass == 0 || tn == pass - 1;
+        if (kTPT > 1 && lane == 0) careful_s[wave] = careful;
 #pragma unroll
         for (int u = 0; u < kTiles; ++u) {
             if (u) __syncthreads();
@@ -381,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                 f[w] = m4[w].x > -INFINITY ? fast_exp2(m4[w].x - M) : 0.f;
                 l_tot += f[w] * m4[w].y;
             }
-            if (tok < L) {
+            if (tok < L && writes) {
                 const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
                 __bf16 *op = out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)(h * kG + n % kG) * out.sh + 4 * g;
 #pragma unroll
@@ -403,7 +427,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                         l_tot > 0.f ? (fast_log2(l_tot) + M) * kLn2 : -INFINITY;
             }
         }
-        return;
+        if (kTPT == 1 || pass == kTPT || !(careful_s[0] | careful_s[1] | careful_s[2] | careful_s[3])) return;
+        __syncthreads();                                  // everyone is past the merge area and the flags
+        continue;
     }
     // ---- normalise and write: lane holds channels 16*dt + 4*g .. +3 of column n -----------------
 #pragma unroll
@@ -423,6 +449,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         if (g == 0)
             lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * kG + n % kG] =
                 l_tot > 0.f ? (fast_log2(l_tot) - neg_m[u]) * kLn2 : -INFINITY;
+    }
+    return;
     }
 }
 
@@ -589,9 +617,14 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(Dims dm, Te
     }
 }
 
-size_t attn_prefill_ws_bytes(const Dims &dm) {
+static size_t packed_bytes(const Dims &dm) {
     const size_t nb_cap = ((size_t)dm.max_seqlen + kBlock - 1) / kBlock;
     return (size_t)dm.batch * dm.Hkv * nb_cap * kPackedBlockU4 * sizeof(uint4);
+}
+// the packed blocks, then the blocks' marks
+size_t attn_prefill_ws_bytes(const Dims &dm) {
+    const size_t marks = packed_bytes(dm) / (kPackedBlockU4 * sizeof(uint4)) * sizeof(uint4);
+    return packed_bytes(dm) + (marks + 255) / 256 * 256;
 }
 
 // Workgroups go to the XCDs round-robin by their id.  A sequence's tiles are dealt to the XCDs in runs of kRun, last
@@ -601,7 +634,7 @@ size_t attn_prefill_ws_bytes(const Dims &dm) {
 
 template <int kG, int kTiles, int kSplit>
 static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
-                               const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
+                               const int32_t *block_idx, Tensor out, float *lse, const uint4 *marks, hipStream_t stream) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTokPerWg - 1) / C::kTokPerWg;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
@@ -613,7 +646,7 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
         if (e != hipSuccess) return (int)e;
     }
     hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
-                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
+                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots, marks);
     return 0;
 }
 
@@ -628,15 +661,15 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
 // only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
 template <int kG>
 static int launch_attn_group(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
-                             const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
+                             const int32_t *block_idx, Tensor out, float *lse, const uint4 *marks, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG == 16)
-        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
     if constexpr (kG > 1)                                // (member bits of at most 32 tokens)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
-    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
+    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
 }
 
 int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int32_t *seqlens,
@@ -644,9 +677,10 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
     const int32_t nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
     if (nb_cap <= 0 || dm.batch <= 0) return 0;
     uint4 *kvp = reinterpret_cast<uint4 *>(ws);
+    uint32_t *marks = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(ws) + packed_bytes(dm));
     timing_begin("pack_kv_kernel", stream);
     hipLaunchKernelGGL(pack_kv_kernel, dim3(nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v,
-                       seqlens, kvp, nb_cap, out, lse);
+                       seqlens, kvp, nb_cap, out, lse, marks);
     timing_end(stream);
     if (dm.shared_q) {                                   // one block list per query block (comparison variant)
         const int32_t n_tiles = (dm.max_seqlen + 7) / 8;
@@ -656,14 +690,15 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
         timing_end(stream);
         return (int)hipGetLastError();
     }
+    const uint4 *mk = reinterpret_cast<const uint4 *>(marks);
     timing_begin("attn_prefill_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
+        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
+        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
+        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
+        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
     }
     if (err) return err;
     timing_end(stream);

@@ -1004,6 +1004,44 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# Tokens that share a tile with one that selected a block of infinities and NaNs must not see them: the rows that do not list
+# the block (or list another head's) are what they are with ordinary values there, and its own rows stay reachable.
+@pytest.mark.parametrize("T,Hq,Hkv", [(300, 4, 1), (770, 8, 1), (1700, 4, 2), (4100, 8, 2), (300, 1, 1), (3100, 2, 2), (600, 16, 1)])
+@pytest.mark.parametrize("where", ["k", "v"])
+def test_values_of_a_block_reach_only_the_tokens_that_selected_it(T, Hq, Hkv, where):
+    print("case non-finite block", T, Hq, Hkv, where, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=3)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, do = (torch.randn((1, T, Hq, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((1, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    own = (torch.arange(T, device="cuda") // 64)[None, :].expand(Hkv, T)
+    lists = torch.arange(T, device="cuda")[None, :] % 3 == 1              # every third token selects block 1
+    idx = torch.stack([torch.zeros_like(own), torch.where(lists, torch.ones_like(own), torch.full_like(own, -1)), own], -1)
+    idx = torch.where((idx == 0) & (own == 0)[..., None] & (torch.arange(3, device="cuda") < 1), torch.full_like(idx, -1), idx)
+    idx = torch.where((torch.arange(3, device="cuda") == 1) & (own <= 1)[..., None], torch.full_like(idx, -1), idx)[None].to(torch.int32).contiguous()
+    sl = dev_i32([T])
+
+    def both(k, v):
+        out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+        clean = torch.nan_to_num(out, 0.0, 0.0, 0.0), torch.nan_to_num(lse, 0.0, 0.0, 0.0)
+        return out, lse, binding.sparse_attn_bwd(prm, q, k, v, clean[0], do, clean[1], sl, T, idx)[0]
+
+    want = both(k, v)
+    k2, v2 = k.clone(), v.clone()
+    bad = k2 if where == "k" else v2
+    bad[:, :, 64 + 3, 5], bad[:, :, 64 + 40, 17], bad[:, :, 64 + 63] = float("nan"), float("inf"), -float("inf")
+    got = both(k2, v2)
+    torch.cuda.synchronize()
+    free = ~lists[0] & (own[0] != 1)                                       # neither listed nor the own block
+    assert bool((~torch.isfinite(got[0][:, ~free].float())).any())
+    for x, y, name in zip(got, want, ("out", "lse", "dq")):
+        x, y = x[:, free].double(), y[:, free].double()
+        assert bool(torch.isfinite(x).all()), name
+        # the same sums with the reference exponent perhaps placed differently: each side is within a bf16 rounding of the result
+        # (outputs and gradients) and of the probabilities in it (whose errors average out over 64 keys and more), or fp32 for lse
+        assert bool(((x - y).abs() <= (1e-4 if name == "lse" else 2.0 ** -7 * y.abs() + 2.0 ** -7 * y.pow(2).mean().sqrt())).all()), name
+
+
 # Caches of up to 8192 tokens take the one-kernel selection: both sides of each of its lines (16, 32, 64, 128 blocks), the
 # three-launch form for many rows, the long path from 8193 tokens on and around a list of 128 blocks, lengths that complete
 # a kernel, are shorter than one, or select everything.
