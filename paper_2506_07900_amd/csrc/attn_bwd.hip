@@ -67,7 +67,7 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.item_cap = (int32_t)((BH * l.n_seg + kQueues - 1) / kQueues * per_seg);
     size_t o = 0;
     l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
-    l.marks = o;    o += al256(BH * l.nb_cap * sizeof(uint4));
+    l.marks = o;    o += al256(dm.G == 16 ? 0 : BH * l.nb_cap * sizeof(uint4));
     l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
     l.bits = o;     o += al256(BH * l.words * l.nb_cap * sizeof(uint32_t));
     l.acc_dk = o;   o += al256(BH * T * kHeadDim * sizeof(float));

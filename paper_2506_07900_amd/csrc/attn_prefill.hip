@@ -621,9 +621,9 @@ static size_t packed_bytes(const Dims &dm) {
     const size_t nb_cap = ((size_t)dm.max_seqlen + kBlock - 1) / kBlock;
     return (size_t)dm.batch * dm.Hkv * nb_cap * kPackedBlockU4 * sizeof(uint4);
 }
-// the packed blocks, then the blocks' marks
+// the packed blocks, then the blocks' marks (G < 16: tiles of several tokens)
 size_t attn_prefill_ws_bytes(const Dims &dm) {
-    const size_t marks = packed_bytes(dm) / (kPackedBlockU4 * sizeof(uint4)) * sizeof(uint4);
+    const size_t marks = dm.G == 16 ? 0 : packed_bytes(dm) / (kPackedBlockU4 * sizeof(uint4)) * sizeof(uint4);
     return packed_bytes(dm) + (marks + 255) / 256 * 256;
 }
 
