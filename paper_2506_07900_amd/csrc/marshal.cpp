@@ -109,6 +109,10 @@ struct Result {
     }
 };
 
+// The kernels write every row of a tensor shaped like q (like k): it has no heads or channels beyond the parameters'.
+bool q_shaped(const at::Tensor &q, const infllmv2_params *prm) { return q.size(2) == prm->n_q_heads && q.size(3) == prm->head_dim; }
+bool k_shaped(const at::Tensor &k, const infllmv2_params *prm) { return k.size(1) == prm->n_kv_heads && k.size(3) == prm->head_dim; }
+
 at::TensorOptions like(const at::Tensor &t, at::ScalarType type) { return at::TensorOptions().dtype(type).device(t.device()); }
 
 // The caller's workspace, or scratch that lives until the call has been enqueued (the allocator reuses it in stream order).
@@ -160,7 +164,7 @@ PyObject *compress_keys(Args a) {
     if (ck.make()) {
         const int64_t n = T < prm->kernel_size ? 0 : (T - prm->kernel_size) / prm->kernel_stride + 1;
         const at::IntArrayRef::value_type shape[4] = {k.size(0), k.size(1), std::max<int64_t>(n, 1), k.size(3)};
-        fill = n > 0 && n_new <= 0;                       // otherwise the kernel does not visit every row
+        fill = n > 0 && n_new <= 0 && k_shaped(k, prm);   // otherwise the kernel does not visit every row
         ck.own = fill ? at::empty(shape, like(k, at::kBFloat16)) : at::zeros(shape, like(k, at::kBFloat16));
     }
     const infllmv2_tensor kd = cache(k), cd = ck.make() ? cache(ck.own) : cache(ck.given, "ck");
@@ -244,7 +248,7 @@ PyObject *sparse_attn_prefill(Args a) {
     Result out(a[7]), lse(a[8]);
     // rows past max_seqlen of a longer tensor, and a tensor next to one of the caller's (whose other rows stay as they
     // are), are cleared by torch; else the call clears what its kernels do not write
-    const bool fill = out.make() && lse.make() && q.size(1) <= T;
+    const bool fill = out.make() && lse.make() && q.size(1) <= T && q_shaped(q, prm);
     if (out.make()) out.own = fill ? at::empty_like(q) : at::zeros_like(q);
     if (lse.make())
         lse.own = fill ? at::empty({B, T, prm->n_q_heads}, like(q, at::kFloat)) : at::zeros({B, T, prm->n_q_heads}, like(q, at::kFloat));
@@ -265,7 +269,7 @@ PyObject *sparse_attn_decode(Args a) {
     const at::Tensor &q = bf16_4d(a[1], "q");
     const int32_t T = integer(a[5]), B = static_cast<int32_t>(q.size(0));
     Result out(a[7]), lse(a[8]);
-    if (out.make()) out.own = q.size(1) == 1 ? at::empty_like(q) : at::zeros_like(q);           // (every row is written)
+    if (out.make()) out.own = q.size(1) == 1 && q_shaped(q, prm) ? at::empty_like(q) : at::zeros_like(q);           // (every row is written)
     if (lse.make()) lse.own = at::empty({B, prm->n_q_heads}, like(q, at::kFloat));
     const Workspace ws(a[9], a[9] == Py_None ? lib.workspace_bytes(INFLLMV2_OP_ATTN_DECODE, prm, B, T) : 0, q);
     const infllmv2_tensor qd = rows(q), kd = cache(a[2], "k"), vd = cache(a[3], "v"),
@@ -293,7 +297,7 @@ PyObject *sparse_attn_verify(Args a) {
     const at::Tensor &q = bf16_4d(a[1], "q");
     const int32_t T = integer(a[5]), B = static_cast<int32_t>(q.size(0)), n = static_cast<int32_t>(q.size(1));
     Result out(a[8]), lse(a[9]);
-    if (out.make()) out.own = at::empty_like(q);
+    if (out.make()) out.own = q_shaped(q, prm) ? at::empty_like(q) : at::zeros_like(q);
     if (lse.make()) lse.own = at::empty({B, n, prm->n_q_heads}, like(q, at::kFloat));
     const uint64_t *mask = tree_mask(a[7], B, n);
     const Workspace ws(a[10], a[10] == Py_None ? lib.verify_workspace_bytes(INFLLMV2_OP_ATTN_VERIFY, prm, B, T, n) : 0, q);
@@ -314,7 +318,7 @@ PyObject *decode_step(Args a) {
     const int32_t T = integer(a[8]), B = static_cast<int32_t>(q.size(0));
     Result idx(a[9]), out(a[10]), lse(a[11]);             // every row of every result is written
     if (idx.make()) idx.own = at::empty({B, prm->n_kv_heads, 1, prm->topk}, like(q, at::kInt));
-    if (out.make()) out.own = q.size(1) == 1 ? at::empty_like(q) : at::zeros_like(q);
+    if (out.make()) out.own = q.size(1) == 1 && q_shaped(q, prm) ? at::empty_like(q) : at::zeros_like(q);
     if (lse.make()) lse.own = at::empty({B, prm->n_q_heads}, like(q, at::kFloat));
     const Workspace ws(a[12], a[12] == Py_None ? lib.workspace_bytes(INFLLMV2_OP_DECODE_STEP, prm, B, T) : 0, q);
     const infllmv2_tensor qd = rows(q), kn = cache(a[2], "k_new"), vn = cache(a[3], "v_new"), k = cache(a[4], "k"),
@@ -336,7 +340,7 @@ PyObject *verify_step(Args a) {
     const int32_t T = integer(a[8]), B = static_cast<int32_t>(q.size(0)), n = static_cast<int32_t>(q.size(1));
     Result idx(a[10]), out(a[11]), lse(a[12]);            // every row of every result is written
     if (idx.make()) idx.own = at::empty({B, prm->n_kv_heads, n, prm->topk}, like(q, at::kInt));
-    if (out.make()) out.own = at::empty_like(q);
+    if (out.make()) out.own = q_shaped(q, prm) ? at::empty_like(q) : at::zeros_like(q);
     if (lse.make()) lse.own = at::empty({B, n, prm->n_q_heads}, like(q, at::kFloat));
     const uint64_t *mask = tree_mask(a[9], B, n);
     const Workspace ws(a[13], a[13] == Py_None ? lib.verify_workspace_bytes(INFLLMV2_OP_VERIFY_STEP, prm, B, T, n) : 0, q);
@@ -357,7 +361,8 @@ PyObject *sparse_attn_bwd(Args a) {
     const at::Tensor &q = bf16_4d(a[1], "q"), &k = bf16_4d(a[2], "k"), &v = bf16_4d(a[3], "v");
     const int32_t T = integer(a[8]), B = static_cast<int32_t>(q.size(0));
     Result dq(a[10]), dk(a[11]), dv(a[12]);
-    const bool fill = dq.make() && dk.make() && dv.make() && q.size(1) <= T && k.size(2) <= T && v.size(2) <= T;
+    const bool fill = dq.make() && dk.make() && dv.make() && q.size(1) <= T && k.size(2) <= T && v.size(2) <= T && q_shaped(q, prm) &&
+                      k_shaped(k, prm) && k_shaped(v, prm) && k.size(0) == B && v.size(0) == B;
     if (dq.make()) dq.own = fill ? at::empty_like(q) : at::zeros_like(q);
     if (dk.make()) dk.own = fill ? at::empty_like(k) : at::zeros_like(k);
     if (dv.make()) dv.own = fill ? at::empty_like(v) : at::zeros_like(v);

@@ -830,6 +830,28 @@ def test_sparse_attn_backward(seqlens, Hq, Hkv, topk, planted):
         assert eq <= 1.0 and ek <= 1.0 and ev <= 1.0
 
 
+def test_results_made_by_the_call_are_clear_beyond_the_heads():
+    # tensors with more heads than the parameters say: what no kernel visits reads 0 in the results the binding allocates
+    Hq, Hkv, T = 4, 2, 300
+    prm = binding.Params(Hq, Hkv, topk=8)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    q, do = (torch.randn((1, T, Hq + 2, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((2, Hkv + 1, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    sl = dev_i32([T])
+    junk = [torch.full((n,), 0x41, dtype=torch.uint8, device="cuda") for n in (1 << 17, 1 << 20, 1 << 22, 1 << 24) for _ in range(8)]
+    torch.cuda.synchronize()
+    del junk                                             # the allocator hands these bytes out again
+    ck = binding.compress_keys(prm, k[:1], sl, T)
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    dq, dk, dv = binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, sl, T, idx)
+    o1 = binding.sparse_attn_decode(prm, q[:, -1:], k, v, sl, T, idx[:, :, -1:].contiguous())[0]
+    o2 = binding.sparse_attn_verify(prm, q[:, -2:], k, v, sl, T, idx[:, :, -2:].contiguous())[0]
+    torch.cuda.synchronize()
+    for t in (ck[:, Hkv:], out[:, :, Hq:], dq[:, :, Hq:], dk[:, Hkv:], dv[:, Hkv:], dk[1:], dv[1:], o1[:, :, Hq:], o2[:, :, Hq:]):
+        assert bool((t == 0).all())
+
+
 # Lists in no particular order with holes, most with the first block: each side of the lines of the backward's dispatch (tiles per workgroup by
 # tokens x key-value heads), per group size; more than 2048 blocks (the membership words are built in rounds).
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [
