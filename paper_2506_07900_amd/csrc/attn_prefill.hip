@@ -127,13 +127,13 @@ constexpr int kNone = 0x7fffffff;
 
 // probabilities 2^(s*c + ne) of 32 keys (two key tiles) of one token in MFMA B layout, and their sum
 __device__ __forceinline__ float half_probs(const f32x4 (&s)[2], float c, float ne, bf16x8 &p8) {
-    float sum = 0.f;
+    float sum;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float p = fast_exp2(__builtin_fmaf(s[t][j], c, ne));
-            sum += p;
+            sum = t + j ? sum + p : p;
             p8[4 * t + j] = (__bf16)p;
         }
     return sum;

@@ -13,6 +13,12 @@
 // VALU work only overlap on this hardware when they alternate inside one instruction stream, so
 // both passes are software-pipelined by hand: the MFMAs of kernel tile t are issued in the same
 // basic block as the exponentials / reductions of tile t-1.
+//
+// What bounds them: vector issue (75 % of the cycles with the MFMAs' own issue slots; matrix pipe 42 - 56 %) at a
+// clock that the matrix work holds at 2.1 - 2.2 GHz.  So what a tile costs is its vector instructions: scalar tile
+// bounds (wave index made uniform), pooling on bit patterns (move + maximum in one DPP instruction), sums that begin with
+// their first term and one overflow test per half took pass 1 / pass 2 from 270 / 372 to 267 / 361 us at 32K tokens and
+// from 3.73 / 4.84 to 3.62 / 4.64 ms at 128K.  A third fragment buffer (prefetch two tiles ahead) changes nothing: 3.62 / 4.69.
 #include "common.h"
 
 namespace infllmv2 {
@@ -27,12 +33,10 @@ __device__ inline int n_visible_lse(int i, int rho) {
     return rho > 1 ? num_coarse(nf, rho) : nf;
 }
 
-// DPP helpers on floats (row = 16 lanes).  Lanes whose source falls outside the row keep `old`.
+// DPP moves (row = 16 lanes).  Lanes whose source falls outside the row keep `old`.
 template <int kCtrl>
-__device__ inline float dpp_f32(float old, float src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
-                                                                  __builtin_bit_cast(int, src), kCtrl,
-                                                                  0xf, 0xf, false));
+__device__ inline int dpp_i32(int old, int src) {
+    return __builtin_amdgcn_update_dpp(old, src, kCtrl, 0xf, 0xf, false);
 }
 constexpr int kRowShl1 = 0x101, kRowShl2 = 0x102, kRowShr1 = 0x111, kRowRor1 = 0x121;
 
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void select_lse16_kernel(Dims dm, Tensor q,
     const int b = blockIdx.x / (n_tiles * dm.Hkv);
     int32_t L = seqlens[b];
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (tile bounds and addresses stay scalar)
     const int t0 = tile * kTokPerWg16 + wave * kMT;
     if (t0 >= L) return;
     const int n = lane & 15, g = lane >> 4;
@@ -169,15 +173,18 @@ __global__ __launch_bounds__(256, 2) void select_lse16_kernel(Dims dm, Tensor q,
 
     auto finish = [&](const f32x4 (&z)[kHalf], int base) {
         float acc[kHalf];
-        bool bad = false;
 #pragma unroll
         for (int u = 0; u < kHalf; ++u) {
-            float a = 0.f;
+            float a = fast_exp2(__builtin_fmaf(z[u][0], c, neg_m[base + u]));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a += fast_exp2(__builtin_fmaf(z[u][j], c, neg_m[base + u]));
+            for (int j = 1; j < 4; ++j) a += fast_exp2(__builtin_fmaf(z[u][j], c, neg_m[base + u]));
             acc[u] = a;
-            bad |= !(a <= 0x1p60f);                      // too large, inf, or NaN (no reference yet)
         }
+        // too large, inf, or NaN (no reference yet): non-negative floats and NaN order like unsigned integers
+        uint32_t top = 0u;
+#pragma unroll
+        for (int u = 0; u < kHalf; ++u) top = max(top, __float_as_uint(acc[u]));
+        const bool bad = top > __float_as_uint(0x1p60f);
         if (__any(bad)) {                                // rare: re-base on this tile's own maximum
 #pragma unroll
             for (int u = 0; u < kHalf; ++u)
@@ -291,7 +298,7 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
     const int b = blockIdx.x / (n_tiles * dm.Hkv);
     int32_t L = seqlens[b];
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (tile bounds and addresses stay scalar)
     const int t0 = tile * kTokPerWg16 + wave * kMT;
     if (kFused && dm.fill) fill_block_rows(dm, b, h, t0, kMT, L, block_idx, lane);
     if (t0 >= L) return;
@@ -321,19 +328,19 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
         for (int i = lane; i < kMT * 16; i += 64)
             nls[i] = (t0 + (i >> 4) < L) ? -lse2[((int64_t)b * dm.max_seqlen + t0 + (i >> 4)) * dm.Hq + h * 16 + (i & 15)] : 0.f;
         __builtin_amdgcn_wave_barrier();
-        const int nt_pipe = min(n_visible16(t0) >> 4, nt_all);                // tiles needing no mask
         const uint4 *ckp_head = ckp + ((int64_t)b * dm.Hkv + h) * nt_cap * 256;
         // packed per-token values: 16-lane group g of half i belongs to token 4i+g
-        float prev_v[2] = {-INFINITY, -INFINITY};
+        constexpr int kNegInf = (int)0xff800000u;
+        int prev_v[2] = {kNegInf, kNegInf};
         float *Rrow[2];
         bool wr[2];
-        int nvis_tok[2];
+        int nvis_tok[2];                                                      // visible kernels of the token, less the lane's place in a tile
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int tok = t0 + 4 * i + g;
             Rrow[i] = kFused ? Rl + (4 * i + g) * kChunkBlocks + (n >> 2) : R + (row0 + 4 * i + g) * nb_cap + (n >> 2);
             wr[i] = ((n & 3) == 0) && tok < L;
-            nvis_tok[i] = n_visible16(tok);
+            nvis_tok[i] = n_visible16(tok) - n;
         }
         if (kFused)
             for (int i = lane; i < lay.carry_words; i += 64) carry[i] = 0ull;
@@ -344,10 +351,10 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
             float e[kHalf];
 #pragma unroll
             for (int u = 0; u < kHalf; ++u) {
-                float a = 0.f;
                 const f32x4 nl4 = *reinterpret_cast<const f32x4 *>(nls + (kHalf * i + u) * 16 + 4 * g);
+                float a = fast_exp2(__builtin_fmaf(z[u][0], c, nl4[0]));   // (not 0 +: 4 of the 60 vector instructions of a half)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a += fast_exp2(__builtin_fmaf(z[u][j], c, nl4[j]));
+                for (int j = 1; j < 4; ++j) a += fast_exp2(__builtin_fmaf(z[u][j], c, nl4[j]));
                 e[u] = a;
             }
             // sum over the four 16-lane groups, leaving token u's total in group u (3 lane swaps)
@@ -359,13 +366,15 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
             const v2u pq = __builtin_amdgcn_permlane32_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
             float v = __uint_as_float(pq[0]) + __uint_as_float(pq[1]);
             v = fminf(fmaxf(v * (1.f / 16.f), kScoreFloor), kScoreCeil);
-            if (t >= nt_pipe && 16 * t + n >= nvis_tok[i]) v = -INFINITY;     // kernel not visible to this token
-            const float a = fmaxf(v, dpp_f32<kRowShl1>(v, v));
-            const float bq = fmaxf(a, dpp_f32<kRowShl2>(a, a));
-            const float halo0 = dpp_f32<kRowRor1>(prev_v[i], prev_v[i]);      // lane 0 <- previous tile's lane 15
-            const float halo = dpp_f32<kRowShr1>(halo0, v);                   // lane n <- v[n-1]
-            const float w = fmaxf(bq, halo);
-            prev_v[i] = v;
+            // The pooling compares bit patterns: positive floats order like integers, and -inf lies below them.  With the
+            // smallest integer outside the row, a move and its maximum are one instruction.
+            const int vi = 16 * t < nvis_tok[i] ? __float_as_int(v) : kNegInf;        // (kernel 16t + n not visible to this token)
+            const int a = max(vi, dpp_i32<kRowShl1>(INT32_MIN, vi));
+            const int bq = max(a, dpp_i32<kRowShl2>(INT32_MIN, a));
+            const int halo0 = dpp_i32<kRowRor1>(prev_v[i], prev_v[i]);        // lane 0 <- previous tile's lane 15
+            const int halo = dpp_i32<kRowShr1>(halo0, vi);                    // lane n <- v[n-1]
+            const float w = __int_as_float(max(bq, halo));
+            prev_v[i] = vi;
             if (kFused) {
                 if (wr[i]) Rrow[i][(4 * t) & (kChunkBlocks - 1)] = w;
             } else {
