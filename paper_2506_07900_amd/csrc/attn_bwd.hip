@@ -50,7 +50,7 @@ static inline int32_t bwd_item_members(const Dims &dm) {
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
     int32_t members, item_cap;                        // most members of an item (unless one word has more); items per queue
-    size_t kvb, marks, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
+    size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
 static inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 static BwdLayout bwd_layout(const Dims &dm) {
@@ -67,7 +67,6 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.item_cap = (int32_t)((BH * l.n_seg + kQueues - 1) / kQueues * per_seg);
     size_t o = 0;
     l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
-    l.marks = o;    o += al256(dm.G == 16 ? 0 : BH * l.nb_cap * sizeof(uint4));
     l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
     l.bits = o;     o += al256(BH * l.words * l.nb_cap * sizeof(uint32_t));
     l.acc_dk = o;   o += al256(BH * T * kHeadDim * sizeof(float));
@@ -94,8 +93,7 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
                                                         uint4 *__restrict__ kvb, int32_t nb_cap,
                                                         const int32_t *__restrict__ block_idx, uint32_t *__restrict__ bits,
                                                         float *__restrict__ acc_dk, float *__restrict__ acc_dv,
-                                                        uint32_t *__restrict__ counters, float *__restrict__ null_row,
-                                                        uint32_t *__restrict__ marks) {
+                                                        uint32_t *__restrict__ counters, float *__restrict__ null_row) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -109,7 +107,6 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
     const int sc = tid & 15, sr = tid >> 4;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
     const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
-    uint32_t top = 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = sr + 16 * i, t = j * kBlock + r;
@@ -120,10 +117,7 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
         }
         *reinterpret_cast<uint4 *>(&Ks[r * 136 + 8 * sc]) = xk;
         *reinterpret_cast<uint4 *>(&Vs[r * 136 + 8 * sc]) = xv;
-        if (dm.G < 16) top = fold_magnitude(fold_magnitude(top, xk), xv);
     }
-    const uint64_t marked = __ballot(is_nonfinite(top));  // (see union_mark; with one token per tile nobody asks)
-    if (dm.G < 16 && (tid & 63) == 0) marks[(((int64_t)b * dm.Hkv + h) * nb_cap + j) * 4 + (tid >> 6)] = marked != 0ull;
     __syncthreads();
     uint4 *dst = kvb + ((((int64_t)b * dm.Hkv + h) * nb_cap + j) * kBwdBlockU4);
 #pragma unroll
@@ -267,8 +261,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                                                               int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                               const int32_t *__restrict__ block_idx,
                                                               const float *__restrict__ lse,
-                                                              float *__restrict__ rowc, Tensor dq, int32_t slots,
-                                                              const uint4 *__restrict__ marks) {
+                                                              float *__restrict__ rowc, Tensor dq, int32_t slots) {
     using C = DqCfg<kG, kTiles>;
     constexpr int kRing = kDqRing, kTPT = C::kTPT, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per workgroup; member bits in one word");
@@ -370,8 +363,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     // this wave's K rows of the half in LDS
     char *kt = reinterpret_cast<char *>(dq_smem) + wave * (C::kRowBytes / 4);
 
-    // One walk; if it met a marked block (see union_mark), another for each token of a tile.
-    __shared__ int careful_s[4];
+    // One walk; if a result is not finite (see not_finite), another for each token of a tile.
+    __shared__ int odd_s[4];
     for (int pass = 0;; ++pass) {
     const uint32_t slot_mask = pass ? 1u << (pass - 1) : (1u << kTPT) - 1u;
 #pragma unroll
@@ -380,19 +373,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
         for (int dt = 0; dt < 8; ++dt) acc[u][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     __builtin_amdgcn_s_waitcnt(0);                        // nothing of the prologue may still be pending inside the ring loop
     uint32_t blk = 0u, bits = 0u;                         // the block at hand and its member bits
-    bool careful = false;                                 // a block of this wavefront's is marked
     if (wave < cnt) {
-        const uint4 *mk = marks + ((int64_t)b * dm.Hkv + h) * nb_cap;
-        uint4 m = {0u, 0u, 0u, 0u};
-        if constexpr (kTPT > 1) m = union_mark(mk, ul, wave, 4, cnt, lane);
-        __builtin_amdgcn_sched_barrier(0);
         const uint2 e = union_entry(wave);
         blk = __builtin_amdgcn_readfirstlane(e.x);
         bits = __builtin_amdgcn_readfirstlane(e.y);
         const __amdgpu_buffer_rsrc_t bp = block_rsrc(blk);
 #pragma unroll
         for (int unit = 0; unit < kRing; ++unit) issue(unit, bp);
-        if constexpr (kTPT > 1) careful = union_marked(m, mk, ul, wave, 4, cnt, lane);
     }
     // `edge`: the tokens' own block, the last of the union: the only one with the causal edge
     auto block = [&](auto edge, int ci) __attribute__((always_inline)) {
@@ -516,7 +503,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     const float scale = c * kLn2;
     float4 *po = reinterpret_cast<float4 *>(dq_smem);     // [wave][dt][lane]
     const bool writes = pass == 0 || tn == pass - 1;
-    if (kTPT > 1 && lane == 0) careful_s[wave] = careful;
+    bool odd = false;
 #pragma unroll
     for (int u = 0; u < kTiles; ++u) {
         __syncthreads();
@@ -536,6 +523,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                     const float4 y = po[(w * 8 + dt) * 64 + lane];
                     x += f32x4{y.x, y.y, y.z, y.w};
                 }
+                if (kTPT > 1) odd |= not_finite(x);
                 bf16x4 r;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = (__bf16)(x[j] * scale);
@@ -543,15 +531,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
             }
         }
     }
+    if (kTPT > 1 && pass == 0) {
+        const bool again = __any(odd);
+        if (lane == 0) odd_s[wave] = again;
     }
-    if (kTPT == 1 || pass == kTPT || !(careful_s[0] | careful_s[1] | careful_s[2] | careful_s[3])) return;
-    __syncthreads();                                      // everyone is past the merge area and the flags
+    }
+    if (kTPT == 1 || pass == kTPT) return;
+    __syncthreads();                                      // (also: everyone is past the merge area)
+    if (!(odd_s[0] | odd_s[1] | odd_s[2] | odd_s[3])) return;
     }
 }
 
 template <int kG, int kTiles>
 static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                             const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, const uint4 *marks, hipStream_t stream) {
+                             const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
     using C = DqCfg<kG, kTiles>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTok - 1) / C::kTok;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
@@ -562,7 +555,7 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, 
         if (e != hipSuccess) return (int)e;
     }
     hipLaunchKernelGGL((attn_bwd_dq_kernel<kG, kTiles>), dim3((uint32_t)((int64_t)slots * 8 * dm.Hkv * dm.batch)), dim3(256), lds,
-                       stream, dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, slots, marks);
+                       stream, dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, slots);
     return 0;
 }
 
@@ -573,13 +566,13 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, 
 // G = 1 is 16 tokens and four would not fit the 32 member bits.
 template <int kG>
 static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                           const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, const uint4 *marks, hipStream_t stream) {
+                           const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG > 1)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream);
-    return launch_dq_variant<kG, 1>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
+    return launch_dq_variant<kG, 1>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
 }
 
 // ---- dk, dv of one block from the tokens that selected it ------------------------------------------------------
@@ -886,14 +879,13 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     uint4 *kvb = reinterpret_cast<uint4 *>(base + l.kvb);
     float *rowc = reinterpret_cast<float *>(base + l.rowc);
     float *null_row = rowc + (size_t)dm.batch * dm.max_seqlen * dm.Hq * 2;
-    uint4 *marks = reinterpret_cast<uint4 *>(base + l.marks);
     uint32_t *bits = reinterpret_cast<uint32_t *>(base + l.bits), *counters = reinterpret_cast<uint32_t *>(base + l.counters);
     uint4 *items = reinterpret_cast<uint4 *>(base + l.items);
     float *acc_dk = reinterpret_cast<float *>(base + l.acc_dk), *acc_dv = reinterpret_cast<float *>(base + l.acc_dv);
     const int T = dm.max_seqlen;
     timing_begin("pack_bwd_kernel", stream);
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,
-                       l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, null_row, reinterpret_cast<uint32_t *>(marks));
+                       l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, null_row);
     timing_end(stream);
     timing_begin("bwd_items_kernel", stream);
     hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)l.n_seg * ((l.nb_cap + 255) / 256), dm.Hkv, dm.batch), dim3(256), 0, stream, dm,
@@ -902,11 +894,11 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_dq_group<1>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream); break;
-        case 2: err = launch_dq_group<2>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream); break;
-        case 4: err = launch_dq_group<4>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream); break;
-        case 8: err = launch_dq_group<8>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream); break;
-        case 16: err = launch_dq_group<16>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, marks, stream); break;
+        case 1: err = launch_dq_group<1>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 2: err = launch_dq_group<2>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 4: err = launch_dq_group<4>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 8: err = launch_dq_group<8>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 16: err = launch_dq_group<16>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
     }
     if (err) return err;
     timing_end(stream);

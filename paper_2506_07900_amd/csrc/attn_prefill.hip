@@ -42,7 +42,7 @@ __device__ inline uint32_t xcd_contiguous_id(uint32_t bid, uint32_t n) {
 __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor v,
                                                        const int32_t *__restrict__ seqlens,
                                                        uint4 *__restrict__ kvp, int32_t nb_cap, Tensor out,
-                                                       float *__restrict__ lse, uint32_t *__restrict__ marks) {
+                                                       float *__restrict__ lse) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
     const int sc = tid & 15, sr = tid >> 4;
     const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
     const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
-    uint32_t top = 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = sr + 16 * i, t = j * kBlock + r;
@@ -71,10 +70,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
         }
         *reinterpret_cast<uint4 *>(&Ks[r * 136 + 8 * sc]) = xk;
         *reinterpret_cast<uint4 *>(&Vs[r * 136 + 8 * sc]) = xv;
-        if (dm.G < 16) top = fold_magnitude(fold_magnitude(top, xk), xv);
     }
-    const uint64_t marked = __ballot(is_nonfinite(top));  // (see union_mark; with one token per tile nobody asks)
-    if (dm.G < 16 && (tid & 63) == 0) marks[(((int64_t)b * dm.Hkv + h) * nb_cap + j) * 4 + (tid >> 6)] = marked != 0ull;
     __syncthreads();
     uint4 *dst = kvp + ((((int64_t)b * dm.Hkv + h) * nb_cap + j) * kPackedBlockU4);
 #pragma unroll
@@ -161,7 +157,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
                                                             Tensor out, float *__restrict__ lse,
-                                                            int32_t slots, const uint4 *__restrict__ marks) {
+                                                            int32_t slots) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     constexpr int kNU = 4, kTPT = C::kTokPerTile, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per wavefront; member bits in one word");
@@ -263,10 +259,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         l_run[u] += ps;
     };
 
-    // One walk; if it met a marked block (see union_mark), another for each token of a tile.  (A wavefront that works alone
+    // One walk; if a result is not finite (see not_finite), another for each token of a tile.  (A wavefront that works alone
     // has one token per tile.)
     static_assert(kSplit > 1 || kTPT == 1, "the flag of the workgroup's waves is exchanged in the merge");
-    __shared__ int careful_s[4];
+    __shared__ int odd_s[4];
     for (int pass = 0;; ++pass) {
     const uint32_t slot_mask = pass ? 1u << (pass - 1) : (1u << kTPT) - 1u;
 #pragma unroll
@@ -283,18 +279,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
     constexpr int kStep = kSplit;                        // the waves of a splitting workgroup take every kSplit-th block
     const int first = kSplit > 1 ? wave : 0;
     uint2 e_cur = {0u, 0u}, e_nxt = {0u, 0u};
-    bool careful = false;                                // a block of this wavefront's is marked
     if (first < cnt) {
-        const uint4 *mk = marks + ((int64_t)b * dm.Hkv + h) * nb_cap;
-        uint4 m = {0u, 0u, 0u, 0u};
-        if constexpr (kTPT > 1) m = union_mark(mk, ul, first, kStep, cnt, lane);
-        __builtin_amdgcn_sched_barrier(0);
         e_cur = union_entry(first);
         e_nxt = union_entry(first + kStep);
         const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
 #pragma unroll
         for (int unit = 0; unit < kNU; ++unit) issue(unit, bp);
-        if constexpr (kTPT > 1) careful = union_marked(m, mk, ul, first, kStep, cnt, lane);
     }
     for (int ci = first; ci < cnt; ci += kStep) {
         const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
@@ -383,7 +373,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         asm volatile("" : "+v"(ln));                      // (what follows is not formed ahead of the walk: no register to spare there)
         const int lane = ln, n = ln & 15, g = ln >> 4, tn = n / kG;
         const bool writes = pass == 0 || tn == pass - 1;
-        if (kTPT > 1 && lane == 0) careful_s[wave] = careful;
+        bool odd = false;
 #pragma unroll
         for (int u = 0; u < kTiles; ++u) {
             if (u) __syncthreads();
@@ -417,6 +407,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                         const float4 y = po[(w * 8 + dt) * 64 + lane];
                         x += f32x4{y.x, y.y, y.z, y.w} * f[w];
                     }
+                    if (kTPT > 1) odd |= not_finite(x);
                     bf16x4 r;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) r[j] = (__bf16)(x[j] * inv);
@@ -427,8 +418,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                         l_tot > 0.f ? (fast_log2(l_tot) + M) * kLn2 : -INFINITY;
             }
         }
-        if (kTPT == 1 || pass == kTPT || !(careful_s[0] | careful_s[1] | careful_s[2] | careful_s[3])) return;
-        __syncthreads();                                  // everyone is past the merge area and the flags
+        if (kTPT == 1 || pass == kTPT) return;
+        if (pass == 0) {
+            const bool again = __any(odd);
+            if (lane == 0) odd_s[wave] = again;
+        }
+        __syncthreads();                                  // (also: everyone is past the merge area)
+        if (!(odd_s[0] | odd_s[1] | odd_s[2] | odd_s[3])) return;
         continue;
     }
     // ---- normalise and write: lane holds channels 16*dt + 4*g .. +3 of column n -----------------
@@ -617,14 +613,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(Dims dm, Te
     }
 }
 
-static size_t packed_bytes(const Dims &dm) {
+size_t attn_prefill_ws_bytes(const Dims &dm) {
     const size_t nb_cap = ((size_t)dm.max_seqlen + kBlock - 1) / kBlock;
     return (size_t)dm.batch * dm.Hkv * nb_cap * kPackedBlockU4 * sizeof(uint4);
-}
-// the packed blocks, then the blocks' marks (G < 16: tiles of several tokens)
-size_t attn_prefill_ws_bytes(const Dims &dm) {
-    const size_t marks = dm.G == 16 ? 0 : packed_bytes(dm) / (kPackedBlockU4 * sizeof(uint4)) * sizeof(uint4);
-    return packed_bytes(dm) + (marks + 255) / 256 * 256;
 }
 
 // Workgroups go to the XCDs round-robin by their id.  A sequence's tiles are dealt to the XCDs in runs of kRun, last
@@ -634,7 +625,7 @@ size_t attn_prefill_ws_bytes(const Dims &dm) {
 
 template <int kG, int kTiles, int kSplit>
 static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
-                               const int32_t *block_idx, Tensor out, float *lse, const uint4 *marks, hipStream_t stream) {
+                               const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTokPerWg - 1) / C::kTokPerWg;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
@@ -646,7 +637,7 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
         if (e != hipSuccess) return (int)e;
     }
     hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
-                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots, marks);
+                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
     return 0;
 }
 
@@ -661,15 +652,15 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
 // only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
 template <int kG>
 static int launch_attn_group(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
-                             const int32_t *block_idx, Tensor out, float *lse, const uint4 *marks, hipStream_t stream) {
+                             const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG == 16)
-        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
+        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
     if constexpr (kG > 1)                                // (member bits of at most 32 tokens)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
-    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, marks, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
 }
 
 int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int32_t *seqlens,
@@ -677,10 +668,9 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
     const int32_t nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
     if (nb_cap <= 0 || dm.batch <= 0) return 0;
     uint4 *kvp = reinterpret_cast<uint4 *>(ws);
-    uint32_t *marks = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(ws) + packed_bytes(dm));
     timing_begin("pack_kv_kernel", stream);
     hipLaunchKernelGGL(pack_kv_kernel, dim3(nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v,
-                       seqlens, kvp, nb_cap, out, lse, marks);
+                       seqlens, kvp, nb_cap, out, lse);
     timing_end(stream);
     if (dm.shared_q) {                                   // one block list per query block (comparison variant)
         const int32_t n_tiles = (dm.max_seqlen + 7) / 8;
@@ -690,15 +680,14 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
         timing_end(stream);
         return (int)hipGetLastError();
     }
-    const uint4 *mk = reinterpret_cast<const uint4 *>(marks);
     timing_begin("attn_prefill_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
-        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
-        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
-        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
-        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, mk, stream); break;
+        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
     }
     if (err) return err;
     timing_end(stream);

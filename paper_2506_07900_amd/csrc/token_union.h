@@ -85,36 +85,13 @@ __device__ inline int build_union(const int32_t *__restrict__ rows, int topk, in
     return cnt;
 }
 
-// Largest magnitude of eight bf16 values per half word, folded into `top`; an infinity or a NaN has 0x7f80 or more.
-typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t fold_magnitude(uint32_t top, const uint4 &x) {
-    u16x2_t t = __builtin_bit_cast(u16x2_t, top);
-    t = __builtin_elementwise_max(t, __builtin_bit_cast(u16x2_t, x.x & 0x7fff7fffu));
-    t = __builtin_elementwise_max(t, __builtin_bit_cast(u16x2_t, x.y & 0x7fff7fffu));
-    t = __builtin_elementwise_max(t, __builtin_bit_cast(u16x2_t, x.z & 0x7fff7fffu));
-    t = __builtin_elementwise_max(t, __builtin_bit_cast(u16x2_t, x.w & 0x7fff7fffu));
-    return __builtin_bit_cast(uint32_t, t);
-}
-__device__ inline bool is_nonfinite(uint32_t top) { return (top & 0xffffu) >= 0x7f80u || (top >> 16) >= 0x7f80u; }
-
-// A block's marks, one per wavefront of the kernel that packed it: not 0 = an infinity or a NaN among its keys and values.
 // A tile whose columns belong to several tokens multiplies a block that only some of them selected with zeros for the
-// others, and 0 * inf reaches their sums.  With a marked block in the union the walk is therefore taken again, once per
-// token of a tile with that token's blocks alone (a select per accumulator in the only walk would cost every call:
-// 487 -> 565 us for a training step on 2 x 4096 tokens, G = 8; a second copy of the walk spills).
-// union_mark reads the marks of entries first, first + step, ... of the union for lanes 0, 1, ..: a load of its own, so that
-// it can be under way together with the first fragments.  union_marked: one of them, or of the entries behind the 64th, is set.
-__device__ inline uint4 union_mark(const uint4 *__restrict__ marks, const UnionLds &u, int first, int step, int cnt, int lane) {
-    return marks[u.list[min(first + step * lane, cnt - 1)].x];
-}
-__device__ inline bool union_marked(uint4 m, const uint4 *__restrict__ marks, const UnionLds &u, int first, int step, int cnt,
-                                    int lane) {
-    uint32_t any = m.x | m.y | m.z | m.w;
-    for (int i = first + step * 64; i < cnt; i += step * 64) {              // uniform; rare
-        const uint4 x = union_mark(marks, u, i, step, cnt, lane);
-        any |= x.x | x.y | x.z | x.w;
-    }
-    return __any(any != 0u);
+// others, and 0 * inf or 0 * NaN reaches their sums.  Such a sum is not finite, so the kernels look at their results and, when
+// one is not, take the walk again once per token of a tile, with that token's blocks alone.  (A select per accumulator
+// would cost every call: 487 -> 565 us for a training step on 2 x 4096 tokens, G = 8; a second copy of the walk spills.)
+__device__ inline bool not_finite(const f32x4 &x) {
+    const float s = (x[0] * 0.f + x[1] * 0.f) + (x[2] * 0.f + x[3] * 0.f);
+    return s != s;
 }
 
 }  // namespace infllmv2
