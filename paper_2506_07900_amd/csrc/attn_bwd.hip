@@ -215,17 +215,6 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
     });
 }
 
-// Rows of 128 channels in LDS: a row's sixteen 16-byte pieces are stored XOR-swizzled with the row's two bit pairs exchanged.  An
-// operand load takes one piece from each of 16 or 32 rows, a transposing load 32 bytes from each of 4 consecutive rows, and
-// both then touch every bank once.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ int bwd_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-// 4 rows x 16 channels per 16-lane group, transposed: lane i of the group gets channel i of the four rows its
-// group addressed (source lane s: row s/4, channels 4(s%4) .. +3)
-__device__ __forceinline__ s16x4 lds_read_tr16(const char *p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-}
-
 // ---- dq: a workgroup owns the tokens of kTiles MFMA tiles of one key-value head ---------------------------
 // As in the forward: the 16 columns of a tile are the G query heads of 16 / G tokens, the union of the tokens' block
 // lists is walked once, every fragment serves every tile with a token that selected the block; the four wavefronts take
@@ -391,8 +380,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
         uint32_t ln = lane;
         asm volatile("" : "+v"(ln));
         const uint32_t kn = ln & 15, kg = ln >> 4, kt_row = 4u * kg + (kn >> 2);
-        const uint32_t kt_put = kn * 256u + ((kg ^ (uint32_t)bwd_swizzle((int)kn)) << 4);            // ^ (ks << 6)
-        const uint32_t kt_get = kt_row * 256u + ((((kn & 3) >> 1) ^ (uint32_t)bwd_swizzle((int)kt_row)) << 4) + 8u * (kn & 1);
+        const uint32_t kt_put = kn * 256u + ((kg ^ (uint32_t)row_swizzle((int)kn)) << 4);            // ^ (ks << 6)
+        const uint32_t kt_get = kt_row * 256u + ((((kn & 3) >> 1) ^ (uint32_t)row_swizzle((int)kt_row)) << 4) + 8u * (kn & 1);
         uint32_t tb[kTiles];                              // member bits of the tile's tokens
 #pragma unroll
         for (int u = 0; u < kTiles; ++u) {
@@ -728,9 +717,9 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
             const uint32_t hf = ln >> 5;
             // operand loads: piece 2ks + hf of row lane % 32; transposed: rows 16s + 8rd + 4hf + 0..3 at channel tile ct, whose pieces
             // start at 4ct and have swizzle 2rd ^ that of row 4hf + 0..3
-            const uint32_t ar = (ln & 31) * 256u + ((hf ^ (uint32_t)bwd_swizzle((int)(ln & 15))) << 4);
+            const uint32_t ar = (ln & 31) * 256u + ((hf ^ (uint32_t)row_swizzle((int)(ln & 15))) << 4);
             const uint32_t t_r = 4u * hf + ((ln & 15) >> 2), t_c = 2u * ((ln >> 4) & 1) + ((ln & 3) >> 1);
-            const uint32_t at = t_r * 256u + ((t_c ^ (uint32_t)bwd_swizzle((int)t_r)) << 4) + 8u * (ln & 1);
+            const uint32_t at = t_r * 256u + ((t_c ^ (uint32_t)row_swizzle((int)t_r)) << 4) + 8u * (ln & 1);
             auto rows_of = [&](const char *x, int ks) __attribute__((always_inline)) {
                 return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(x + (ar ^ (uint32_t)(ks << 5))));
             };

@@ -151,9 +151,13 @@ struct AttnCfg {
     }
 };
 
-template <int kG, int kTiles, int kSplit>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q, const uint4 *__restrict__ kvp,
-                                                            int32_t nb_cap,
+// kDirect (short prompts, one tile per workgroup): no packed copy, hence one launch and its round trip to memory less.  Whole
+// rows come from the cache and take their operand form by way of 8 KiB of LDS per wavefront, V by the transposing load.
+// (Rows fetched as the operand wants them, 16 x 64 bytes per load, were slower from 256 tokens on: half lines.  Two tiles
+// spill with their queries in registers and lose more to LDS than the launch costs without: 2048 tokens, G = 4 19.1 / 21.6 us.)
+template <int kG, int kTiles, int kSplit, bool kDirect>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
+                                                            const uint4 *__restrict__ kvp, int32_t nb_cap,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
                                                             Tensor out, float *__restrict__ lse,
@@ -170,6 +174,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
     const int tile = (L + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t0 = kSplit > 1 ? tile * kTok : (tile * 4 + wave) * kTok;   // this wavefront's first token
+    if (kDirect && dm.fill) {                            // rows past the end: this tile's, or one of those behind the last
+        const int f0 = tile >= 0 ? t0 : ((L + kTok - 1) / kTok - 1 - tile) * kTok;
+        for (int i = threadIdx.x; i < kTok * kG * 16; i += 256) {
+            const int tok = f0 + i / (kG * 16), hq = h * kG + i / 16 % kG;
+            if (tok >= L && tok < dm.max_seqlen) {
+                *reinterpret_cast<uint4 *>(out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)hq * out.sh + 8 * (i & 15)) =
+                    uint4{0u, 0u, 0u, 0u};
+                if ((i & 15) == 0) lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + hq] = 0.f;
+            }
+        }
+    }
     if (tile < 0 || t0 >= L) return;                     // (uniform over the workgroup when it splits the blocks)
     const int b_own = t0 / kBlock;                       // kTok divides 64: one own block per wavefront
     const int n = lane & 15, g = lane >> 4;              // MFMA column (token, query head) and 16-lane group
@@ -212,16 +227,31 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
     const char *kv_head = reinterpret_cast<const char *>(kvp) + ((int64_t)b * dm.Hkv + h) * nb_cap * (kPackedBlockU4 * 16);
     const uint32_t lane16 = 16u * lane;
     u32x4 ring[kNU][4];
+    // kDirect: 32-bit offsets from the head's first row; rows past the sequence's last one lie outside the resource and read 0
+    const uint32_t kst = 2u * (uint32_t)k.st, vst = 2u * (uint32_t)v.st, last_row = (uint32_t)L - 1u;
+    const __amdgpu_buffer_rsrc_t k_rows = __builtin_amdgcn_make_buffer_rsrc(k.ptr + b * k.sb + h * k.sh, 0, last_row * kst + 256u, 0x00027000);
+    const __amdgpu_buffer_rsrc_t v_rows = __builtin_amdgcn_make_buffer_rsrc(v.ptr + b * v.sb + h * v.sh, 0, last_row * vst + 256u, 0x00027000);
     auto block_rsrc = [&](uint32_t blk) __attribute__((always_inline)) {
-        const int64_t at = (int64_t)(int)__builtin_amdgcn_readfirstlane(blk) * (kPackedBlockU4 * 16);
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kv_head) + at, 0, kPackedBlockU4 * 16, 0x00027000);
+        if constexpr (kDirect) {
+            return (uint32_t)__builtin_amdgcn_readfirstlane(blk) * kBlock;           // the block's first row
+        } else {
+            const int64_t at = (int64_t)(int)__builtin_amdgcn_readfirstlane(blk) * (kPackedBlockU4 * 16);
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kv_head) + at, 0, kPackedBlockU4 * 16, 0x00027000);
+        }
     };
     auto fragment = [&](__amdgpu_buffer_rsrc_t bp, int f) __attribute__((always_inline)) {
         return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(bp, lane16, f * 1024, 0));
     };
-    auto issue = [&](int unit, __amdgpu_buffer_rsrc_t bp) __attribute__((always_inline)) {
+    auto issue = [&](int unit, auto bp) __attribute__((always_inline)) {
         const int hs = unit >> 2, r = unit & 3;
-        if (r < 2) {
+        if constexpr (kDirect) {                         // units of a half: K rows of key tiles 2hs, 2hs + 1, V rows of the same
+            const uint32_t st = r < 2 ? kst : vst, row = bp + 16u * (2 * hs + (r & 1)) + (uint32_t)g;
+            const uint32_t at = __umul24(row, st) + 16u * n;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)                  // (whole rows: 4i + g)
+                ring[unit % kNU][i] =
+                    __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r < 2 ? k_rows : v_rows, at + 4u * i * st, 0, 0));
+        } else if (r < 2) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) ring[unit % kNU][ks] = fragment(bp, ks * 4 + 2 * hs + r);
         } else {
@@ -259,8 +289,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
         l_run[u] += ps;
     };
 
+    // kDirect: the rows of a half (K, then V) in LDS, this wavefront's own piece of the merge area
+    char *xt = reinterpret_cast<char *>(attn_smem + C::merge_at(dm.topk)) + wave * (8 * 64 * sizeof(float4));
+
     // One walk; if a result is not finite (see not_finite), another for each token of a tile.  (A wavefront that works alone
     // has one token per tile.)
+    static_assert(!kDirect || (kSplit > 1 && !C::kQLds), "one copy of the tokens, queries in registers");
     static_assert(kSplit > 1 || kTPT == 1, "the flag of the workgroup's waves is exchanged in the merge");
     __shared__ int odd_s[4];
     for (int pass = 0;; ++pass) {
@@ -282,17 +316,26 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
     if (first < cnt) {
         e_cur = union_entry(first);
         e_nxt = union_entry(first + kStep);
-        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x);
+        const auto bp = block_rsrc(e_cur.x);
 #pragma unroll
         for (int unit = 0; unit < kNU; ++unit) issue(unit, bp);
     }
     for (int ci = first; ci < cnt; ci += kStep) {
         const int blk = __builtin_amdgcn_readfirstlane(e_cur.x);
         const uint32_t bits = __builtin_amdgcn_readfirstlane(e_cur.y);
-        const __amdgpu_buffer_rsrc_t bp = block_rsrc(e_cur.x), bn = block_rsrc(e_nxt.x);
+        const auto bp = block_rsrc(e_cur.x), bn = block_rsrc(e_nxt.x);
         e_cur = e_nxt;
         e_nxt = union_entry(ci + 2 * kStep);
         const int key0 = blk * kBlock;
+        // kDirect: where the lane's piece of row 16t + 4i + g goes (^ (i << 4), + 1024 i), where its piece of the K operand lies
+        // (^ (ks << 6)), and where its four V rows for the transposing load begin (keys 16t + 4g .. +3, channels 16dt ..: ^ (dt << 5));
+        // formed anew per block: kept, their variants are spilled, and a spill in this loop waits for every load
+        uint32_t ln = lane;
+        if constexpr (kDirect) asm volatile("" : "+v"(ln));
+        const uint32_t xn = ln & 15, xg = ln >> 4, xt_row = 4u * xg + (xn >> 2);
+        const uint32_t xt_put = xg * 256u + ((xn ^ (xg << 2)) << 4);
+        const uint32_t xt_k = xn * 256u + ((xg ^ (uint32_t)row_swizzle((int)xn)) << 4);
+        const uint32_t xt_v = xt_row * 256u + ((((xn & 3) >> 1) ^ (uint32_t)row_swizzle((int)xt_row)) << 4) + 8u * (xn & 1);
         const bool edge = blk == b_own;                  // the last, partial block of a sequence is its last tokens' own
         uint32_t tb[kTiles];                             // member bits of the tile's tokens
 #pragma unroll
@@ -312,7 +355,27 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                 return acc;
             };
             f32x4 s[kTiles][2];
-            if constexpr (!C::kQLds) {
+            auto keep = [&](int unit) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    *reinterpret_cast<u32x4 *>(xt + (xt_put ^ (uint32_t)(i << 4)) + i * 1024 + (unit & 1) * 4096) = ring[unit % kNU][i];
+                refill(unit);
+            };
+            if constexpr (kDirect) {
+                keep(4 * hs);
+                keep(4 * hs + 1);
+#pragma unroll
+                for (int u = 0; u < kTiles; ++u) {
+                    if (!tb[u]) continue;
+                    s[u][0] = s[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                        for (int r = 0; r < 2; ++r)
+                            s[u][r] = mfma16(__builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(xt + (xt_k ^ (uint32_t)(ks << 6)) + r * 4096)),
+                                             qf[u][ks], s[u][r]);
+                }
+            } else if constexpr (!C::kQLds) {
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
 #pragma unroll
@@ -348,6 +411,26 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q,
                 for (int r = 0; r < 2; ++r) refill(4 * hs + r);
             }
             // ---- O^T += V^T . P^T, four channel tiles per unit --------------------------------
+            if constexpr (kDirect) {
+                keep(4 * hs + 2);
+                keep(4 * hs + 3);
+#pragma unroll
+                for (int d4 = 0; d4 < 8; d4 += 4) {
+                    bf16x8 vf[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t at = xt_v ^ (uint32_t)((d4 + i) << 5);
+                        const s16x4 x0 = lds_read_tr16(xt + at), x1 = lds_read_tr16(xt + at + 4096);
+                        vf[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
+                    }
+#pragma unroll
+                    for (int u = 0; u < kTiles; ++u) {
+                        if (!tb[u]) continue;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) o[u][d4 + i] = mfma16(vf[i], pf[u], o[u][d4 + i]);
+                    }
+                }
+            } else
 #pragma unroll
             for (int r = 2; r < 4; ++r) {
                 const int unit = 4 * hs + r, dh = r - 2;
@@ -623,8 +706,8 @@ size_t attn_prefill_ws_bytes(const Dims &dm) {
 // unequal lengths leaves no XCD idle: 12289 + 8693 + 5096 + 1500 tokens 1256 -> 700 us from this alone), neighbours,
 // which share blocks, still meet in one L2, and the long rows start first.
 
-template <int kG, int kTiles, int kSplit>
-static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
+template <int kG, int kTiles, int kSplit, bool kDirect = false>
+static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
                                const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTokPerWg - 1) / C::kTokPerWg;
@@ -632,12 +715,12 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
     const int64_t n_wg = (int64_t)slots * 8 * dm.Hkv * dm.batch;
     const size_t lds = C::lds_bytes(dm.topk);
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)attn_prefill_kernel<kG, kTiles, kSplit>,
+        const hipError_t e = hipFuncSetAttribute((const void *)attn_prefill_kernel<kG, kTiles, kSplit, kDirect>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
-                       dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
+    hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit, kDirect>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
+                       dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
     return 0;
 }
 
@@ -651,16 +734,29 @@ static int launch_attn_variant(const Dims &dm, Tensor q, const uint4 *kvp, int32
 // from 192 (at 190 it meets one tile); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
 // only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
 template <int kG>
-static int launch_attn_group(const Dims &dm, Tensor q, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
+static int launch_attn_group(const Dims &dm, Tensor q, Tensor k, Tensor v, bool direct, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
                              const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG == 16)
-        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+        if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
     if constexpr (kG > 1)                                // (member bits of at most 32 tokens)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
-    return launch_attn_variant<kG, 1, 4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    return direct ? launch_attn_variant<kG, 1, 4, true>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream)
+                  : launch_attn_variant<kG, 1, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+}
+
+// Straight from the cache instead of from a packed copy: where a workgroup has one tile (see launch_attn_group) and the sequences are
+// short.  Attention call, packed / direct, us, 2 key-value heads: 100 tokens 7.6 / 5.6 (every G); 256 tokens G = 16 10.3 / 8.0,
+// G = 4 8.1 / 6.2; 750 tokens G = 4 13.7 / 12.5, G = 1 11.1 / 10.3; they meet at about 1000 (1 head, G = 4: 11.8 / 12.1; G = 1: 12.6 / 12.2)
+// and at 2000 tokens G = 1 takes 18.9 / 20.0.  Offsets are 32-bit and formed by a 24-bit product, and rows must not overlap
+// (those past the end are told by their offset).
+constexpr int kDirectTokens = 896;
+static bool attn_direct(const Dims &dm, const Tensor &k, const Tensor &v) {
+    if (dm.shared_q || dm.max_seqlen > kDirectTokens || (int64_t)dm.batch * dm.max_seqlen * dm.Hkv >= (int64_t)192 * 2 * (16 / dm.G)) return false;
+    const int64_t lo = k.st < v.st ? k.st : v.st, hi = k.st < v.st ? v.st : k.st;
+    return lo >= kHeadDim && hi < 1 << 19;
 }
 
 int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int32_t *seqlens,
@@ -668,10 +764,13 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
     const int32_t nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
     if (nb_cap <= 0 || dm.batch <= 0) return 0;
     uint4 *kvp = reinterpret_cast<uint4 *>(ws);
-    timing_begin("pack_kv_kernel", stream);
-    hipLaunchKernelGGL(pack_kv_kernel, dim3(nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v,
-                       seqlens, kvp, nb_cap, out, lse);
-    timing_end(stream);
+    const bool direct = attn_direct(dm, k, v);
+    if (!direct) {
+        timing_begin("pack_kv_kernel", stream);
+        hipLaunchKernelGGL(pack_kv_kernel, dim3(nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v,
+                           seqlens, kvp, nb_cap, out, lse);
+        timing_end(stream);
+    }
     if (dm.shared_q) {                                   // one block list per query block (comparison variant)
         const int32_t n_tiles = (dm.max_seqlen + 7) / 8;
         timing_begin("attn_prefill_shared_kernel", stream);
@@ -683,11 +782,11 @@ int launch_attn_prefill(const Dims &dm, Tensor q, Tensor k, Tensor v, const int3
     timing_begin("attn_prefill_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_attn_group<1>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 2: err = launch_attn_group<2>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 4: err = launch_attn_group<4>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 8: err = launch_attn_group<8>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
-        case 16: err = launch_attn_group<16>(dm, q, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 1: err = launch_attn_group<1>(dm, q, k, v, direct, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 2: err = launch_attn_group<2>(dm, q, k, v, direct, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 4: err = launch_attn_group<4>(dm, q, k, v, direct, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 8: err = launch_attn_group<8>(dm, q, k, v, direct, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
+        case 16: err = launch_attn_group<16>(dm, q, k, v, direct, kvp, nb_cap, seqlens, block_idx, out, lse, stream); break;
     }
     if (err) return err;
     timing_end(stream);

@@ -85,6 +85,17 @@ __device__ inline int build_union(const int32_t *__restrict__ rows, int topk, in
     return cnt;
 }
 
+// Rows of 128 channels in LDS: a row's sixteen 16-byte pieces are stored XOR-swizzled with the row's two bit pairs exchanged.  An
+// operand load takes one piece from each of 16 or 32 rows, a transposing load 32 bytes from each of 4 consecutive rows, and
+// both then touch every bank once.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int row_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// 4 rows x 16 channels per 16-lane group, transposed: lane i of the group gets channel i of the four rows its
+// group addressed (source lane s: row s/4, channels 4(s%4) .. +3)
+__device__ __forceinline__ s16x4 lds_read_tr16(const char *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+}
+
 // A tile whose columns belong to several tokens multiplies a block that only some of them selected with zeros for the
 // others, and 0 * inf or 0 * NaN reaches their sums.  Such a sum is not finite, so the kernels look at their results and, when
 // one is not, take the walk again once per token of a tile, with that token's blocks alone.  (A select per accumulator

@@ -1026,6 +1026,37 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# Short prompts read keys and values where they lie: both sides of its lines, padded and interleaved token strides, an end inside a
+# block, sequences of nothing; the same bits whatever the strides.
+@pytest.mark.parametrize("seqlens,Hq,Hkv", [([1], 32, 2), ([64, 0, 17], 16, 1), ([190], 32, 2), ([193], 32, 2), ([383, 100], 8, 2), ([767], 8, 2),
+                                            ([895], 4, 1), ([897], 4, 1), ([896, 1], 1, 1), ([333, 65], 2, 2)])
+def test_sparse_attn_prefill_direct(seqlens, Hq, Hkv):
+    print("case direct", seqlens, Hq, Hkv, flush=True)
+    prm, oprm = binding.Params(Hq, Hkv, topk=6), oracle_params(binding.Params(Hq, Hkv, topk=6))
+    B, T = len(seqlens), max(seqlens)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    q = torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16()
+    pad = torch.randn((B, Hkv, T, 128 + 72), device="cuda", generator=gen).bfloat16()
+    inter = torch.randn((B, T, Hkv + 1, 128), device="cuda", generator=gen).bfloat16()
+    k, v = pad[..., :128], inter.transpose(1, 2)[:, :Hkv]                # token strides 200 and 128 (Hkv + 1)
+    own = (torch.arange(T, device="cuda") // 64)[None, None, :, None]
+    idx = own - torch.arange(6, device="cuda")[None, None, None, :] * torch.tensor([1, 2], device="cuda")[torch.arange(T, device="cuda") % 2][None, None, :, None]
+    idx = torch.where(idx < 0, torch.full_like(idx, -1), idx).expand(B, Hkv, T, 6).to(torch.int32).contiguous()
+    sl = dev_i32(seqlens)
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    out2, lse2 = torch.full_like(q, 3.0), torch.full((B, T, Hq), 5.0, device="cuda")
+    binding.sparse_attn_prefill(prm, q, k.contiguous(), v.contiguous(), sl, T, idx, out=out2, lse=lse2)
+    torch.cuda.synchronize()
+    for b, l in enumerate(seqlens):
+        assert torch.equal(out[b, :l], out2[b, :l]) and torch.equal(lse[b, :l], lse2[b, :l])
+        assert bool((out[b, l:] == 0).all()) and bool((lse[b, l:] == 0).all())
+        assert bool((out2[b, l:] == 3.0).all()) and bool((lse2[b, l:] == 5.0).all())
+        if l:
+            pos = np.arange(l, dtype=np.int32)
+            wo, wl = ref.sparse_attn(to_bits(q[b, :l]), to_bits(k[b, :, :l].contiguous()), to_bits(v[b, :, :l].contiguous()), pos, idx[b, :, :l].cpu().numpy(), oprm)
+            assert np.abs(out[b, :l].double().cpu().numpy() - wo).max() <= OUT_TOL and lse_err(lse[b, :l].double().cpu().numpy(), wl) <= 1.0
+
+
 # Tokens that share a tile with one that selected a block of infinities and NaNs must not see them: the rows that do not list
 # the block (or list another head's) are what they are with ordinary values there, and its own rows stay reachable.
 @pytest.mark.parametrize("T,Hq,Hkv", [(300, 4, 1), (770, 8, 1), (1700, 4, 2), (4100, 8, 2), (300, 1, 1), (3100, 2, 2), (600, 16, 1)])
