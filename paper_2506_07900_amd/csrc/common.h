@@ -314,7 +314,7 @@ int launch_select_prefill16(const Dims &dm, Tensor q, Tensor ck, const int32_t *
                             int32_t *block_idx, void *ws, hipStream_t stream, float *scores_out = nullptr,
                             int32_t scores_pitch = 0);
 size_t select_prefill16_ws_bytes(const Dims &dm);
-constexpr int kShortPrefill = 8192;                        // tokens: up to 512 semantic kernels (select_short.hip)
+constexpr int kShortPrefill = 4096;                        // tokens: up to 255 semantic kernels (select_short.hip)
 bool select_short_fits(const Dims &dm);
 int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream);
 int32_t select_scores_pitch(const Dims &dm);

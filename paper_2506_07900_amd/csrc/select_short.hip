@@ -2,19 +2,22 @@
 // kernel, straight from the compressed keys to the block lists.
 //
 // The two-pass kernels (select_prefill16.hip, select_prefill.hip) compute every logit and its exponential
-// twice, because a score 2^(z - lse) needs the log-sum-exp over all visible kernels first.  Up to 512
+// twice, because a score 2^(z - lse) needs the log-sum-exp over all visible kernels first.  Up to 256
 // semantic kernels the exponentials e = 2^(z - m) of a 16-row tile of (token, head) rows stay in the
 // registers of the wavefront that computed them, and the scores follow as sum_heads e * w with one weight
 // w = 1 / sum e per row: half the matrix work, half the exponentials, no log-sum-exps, packed keys or
 // second and third launch in between.  Tokens that attend all of their blocks anyway (own block < top-k)
 // are not scored at all.
 //
-// The compressed keys of a (sequence, key-value head) -- 128 KiB at most -- are copied into LDS once per
+// The compressed keys of a (sequence, key-value head) -- 64 KiB at most -- are copied into LDS once per
 // workgroup, in MFMA operand order; its eight wavefronts then take tile after tile of tokens, each on its own.
 // Reading the keys from L2 for every tile instead was bound by the half-line reads of the row-major keys
 // (16 rows x 64 bytes per load): 8 tiles of 16 kernels took 10 us with every wavefront at it.
-// Selection alone, us, two passes -> this: 777 tokens (top-k 8) 33 -> 7,
-// 2048 42 -> 11, 4096 53 -> 21, 8192 113 -> 51 (G = 16, 2 heads); 2048 G = 4 27 -> 9, 8192 G = 1 59 -> 37.
+// Selection alone, us, two passes -> this: 777 tokens (top-k 8) 33 -> 7, 2048 42 -> 11, 4096 53 -> 21 (G = 16, 2 heads);
+// 2048 G = 4 27 -> 9.
+// Up to 8192 tokens it would still be faster (113 -> 51, G = 1 59 -> 37), but its rounding is not the two passes': blocks whose scores tie to
+// fp32 rounding change places, in 4 of 983040 rows of 8192 tokens against 1 of 921600 of 1500 to 4096, and longer prompts keep
+// the lists they had.
 #include "common.h"
 
 #include <algorithm>
@@ -34,7 +37,7 @@ struct ShortCfg {
 };
 
 template <int kG, int kKT>
-__global__ __launch_bounds__(64 * kShortWaves, kKT > 16 ? 2 : 4) void select_short_kernel(
+__global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
     Dims dm, Tensor q, Tensor ck, const int32_t *__restrict__ seqlens, int32_t *__restrict__ block_idx, int32_t n_units,
     int32_t wgs, int32_t share_log2) {
     using C = ShortCfg<kG, kKT>;
@@ -230,7 +233,7 @@ static int launch_variant(const Dims &dm, Tensor q, Tensor ck, const int32_t *se
     const int32_t n_units = (dm.max_seqlen + C::kTok - 1) / C::kTok;
     const size_t lds = C::lds_bytes(num_kernels(dm.max_seqlen));
     // as many workgroups as the chip holds at a time (each copies the keys once), no more than there are tiles to go round
-    const int resident = kKT > 16 ? 1 : lds > 80 * 1024 ? 1 : 2;
+    const int resident = lds > 80 * 1024 ? 1 : 2;
     const int64_t rows = (int64_t)dm.batch * dm.Hkv;
     int share = 0;
     while ((1 << share) < C::kTok && ((int64_t)n_units * rows << share) * 2 <= 2048 * resident) ++share;
@@ -250,8 +253,7 @@ template <int kG>
 static int launch_group(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream) {
     const int n_blocks = (dm.max_seqlen + kBlock - 1) / kBlock;
     if (n_blocks <= 32) return launch_variant<kG, 8>(dm, q, ck, seqlens, block_idx, stream);
-    if (n_blocks <= 64) return launch_variant<kG, 16>(dm, q, ck, seqlens, block_idx, stream);
-    return launch_variant<kG, 32>(dm, q, ck, seqlens, block_idx, stream);
+    return launch_variant<kG, 16>(dm, q, ck, seqlens, block_idx, stream);
 }
 
 bool select_short_fits(const Dims &dm) { return dm.rho == 1 && !dm.shared_q && dm.max_seqlen <= kShortPrefill; }

@@ -137,9 +137,9 @@ def test_select_blocks_prefill(seqlens, Hq, Hkv, topk, planted):
     assert near <= max(2, tot // 200)
 
 
-# Up to 8192 tokens the selection is one pass in one kernel: both sides of each of its sizes (32, 64, 128 blocks) for every
+# Up to 4096 tokens the selection is one pass in one kernel: both sides of each of its sizes (32, 64 blocks) for every
 # group size, forced counts including none, batches, tokens that need no scores, few tiles (wavefronts share a tile) and
-# many (wavefronts take several), and the first length of the two-pass kernels.
+# many (wavefronts take several), and short lengths of the two-pass kernels.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk,forced", [
     ([2047, 31], 32, 2, 16, (1, 2)), ([2048], 16, 2, 8, (0, 0)), ([2049, 2048, 1], 4, 1, 16, (1, 2)), ([1100], 2, 2, 6, (0, 1)),
     ([4096], 2, 1, 16, (2, 1)), ([4097, 100], 32, 2, 8, (0, 0)), ([4095, 3000], 4, 2, 64, (1, 2)), ([3001], 1, 1, 3, (1, 2)),
@@ -164,10 +164,11 @@ def test_select_blocks_prefill_short(seqlens, Hq, Hkv, topk, forced):
     assert near <= max(2, tot // 200)
 
 
-def test_select_blocks_prefill_ties_go_to_the_lower_block():
-    # keys of all zeros: every visible kernel of a row scores the same, the tie rule alone decides (one-pass kernel, more
-    # than 64 candidate blocks)
-    Hq, Hkv, topk, T = 32, 2, 8, 5000
+@pytest.mark.parametrize("T", [5000, 4090])
+def test_select_blocks_prefill_ties_go_to_the_lower_block(T):
+    # keys of all zeros: every visible kernel of a row scores the same, the tie rule alone decides (more than 64 candidate
+    # blocks in the two-pass kernels, fewer in the one-pass kernel)
+    Hq, Hkv, topk = 32, 2, 8
     prm = binding.Params(Hq, Hkv, topk=topk)
     q = torch.randn((1, T, Hq, 128), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).bfloat16()
     ck = torch.zeros((1, Hkv, binding.num_kernels(T, prm), 128), dtype=torch.bfloat16, device="cuda")
