@@ -70,7 +70,7 @@ def measured_hbm_traffic(kernel, workload):
     (the row carries their digest).  None when there is no such row: a stale reading is not reported."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.md")
     try:
-        digest = source_digest("attn_prefill.hip", "common.h")
+        digest = source_digest("attn_prefill.hip", "common.h", "token_union.h")
         for line in open(path):
             cells = [c.strip().strip("`") for c in line.split("|")]
             if len(cells) >= 8 and cells[1].startswith(kernel) and cells[2] == workload and cells[6] == digest:
