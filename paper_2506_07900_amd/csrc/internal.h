@@ -1,7 +1,8 @@
 /* Entry points for the Python binding (csrc/marshal.cpp), not part of the public ABI: the public calls of the same
  * name plus `fill`.  With fill != 0 the call also clears what the public one leaves alone -- rows of sequences shorter
  * than max_seqlen: compressed keys, outputs, log-sum-exps and gradients 0, block lists -1 -- so that the binding can
- * hand it uninitialised tensors instead of filling them by launches of their own. */
+ * hand it uninitialised tensors instead of filling them by launches of their own.  Every result then holds max_seqlen rows
+ * per sequence (compressed keys: n_c(max_seqlen)); the public calls write rows below seqlens[b] only. */
 #ifndef INFLLMV2_INTERNAL_H
 #define INFLLMV2_INTERNAL_H
 

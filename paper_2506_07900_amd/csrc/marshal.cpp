@@ -246,9 +246,10 @@ PyObject *sparse_attn_prefill(Args a) {
     const at::Tensor &q = bf16_4d(a[1], "q");
     const int32_t T = integer(a[5]), B = static_cast<int32_t>(q.size(0));
     Result out(a[7]), lse(a[8]);
-    // rows past max_seqlen of a longer tensor, and a tensor next to one of the caller's (whose other rows stay as they
-    // are), are cleared by torch; else the call clears what its kernels do not write
-    const bool fill = out.make() && lse.make() && q.size(1) <= T && q_shaped(q, prm);
+    // the call clears rows up to max_seqlen: only where `out`, shaped like q, has just those.  Rows past max_seqlen of a longer
+    // tensor, a tensor shorter than max_seqlen, and a tensor next to one of the caller's (whose other rows stay as they
+    // are), are cleared by torch
+    const bool fill = out.make() && lse.make() && q.size(1) == T && q_shaped(q, prm);
     if (out.make()) out.own = fill ? at::empty_like(q) : at::zeros_like(q);
     if (lse.make())
         lse.own = fill ? at::empty({B, T, prm->n_q_heads}, like(q, at::kFloat)) : at::zeros({B, T, prm->n_q_heads}, like(q, at::kFloat));
@@ -361,8 +362,8 @@ PyObject *sparse_attn_bwd(Args a) {
     const at::Tensor &q = bf16_4d(a[1], "q"), &k = bf16_4d(a[2], "k"), &v = bf16_4d(a[3], "v");
     const int32_t T = integer(a[8]), B = static_cast<int32_t>(q.size(0));
     Result dq(a[10]), dk(a[11]), dv(a[12]);
-    const bool fill = dq.make() && dk.make() && dv.make() && q.size(1) <= T && k.size(2) <= T && v.size(2) <= T && q_shaped(q, prm) &&
-                      k_shaped(k, prm) && k_shaped(v, prm) && k.size(0) == B && v.size(0) == B;
+    const bool fill = dq.make() && dk.make() && dv.make() && q.size(1) == T && k.size(2) == T && v.size(2) == T && q_shaped(q, prm) &&
+                      k_shaped(k, prm) && k_shaped(v, prm) && k.size(0) == B && v.size(0) == B;   // (as for sparse_attn_prefill)
     if (dq.make()) dq.own = fill ? at::empty_like(q) : at::zeros_like(q);
     if (dk.make()) dk.own = fill ? at::empty_like(k) : at::zeros_like(k);
     if (dv.make()) dv.own = fill ? at::empty_like(v) : at::zeros_like(v);

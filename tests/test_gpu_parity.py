@@ -442,6 +442,66 @@ def test_results_made_by_the_call_are_clear_past_the_end(seqlens, T, Hq, Hkv):
         binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx, workspace=torch.empty(8, dtype=torch.uint8, device="cuda"))
 
 
+# Tensors with fewer rows than max_seqlen (a prompt's own queries beside caches of a larger capacity): the results, made like
+# them by the binding, hold just those rows.  Nothing behind a sequence's last row is written: not the next sequence's rows,
+# not the memory after the tensor.  Both forms of the attention (straight from the cache, packed), both tile counts of dq.
+@pytest.mark.parametrize("rows,lens,T,Hq,Hkv", [(100, [100, 65], 300, 16, 1), (200, [1, 200], 257, 4, 2), (1000, [1000, 999], 2100, 16, 1)])
+def test_results_made_by_the_call_end_with_the_tensor(rows, lens, T, Hq, Hkv):
+    print("case short tensors", rows, lens, T, Hq, Hkv, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=8)
+    B = len(lens)
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    q, do = (torch.randn((B, rows, Hq, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, rows, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    sl = dev_i32(lens)
+
+    def padded(x, dim):                                  # the same rows in a tensor of max_seqlen
+        y = torch.zeros(tuple(T if i == dim else n for i, n in enumerate(x.shape)), dtype=x.dtype, device="cuda")
+        y.narrow(dim, 0, rows).copy_(x)
+        return y
+
+    ck = binding.compress_keys(prm, k, sl, T)
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)
+    ws_f = torch.empty(binding.workspace_bytes(binding.OP_ATTN_PREFILL, prm, B, T), dtype=torch.uint8, device="cuda")
+    ws_b = torch.empty(binding.workspace_bytes(binding.OP_ATTN_BWD, prm, B, T), dtype=torch.uint8, device="cuda")
+    q2, do2, k2, v2 = padded(q, 1), padded(do, 1), padded(k, 2), padded(v, 2)
+    want_out, want_lse = binding.sparse_attn_prefill(prm, q2, k2, v2, sl, T, idx, workspace=ws_f)
+    want_dq, want_dk, want_dv = binding.sparse_attn_bwd(prm, q2, k2, v2, want_out, do2, want_lse, sl, T, idx, workspace=ws_b)
+    assert torch.equal(idx, binding.select_blocks(prm, binding.MODE_PREFILL, q2, ck, sl, T))
+
+    def holes(*sizes):                                   # gaps for the results, each with a known pattern right behind it
+        guards, gaps = [], []
+        for n in sizes:
+            gaps.append(torch.empty((n,), dtype=torch.uint8, device="cuda"))
+            guards.append(torch.full((1536 << 10 if n > 1 << 20 else 64 << 10,), 0x5a, dtype=torch.uint8, device="cuda"))
+            assert guards[-1].data_ptr() - gaps[-1].data_ptr() == (n + 511) // 512 * 512
+        torch.cuda.synchronize()
+        return guards, [x.data_ptr() for x in gaps]
+
+    pools = torch.cuda.MemPool(), torch.cuda.MemPool()
+    with torch.cuda.use_mem_pool(pools[0]):
+        guards, at = holes(q.numel() * 2, B * T * Hq * 4)
+        out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx, workspace=ws_f)
+        assert [x.data_ptr() for x in (out, lse)] == at
+    with torch.cuda.use_mem_pool(pools[1]):
+        more, at = holes(q.numel() * 2, k.numel() * 2, v.numel() * 2)
+        dq, dk, dv = binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, sl, T, idx, workspace=ws_b)
+        assert [x.data_ptr() for x in (dq, dk, dv)] in (at, [at[0], at[2], at[1]])
+    torch.cuda.synchronize()
+    for x in guards + more:
+        assert bool((x == 0x5a).all())
+    for x, y, dim in ((out, want_out, 1), (dq, want_dq, 1), (dk, want_dk, 2), (dv, want_dv, 2)):
+        assert x.shape == (q if dim == 1 else k).shape
+        for b, l in enumerate(lens):
+            a, w = x[b].narrow(dim - 1, 0, l), y[b].narrow(dim - 1, 0, l)
+            if x is out or x is dq:
+                assert torch.equal(a, w)
+            else:                                        # summed with atomics: fp32 order, one bf16 rounding of the sum
+                assert bool(((a.double() - w.double()).abs() <= 2.0 ** -7 * w.double().abs() + 1e-5).all())
+            assert bool((x[b].narrow(dim - 1, l, rows - l) == 0).all())
+    assert torch.equal(lse, want_lse)
+
+
 def test_sparse_attn_prefill_row_that_repeats_a_block():
     # the contract asks for duplicate-free rows; a row that repeats a block all the same must stay inside
     # the caches and attend that block once: same output as the clean row, bit for bit
