@@ -1187,19 +1187,22 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
 }
 
 // ---- attention, part 2: merge the k partials of every query head ---------------------------------
-// grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge, unconditionally
-// (entries past the top-k re-read the last one and get weight zero): kTop is the top-k rounded up.
+// grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge, unconditionally.
+// kTop is the top-k rounded up to 8, 16, 32 or 64 (so entries below kTop / 2 always exist from 16 on); entries past the
+// top-k re-read the last one, and their bits are masked to zero: not weighted with zero (0 * inf), and not by a condition, which
+// the compiler makes a branch around the load (128K context, a step 18.8 -> 19.4 us).
 template <int kTop>
 __global__ __launch_bounds__(128) void decode_merge_kernel(Dims dm, const float *__restrict__ o_part,
                                                             const float2 *__restrict__ ml_part, Tensor out,
                                                             float *__restrict__ lse) {
     const int hq = blockIdx.x, bv = blockIdx.y, cch = threadIdx.x;
     const int64_t pbase = ((int64_t)bv * dm.Hq + hq) * dm.topk;
+    constexpr int kSure = kTop > 8 ? kTop / 2 : 1;
     float2 ml[kTop];
     float ov[kTop];
 #pragma unroll
     for (int c = 0; c < kTop; ++c) {
-        const int64_t at = pbase + min(c, dm.topk - 1);
+        const int64_t at = pbase + (c < kSure ? c : min(c, dm.topk - 1));
         ml[c] = ml_part[at];
         ov[c] = o_part[at * kHeadDim + cch];
     }
@@ -1211,9 +1214,10 @@ __global__ __launch_bounds__(128) void decode_merge_kernel(Dims dm, const float 
     if (M > -INFINITY) {
 #pragma unroll
         for (int c = 0; c < kTop; ++c) {
-            const float w = c < dm.topk ? fast_exp2(ml[c].x - M) : 0.f;
-            den += w * ml[c].y;
-            num += w * ov[c];
+            const uint32_t keep = c < kSure ? ~0u : (uint32_t)((c - dm.topk) >> 31);
+            const float w = fast_exp2(ml[c].x - M);
+            den += w * __uint_as_float(__float_as_uint(ml[c].y) & keep);
+            num += w * __uint_as_float(__float_as_uint(ov[c]) & keep);
         }
     }
     const float o = den > 0.f ? num / den : 0.f;

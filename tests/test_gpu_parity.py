@@ -1205,6 +1205,30 @@ def test_decode_step_short_caches(cap, lens, Hq, Hkv, topk, forced):
         assert out_err(out[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(lse[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# An infinite value in the last selected block makes its channel infinite (as IEEE sums do), and no other: the merge rounds the top-k up
+# and what it adds for the places past the end must not turn the infinity into a NaN.
+@pytest.mark.parametrize("topk", [3, 8, 12, 16, 24, 33])
+def test_decode_merge_keeps_an_infinity_of_the_last_block(topk):
+    print("case infinite value", topk, flush=True)
+    Hq, Hkv, L, n = 8, 2, 64 * 70 - 9, 3
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    gen = torch.Generator(device="cuda").manual_seed(topk)
+    q = torch.randn((1, n, Hq, 128), device="cuda", generator=gen).bfloat16()
+    k, v = (torch.randn((1, Hkv, L, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    v[0, :, L - 20, 7], v[0, 1, L - 21, 100] = float("inf"), -float("inf")
+    idx = torch.cat([torch.arange(topk - 1), torch.tensor([69])]).to(torch.int32).expand(1, Hkv, n, topk).contiguous().cuda()
+    sl = dev_i32([L])
+    q1, idx1 = q[:, -1:].contiguous(), idx[:, :, -1:].contiguous()
+    out, lse = torch.zeros_like(q1), torch.zeros((1, Hq), dtype=torch.float32, device="cuda")
+    results = [binding.sparse_attn_decode(prm, q1, k, v, sl, L, idx1), binding.sparse_attn_verify(prm, q, k, v, sl, L, idx),
+               binding.sparse_attn_decode_noalloc(prm, q1, k, v, sl, L, idx1, out, lse)]
+    for o, ls in results:
+        o = o.float()
+        assert bool((o[..., 7] == float("inf")).all()) and bool((o[:, :, Hq // Hkv:, 100] == -float("inf")).all())
+        o[..., 7], o[:, :, Hq // Hkv:, 100] = 0.0, 0.0
+        assert bool(torch.isfinite(o).all()) and bool(torch.isfinite(ls).all())
+
+
 @pytest.mark.parametrize("B", [1, 4])
 @pytest.mark.parametrize("rho", [2, 4])
 def test_decode_step_approximate_lse_when_the_new_kernel_feeds_another_workgroup(rho, B):
