@@ -147,7 +147,8 @@ int32_t infllmv2_compress_keys(const infllmv2_params *prm, const infllmv2_tensor
  *     R[j]    = max of r[jh] over kernels whose tokens intersect block j,   j <= floor(i/m)
  *     R[j]    = +inf for j < n_init_blocks and for j > floor(i/m) - n_local_blocks
  *     select the min(topk, floor(i/m)+1) blocks of largest R, ties to the lower index.
- * The softmax is computed exactly in two passes (log-sum-exp first, scores second).
+ * The softmax is exact: prefill up to 4096 tokens keeps a row's exponentials and scales them by their sum; elsewhere the
+ * log-sum-exp comes first and the scores in a second pass.
  *   mode       INFLLMV2_MODE_PREFILL: q is [batch, max_seqlen, Hq, d], row t = position t,
  *              rows t >= seqlens[b] are ignored; n_q = max_seqlen rows per sequence.
  *              INFLLMV2_MODE_DECODE: q is [batch, 1, Hq, d], position seqlens[b]-1; n_q = 1.
@@ -157,8 +158,8 @@ int32_t infllmv2_compress_keys(const infllmv2_params *prm, const infllmv2_tensor
  *   workspace  device scratch of infllmv2_workspace_bytes(INFLLMV2_OP_SELECT_*, ...) bytes,
  *              256-byte aligned; contents are undefined before and after the call.  Prefill: the
  *              log-sum-exps of pass 1 (4 bytes per query token and head) and a tiled copy of ck, so
- *              linear in max_seqlen; the block scores are ranked inside pass 2, chunk by chunk in
- *              on-chip memory, and are never stored.
+ *              linear in max_seqlen (asked for and unused where one pass suffices); the block scores are
+ *              ranked in on-chip memory and are never stored.
  */
 int32_t infllmv2_select_blocks(const infllmv2_params *prm, int32_t mode, const infllmv2_tensor *q,
                                const infllmv2_tensor *ck, const int32_t *seqlens, int32_t batch,

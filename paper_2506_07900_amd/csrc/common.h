@@ -316,7 +316,8 @@ int launch_select_prefill16(const Dims &dm, Tensor q, Tensor ck, const int32_t *
 size_t select_prefill16_ws_bytes(const Dims &dm);
 constexpr int kShortPrefill = 4096;                        // tokens: up to 255 semantic kernels (select_short.hip)
 bool select_short_fits(const Dims &dm);
-int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream);
+int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream,
+                        float *scores_out = nullptr, int32_t scores_pitch = 0);
 int32_t select_scores_pitch(const Dims &dm);
 size_t select_scores_bytes(const Dims &dm);
 size_t select_shared_scores_bytes(const Dims &dm);

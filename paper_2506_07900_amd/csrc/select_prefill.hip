@@ -534,12 +534,12 @@ static int launch_select_prefill_g(const Dims &dm, Tensor q, Tensor ck, const in
     return (int)hipGetLastError();
 }
 
-// scores_out != null: stop after pass 2 and leave the block scores of the candidate blocks in
-// scores_out[((b * Hkv + h) * max_seqlen + t) * scores_pitch + j] instead of ranking them.
+// scores_out != null: leave the block scores of the candidate blocks in
+// scores_out[((b * Hkv + h) * max_seqlen + t) * scores_pitch + j] instead of ranking them (the same kernels up to there).
 int launch_select_prefill(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens,
                           int32_t *block_idx, void *ws, hipStream_t stream, float *scores_out,
                           int32_t scores_pitch) {
-    if (!scores_out && select_short_fits(dm)) return launch_select_short(dm, q, ck, seqlens, block_idx, stream);
+    if (select_short_fits(dm)) return launch_select_short(dm, q, ck, seqlens, block_idx, stream, scores_out, scores_pitch);
     switch (dm.G) {
         case 1: return launch_select_prefill_g<1>(dm, q, ck, seqlens, block_idx, ws, stream, scores_out, scores_pitch);
         case 2: return launch_select_prefill_g<2>(dm, q, ck, seqlens, block_idx, ws, stream, scores_out, scores_pitch);

@@ -36,10 +36,11 @@ struct ShortCfg {
     static size_t lds_bytes(int n_c) { return (size_t)((n_c + 15) / 16) * 4096 + (size_t)kShortWaves * kPitch * sizeof(float); }
 };
 
-template <int kG, int kKT>
+// kScores: the scores of every candidate block go to `scores` (infllmv2_block_scores) instead of being ranked.
+template <int kG, int kKT, bool kScores>
 __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
     Dims dm, Tensor q, Tensor ck, const int32_t *__restrict__ seqlens, int32_t *__restrict__ block_idx, int32_t n_units,
-    int32_t wgs, int32_t share_log2) {
+    int32_t wgs, int32_t share_log2, float *__restrict__ scores, int32_t scores_pitch) {
     using C = ShortCfg<kG, kKT>;
     static_assert(64 % C::kTok == 0, "one own block per tile");
     extern __shared__ __align__(16) unsigned char short_smem[];
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
 
     // ---- compressed keys to LDS: tile t, piece p = 4ks + g of row n at [t][ks][16g + (n ^ p)] (an operand read covers 1 KiB
     // in some order, a write's 16 pieces of a row go to 16 different bank groups) -------------------------------
-    if (dm.topk <= (L - 1) / kBlock) {                    // (else every token attends everything)
+    if (kScores || dm.topk <= (L - 1) / kBlock) {         // (else every token attends everything)
         const __bf16 *ckh = ck.ptr + b * ck.sb + h * ck.sh + 8 * (tid & 15);
 #pragma unroll 1
         for (int r0 = tid >> 4; r0 < n_c; r0 += 4 * 4 * kShortWaves) {
@@ -86,7 +87,15 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
         const int n_pick = n_sel - (n_init + (b_own - lo_local + 1));         // from the candidates n_init..lo_local-1
         int32_t *row0 = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
         const int n_tok = min(C::kTok, L - t0);
-        if (n_sel == n_blk || n_pick <= 0) {              // every block, or the forced ones only: nothing to score
+        const int n_vis_lo = num_kernels(t0 + 1), n_vis_hi = num_kernels(t0 + n_tok);
+        if constexpr (kScores) {
+            if (lo_local <= n_init) continue;             // no candidate
+            if (n_vis_hi == 0) {                          // nothing to score: all within the first block
+                for (int u = sub; u < n_tok; u += sub_mask + 1)
+                    if (lane == 0) scores[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0 + u) * scores_pitch] = -INFINITY;
+                continue;
+            }
+        } else if (n_sel == n_blk || n_pick <= 0) {              // every block, or the forced ones only: nothing to score
             for (int u = sub; u < n_tok; u += sub_mask + 1)
                 if (lane < dm.topk) {
                     int x = lane;
@@ -102,7 +111,6 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) qf[ks] = load8(qr + 32 * ks);
         }
-        const int n_vis_lo = num_kernels(t0 + 1), n_vis_hi = num_kernels(t0 + n_tok);
 
         // Straight-line code for kNT kernel tiles (those past the end are masked), so that the products of one tile run
         // under the LDS reads of the next.  Z = Q . CK^T: lane = kernel, accumulator entries = rows 4g .. 4g+3.
@@ -200,10 +208,12 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
                         const f32x4 x = *reinterpret_cast<const f32x4 *>(&rs[4 * j]);
                         const float r = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), rs[4 * j + 4]);
                         key[s] = r == -INFINITY ? 1u : __float_as_uint(r);    // a block without a visible kernel comes last
+                        if constexpr (kScores) scores[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0 + u) * scores_pitch + j] = r;
                     }
                     top = max(top, key[s]);
                 }
                 __builtin_amdgcn_wave_barrier();
+                if constexpr (kScores) continue;
                 uint64_t chosen[C::kVPL];
                 pick_by_bisection<C::kVPL>(key, wave_max_u32(top), n_pick, chosen);
                 int at = n_init;
@@ -227,8 +237,9 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
     }
 }
 
-template <int kG, int kKT>
-static int launch_variant(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream) {
+template <int kG, int kKT, bool kScores>
+static int launch_variant(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream,
+                          float *scores, int32_t scores_pitch) {
     using C = ShortCfg<kG, kKT>;
     const int32_t n_units = (dm.max_seqlen + C::kTok - 1) / C::kTok;
     const size_t lds = C::lds_bytes(num_kernels(dm.max_seqlen));
@@ -240,34 +251,39 @@ static int launch_variant(const Dims &dm, Tensor q, Tensor ck, const int32_t *se
     const int32_t wgs = std::max<int32_t>(1, std::min<int32_t>(((n_units << share) + kShortWaves - 1) / kShortWaves,
                                                               (int32_t)(256 * resident / rows)));
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)select_short_kernel<kG, kKT>,
+        const hipError_t e = hipFuncSetAttribute((const void *)select_short_kernel<kG, kKT, kScores>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((select_short_kernel<kG, kKT>), dim3((uint32_t)((int64_t)wgs * dm.Hkv * dm.batch)), dim3(64 * kShortWaves),
-                       lds, stream, dm, q, ck, seqlens, block_idx, n_units, wgs, share);
+    hipLaunchKernelGGL((select_short_kernel<kG, kKT, kScores>), dim3((uint32_t)((int64_t)wgs * dm.Hkv * dm.batch)), dim3(64 * kShortWaves),
+                       lds, stream, dm, q, ck, seqlens, block_idx, n_units, wgs, share, scores, scores_pitch);
     return 0;
 }
 
 template <int kG>
-static int launch_group(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream) {
+static int launch_group(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream,
+                        float *scores, int32_t pitch) {
     const int n_blocks = (dm.max_seqlen + kBlock - 1) / kBlock;
-    if (n_blocks <= 32) return launch_variant<kG, 8>(dm, q, ck, seqlens, block_idx, stream);
-    return launch_variant<kG, 16>(dm, q, ck, seqlens, block_idx, stream);
+    if (scores)
+        return n_blocks <= 32 ? launch_variant<kG, 8, true>(dm, q, ck, seqlens, block_idx, stream, scores, pitch)
+                              : launch_variant<kG, 16, true>(dm, q, ck, seqlens, block_idx, stream, scores, pitch);
+    return n_blocks <= 32 ? launch_variant<kG, 8, false>(dm, q, ck, seqlens, block_idx, stream, nullptr, 0)
+                          : launch_variant<kG, 16, false>(dm, q, ck, seqlens, block_idx, stream, nullptr, 0);
 }
 
 bool select_short_fits(const Dims &dm) { return dm.rho == 1 && !dm.shared_q && dm.max_seqlen <= kShortPrefill; }
 
-int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream) {
+int launch_select_short(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens, int32_t *block_idx, hipStream_t stream,
+                        float *scores, int32_t scores_pitch) {
     if (dm.max_seqlen <= 0 || dm.batch <= 0) return 0;
     int err = (int)hipErrorInvalidValue;
     timing_begin("select_short_kernel", stream);
     switch (dm.G) {
-        case 1: err = launch_group<1>(dm, q, ck, seqlens, block_idx, stream); break;
-        case 2: err = launch_group<2>(dm, q, ck, seqlens, block_idx, stream); break;
-        case 4: err = launch_group<4>(dm, q, ck, seqlens, block_idx, stream); break;
-        case 8: err = launch_group<8>(dm, q, ck, seqlens, block_idx, stream); break;
-        case 16: err = launch_group<16>(dm, q, ck, seqlens, block_idx, stream); break;
+        case 1: err = launch_group<1>(dm, q, ck, seqlens, block_idx, stream, scores, scores_pitch); break;
+        case 2: err = launch_group<2>(dm, q, ck, seqlens, block_idx, stream, scores, scores_pitch); break;
+        case 4: err = launch_group<4>(dm, q, ck, seqlens, block_idx, stream, scores, scores_pitch); break;
+        case 8: err = launch_group<8>(dm, q, ck, seqlens, block_idx, stream, scores, scores_pitch); break;
+        case 16: err = launch_group<16>(dm, q, ck, seqlens, block_idx, stream, scores, scores_pitch); break;
     }
     timing_end(stream);
     return err ? err : (int)hipGetLastError();

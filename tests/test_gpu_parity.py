@@ -211,6 +211,36 @@ def test_block_scores_against_the_oracle(seqlens, Hq, Hkv, topk):
     assert worst <= 2e-5
 
 
+# The block scores are those the selection ranks, bit for bit: ranking them gives its lists exactly, on inputs so small that
+# scores differ in their last bits only (an independent computation of them ranks about one row in a hundred otherwise).
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk,forced", [
+    ([1500, 20, 65], 32, 2, 8, (1, 2)), ([3000], 32, 2, 16, (0, 0)), ([4096, 4000], 16, 2, 8, (1, 2)), ([4097, 31], 16, 1, 8, (1, 1)),
+    ([2000, 1], 4, 1, 8, (0, 1)), ([4097], 16, 2, 6, (2, 0)), ([2049, 2048], 4, 2, 12, (1, 2)), ([1000], 2, 2, 64, (0, 0)), ([5000], 1, 1, 8, (1, 2))])
+def test_block_scores_rank_as_the_selection_does(seqlens, Hq, Hkv, topk, forced):
+    print("case scores ranked", seqlens, Hq, Hkv, topk, forced, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk, n_init_blocks=forced[0], n_local_blocks=forced[1])
+    B, T = len(seqlens), max(seqlens)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    q = (0.02 * torch.randn((B, T, Hq, 128), device="cuda", generator=gen)).bfloat16()
+    k = (0.02 * torch.randn((B, Hkv, T, 128), device="cuda", generator=gen)).bfloat16()
+    sl = dev_i32(seqlens)
+    ck = binding.compress_keys(prm, k, sl, T)
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)
+    R = binding.block_scores(prm, q, ck, sl, T)
+    own = torch.arange(T, device="cuda")[:, None] // 64
+    j = torch.arange(R.shape[-1], device="cuda")[None]
+    candidate = (j >= forced[0]) & (j <= own - forced[1])
+    for b, l in enumerate(seqlens):
+        r = R[b, :, :l]
+        assert not bool(torch.isnan(r[:, candidate[:l]]).any())             # every candidate's score is written
+        r = torch.where(candidate[:l], r, torch.where(j <= own[:l], float("inf"), -float("inf")))
+        best = torch.sort(r, dim=-1, descending=True, stable=True)[1][..., :topk]      # (ties: the lower block)
+        best = torch.where(torch.arange(best.shape[-1], device="cuda") <= own[:l], best, 1 << 20)
+        best = torch.sort(best, dim=-1)[0]
+        best = torch.nn.functional.pad(torch.where(best == 1 << 20, -1, best), (0, topk - best.shape[-1]), value=-1)
+        assert bool((best == idx[b, :, :l]).all()), (b, int((best != idx[b, :, :l]).any(-1).sum()))
+
+
 @pytest.mark.parametrize("forced", [(0, 0), (0, 1), (3, 0), (2, 4)])
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([1100, 333, 70], 32, 2, 8), ([700, 65], 4, 1, 6)])
 def test_select_blocks_prefill_other_forced_counts(seqlens, Hq, Hkv, topk, forced):
