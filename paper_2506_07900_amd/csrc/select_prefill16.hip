@@ -318,8 +318,8 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
     uint64_t *carry = reinterpret_cast<uint64_t *>(Rl + kMT * kChunkBlocks);          // [kMT][carry_words / kMT]
     uint64_t *tk_lds = carry + lay.carry_words;
     const int carry_pitch = lay.carry_words / kMT;
-    const int nt_all = (n_pick > 0 && jc_max >= n_init) ? min((4 * jc_max + 4 + 15) >> 4, nt_cap) : 0;
-    if (!kFused && nt_all <= 0) return;                                       // forced blocks only
+    const int nt_all = ((!kFused || n_pick > 0) && jc_max >= n_init) ? min((4 * jc_max + 4 + 15) >> 4, nt_cap) : 0;
+    if (!kFused && nt_all <= 0) return;                                       // no candidates
 
     if (nt_all > 0) {
         bf16x8 qf[kMT][4];

@@ -215,7 +215,8 @@ def test_block_scores_against_the_oracle(seqlens, Hq, Hkv, topk):
 # scores differ in their last bits only (an independent computation of them ranks about one row in a hundred otherwise).
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk,forced", [
     ([1500, 20, 65], 32, 2, 8, (1, 2)), ([3000], 32, 2, 16, (0, 0)), ([4096, 4000], 16, 2, 8, (1, 2)), ([4097, 31], 16, 1, 8, (1, 1)),
-    ([2000, 1], 4, 1, 8, (0, 1)), ([4097], 16, 2, 6, (2, 0)), ([2049, 2048], 4, 2, 12, (1, 2)), ([1000], 2, 2, 64, (0, 0)), ([5000], 1, 1, 8, (1, 2))])
+    ([2000, 1], 4, 1, 8, (0, 1)), ([4097], 16, 2, 6, (2, 0)), ([2049, 2048], 4, 2, 12, (1, 2)), ([1000], 2, 2, 64, (0, 0)), ([5000], 1, 1, 8, (1, 2)),
+    ([5000], 16, 1, 3, (1, 2)), ([5000, 700], 4, 1, 3, (1, 2)), ([1500], 32, 2, 2, (0, 2))])         # (every selected block is forced)
 def test_block_scores_rank_as_the_selection_does(seqlens, Hq, Hkv, topk, forced):
     print("case scores ranked", seqlens, Hq, Hkv, topk, forced, flush=True)
     prm = binding.Params(Hq, Hkv, topk=topk, n_init_blocks=forced[0], n_local_blocks=forced[1])
