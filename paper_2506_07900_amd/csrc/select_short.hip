@@ -31,7 +31,6 @@ template <int kG, int kKT>
 struct ShortCfg {
     static constexpr int kTok = 16 / kG;                  // tokens per tile
     static constexpr int kPitch = 16 * kKT + 16;          // floats of the one token a wavefront ranks at a time
-    static constexpr int kVPL = (4 * kKT + 63) / 64;      // blocks per lane in the ranking
     static constexpr int kStep = kKT >= 16 ? kKT / 4 : 4; // kernel tiles between the sizes the code is unrolled for
     static size_t lds_bytes(int n_c) { return (size_t)((n_c + 15) / 16) * 4096 + (size_t)kShortWaves * kPitch * sizeof(float); }
 };
@@ -43,6 +42,7 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
     int32_t wgs, int32_t share_log2, float *__restrict__ scores, int32_t scores_pitch) {
     using C = ShortCfg<kG, kKT>;
     static_assert(64 % C::kTok == 0, "one own block per tile");
+    static_assert(4 * kKT <= 64, "a block per lane in the ranking");
     extern __shared__ __align__(16) unsigned char short_smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x % wgs, h = (blockIdx.x / wgs) % dm.Hkv, b = blockIdx.x / (wgs * dm.Hkv);
@@ -199,31 +199,20 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
                 }
                 __builtin_amdgcn_wave_barrier();          // same wavefront: LDS keeps the order
                 // The n_pick best by bisection on the scores' bit patterns (positive floats order like integers).
-                uint32_t key[C::kVPL], top = 0u;
-#pragma unroll
-                for (int s = 0; s < C::kVPL; ++s) {
-                    const int j = lane + 64 * s;
-                    key[s] = 0u;
-                    if (j >= n_init && j < lo_local) {    // kernels 4j-1 .. 4j+3 = slots 4j .. 4j+4
-                        const f32x4 x = *reinterpret_cast<const f32x4 *>(&rs[4 * j]);
-                        const float r = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), rs[4 * j + 4]);
-                        key[s] = r == -INFINITY ? 1u : __float_as_uint(r);    // a block without a visible kernel comes last
-                        if constexpr (kScores) scores[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0 + u) * scores_pitch + j] = r;
-                    }
-                    top = max(top, key[s]);
+                uint32_t key = 0u;                        // of block `lane`
+                if (lane >= n_init && lane < lo_local) {  // kernels 4 lane - 1 .. 4 lane + 3 = slots 4 lane .. 4 lane + 4
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(&rs[4 * lane]);
+                    const float r = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), rs[4 * lane + 4]);
+                    key = (uint32_t)max(__float_as_int(r), 1);                // a block without a visible kernel (-inf) comes last
+                    if constexpr (kScores) scores[(((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0 + u) * scores_pitch + lane] = r;
                 }
                 __builtin_amdgcn_wave_barrier();
                 if constexpr (kScores) continue;
-                uint64_t chosen[C::kVPL];
-                pick_by_bisection<C::kVPL>(key, wave_max_u32(top), n_pick, chosen);
-                int at = n_init;
-                const uint64_t below = (1ull << lane) - 1ull;
+                uint64_t chosen;
+                pick_by_bisection(key, wave_max_u32(key), n_pick, chosen);
+                const int at = n_init + __popcll(chosen);
                 int32_t *o = row0 + u * dm.topk;
-#pragma unroll
-                for (int s = 0; s < C::kVPL; ++s) {
-                    if ((chosen[s] >> lane) & 1ull) o[at + __popcll(chosen[s] & below)] = lane + 64 * s;
-                    at += __popcll(chosen[s]);
-                }
+                if ((chosen >> lane) & 1ull) o[n_init + __popcll(chosen & ((1ull << lane) - 1ull))] = lane;
                 if (lane < n_init) o[lane] = lane;
                 if (lane >= at && lane < dm.topk) o[lane] = lane < n_sel ? lo_local + (lane - at) : -1;
             }
@@ -242,9 +231,9 @@ static int launch_variant(const Dims &dm, Tensor q, Tensor ck, const int32_t *se
                           float *scores, int32_t scores_pitch) {
     using C = ShortCfg<kG, kKT>;
     const int32_t n_units = (dm.max_seqlen + C::kTok - 1) / C::kTok;
-    const size_t lds = C::lds_bytes(num_kernels(dm.max_seqlen));
+    const size_t lds = C::lds_bytes(num_kernels(dm.max_seqlen));              // at most 73 KiB: two fit a compute unit
     // as many workgroups as the chip holds at a time (each copies the keys once), no more than there are tiles to go round
-    const int resident = lds > 80 * 1024 ? 1 : 2;
+    constexpr int resident = 2;
     const int64_t rows = (int64_t)dm.batch * dm.Hkv;
     int share = 0;
     while ((1 << share) < C::kTok && ((int64_t)n_units * rows << share) * 2 <= 2048 * resident) ++share;
