@@ -215,7 +215,9 @@ int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_
  *     dq_i = softmax_scale sum_t ds k_t        dk_t = softmax_scale sum ds q_i
  * (sums for dk, dv over the tokens that selected t's block and the query heads of the group).
  * bf16 products accumulated in fp32; p and ds are rounded to bf16 before the second products;
- * dk, dv are merged with fp32 atomic adds (the last bits depend on the order).
+ * dk, dv are merged with fp32 atomic adds, one per work item of a block: the tokens that selected it are cut into items of
+ * 12 (short sequences) to 64 steps of 32 (token, head) rows, at G = 16 24 to 128 tokens.  The items' order is not fixed, so
+ * dk and dv of a block with more than two of them can differ from run to run in the last bits of the fp32 sum.  dq repeats.
  *   q, out, dout  in   [batch, max_seqlen, Hq, d] bf16: the forward's input, output and its gradient
  *                      (q, dout: group size x head stride at most 2^30 elements, else INFLLMV2_ERR_UNSUPPORTED)
  *   k, v          in   bf16 caches [batch, Hkv, >=max_seqlen, d]
@@ -224,8 +226,8 @@ int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_
  *   dq            out  [batch, max_seqlen, Hq, d] bf16 (rows t >= seqlens[b] not written)
  *   dk, dv        out  [batch, Hkv, >=max_seqlen, d] bf16 (rows t >= seqlens[b] not written)
  *   workspace     device scratch of infllmv2_workspace_bytes(INFLLMV2_OP_ATTN_BWD, ...) bytes: packed
- *                 copies of the K and V blocks, D and the exponent offsets per (token, head), a block x token
- *                 membership bitmap, fp32 dk / dv
+ *                 copies of the K and V blocks, D and the exponent offsets per (token, head), membership words
+ *                 (32 tokens x block), fp32 dk / dv and the queues of work items cut from the words
  */
 int32_t infllmv2_sparse_attn_bwd(const infllmv2_params *prm, const infllmv2_tensor *q,
                                  const infllmv2_tensor *k, const infllmv2_tensor *v,
@@ -297,7 +299,9 @@ int32_t infllmv2_append_kv(const infllmv2_params *prm, const infllmv2_tensor *k_
  * infllmv2_append_kv (with ck) + infllmv2_select_blocks(INFLLMV2_MODE_DECODE) +
  * infllmv2_sparse_attn_decode, with the append folded into the first selection kernel and the top-k
  * into the per-block attention kernel: four launches instead of six (five when batch * Hkv * topk
- * exceeds 1024: the top-k then runs once per row in a launch of its own), the same caches, ck,
+ * exceeds 1024: the top-k then runs once per row in a launch of its own); with max_seqlen <= 8192 and
+ * the exact log-sum-exp two, append, selection and partial attention being one kernel (three when
+ * batch * Hkv * topk exceeds 1024, 768, 384, 256 for max_seqlen <= 1024, 2048, 4096, 8192).  The same caches, ck,
  * block_idx, out and lse bit for bit.
  *   q, out        [batch, 1, Hq, d] bf16;  k_new, v_new  [batch, Hkv, 1, d] bf16
  *   k, v, ck      the caches (updated in place);  seqlens counts the new token

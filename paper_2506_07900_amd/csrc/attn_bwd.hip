@@ -224,11 +224,12 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
 //   K rows of key tile 2hs, of key tile 2hs+1      -> S^T  = K . Q^T
 //   V rows of key tile 2hs, of key tile 2hs+1      -> dP^T = V . dO^T
 // and the K rows also go to 8 KiB of LDS, from which the transposing load makes the A fragments of dQ^T += K^T . dS^T.
-// No single bound at 32K tokens, G = 16: matrix cores 30 %, vector issue 43 %, L2 -> register 32 KiB per block and
-// union, 35 % of the wavefronts' time in waits.  With several tiles the queries and upstream gradients sit in LDS and a
-// tile's scores and dP are formed together; with one tile they sit in registers and the units are used one at a time.
+// No single bound at 32K tokens, G = 16: matrix cores 33 % of the time, vector arithmetic 33 %, waits 35 % of the wavefronts'
+// time (all four ring units are asked for again only after the last tile's dP).  With several tiles the queries and upstream
+// gradients sit in LDS and a tile's scores and dP are formed together; with one tile they sit in registers and the units are
+// used one at a time.
 // Against two whole tokens per wavefront: 2 x 4096 tokens, G = 8 332 -> 171; 8192 tokens, G = 1 (16 tokens a tile) ~480 -> 96; 32K
-// tokens, G = 16 1590 -> 1350 (1415 with a third, transposed copy of K read from memory in place of the LDS turn), D included.
+// tokens, G = 16 1590 -> 1276 (1415 with a third, transposed copy of K read from memory in place of the LDS turn), D included.
 constexpr int kDqUnits = 8, kDqRing = 4;
 template <int kG, int kTiles>
 struct DqCfg {
@@ -572,8 +573,8 @@ static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, co
 //   P = exp(S - lse), dS = P (dP - D)         lane = key, 16 rows: as bf16 they are the next products' A operands
 //   dV[key, c] += P^T.dO, dK += dS^T.Q        B = the same rows through the transposing LDS load, contraction index permuted to match
 // Nothing passes between the two waves but the staged rows: one barrier per step.
-// Bound by the matrix cores (half of their time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (9.4 GB, L2
-// hit 17 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
+// Bound by the matrix cores (busy 51 % of the time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (9.4 GB
+// past L2, whose hit rate is 17 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
 // keys the LDS reads double.  Against a workgroup per (block, 2048-token segment) with P and dS exchanged through LDS, rows
 // of two whole tokens a step, and blocks dealt to the XCDs by their number (the first block, which every token selects, kept
 // one XCD busy while the others waited: CUs 55 % busy): 32K tokens, G = 16 3440 -> 1190 us; 2 x 4096 tokens, G = 8

@@ -109,10 +109,14 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
 // of the wavefront's list) is issued into the same registers, so loads stay in flight under the
 // wavefront's own arithmetic.
 //
-// What bounds it: the L2 -> register path (64 bytes per clock and compute unit).  At 32K tokens (2 heads, G = 16,
-// top-k 16) the union of two tokens has 24 blocks, of four 33: four tokens per wavefront, their queries in LDS so that
-// the accumulators (128 registers) and a ring of four units fit 256 registers, move 15.9 GB instead of 22.5 GB through
-// that path: 1.00 -> 0.78 ms.  Without misses (32 blocks in all) it would take 0.75 ms, without the softmax 0.76 ms.
+// What bounds it: no unit on its own.  At 32K tokens (2 heads, G = 16, top-k 16) the matrix pipe is busy 32 % of the time, vector
+// arithmetic 34 %, and 32 % of the wavefronts' time is waits: inside a wavefront a tile's products and its exponentials follow
+// one another (11 % of the matrix time runs under vector work).  Leaving parts out, of 0.79 ms (with the events around the
+// launch): the loads alone 0.69, all but the loads 0.52, the matrix products alone 0.43; without the exponentials 0.74, without
+// the value product 0.72, without misses (32 blocks in all) 0.73.  The loads are 16.6 GB (2.7 GB of them past L2), 0.46 ms at the
+// 36 TB/s that a kernel of nothing but fragment loads reaches; with four units of 4 KiB per wavefront under way they run at 24.
+// The union of two tokens has 24 blocks, of four 33: four tokens per wavefront, their queries in LDS so that the accumulators
+// (128 registers) and a ring of four units fit 256 registers, load 16.6 GB instead of 22.5: 1.00 -> 0.78 ms.
 //
 // The softmax keeps a per-head reference exponent taken from the data and re-bases it only when
 // a partial sum leaves the safe range (or on first use, when it is still NaN): the common path is

@@ -6,17 +6,18 @@
 // over n query rows per sequence, with the causal test of the last n x n region replaced by a
 // bit-packed tree mask.
 //
-// A decode step moves a few megabytes, so it is bound by launch and memory latency, not by
+// A step of a few sequences moves a few megabytes, so it is bound by launch and memory latency, not by
 // bandwidth: every kernel below spreads its reads over many workgroups and issues all the loads
 // of a thread before using any of them.
 //
 // Selection (the softmax needs the log-sum-exp over ALL visible kernels before any score exists):
-//   decode_logits_kernel   64 kernels per workgroup: MFMA logits, one partial (max, sum) per head
+//   decode_logits_kernel   128 or 256 kernels per workgroup: MFMA logits, one partial (max, sum) per head
 //                          and workgroup
 //   decode_scores_*kernel  merges the partials into the log-sum-exp, group-mean scores, 5/4 max-pool
 //                          -> block scores; the logits come from scratch (plain decode) or are
 //                          computed again on the matrix cores (verification)
-//   decode_pick_kernel     two-level top-k of the block-score row
+//   decode_pick_kernel     two-level top-k of the block scores (sorted lists of 128 blocks, or a row)
+// Caches of up to 8192 tokens: decode_short_kernel does all of this, and the attention, in one workgroup per block.
 // Attention: one workgroup per selected block (split-KV) writes an unnormalised partial
 // (o, max, sum); decode_merge_kernel combines the k partials per query head.  The one-call steps
 // run the top-k inside the attention kernel (decode_pick_partial_kernel): one launch fewer.
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int
 //   2.  the n_pick best threads publish their elements >= tau; rank by counting among those
 //   3.  every wavefront repeats the ranking of the survivors of all of them and orders the selected blocks
 //
-// Plain decode: the elements are the nb / 64 sorted lists the scoring kernel left.  Verification: a row of nb scores.
+// Plain decode: the elements are the sorted lists, one per 128 blocks, the scoring kernel left.  Verification: a row of nb scores.
 constexpr int kPickThreads = 256, kPickWaves = kPickThreads / 64, kPickMaxVPT = 16;
 // LDS of the top-k, carved out of the kernel's dynamic shared memory (16-byte aligned) so that its size
 // follows the call's top-k instead of the largest one supported.
@@ -1230,7 +1231,7 @@ static inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct DecodeSelLayout {
     int32_t n_c_cap, n_part, nb_cap;
-    int32_t n_lists, list_len;                        // plain decode: sorted lists of pick words, one per 64 blocks
+    int32_t n_lists, list_len;                        // plain decode: sorted lists of pick words, one per kListBlocks blocks
     size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists, or rows of scores
 };
 static DecodeSelLayout decode_sel_layout(const Dims &dm) {
@@ -1257,7 +1258,9 @@ size_t select_decode_ws_bytes(const Dims &dm) {
 // One workgroup per row can score it all (see decode_short_kernel); the approximate log-sum-exp keeps the long path.
 static bool short_cache(const Dims &dm) { return dm.n_q == 1 && dm.rho == 1 && dm.max_seqlen <= kShortTokens; }
 // Fused top-k and attention: every workgroup repeats the top-k of its row, which is free while compute units idle and
-// costs throughput once the launch fills the machine.
+// costs throughput once the launch fills the machine.  Measured (us per step, fused / apart): 512 units 35.7 / 37.3 (16 sequences
+// of 128K), 22.4 / 24.2 (of 20K), 31.9 / 33.8 (16 drafted tokens at 128K); 1024 units 56.6 / 58.3, 29.8 / 31.6, 42.3 / 44.0; 1536
+// units 84.7 / 84.9, 37.6 / 37.1, 54.4 / 53.4; 2048 units 110.3 / 110.6, 44.1 / 44.0, 65.0 / 63.3.
 constexpr int64_t kMaxFusedUnits = 1024;              // (row, key-value head, block) workgroups
 static bool fuse_units(const Dims &dm) { return (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk <= kMaxFusedUnits; }
 
@@ -1419,7 +1422,8 @@ int launch_attn_decode(const Dims &dm, Tensor q, Tensor k, Tensor v, const int32
     return launch_decode_merge(dm, o_part, ml_part, out, lse, stream);
 }
 
-// One decode step for one query per sequence: cache append + selection + attention, four launches.
+// One decode step for one query per sequence: cache append + selection + attention.  Four launches (five with the top-k in one of
+// its own, see fuse_units); two or three up to kShortTokens (see fuse_short).
 int launch_decode_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &append, const int32_t *seqlens,
                        int32_t *block_idx, Tensor out, float *lse, void *ws_select, void *ws_attn,
                        hipStream_t stream) {
@@ -1441,7 +1445,7 @@ int launch_decode_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap
 }
 
 // One verification step for n_q drafted tokens per sequence: append (+ completed semantic kernels),
-// selection per drafted token, tree-masked attention; five launches.
+// selection per drafted token, tree-masked attention; five launches (six with the top-k in one of its own).
 int launch_verify_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &append, const int32_t *seqlens,
                        const uint64_t *tree_mask, int32_t *block_idx, Tensor out, float *lse, void *ws_select,
                        void *ws_attn, hipStream_t stream) {

@@ -982,9 +982,9 @@ def test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk):
 
 
 def test_sparse_attn_backward_long_capacity():
-    # buffers sized for more than 65536 tokens make the dk/dv kernel work on 8192-token segments
-    # (2048 below that); a sequence that crosses a segment boundary and one that does not, the rest
-    # of the capacity unused
+    # buffers much longer than the sequences: the membership words and the dk / dv sums are laid out by the
+    # capacity, the work items cut by 2048-token segments of the sequence; one that ends inside its fifth
+    # segment and one inside its third, the rest of the capacity unused
     seqlens, Hq, Hkv, topk, cap = [9000, 4200], 16, 1, 8, 66000
     prm = binding.Params(Hq, Hkv, topk=topk)
     oprm = oracle_params(prm)
