@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
 // gradients sit in LDS and a tile's scores and dP are formed together; with one tile they sit in registers and the units are
 // used one at a time.
 // Against two whole tokens per wavefront: 2 x 4096 tokens, G = 8 332 -> 171; 8192 tokens, G = 1 (16 tokens a tile) ~480 -> 96; 32K
-// tokens, G = 16 1590 -> 1276 (1415 with a third, transposed copy of K read from memory in place of the LDS turn), D included.
+// tokens, G = 16 1590 -> 1280 (1415 with a third, transposed copy of K read from memory in place of the LDS turn), D included.
 constexpr int kDqUnits = 8, kDqRing = 4;
 template <int kG, int kTiles>
 struct DqCfg {

@@ -14,8 +14,9 @@
 // both passes are software-pipelined by hand: the MFMAs of kernel tile t are issued in the same
 // basic block as the exponentials / reductions of tile t-1.
 //
-// What bounds them: vector arithmetic (active 65 % of the cycles in both passes; matrix pipe 47 % in pass 1 and 34 % in pass 2,
-// 41 % of that under vector work; waits 21 - 26 % of the wavefronts' time) at a clock that the matrix work holds at 2.1 - 2.2 GHz.  So what a tile costs is its vector instructions: scalar tile
+// What bounds them: vector arithmetic (active 65 % of the cycles in both passes at 32K tokens, 75 % at 128K; matrix pipe 47 and
+// 57 % in pass 1, 34 and 43 % in pass 2, 42 % of that under vector work; waits 17 - 26 % of the wavefronts' time) at a clock that
+// the matrix work holds at 2.1 - 2.2 GHz.  So what a tile costs is its vector instructions: scalar tile
 // bounds (wave index made uniform), pooling on bit patterns (move + maximum in one DPP instruction), sums that begin with
 // their first term and one overflow test per half took pass 1 / pass 2 from 270 / 372 to 267 / 361 us at 32K tokens and
 // from 3.73 / 4.84 to 3.62 / 4.64 ms at 128K.  A third fragment buffer (prefetch two tiles ahead) changes nothing: 3.62 / 4.69.
