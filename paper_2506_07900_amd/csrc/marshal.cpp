@@ -85,6 +85,7 @@ int32_t *i32(PyObject *o, const char *name) {
 int32_t integer(PyObject *o) {
     const long long v = PyLong_AsLongLong(o);
     if (v == -1 && PyErr_Occurred()) throw python_error();
+    if (v != static_cast<int32_t>(v)) throw MarshalError("an integer argument does not fit 32 bits");
     return static_cast<int32_t>(v);
 }
 
@@ -162,7 +163,8 @@ PyObject *compress_keys(Args a) {
     Result ck(a[4]);
     int32_t fill = 0;
     if (ck.make()) {
-        const int64_t n = T < prm->kernel_size ? 0 : (T - prm->kernel_size) / prm->kernel_stride + 1;
+        const bool kernels = prm->kernel_size > 0 && prm->kernel_stride > 0 && T >= prm->kernel_size;   // (the library refuses the rest)
+        const int64_t n = kernels ? (T - prm->kernel_size) / prm->kernel_stride + 1 : 0;
         const at::IntArrayRef::value_type shape[4] = {k.size(0), k.size(1), std::max<int64_t>(n, 1), k.size(3)};
         fill = n > 0 && n_new <= 0 && k_shaped(k, prm);   // otherwise the kernel does not visit every row
         ck.own = fill ? at::empty(shape, like(k, at::kBFloat16)) : at::zeros(shape, like(k, at::kBFloat16));

@@ -533,6 +533,23 @@ def test_results_made_by_the_call_end_with_the_tensor(rows, lens, T, Hq, Hkv):
     assert torch.equal(lse, want_lse)
 
 
+def test_numbers_the_library_refuses_raise():
+    # what the binding works out itself (result shapes) must not trip over them first: a stride of zero, more tokens than 32 bits hold
+    k = torch.zeros((1, 1, 64, 128), dtype=torch.bfloat16, device="cuda")
+    q = torch.zeros((1, 64, 4, 128), dtype=torch.bfloat16, device="cuda")
+    sl = dev_i32([64])
+    for bad in (dict(kernel_stride=0), dict(kernel_stride=-16), dict(kernel_size=0), dict(kernel_size=-(1 << 31)), dict(topk=0)):
+        with pytest.raises(binding.InfLLMv2Error, match="invalid argument"):
+            binding.compress_keys(binding.Params(4, 1, **bad), k, sl, 64)
+    prm = binding.Params(4, 1, topk=4)
+    ck = binding.compress_keys(prm, k, sl, 64)
+    for T in ((1 << 32) + 64, 1 << 31, -(1 << 32) + 64):
+        with pytest.raises(binding.InfLLMv2Error, match="32 bits"):
+            binding.compress_keys(prm, k, sl, T)
+        with pytest.raises(binding.InfLLMv2Error, match="32 bits"):
+            binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)
+
+
 def test_sparse_attn_prefill_row_that_repeats_a_block():
     # the contract asks for duplicate-free rows; a row that repeats a block all the same must stay inside
     # the caches and attend that block once: same output as the clean row, bit for bit
