@@ -10,7 +10,7 @@
 // membership words (word of 32 tokens x block) built from the block lists, so both big kernels accumulate
 // in registers:
 //   pack_bwd_kernel     fragment-major copies of every block (K rows, V rows), its tokens' membership bits, its cleared sums
-//   bwd_items_kernel    the members of every block, cut into work items, queued per XCD
+//   bwd_items_kernel    the members of every block, cut into work items, queued per XCD by the tokens they hold
 //   attn_bwd_dq_kernel  workgroup = 1 to 4 MFMA tiles of 16 (token, head) columns, walks the union of the tokens' block lists:
 //                       D, then S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T
 //   attn_bwd_dkdv_kernel  workgroup = one item of a block after the other, wavefront = 32 keys x 128 channels:
@@ -29,27 +29,30 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBwdBlockU4 = 2 * 16 * 64;              // uint4 per packed block: K rows, V rows (32 KiB)
-// The scatter's work items (see bwd_items_kernel): a block with the tokens of at most kSegWords words of 32 tokens.
-constexpr int kSegWords = 64;
+// The scatter's work items (see bwd_items_kernel): a block with some of the tokens of a segment of kSegWords words of 32 tokens.  A
+// segment has a window per XCD, the XCD's queue a bin per segment (or run of segments).
+constexpr int kSegWords = 256;
 constexpr int kQueues = 8;                            // one per XCD
-constexpr int kQueueStride = 64;                      // words between two queues' counters: {length, ..., head, ...} on lines of their own
+constexpr int kWindowWords = kSegWords / kQueues;
+constexpr int kBins = 64;                             // at most, of a queue
+constexpr int kQueueStride = 128;                     // counters of a queue: kBins lengths, then, on a line of its own, the place drawn last
 
 // Members of an item, in steps of 32 (token, head) rows: an equal share for each of the chip's kDkdvGroups workgroups, within
 // 12 .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us
 // with at least 8 / 16 / 32 steps; 1000 tokens, G = 4 would take 31 / 43 / 62); above, the last items keep the others
 // waiting (32K tokens, G = 16: 1190 / 1310 us with at most 64 / 256).
 constexpr int kDkdvGroups = 256 * 4;
-constexpr int kMaxMembers = 1024;
+constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
 static inline int32_t bwd_item_members(const Dims &dm) {
     const int64_t all = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv * dm.topk;
     const int64_t steps = all * dm.G / 32 / kDkdvGroups;             // of 32 rows
     const int64_t m = (steps < 12 ? 12 : steps > 64 ? 64 : steps) * 32 / dm.G;
-    return (int32_t)(m > kMaxMembers ? kMaxMembers : m);
+    return (int32_t)(m > kMaxMembers - 32 ? kMaxMembers - 32 : m);
 }
 
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
-    int32_t members, item_cap;                        // most members of an item (unless one word has more); items per queue
+    int32_t members, seg_shift, n_bins, bin_cap;      // an item's members; segments of a bin (log2), bins of a queue, items of a bin
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
 static inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
@@ -60,11 +63,14 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
     l.members = bwd_item_members(dm);
-    // a segment's items: one per block with a member and one more for the own tokens, and two neighbours of one block together
-    // exceed `members`
-    const size_t ent = (size_t)kSegWords * 32 * dm.topk;
-    const size_t per_seg = (ent < (size_t)l.nb_cap ? ent : (size_t)l.nb_cap) + 2 * ent / l.members + kSegWords / 2 + 1;
-    l.item_cap = (int32_t)((BH * l.n_seg + kQueues - 1) / kQueues * per_seg);
+    l.seg_shift = 0;
+    while ((BH * l.n_seg + ((size_t)1 << l.seg_shift) - 1) >> l.seg_shift > (size_t)kBins) ++l.seg_shift;
+    l.n_bins = (int32_t)((BH * l.n_seg + ((size_t)1 << l.seg_shift) - 1) >> l.seg_shift);
+    // items that end in a window: one per `members` list entries, one more per block with an entry (begun before the window), the
+    // own tokens' of its blocks; and every eighth block's last of the segment
+    const size_t ent = (size_t)kWindowWords * 32 * dm.topk, nb = (size_t)l.nb_cap;
+    const size_t per_window = (ent < nb ? ent : nb) + ent / l.members + kWindowWords / 2 + (nb + kQueues - 1) / kQueues;
+    l.bin_cap = (int32_t)(per_window << l.seg_shift);
     size_t o = 0;
     l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
     l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
@@ -72,7 +78,7 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.acc_dk = o;   o += al256(BH * T * kHeadDim * sizeof(float));
     l.acc_dv = o;   o += al256(BH * T * kHeadDim * sizeof(float));
     l.counters = o; o += al256((size_t)kQueues * kQueueStride * sizeof(uint32_t));
-    l.items = o;    o += al256((size_t)kQueues * l.item_cap * sizeof(uint4));
+    l.items = o;    o += al256((size_t)kQueues * l.n_bins * l.bin_cap * sizeof(uint4));
     l.total = o;
     return l;
 }
@@ -159,60 +165,102 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
 }
 
 // ---- the scatter's work items --------------------------------------------------------------------------------------
-// A thread per (segment, block): the block's members in the segment, cut at word borders into items of about `members`
-// tokens (those inside the block itself, which alone meet the causal edge, apart from the others); item = {sequence and head, block, first word, words | members << 16}.  The items of a segment go to one XCD's queue, so
-// that the q and dout rows that its blocks share are fetched into one L2.
+// A wavefront per (segment, kItemBlocks blocks), a lane per four words: the block's members in the segment, cut behind the word that holds
+// every `members`-th of them (and behind those inside the block itself, which alone meet the causal edge); item = {sequence and head,
+// block, first word, words}.  An item goes to the queue of the window that it ends in, what is left at the segment's end to one by
+// the block's number.  So workgroups that run together on an XCD read the same tokens' q and dout rows, and a block that few tokens
+// select is cut once per 8192 of them: every item costs 32 KiB of K and V and 64 KiB of atomic sums (four times the items: 1190 -> 2210 us
+// for 32K tokens).  Against segments of 2048 tokens, queued as their wavefronts finished: dk/dv 1220 -> 1120 us at 32K tokens, G = 16
+// (segments of 4096: 1100 with the windows' order, 1150 with 2048); this kernel 11.5 -> 14 us there and 11.4 -> 6.9 us for
+// 2 x 4096 tokens (a thread per block walked its words twice, one after the other).
+constexpr int kItemBlocks = 4;
 __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
-                                                         int32_t nb_cap, int32_t n_seg, int32_t members, uint32_t *__restrict__ counters,
-                                                         uint4 *__restrict__ items, int32_t item_cap) {
-    const int seg = blockIdx.x % n_seg, j = (int)(blockIdx.x / n_seg) * 256 + threadIdx.x;
+                                                         int32_t nb_cap, int32_t n_seg, int32_t members, int32_t seg_shift, int32_t n_bins,
+                                                         int32_t bin_cap, uint32_t *__restrict__ counters, uint4 *__restrict__ items) {
+    static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8, "four words a lane, eight lanes a window");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int seg = blockIdx.x % n_seg, j0 = (int)(blockIdx.x / n_seg * 4 + wave) * kItemBlocks;
     const int h = blockIdx.y, b = blockIdx.z;
     const int64_t bh = (int64_t)b * dm.Hkv + h;
     const int L = seq_len(dm, seqlens, b);
     const int w0 = seg * kSegWords, w1 = min(w0 + kSegWords, (L + 31) / 32);   // block j's tokens start at word 2j
-    if (w0 >= w1 || 2 * (int)(blockIdx.x / n_seg) * 256 >= w1) return;         // uniform
-    const uint32_t *src = bits + bh * 2 * nb_cap * nb_cap + min(j, nb_cap - 1);
-    uint32_t count[kSegWords / 4];                       // members per word, a byte each
+    if (w0 >= w1 || 2 * j0 >= w1) return;
+    const int at = w0 + 4 * lane;                         // this lane's words
+    const uint32_t *src = bits + bh * 2 * nb_cap * nb_cap;
+    uint32_t x[kItemBlocks][4];
 #pragma unroll
-    for (int i = 0; i < kSegWords / 4; ++i) {
-        count[i] = 0u;
+    for (int i = 0; i < kItemBlocks; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
+    const float inv = 1.f / (float)members;
+    const int bin = (int)((bh * n_seg + seg) >> seg_shift);
+    uint32_t ends[kItemBlocks];                           // bits 0 .. 3: an item ends with the lane's word; bit 4: the block's last one
+    int place[kItemBlocks];                               // (lanes 8w: where the window's items go; else behind the lanes before)
+#pragma unroll
+    for (int i = 0; i < kItemBlocks; ++i) {
+        const int j = j0 + i;
+        int n[4], sum = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int w = w0 + 4 * i + e;
-            const uint32_t x = src[(int64_t)min(w, w1 - 1) * nb_cap];
-            count[i] |= (w < w1 && w >= 2 * j ? (uint32_t)__popc(x) : 0u) << (8 * e);
+            n[e] = at + e < w1 && at + e >= 2 * j ? __popc(x[i][e]) : 0;
+            sum += n[e];
         }
-    }
-    auto cut = [&](auto emit) __attribute__((always_inline)) {
-        uint32_t sum = 0;
-        int first = 0, last = 0;
+        const int incl = wave_inclusive_sum(sum);
+        int before = incl - sum, left = 0;                // members so far; those behind the lane's last end (or all, if it has none)
+        uint32_t m = 0u;
 #pragma unroll
-        for (int i = 0; i < kSegWords; ++i) {
-            const uint32_t x = (count[i / 4] >> (8 * (i % 4))) & 255u;
-            if (sum && (sum + x > (uint32_t)members || w0 + i == 2 * j + 2)) {
-                emit(first, last, sum);
-                sum = 0;
+        for (int e = 0; e < 4; ++e) {
+            // quotients of integers below 2^13 + 32: half a unit away from the next one, more than the product's error
+            const bool full = (int)(((float)(before + n[e]) + 0.5f) * inv) > (int)(((float)before + 0.5f) * inv);
+            left += n[e];
+            if (full || (at + e == 2 * j + 1 && left > 0)) {
+                m |= 1u << e;
+                left = 0;
             }
-            if (x) {
-                if (!sum) first = i;
-                last = i;
-                sum += x;
-            }
+            before += n[e];
         }
-        if (sum) emit(first, last, sum);
-    };
-    int n = 0;
-    cut([&](int, int, uint32_t) { ++n; });
-    const int incl = wave_inclusive_sum(n), all = __builtin_amdgcn_readlane(incl, 63);
-    if (all == 0) return;
-    const int q = (int)((bh * n_seg + seg) % kQueues);
-    int at = 0;
-    if ((threadIdx.x & 63) == 0) at = (int)atomicAdd(&counters[q * kQueueStride], (uint32_t)all);
-    at = __builtin_amdgcn_readfirstlane(at) + incl - n;
-    uint4 *dst = items + (int64_t)q * item_cap;
-    cut([&](int first, int last, uint32_t sum) {
-        dst[at++] = uint4{(uint32_t)bh, (uint32_t)j, (uint32_t)(w0 + first), (uint32_t)(last - first + 1) | (sum << 16)};
-    });
+        // what is left at the end: behind the last lane that has an end
+        const uint64_t have = __ballot(m != 0u);
+        const int lane_end = have ? 63 - __builtin_clzll(have) : -1;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        const int tail = have ? total - __builtin_amdgcn_readlane(incl, max(lane_end, 0)) + __builtin_amdgcn_readlane(left, max(lane_end, 0)) : total;
+        if (tail > 0 && lane == 8 * (j & 7)) m |= 16u;
+        ends[i] = m;
+        const int mine = __popc(m), sums = wave_inclusive_sum(mine);
+        const int start = __builtin_amdgcn_ds_bpermute(4 * ((lane & 56) - 1), sums);       // lanes before the window
+        const int own = sums - ((lane & 56) ? start : 0);                                  // of the window's, up to this lane
+        const int all = __builtin_amdgcn_ds_bpermute(4 * (lane | 7), own);
+        int to = 0;
+        if ((lane & 7) == 0 && all > 0) to = (int)atomicAdd(&counters[(lane >> 3) * kQueueStride + bin], (uint32_t)all);
+        place[i] = to;
+        n[0] = own - mine;
+        ends[i] |= (uint32_t)n[0] << 8;
+    }
+#pragma unroll
+    for (int i = 0; i < kItemBlocks; ++i) {
+        const uint32_t m = ends[i] & 31u;
+        const uint64_t have = __ballot((m & 15u) != 0u);
+        const int lane_end = have ? 63 - __builtin_clzll(have) : 0;
+        // first word behind the last end of the lanes before this one, and of all
+        const uint64_t below = have & ((1ull << lane) - 1ull);
+        const int mine_end = 4 * lane + 32 - __clz(m & 15u);                               // (behind the lane's own last end)
+        const int prev = __builtin_amdgcn_ds_bpermute(4 * (below ? 63 - __builtin_clzll(below) : 0), mine_end);
+        const int last = __builtin_amdgcn_readlane(mine_end, lane_end);
+        const int own = max(2 * (j0 + i) - w0, 0);        // (the words before the block's own tokens hold nothing: not even zeros)
+        int first = below ? prev : own;
+        int to = __builtin_amdgcn_ds_bpermute(4 * (lane & 56), place[i]) + (int)(ends[i] >> 8);
+        uint4 *dst = items + ((int64_t)(lane >> 3) * n_bins + bin) * bin_cap;
+        auto put = [&](int f, int e) __attribute__((always_inline)) {
+            dst[to++] = uint4{(uint32_t)bh, (uint32_t)(j0 + i), (uint32_t)(w0 + f), (uint32_t)(e - f)};
+        };
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (m & (1u << e)) {
+                put(first, 4 * lane + e + 1);
+                first = 4 * lane + e + 1;
+            }
+        if (m & 16u) put(have ? last : own, w1 - w0);
+    }
 }
 
 // ---- dq: a workgroup owns the tokens of kTiles MFMA tiles of one key-value head ---------------------------
@@ -597,13 +645,14 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                                                                 int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                                 const float *__restrict__ rowc, const float *__restrict__ null_row,
                                                                 const uint32_t *__restrict__ bits, uint32_t *__restrict__ counters,
-                                                                const uint4 *__restrict__ items, int32_t item_cap,
+                                                                const uint4 *__restrict__ items, int32_t n_bins, int32_t bin_cap,
                                                                 float *__restrict__ acc_dk, float *__restrict__ acc_dv) {
     constexpr int kTPS = 32 / kG;                         // tokens per step
     __shared__ uint16_t list[kMaxMembers];                // the item's member tokens as offsets from its first word's first token
     __shared__ BwdSlot slot0, slot1;
     __shared__ uint4 item_s;
-    __shared__ int tries_s;
+    __shared__ int tries_s, total_s;
+    __shared__ uint32_t bins_s[kBins];                    // items in the queue's bins up to this one
     const int tid = threadIdx.x, lane = tid & 63;
     int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     asm volatile("" : "+s"(wave));                        // (a scalar, also after the compiler's own rewriting)
@@ -614,34 +663,46 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     const int64_t s_sb = wave == 0 ? q.sb : dout.sb, s_sh = wave == 0 ? q.sh : dout.sh, s_st = wave == 0 ? q.st : dout.st;
     const uint32_t s_head = (uint32_t)(s_sh * 2);         // bytes from head to head
     auto draw = [&](int x) __attribute__((always_inline)) {
-        return atomicAdd(&counters[((blockIdx.x + x) % kQueues) * kQueueStride + kQueueStride / 2], 1u);
+        return atomicAdd(&counters[((blockIdx.x + x) % kQueues) * kQueueStride + kBins], 1u);
+    };
+    auto count_bins = [&](int x) __attribute__((always_inline)) {
+        const uint32_t n = lane < n_bins ? counters[((blockIdx.x + x) % kQueues) * kQueueStride + lane] : 0u;
+        bins_s[lane] = (uint32_t)wave_inclusive_sum((int)n);
     };
     uint32_t ticket = 0;                                  // thread 0: place in queue `tries` behind the own one
-    if (tid == 0) {
-        tries_s = 0;
-        ticket = draw(0);
+    if (wave == 0) {
+        if (lane == 0) {
+            tries_s = 0;
+            ticket = draw(0);
+        }
+        count_bins(0);
     }
     for (;;) {
         // ---- next item ----------------------------------------------------------------------------------------------
-        if (tid == 0) {
+        if (wave == 0) {
             uint4 it = {0u, 0u, 0u, 0u};
-            for (int x = tries_s; x < kQueues; ticket = draw(x)) {      // ends: a queue that is found empty stays empty
-                const int at = (int)((blockIdx.x + x) % kQueues);
-                if (ticket < counters[at * kQueueStride]) {
-                    it = items[(int64_t)at * item_cap + ticket];
+            for (int x = __builtin_amdgcn_readfirstlane(tries_s);;) {   // ends: a queue that is found empty stays empty
+                const uint32_t t = __builtin_amdgcn_readfirstlane(ticket), upto = bins_s[lane];
+                const int bin = __popcll(__ballot(upto <= t));
+                if (bin < kBins) {
+                    const uint32_t before = bin ? __builtin_amdgcn_readlane((int)upto, max(bin - 1, 0)) : 0u;
+                    it = items[((int64_t)((blockIdx.x + x) % kQueues) * n_bins + bin) * bin_cap + (t - before)];
                     break;
                 }
-                tries_s = ++x;
-                if (x == kQueues) break;
+                if (++x == kQueues) break;
+                if (lane == 0) {
+                    tries_s = x;
+                    ticket = draw(x);
+                }
+                count_bins(x);
             }
-            item_s = it;
+            if (lane == 0) item_s = it;
         }
         __syncthreads();                                  // (also: everyone is past the last item's reads of the list and the slots)
         const int bh = (int)__builtin_amdgcn_readfirstlane(item_s.x), j = (int)__builtin_amdgcn_readfirstlane(item_s.y);
         const int tok0 = 32 * (int)__builtin_amdgcn_readfirstlane(item_s.z);
-        const uint32_t nw = __builtin_amdgcn_readfirstlane(item_s.w);
-        const int total = (int)(nw >> 16);
-        if (total == 0) return;                           // uniform: every queue is empty
+        const int nw = (int)__builtin_amdgcn_readfirstlane(item_s.w);
+        if (nw == 0) return;                              // uniform: every queue is empty
         const int b = bh / dm.Hkv, h = bh - b * dm.Hkv;
         const int L = seq_len(dm, seqlens, b);
         // ---- B operands: K and V rows of keys 32kh + c32, channels 16ks + 8hf .. +7 -------------------------------------
@@ -656,17 +717,23 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         }
         // ---- member tokens, ascending -----------------------------------------------------------------------------------
         if (wave == 0) {
-            uint32_t w = 0u;
-            if (lane < (int)(nw & 0xffffu)) w = bits[((int64_t)bh * 2 * nb_cap + (tok0 >> 5) + lane) * nb_cap + j];
-            const int mine = __popc(w);
-            int at = wave_inclusive_sum(mine) - mine;
-            while (w) {
-                const int bit = __ffs(w) - 1;
-                w &= w - 1;
-                list[at++] = (uint16_t)(lane * 32 + bit);
+            int n = 0;
+            for (int w0 = 0; w0 < nw; w0 += 64) {
+                uint32_t w = 0u;
+                if (w0 + lane < nw) w = bits[((int64_t)bh * 2 * nb_cap + (tok0 >> 5) + w0 + lane) * nb_cap + j];
+                const int mine = __popc(w), incl = wave_inclusive_sum(mine);
+                int at = n + incl - mine;
+                n += __builtin_amdgcn_readlane(incl, 63);
+                while (w) {
+                    const int bit = __ffs(w) - 1;
+                    w &= w - 1;
+                    list[at++] = (uint16_t)((w0 + lane) * 32 + bit);
+                }
             }
+            if (lane == 0) total_s = n;
         }
         __syncthreads();
+        const int total = __builtin_amdgcn_readfirstlane(total_s);
         const int steps = (total + kTPS - 1) / kTPS;
 
         const __bf16 *s_base = s_ptr + b * s_sb + (int64_t)(h * kG) * s_sh + (int64_t)tok0 * s_st;
@@ -827,7 +894,7 @@ static void launch_dkdv(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb,
                         const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint4 *items,
                         float *acc_dk, float *acc_dv, hipStream_t stream) {
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<kG>, dim3(kDkdvGroups), dim3(128), 0, stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc,
-                       null_row, bits, counters, items, l.item_cap, acc_dk, acc_dv);
+                       null_row, bits, counters, items, l.n_bins, l.bin_cap, acc_dk, acc_dv);
 }
 
 // ---- fp32 accumulators -> bf16 gradients ------------------------------------------------------------------
@@ -878,8 +945,8 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
                        l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, null_row);
     timing_end(stream);
     timing_begin("bwd_items_kernel", stream);
-    hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)l.n_seg * ((l.nb_cap + 255) / 256), dm.Hkv, dm.batch), dim3(256), 0, stream, dm,
-                       seqlens, bits, l.nb_cap, l.n_seg, l.members, counters, items, l.item_cap);
+    hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)(l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks))), dm.Hkv, dm.batch),
+                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, l.members, l.seg_shift, l.n_bins, l.bin_cap, counters, items);
     timing_end(stream);
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;
