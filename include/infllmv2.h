@@ -340,7 +340,7 @@ int32_t infllmv2_decode_step(const infllmv2_params *prm, const infllmv2_tensor *
  * infllmv2_sparse_attn_verify   q, out bf16 [batch, n_draft, Hq, d]; tree_mask DEVICE uint64
  *                               [batch, n_draft] or NULL; lse out fp32 [batch, n_draft, Hq];
  *                               arithmetic as in infllmv2_sparse_attn_decode.
- * infllmv2_verify_step          the three calls in one (ck required), five launches instead of six
+ * infllmv2_verify_step          the three calls in one (ck required), four launches instead of six
  *                               (the top-k is folded into the per-block attention kernel unless
  *                               batch * n_draft * Hkv * topk exceeds 1024); the same caches, ck,
  *                               block_idx, out and lse bit for bit.

@@ -92,7 +92,7 @@ struct RowRange {
 // ---- selection, parts 1 and 2 -------------------------------------------------------------------
 // Both parts score semantic kernels against kQT consecutive query tokens of one sequence on the
 // matrix cores.  kQT = 1 is plain decode; verification uses kQT = kVerifyQT.  A workgroup of part 1
-// covers kTW tiles of 16 kernels per wave, one of part 2 tiles_per_wave2 (plus one halo tile).  More
+// covers kTW tiles of 16 kernels per wave, one of part 2 verify_tiles2 (plus one halo tile).  More
 // tiles per wave mean fewer workgroups and fewer log-sum-exp partials for part 2 to merge (every
 // workgroup of part 2 reads all partials of its heads); fewer tiles spread a lone step over more compute
 // units.  Measured at 128K context, plain decode, 1 / 2 / 4 tiles: 21.6 / 21.1 / 21.6 us per step for
@@ -100,10 +100,9 @@ struct RowRange {
 // tiles: 63 us);
 // verification (4 to 64 drafted tokens): under 10 % between them.
 constexpr int kVerifyQT = 4;
-__host__ __device__ constexpr int tiles_per_wave(int qt) { return 2; }                   // part 1, verification
+constexpr int kVerifyTiles = 2;                                                          // part 1, verification
 // part 1, plain decode: by batch size
 static inline int decode_tiles_per_wave(const Dims &dm) { return dm.batch >= 4 ? 4 : 2; }
-__host__ __device__ constexpr int tiles_per_wave2(int qt) { return qt == 1 ? 1 : 2; }   // part 2
 
 // length of the cache up to and including query token qi of sequence b (0: no such row)
 __device__ inline int row_len(const Dims &dm, int L_all, int qi) {
@@ -141,11 +140,13 @@ __device__ inline bf16x8 fresh_kernel_row8(const AppendArgs &ap, int b, int h, i
 // ---- part 1: partial (max, sum) of the relevance softmax ---------------------------------------------
 // grid (n_c_cap / (64*kTW), Hkv, B * ceil(n_q/kQT)); wave w owns kernels chunk + 16*kTW*w .. +16*kTW-1.
 // Z^T = CK . Q^T: lane = query head, 4 accumulator entries = 4 consecutive kernels.
-// With kAppend (plain decode, the fused step) the kernel also opens the step: the workgroups of chunk 0
+// With kAppend (the one-call steps) the kernel also opens the step: the workgroups of chunk 0
 // copy the new token's key and value rows into the caches (nothing before the attention kernel reads
 // them), and the wave that owns the semantic kernel the new token completes builds its representation
 // itself -- 31 cached rows and the new one, fp64 sum in token order, one rounding, the same bits as
-// compress_keys_kernel -- uses it, and stores it for the steps to come.
+// compress_keys_kernel -- uses it, and stores it for the steps to come.  Verification: the same for the n_q new tokens and the up to
+// four kernels they complete, which every workgroup whose chunk holds one builds for itself; the last query tile's stores them.
+// A launch fewer: 16 drafted tokens at 128K 31.5 -> 27.7 us per step, 4 22.4 -> 20.6, 2 x 60K tokens 31.7 -> 27.6.
 template <int kQT, bool kAppend, int kTW>
 __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, Tensor ck,
                                                              const int32_t *__restrict__ seqlens,
@@ -153,19 +154,35 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
                                                              float2 *__restrict__ part,
                                                              float2 *__restrict__ part_c, int32_t n_part,
                                                              AppendArgs ap) {
-    static_assert(!kAppend || kQT == 1, "the fused append is for one query per sequence");
     constexpr int kChunk = 64 * kTW;
+    constexpr int kNewKernels = 5;                    // at most, that the new tokens complete (64 drafted tokens: 4)
     __shared__ float2 wpart[kQT][4][16];
     __shared__ float2 wpart_c[kQT][4][16];
     __shared__ __align__(16) uint16_t qs[kQT > 1 ? kQT * 16 * kQsPitch : 8];
     __shared__ __align__(16) uint32_t newrow[kAppend ? 64 : 1];
+    __shared__ __align__(16) uint16_t newrows[kAppend && kQT > 1 ? kNewKernels * kQsPitch : 8];
     const int h = blockIdx.y;
     const int n_qt = (dm.n_q + kQT - 1) / kQT;        // query tiles per sequence
     const int b = kQT == 1 ? blockIdx.z : blockIdx.z / n_qt;   // kQT = 1 is only launched with n_q = 1
     const int qi0 = (blockIdx.z - b * n_qt) * kQT;
     const int L_all = clamp_len(seqlens[b], dm.max_seqlen);
     bool closes = false;                              // the new token completes semantic kernel n_vis - 1
-    if constexpr (kAppend) {
+    int new_from = 0x7fffffff;                        // several tokens: the kernels from here on are completed by them
+    if constexpr (kAppend && kQT > 1) {
+        const int32_t L_raw = seqlens[b];
+        if (L_raw >= dm.n_q && L_raw <= dm.max_seqlen) {              // as the stand-alone append: others are skipped
+            new_from = num_kernels(L_raw - dm.n_q);
+            if (blockIdx.x == 0 && qi0 == 0)
+                for (int i = threadIdx.x; i < 32 * dm.n_q; i += 256) {
+                    const int qi = i >> 5, c8 = (i & 15) * 8;
+                    const Tensor &src = i & 16 ? ap.v_new : ap.k_new;
+                    const Tensor &dst = i & 16 ? ap.v : ap.k;
+                    *reinterpret_cast<uint4 *>(dst.ptr + b * dst.sb + h * dst.sh + (int64_t)(L_raw - dm.n_q + qi) * dst.st + c8) =
+                        *reinterpret_cast<const uint4 *>(src.ptr + b * src.sb + h * src.sh + qi * src.st + c8);
+                }
+        }
+    }
+    if constexpr (kAppend && kQT == 1) {
         const int32_t L_raw = seqlens[b];
         const bool live = L_raw >= 1 && L_raw <= dm.max_seqlen;       // as the stand-alone append: others are skipped
         if (live && blockIdx.x == 0 && threadIdx.x < 32) {
@@ -188,6 +205,39 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     const int n = lane & 15, g = lane >> 4;
     const int jw = blockIdx.x * kChunk + wave * 16 * kTW; // first kernel of this wave
     const int G = dm.G;
+    const int build_from = max(new_from, (int)blockIdx.x * kChunk), build_to = min(n_vis_max, (int)(blockIdx.x + 1) * kChunk);
+    const bool builds = kAppend && kQT > 1 && build_from < build_to;   // uniform over the workgroup
+    if constexpr (kAppend && kQT > 1)
+        if (builds) {                                 // 32 lanes per kernel: new rows from the call's inputs, older ones from the cache
+            const int c = (threadIdx.x & 31) * 4, jh = build_from + (threadIdx.x >> 5), first_new = L_all - dm.n_q;
+            if (jh < build_to) {
+                const __bf16 *kb = ap.k.ptr + b * ap.k.sb + h * ap.k.sh + c, *nb = ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + c;
+                double acc[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = 0.0;
+                uint2 row[kKernel];
+#pragma unroll
+                for (int t = 0; t < kKernel; ++t) {
+                    const int r = jh * kStride + t;
+                    row[t] = *reinterpret_cast<const uint2 *>(r >= first_new ? nb + (int64_t)(r - first_new) * ap.k_new.st : kb + (int64_t)r * ap.k.st);
+                }
+#pragma unroll
+                for (int t = 0; t < kKernel; ++t) {
+                    acc[0] += (double)__uint_as_float(row[t].x << 16);
+                    acc[1] += (double)__uint_as_float(row[t].x & 0xffff0000u);
+                    acc[2] += (double)__uint_as_float(row[t].y << 16);
+                    acc[3] += (double)__uint_as_float(row[t].y & 0xffff0000u);
+                }
+                uint32_t w[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = f64_to_bf16_rne(acc[e] / (double)kKernel);
+                const uint2 x = {w[0] | w[1] << 16, w[2] | w[3] << 16};
+                *reinterpret_cast<uint2 *>(&newrows[(threadIdx.x >> 5) * kQsPitch + c]) = x;
+                if (qi0 + kQT >= dm.n_q)              // the last query tile sees every kernel: it stores them
+                    *reinterpret_cast<uint2 *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh * ck.st + c) = x;
+            }
+        }
+    __builtin_amdgcn_sched_barrier(0);                // (the rows' registers are free again)
     bf16x8 a[kTW][4], bq[kQT][4];
 #pragma unroll
     for (int i = 0; i < kTW; ++i) {
@@ -195,11 +245,23 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             a[i][ks] = zero8();
-            if (jw + 16 * i + n < n_vis_max) a[i][ks] = load8(ckr + 32 * ks);
+            if (jw + 16 * i + n < (kAppend && kQT > 1 ? min(n_vis_max, new_from) : n_vis_max)) a[i][ks] = load8(ckr + 32 * ks);
         }
     }
     load_query_operands<kQT>(dm, q, b, h, qi0, qs, bq);   // heads >= G repeat head G-1: their columns are never used
-    if constexpr (kAppend) {
+    if constexpr (kAppend && kQT > 1)
+        if (builds) {                                 // (a barrier lies between: the query rows went through LDS too)
+#pragma unroll
+            for (int i = 0; i < kTW; ++i) {
+                const int x = jw + 16 * i + n;
+                if (x >= build_from && x < build_to) {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+                        a[i][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&newrows[(x - build_from) * kQsPitch + 32 * ks + 8 * g]));
+                }
+            }
+        }
+    if constexpr (kAppend && kQT == 1) {
         const int jh_new = n_vis_max - 1;             // = (L - p) / s when the new token closes a kernel
         if (closes && jh_new >= jw && jh_new < jw + 16 * kTW) {       // uniform over the wave
             // lane = channels 2*lane, 2*lane+1: rows L-32 .. L-2 from the cache, row L-1 from k_new
@@ -304,7 +366,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
                         if (r >= dm.rho) break;
                         const int jf = dm.rho * cc + 2 * r;
                         bf16x8 v;
-                        if (kAppend && closes && jf == n_vis_max - 1)
+                        if (kAppend && kQT == 1 && closes && jf == n_vis_max - 1)
                             // the kernel this step completes: another workgroup may be storing it right now,
                             // so its row is built here from the cache and the new key, never read back
                             v = fresh_kernel_row8(ap, b, h, L_all, 32 * ks + 8 * g);
@@ -365,7 +427,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 }
 
 // ---- part 2, several queries per sequence: block scores ----------------------------------------------
-// grid (nb_cap / (16*kTW), Hkv, B * ceil(n_q/kQT)), 256 threads (every block has a workgroup, also a
+// grid (n_lists, Hkv, B * ceil(n_q/kQT)), 256 threads (every block has a workgroup, also a
 // last one too short to hold a complete kernel).  Workgroup bx pools blocks
 // 16*kTW*bx .. +16*kTW-1 of kQT consecutive query tokens; block j needs kernels 4j-1 .. 4j+3, so the
 // workgroup scores 4*kTW+1 tiles of 16 kernels starting one tile before its chunk (of that halo tile
@@ -375,18 +437,21 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 // Z = Q . CK^T: lane = kernel (column), 4 accumulator entries = 4 consecutive heads.  A lane adds its 4
 // heads; the four 16-lane groups leave their sums side by side in LDS and the pooling adds them, so
 // no cross-lane traffic sits between the matrix cores and the scores.
-template <int kQT>
+template <int kQT, int kTW>
 __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, Tensor ck,
                                                              const int32_t *__restrict__ seqlens,
                                                              const float2 *__restrict__ part, int32_t n_part,
-                                                             float *__restrict__ R, int32_t nb_cap) {
-    constexpr int kTW = tiles_per_wave2(kQT), kChunk = 64 * kTW, kTiles = 4 * kTW + 1;
-    constexpr int kChunk1 = 64 * tiles_per_wave(kQT);  // kernels per partial of part 1
+                                                             uint64_t *__restrict__ lists, int32_t list_len) {
+    constexpr int kChunk = 64 * kTW, kTiles = 4 * kTW + 1;
+    constexpr int kBlocks = 16 * kTW;                 // of a list
+    static_assert(kBlocks <= 64 && kQT * kBlocks <= 256, "a lane per block, a query within a wavefront");
+    constexpr int kChunk1 = 64 * kVerifyTiles;  // kernels per partial of part 1
     constexpr int kLanesPerPair = 256 / (16 * kQT);   // lanes that merge the partials of one (query, head)
     constexpr int kMaxPartsPerLane = 16384 / kChunk1 / kLanesPerPair;   // contexts up to 262144 tokens
     __shared__ __align__(16) float lse_h[kQT][16];
     __shared__ float rs[kQT][4][kTiles * 16];         // per 16-lane group: head sums of kernels chunk-16 .. chunk+kChunk-1
     __shared__ __align__(16) uint16_t qs[kQT > 1 ? kQT * 16 * kQsPitch : 8];
+    __shared__ __align__(16) uint64_t words[kQT][16 * kTW];
     const int h = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
@@ -466,23 +531,25 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
         }
     }
     __syncthreads();
-    // ---- group mean, clamps, 5/4 max-pool: thread (t, jl) takes kernels 4j-1 .. 4j+3 = rs[..][4*jl+15 .. +19] ----
-    if (tid < kQT * 16 * kTW) {
-        const int t = tid / (16 * kTW), jl = tid % (16 * kTW);
-        const int j = blockIdx.x * 16 * kTW + jl;
-        const int L = row_len(dm, L_all, qi0 + t);
-        if (L >= 1 && j <= (L - 1) / kBlock) {
-            const int n_vis = num_kernels(L);
-            float v = -INFINITY;
+    // ---- group mean, clamps, 5/4 max-pool: thread (t, jl) takes kernels 4j-1 .. 4j+3 = rs[..][4*jl+15 .. +19]; the list_len
+    // best of a query's kBlocks go to a descending list ----
+    const int t = tid / kBlocks, jl = tid % kBlocks, L = t < kQT ? row_len(dm, L_all, qi0 + t) : 0;
+    if (L >= 1) {
+        const int j = blockIdx.x * kBlocks + jl, n_vis = num_kernels(L);
+        float v = -INFINITY;
 #pragma unroll
-            for (int x = 0; x < 5; ++x) {
-                const int c = 4 * jl + 15 + x, jh = first + c;
-                const float sum = (rs[t][0][c] + rs[t][1][c]) + (rs[t][2][c] + rs[t][3][c]);
-                if (jh >= 0 && jh < n_vis) v = fmaxf(v, fminf(fmaxf(sum * (1.f / G), kScoreFloor), kScoreCeil));
-            }
-            const int64_t bv = (int64_t)b * dm.n_q + qi0 + t;
-            R[(bv * dm.Hkv + h) * nb_cap + j] = v;
+        for (int x = 0; x < 5; ++x) {
+            const int c = 4 * jl + 15 + x, jh = first + c;
+            const float sum = (rs[t][0][c] + rs[t][1][c]) + (rs[t][2][c] + rs[t][3][c]);
+            if (jh >= 0 && jh < n_vis) v = fmaxf(v, fminf(fmaxf(sum * (1.f / G), kScoreFloor), kScoreCeil));
         }
+        const RowRange rr(dm, L);
+        const uint64_t e = pick_element(v, j, rr.n_init, rr.jc_max);
+        words[t][jl] = e;
+        __builtin_amdgcn_wave_barrier();              // same wavefront: LDS keeps the order
+        const int rank = count_larger(words[t], kBlocks, e);   // no two words are equal
+        const int64_t bv = (int64_t)b * dm.n_q + qi0 + t;
+        if (rank < list_len) lists[((bv * dm.Hkv + h) * gridDim.x + blockIdx.x) * list_len + rank] = e;
     }
 }
 
@@ -598,7 +665,7 @@ __global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int
 //   2.  the n_pick best threads publish their elements >= tau; rank by counting among those
 //   3.  every wavefront repeats the ranking of the survivors of all of them and orders the selected blocks
 //
-// Plain decode: the elements are the sorted lists, one per 128 blocks, the scoring kernel left.  Verification: a row of nb scores.
+// The elements are the sorted lists, one per 128 blocks (verification: 32), the scoring kernel left.
 constexpr int kPickThreads = 256, kPickWaves = kPickThreads / 64, kPickMaxVPT = 16;
 // LDS of the top-k, carved out of the kernel's dynamic shared memory (16-byte aligned) so that its size
 // follows the call's top-k instead of the largest one supported.
@@ -620,39 +687,30 @@ static inline size_t pick_shared_bytes(int topk, int vpt) {
     return words * sizeof(uint64_t);
 }
 
-// This thread's kVPT elements of row `row` of the top-k's input: words of the lists (kLists) or scores of a row.  Every
+// This thread's kVPT elements of row `row` of the top-k's input, words of the lists.  Every
 // load goes out before the sequence length is known; what lies past the end is dropped afterwards.
 struct PickInput {
-    const void *base;                                     // lists: uint64 [rows][n_lists][list_len]; scores: float [rows][pitch]
+    const uint64_t *lists;                                // [rows][n_lists][list_len]
     int32_t n_lists, list_len, inv;                       // inv: i / n_lists = (i * inv) >> 20 for i < 4096
-    int32_t pitch;
+    int32_t blocks;                                       // of a list
 };
-template <bool kLists, int kVPT>
+template <int kVPT>
 struct PickLoad {
-    uint64_t w[kLists ? kVPT : 1];
-    float r[kLists ? 1 : kVPT];
+    uint64_t w[kVPT];
     __device__ PickLoad(const PickInput &in, int64_t row) {
 #pragma unroll
         for (int s = 0; s < kVPT; ++s) {
             const int i = threadIdx.x + kPickThreads * s;
-            if constexpr (kLists) {                       // element i = entry i / n_lists of list i % n_lists
-                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
-                w[s] = reinterpret_cast<const uint64_t *>(in.base)[(row * in.n_lists + list) * in.list_len + min(rank, in.list_len - 1)];
-            } else {
-                r[s] = reinterpret_cast<const float *>(in.base)[row * in.pitch + min(i, in.pitch - 1)];
-            }
+            const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;   // entry i / n_lists of list i % n_lists
+            w[s] = in.lists[(row * in.n_lists + list) * in.list_len + min(rank, in.list_len - 1)];
         }
     }
-    __device__ void elements(const PickInput &in, const RowRange &rr, int L, uint64_t (&el)[kVPT]) const {
+    __device__ void elements(const PickInput &in, int L, uint64_t (&el)[kVPT]) const {
 #pragma unroll
         for (int s = 0; s < kVPT; ++s) {
             const int i = threadIdx.x + kPickThreads * s;
-            if constexpr (kLists) {
-                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
-                el[s] = (rank < in.list_len && list * kListBlocks <= (L - 1) / kBlock) ? w[s] : 0ull;   // (later lists were not written)
-            } else {
-                el[s] = pick_element(r[s], i, rr.n_init, rr.jc_max);
-            }
+            const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
+            el[s] = (rank < in.list_len && list * in.blocks <= (L - 1) / kBlock) ? w[s] : 0ull;   // (later lists were not written)
         }
     }
 };
@@ -754,13 +812,13 @@ __device__ inline int order_row(int *mine, int n_sel, int topk, int32_t *__restr
     return rank;
 }
 
-template <bool kLists, int kVPT>
+template <int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, const int32_t *__restrict__ seqlens,
                                                                     PickInput in, int32_t *__restrict__ block_idx) {
     extern __shared__ __align__(16) unsigned char pick_smem[];
     const PickShared sh(pick_smem, dm.topk, kVPT);
     const int row = blockIdx.x, bv = row / dm.Hkv, h = row - bv * dm.Hkv;
-    const PickLoad<kLists, kVPT> load(in, row);
+    const PickLoad<kVPT> load(in, row);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     int32_t *o = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
@@ -770,7 +828,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, cons
     }
     const RowRange rr(dm, L);
     uint64_t el[kVPT];
-    load.elements(in, rr, L, el);
+    load.elements(in, L, el);
     __shared__ __align__(16) int mine[kPickWaves][64];
     pick_row<kVPT>(rr, el, sh, mine[threadIdx.x >> 6]);
     if (threadIdx.x < 64) order_row(mine[0], rr.n_sel, dm.topk, o);
@@ -953,7 +1011,7 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
 // key-value head) repeats the top-k on the same input (same result; workgroup 0 writes it out) and goes on with one
 // entry of the result as it stands, best first; the list's ascending order, which decides where the partial result goes,
 // is worked out while the block's rows are on their way.
-template <bool kLists, int kVPT>
+template <int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                                             const int32_t *__restrict__ seqlens,
                                                                             PickInput in,
@@ -964,7 +1022,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     extern __shared__ __align__(16) unsigned char pick_smem[];
     const PickShared sh(pick_smem, dm.topk, kVPT);
     const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
-    const PickLoad<kLists, kVPT> load(in, (int64_t)bv * dm.Hkv + h);
+    const PickLoad<kVPT> load(in, (int64_t)bv * dm.Hkv + h);
     const BlockRows rows(k, v, kBlock - 1);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
@@ -977,7 +1035,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     } else {
         const RowRange rr(dm, L);
         uint64_t el[kVPT];
-        load.elements(in, rr, L, el);
+        load.elements(in, L, el);
         pick_row<kVPT>(rr, el, sh, mine[wave]);
         n_sel = rr.n_sel;
         if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
@@ -1229,24 +1287,32 @@ __global__ __launch_bounds__(128) void decode_merge_kernel(Dims dm, const float 
 // ---- host side -------------------------------------------------------------------------------------
 static inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// Part 2, verification: tiles per wave, and so blocks per list of the top-k: four where that leaves a workgroup for every compute
+// unit.  Measured (us per step at 128K, two / four): 4 drafted tokens 20.5 / 22.1, 16 27.9 / 27.6, 64 62.1 / 59.8.
+static int verify_tiles2(const Dims &dm) {
+    const int64_t wide = (int64_t)((dm.max_seqlen + 64 * kBlock - 1) / (64 * kBlock)) * dm.Hkv * dm.batch * ((dm.n_q + kVerifyQT - 1) / kVerifyQT);
+    return wide >= 256 ? 4 : 2;
+}
+
 struct DecodeSelLayout {
     int32_t n_c_cap, n_part, nb_cap;
-    int32_t n_lists, list_len;                        // plain decode: sorted lists of pick words, one per kListBlocks blocks
-    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists, or rows of scores
+    int32_t list_blocks, n_lists, list_len;           // sorted lists of pick words, one per list_blocks blocks
+    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists
 };
 static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     DecodeSelLayout l;
     int32_t n_c = num_kernels(dm.max_seqlen);
     l.n_c_cap = (n_c + 255) / 256 * 256;
     if (l.n_c_cap < 256) l.n_c_cap = 256;
-    l.n_part = l.n_c_cap / (64 * (dm.n_q == 1 ? decode_tiles_per_wave(dm) : tiles_per_wave(kVerifyQT)));
+    l.n_part = l.n_c_cap / (64 * (dm.n_q == 1 ? decode_tiles_per_wave(dm) : kVerifyTiles));
     l.nb_cap = ((dm.max_seqlen + kBlock - 1) / kBlock + 63) / 64 * 64;
     const size_t rows = (size_t)dm.batch * dm.n_q;
     l.z_bytes = dm.n_q == 1 ? align256(rows * dm.Hq * l.n_c_cap * sizeof(float)) : 0;
     l.part_bytes = align256(rows * dm.Hq * l.n_part * sizeof(float2));
-    l.n_lists = max(1, (dm.max_seqlen + kBlock * kListBlocks - 1) / (kBlock * kListBlocks));
-    l.list_len = max(1, dm.topk - dm.n_init - dm.n_local);
-    l.r_bytes = align256(rows * dm.Hkv * (dm.n_q == 1 ? (size_t)l.n_lists * l.list_len * sizeof(uint64_t) : l.nb_cap * sizeof(float)));
+    l.list_blocks = dm.n_q == 1 ? kListBlocks : 16 * verify_tiles2(dm);
+    l.n_lists = max(1, (dm.max_seqlen + kBlock * l.list_blocks - 1) / (kBlock * l.list_blocks));
+    l.list_len = min(l.list_blocks, max(1, dm.topk - dm.n_init - dm.n_local));
+    l.r_bytes = align256(rows * dm.Hkv * l.n_lists * l.list_len * sizeof(uint64_t));
     return l;
 }
 
@@ -1310,7 +1376,7 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     float *zbuf = reinterpret_cast<float *>(wsb);
     float2 *part = reinterpret_cast<float2 *>(wsb + l.z_bytes);
     float2 *part_c = reinterpret_cast<float2 *>(wsb + l.z_bytes + l.part_bytes);
-    void *R = wsb + l.z_bytes + 2 * l.part_bytes;
+    uint64_t *lists = reinterpret_cast<uint64_t *>(wsb + l.z_bytes + 2 * l.part_bytes);
     const int rows = dm.batch * dm.n_q;                              // <= 65535, checked by the C ABI
     const int n_qt = (dm.n_q + kVerifyQT - 1) / kVerifyQT;
     const float2 *part_lse = dm.rho > 1 ? part_c : part;
@@ -1328,9 +1394,13 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
         if (tw4) INFLLMV2_LOGITS(false, 4, no_append);
         else INFLLMV2_LOGITS(false, 2, no_append);
     } else {
-        hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, false, tiles_per_wave(kVerifyQT)>),
-                           dim3(l.n_part, dm.Hkv, dm.batch * n_qt), dim3(256), 0, stream, dm, q, ck, seqlens, nullptr, 0,
-                           part, part_c, l.n_part, no_append);
+        const dim3 grid(l.n_part, dm.Hkv, dm.batch * n_qt);
+        if (append)
+            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, true, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
+                               nullptr, 0, part, part_c, l.n_part, *append);
+        else
+            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, false, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
+                               nullptr, 0, part, part_c, l.n_part, no_append);
     }
 #undef INFLLMV2_LOGITS
     timing_end(stream);
@@ -1338,41 +1408,34 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     if (dm.n_q == 1)
         hipLaunchKernelGGL(decode_scores_z_kernel, dim3(l.n_lists, dm.Hkv, dm.batch), dim3(576), 0, stream,
                            dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm),
-                           reinterpret_cast<uint64_t *>(R), l.list_len);
+                           lists, l.list_len);
     else
-        hipLaunchKernelGGL(decode_scores_kernel<kVerifyQT>,
-                           dim3(l.nb_cap / (16 * tiles_per_wave2(kVerifyQT)), dm.Hkv, dm.batch * n_qt), dim3(256), 0,
-                           stream, dm, q, ck, seqlens, part_lse, l.n_part, reinterpret_cast<float *>(R), l.nb_cap);
+        hipLaunchKernelGGL((l.list_blocks == 64 ? decode_scores_kernel<kVerifyQT, 4> : decode_scores_kernel<kVerifyQT, 2>),
+                           dim3(l.n_lists, dm.Hkv, dm.batch * n_qt), dim3(256), 0, stream, dm, q, ck, seqlens, part_lse, l.n_part,
+                           lists, l.list_len);
     timing_end(stream);
-    const bool lists = dm.n_q == 1;
-    const int n_elements = lists ? l.n_lists * l.list_len : (dm.max_seqlen + kBlock - 1) / kBlock;
+    const int n_elements = l.n_lists * l.list_len;
     const int vpt = (n_elements + kPickThreads - 1) / kPickThreads;
     if (vpt > kPickMaxVPT) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
-    const PickInput in = {R, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.nb_cap};
+    const PickInput in = {lists, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.list_blocks};
     if (attend) attend->fused = fuse_units(dm);
     const bool fused = attend && attend->fused;
     timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
-#define INFLLMV2_PICK(LISTS, VPT)                                                                                       \
+#define INFLLMV2_PICK(VPT)                                                                                              \
     do {                                                                                                                \
         if (fused)                                                                                                      \
-            hipLaunchKernelGGL((decode_pick_partial_kernel<LISTS, VPT>), dim3(dm.topk, dm.Hkv, rows),                   \
+            hipLaunchKernelGGL((decode_pick_partial_kernel<VPT>), dim3(dm.topk, dm.Hkv, rows),                          \
                                dim3(kPickThreads), pick_shared_bytes(dm.topk, VPT), stream, dm, q, attend->k,           \
                                attend->v, seqlens, in, attend->tree_mask, block_idx, attend->o_part, attend->ml_part);  \
         else                                                                                                            \
-            hipLaunchKernelGGL((decode_pick_kernel<LISTS, VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),               \
+            hipLaunchKernelGGL((decode_pick_kernel<VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),                      \
                                pick_shared_bytes(dm.topk, VPT), stream, dm, seqlens, in, block_idx);                    \
     } while (0)
-    if (lists) {
-        if (vpt <= 1) INFLLMV2_PICK(true, 1);
-        else if (vpt <= 2) INFLLMV2_PICK(true, 2);
-        else if (vpt <= 4) INFLLMV2_PICK(true, 4);
-        else if (vpt <= 8) INFLLMV2_PICK(true, 8);
-        else INFLLMV2_PICK(true, 16);
-    } else {
-        if (vpt <= 4) INFLLMV2_PICK(false, 4);
-        else if (vpt <= 8) INFLLMV2_PICK(false, 8);
-        else INFLLMV2_PICK(false, 16);
-    }
+    if (vpt <= 1) INFLLMV2_PICK(1);
+    else if (vpt <= 2) INFLLMV2_PICK(2);
+    else if (vpt <= 4) INFLLMV2_PICK(4);
+    else if (vpt <= 8) INFLLMV2_PICK(8);
+    else INFLLMV2_PICK(16);
 #undef INFLLMV2_PICK
     timing_end(stream);
     return (int)hipGetLastError();
@@ -1445,16 +1508,18 @@ int launch_decode_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap
 }
 
 // One verification step for n_q drafted tokens per sequence: append (+ completed semantic kernels),
-// selection per drafted token, tree-masked attention; five launches (six with the top-k in one of its own).
+// selection per drafted token, tree-masked attention; four launches (one more with the top-k in one of its own, and with the
+// append in one of its own for the approximate log-sum-exp).
 int launch_verify_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &append, const int32_t *seqlens,
                        const uint64_t *tree_mask, int32_t *block_idx, Tensor out, float *lse, void *ws_select,
                        void *ws_attn, hipStream_t stream) {
     if (dm.batch <= 0) return 0;
-    int err = launch_append_kv(dm, append.k_new, append.v_new, append.k, append.v, &ck, seqlens, stream);
+    const bool folded = dm.n_q > 1 && dm.rho == 1;        // (a coarse kernel would need rows that other workgroups are storing)
+    int err = folded ? 0 : launch_append_kv(dm, append.k_new, append.v_new, append.k, append.v, &ck, seqlens, stream);
     if (err) return err;
     AttendArgs at = {append.k, append.v, tree_mask, false, nullptr, nullptr};
     attn_decode_ws(dm, ws_attn, at.o_part, at.ml_part);
-    err = launch_select_decode(dm, q, ck, seqlens, block_idx, ws_select, stream, nullptr, &at);
+    err = launch_select_decode(dm, q, ck, seqlens, block_idx, ws_select, stream, folded ? &append : nullptr, &at);
     if (err) return err;
     if (!at.fused) launch_decode_partial(dm, q, append.k, append.v, seqlens, block_idx, tree_mask, at.o_part, at.ml_part, stream);
     return launch_decode_merge(dm, at.o_part, at.ml_part, out, lse, stream);

@@ -890,6 +890,33 @@ def test_verify_append_writes_rows_and_completed_kernels():
         assert np.array_equal(got[b, :, :w.shape[1]], w), (b, l)
 
 
+# One call against its parts, bit for bit: new kernels on either side of a workgroup's 128, caches no longer than the draft, a length
+# beyond the cache, both widths of the scoring workgroups.
+@pytest.mark.parametrize("seqlens,n,Hq,Hkv,topk,rho", [
+    ([2080, 2079, 2096, 4128, 31], 33, 32, 2, 16, 1), ([2081, 2, 33, 1], 2, 4, 1, 6, 1), ([4200, 64, 95, 63, 9999], 64, 16, 2, 64, 1),
+    ([3000, 2090], 16, 16, 1, 24, 2)])
+def test_verify_step_equals_its_parts(seqlens, n, Hq, Hkv, topk, rho):
+    print("case verify step", seqlens, n, Hq, Hkv, topk, rho, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk, lse_coarse_ratio=rho)
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    B, T = len(seqlens), max(x for x in seqlens if x < 9000) + 3
+    q = torch.randn((B, n, Hq, 128), device="cuda", generator=gen).bfloat16()
+    kn, vn = (torch.randn((B, Hkv, n, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    sl = dev_i32(seqlens)
+    ck = torch.full((B, Hkv, binding.num_kernels(T, prm), 128), 5.0, dtype=torch.bfloat16, device="cuda")
+    binding.compress_keys(prm, k, dev_i32([x - n if n <= x <= T else min(x, T) for x in seqlens]), T, ck=ck)
+    masks = dev_masks(np.stack([tree_masks(np.random.default_rng(3 + b), n, "tree") for b in range(B)]))
+    parts, step = [x.clone() for x in (k, v, ck)], [x.clone() for x in (k, v, ck)]
+    binding.append_kv_verify(prm, kn, vn, parts[0], parts[1], sl, T, ck=parts[2])
+    idx = binding.select_blocks_verify(prm, q, parts[2], sl, T)
+    out, lse = binding.sparse_attn_verify(prm, q, parts[0], parts[1], sl, T, idx, tree_mask=masks)
+    got = binding.verify_step(prm, q, kn, vn, *step, sl, T, tree_mask=masks)
+    torch.cuda.synchronize()
+    for a, b in zip(parts + [idx, out, lse], step + list(got)):
+        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
+
+
 # ------------------------------------------------------------------ backward of the sparse attention
 
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk,planted", [
