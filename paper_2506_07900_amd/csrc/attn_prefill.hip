@@ -143,7 +143,11 @@ __device__ __forceinline__ float half_probs(const f32x4 (&s)[2], float c, float 
 
 template <int kG, int kTiles, int kSplit>
 struct AttnCfg {
-    static constexpr bool kQLds = kTiles > 2;             // queries in LDS: registers hold the accumulators of four tiles
+    // Queries in LDS: with four tiles the registers hold the accumulators.  With two, G = 16 then fits 168 registers and three
+    // workgroups share a compute unit: 777 tokens 22.4 -> 20.5 us, 1020 28.1 -> 26.8, 2 x 700 with one head 18.9 -> 17.1 (G = 8:
+    // 180 registers, 500 tokens 12.2 -> 11.9; G = 4 and 2: 22.6 -> 23.0 at 2000 tokens, 73.8 -> 75.5 at 7000).
+    static constexpr bool kQLds = kTiles > 2 || (kTiles == 2 && kG >= 8);
+    static constexpr int kWavesPerSimd = kTiles == 2 && kG == 16 ? 3 : 2;
     static constexpr int kTokPerTile = 16 / kG;           // tokens in the 16 columns of one MFMA tile
     static constexpr int kTok = kTiles * kTokPerTile;     // tokens of a wavefront (of the workgroup when its waves split the blocks)
     static constexpr int kTokPerWg = kSplit > 1 ? kTok : 4 * kTok;
@@ -162,7 +166,7 @@ struct AttnCfg {
 // (Rows fetched as the operand wants them, 16 x 64 bytes per load, were slower from 256 tokens on: half lines.  Two tiles
 // spill with their queries in registers and lose more to LDS than the launch costs without: 2048 tokens, G = 4 19.1 / 21.6 us.)
 template <int kG, int kTiles, int kSplit, bool kDirect>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
+__global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) void attn_prefill_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                             const uint4 *__restrict__ kvp, int32_t nb_cap,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
@@ -744,7 +748,7 @@ static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, con
 // call fills (two fit a compute unit: 512 fill the chip).  More tiles per wavefront mean fewer bytes per token, since
 // a fetched block serves every token that selected it; splitting the blocks over four waves makes four times as many
 // waves out of few tokens.  Measured over 150 .. 32768 tokens, 2 key-value heads, top-k 16 (us, start -> now):
-//   G = 16: 150 17 -> 9, 1500 56 -> 37, 4096 128 -> 100, 32768 1024 -> 777;  G = 4: 777 31 -> 15, 4096 123 -> 57,
+//   G = 16: 150 17 -> 9, 1500 56 -> 36, 4096 128 -> 97, 32768 1024 -> 775;  G = 4: 777 31 -> 15, 4096 123 -> 57,
 //   32768 1148 -> 755;  G = 1: 777 31 -> 12, 4096 124 -> 38, 32768 1339 -> 534
 // The lines: four tiles, split, from 512 workgroups on (at 390 .. 750 it meets two tiles for every G); two tiles, split,
 // from 192 (at 190 it meets one tile); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
