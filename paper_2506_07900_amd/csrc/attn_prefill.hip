@@ -179,23 +179,31 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
     // grid: 8 XCDs x slots x (sequence, key-value head); see launch_attn_variant
     const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
     const int h = bh % dm.Hkv, b = bh / dm.Hkv;
-    int32_t L = __builtin_amdgcn_readfirstlane(seqlens[b]);
-    L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int tile = (L + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Tiles are dealt last first.  Waves that work alone count them from the sequence's end; a splitting workgroup counts them from
+    // the capacity, so that it can ask for its rows of block lists before the length has arrived.
+    int32_t L = __builtin_amdgcn_readfirstlane(seqlens[b]);
+    if (kSplit == 1) L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
+    const int tile = ((kSplit > 1 ? dm.max_seqlen : L) + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
     const int t0 = kSplit > 1 ? tile * kTok : (tile * 4 + wave) * kTok;   // this wavefront's first token
-    if (kDirect && dm.fill) {                            // rows past the end: this tile's, or one of those behind the last
-        const int f0 = tile >= 0 ? t0 : ((L + kTok - 1) / kTok - 1 - tile) * kTok;
+    if (tile < 0) return;
+    const int32_t *idx_rows = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
+    const UnionRows<kTok> idx_head(idx_rows, kSplit == 1 ? min(kTok, (int)L - t0) * dm.topk :
+                                             wave == 0 ? min(kTok, dm.max_seqlen - t0) * dm.topk : 0, lane);
+    if (kSplit > 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
+    }
+    if (kDirect && dm.fill)                              // rows past the end
         for (int i = threadIdx.x; i < kTok * kG * 16; i += 256) {
-            const int tok = f0 + i / (kG * 16), hq = h * kG + i / 16 % kG;
+            const int tok = t0 + i / (kG * 16), hq = h * kG + i / 16 % kG;
             if (tok >= L && tok < dm.max_seqlen) {
                 *reinterpret_cast<uint4 *>(out.ptr + b * out.sb + (int64_t)tok * out.st + (int64_t)hq * out.sh + 8 * (i & 15)) =
                     uint4{0u, 0u, 0u, 0u};
                 if ((i & 15) == 0) lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + hq] = 0.f;
             }
         }
-    }
-    if (tile < 0 || t0 >= L) return;                     // (uniform over the workgroup when it splits the blocks)
+    if (t0 >= L) return;                                 // (uniform over the workgroup when it splits the blocks)
     const int b_own = t0 / kBlock;                       // kTok divides 64: one own block per wavefront
     const int n = lane & 15, g = lane >> 4;              // MFMA column (token, query head) and 16-lane group
     const int tn = n / kG;                               // token of the column inside its tile
@@ -222,8 +230,7 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
     const UnionLds ul(attn_smem + (kSplit > 1 ? 0 : wave * UnionLds::bytes(kTok, dm.topk)));
     int cnt = 0;
     if (kSplit == 1 || wave == 0)
-        cnt = build_union<kTok>(block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk, dm.topk,
-                                min(kTok, (int)L - t0), b_own, ul, lane);
+        cnt = build_union<kTok>(idx_head, idx_rows, dm.topk, min(kTok, (int)L - t0), b_own, ul, lane);
     if constexpr (kSplit > 1) {
         __shared__ int cnt_s;
         if (threadIdx.x == 0) cnt_s = cnt;

@@ -29,23 +29,32 @@ struct UnionLds {
         : words(reinterpret_cast<uint32_t *>(p)), prefix(words + 64), list(reinterpret_cast<uint2 *>(p + 512)) {}
 };
 
+// A lane's first entries of the tokens' rows.  A workgroup that lives for a few round trips to memory asks for them before it knows
+// the sequence's length: n_ent are those that lie within the tensor (max_seqlen rows per sequence and head).
+template <int NT>
+struct UnionRows {
+    static constexpr int kE = NT >= 4 ? NT / 4 : 1;      // entries per lane kept in registers: top-k 16; more are re-read
+    int ent[kE];
+    __device__ UnionRows(const int32_t *__restrict__ rows, int n_ent, int lane) {
+#pragma unroll
+        for (int i = 0; i < kE; ++i) ent[i] = lane + 64 * i < n_ent ? rows[lane + 64 * i] : -1;
+    }
+};
+
 // Ascending union of the lists of n_tok <= NT <= 32 consecutive tokens.  rows: their n_tok * topk entries, contiguous;
 // entries < 0 or > b_own are dropped, a block that a row lists twice counts once.  Returns the number of distinct
 // blocks.  An entry's place is the number of set bits before its own in the bitmap, so nothing is sorted and the
 // order of the rows' entries does not matter; sequences of more than 2048 blocks take several rounds.
 template <int NT>
-__device__ inline int build_union(const int32_t *__restrict__ rows, int topk, int n_tok, int b_own, const UnionLds &u,
-                                  int lane) {
-    constexpr int kE = NT >= 4 ? NT / 4 : 1;             // entries per lane kept in registers: top-k 16; more are re-read
+__device__ inline int build_union(const UnionRows<NT> &head, const int32_t *__restrict__ rows, int topk, int n_tok, int b_own,
+                                  const UnionLds &u, int lane) {
+    constexpr int kE = UnionRows<NT>::kE;
     const int n_ent = n_tok * topk;
     const uint32_t inv = (1u << 20) / (uint32_t)topk + 1u;   // entry i belongs to token i / topk (exact for i < 2048)
     int ent[kE];
 #pragma unroll
     for (int i = 0; i < kE; ++i) {
-        const int at = lane + 64 * i;
-        int x = -1;
-        if (at < n_ent) x = rows[at];
-        ent[i] = x > b_own ? -1 : x;
+        ent[i] = lane + 64 * i < n_ent && head.ent[i] <= b_own ? head.ent[i] : -1;
     }
     auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
