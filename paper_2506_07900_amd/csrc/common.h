@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/infllmv2.h"
 
 namespace infllmv2 {
@@ -255,6 +257,166 @@ __device__ inline void pick_by_bisection(uint32_t key, uint32_t top, int n, uint
     const uint64_t eq = __ballot(key == lo);              // the keys above lo, and the first n - n_hi of those equal to it
     const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
     chosen = __ballot(key > lo || (key == lo && before < n - n_hi));
+}
+
+// The running picks of one row, merged with a chunk of kVPL * 64 blocks by one wavefront: lane l brings the keys (0 = not a candidate)
+// of blocks j0 + l + 64 s.  picks (LDS): the n_have best so far as key << 32 | block, all blocks below j0; afterwards the n_pick best in
+// ascending order of their blocks.  Ties go to the lower block.  tmp: 64 + topk_cand_cap(n_pick, kVPL + 1) words of this wavefront's own.
+template <int kVPL>
+__device__ inline void merge_picks(const uint32_t (&key)[kVPL], int j0, int n_have, int n_pick, uint64_t *picks, uint64_t *tmp, int lane) {
+    uint64_t el[kVPL + 1];
+#pragma unroll
+    for (int s = 0; s < kVPL; ++s) el[s] = (uint64_t)key[s] << 32 | (uint32_t)~(j0 + lane + 64 * s);
+    el[kVPL] = lane < n_have ? picks[lane] ^ 0xffffffffull : 0ull;
+    const uint64_t res = wave_topk<kVPL + 1>(el, n_pick, tmp, lane) ^ 0xffffffffull;
+    int rank = 0;
+    for (int e = 0; e < n_pick; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)res, e) < (uint32_t)res ? 1 : 0;
+    if (lane < n_pick) picks[rank] = res;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// How many of the other 15 lanes of a group hold an x larger than this lane's y.
+template <int kR = 15>
+__device__ inline int row_count_larger(uint32_t x, uint32_t y) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + kR, 0xf, 0xf, false);
+    int c = o > y ? 1 : 0;
+    if constexpr (kR > 1) c += row_count_larger<kR - 1>(x, y);
+    return c;
+}
+template <typename F>
+__device__ inline uint32_t row_reduce_u32(uint32_t x, F f) {
+    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));
+    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false));
+    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false));
+    return f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false));
+}
+
+// merge_picks for four rows at a time, one per 16-lane group, of up to 14 (kP = 1) or 32 (kP = 2) picks each.  R (LDS): the chunk's
+// scores of this lane's row, 16 kE of them; first, count: the chunk's candidates; live: the row exists; picks, n_have, n_pick as above.
+// tmp: 4 * 64 words.  Returns false, with nothing changed, if a row has more than 64 elements that could enter.
+// The wavefront runs alone in this (its neighbour on the SIMD multiplies), at about ten cycles an instruction, so what counts is how many there are:
+// 130 a row (kP = 1) instead of 430.  A few lanes' largest elements give a threshold that n_pick of them reach: the n_pick-th
+// of the 16 lanes' (of 512 random scores 26 reach it for 13 picks; beyond 14 it says too little), or, by bisection, about that of the
+// 64 quarter lanes'; counting over the elements that reach it gives the order.  Ranking a row's chunk 4500 -> 2000 cycles;
+// selection, top-k 16, G = 16: 5000 tokens 64 -> 55 us, 32K 613 -> 579; G = 8: 8192 118 -> 75, 32K 925 -> 590; G = 1: 16000 176 -> 109.
+constexpr int kGroupPicks = 32;
+inline int pick_form(const Dims &dm) { return dm.topk - dm.n_init - dm.n_local <= 14 ? 1 : 2; }   // kP; a row has no more picks
+template <int kE, int kP>
+__device__ inline bool merge_picks_group(const float *R, int j0, int first, int count, bool live, int n_have, int n_pick, uint64_t *picks,
+                                         uint64_t *tmp, int lane) {
+    const auto larger = [](uint32_t x, uint32_t y) { return max(x, y); };
+    const int l = lane & 15;
+    uint64_t *mine = tmp + 64 * (lane >> 4);
+    uint64_t old[kP];                                     // key << 32 | ~block: larger is better
+    uint32_t lo = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < kP; ++i) {
+        old[i] = l + 16 * i < n_have ? picks[l + 16 * i] ^ 0xffffffffull : 0ull;
+        if (l + 16 * i < n_have) lo = min(lo, (uint32_t)(old[i] >> 32));
+    }
+    lo = n_have == n_pick ? ~row_reduce_u32(~lo, larger) + 1u : 1u;          // larger than the smallest pick
+    constexpr int kSub = kP == 1 ? 1 : 4;
+    uint32_t key[kE], best[kSub];
+#pragma unroll
+    for (int i = 0; i < kSub; ++i) best[i] = 0u;
+#pragma unroll
+    for (int i = 0; i < kE / 4; ++i) {                    // (every lane holds some of a chunk that is not full)
+        const int at = 4 * (l + 16 * i);
+        const int4 x = *reinterpret_cast<const int4 *>(R + at);
+        const uint32_t from = (uint32_t)(j0 + at - first);
+        const int b[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {                     // (a block without a visible kernel, -inf, comes last)
+            const uint32_t k = from + e < (uint32_t)(live ? count : 0) ? (uint32_t)max(b[e], 1) : 0u;
+            key[4 * i + e] = k;
+            best[e % kSub] = max(best[e % kSub], k);
+        }
+    }
+    if constexpr (kP == 1) {
+        lo = max(lo, ~row_reduce_u32(row_count_larger<>(best[0], best[0]) < n_pick ? ~best[0] : 0u, larger));
+    } else {
+        const uint32_t top = row_reduce_u32(max(max(best[0], best[1]), max(best[2], best[3])), larger);
+        uint32_t hi = max(top, lo) + 1u, mid = top > lo + (3u << 23) ? top - (3u << 23) : lo;   // first an eighth of the largest
+        for (int i = 0; i < 12; ++i) {
+            uint32_t c = 0u;
+#pragma unroll
+            for (int e = 0; e < kSub; ++e) c += best[e] >= mid ? 1u : 0u;
+            const bool ok = row_reduce_u32(c, [](uint32_t x, uint32_t y) { return x + y; }) >= (uint32_t)n_pick;
+            lo = ok ? mid : lo;
+            hi = ok ? hi : mid;
+            mid = lo + ((hi - lo) >> 1);
+        }
+    }
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < kE; ++i) c += key[i] >= lo ? 1 : 0;
+    int incl = c;                                         // up to this lane of the group
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);
+    const int r0 = __builtin_amdgcn_readlane(incl, 15), r1 = __builtin_amdgcn_readlane(incl, 31);
+    const int r2 = __builtin_amdgcn_readlane(incl, 47), r3 = __builtin_amdgcn_readlane(incl, 63);
+    const int most = max(max(r0, r1), max(r2, r3)) + n_have;
+    if (most == n_have) return true;
+    if (most > 64) return false;
+    const int total = (lane < 32 ? (lane < 16 ? r0 : r1) : (lane < 48 ? r2 : r3)) + n_have;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (l + 16 * i >= total) mine[l + 16 * i] = 0ull;
+#pragma unroll
+    for (int i = 0; i < kP; ++i)
+        if (l + 16 * i < n_have) mine[l + 16 * i] = old[i];
+    int at = n_have + incl - c;
+#pragma unroll
+    for (int i = 0; i < kE; ++i)
+        if (key[i] >= lo) mine[at++] = (uint64_t)key[i] << 32 | (uint32_t)~(j0 + 4 * (l + 16 * (i / 4)) + i % 4);
+    __builtin_amdgcn_wave_barrier();                      // same wavefront: LDS keeps the order
+    uint64_t w[4];
+    int rank[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        w[i] = mine[l + 16 * i];
+        rank[i] = 0;
+    }
+    auto count_from = [&](auto parts) __attribute__((always_inline)) {
+        for (int e = 0; e < most; e += 4) {
+            const ulonglong2 x = *reinterpret_cast<const ulonglong2 *>(mine + e), y = *reinterpret_cast<const ulonglong2 *>(mine + e + 2);
+#pragma unroll
+            for (int i = 0; i < decltype(parts)::value; ++i)
+                rank[i] += ((x.x > w[i] ? 1 : 0) + (x.y > w[i] ? 1 : 0)) + ((y.x > w[i] ? 1 : 0) + (y.y > w[i] ? 1 : 0));
+        }
+    };
+    if (most <= 32) count_from(std::integral_constant<int, 2>{});
+    else count_from(std::integral_constant<int, 4>{});
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (w[i] != 0ull && rank[i] < n_pick) mine[rank[i]] = w[i];           // (no two words are equal)
+    __builtin_amdgcn_wave_barrier();
+    const int n = min(total, n_pick);
+    uint64_t p[kP];
+#pragma unroll
+    for (int i = 0; i < kP; ++i) p[i] = l + 16 * i < n ? mine[l + 16 * i] : 0ull;
+#pragma unroll
+    for (int i = 0; i < kP; ++i) {                        // ~block: larger is a lower block; the unused ones are 0
+        int place = 0;
+#pragma unroll
+        for (int j = 0; j < kP; ++j) place += row_count_larger<>((uint32_t)p[j], (uint32_t)p[i]) + ((uint32_t)p[j] > (uint32_t)p[i] ? 1 : 0);
+        if (l + 16 * i < n) picks[place] = p[i] ^ 0xffffffffull;
+    }
+    __builtin_amdgcn_wave_barrier();
+    return true;
+}
+
+// The row of selected blocks of one query, ascending, padded with -1 up to topk: the first n_init, the n_pick picks (ascending), and
+// lo_local .. the own one, n_sel in all.
+__device__ inline void write_picks_row(const uint64_t *picks, int n_pick, int n_sel, int n_init, int lo_local, int topk,
+                                       int32_t *__restrict__ o, int lane) {
+    if (lane >= topk) return;
+    int x = lane;
+    if (lane >= n_init) x = lane < n_init + n_pick ? (int)(uint32_t)picks[lane - n_init] : lo_local + (lane - n_init - n_pick);
+    o[lane] = lane < n_sel ? x : -1;
 }
 
 // The row of selected blocks of one query: lane c < n_pick brings a picked candidate block, the forced

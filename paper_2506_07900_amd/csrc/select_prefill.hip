@@ -149,29 +149,30 @@ __global__ __launch_bounds__(256) void select_lse_kernel(Dims dm, Tensor q, Tens
 // MFMA computes Z = Q . CK^T: lane = one kernel, its 4 accumulator entries are 4 consecutive
 // (token, head) rows, so the sum over a token's heads is 3 adds plus at most 2 cross-group adds.
 //
-// kFused: the block scores stay in LDS, a chunk of kPickChunk blocks per token; when a chunk is complete
-// each wavefront merges it into the running top n_pick of its tokens (wave_topk over the chunk's scores
-// plus the carried picks), and after the last chunk adds the forced blocks and writes the rows.  No
-// score matrix, no separate ranking kernel.  !kFused: the scores R[token, j] go to memory (only the
+// kRank > 0 (the ranking's form, pick_form): the block scores stay in LDS, a chunk of kPickChunk blocks per token; when a chunk is complete
+// each wavefront merges it into the running top n_pick of its tokens (merge_picks_group, four at a
+// time), and after the last chunk adds the forced blocks and writes the rows.  No
+// score matrix, no separate ranking kernel.  kRank = 0: the scores R[token, j] go to memory (only the
 // query-block-shared comparison variant, which averages them over 64 tokens first, needs that).
 constexpr int kPickVpl = 4, kPickChunk = 64 * kPickVpl;           // blocks per chunk of the in-kernel top-k
 template <int G> struct ScoreLds {                                 // dynamic LDS of the fused variant
     int carry_pitch, topk_words;
     __host__ __device__ explicit ScoreLds(int topk)
-        : carry_pitch((topk + 1) & ~1), topk_words(64 + topk_cand_cap(topk, kPickVpl + 1)) {}
+        : carry_pitch((topk + 1) & ~1), topk_words(max(4 * 64, 64 + topk_cand_cap(topk, kPickVpl + 1))) {}
     __host__ __device__ size_t bytes() const {
         return (size_t)SelCfg<G>::kTokPerWg * kPickChunk * sizeof(float) +
                ((size_t)SelCfg<G>::kTokPerWg * carry_pitch + 4 * (size_t)topk_words) * sizeof(uint64_t);
     }
 };
 
-template <int G, bool kFused>
-__global__ __launch_bounds__(256) void select_score_kernel(Dims dm, Tensor q, Tensor ck,
+template <int G, int kRank>
+__global__ __launch_bounds__(256, 2) void select_score_kernel(Dims dm, Tensor q, Tensor ck,
                                                             const int32_t *__restrict__ seqlens,
                                                             const float *__restrict__ lse2,
                                                             float *__restrict__ R, int32_t nb_cap,
                                                             int32_t n_tiles, int32_t *__restrict__ block_idx) {
     using C = SelCfg<G>;
+    constexpr bool kFused = kRank > 0;
     constexpr int TL = (G >= 4) ? 1 : 4 / G;     // tokens held by one lane of a row tile
     constexpr int RL = (G >= 4) ? 4 : G;         // rows of one token held by one lane
     __shared__ __align__(16) __bf16 cks[kChunk * kCkPitch];
@@ -218,20 +219,28 @@ __global__ __launch_bounds__(256) void select_score_kernel(Dims dm, Tensor q, Te
     const int jc_max = lo_local - 1;                                          // candidates: n_init..jc_max
     const int n_pick = max(0, n_sel - (n_init + (b_own - lo_local + 1)));
     uint64_t *tk_lds = carry + C::kTokPerWg * lay.carry_pitch + wave * lay.topk_words;
-    if (kFused)
-        for (int i = tid; i < C::kTokPerWg * lay.carry_pitch; i += 256) carry[i] = 0ull;
     // merges the chunk of blocks j0 .. j0 + kPickChunk - 1 into the running picks of this wavefront's tokens
     auto merge_chunk = [&](int j0) {
-        for (int u = 0; u < C::kTokPerWave; ++u) {
+        const int n_have = min(max(j0 - n_init, 0), n_pick);
+        int done = 0;                                    // tokens
+        if (n_pick > 0 && n_pick <= kGroupPicks)
+            for (; done < C::kTokPerWave; done += 4) {
+                const int tloc = wave * C::kTokPerWave + done + g;
+                if (!merge_picks_group<4 * kPickVpl, kFused ? kRank : 1>(Rl + tloc * kPickChunk, j0, n_init, jc_max + 1 - n_init, t0 + tloc < L,
+                                                                         n_have, n_pick, carry + tloc * lay.carry_pitch, tk_lds, lane))
+                    break;
+            }
+        for (int u = done; u < C::kTokPerWave; ++u) {
             const int tloc = wave * C::kTokPerWave + u;
             if (t0 + tloc >= L || n_pick <= 0) break;
-            uint64_t el[kPickVpl + 1];
+            uint32_t key[kPickVpl];
 #pragma unroll
-            for (int s2 = 0; s2 < kPickVpl; ++s2)
-                el[s2] = pick_element(Rl[tloc * kPickChunk + lane + 64 * s2], j0 + lane + 64 * s2, n_init, jc_max);
-            el[kPickVpl] = lane < n_pick ? carry[tloc * lay.carry_pitch + lane] : 0ull;
-            const uint64_t res = wave_topk<kPickVpl + 1>(el, n_pick, tk_lds, lane);
-            if (lane < n_pick) carry[tloc * lay.carry_pitch + lane] = res;
+            for (int s2 = 0; s2 < kPickVpl; ++s2) {
+                const int j = j0 + lane + 64 * s2;       // (a block without a visible kernel, -inf, comes last)
+                const uint32_t k = (uint32_t)max(__float_as_int(Rl[tloc * kPickChunk + lane + 64 * s2]), 1);
+                key[s2] = j >= n_init && j <= jc_max ? k : 0u;
+            }
+            merge_picks<kPickVpl>(key, j0, n_have, n_pick, carry + tloc * lay.carry_pitch, tk_lds, lane);
         }
     };
 
@@ -316,8 +325,7 @@ __global__ __launch_bounds__(256) void select_score_kernel(Dims dm, Tensor q, Te
         for (int u = 0; u < C::kTokPerWave; ++u) {
             const int tloc = wave * C::kTokPerWave + u;
             if (t0 + tloc >= L) break;
-            const int picked = lane < n_pick ? (int)~(uint32_t)carry[tloc * lay.carry_pitch + lane] : 0;
-            write_block_row(picked, n_pick, n_sel, n_init, lo_local, dm.topk,
+            write_picks_row(carry + tloc * lay.carry_pitch, n_pick, n_sel, n_init, lo_local, dm.topk,
                             block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0 + tloc) * dm.topk, lane);
         }
     }
@@ -518,18 +526,17 @@ static int launch_select_prefill_g(const Dims &dm, Tensor q, Tensor ck, const in
     timing_end(stream);
     timing_begin("select_score_kernel", stream);
     if (dm.shared_q || scores_out) {
-        hipLaunchKernelGGL((select_score_kernel<G, false>), dim3((uint32_t)n_wg), dim3(256), 0, stream, dm, q, ck,
+        hipLaunchKernelGGL((select_score_kernel<G, 0>), dim3((uint32_t)n_wg), dim3(256), 0, stream, dm, q, ck,
                            seqlens, lse2, R, nb_cap, n_tiles, block_idx);
         timing_end(stream);
         if (scores_out) return (int)hipGetLastError();    // the caller wanted the scores, not the block sets
         return launch_select_pick(dm, seqlens, R, nb_cap, block_idx, stream);
     }
     const size_t lds = ScoreLds<G>(dm.topk).bytes();     // beside 26 to 34 KiB of static LDS
-    const hipError_t e = hipFuncSetAttribute((const void *)select_score_kernel<G, true>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const auto fn = pick_form(dm) == 1 ? select_score_kernel<G, 1> : select_score_kernel<G, 2>;
+    const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
-    hipLaunchKernelGGL((select_score_kernel<G, true>), dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ck,
-                       seqlens, lse2, R, nb_cap, n_tiles, block_idx);
+    hipLaunchKernelGGL(fn, dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ck, seqlens, lse2, R, nb_cap, n_tiles, block_idx);
     timing_end(stream);
     return (int)hipGetLastError();
 }

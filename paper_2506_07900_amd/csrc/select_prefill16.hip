@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void select_lse16_kernel(Dims dm, Tensor q,
 // Lane = kernel n of the tile, accumulator entries = heads 4g..4g+3 of the token.  The block scores
 // never leave the compute unit: the wavefront keeps the scores of its 8 tokens for a chunk of 64*VPL
 // key-value blocks in LDS, and at the end of a chunk merges them into each token's running top
-// n_pick (wave_topk over the chunk's scores plus the carried picks), so the selection costs no score
+// n_pick (merge_picks_group, four tokens at a time; kRank: its kP), so the selection costs no score
 // matrix and no second kernel.  After the last chunk the forced blocks are added and the row written.
 // VPL = 0: the scores R[token, j] of the candidate blocks go to memory instead (-inf when no visible
 // kernel intersects the block); only the query-block-shared comparison variant, which averages them
@@ -277,14 +277,14 @@ struct Score16Lds {                                      // layout of one wavefr
     int chunk_blocks, carry_words, topk_words;
     __host__ __device__ Score16Lds(int vpl, int topk)
         : chunk_blocks(64 * vpl), carry_words(kMT * ((topk + 1) & ~1)),
-          topk_words(64 + topk_cand_cap(topk, vpl + 1)) {}
+          topk_words(max(4 * 64, 64 + topk_cand_cap(topk, vpl + 1))) {}
     __host__ __device__ size_t bytes() const {
         return (size_t)kMT * chunk_blocks * sizeof(float) + (size_t)(carry_words + topk_words) * sizeof(uint64_t) +
                kMT * 16 * sizeof(float);
     }
 };
 
-template <int VPL>
+template <int VPL, int kRank>
 __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor q, const uint4 *__restrict__ ckp,
                                                               int32_t nt_cap, const int32_t *__restrict__ seqlens,
                                                               const float *__restrict__ lse2,
@@ -323,8 +323,6 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
     if (!kFused && nt_all <= 0) return;                                       // no candidates
 
     if (nt_all > 0) {
-        bf16x8 qf[kMT][4];
-        load_q16(qf, q, b, h, t0, L, n, g);
         float *nls = reinterpret_cast<float *>(tk_lds + lay.topk_words);    // [kMT][16]: -lse of head, token
         for (int i = lane; i < kMT * 16; i += 64)
             nls[i] = (t0 + (i >> 4) < L) ? -lse2[((int64_t)b * dm.max_seqlen + t0 + (i >> 4)) * dm.Hq + h * 16 + (i & 15)] : 0.f;
@@ -343,9 +341,6 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
             wr[i] = ((n & 3) == 0) && tok < L;
             nvis_tok[i] = n_visible16(tok) - n;
         }
-        if (kFused)
-            for (int i = lane; i < lay.carry_words; i += 64) carry[i] = 0ull;
-
         // epilogue of tile t for half i: 2^(z*c - lse), sum over the 16 heads, mean, floor, causal mask,
         // 5-wide / stride-4 max over kernels -> lanes n = 0,4,8,12 hold blocks 4t + n/4
         auto finish = [&](const f32x4 (&z)[kHalf], int i, int t) {
@@ -387,6 +382,10 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
         // the tiles [ta, te) through the software pipeline
         auto run_tiles = [&](int ta, int te) {
             f32x4 zA[kHalf], zB[kHalf];
+            bf16x8 qf[kMT][4];                               // (loaded again for every chunk: the ranking in between needs the registers)
+            int ln = lane;
+            asm volatile("" : "+v"(ln));                     // (its addresses are not formed ahead of the chunks either)
+            load_q16(qf, q, b, h, t0, L, ln & 15, ln >> 4);
             // two fragment buffers that swap roles each tile (loop unrolled by two: no register copies)
             Frag4 f0 = load_ck_tile(ckp_head, ta, lane);
             Frag4 f1 = f0;
@@ -416,15 +415,27 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
             if (kFused) {                                                     // merge the chunk into the running picks
                 __builtin_amdgcn_wave_barrier();
                 const int j0 = 4 * ta;
-                for (int u = 0; u < kMT && t0 + u < L; ++u) {
-                    constexpr int NE = kFused ? VPL + 1 : 1;
-                    uint64_t el[NE];
+                const int n_have = min(max(j0 - n_init, 0), n_pick);
+                constexpr int NE = kFused ? VPL : 1;
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                int done = 0;                                                 // tokens
+                if (n_pick <= kGroupPicks)
+                    for (; done < kMT; done += 4) {
+                        const int u = done + (ln >> 4);
+                        if (!merge_picks_group<4 * NE, kRank>(Rl + u * kChunkBlocks, j0, n_init, jc_max + 1 - n_init, t0 + u < L, n_have, n_pick,
+                                                              carry + u * carry_pitch, tk_lds, ln))
+                            break;
+                    }
+                for (int u = done; u < kMT && t0 + u < L; ++u) {
+                    uint32_t key[NE];
 #pragma unroll
-                    for (int s2 = 0; s2 < NE - 1; ++s2)
-                        el[s2] = pick_element(Rl[u * kChunkBlocks + lane + 64 * s2], j0 + lane + 64 * s2, n_init, jc_max);
-                    el[NE - 1] = lane < n_pick ? carry[u * carry_pitch + lane] : 0ull;
-                    const uint64_t res = wave_topk<NE>(el, n_pick, tk_lds, lane);
-                    if (lane < n_pick) carry[u * carry_pitch + lane] = res;
+                    for (int s2 = 0; s2 < NE; ++s2) {
+                        const int j = j0 + lane + 64 * s2;                    // (a block without a visible kernel, -inf, comes last)
+                        const uint32_t k = (uint32_t)max(__float_as_int(Rl[u * kChunkBlocks + lane + 64 * s2]), 1);
+                        key[s2] = j >= n_init && j <= jc_max ? k : 0u;
+                    }
+                    merge_picks<NE>(key, j0, n_have, n_pick, carry + u * carry_pitch, tk_lds, lane);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
@@ -432,9 +443,7 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
     }
     if (kFused) {
         for (int u = 0; u < kMT && t0 + u < L; ++u) {
-            const int picked = (nt_all > 0 && lane < n_pick) ? (int)~(uint32_t)carry[u * carry_pitch + lane] : 0;
-            write_block_row(picked, n_pick > 0 ? n_pick : 0, n_sel, n_init, lo_local, dm.topk,
-                            block_idx + (row0 + u) * dm.topk, lane);
+            write_picks_row(carry + u * carry_pitch, nt_all > 0 ? n_pick : 0, n_sel, n_init, lo_local, dm.topk, block_idx + (row0 + u) * dm.topk, lane);
         }
     }
 }
@@ -504,28 +513,22 @@ int launch_select_prefill16(const Dims &dm, Tensor q, Tensor ck, const int32_t *
         timing_end(stream);
         timing_begin("select_score16_kernel", stream);
         if (dm.shared_q || scores_out) {
-            hipLaunchKernelGGL(select_score16_kernel<0>, dim3((uint32_t)n_wg), dim3(256),
+            hipLaunchKernelGGL((select_score16_kernel<0, 1>), dim3((uint32_t)n_wg), dim3(256),
                                4 * Score16Lds(0, dm.topk).bytes(), stream, dm, q, ckp, nt_cap, seqlens, lse2, R, nb_cap,
                                n_tiles, block_idx);
         } else {
             const int vpl = score16_vpl(dm);
             const size_t lds = 4 * Score16Lds(vpl, dm.topk).bytes();
-            const void *fn = vpl == 8 ? (const void *)select_score16_kernel<8>
-                             : vpl == 4 ? (const void *)select_score16_kernel<4>
-                                        : (const void *)select_score16_kernel<2>;
+            const bool few = pick_form(dm) == 1;
+            const auto fn = vpl == 8   ? (few ? select_score16_kernel<8, 1> : select_score16_kernel<8, 2>)
+                            : vpl == 4 ? (few ? select_score16_kernel<4, 1> : select_score16_kernel<4, 2>)
+                                       : (few ? select_score16_kernel<2, 1> : select_score16_kernel<2, 2>);
             if (lds > 64 * 1024) {
-                const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                 if (e != hipSuccess) return (int)e;
             }
-            if (vpl == 8)
-                hipLaunchKernelGGL(select_score16_kernel<8>, dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ckp,
-                                   nt_cap, seqlens, lse2, R, nb_cap, n_tiles, block_idx);
-            else if (vpl == 4)
-                hipLaunchKernelGGL(select_score16_kernel<4>, dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ckp,
-                                   nt_cap, seqlens, lse2, R, nb_cap, n_tiles, block_idx);
-            else
-                hipLaunchKernelGGL(select_score16_kernel<2>, dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ckp,
-                                   nt_cap, seqlens, lse2, R, nb_cap, n_tiles, block_idx);
+            hipLaunchKernelGGL(fn, dim3((uint32_t)n_wg), dim3(256), lds, stream, dm, q, ckp, nt_cap, seqlens, lse2, R, nb_cap, n_tiles,
+                               block_idx);
         }
         timing_end(stream);
     }

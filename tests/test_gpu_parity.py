@@ -242,6 +242,36 @@ def test_block_scores_rank_as_the_selection_does(seqlens, Hq, Hkv, topk, forced)
         assert bool((best == idx[b, :, :l]).all()), (b, int((best != idx[b, :, :l]).any(-1).sum()))
 
 
+# The ranking of the two-pass selection, row by row of sixteen lanes and chunk by chunk, where its threshold and its limits lie: 1, 13 | 14,
+# 15 .. 32 | 33 picks beside the forced blocks; scores that rise along the row (every chunk replaces all picks), that are high in
+# one lane's blocks only (more could enter than are kept) and that tie.
+@pytest.mark.parametrize("T,Hq,Hkv,topk", [
+    (4500, 16, 1, 4), (4500, 16, 1, 17), (4500, 8, 1, 18), (4500, 4, 1, 35), (4500, 1, 1, 36), (4500, 2, 1, 16),
+    (18000, 4, 1, 16), (18000, 8, 1, 35), (36000, 16, 1, 16), (36000, 16, 1, 35), (70000, 16, 1, 17)])
+@pytest.mark.parametrize("shape", ["rising", "lane", "ties"])
+def test_block_scores_rank_as_the_selection_does_at_its_limits(T, Hq, Hkv, topk, shape):
+    print("case ranking", T, Hq, Hkv, topk, shape, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    gen = torch.Generator(device="cuda").manual_seed(topk)
+    n_c = binding.num_kernels(T, prm)
+    u = torch.randn((128,), device="cuda", generator=gen)
+    block = torch.arange(n_c, device="cuda") // 4
+    a = {"rising": torch.arange(n_c, device="cuda") / n_c,
+         "lane": torch.rand((n_c,), device="cuda", generator=gen) * 0.3 + ((block // 4) % 16 == 3),
+         "ties": torch.randint(0, 3, (n_c,), device="cuda", generator=gen) * 0.25}[shape]
+    ck = (a[:, None] * u[None])[None, None].bfloat16().contiguous()
+    q = (0.1 * u + 0.01 * torch.randn((1, T, Hq, 128), device="cuda", generator=gen)).bfloat16()
+    sl = dev_i32([T])
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, ck, sl, T)[0, 0]
+    R = binding.block_scores(prm, q, ck, sl, T)[0, 0]
+    for t in [x for x in range(0, T, 1531)] + [63, 64, 1023, T // 2, T - 65, T - 1]:
+        own = t // 64
+        r = R[t, 1:max(1, own - 1)].double()                                # the candidates
+        order = torch.argsort(r, descending=True, stable=True)[:max(0, topk - 3)] + 1       # (ties: the lower block)
+        want = sorted(set([0] + order.tolist() + [x for x in (own - 1, own) if x >= 0]))
+        assert idx[t].tolist() == want + [-1] * (topk - len(want)), t
+
+
 @pytest.mark.parametrize("forced", [(0, 0), (0, 1), (3, 0), (2, 4)])
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([1100, 333, 70], 32, 2, 8), ([700, 65], 4, 1, 6)])
 def test_select_blocks_prefill_other_forced_counts(seqlens, Hq, Hkv, topk, forced):
