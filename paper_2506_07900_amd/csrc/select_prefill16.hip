@@ -19,7 +19,8 @@
 // the matrix work holds at 2.1 - 2.2 GHz.  So what a tile costs is its vector instructions: scalar tile
 // bounds (wave index made uniform), pooling on bit patterns (move + maximum in one DPP instruction), sums that begin with
 // their first term and one overflow test per half took pass 1 / pass 2 from 270 / 372 to 267 / 361 us at 32K tokens and
-// from 3.73 / 4.84 to 3.62 / 4.64 ms at 128K.  A third fragment buffer (prefetch two tiles ahead) changes nothing: 3.62 / 4.69.
+// from 3.73 / 4.84 to 3.62 / 4.64 ms at 128K; no visibility test on the tiles that every token sees, the sum ranked in place of the mean and
+// moves merged into their maxima (106 -> 100 instructions per half) the whole selection from 584 to 578 us and from 7.87 to 7.73 ms.  A third fragment buffer (prefetch two tiles ahead) changes nothing: 3.62 / 4.69.
 #include "common.h"
 
 namespace infllmv2 {
@@ -343,7 +344,9 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
         }
         // epilogue of tile t for half i: 2^(z*c - lse), sum over the 16 heads, mean, floor, causal mask,
         // 5-wide / stride-4 max over kernels -> lanes n = 0,4,8,12 hold blocks 4t + n/4
-        auto finish = [&](const f32x4 (&z)[kHalf], int i, int t) {
+        // (kMasked: some kernel of the tile is not visible to some token)
+        auto finish = [&](auto masked, const f32x4 (&z)[kHalf], int i, int t) __attribute__((always_inline)) {
+            constexpr bool kMasked = decltype(masked)::value;
             float e[kHalf];
 #pragma unroll
             for (int u = 0; u < kHalf; ++u) {
@@ -361,12 +364,14 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
             const float s23 = __uint_as_float(p23[0]) + __uint_as_float(p23[1]);
             const v2u pq = __builtin_amdgcn_permlane32_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
             float v = __uint_as_float(pq[0]) + __uint_as_float(pq[1]);
-            v = fminf(fmaxf(v * (1.f / 16.f), kScoreFloor), kScoreCeil);
-            // The pooling compares bit patterns: positive floats order like integers, and -inf lies below them.  With the
-            // smallest integer outside the row, a move and its maximum are one instruction.
-            const int vi = 16 * t < nvis_tok[i] ? __float_as_int(v) : kNegInf;        // (kernel 16t + n not visible to this token)
-            const int a = max(vi, dpp_i32<kRowShl1>(INT32_MIN, vi));
-            const int bq = max(a, dpp_i32<kRowShl2>(INT32_MIN, a));
+            // (ranked, the sum serves as well as the mean; NaN goes to the floor)
+            if constexpr (kFused) v = __builtin_amdgcn_fmed3f(v, 16.f * kScoreFloor, 16.f * kScoreCeil);
+            else v = fminf(fmaxf(v * (1.f / 16.f), kScoreFloor), kScoreCeil);
+            // The pooling compares bit patterns: positive floats order like integers, and -inf lies below them.  What comes from
+            // outside the row (0) reaches lanes 14 and 15 only, which write nothing: a move and its maximum are one instruction.
+            const int vi = !kMasked || 16 * t < nvis_tok[i] ? __float_as_int(v) : kNegInf;    // (kernel 16t + n not visible to this token)
+            const int a = max(vi, __builtin_amdgcn_update_dpp(0, vi, kRowShl1, 0xf, 0xf, true));
+            const int bq = max(a, __builtin_amdgcn_update_dpp(0, a, kRowShl2, 0xf, 0xf, true));
             const int halo0 = dpp_i32<kRowRor1>(prev_v[i], prev_v[i]);        // lane 0 <- previous tile's lane 15
             const int halo = dpp_i32<kRowShr1>(halo0, vi);                    // lane n <- v[n-1]
             const float w = __int_as_float(max(bq, halo));
@@ -380,24 +385,21 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
         };
 
         // the tiles [ta, te) through the software pipeline
-        auto run_tiles = [&](int ta, int te) {
+        auto run_tiles = [&](auto masked, const bf16x8 (&qf)[kMT][4], int ta, int te) __attribute__((always_inline)) {
+            if (ta >= te) return;
             f32x4 zA[kHalf], zB[kHalf];
-            bf16x8 qf[kMT][4];                               // (loaded again for every chunk: the ranking in between needs the registers)
-            int ln = lane;
-            asm volatile("" : "+v"(ln));                     // (its addresses are not formed ahead of the chunks either)
-            load_q16(qf, q, b, h, t0, L, ln & 15, ln >> 4);
             // two fragment buffers that swap roles each tile (loop unrolled by two: no register copies)
             Frag4 f0 = load_ck_tile(ckp_head, ta, lane);
             Frag4 f1 = f0;
             if (ta + 1 < te) f1 = load_ck_tile(ckp_head, ta + 1, lane);
             mfma_half<false>(f0, qf, 0, zA);
             mfma_half<false>(f0, qf, kHalf, zB);
-            finish(zA, 0, ta);
+            finish(masked, zA, 0, ta);
             auto tile_step = [&](const Frag4 &f, int t) {
                 mfma_half<false>(f, qf, 0, zA);              // matrix work on half A of tile t ...
-                finish(zB, 1, t - 1);                        // ... alternates with the epilogue of half B, tile t-1
+                finish(masked, zB, 1, t - 1);                // ... alternates with the epilogue of half B, tile t-1
                 mfma_half<false>(f, qf, kHalf, zB);
-                finish(zA, 0, t);
+                finish(masked, zA, 0, t);
             };
             int t = ta + 1;
             for (; t + 1 < te; t += 2) {
@@ -407,11 +409,20 @@ __global__ __launch_bounds__(256, 2) void select_score16_kernel(Dims dm, Tensor 
                 tile_step(f0, t + 1);
             }
             if (t < te) tile_step(f1, t);
-            finish(zB, 1, te - 1);
+            finish(masked, zB, 1, te - 1);
         };
 
+        const int nt_full = n_visible16(t0) >> 4;                             // tiles wholly visible to every token here
         for (int ta = 0; ta < nt_all; ta += kChunkTiles) {
-            run_tiles(ta, min(ta + kChunkTiles, nt_all));
+            {
+                bf16x8 qf[kMT][4];                           // (loaded again for every chunk: the ranking in between needs the registers)
+                int ln = lane;
+                asm volatile("" : "+v"(ln));                 // (its addresses are not formed ahead of the chunks either)
+                load_q16(qf, q, b, h, t0, L, ln & 15, ln >> 4);
+                const int te = min(ta + kChunkTiles, nt_all), tm = min(max(nt_full, ta), te);
+                run_tiles(std::false_type{}, qf, ta, tm);
+                run_tiles(std::true_type{}, qf, tm, te);
+            }
             if (kFused) {                                                     // merge the chunk into the running picks
                 __builtin_amdgcn_wave_barrier();
                 const int j0 = 4 * ta;
