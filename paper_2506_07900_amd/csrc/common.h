@@ -238,25 +238,21 @@ __device__ inline uint32_t wave_max_u32(uint32_t x) {
 // counting, and it ends early once a threshold splits off exactly n keys.  The first threshold lies a factor of 8 below the
 // largest key, which in practice leaves 2^25 patterns instead of 2^30: about ten steps on scores that differ in the second
 // digit, 32 at most.
-// (The mask is written inside the loop, not returned: the loop grows by a branch and six scalar instructions otherwise.
-// With those and a select in place of the caller's integer maximum a 777-token prompt took 35.9 us instead of 35.1.)
+// Bound by the chain of a step, eleven instructions with one branch; a threshold that splits off exactly n closes the interval instead
+// of leaving the loop, which took a second branch and six scalar instructions.  Selection: 777 tokens (top-k 8, G = 16)
+// 7.3 -> 6.8 us, 2048 (G = 4) 8.2 -> 7.5, 2 x 4096 (G = 8) 23.0 -> 20.6; two or four steps per branch: the same.
 __device__ inline void pick_by_bisection(uint32_t key, uint32_t top, int n, uint64_t &chosen) {
-    uint32_t lo = 1u, hi = top + 1u;                      // count(key >= lo) >= n > count(key >= hi)
-    int n_hi = 0;
+    uint32_t lo = 1u, hi = top + 1u;                      // count(key >= lo) >= n >= count(key >= hi)
     uint32_t mid = top > (3u << 23) + 1u ? top - (3u << 23) : lo + ((hi - lo) >> 1);
-    for (; hi - lo > 1u; mid = lo + ((hi - lo) >> 1)) {
-        chosen = __ballot(key >= mid);
-        const int cnt = __popcll(chosen);
-        if (cnt == n) return;
-        if (cnt > n) lo = mid;
-        else {
-            hi = mid;
-            n_hi = cnt;
-        }
+    while (hi - lo > 1u) {                                // (as uint32: 0 once lo = hi)
+        const int cnt = __popcll(__ballot(key >= mid));
+        lo = cnt >= n ? mid : lo;
+        hi = cnt > n ? hi : mid;
+        mid = lo + ((hi - lo) >> 1);
     }
-    const uint64_t eq = __ballot(key == lo);              // the keys above lo, and the first n - n_hi of those equal to it
+    const uint64_t above = __ballot(key > lo), eq = __ballot(key == lo);      // the keys above lo, and the first of those equal to it
     const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
-    chosen = __ballot(key > lo || (key == lo && before < n - n_hi));
+    chosen = above | __ballot(key == lo && before < n - __popcll(above));
 }
 
 // The running picks of one row, merged with a chunk of kVPL * 64 blocks by one wavefront: lane l brings the keys (0 = not a candidate)

@@ -13,8 +13,8 @@
 // workgroup, in MFMA operand order; its eight wavefronts then take tile after tile of tokens, each on its own.
 // Reading the keys from L2 for every tile instead was bound by the half-line reads of the row-major keys
 // (16 rows x 64 bytes per load): 8 tiles of 16 kernels took 10 us with every wavefront at it.
-// Selection alone, us, two passes -> this: 777 tokens (top-k 8) 33 -> 7, 2048 42 -> 11, 4096 53 -> 21 (G = 16, 2 heads);
-// 2048 G = 4 27 -> 9.
+// Selection alone, us, two passes -> this: 777 tokens (top-k 8) 33 -> 6.8, 2048 42 -> 11, 4096 53 -> 21 (G = 16, 2 heads);
+// 2048 G = 4 27 -> 7.5.
 // Its scores are nearer to 64-bit ones than the two passes' (largest relative error over 300 to 4096 tokens and every G 2.5e-7
 // against 8.4e-7; no rounded log-sum-exp in between), but not theirs: blocks whose scores tie to fp32 rounding change places, in
 // 4 of 983040 rows of 8192 tokens against 1 of 921600 of 1500 to 4096.  Up to 8192 tokens it would still be faster (113 -> 51,
@@ -114,7 +114,8 @@ __global__ __launch_bounds__(64 * kShortWaves, 4) void select_short_kernel(
         }
 
         // Straight-line code for kNT kernel tiles (those past the end are masked), so that the products of one tile run
-        // under the LDS reads of the next.  Z = Q . CK^T: lane = kernel, accumulator entries = rows 4g .. 4g+3.
+        // under the LDS reads of the next.  (All products first and the masks after them: 20.6 -> 19.4 us for 2 x 4096 tokens, G = 8, but
+        // the kernels that follow it then run at a lower clock: a training step on them 480 -> 496 us back to back.)  Z = Q . CK^T: lane = kernel, accumulator entries = rows 4g .. 4g+3.
         auto run = [&](auto nt) __attribute__((always_inline)) {
             constexpr int kNT = decltype(nt)::value;
             f32x4 z[kNT];
