@@ -1312,7 +1312,9 @@ static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     l.list_blocks = dm.n_q == 1 ? kListBlocks : 16 * verify_tiles2(dm);
     l.n_lists = max(1, (dm.max_seqlen + kBlock * l.list_blocks - 1) / (kBlock * l.list_blocks));
     l.list_len = min(l.list_blocks, max(1, dm.topk - dm.n_init - dm.n_local));
-    l.r_bytes = align256(rows * dm.Hkv * l.n_lists * l.list_len * sizeof(uint64_t));
+    // (verification: no less than a row of scores, which short lists would fit twice)
+    const size_t row = (size_t)l.n_lists * l.list_len * sizeof(uint64_t), scores = dm.n_q == 1 ? 0 : l.nb_cap * sizeof(float);
+    l.r_bytes = align256(rows * dm.Hkv * (row > scores ? row : scores));
     return l;
 }
 
