@@ -1010,7 +1010,8 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
 // list is the only thing the attention waits for.  Every one of the k workgroups of a (query row,
 // key-value head) repeats the top-k on the same input (same result; workgroup 0 writes it out) and goes on with one
 // entry of the result as it stands, best first; the list's ascending order, which decides where the partial result goes,
-// is worked out while the block's rows are on their way.
+// is worked out while the block's rows are on their way.  Those whose entry is a forced block rank nothing: their rows are on
+// their way while the others rank (32 sequences of 128K: this kernel 12.1 -> 11.7 us, the step 63.6 -> 62.9).
 template <int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                                             const int32_t *__restrict__ seqlens,
@@ -1029,19 +1030,27 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     int32_t *orow = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
     __shared__ __align__(16) int mine[kPickWaves][64];
     const int wave = threadIdx.x >> 6;
-    int blk = -1, n_sel = 0;
+    int blk = -1, n_sel = 0, at = cidx;
     if (L < 1) {                                          // uniform over the workgroup
         if (cidx == 0 && (int)threadIdx.x < dm.topk) orow[threadIdx.x] = -1;
     } else {
         const RowRange rr(dm, L);
-        uint64_t el[kVPT];
-        load.elements(in, L, el);
-        pick_row<kVPT>(rr, el, sh, mine[wave]);
-        n_sel = rr.n_sel;
-        if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
+        const int f = cidx - rr.n_pick;
+        if (rr.n_pick > 0 && f >= 0) {                    // a forced block, or no block: nothing to rank
+            if (cidx < rr.n_sel) {
+                blk = f < rr.n_init ? f : rr.lo_local + (f - rr.n_init);
+                at = f < rr.n_init ? f : cidx;
+            }
+        } else {
+            uint64_t el[kVPT];
+            load.elements(in, L, el);
+            pick_row<kVPT>(rr, el, sh, mine[wave]);
+            n_sel = rr.n_sel;
+            if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
+        }
     }
     attend_block<false>(dm, q, k, v, rows, bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
-        if (n_sel == 0) return cidx;
+        if (n_sel == 0) return at;
         const int rank = order_row(mine[wave], n_sel, dm.topk, cidx == 0 && wave == 0 ? orow : nullptr);
         return cidx < n_sel ? __builtin_amdgcn_readlane(rank, cidx) : cidx;
     });
