@@ -30,12 +30,13 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBwdBlockU4 = 2 * 16 * 64;              // uint4 per packed block: K rows, V rows (32 KiB)
 // The scatter's work items (see bwd_items_kernel): a block with some of the tokens of a segment of kSegWords words of 32 tokens.  A
-// segment has a window per XCD, the XCD's queue a bin per segment (or run of segments).
+// segment has a window per XCD, a window kSlices slices, the XCD's queue a bin per slice (or run of slices).
 constexpr int kSegWords = 256;
 constexpr int kQueues = 8;                            // one per XCD
 constexpr int kWindowWords = kSegWords / kQueues;
-constexpr int kBins = 64;                             // at most, of a queue
-constexpr int kQueueStride = 128;                     // counters of a queue: kBins lengths, then, on a line of its own, the place drawn last
+constexpr int kSlices = 8;
+constexpr int kBins = 256;                            // at most, of a queue
+constexpr int kQueueStride = kBins + 64;                     // counters of a queue: kBins lengths, then, on a line of its own, the place drawn last
 
 // Members of an item, in steps of 32 (token, head) rows: an equal share for each of the chip's kDkdvGroups workgroups, within
 // 12 .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us
@@ -52,7 +53,7 @@ static inline int32_t bwd_item_members(const Dims &dm) {
 
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
-    int32_t members, seg_shift, n_bins, bin_cap;      // an item's members; segments of a bin (log2), bins of a queue, items of a bin
+    int32_t members, bin_shift, n_bins, bin_cap;      // an item's members; slices of a bin (log2), bins of a queue, items of a bin
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
 static inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
@@ -63,14 +64,16 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
     l.members = bwd_item_members(dm);
-    l.seg_shift = 0;
-    while ((BH * l.n_seg + ((size_t)1 << l.seg_shift) - 1) >> l.seg_shift > (size_t)kBins) ++l.seg_shift;
-    l.n_bins = (int32_t)((BH * l.n_seg + ((size_t)1 << l.seg_shift) - 1) >> l.seg_shift);
-    // items that end in a window: one per `members` list entries, one more per block with an entry (begun before the window), the
-    // own tokens' of its blocks; and every eighth block's last of the segment
-    const size_t ent = (size_t)kWindowWords * 32 * dm.topk, nb = (size_t)l.nb_cap;
-    const size_t per_window = (ent < nb ? ent : nb) + ent / l.members + kWindowWords / 2 + (nb + kQueues - 1) / kQueues;
-    l.bin_cap = (int32_t)(per_window << l.seg_shift);
+    const size_t slices = BH * l.n_seg * kSlices, nb = (size_t)l.nb_cap;
+    l.bin_shift = 0;
+    while ((slices + ((size_t)1 << l.bin_shift) - 1) >> l.bin_shift > (size_t)kBins) ++l.bin_shift;
+    l.n_bins = (int32_t)((slices + ((size_t)1 << l.bin_shift) - 1) >> l.bin_shift);
+    // items that end in a run of slices: one per `members` list entries, one more per block with an entry (begun before), the own
+    // tokens' of its blocks; and every eighth block's last of the segment.  A bin is such a run, or several windows.
+    const int run = l.bin_shift < 3 ? l.bin_shift : 3;
+    const size_t words = (size_t)(kWindowWords / kSlices) << run, ent = words * 32 * dm.topk;
+    const size_t per_run = (ent < nb ? ent : nb) + ent / l.members + words / 2 + (nb + kQueues - 1) / kQueues;
+    l.bin_cap = (int32_t)(per_run << (l.bin_shift - run));
     size_t o = 0;
     l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
     l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
@@ -167,17 +170,22 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
 // ---- the scatter's work items --------------------------------------------------------------------------------------
 // A wavefront per (segment, kItemBlocks blocks), a lane per four words: the block's members in the segment, cut behind the word that holds
 // every `members`-th of them (and behind those inside the block itself, which alone meet the causal edge); item = {sequence and head,
-// block, first word, words}.  An item goes to the queue of the window that it ends in, what is left at the segment's end to one by
-// the block's number.  So workgroups that run together on an XCD read the same tokens' q and dout rows, and a block that few tokens
+// block, first word, words}.  An item goes to the slice of 128 tokens that it ends in, in the queue of that slice's window, what is
+// left at the segment's end to the last slice of one by the block's number.  So workgroups that run together on an XCD read the same
+// tokens' q and dout rows, and a block that few tokens
 // select is cut once per 8192 of them: every item costs 32 KiB of K and V and 64 KiB of atomic sums (four times the items: 1190 -> 2210 us
 // for 32K tokens).  Against segments of 2048 tokens, queued as their wavefronts finished: dk/dv 1220 -> 1120 us at 32K tokens, G = 16
-// (segments of 4096: 1100 with the windows' order, 1150 with 2048); this kernel 11.5 -> 14 us there and 11.4 -> 6.9 us for
-// 2 x 4096 tokens (a thread per block walked its words twice, one after the other).
+// (segments of 4096: 1100 with the windows' order, 1150 with 2048); this kernel 11.5 -> 9.6 us there and 11.4 -> 6.5 us for
+// 2 x 4096 tokens (a thread per block walked its words twice, one after the other).  The slices' order instead of the order in which the
+// wavefronts finished inside a window (1024 tokens are 8 MiB of rows, an XCD's L2 holds 4): misses 64 -> 54 million lines, dk/dv by
+// itself the same, the backward call 2410 -> 2350 us at 32K tokens, 10950 -> 10850 at 128K (fewer lines from the far cache: the clock
+// stays higher in dq too).  With windows dealt by their place in the segment, four sequences of 4096 tokens kept half the
+// queues empty: 1125 -> 1110.
 constexpr int kItemBlocks = 4;
 __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
-                                                         int32_t nb_cap, int32_t n_seg, int32_t members, int32_t seg_shift, int32_t n_bins,
+                                                         int32_t nb_cap, int32_t n_seg, int32_t members, int32_t bin_shift, int32_t n_bins,
                                                          int32_t bin_cap, uint32_t *__restrict__ counters, uint4 *__restrict__ items) {
-    static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8, "four words a lane, eight lanes a window");
+    static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8 && kSlices == 8, "four words a lane, eight lanes a window, one a slice");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int seg = blockIdx.x % n_seg, j0 = (int)(blockIdx.x / n_seg * 4 + wave) * kItemBlocks;
     const int h = blockIdx.y, b = blockIdx.z;
@@ -193,9 +201,12 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
     const float inv = 1.f / (float)members;
-    const int bin = (int)((bh * n_seg + seg) >> seg_shift);
+    const int bin = (int)(((bh * n_seg + seg) * kSlices + (lane & 7)) >> bin_shift);
+    // windows are dealt to the queues round robin over all sequences and heads (short sequences have less than a segment)
+    const int queue = (int)((lane >> 3) + bh * ((2 * nb_cap + kWindowWords - 1) / kWindowWords)) & (kQueues - 1);
+    const int run = (1 << min(bin_shift, 3)) - 1;         // lanes of a window that share a bin: run + 1
     uint32_t ends[kItemBlocks];                           // bits 0 .. 3: an item ends with the lane's word; bit 4: the block's last one
-    int place[kItemBlocks];                               // (lanes 8w: where the window's items go; else behind the lanes before)
+    int place[kItemBlocks];                               // (the first lane of a run: where the run's items go)
 #pragma unroll
     for (int i = 0; i < kItemBlocks; ++i) {
         const int j = j0 + i;
@@ -224,14 +235,14 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
         const int lane_end = have ? 63 - __builtin_clzll(have) : -1;
         const int total = __builtin_amdgcn_readlane(incl, 63);
         const int tail = have ? total - __builtin_amdgcn_readlane(incl, max(lane_end, 0)) + __builtin_amdgcn_readlane(left, max(lane_end, 0)) : total;
-        if (tail > 0 && lane == 8 * (j & 7)) m |= 16u;
+        if (tail > 0 && lane == 8 * (j & 7) + 7) m |= 16u;
         ends[i] = m;
         const int mine = __popc(m), sums = wave_inclusive_sum(mine);
-        const int start = __builtin_amdgcn_ds_bpermute(4 * ((lane & 56) - 1), sums);       // lanes before the window
-        const int own = sums - ((lane & 56) ? start : 0);                                  // of the window's, up to this lane
-        const int all = __builtin_amdgcn_ds_bpermute(4 * (lane | 7), own);
+        const int start = __builtin_amdgcn_ds_bpermute(4 * ((lane & ~run) - 1), sums);     // lanes before the run
+        const int own = sums - ((lane & ~run) ? start : 0);                                // of the run's, up to this lane
+        const int all = __builtin_amdgcn_ds_bpermute(4 * (lane | run), own);
         int to = 0;
-        if ((lane & 7) == 0 && all > 0) to = (int)atomicAdd(&counters[(lane >> 3) * kQueueStride + bin], (uint32_t)all);
+        if ((lane & run) == 0 && all > 0) to = (int)atomicAdd(&counters[queue * kQueueStride + bin], (uint32_t)all);
         place[i] = to;
         n[0] = own - mine;
         ends[i] |= (uint32_t)n[0] << 8;
@@ -248,8 +259,8 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
         const int last = __builtin_amdgcn_readlane(mine_end, lane_end);
         const int own = max(2 * (j0 + i) - w0, 0);        // (the words before the block's own tokens hold nothing: not even zeros)
         int first = below ? prev : own;
-        int to = __builtin_amdgcn_ds_bpermute(4 * (lane & 56), place[i]) + (int)(ends[i] >> 8);
-        uint4 *dst = items + ((int64_t)(lane >> 3) * n_bins + bin) * bin_cap;
+        int to = __builtin_amdgcn_ds_bpermute(4 * (lane & ~run), place[i]) + (int)(ends[i] >> 8);
+        uint4 *dst = items + ((int64_t)queue * n_bins + bin) * bin_cap;
         auto put = [&](int f, int e) __attribute__((always_inline)) {
             dst[to++] = uint4{(uint32_t)bh, (uint32_t)(j0 + i), (uint32_t)(w0 + f), (uint32_t)(e - f)};
         };
@@ -623,8 +634,8 @@ static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, co
 //   P = exp(S - lse), dS = P (dP - D)         lane = key, 16 rows: as bf16 they are the next products' A operands
 //   dV[key, c] += P^T.dO, dK += dS^T.Q        B = the same rows through the transposing LDS load, contraction index permuted to match
 // Nothing passes between the two waves but the staged rows: one barrier per step.
-// Bound by the matrix cores (busy 51 % of the time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (9.4 GB
-// past L2, whose hit rate is 17 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
+// Bound by the matrix cores (busy 51 % of the time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (6.9 GB
+// past L2, whose hit rate is 34 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
 // keys the LDS reads double.  Against a workgroup per (block, 2048-token segment) with P and dS exchanged through LDS, rows
 // of two whole tokens a step, and blocks dealt to the XCDs by their number (the first block, which every token selects, kept
 // one XCD busy while the others waited: CUs 55 % busy): 32K tokens, G = 16 3440 -> 1190 us; 2 x 4096 tokens, G = 8
@@ -654,7 +665,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     __shared__ BwdSlot slot0, slot1;
     __shared__ uint4 item_s;
     __shared__ int tries_s, total_s;
-    __shared__ uint32_t bins_s[kBins];                    // items in the queue's bins up to this one
+    __shared__ __align__(16) uint32_t bins_s[kBins];                  // items in the queue's bins up to this one
     const int tid = threadIdx.x, lane = tid & 63;
     int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     asm volatile("" : "+s"(wave));                        // (a scalar, also after the compiler's own rewriting)
@@ -668,8 +679,13 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         return atomicAdd(&counters[((blockIdx.x + x) % kQueues) * kQueueStride + kBins], 1u);
     };
     auto count_bins = [&](int x) __attribute__((always_inline)) {
-        const uint32_t n = lane < n_bins ? counters[((blockIdx.x + x) % kQueues) * kQueueStride + lane] : 0u;
-        bins_s[lane] = (uint32_t)wave_inclusive_sum((int)n);
+        static_assert(kBins == 4 * 64, "four bins a lane");
+        uint4 n = reinterpret_cast<const uint4 *>(counters + ((blockIdx.x + x) % kQueues) * kQueueStride)[lane];   // (0 past n_bins)
+        n.y += n.x;
+        n.z += n.y;
+        n.w += n.z;
+        const uint32_t before = (uint32_t)wave_inclusive_sum((int)n.w) - n.w;
+        reinterpret_cast<uint4 *>(bins_s)[lane] = uint4{n.x + before, n.y + before, n.z + before, n.w + before};
     };
     uint32_t ticket = 0;                                  // thread 0: place in queue `tries` behind the own one
     if (wave == 0) {
@@ -684,10 +700,11 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         if (wave == 0) {
             uint4 it = {0u, 0u, 0u, 0u};
             for (int x = __builtin_amdgcn_readfirstlane(tries_s);;) {   // ends: a queue that is found empty stays empty
-                const uint32_t t = __builtin_amdgcn_readfirstlane(ticket), upto = bins_s[lane];
-                const int bin = __popcll(__ballot(upto <= t));
-                if (bin < kBins) {
-                    const uint32_t before = bin ? __builtin_amdgcn_readlane((int)upto, max(bin - 1, 0)) : 0u;
+                const uint32_t t = __builtin_amdgcn_readfirstlane(ticket);
+                const int four = __popcll(__ballot(bins_s[4 * lane + 3] <= t));
+                const int bin = 4 * four + __popcll(__ballot(bins_s[min(4 * four + (lane & 3), kBins - 1)] <= t) & 15ull);
+                if (four < 64) {
+                    const uint32_t before = bin ? __builtin_amdgcn_readfirstlane(bins_s[bin - 1]) : 0u;
                     it = items[((int64_t)((blockIdx.x + x) % kQueues) * n_bins + bin) * bin_cap + (t - before)];
                     break;
                 }
@@ -948,7 +965,7 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     timing_end(stream);
     timing_begin("bwd_items_kernel", stream);
     hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)(l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks))), dm.Hkv, dm.batch),
-                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, l.members, l.seg_shift, l.n_bins, l.bin_cap, counters, items);
+                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, l.members, l.bin_shift, l.n_bins, l.bin_cap, counters, items);
     timing_end(stream);
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;

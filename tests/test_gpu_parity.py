@@ -1055,8 +1055,10 @@ def test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk):
         assert bool((dq[b, l:] == 3.0).all()) and bool((dk[b, :, l:] == 3.0).all()) and bool((dv[b, :, l:] == 3.0).all())
 
 
-# The scatter's work items: more (sequence, head) segments than a queue has bins, and the first word of a second segment of 8192 tokens.
-@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([200 - 6 * i for i in range(33)], 2, 2, 4), ([8193, 8192, 8161], 16, 1, 3)])
+# The scatter's work items: more slices than a queue has bins (a bin is part of a window, or several), and the first word of a second
+# segment of 8192 tokens.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([200 - 6 * i for i in range(33)], 2, 2, 4), ([8193, 8192, 8161], 16, 1, 3),
+                                                 ([65 - i % 61 for i in range(130)], 2, 2, 3)])
 def test_sparse_attn_backward_items(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
