@@ -393,7 +393,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     }
     __syncthreads();
     const int cnt = __builtin_amdgcn_readfirstlane(cnt_s);
-    auto union_entry = [&](int i) __attribute__((always_inline)) { return ul.list[min(i, cnt - 1)]; };
+    // the tokens' own block, the one with the causal edge, comes last; the others from `start` on
+    const int own_at = __builtin_amdgcn_readfirstlane(cnt > 0 && ul.list[max(cnt - 1, 0)].x == (uint32_t)b_own ? cnt - 1 : cnt);
+    const int start = walk_start(own_at, sl, 64, b_own);
+    auto union_entry = [&](int i) __attribute__((always_inline)) {
+        const int at = i + start;
+        return ul.list[i >= own_at ? min(i, cnt - 1) : at >= own_at ? at - own_at : at];
+    };
 
     // block addresses are uniform: buffer loads, no vector address arithmetic
     const char *kv_head = reinterpret_cast<const char *>(kvb) + ((int64_t)b * dm.Hkv + h) * nb_cap * (kBwdBlockU4 * 16);
@@ -543,7 +549,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
             }
         }
     };
-    const int own_at = cnt > 0 && ul.list[max(cnt - 1, 0)].x == (uint32_t)b_own ? cnt - 1 : cnt;
     for (int ci = wave; ci < own_at; ci += 4) block(std::false_type{}, ci);
     if (own_at < cnt && (own_at & 3) == wave) block(std::true_type{}, own_at);
     // ---- add the four wavefronts' sums, a tile at a time, and write: lane holds channels 16*dt + 4*g .. +3 of column n ----

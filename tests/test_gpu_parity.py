@@ -1063,6 +1063,13 @@ def test_sparse_attn_backward_items(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Walks that begin inside the list (from block 128 on): lists shorter than the workgroups that share an XCD are many, tiles of one and of
+# several tokens, wavefronts that work alone and that split the list.  The gradients take the forward's out and lse in.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([9001, 8400], 16, 1, 16), ([8500], 16, 1, 3), ([8450], 8, 1, 4), ([8777], 2, 1, 7)])
+def test_sparse_attn_beyond_one_l2(seqlens, Hq, Hkv, topk):
+    test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
+
+
 def test_sparse_attn_backward_long_capacity():
     # buffers much longer than the sequences: the membership words and the dk / dv sums are laid out by the
     # capacity, the work items cut by 2048-token segments of the sequence; one that ends inside its fifth
