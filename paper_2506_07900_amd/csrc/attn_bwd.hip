@@ -639,8 +639,9 @@ static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, co
 //   P = exp(S - lse), dS = P (dP - D)         lane = key, 16 rows: as bf16 they are the next products' A operands
 //   dV[key, c] += P^T.dO, dK += dS^T.Q        B = the same rows through the transposing LDS load, contraction index permuted to match
 // Nothing passes between the two waves but the staged rows: one barrier per step.
-// Bound by the matrix cores (busy 51 % of the time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (6.9 GB
-// past L2, whose hit rate is 34 %).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
+// Bound by the matrix cores (busy 54 % of the time at 32K tokens, G = 16) and by the rows' way from the memory-side cache (5.3 GB
+// past L2, whose hit rate is 36 %; at 128K 35 GB at 7.1 TB/s).  Leaving parts out, of 1120 us: without the copies 910, without the products 980,
+// without the atomic sums 1060.  Operands are read one product ahead; two ahead spill (1120 -> 1690 us).  The 32 keys are what lets 128 accumulator registers and the 64 of K and V fit a wavefront of two per SIMD; with 16
 // keys the LDS reads double.  Against a workgroup per (block, 2048-token segment) with P and dS exchanged through LDS, rows
 // of two whole tokens a step, and blocks dealt to the XCDs by their number (the first block, which every token selects, kept
 // one XCD busy while the others waited: CUs 55 % busy): 32K tokens, G = 16 3440 -> 1190 us; 2 x 4096 tokens, G = 8

@@ -114,7 +114,8 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
 // one another (11 % of the matrix time runs under vector work).  Leaving parts out, of 0.79 ms (with the events around the
 // launch): the loads alone 0.69, all but the loads 0.52, the matrix products alone 0.43; without the exponentials 0.74, without
 // the value product 0.72, without misses (32 blocks in all) 0.73.  The loads are 16.6 GB (2.7 GB of them past L2), 0.46 ms at the
-// 36 TB/s that a kernel of nothing but fragment loads reaches; with four units of 4 KiB per wavefront under way they run at 24.
+// 36 TB/s that a kernel of nothing but fragment loads reaches; here they run at 24 - 28, with two, four or eight units of 4 KiB per
+// wavefront under way.  (Walks that begin where the others are have since made that 0.77 ms and 1.9 GB.)
 // The union of two tokens has 24 blocks, of four 33: four tokens per wavefront, their queries in LDS so that the accumulators
 // (128 registers) and a ring of four units fit 256 registers, load 16.6 GB instead of 22.5: 1.00 -> 0.78 ms.
 //
