@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     const int cnt = __builtin_amdgcn_readfirstlane(cnt_s);
     // the tokens' own block, the one with the causal edge, comes last; the others from `start` on
     const int own_at = __builtin_amdgcn_readfirstlane(cnt > 0 && ul.list[max(cnt - 1, 0)].x == (uint32_t)b_own ? cnt - 1 : cnt);
-    const int start = walk_start(own_at, sl, 64, b_own);
+    const int start = walk_start(own_at, tile, 64, b_own);
     auto union_entry = [&](int i) __attribute__((always_inline)) {
         const int at = i + start;
         return ul.list[i >= own_at ? min(i, cnt - 1) : at >= own_at ? at - own_at : at];

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
         __syncthreads();
         cnt = __builtin_amdgcn_readfirstlane(cnt_s);
     }
-    const int start = walk_start(cnt, sl, 32 * C::kWavesPerSimd, b_own);      // (32 compute units per XCD, four wavefronts per workgroup)
+    const int start = walk_start(cnt, tile, 32 * C::kWavesPerSimd, b_own);      // (32 compute units per XCD, four wavefronts per workgroup)
     auto union_entry = [&](int i) __attribute__((always_inline)) {
         const int at = min(i, cnt - 1) + start;
         return ul.list[at >= cnt ? at - cnt : at];

@@ -97,13 +97,17 @@ __device__ inline int build_union(const UnionRows<NT> &head, const int32_t *__re
 // Where in its list of n blocks a workgroup begins its walk (which goes round).  Once a head's packed keys and values are more than an XCD's
 // L2 holds, what a block costs depends on who asked for it last: workgroups that begin one after another and all walk upwards are spread
 // over the whole sequence.  The `resident` workgroups of an XCD begin one walk's time / resident apart, so beginning slot / resident
-// into the list puts them all near the same blocks.  (The order depends on the call's sizes alone.)  Lines past L2, attention, 128K tokens,
+// into the list puts them all near the same blocks.  The slot is counted back from a fixed tile (the launches deal tiles last first, in runs to
+// the XCDs), so in one form of the kernel the order of a token's sums depends
+// neither on the capacity nor on the other sequences.  Lines past L2, attention, 128K tokens,
 // 2 x 16 heads: 219 -> 159 million, 4250 -> 3950 us; top-k 64, 64K 9550 -> 6740; G = 8, 32K 768 -> 688; G = 4, 32K 775 -> 630; G = 16, 32K 803
 // -> 790, 16K and below: the same.  Half as many residents, or the other way round: 4310 for the first.  dq: 64K, G = 4 3490 -> 2975 us
 // for the whole backward, top-k 64, G = 16 18.7 -> 16.8 ms; G = 16, top-k 16: the same.
 constexpr int kFarBlocks = 128;                          // 4 MiB of packed blocks
-__device__ inline int walk_start(int n, int slot, int resident, int b_own) {
-    return b_own >= kFarBlocks ? __builtin_amdgcn_readfirstlane((int)((uint32_t)n * (uint32_t)(slot % resident) / (uint32_t)resident)) : 0;
+__device__ inline int walk_start(int n, int tile, uint32_t resident, int b_own) {
+    if (b_own < kFarBlocks) return 0;
+    const uint32_t r = 0x40000000u - (uint32_t)tile, slot = r / (8 * kRun) * kRun + r % kRun;
+    return __builtin_amdgcn_readfirstlane((int)((uint32_t)n * (slot % resident) / resident));
 }
 
 // Rows of 128 channels in LDS: a row's sixteen 16-byte pieces are stored XOR-swizzled with the row's two bit pairs exchanged.  An
