@@ -238,10 +238,11 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
         __syncthreads();
         cnt = __builtin_amdgcn_readfirstlane(cnt_s);
     }
-    const int start = walk_start(cnt, tile, 32 * C::kWavesPerSimd, b_own);      // (32 compute units per XCD, four wavefronts per workgroup)
+    // (32 compute units per XCD, four wavefronts per workgroup; direct fetches are for short prompts)
+    const int start = kDirect ? 0 : walk_start(cnt, tile, 32 * C::kWavesPerSimd, b_own);
     auto union_entry = [&](int i) __attribute__((always_inline)) {
         const int at = min(i, cnt - 1) + start;
-        return ul.list[at >= cnt ? at - cnt : at];
+        return ul.list[!kDirect && at >= cnt ? at - cnt : at];
     };
 
     // A block's address is uniform: fragments come by buffer loads (scalar base and offset, one vector register of lane
