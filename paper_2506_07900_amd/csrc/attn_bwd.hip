@@ -36,7 +36,8 @@ constexpr int kQueues = 8;                            // one per XCD
 constexpr int kWindowWords = kSegWords / kQueues;
 constexpr int kSlices = 8;
 constexpr int kBins = 256;                            // at most, of a queue
-constexpr int kQueueStride = kBins + 64;                     // counters of a queue: kBins lengths, then, on a line of its own, the place drawn last
+constexpr int kCounterLine = 32;
+constexpr uint32_t kBehind = 1u << 31;                // in a queue's place drawn last: there are items behind the queues
 
 // Members of an item, in steps of 32 (token, head) rows: an equal share for each of the chip's kDkdvGroups workgroups, within
 // 12 .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us
@@ -51,9 +52,33 @@ static inline int32_t bwd_item_members(const Dims &dm) {
     return (int32_t)(m > kMaxMembers - 32 ? kMaxMembers - 32 : m);
 }
 
+// Where items lie and what an item says.  A queue has n bins of `cap` places, the last bin of a window `tail` more; what finds its bin
+// full goes to one list behind the queues, taken when they are empty, which has room for every item of the call.  Counters, of a
+// queue and then of that list: the bins' lengths, then, on a line of its own, the place drawn last.  (That the list has items is told
+// with the places: every workgroup's look at its length is one address for the chip, 3.5 of 35 us for 500 tokens.)
+struct BwdBins {
+    int32_t n, shift;                                 // bins of a queue; slices of a bin (log2)
+    int32_t cap, tail, window;                        // a window's bins (log2)
+    int32_t size, stride;                             // places, counters of a queue
+    int32_t block_bits;
+    __host__ __device__ int64_t begin(int queue, int bin) const {
+        return (int64_t)queue * size + (int64_t)bin * cap + (int64_t)(bin >> window) * tail;
+    }
+    __device__ uint32_t places(int bin) const { return (uint32_t)(cap + ((bin + 1) & ((1 << window) - 1) ? 0 : tail)); }
+    // {sequence and head, block, first word, words - 1}.  It fits: the membership words, two per block and block, are in memory.
+    __device__ uint64_t item(int64_t bh, int j, int w, int n_words) const {
+        return ((((uint64_t)bh << block_bits | (uint32_t)j) << (block_bits + 1) | (uint32_t)w) << 8) | (uint32_t)(n_words - 1);
+    }                                                 // (a segment's first word is a multiple of 256: the words' bits are the low 16)
+    __device__ uint4 unpack(uint64_t x) const {
+        const uint64_t w = x >> 8, j = w >> (block_bits + 1);
+        return uint4{(uint32_t)(j >> block_bits), (uint32_t)j & ((1u << block_bits) - 1u), (uint32_t)w & ((2u << block_bits) - 1u),
+                     (uint32_t)(x & 255u) + 1u};
+    }
+};
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
-    int32_t members, bin_shift, n_bins, bin_cap;      // an item's members; slices of a bin (log2), bins of a queue, items of a bin
+    int32_t members;                                  // of an item
+    BwdBins bins;
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
 static inline size_t al256(size_t x) { return (x + 255) / 256 * 256; }
@@ -64,24 +89,47 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
     l.members = bwd_item_members(dm);
-    const size_t slices = BH * l.n_seg * kSlices, nb = (size_t)l.nb_cap;
-    l.bin_shift = 0;
-    while ((slices + ((size_t)1 << l.bin_shift) - 1) >> l.bin_shift > (size_t)kBins) ++l.bin_shift;
-    l.n_bins = (int32_t)((slices + ((size_t)1 << l.bin_shift) - 1) >> l.bin_shift);
-    // items that end in a run of slices: one per `members` list entries, one more per block with an entry (begun before), the own
-    // tokens' of its blocks; and every eighth block's last of the segment.  A bin is such a run, or several windows.
-    const int run = l.bin_shift < 3 ? l.bin_shift : 3;
-    const size_t words = (size_t)(kWindowWords / kSlices) << run, ent = words * 32 * dm.topk;
-    const size_t per_run = (ent < nb ? ent : nb) + ent / l.members + words / 2 + (nb + kQueues - 1) / kQueues;
-    l.bin_cap = (int32_t)(per_run << (l.bin_shift - run));
+    const size_t nb = (size_t)l.nb_cap, words = (size_t)l.words, windows = BH * ((words + kWindowWords - 1) / kWindowWords);
+    const size_t slots = windows ? (windows + kQueues - 1) / kQueues : 1;       // windows of a queue
+    BwdBins &t = l.bins;
+    t.shift = 0;
+    while ((slots * kSlices + ((size_t)1 << t.shift) - 1) >> t.shift > (size_t)kBins) ++t.shift;
+    t.n = (int32_t)((slots * kSlices + ((size_t)1 << t.shift) - 1) >> t.shift);
+    t.stride = (t.n + kCounterLine - 1) / kCounterLine * kCounterLine + kCounterLine;
+    t.block_bits = 1;
+    while (nb >> t.block_bits) ++t.block_bits;
+    // Items that end in a run of slices: at most one per `members` list entries, one more per block with an entry (begun before) and the
+    // own tokens' of its blocks.  That every block's ends there is provided for in the list behind; a bin has room for twice the mean
+    // and, blocks that are equally popular being cut at about the same tokens, a sixteenth of the blocks.  (Bins for the worst case
+    // took 4.9 MB for 32K tokens x 2 heads, top-k 16, and 76 MB for 128K; these 0.4 and 3.0.)
+    const int run = t.shift < 3 ? t.shift : 3;
+    const size_t run_words = (size_t)(kWindowWords / kSlices) << run, rw = run_words < words ? run_words : words;
+    const size_t ent = rw * 32 * dm.topk, most = (ent < nb ? ent : nb) + ent / l.members + rw / 2;
+    const size_t sparse = 64 * (size_t)dm.topk < nb ? 64 * (size_t)dm.topk : nb;
+    size_t cap = 2 * ent / l.members + rw / 2 + sparse / 16;
+    cap = cap < most ? cap : most;
+    // what is left of the blocks at the segments' ends: to the last slices of all windows alike
+    const size_t seg_ent = (words < (size_t)kSegWords ? words : (size_t)kSegWords) * 32 * dm.topk;
+    const size_t tails = BH * l.n_seg * (seg_ent < nb ? seg_ent : nb), tail = (tails + slots * kQueues - 1) / (slots * kQueues);
+    const size_t spill = BH * (words * 32 * dm.topk / l.members + nb) + tails;
+    // Never more than a list per queue took when segments had 2048 tokens and an item 16 bytes: buffers of that size stay large enough.
+    const size_t ent0 = (size_t)64 * 32 * dm.topk, seg0 = (ent0 < nb ? ent0 : nb) + 2 * ent0 / l.members + 33;
+    const size_t lists0 = 2 * ((BH * ((words + 63) / 64) + kQueues - 1) / kQueues) * seg0;            // places per queue
+    const size_t rest = spill / kQueues + slots * tail + (size_t)9 * t.stride / 16 + 64;
+    const size_t room = (lists0 > rest ? lists0 - rest : 0) / (slots * kSlices >> run);
+    cap = cap < room ? cap : room;
+    t.window = 3 - run;
+    t.cap = (int32_t)(t.shift < 3 ? cap : cap << (t.shift - 3));
+    t.tail = (int32_t)(t.shift < 3 ? tail : tail << (t.shift - 3));
+    t.size = (int32_t)t.begin(0, t.n);
     size_t o = 0;
     l.kvb = o;      o += al256(BH * l.nb_cap * kBwdBlockU4 * sizeof(uint4));
     l.rowc = o;     o += al256(((size_t)dm.batch * T * dm.Hq * 2 + 32) * sizeof(float));
     l.bits = o;     o += al256(BH * l.words * l.nb_cap * sizeof(uint32_t));
     l.acc_dk = o;   o += al256(BH * T * kHeadDim * sizeof(float));
     l.acc_dv = o;   o += al256(BH * T * kHeadDim * sizeof(float));
-    l.counters = o; o += al256((size_t)kQueues * kQueueStride * sizeof(uint32_t));
-    l.items = o;    o += al256((size_t)kQueues * l.n_bins * l.bin_cap * sizeof(uint4));
+    l.counters = o; o += al256((size_t)(kQueues + 1) * t.stride * sizeof(uint32_t));
+    l.items = o;    o += al256(((size_t)kQueues * t.size + spill) * sizeof(uint64_t));
     l.total = o;
     return l;
 }
@@ -102,14 +150,14 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
                                                         uint4 *__restrict__ kvb, int32_t nb_cap,
                                                         const int32_t *__restrict__ block_idx, uint32_t *__restrict__ bits,
                                                         float *__restrict__ acc_dk, float *__restrict__ acc_dv,
-                                                        uint32_t *__restrict__ counters, float *__restrict__ null_row) {
+                                                        uint32_t *__restrict__ counters, int32_t n_counters, float *__restrict__ null_row) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int L = seq_len(dm, seqlens, b);
     const int tid = threadIdx.x;
     if ((j | h | b) == 0) {
-        for (int i = tid; i < kQueues * kQueueStride; i += 256) counters[i] = 0u;
+        for (int i = tid; i < n_counters; i += 256) counters[i] = 0u;
         if (tid < 32) null_row[tid] = tid < 16 ? -INFINITY : 0.f;       // the constants of a row that is not there: p = 0
     }
     if (j * kBlock >= L) return;
@@ -183,9 +231,12 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
 // queues empty: 1125 -> 1110.
 constexpr int kItemBlocks = 4;
 __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
-                                                         int32_t nb_cap, int32_t n_seg, int32_t members, int32_t bin_shift, int32_t n_bins,
-                                                         int32_t bin_cap, uint32_t *__restrict__ counters, uint4 *__restrict__ items) {
+                                                         int32_t nb_cap, int32_t n_seg, int32_t members, BwdBins bins,
+                                                         uint32_t *__restrict__ counters, uint64_t *__restrict__ items) {
     static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8 && kSlices == 8, "four words a lane, eight lanes a window, one a slice");
+    // (the arguments arrive together, not one round trip after another where each is first used)
+    asm volatile("" : "+s"(bins.shift), "+s"(bins.cap), "+s"(bins.tail), "+s"(bins.window), "+s"(bins.size), "+s"(bins.stride),
+                 "+s"(bins.block_bits), "+s"(members), "+s"(counters), "+s"(items));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int seg = blockIdx.x % n_seg, j0 = (int)(blockIdx.x / n_seg * 4 + wave) * kItemBlocks;
     const int h = blockIdx.y, b = blockIdx.z;
@@ -201,10 +252,14 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
     const float inv = 1.f / (float)members;
-    const int bin = (int)(((bh * n_seg + seg) * kSlices + (lane & 7)) >> bin_shift);
-    // windows are dealt to the queues round robin over all sequences and heads (short sequences have less than a segment)
-    const int queue = (int)((lane >> 3) + bh * ((2 * nb_cap + kWindowWords - 1) / kWindowWords)) & (kQueues - 1);
-    const int run = (1 << min(bin_shift, 3)) - 1;         // lanes of a window that share a bin: run + 1
+    // Windows are numbered through all sequences and heads and dealt to the queues round robin (short sequences have less than a segment).
+    const int windows = (2 * nb_cap + kWindowWords - 1) / kWindowWords;
+    const int slot = min((int)(bh * windows + seg * kQueues + (lane >> 3)) / kQueues, ((int)(dm.batch * dm.Hkv * windows) + kQueues - 1) / kQueues - 1);
+    const int bin = (slot * kSlices + (lane & 7)) >> bins.shift;
+    const int queue = (int)((lane >> 3) + bh * windows) & (kQueues - 1);
+    const int run = (1 << min(bins.shift, 3)) - 1;        // lanes of a window that share a bin: run + 1
+    const uint32_t places = bins.places(bin);
+    const uint32_t begin = (uint32_t)bins.begin(queue, bin);          // (all of it is under a hundredth of a workspace that fits the card)
     uint32_t ends[kItemBlocks];                           // bits 0 .. 3: an item ends with the lane's word; bit 4: the block's last one
     int place[kItemBlocks];                               // (the first lane of a run: where the run's items go)
 #pragma unroll
@@ -242,10 +297,26 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
         const int own = sums - ((lane & ~run) ? start : 0);                                // of the run's, up to this lane
         const int all = __builtin_amdgcn_ds_bpermute(4 * (lane | run), own);
         int to = 0;
-        if ((lane & run) == 0 && all > 0) to = (int)atomicAdd(&counters[queue * kQueueStride + bin], (uint32_t)all);
+        if ((lane & run) == 0 && all > 0) to = (int)atomicAdd(&counters[queue * bins.stride + bin], (uint32_t)all);
         place[i] = to;
         n[0] = own - mine;
         ends[i] |= (uint32_t)n[0] << 8;
+    }
+    int over = 0;                                         // this lane's items that find their bin full
+#pragma unroll
+    for (int i = 0; i < kItemBlocks; ++i) {
+        const int mine = __popc(ends[i] & 31u);
+        place[i] = __builtin_amdgcn_ds_bpermute(4 * (lane & ~run), place[i]) + (int)(ends[i] >> 8);
+        over += max(0, min(mine, place[i] + mine - (int)places));
+    }
+    uint32_t behind = 0;
+    if (__any(over > 0)) {
+        const int incl = wave_inclusive_sum(over);
+        if (lane == 63) behind = atomicAdd(&counters[kQueues * bins.stride], (uint32_t)incl);
+        behind = (uint32_t)bins.begin(kQueues, 0) + (uint32_t)__builtin_amdgcn_readlane((int)behind, 63) + (uint32_t)(incl - over);
+        // (a length never falls below `places` again: in the end it is what the bin holds)
+        if (over > 0) atomicSub(&counters[queue * bins.stride + bin], (uint32_t)over);
+        if (lane < kQueues) atomicOr(&counters[lane * bins.stride + bins.stride - kCounterLine], kBehind);
     }
 #pragma unroll
     for (int i = 0; i < kItemBlocks; ++i) {
@@ -259,10 +330,13 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
         const int last = __builtin_amdgcn_readlane(mine_end, lane_end);
         const int own = max(2 * (j0 + i) - w0, 0);        // (the words before the block's own tokens hold nothing: not even zeros)
         int first = below ? prev : own;
-        int to = __builtin_amdgcn_ds_bpermute(4 * (lane & ~run), place[i]) + (int)(ends[i] >> 8);
-        uint4 *dst = items + ((int64_t)queue * n_bins + bin) * bin_cap;
+        uint32_t to = begin + (uint32_t)place[i];
+        const uint64_t head = bins.item(bh, j0 + i, w0, 1);
         auto put = [&](int f, int e) __attribute__((always_inline)) {
-            dst[to++] = uint4{(uint32_t)bh, (uint32_t)(j0 + i), (uint32_t)(w0 + f), (uint32_t)(e - f)};
+            const uint32_t at = to < begin + places ? to : behind;
+            behind += to >= begin + places ? 1u : 0u;
+            ++to;
+            items[at] = head | (uint64_t)(uint32_t)(f << 8 | (e - f - 1));
         };
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -664,7 +738,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                                                                 int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                                 const float *__restrict__ rowc, const float *__restrict__ null_row,
                                                                 const uint32_t *__restrict__ bits, uint32_t *__restrict__ counters,
-                                                                const uint4 *__restrict__ items, int32_t n_bins, int32_t bin_cap,
+                                                                const uint64_t *__restrict__ items, BwdBins bins,
                                                                 float *__restrict__ acc_dk, float *__restrict__ acc_dv) {
     constexpr int kTPS = 32 / kG;                         // tokens per step
     __shared__ uint16_t list[kMaxMembers];                // the item's member tokens as offsets from its first word's first token
@@ -672,6 +746,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     __shared__ uint4 item_s;
     __shared__ int tries_s, total_s;
     __shared__ __align__(16) uint32_t bins_s[kBins];                  // items in the queue's bins up to this one
+    __shared__ BwdBins geo;                               // `bins`, which would hold scalar registers through the walk
     const int tid = threadIdx.x, lane = tid & 63;
     int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     asm volatile("" : "+s"(wave));                        // (a scalar, also after the compiler's own rewriting)
@@ -681,45 +756,44 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     const __bf16 *const s_ptr = wave == 0 ? q.ptr : dout.ptr;
     const int64_t s_sb = wave == 0 ? q.sb : dout.sb, s_sh = wave == 0 ? q.sh : dout.sh, s_st = wave == 0 ? q.st : dout.st;
     const uint32_t s_head = (uint32_t)(s_sh * 2);         // bytes from head to head
+    auto queue_of = [&](int x) __attribute__((always_inline)) { return x < kQueues ? (int)((blockIdx.x + x) % kQueues) : kQueues; };
     auto draw = [&](int x) __attribute__((always_inline)) {
-        return atomicAdd(&counters[((blockIdx.x + x) % kQueues) * kQueueStride + kBins], 1u);
+        return atomicAdd(&counters[queue_of(x) * geo.stride + geo.stride - kCounterLine], 1u);
     };
-    auto count_bins = [&](int x) __attribute__((always_inline)) {
-        static_assert(kBins == 4 * 64, "four bins a lane");
-        uint4 n = reinterpret_cast<const uint4 *>(counters + ((blockIdx.x + x) % kQueues) * kQueueStride)[lane];   // (0 past n_bins)
+    uint32_t ticket = 0;                                  // thread 0: place in queue `tries` behind the own one
+    auto look_at = [&](int x) __attribute__((always_inline)) {       // wave 0: a queue's lengths and a place in it, one round trip
+        static_assert(kBins == 4 * 64 && kCounterLine % 4 == 0, "four bins a lane");
+        uint4 n = {0u, 0u, 0u, 0u};
+        if (4 * lane < geo.stride - kCounterLine) n = reinterpret_cast<const uint4 *>(counters + queue_of(x) * geo.stride)[lane];   // (0 past geo.n)
+        if (lane == 0) {
+            tries_s = x;
+            ticket = draw(x);
+        }
         n.y += n.x;
         n.z += n.y;
         n.w += n.z;
         const uint32_t before = (uint32_t)wave_inclusive_sum((int)n.w) - n.w;
         reinterpret_cast<uint4 *>(bins_s)[lane] = uint4{n.x + before, n.y + before, n.z + before, n.w + before};
     };
-    uint32_t ticket = 0;                                  // thread 0: place in queue `tries` behind the own one
     if (wave == 0) {
-        if (lane == 0) {
-            tries_s = 0;
-            ticket = draw(0);
-        }
-        count_bins(0);
+        geo = bins;                                       // by every lane: each reads what it has written itself
+        look_at(0);
     }
     for (;;) {
         // ---- next item ----------------------------------------------------------------------------------------------
         if (wave == 0) {
             uint4 it = {0u, 0u, 0u, 0u};
             for (int x = __builtin_amdgcn_readfirstlane(tries_s);;) {   // ends: a queue that is found empty stays empty
-                const uint32_t t = __builtin_amdgcn_readfirstlane(ticket);
+                const uint32_t drawn = __builtin_amdgcn_readfirstlane(ticket), t = drawn & ~kBehind;
                 const int four = __popcll(__ballot(bins_s[4 * lane + 3] <= t));
                 const int bin = 4 * four + __popcll(__ballot(bins_s[min(4 * four + (lane & 3), kBins - 1)] <= t) & 15ull);
                 if (four < 64) {
                     const uint32_t before = bin ? __builtin_amdgcn_readfirstlane(bins_s[bin - 1]) : 0u;
-                    it = items[((int64_t)((blockIdx.x + x) % kQueues) * n_bins + bin) * bin_cap + (t - before)];
+                    it = geo.unpack(items[geo.begin(queue_of(x), bin) + (t - before)]);
                     break;
                 }
-                if (++x == kQueues) break;
-                if (lane == 0) {
-                    tries_s = x;
-                    ticket = draw(x);
-                }
-                count_bins(x);
+                if (++x >= kQueues + (int)(drawn / kBehind)) break;
+                look_at(x);
             }
             if (lane == 0) item_s = it;
         }
@@ -916,10 +990,10 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
 
 template <int kG>
 static void launch_dkdv(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, const BwdLayout &l, const int32_t *seqlens,
-                        const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint4 *items,
+                        const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint64_t *items,
                         float *acc_dk, float *acc_dv, hipStream_t stream) {
     hipLaunchKernelGGL(attn_bwd_dkdv_kernel<kG>, dim3(kDkdvGroups), dim3(128), 0, stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc,
-                       null_row, bits, counters, items, l.n_bins, l.bin_cap, acc_dk, acc_dv);
+                       null_row, bits, counters, items, l.bins, acc_dk, acc_dv);
 }
 
 // ---- fp32 accumulators -> bf16 gradients ------------------------------------------------------------------
@@ -962,16 +1036,16 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     float *rowc = reinterpret_cast<float *>(base + l.rowc);
     float *null_row = rowc + (size_t)dm.batch * dm.max_seqlen * dm.Hq * 2;
     uint32_t *bits = reinterpret_cast<uint32_t *>(base + l.bits), *counters = reinterpret_cast<uint32_t *>(base + l.counters);
-    uint4 *items = reinterpret_cast<uint4 *>(base + l.items);
+    uint64_t *items = reinterpret_cast<uint64_t *>(base + l.items);
     float *acc_dk = reinterpret_cast<float *>(base + l.acc_dk), *acc_dv = reinterpret_cast<float *>(base + l.acc_dv);
     const int T = dm.max_seqlen;
     timing_begin("pack_bwd_kernel", stream);
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,
-                       l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, null_row);
+                       l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, (kQueues + 1) * l.bins.stride, null_row);
     timing_end(stream);
     timing_begin("bwd_items_kernel", stream);
     hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)(l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks))), dm.Hkv, dm.batch),
-                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, l.members, l.bin_shift, l.n_bins, l.bin_cap, counters, items);
+                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, l.members, l.bins, counters, items);
     timing_end(stream);
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;

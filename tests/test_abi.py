@@ -199,6 +199,14 @@ def test_verify_validation(lib):
     assert lib.infllmv2_append_kv_verify(P, T, T, T, T, None, FAKE, 0, 4096, 4, None) == 0
 
 
+# (batch, max_seqlen, key-value heads, top-k, group size): bytes
+FORMER_BACKWARD_BYTES = {
+    (1, 64, 1, 3, 1): 109824, (1, 777, 2, 8, 16): 2828032, (2, 1969, 3, 3, 2): 18446336, (33, 200, 2, 4, 1): 22374912,
+    (1, 2048, 1, 8, 4): 3273728, (2, 4096, 2, 16, 8): 26393088, (4, 12289, 2, 16, 16): 166896896,
+    (1, 9178, 16, 3, 8): 238212608, (1, 32768, 2, 16, 16): 113789696, (1, 32768, 2, 64, 16): 114576128,
+    (1, 131072, 2, 16, 16): 508629248, (4, 131072, 1, 16, 1): 952506624, (64, 1000, 8, 16, 1): 798796032}
+
+
 def test_backward_validation(lib):
     prm, t = good_params(), tensor()
     P, T = ctypes.byref(prm), ctypes.byref(t)
@@ -209,6 +217,10 @@ def test_backward_validation(lib):
     assert call(lse=None) == INVALID and call(idx=None) == INVALID and call(dq=None) == INVALID
     assert call(w=None, wb=0) == WORKSPACE and call(wb=need - 1) == WORKSPACE and call(w=FAKE + 16) == WORKSPACE
     assert lib.infllmv2_sparse_attn_bwd(P, T, T, T, T, T, FAKE, FAKE, 0, 4096, FAKE, T, T, T, FAKE, 1 << 40, None) == 0
+    # no larger than it was when an item of the scatter took 16 bytes and its segments 2048 tokens: callers may hold such buffers
+    for (batch, T_, hkv, topk, G), most in FORMER_BACKWARD_BYTES.items():
+        got = binding.workspace_bytes(binding.OP_ATTN_BWD, binding.Params(G * hkv, hkv, topk=topk), batch, T_)
+        assert 0 < got <= most, (batch, T_, hkv, topk, G, got, most)
     far = tensor()                                                                      # heads of a group too far apart
     far.stride_h = 1 << 28
     assert lib.infllmv2_sparse_attn_bwd(P, ctypes.byref(far), T, T, T, T, FAKE, FAKE, 1, 4096, FAKE, T, T, T, FAKE, 1 << 40,

@@ -1063,6 +1063,33 @@ def test_sparse_attn_backward_items(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Lists in which all blocks are equally popular, so that their items end at the same tokens: more than a bin holds (47 of 1125 items, 42 of
+# 462, where a bin has three places and a window's tails), the rest from the list behind the queues.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([10000], 2, 1, 16), ([1969, 1969], 6, 3, 3)])
+def test_sparse_attn_backward_items_beyond_their_bin(seqlens, Hq, Hkv, topk):
+    print("case attn backward bins", seqlens, Hq, Hkv, topk, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    oprm = oracle_params(prm)
+    gen = torch.Generator(device="cuda").manual_seed(79)
+    B, T = len(seqlens), max(seqlens)
+    q, do = (torch.randn((B, T, Hq, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    t = torch.arange(T)
+    n = torch.clamp(t // 64 + 1, max=topk)
+    i = torch.arange(topk)[None]
+    idx = torch.where(i < n[:, None], ((t * n)[:, None] + i) % (t // 64 + 1)[:, None], -1)
+    idx = idx.to(torch.int32)[None, None].expand(B, Hkv, T, topk).contiguous().cuda()
+    sl = dev_i32(seqlens)
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    dq, dk, dv = binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, sl, T, idx)
+    torch.cuda.synchronize()
+    for b, l in enumerate(seqlens):
+        wq, wk, wv, mq, mk, mv = ref.sparse_attn_bwd(to_bits(q[b, :l]), to_bits(k[b, :, :l]), to_bits(v[b, :, :l]), to_bits(do[b, :l]),
+                                                     np.arange(l, dtype=np.int32), idx[b, :, :l].cpu().numpy(), oprm, want_mag=True)
+        for got, want, mag in ((dq[b, :l], wq, mq), (dk[b, :, :l], wk, mk), (dv[b, :, :l], wv, mv)):
+            assert grad_err(got.double().cpu().numpy(), want, mag) <= 1.0
+
+
 # Walks that begin inside the list (from block 128 on): lists shorter than the workgroups that share an XCD are many, tiles of one and of
 # several tokens, wavefronts that work alone and that split the list.  The gradients take the forward's out and lse in.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([9001, 8400], 16, 1, 16), ([8500], 16, 1, 3), ([8450], 8, 1, 4), ([8777], 2, 1, 7)])
