@@ -252,11 +252,13 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
     const float inv = 1.f / (float)members;
-    // Windows are numbered through all sequences and heads and dealt to the queues round robin (short sequences have less than a segment).
+    // Windows are numbered through all sequences and heads of the capacity, eight to the queues' next slices; a sequence's are dealt to the
+    // queues round robin by its own length (by the capacity's, short sequences in long buffers meet in one queue: 1000 tokens of 8000,
+    // 2 heads, G = 16, top-k 8: dk/dv 121 us, so 115; one of 16384 and three short ones 677, so 667).
     const int windows = (2 * nb_cap + kWindowWords - 1) / kWindowWords;
     const int slot = min((int)(bh * windows + seg * kQueues + (lane >> 3)) / kQueues, ((int)(dm.batch * dm.Hkv * windows) + kQueues - 1) / kQueues - 1);
     const int bin = (slot * kSlices + (lane & 7)) >> bins.shift;
-    const int queue = (int)((lane >> 3) + bh * windows) & (kQueues - 1);
+    const int queue = (int)((lane >> 3) + bh * ((L + 32 * kWindowWords - 1) / (32 * kWindowWords))) & (kQueues - 1);
     const int run = (1 << min(bins.shift, 3)) - 1;        // lanes of a window that share a bin: run + 1
     const uint32_t places = bins.places(bin);
     const uint32_t begin = (uint32_t)bins.begin(queue, bin);          // (all of it is under a hundredth of a workspace that fits the card)
