@@ -46,7 +46,7 @@ constexpr uint32_t kBehind = 1u << 31;                // in a queue's place draw
 constexpr int kDkdvGroups = 256 * 4;
 constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
 static inline int32_t bwd_item_members(const Dims &dm) {
-    const int64_t all = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv * dm.topk;
+    const int64_t all = (int64_t)dm.batch * ((dm.max_seqlen + kBlock - 1) / kBlock * kBlock) * dm.Hkv * dm.topk;
     const int64_t steps = all * dm.G / 32 / kDkdvGroups;             // of 32 rows
     const int64_t m = (steps < 12 ? 12 : steps > 64 ? 64 : steps) * 32 / dm.G;
     return (int32_t)(m > kMaxMembers - 32 ? kMaxMembers - 32 : m);
@@ -98,12 +98,12 @@ static BwdLayout bwd_layout(const Dims &dm) {
     t.stride = (t.n + kCounterLine - 1) / kCounterLine * kCounterLine + kCounterLine;
     t.block_bits = 1;
     while (nb >> t.block_bits) ++t.block_bits;
-    // Items that end in a run of slices: at most one per `members` list entries, one more per block with an entry (begun before) and the
+    // Items that end in a slice: at most one per `members` list entries, one more per block with an entry (begun before) and the
     // own tokens' of its blocks.  That every block's ends there is provided for in the list behind; a bin has room for twice the mean
     // and, blocks that are equally popular being cut at about the same tokens, a sixteenth of the blocks.  (Bins for the worst case
-    // took 4.9 MB for 32K tokens x 2 heads, top-k 16, and 76 MB for 128K; these 0.4 and 3.0.)
-    const int run = t.shift < 3 ? t.shift : 3;
-    const size_t run_words = (size_t)(kWindowWords / kSlices) << run, rw = run_words < words ? run_words : words;
+    // took 4.9 MB for 32K tokens x 2 heads, top-k 16, and 76 MB for 128K; these 0.4 and 3.0.)  A bin of several
+    // slices has several slices' places, so that a call of fewer or shorter sequences never asks for more than a larger one.
+    const size_t slice_words = kWindowWords / kSlices, rw = slice_words < words ? slice_words : words;
     const size_t ent = rw * 32 * dm.topk, most = (ent < nb ? ent : nb) + ent / l.members + rw / 2;
     const size_t sparse = 64 * (size_t)dm.topk < nb ? 64 * (size_t)dm.topk : nb;
     size_t cap = 2 * ent / l.members + rw / 2 + sparse / 16;
@@ -116,10 +116,10 @@ static BwdLayout bwd_layout(const Dims &dm) {
     const size_t ent0 = (size_t)64 * 32 * dm.topk, seg0 = (ent0 < nb ? ent0 : nb) + 2 * ent0 / l.members + 33;
     const size_t lists0 = 2 * ((BH * ((words + 63) / 64) + kQueues - 1) / kQueues) * seg0;            // places per queue
     const size_t rest = spill / kQueues + slots * tail + (size_t)9 * t.stride / 16 + 64;
-    const size_t room = (lists0 > rest ? lists0 - rest : 0) / (slots * kSlices >> run);
+    const size_t room = (lists0 > rest ? lists0 - rest : 0) / (slots * kSlices);
     cap = cap < room ? cap : room;
-    t.window = 3 - run;
-    t.cap = (int32_t)(t.shift < 3 ? cap : cap << (t.shift - 3));
+    t.window = t.shift < 3 ? 3 - t.shift : 0;
+    t.cap = (int32_t)(cap << t.shift);
     t.tail = (int32_t)(t.shift < 3 ? tail : tail << (t.shift - 3));
     t.size = (int32_t)t.begin(0, t.n);
     size_t o = 0;

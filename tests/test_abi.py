@@ -227,6 +227,23 @@ def test_backward_validation(lib):
                                         None) == UNSUPPORTED
 
 
+# A buffer that is large enough for a call is so for shorter and for fewer sequences, also where a queue's bins become as many as
+# they may (256: 131072 tokens x 2 heads, 65536 x 4, 2 x 32768 x 4 ..) and hold two slices from there on.
+@pytest.mark.parametrize("topk", [3, 16, 64])
+@pytest.mark.parametrize("G,hkv", [(16, 2), (16, 8), (8, 4), (1, 2)])
+def test_backward_workspace_never_decreases(lib, G, hkv, topk):
+    prm = binding.Params(G * hkv, hkv, topk=topk)
+    size = lambda b, t: binding.workspace_bytes(binding.OP_ATTN_BWD, prm, b, t)
+    lengths = [1, 8, 63, 64, 65, 777, 1024, 1088, 2048, 2112, 4096, 8192, 8256, 16384, 16448, 32768, 32832, 33792, 65536, 65600, 67584,
+               131072, 131136, 135168, 262144, 262208]
+    for b in (1, 2, 3, 8, 33):
+        sizes = [size(b, t) for t in lengths]
+        assert sizes == sorted(sizes), (b, [t for t, x, y in zip(lengths[1:], sizes, sizes[1:]) if y < x])
+    for t in lengths:
+        sizes = [size(b, t) for b in range(1, 70)]
+        assert sizes == sorted(sizes), (t, [b + 2 for b, (x, y) in enumerate(zip(sizes, sizes[1:])) if y < x])
+
+
 def test_decode_step_validation(lib):
     prm, t = good_params(), tensor()
     P, T = ctypes.byref(prm), ctypes.byref(t)
