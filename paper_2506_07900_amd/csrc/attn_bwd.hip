@@ -396,22 +396,21 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
     const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
     const int h = bh % dm.Hkv, b = bh / dm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int L_raw = seqlens[b];
-    const int tile = (dm.max_seqlen + kTok - 1) / kTok - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);   // (see the forward)
-    if (tile < 0) return;                                 // uniform over the workgroup
+    const int L = __builtin_amdgcn_readfirstlane(seq_len(dm, seqlens, b));
+    const int n_tiles = (L + kTok - 1) / kTok, tile = n_tiles - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);   // (see the forward's launch)
     const int t0 = tile * kTok;
-    const int32_t *idx_rows = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
-    const UnionRows<kTok> idx_head(idx_rows, wave == 0 ? min(kTok, dm.max_seqlen - t0) * dm.topk : 0, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    const int L = __builtin_amdgcn_readfirstlane(min(max(L_raw, 0), dm.max_seqlen));
-    if (dm.fill)                                          // rows past the end
+    if (dm.fill) {                                        // rows past the end: this tile's, or those of a tile behind the last
+        const int f0 = tile >= 0 ? t0 : (n_tiles - 1 - tile) * kTok;
         for (int i = threadIdx.x; i < kTok * kG * 16; i += 256) {
-            const int tok = t0 + i / (kG * 16);
+            const int tok = f0 + i / (kG * 16);
             if (tok >= L && tok < dm.max_seqlen)
                 *reinterpret_cast<uint4 *>(dq.ptr + b * dq.sb + (int64_t)tok * dq.st +
                                            (int64_t)(h * kG + i / 16 % kG) * dq.sh + 8 * (i & 15)) = uint4{0u, 0u, 0u, 0u};
         }
-    if (t0 >= L) return;
+    }
+    if (tile < 0) return;                                 // uniform over the workgroup
+    const int32_t *idx_rows = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
+    const UnionRows<kTok> idx_head(idx_rows, wave == 0 ? min(kTok, L - t0) * dm.topk : 0, lane);
     const int b_own = t0 / kBlock;
     const int n = lane & 15, g = lane >> 4;               // MFMA column (token, query head) and 16-lane group
     const int tn = n / kG;

@@ -181,17 +181,19 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
     const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
     const int h = bh % dm.Hkv, b = bh / dm.Hkv;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Tiles are dealt last first.  Waves that work alone count them from the sequence's end; a splitting workgroup counts them from
-    // the capacity, so that it can ask for its rows of block lists before the length has arrived.
+    // Tiles are dealt last first, counted from the sequence's end.  Direct fetches, which are for short buffers, count them from the
+    // capacity: their rows of block lists are asked for before the length has arrived (100 tokens 5.9 -> 5.4 us, 250 10.5 -> 9.9).  In
+    // longer ones the workgroups of the tiles behind the sequence would all start, and wait for both, before the first real one:
+    // 777 tokens in a buffer of 131072, G = 8, 33 us, counted from the capacity 57; in one of their own length, G = 16, 21.6 and 21.5.
     int32_t L = __builtin_amdgcn_readfirstlane(seqlens[b]);
-    if (kSplit == 1) L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int tile = ((kSplit > 1 ? dm.max_seqlen : L) + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
+    if (!kDirect) L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
+    const int last = kDirect ? dm.max_seqlen : L;
+    const int tile = (last + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
     const int t0 = kSplit > 1 ? tile * kTok : (tile * 4 + wave) * kTok;   // this wavefront's first token
     if (tile < 0) return;
     const int32_t *idx_rows = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
-    const UnionRows<kTok> idx_head(idx_rows, kSplit == 1 ? min(kTok, (int)L - t0) * dm.topk :
-                                             wave == 0 ? min(kTok, dm.max_seqlen - t0) * dm.topk : 0, lane);
-    if (kSplit > 1) {
+    const UnionRows<kTok> idx_head(idx_rows, kSplit == 1 || wave == 0 ? min(kTok, last - t0) * dm.topk : 0, lane);
+    if (kDirect) {
         __builtin_amdgcn_sched_barrier(0);
         L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
     }
@@ -737,7 +739,7 @@ size_t attn_prefill_ws_bytes(const Dims &dm) {
 // Workgroups go to the XCDs round-robin by their id.  A sequence's tiles are dealt to the XCDs in runs of kRun, last
 // tile first, counted from the sequence's own length: every XCD gets the same share of every sequence (a batch of
 // unequal lengths leaves no XCD idle: 12289 + 8693 + 5096 + 1500 tokens 1256 -> 700 us from this alone), neighbours,
-// which share blocks, still meet in one L2, and the long rows start first.
+// which share blocks, still meet in one L2, and the long rows start first.  (Direct fetches: from the capacity, see the kernel.)
 
 template <int kG, int kTiles, int kSplit, bool kDirect = false>
 static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,

@@ -29,8 +29,8 @@ struct UnionLds {
         : words(reinterpret_cast<uint32_t *>(p)), prefix(words + 64), list(reinterpret_cast<uint2 *>(p + 512)) {}
 };
 
-// A lane's first entries of the tokens' rows.  A workgroup that lives for a few round trips to memory asks for them before it knows
-// the sequence's length: n_ent are those that lie within the tensor (max_seqlen rows per sequence and head).
+// A lane's first entries of the tokens' rows, asked for before anything else is done.  A workgroup with direct fetches does so before it
+// knows the sequence's length: n_ent are those that lie within the tensor (max_seqlen rows per sequence and head).
 template <int NT>
 struct UnionRows {
     static constexpr int kE = NT >= 4 ? NT / 4 : 1;      // entries per lane kept in registers: top-k 16; more are re-read

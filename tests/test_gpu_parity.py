@@ -1097,6 +1097,43 @@ def test_sparse_attn_beyond_one_l2(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Longer buffers and other sequences beside it change no bit of a sequence's output and dq: where a walk begins and the order of its sums follow the
+# token alone (wavefronts that work alone and that split the list, one and several tokens a tile).  What lies behind the end reads 0.
+@pytest.mark.parametrize("l,others,cap,Hq,Hkv,topk", [
+    (8777, [], 12345, 32, 2, 16), (8777, [9001, 64], 9100, 32, 2, 16), (8450, [300], 20000, 8, 1, 8), (8601, [], 131072, 4, 1, 12),
+    (8300, [8200], 8999, 2, 2, 5), (4100, [500], 131072, 16, 2, 16)])
+def test_results_do_not_depend_on_the_capacity(l, others, cap, Hq, Hkv, topk):
+    print("case capacity", l, others, cap, Hq, Hkv, topk, flush=True)
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    gen = torch.Generator(device="cuda").manual_seed(l)
+    T = (l + 63) // 64 * 64
+    q, do = (torch.randn((1, T, Hq, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((1, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    sl = dev_i32([l])
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, binding.compress_keys(prm, k, sl, T), sl, T)
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)
+    want = out[0, :l], lse[0, :l], binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, sl, T, idx)[0][0, :l]
+
+    def longer(x, axis, fill=0):                           # the sequence among the others, last
+        shape = list(x.shape)
+        shape[0], shape[axis] = len(others) + 1, cap
+        t = torch.full(shape, fill, dtype=x.dtype, device="cuda")
+        for b, n in enumerate(others + [l]):
+            t[b].narrow(axis - 1, 0, n).copy_(x[0].narrow(axis - 1, 0, min(n, T)) if n <= T else
+                                              torch.cat([x[0], x[0]], axis - 1).narrow(axis - 1, 0, n))
+        return t
+
+    q, do, k, v, idx = longer(q, 1), longer(do, 1), longer(k, 2), longer(v, 2), longer(idx, 2, -1)
+    lens = others + [l]
+    out, lse = binding.sparse_attn_prefill(prm, q, k, v, dev_i32(lens), cap, idx)
+    dq = binding.sparse_attn_bwd(prm, q, k, v, out, do, lse, dev_i32(lens), cap, idx)[0]
+    torch.cuda.synchronize()
+    for a, b in zip(want, (out[-1, :l], lse[-1, :l], dq[-1, :l])):
+        assert torch.equal(a, b)
+    for b, n in enumerate(lens):
+        assert not bool(out[b, n:].any()) and not bool(lse[b, n:].any()) and not bool(dq[b, n:].any())
+
+
 def test_sparse_attn_backward_long_capacity():
     # buffers much longer than the sequences: the membership words and the dk / dv sums are laid out by the
     # capacity, the work items cut by 2048-token segments of the sequence; one that ends inside its fifth
