@@ -441,7 +441,7 @@ template <int kQT, int kTW>
 __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, Tensor ck,
                                                              const int32_t *__restrict__ seqlens,
                                                              const float2 *__restrict__ part, int32_t n_part,
-                                                             uint64_t *__restrict__ lists, int32_t list_len) {
+                                                             void *__restrict__ found, int32_t list_len, int32_t pitch) {
     constexpr int kChunk = 64 * kTW, kTiles = 4 * kTW + 1;
     constexpr int kBlocks = 16 * kTW;                 // of a list
     static_assert(kBlocks <= 64 && kQT * kBlocks <= 256, "a lane per block, a query within a wavefront");
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
     }
     __syncthreads();
     // ---- group mean, clamps, 5/4 max-pool: thread (t, jl) takes kernels 4j-1 .. 4j+3 = rs[..][4*jl+15 .. +19]; the list_len
-    // best of a query's kBlocks go to a descending list ----
+    // best of a query's kBlocks go to a descending list, or (list_len = 0) the scores of all of them to the query's row ----
     const int t = tid / kBlocks, jl = tid % kBlocks, L = t < kQT ? row_len(dm, L_all, qi0 + t) : 0;
     if (L >= 1) {
         const int j = blockIdx.x * kBlocks + jl, n_vis = num_kernels(L);
@@ -543,13 +543,17 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
             const float sum = (rs[t][0][c] + rs[t][1][c]) + (rs[t][2][c] + rs[t][3][c]);
             if (jh >= 0 && jh < n_vis) v = fmaxf(v, fminf(fmaxf(sum * (1.f / G), kScoreFloor), kScoreCeil));
         }
+        const int64_t row = ((int64_t)b * dm.n_q + qi0 + t) * dm.Hkv + h;
+        if (list_len == 0) {
+            if (j <= (L - 1) / kBlock) reinterpret_cast<float *>(found)[row * pitch + j] = v;
+            return;                                   // (uniform over the wavefront, and nothing waits below)
+        }
         const RowRange rr(dm, L);
         const uint64_t e = pick_element(v, j, rr.n_init, rr.jc_max);
         words[t][jl] = e;
         __builtin_amdgcn_wave_barrier();              // same wavefront: LDS keeps the order
         const int rank = count_larger(words[t], kBlocks, e);   // no two words are equal
-        const int64_t bv = (int64_t)b * dm.n_q + qi0 + t;
-        if (rank < list_len) lists[((bv * dm.Hkv + h) * gridDim.x + blockIdx.x) * list_len + rank] = e;
+        if (rank < list_len) reinterpret_cast<uint64_t *>(found)[(row * gridDim.x + blockIdx.x) * list_len + rank] = e;
     }
 }
 
@@ -665,7 +669,7 @@ __global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int
 //   2.  the n_pick best threads publish their elements >= tau; rank by counting among those
 //   3.  every wavefront repeats the ranking of the survivors of all of them and orders the selected blocks
 //
-// The elements are the sorted lists, one per 128 blocks (verification: 32), the scoring kernel left.
+// The elements are the sorted lists, one per 128 blocks (verification: 32 or 64), the scoring kernel left, or a row of scores.
 constexpr int kPickThreads = 256, kPickWaves = kPickThreads / 64, kPickMaxVPT = 16;
 // LDS of the top-k, carved out of the kernel's dynamic shared memory (16-byte aligned) so that its size
 // follows the call's top-k instead of the largest one supported.
@@ -687,30 +691,40 @@ static inline size_t pick_shared_bytes(int topk, int vpt) {
     return words * sizeof(uint64_t);
 }
 
-// This thread's kVPT elements of row `row` of the top-k's input, words of the lists.  Every
+// This thread's kVPT elements of row `row` of the top-k's input: words of the lists (kLists) or scores of a row.  Every
 // load goes out before the sequence length is known; what lies past the end is dropped afterwards.
 struct PickInput {
-    const uint64_t *lists;                                // [rows][n_lists][list_len]
+    const void *found;                                    // lists: uint64 [rows][n_lists][list_len]; scores: float [rows][pitch]
     int32_t n_lists, list_len, inv;                       // inv: i / n_lists = (i * inv) >> 20 for i < 4096
     int32_t blocks;                                       // of a list
+    int32_t pitch;
 };
-template <int kVPT>
+template <bool kLists, int kVPT>
 struct PickLoad {
-    uint64_t w[kVPT];
+    uint64_t w[kLists ? kVPT : 1];
+    float r[kLists ? 1 : kVPT];
     __device__ PickLoad(const PickInput &in, int64_t row) {
 #pragma unroll
         for (int s = 0; s < kVPT; ++s) {
             const int i = threadIdx.x + kPickThreads * s;
-            const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;   // entry i / n_lists of list i % n_lists
-            w[s] = in.lists[(row * in.n_lists + list) * in.list_len + min(rank, in.list_len - 1)];
+            if constexpr (kLists) {                       // element i = entry i / n_lists of list i % n_lists
+                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
+                w[s] = reinterpret_cast<const uint64_t *>(in.found)[(row * in.n_lists + list) * in.list_len + min(rank, in.list_len - 1)];
+            } else {
+                r[s] = reinterpret_cast<const float *>(in.found)[row * in.pitch + min(i, in.pitch - 1)];
+            }
         }
     }
-    __device__ void elements(const PickInput &in, int L, uint64_t (&el)[kVPT]) const {
+    __device__ void elements(const PickInput &in, const RowRange &rr, int L, uint64_t (&el)[kVPT]) const {
 #pragma unroll
         for (int s = 0; s < kVPT; ++s) {
             const int i = threadIdx.x + kPickThreads * s;
-            const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
-            el[s] = (rank < in.list_len && list * in.blocks <= (L - 1) / kBlock) ? w[s] : 0ull;   // (later lists were not written)
+            if constexpr (kLists) {
+                const int rank = ((uint32_t)i * (uint32_t)in.inv) >> 20, list = i - rank * in.n_lists;
+                el[s] = (rank < in.list_len && list * in.blocks <= (L - 1) / kBlock) ? w[s] : 0ull;   // (later lists were not written)
+            } else {
+                el[s] = pick_element(r[s], i, rr.n_init, rr.jc_max);
+            }
         }
     }
 };
@@ -812,13 +826,13 @@ __device__ inline int order_row(int *mine, int n_sel, int topk, int32_t *__restr
     return rank;
 }
 
-template <int kVPT>
+template <bool kLists, int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, const int32_t *__restrict__ seqlens,
                                                                     PickInput in, int32_t *__restrict__ block_idx) {
     extern __shared__ __align__(16) unsigned char pick_smem[];
     const PickShared sh(pick_smem, dm.topk, kVPT);
     const int row = blockIdx.x, bv = row / dm.Hkv, h = row - bv * dm.Hkv;
-    const PickLoad<kVPT> load(in, row);
+    const PickLoad<kLists, kVPT> load(in, row);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     int32_t *o = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
@@ -828,7 +842,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, cons
     }
     const RowRange rr(dm, L);
     uint64_t el[kVPT];
-    load.elements(in, L, el);
+    load.elements(in, rr, L, el);
     __shared__ __align__(16) int mine[kPickWaves][64];
     pick_row<kVPT>(rr, el, sh, mine[threadIdx.x >> 6]);
     if (threadIdx.x < 64) order_row(mine[0], rr.n_sel, dm.topk, o);
@@ -1012,7 +1026,7 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
 // entry of the result as it stands, best first; the list's ascending order, which decides where the partial result goes,
 // is worked out while the block's rows are on their way.  Those whose entry is a forced block rank nothing: their rows are on
 // their way while the others rank (32 sequences of 128K: this kernel 12.1 -> 11.7 us, the step 63.6 -> 62.9).
-template <int kVPT>
+template <bool kLists, int kVPT>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                                             const int32_t *__restrict__ seqlens,
                                                                             PickInput in,
@@ -1023,7 +1037,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     extern __shared__ __align__(16) unsigned char pick_smem[];
     const PickShared sh(pick_smem, dm.topk, kVPT);
     const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
-    const PickLoad<kVPT> load(in, (int64_t)bv * dm.Hkv + h);
+    const PickLoad<kLists, kVPT> load(in, (int64_t)bv * dm.Hkv + h);
     const BlockRows rows(k, v, kBlock - 1);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
@@ -1043,7 +1057,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
             }
         } else {
             uint64_t el[kVPT];
-            load.elements(in, L, el);
+            load.elements(in, rr, L, el);
             pick_row<kVPT>(rr, el, sh, mine[wave]);
             n_sel = rr.n_sel;
             if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
@@ -1305,8 +1319,9 @@ static int verify_tiles2(const Dims &dm) {
 
 struct DecodeSelLayout {
     int32_t n_c_cap, n_part, nb_cap;
-    int32_t list_blocks, n_lists, list_len;           // sorted lists of pick words, one per list_blocks blocks
-    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists
+    int32_t list_blocks, n_lists, list_len;           // sorted lists of pick words, one per list_blocks blocks; 0: a row of scores
+    size_t z_bytes, part_bytes, r_bytes;              // z: logits, plain decode only; r: those lists, or rows of nb_cap scores
+    size_t found;                                     // where the lists, or the rows, begin
 };
 static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     DecodeSelLayout l;
@@ -1321,9 +1336,16 @@ static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     l.list_blocks = dm.n_q == 1 ? kListBlocks : 16 * verify_tiles2(dm);
     l.n_lists = max(1, (dm.max_seqlen + kBlock * l.list_blocks - 1) / (kBlock * l.list_blocks));
     l.list_len = min(l.list_blocks, max(1, dm.topk - dm.n_init - dm.n_local));
-    // (verification: no less than a row of scores, which short lists would fit twice)
-    const size_t row = (size_t)l.n_lists * l.list_len * sizeof(uint64_t), scores = dm.n_q == 1 ? 0 : l.nb_cap * sizeof(float);
-    l.r_bytes = align256(rows * dm.Hkv * (row > scores ? row : scores));
+    // Verification: two sets of partials and a row of scores, whatever the lists, so that the scratch grows with the rows alone.  Lists
+    // that take more than the row begin in the second set (the approximate log-sum-exp's alone), or give way to the scores (128K
+    // tokens, 16 drafted, G = 4, top-k 32: 24.9 us by lists, 24.5 by scores; top-k 64 43.1 and 49.5).
+    const size_t lists = rows * dm.Hkv * l.n_lists * l.list_len * sizeof(uint64_t);
+    l.r_bytes = align256(dm.n_q == 1 ? lists : rows * dm.Hkv * l.nb_cap * sizeof(float));
+    l.found = l.z_bytes + 2 * l.part_bytes;
+    if (lists > l.r_bytes) {
+        if (dm.rho == 1 && lists <= l.r_bytes + l.part_bytes) l.found -= l.part_bytes;
+        else l.list_len = 0;
+    }
     return l;
 }
 
@@ -1387,7 +1409,7 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     float *zbuf = reinterpret_cast<float *>(wsb);
     float2 *part = reinterpret_cast<float2 *>(wsb + l.z_bytes);
     float2 *part_c = reinterpret_cast<float2 *>(wsb + l.z_bytes + l.part_bytes);
-    uint64_t *lists = reinterpret_cast<uint64_t *>(wsb + l.z_bytes + 2 * l.part_bytes);
+    void *found = wsb + l.found;
     const int rows = dm.batch * dm.n_q;                              // <= 65535, checked by the C ABI
     const int n_qt = (dm.n_q + kVerifyQT - 1) / kVerifyQT;
     const float2 *part_lse = dm.rho > 1 ? part_c : part;
@@ -1419,34 +1441,41 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     if (dm.n_q == 1)
         hipLaunchKernelGGL(decode_scores_z_kernel, dim3(l.n_lists, dm.Hkv, dm.batch), dim3(576), 0, stream,
                            dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm),
-                           lists, l.list_len);
+                           reinterpret_cast<uint64_t *>(found), l.list_len);
     else
         hipLaunchKernelGGL((l.list_blocks == 64 ? decode_scores_kernel<kVerifyQT, 4> : decode_scores_kernel<kVerifyQT, 2>),
                            dim3(l.n_lists, dm.Hkv, dm.batch * n_qt), dim3(256), 0, stream, dm, q, ck, seqlens, part_lse, l.n_part,
-                           lists, l.list_len);
+                           found, l.list_len, l.nb_cap);
     timing_end(stream);
-    const int n_elements = l.n_lists * l.list_len;
+    const bool lists = l.list_len > 0;
+    const int n_elements = lists ? l.n_lists * l.list_len : (dm.max_seqlen + kBlock - 1) / kBlock;
     const int vpt = (n_elements + kPickThreads - 1) / kPickThreads;
     if (vpt > kPickMaxVPT) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
-    const PickInput in = {lists, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.list_blocks};
+    const PickInput in = {found, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.list_blocks, l.nb_cap};
     if (attend) attend->fused = fuse_units(dm);
     const bool fused = attend && attend->fused;
     timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
-#define INFLLMV2_PICK(VPT)                                                                                              \
+#define INFLLMV2_PICK(LISTS, VPT)                                                                                       \
     do {                                                                                                                \
         if (fused)                                                                                                      \
-            hipLaunchKernelGGL((decode_pick_partial_kernel<VPT>), dim3(dm.topk, dm.Hkv, rows),                          \
+            hipLaunchKernelGGL((decode_pick_partial_kernel<LISTS, VPT>), dim3(dm.topk, dm.Hkv, rows),                   \
                                dim3(kPickThreads), pick_shared_bytes(dm.topk, VPT), stream, dm, q, attend->k,           \
                                attend->v, seqlens, in, attend->tree_mask, block_idx, attend->o_part, attend->ml_part);  \
         else                                                                                                            \
-            hipLaunchKernelGGL((decode_pick_kernel<VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),                      \
+            hipLaunchKernelGGL((decode_pick_kernel<LISTS, VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),               \
                                pick_shared_bytes(dm.topk, VPT), stream, dm, seqlens, in, block_idx);                    \
     } while (0)
-    if (vpt <= 1) INFLLMV2_PICK(1);
-    else if (vpt <= 2) INFLLMV2_PICK(2);
-    else if (vpt <= 4) INFLLMV2_PICK(4);
-    else if (vpt <= 8) INFLLMV2_PICK(8);
-    else INFLLMV2_PICK(16);
+    if (lists) {
+        if (vpt <= 1) INFLLMV2_PICK(true, 1);
+        else if (vpt <= 2) INFLLMV2_PICK(true, 2);
+        else if (vpt <= 4) INFLLMV2_PICK(true, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(true, 8);
+        else INFLLMV2_PICK(true, 16);
+    } else {
+        if (vpt <= 4) INFLLMV2_PICK(false, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(false, 8);
+        else INFLLMV2_PICK(false, 16);
+    }
 #undef INFLLMV2_PICK
     timing_end(stream);
     return (int)hipGetLastError();

@@ -199,6 +199,23 @@ def test_verify_validation(lib):
     assert lib.infllmv2_append_kv_verify(P, T, T, T, T, None, FAKE, 0, 4096, 4, None) == 0
 
 
+# The selection's scratch for drafts is two sets of partials and a row of scores, whatever the top-k and the form of the hand-over: no
+# draft, batch or capacity asks for more than a larger one.
+@pytest.mark.parametrize("topk", [3, 16, 19, 20, 24, 35, 36, 48, 64])
+@pytest.mark.parametrize("hq,hkv", [(32, 2), (4, 1), (2, 2)])
+def test_verify_scratch_is_linear_in_the_rows(lib, hq, hkv, topk):
+    prm = binding.Params(hq, hkv, topk=topk)
+    up = lambda x: (x + 255) // 256 * 256
+    for T in (100, 4096, 32768, 74752, 131072, 262144):
+        parts = max(256, (binding.num_kernels(T, prm) + 255) // 256 * 256) // 128
+        for b, n in [(b, n) for b in (1, 2, 4, 16) for n in (2, 3, 4, 12, 13, 28, 29, 33, 61, 64)]:
+            rows = b * n
+            want = 2 * up(rows * hq * parts * 8) + up(rows * hkv * ((T + 4095) // 4096 * 64) * 4)
+            assert binding.verify_workspace_bytes(binding.OP_SELECT_VERIFY, prm, b, T, n) == want, (T, b, n)
+            assert binding.verify_workspace_bytes(binding.OP_VERIFY_STEP, prm, b, T, n) == \
+                want + binding.verify_workspace_bytes(binding.OP_ATTN_VERIFY, prm, b, T, n)
+
+
 # (batch, max_seqlen, key-value heads, top-k, group size): bytes
 FORMER_BACKWARD_BYTES = {
     (1, 64, 1, 3, 1): 109824, (1, 777, 2, 8, 16): 2828032, (2, 1969, 3, 3, 2): 18446336, (33, 200, 2, 4, 1): 22374912,

@@ -891,6 +891,16 @@ def test_verify_select_and_attn(seqlens, n, Hq, Hkv, topk, kind):
         assert eo <= OUT_TOL and el <= 1.0
 
 
+# The two forms in which the scoring workgroups hand on what they found, on either side of their line (lists that fit the scratch of the rows'
+# scores and the second partials, or those scores): 26 | 27 picks beside the forced blocks for lists of 32, 40 | 41 for the lists of 64
+# that a larger call has; G = 16, whose lists always fit.
+@pytest.mark.parametrize("seqlens,n,Hq,Hkv,topk", [
+    ([4500, 2100], 5, 4, 1, 29), ([4500, 2100], 5, 4, 1, 30), ([4500, 4160], 64, 16, 4, 43), ([4500, 4160], 64, 16, 4, 44),
+    ([8300, 4100], 3, 4, 1, 64), ([8300, 4100], 6, 32, 2, 64)])
+def test_verify_selection_lists_and_rows(seqlens, n, Hq, Hkv, topk):
+    test_verify_select_and_attn(seqlens, n, Hq, Hkv, topk, "tree")
+
+
 def test_verify_append_writes_rows_and_completed_kernels():
     print("case verify append", flush=True)
     Hkv, n = 2, 12
