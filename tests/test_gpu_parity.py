@@ -965,7 +965,7 @@ def test_verify_step_equals_its_parts(seqlens, n, Hq, Hkv, topk, rho):
     ([300, 64, 63, 1, 0], 4, 2, 4, 0),  # G = 2, tiny and empty sequences
     ([450], 2, 2, 5, 2),             # G = 1
     ([1500], 16, 1, 32, 5),          # everything selected: dense causal attention
-    ([2500], 32, 2, 8, 4),           # two 2048-token segments per block row
+    ([2500], 32, 2, 8, 4),           # blocks whose members make many work items
 ])
 def test_sparse_attn_backward(seqlens, Hq, Hkv, topk, planted):
     print("case attn backward", seqlens, Hq, Hkv, topk, flush=True)
@@ -1146,9 +1146,9 @@ def test_results_do_not_depend_on_the_capacity(l, others, cap, Hq, Hkv, topk):
 
 def test_sparse_attn_backward_long_capacity():
     # buffers much longer than the sequences: the membership words and the dk / dv sums are laid out by the
-    # capacity, the work items cut by 2048-token segments of the sequence; one that ends inside its fifth
-    # segment and one inside its third, the rest of the capacity unused
-    seqlens, Hq, Hkv, topk, cap = [9000, 4200], 16, 1, 8, 66000
+    # capacity, the work items cut by 8192-token segments of the sequence; one that ends inside its third
+    # segment and one just past its first, the rest of the capacity unused
+    seqlens, Hq, Hkv, topk, cap = [20000, 8300], 16, 1, 8, 66000
     prm = binding.Params(Hq, Hkv, topk=topk)
     oprm = oracle_params(prm)
     q, k, v, T = make_batch(57, seqlens, Hq, Hkv, n_planted=4)
