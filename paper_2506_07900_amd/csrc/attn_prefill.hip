@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
                 }
                 if (g == 0 && wave == 0)
                     lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * kG + n % kG] =
-                        l_tot > 0.f ? (fast_log2(l_tot) + M) * kLn2 : -INFINITY;
+                        l_tot > 0.f ? lse_of(M, l_tot) : -INFINITY;
             }
         }
         if (kTPT == 1 || pass == kTPT) return;
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
         }
         if (g == 0)
             lse[((int64_t)b * dm.max_seqlen + tok) * dm.Hq + h * kG + n % kG] =
-                l_tot > 0.f ? (fast_log2(l_tot) - neg_m[u]) * kLn2 : -INFINITY;
+                l_tot > 0.f ? lse_of(-neg_m[u], l_tot) : -INFINITY;
     }
     return;
     }

@@ -1144,6 +1144,32 @@ def test_results_do_not_depend_on_the_capacity(l, others, cap, Hq, Hkv, topk):
         assert not bool(out[b, n:].any()) and not bool(lse[b, n:].any()) and not bool(dq[b, n:].any())
 
 
+# The log-sum-exps against 64 bits: no more than the rounding of the results themselves (0.29 units in the last place, root mean square) and as much
+# again for the sums; walks from the first block and, from 8192 tokens on, from inside the list; every form of the kernel.
+@pytest.mark.parametrize("T,Hq,Hkv,topk", [(777, 32, 2, 8), (3000, 16, 1, 16), (12000, 32, 2, 16), (9000, 16, 2, 16), (9000, 4, 1, 12), (9000, 2, 2, 8)])
+def test_log_sum_exps_are_as_near_as_fp32_allows(T, Hq, Hkv, topk):
+    print("case lse", T, Hq, Hkv, topk, flush=True)
+    prm, G = binding.Params(Hq, Hkv, topk=topk), Hq // Hkv
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    q = torch.randn((1, T, Hq, 128), device="cuda", generator=gen).bfloat16()
+    k, v = (torch.randn((1, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    u = q[0].float().mean(0).reshape(Hkv, G, 128).mean(1)
+    for j in range(2, T // 64 - 3, 16):                    # some blocks of keys along the mean query
+        k[0, :, 64 * j:64 * j + 64] = (128 ** 0.5 * (u / u.norm(dim=-1, keepdim=True))[:, None] + 0.1 * k[0, :, 64 * j:64 * j + 64]).bfloat16()
+    sl = dev_i32([T])
+    idx = binding.select_blocks(prm, binding.MODE_PREFILL, q, binding.compress_keys(prm, k, sl, T), sl, T)
+    lse = binding.sparse_attn_prefill(prm, q, k, v, sl, T, idx)[1][0].double()
+    err = []
+    for t in range(T // 3, T, T // 150):
+        for h in range(Hkv):
+            b = idx[0, h, t][idx[0, h, t] >= 0].long()
+            rows = (b[:, None] * 64 + torch.arange(64, device="cuda")).reshape(-1)
+            z = q[0, t, h * G:(h + 1) * G].double() @ k[0, h, rows[rows <= t]].double().T * 128 ** -0.5
+            want = torch.logsumexp(z, -1)
+            err.append((lse[t, h * G:(h + 1) * G] - want) / torch.exp2(torch.floor(torch.log2(want)) - 23))
+    assert float(torch.cat(err).square().mean().sqrt()) <= 0.58
+
+
 def test_sparse_attn_backward_long_capacity():
     # buffers much longer than the sequences: the membership words and the dk / dv sums are laid out by the
     # capacity, the work items cut by 8192-token segments of the sequence; one that ends inside its third
