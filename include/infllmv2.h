@@ -342,8 +342,10 @@ int32_t infllmv2_decode_step(const infllmv2_params *prm, const infllmv2_tensor *
  *                               arithmetic as in infllmv2_sparse_attn_decode.
  * infllmv2_verify_step          the three calls in one (ck required), four launches instead of six
  *                               (the top-k is folded into the per-block attention kernel unless
- *                               batch * n_draft * Hkv * topk exceeds 1024); the same caches, ck,
- *                               block_idx, out and lse bit for bit.
+ *                               batch * n_draft * Hkv * topk exceeds 1024, the append into the first
+ *                               selection kernel unless lse_coarse_ratio > 1 or n_draft == 1: one
+ *                               launch more each); the same caches, ck, block_idx, out and lse bit
+ *                               for bit.
  * Workspaces: infllmv2_verify_workspace_bytes(INFLLMV2_OP_SELECT_VERIFY / _ATTN_VERIFY /
  * _VERIFY_STEP, ...) (0 if the arguments are invalid), 256-byte aligned.
  */
