@@ -111,11 +111,12 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
 //
 // What bounds it: no unit on its own.  At 32K tokens (2 heads, G = 16, top-k 16) the matrix pipe is busy 32 % of the time, vector
 // arithmetic 34 %, and 32 % of the wavefronts' time is waits: inside a wavefront a tile's products and its exponentials follow
-// one another (11 % of the matrix time runs under vector work).  Leaving parts out, of 0.79 ms (with the events around the
-// launch): the loads alone 0.69, all but the loads 0.52, the matrix products alone 0.43; without the exponentials 0.74, without
-// the value product 0.72, without misses (32 blocks in all) 0.73.  The loads are 16.6 GB (2.7 GB of them past L2), 0.46 ms at the
+// one another (11 % of the matrix time runs under vector work).  It takes 0.73 ms back to back (0.75 with events around
+// every launch).  Leaving parts out was measured when it took 0.79, with 2.7 GB past L2, before walks began where the others are (1.9 GB):
+// the loads alone 0.69, all but the loads 0.52, the matrix products alone 0.43; without the exponentials 0.74, without
+// the value product 0.72, without misses (32 blocks in all) 0.73.  The loads are 16.6 GB, 0.46 ms at the
 // 36 TB/s that a kernel of nothing but fragment loads reaches; here they run at 24 - 28, with two, four or eight units of 4 KiB per
-// wavefront under way.  (Walks that begin where the others are have since made that 0.77 ms and 1.9 GB.)
+// wavefront under way.
 // The union of two tokens has 24 blocks, of four 33: four tokens per wavefront, their queries in LDS so that the accumulators
 // (128 registers) and a ring of four units fit 256 registers, load 16.6 GB instead of 22.5: 1.00 -> 0.78 ms.
 //
@@ -760,13 +761,15 @@ static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, con
 }
 
 // How many tiles a wavefront takes and whether the waves of a workgroup share their tokens, by how many workgroups the
-// call fills (two fit a compute unit: 512 fill the chip).  More tiles per wavefront mean fewer bytes per token, since
+// call fills (two fit a compute unit, of two tiles at G = 16 three: 512 or 768 fill the chip).  More tiles per wavefront mean fewer bytes per token, since
 // a fetched block serves every token that selected it; splitting the blocks over four waves makes four times as many
 // waves out of few tokens.  Measured over 150 .. 32768 tokens, 2 key-value heads, top-k 16 (us, start -> now):
 //   G = 16: 150 17 -> 9, 1500 56 -> 36, 4096 128 -> 97, 32768 1024 -> 775;  G = 4: 777 31 -> 15, 4096 123 -> 57,
 //   32768 1148 -> 755;  G = 1: 777 31 -> 12, 4096 124 -> 38, 32768 1339 -> 534
-// The lines: four tiles, split, from 512 workgroups on (at 390 .. 750 it meets two tiles for every G); two tiles, split,
-// from 192 (at 190 it meets one tile); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
+// The lines: four tiles, split, from 512 workgroups on (at 390 .. 750 it met two tiles for every G; with three workgroups of two tiles
+// on a compute unit, G = 16, two heads, two / four tiles: 1040 tokens 27.1 / 27.7, 1280 34.4 / 29.8, 1500 42.4 / 35.5; one head, 2100 31.6 / 30.0); two tiles,
+// split, from 192 (at 190 it met one tile, with packed blocks; against direct fetches two tiles come too early there: G = 16, one tile / two, with
+// the packing, 200 tokens x 2 heads 7.2 / 9.5, 280 9.2 / 11.2); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
 // only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
 template <int kG>
 static int launch_attn_group(const Dims &dm, Tensor q, Tensor k, Tensor v, bool direct, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,

@@ -304,7 +304,7 @@ __device__ inline uint32_t row_reduce_u32(uint32_t x, F f) {
 // 130 a row (kP = 1) instead of 430.  A few lanes' largest elements give a threshold that n_pick of them reach: the n_pick-th
 // of the 16 lanes' (of 512 random scores 26 reach it for 13 picks; beyond 14 it says too little), or, by bisection, about that of the
 // 64 quarter lanes'; counting over the elements that reach it gives the order.  Ranking a row's chunk 4500 -> 2000 cycles;
-// selection, top-k 16, G = 16: 5000 tokens 64 -> 55 us, 32K 613 -> 579; G = 8: 8192 118 -> 75, 32K 925 -> 590; G = 1: 16000 176 -> 109.
+// selection, top-k 16, G = 16: 5000 tokens 64 -> 55 us, 32K 613 -> 579; G = 8: 8192 118 -> 75, 32K 925 -> 585; G = 1: 16000 176 -> 108.
 constexpr int kGroupPicks = 32;
 inline int pick_form(const Dims &dm) { return dm.topk - dm.n_init - dm.n_local <= 14 ? 1 : 2; }   // kP; a row has no more picks
 template <int kE, int kP>
