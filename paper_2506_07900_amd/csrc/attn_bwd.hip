@@ -39,13 +39,16 @@ constexpr int kBins = 256;                            // at most, of a queue
 constexpr int kCounterLine = 32;
 constexpr uint32_t kBehind = 1u << 31;                // in a queue's place drawn last: there are items behind the queues
 
-// Members of an item, in steps of 32 (token, head) rows: an equal share for each of the chip's kDkdvGroups workgroups of what the call
-// would be if every sequence were as long as this one, within 12 (G = 16: 8) .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic
+// Members of an item, in steps of 32 (token, head) rows: an equal share of the call for each of the chip's kDkdvGroups workgroups,
+// within 12 (G = 16: 8) .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic
 // sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us with at least 8 / 16 / 32 steps; 1000 tokens, G = 4 would take
 // 31 / 43 / 62); above, the last items keep the others waiting (32K tokens, G = 16: 1190 / 1310 us with at most 64 / 256).  An
 // item ends with a whole word of 32 tokens, which may exceed its share by G steps: G = 16, 777 tokens 55 us with at least 12, 51.6 with
-// 8.  A share of the capacity instead of the sequence leaves most of the chip idle: 777 tokens in a buffer of 2000, top-k 8, 65 us, so
-// 52; in one of 4096, top-k 16, 112 and 54.
+// 8.  A share of the capacity instead of the call's tokens leaves most of the chip idle: 777 tokens in a buffer of 2000, top-k 8, 65 us, so
+// 52; in one of 4096, top-k 16, 112 and 54.  So does one that takes all sequences for as long as the item's own: with the cutting, G = 8,
+// 300 + 100 + 900 + 64 tokens 77 us, so 56; G = 16, 1500 + 200 + 800 129 and 100.  From 96 on a share is rounded up to whole words (see
+// bwd_items_kernel): blocks that every token selects are then cut evenly, G = 8, 5000 + 700 tokens, 136 -> 160 members, 129 -> 111 us,
+// 4096 + 3333, 236 -> 256, 168 -> 162.  Smaller ones grow too much by it: 1500 + 200 + 800, 80 -> 96, 100 -> 112.
 constexpr int kDkdvGroups = 256 * 4;
 constexpr int kShareRows = 32 * kDkdvGroups;
 constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
@@ -53,13 +56,14 @@ __host__ __device__ inline int32_t item_members(int64_t steps, int G) {
     const int least = G == 16 ? 8 : 12, m = (int)(steps < least ? least : steps > 64 ? 64 : steps) * 32 / G;
     return m > kMaxMembers - 32 ? kMaxMembers - 32 : m;
 }
-// rows of (token, head) per token of such a call
-static inline int64_t share_per_token(const Dims &dm) { return (int64_t)dm.batch * dm.Hkv * dm.topk * dm.G; }
+// rows of (token, head) per block of 64 tokens
+static inline int64_t rows_per_block(const Dims &dm) { return (int64_t)kBlock * dm.Hkv * dm.topk * dm.G; }
 
 // Where items lie and what an item says.  A queue has n bins of `cap` places, the last bin of a window `tail` more; what finds its bin
 // full goes to one list behind the queues, taken when they are empty, which has room for every item of the call.  Counters, of a
-// queue and then of that list: the bins' lengths, then, on a line of its own, the place drawn last.  (That the list has items is told
-// with the places: every workgroup's look at its length is one address for the chip, 3.5 of 35 us for 500 tokens.)
+// queue and then of that list: the bins' lengths, then, on a line of its own, the place drawn last; on the list's also the call's
+// blocks, in four words to be added.  (That the list has items is told with the places: every workgroup's look at its length is one
+// address for the chip, 3.5 of 35 us for 500 tokens.)
 struct BwdBins {
     int32_t n, shift;                                 // bins of a queue; slices of a bin (log2)
     int32_t cap, tail, window;                        // a window's bins (log2)
@@ -81,7 +85,7 @@ struct BwdBins {
 };
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
-    int32_t members;                                  // of an item of the longest sequence that fits
+    int32_t members;                                  // of an item of the largest call that fits, before it is rounded up to whole words
     BwdBins bins;
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
@@ -92,7 +96,7 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
-    l.members = item_members((int64_t)l.nb_cap * kBlock * share_per_token(dm) / kShareRows, dm.G);
+    l.members = item_members(dm.batch * (int64_t)l.nb_cap * rows_per_block(dm) / kShareRows, dm.G);
     const size_t nb = (size_t)l.nb_cap, words = (size_t)l.words, windows = BH * ((words + kWindowWords - 1) / kWindowWords);
     const size_t slots = windows ? (windows + kQueues - 1) / kQueues : 1;       // windows of a queue
     BwdBins &t = l.bins;
@@ -102,7 +106,7 @@ static BwdLayout bwd_layout(const Dims &dm) {
     t.stride = (t.n + kCounterLine - 1) / kCounterLine * kCounterLine + kCounterLine;
     t.block_bits = 1;
     while (nb >> t.block_bits) ++t.block_bits;
-    // Items that end in a slice: at most one per `members` list entries (a shorter sequence has smaller items, not more of them), one more per block with an entry (begun before) and the
+    // Items that end in a slice: at most one per `members` list entries (a smaller call has smaller items, not more of them), one more per block with an entry (begun before) and the
     // own tokens' of its blocks.  That every block's ends there is provided for in the list behind; a bin has room for twice the mean
     // and, blocks that are equally popular being cut at about the same tokens, a sixteenth of the blocks.  (Bins for the worst case
     // took 4.9 MB for 32K tokens x 2 heads, top-k 16, and 76 MB for 128K; these 0.4 and 3.0.)  A bin of several
@@ -116,10 +120,10 @@ static BwdLayout bwd_layout(const Dims &dm) {
     // what is left of the blocks at the segments' ends: to the last slices of all windows alike
     const size_t seg_ent = (words < (size_t)kSegWords ? words : (size_t)kSegWords) * 32 * topk;
     const size_t tails = BH * l.n_seg * (seg_ent < nb ? seg_ent : nb), tail = (tails + slots * kQueues - 1) / (slots * kQueues);
-    const size_t spill = BH * (words * 32 * topk / l.members + nb) + tails;
+    const size_t spill = BH * words * 32 * topk / l.members + BH * nb + tails;   // (one long sequence may have more than its part of the first)
     // Never more than a list per queue took when segments had 2048 tokens, an item 16 bytes and at least 12 steps: buffers of that size stay
     // large enough.
-    const int64_t steps0 = (int64_t)T * share_per_token(dm) / kShareRows;
+    const int64_t steps0 = dm.batch * (int64_t)T * (rows_per_block(dm) / kBlock) / kShareRows;
     const size_t members0 = (size_t)(steps0 < 12 ? 12 : steps0 > 64 ? 64 : steps0) * 32 / dm.G;
     const size_t ent0 = (size_t)64 * 32 * dm.topk, seg0 = (ent0 < nb ? ent0 : nb) + 2 * ent0 / (members0 < 1024 ? members0 : 1024) + 33;
     const size_t lists0 = 2 * ((BH * ((words + 63) / 64) + kQueues - 1) / kQueues) * seg0;            // places per queue
@@ -165,7 +169,12 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
     const int L = seq_len(dm, seqlens, b);
     const int tid = threadIdx.x;
     if ((j | h | b) == 0) {
-        for (int i = tid; i < n_counters; i += 256) counters[i] = 0u;
+        int blocks = 0;                                   // of the call, a word per wavefront
+        for (int i = tid; i < dm.batch; i += 256) blocks += (seq_len(dm, seqlens, i) + kBlock - 1) / kBlock;
+        blocks = wave_inclusive_sum(blocks);
+        for (int i = tid; i < n_counters; i += 256)
+            if (i < n_counters - kCounterLine + 4 || i >= n_counters - kCounterLine + 8) counters[i] = 0u;
+        if ((tid & 63) == 63) counters[n_counters - kCounterLine + 4 + (tid >> 6)] = (uint32_t)blocks;
         if (tid < 32) null_row[tid] = tid < 16 ? -INFINITY : 0.f;       // the constants of a row that is not there: p = 0
     }
     if (j * kBlock >= L) return;
@@ -239,17 +248,18 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
 // queues empty: 1125 -> 1110.
 constexpr int kItemBlocks = 4;
 __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
-                                                         int32_t nb_cap, int32_t n_seg, int64_t share, BwdBins bins,
+                                                         int32_t nb_cap, int32_t n_seg, int64_t rows_per_block, BwdBins bins,
                                                          uint32_t *__restrict__ counters, uint64_t *__restrict__ items) {
     static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8 && kSlices == 8, "four words a lane, eight lanes a window, one a slice");
     // (the arguments arrive together, not one round trip after another where each is first used)
     asm volatile("" : "+s"(bins.shift), "+s"(bins.cap), "+s"(bins.tail), "+s"(bins.window), "+s"(bins.size), "+s"(bins.stride),
-                 "+s"(bins.block_bits), "+s"(share), "+s"(counters), "+s"(items));
+                 "+s"(bins.block_bits), "+s"(rows_per_block), "+s"(counters), "+s"(items));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int seg = blockIdx.x % n_seg, j0 = (int)(blockIdx.x / n_seg * 4 + wave) * kItemBlocks;
     const int h = blockIdx.y, b = blockIdx.z;
     const int64_t bh = (int64_t)b * dm.Hkv + h;
     const int L = seq_len(dm, seqlens, b);
+    const uint4 blocks = *reinterpret_cast<const uint4 *>(counters + (kQueues + 1) * bins.stride - kCounterLine + 4);
     const int w0 = seg * kSegWords, w1 = min(w0 + kSegWords, (L + 31) / 32);   // block j's tokens start at word 2j
     if (w0 >= w1 || 2 * j0 >= w1) return;
     const int at = w0 + 4 * lane;                         // this lane's words
@@ -259,8 +269,10 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
     for (int i = 0; i < kItemBlocks; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
-    // (rounded up: with the capacity's share rounded down, no call has more items than the longest that fits)
-    const float inv = 1.f / (float)item_members(((int64_t)((L + kBlock - 1) / kBlock * kBlock) * share + kShareRows - 1) / kShareRows, dm.G);
+    // (rounded up: with the capacity's share rounded down, no call has more items than the largest that fits)
+    const int64_t rows = (int64_t)__builtin_amdgcn_readfirstlane(blocks.x + blocks.y + blocks.z + blocks.w) * rows_per_block;
+    const int share = item_members((rows + kShareRows - 1) / kShareRows, dm.G);
+    const float inv = 1.f / (float)(share >= 96 ? min((share + 31) / 32 * 32, kMaxMembers - 32) : share);
     // Windows are numbered through all sequences and heads of the capacity, eight to the queues' next slices; a sequence's are dealt to the
     // queues round robin by its own length (by the capacity's, short sequences in long buffers meet in one queue: 1000 tokens of 8000,
     // 2 heads, G = 16, top-k 8: dk/dv 121 us, so 115; one of 16384 and three short ones 677, so 667).
@@ -1055,7 +1067,7 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     timing_end(stream);
     timing_begin("bwd_items_kernel", stream);
     hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)(l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks))), dm.Hkv, dm.batch),
-                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, share_per_token(dm), l.bins, counters, items);
+                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, rows_per_block(dm), l.bins, counters, items);
     timing_end(stream);
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;

@@ -1073,6 +1073,14 @@ def test_sparse_attn_backward_items(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Items sized by the tokens of the whole call: more sequences than the workgroup that counts them has threads, and one long one among
+# short and empty ones, which then has more than its part of the items (whole words of 32 tokens, and less than that).
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([90 - i % 90 for i in range(300)], 4, 1, 3), ([3000] + [40, 0] * 6, 16, 1, 12),
+                                                 ([2100, 70, 0, 500, 1], 16, 2, 16)])
+def test_sparse_attn_backward_items_of_ragged_batches(seqlens, Hq, Hkv, topk):
+    test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
+
+
 # Lists in which all blocks are equally popular, so that their items end at the same tokens: more than a bin holds (47 of 1125 items, 42 of
 # 462, where a bin has three places and a window's tails), the rest from the list behind the queues.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([10000], 2, 1, 16), ([1969, 1969], 6, 3, 3)])
