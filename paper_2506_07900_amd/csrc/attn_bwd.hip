@@ -40,7 +40,8 @@ constexpr int kCounterLine = 32;
 constexpr uint32_t kBehind = 1u << 31;                // in a queue's place drawn last: there are items behind the queues
 
 // Members of an item, in steps of 32 (token, head) rows: an equal share of the call for each of the chip's kDkdvGroups workgroups,
-// within 12 (G = 16: 8) .. 64.  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic
+// within 12 (G = 16: 8) .. 64; a larger share in equal parts of at most 64 (all in items of 64, most workgroups wait for those that have one
+// more: 9000 tokens, G = 4, top-k 48, 300 -> 287 us, 6000, G = 16, 250 -> 236).  Below, the fixed part (32 KiB of K and V, 64 KiB of atomic
 // sums) is most of an item (8192 tokens, G = 1: 92 / 72 / 80 us with at least 8 / 16 / 32 steps; 1000 tokens, G = 4 would take
 // 31 / 43 / 62); above, the last items keep the others waiting (32K tokens, G = 16: 1190 / 1310 us with at most 64 / 256).  An
 // item ends with a whole word of 32 tokens, which may exceed its share by G steps: G = 16, 777 tokens 55 us with at least 12, 51.6 with
@@ -52,9 +53,17 @@ constexpr uint32_t kBehind = 1u << 31;                // in a queue's place draw
 constexpr int kDkdvGroups = 256 * 4;
 constexpr int kShareRows = 32 * kDkdvGroups;
 constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
-__host__ __device__ inline int32_t item_members(int64_t steps, int G) {
-    const int least = G == 16 ? 8 : 12, m = (int)(steps < least ? least : steps > 64 ? 64 : steps) * 32 / G;
+constexpr int kMostSteps = 64;
+__host__ __device__ constexpr int least_steps(int G) { return G == 16 ? 8 : 12; }
+__host__ __device__ inline int members_of(int steps, int G) {
+    const int m = (steps < least_steps(G) ? least_steps(G) : steps) * 32 / G;
     return m > kMaxMembers - 32 ? kMaxMembers - 32 : m;
+}
+__host__ __device__ inline int share_rounds(int share) { return share > kMostSteps ? (share + kMostSteps - 1) / kMostSteps : 1; }
+// steps of a workgroup's share of a call with so many rows (beyond 4096 it is cut into items of kMostSteps either way)
+__host__ __device__ inline int share_steps(int64_t rows) {
+    const int64_t s = (rows + kShareRows - 1) / kShareRows;
+    return (int)(s < 4096 ? s : 4096);
 }
 // rows of (token, head) per block of 64 tokens
 static inline int64_t rows_per_block(const Dims &dm) { return (int64_t)kBlock * dm.Hkv * dm.topk * dm.G; }
@@ -85,7 +94,7 @@ struct BwdBins {
 };
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
-    int32_t members;                                  // of an item of the largest call that fits, before it is rounded up to whole words
+    int32_t members;                                  // of an item, about: what the bins are laid out for
     BwdBins bins;
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
@@ -96,7 +105,8 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.nb_cap = (dm.max_seqlen + kBlock - 1) / kBlock;
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
-    l.members = item_members(dm.batch * (int64_t)l.nb_cap * rows_per_block(dm) / kShareRows, dm.G);
+    const int64_t rows = dm.batch * (int64_t)l.nb_cap * rows_per_block(dm);
+    l.members = members_of((int)(rows / kShareRows < kMostSteps ? rows / kShareRows : kMostSteps), dm.G);
     const size_t nb = (size_t)l.nb_cap, words = (size_t)l.words, windows = BH * ((words + kWindowWords - 1) / kWindowWords);
     const size_t slots = windows ? (windows + kQueues - 1) / kQueues : 1;       // windows of a queue
     BwdBins &t = l.bins;
@@ -120,7 +130,13 @@ static BwdLayout bwd_layout(const Dims &dm) {
     // what is left of the blocks at the segments' ends: to the last slices of all windows alike
     const size_t seg_ent = (words < (size_t)kSegWords ? words : (size_t)kSegWords) * 32 * topk;
     const size_t tails = BH * l.n_seg * (seg_ent < nb ? seg_ent : nb), tail = (tails + slots * kQueues - 1) / (slots * kQueues);
-    const size_t spill = BH * words * 32 * topk / l.members + BH * nb + tails;   // (one long sequence may have more than its part of the first)
+    // The most items that a call of up to so many rows has where `members` are full, all sequences together (one of them may have more than its
+    // part): a share's parts make kDkdvGroups x rounds, but no item is smaller than the least and, of the largest, each is full.
+    const size_t entries = BH * words * 32 * topk;
+    const size_t parts = (size_t)kDkdvGroups * share_rounds(share_steps(rows)), by_least = entries / members_of(0, dm.G);
+    const size_t by_most = entries / members_of(kMostSteps, dm.G), some = parts < by_least ? parts : by_least;
+    const size_t full = some > by_most ? some : by_most;
+    const size_t spill = full + BH * nb + tails;
     // Never more than a list per queue took when segments had 2048 tokens, an item 16 bytes and at least 12 steps: buffers of that size stay
     // large enough.
     const int64_t steps0 = dm.batch * (int64_t)T * (rows_per_block(dm) / kBlock) / kShareRows;
@@ -269,10 +285,9 @@ __global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *
     for (int i = 0; i < kItemBlocks; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
-    // (rounded up: with the capacity's share rounded down, no call has more items than the largest that fits)
     const int64_t rows = (int64_t)__builtin_amdgcn_readfirstlane(blocks.x + blocks.y + blocks.z + blocks.w) * rows_per_block;
-    const int share = item_members((rows + kShareRows - 1) / kShareRows, dm.G);
-    const float inv = 1.f / (float)(share >= 96 ? min((share + 31) / 32 * 32, kMaxMembers - 32) : share);
+    const int share = share_steps(rows), rounds = share_rounds(share), m = members_of((share + rounds - 1) / rounds, dm.G);
+    const float inv = 1.f / (float)(m >= 96 ? min((m + 31) / 32 * 32, kMaxMembers - 32) : m);
     // Windows are numbered through all sequences and heads of the capacity, eight to the queues' next slices; a sequence's are dealt to the
     // queues round robin by its own length (by the capacity's, short sequences in long buffers meet in one queue: 1000 tokens of 8000,
     // 2 heads, G = 16, top-k 8: dk/dv 121 us, so 115; one of 16384 and three short ones 677, so 667).
