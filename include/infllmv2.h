@@ -216,8 +216,9 @@ int32_t infllmv2_sparse_attn_prefill(const infllmv2_params *prm, const infllmv2_
  * (sums for dk, dv over the tokens that selected t's block and the query heads of the group).
  * bf16 products accumulated in fp32; p and ds are rounded to bf16 before the second products;
  * dk, dv are merged with fp32 atomic adds, one per work item of a block: the tokens that selected it are cut into items of
- * 12 (short sequences) to 64 steps of 32 (token, head) rows, at G = 16 24 to 128 tokens.  The items' order is not fixed, so
- * dk and dv of a block with more than two of them can differ from run to run in the last bits of the fp32 sum.  dq repeats.
+ * about 12 (short sequences; G = 16: 8) to 64 steps of 32 (token, head) rows, at G = 16 16 to 128 tokens, each up to the end of a word
+ * of 32 tokens.  The items' order is not fixed, so dk and dv of a block with more than two of them can differ from run to run in the
+ * last bits of the fp32 sum.  dq repeats.
  *   q, out, dout  in   [batch, max_seqlen, Hq, d] bf16: the forward's input, output and its gradient
  *                      (q, dout: group size x head stride at most 2^30 elements, else INFLLMV2_ERR_UNSUPPORTED)
  *   k, v          in   bf16 caches [batch, Hkv, >=max_seqlen, d]

@@ -1081,6 +1081,12 @@ def test_sparse_attn_backward_items_of_ragged_batches(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Items of an equal part of a share beyond 64 steps: 2 x 35 of 69 (70 members, less than whole words), 2 x 40 of 80 (ten whole words).
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([2100], 32, 2, 33), ([5000], 8, 2, 64)])
+def test_sparse_attn_backward_items_of_large_shares(seqlens, Hq, Hkv, topk):
+    test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
+
+
 # Lists in which all blocks are equally popular, so that their items end at the same tokens: more than a bin holds (47 of 1125 items, 42 of
 # 462, where a bin has three places and a window's tails), the rest from the list behind the queues.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([10000], 2, 1, 16), ([1969, 1969], 6, 3, 3)])
