@@ -52,6 +52,17 @@ struct AttendArgs {      // the per-block attention folded into the top-k kernel
     float2 *ml_part;
 };
 
+// A kernel's arguments, asked for together before anything else is done: left to itself the compiler loads each where it is first used, one
+// round trip to memory after another.
+template <typename A, typename... T>
+__device__ inline void arguments_arrive(const A &a, const T &...x) {
+    if constexpr (sizeof...(x) < 11) arguments_arrive(a, x..., a);
+    else [](const auto &x0, const auto &x1, const auto &x2, const auto &x3, const auto &x4, const auto &x5, const auto &x6, const auto &x7,
+            const auto &x8, const auto &x9, const auto &x10, const auto &x11) __attribute__((always_inline)) {
+        asm volatile("" ::"s"(x0), "s"(x1), "s"(x2), "s"(x3), "s"(x4), "s"(x5), "s"(x6), "s"(x7), "s"(x8), "s"(x9), "s"(x10), "s"(x11));
+    }(a, x...);
+}
+
 // Number of complete semantic kernels of a sequence of l tokens (p=32, s=16).
 __host__ __device__ inline int32_t num_kernels(int32_t l) {
     return l < kKernel ? 0 : (l - kKernel) / kStride + 1;

@@ -1269,42 +1269,54 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
 }
 
 // ---- attention, part 2: merge the k partials of every query head ---------------------------------
-// grid (Hq, B*n_q), 128 threads: thread = channel.  All partial loads are issued before the merge, unconditionally.
-// kTop is the top-k rounded up to 8, 16, 32 or 64 (so entries below kTop / 2 always exist from 16 on); entries past the
-// top-k re-read the last one, and their bits are masked to zero: not weighted with zero (0 * inf), and not by a condition, which
-// the compiler makes a branch around the load (128K context, a step 18.8 -> 19.4 us).
+// grid (Hq, n_q, B), one wavefront: lane = two channels.  kTop is the top-k rounded up to 8, 16, 32 or 64; entries past the top-k lie
+// outside the loads' resources and read 0.
+// Bound by latency: arguments, one round trip for everything the partials say, and a chain of instructions.  So all arguments and
+// all loads are asked for before anything is used and no branch lies between (the compiler sinks a load into the branch that
+// uses it), and a lane works out one entry's weight, which the others read from it.
 template <int kTop>
-__global__ __launch_bounds__(128) void decode_merge_kernel(Dims dm, const float *__restrict__ o_part,
-                                                            const float2 *__restrict__ ml_part, Tensor out,
-                                                            float *__restrict__ lse) {
-    const int hq = blockIdx.x, bv = blockIdx.y, cch = threadIdx.x;
-    const int64_t pbase = ((int64_t)bv * dm.Hq + hq) * dm.topk;
-    constexpr int kSure = kTop > 8 ? kTop / 2 : 1;
-    float2 ml[kTop];
-    float ov[kTop];
+__global__ __launch_bounds__(64) void decode_merge_kernel(Dims dm, const float *__restrict__ o_part,
+                                                           const float2 *__restrict__ ml_part, Tensor out,
+                                                           float *__restrict__ lse) {
+    arguments_arrive(dm.Hq, dm.topk, dm.n_q, o_part, ml_part, out.ptr, out.sb, out.sh, out.st, lse);
+    const int hq = blockIdx.x, qi = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+    const int64_t row = ((int64_t)b * dm.n_q + qi) * dm.Hq + hq, pbase = row * dm.topk;
+    const int mine = lane & (kTop - 1);
+    const auto ml_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(ml_part + pbase), 0, dm.topk * (int)sizeof(float2), 0x00027000);
+    const auto o_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(o_part + pbase * kHeadDim), 0,
+                                                          dm.topk * kHeadDim * (int)sizeof(float), 0x00027000);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 ml2 = __builtin_amdgcn_raw_buffer_load_b64(ml_rows, mine * (int)sizeof(float2), 0, 0);
+    u32x2 ov[kTop];
+#pragma unroll
+    for (int c = 0; c < kTop; ++c)
+        ov[c] = __builtin_amdgcn_raw_buffer_load_b64(o_rows, lane * (int)sizeof(float2) + c * kHeadDim * (int)sizeof(float), 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    const float2 ml = {mine < dm.topk ? __uint_as_float(ml2[0]) : -INFINITY, __uint_as_float(ml2[1])};
+    const auto larger = [](float x, float y) { return fmaxf(x, y); };
+    const auto sum = [](float x, float y) { return x + y; };
+    float M = row_reduce(ml.x, larger);
+    if constexpr (kTop >= 32) M = xgroup_reduce(M, larger);
+    M = M == -INFINITY ? 0.f : M;
+    const float w = fast_exp2(ml.x - M);
+    float den = lane < kTop ? w * ml.y : 0.f;
+    den = row_reduce(den, sum);
+    if constexpr (kTop >= 32) den = xgroup_reduce(den, sum);
+    den = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(den)));
+    float2 num = {0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < kTop; ++c) {
-        const int64_t at = pbase + (c < kSure ? c : min(c, dm.topk - 1));
-        ml[c] = ml_part[at];
-        ov[c] = o_part[at * kHeadDim + cch];
+        const float wc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), c));
+        num.x += wc * __uint_as_float(ov[c][0]);
+        num.y += wc * __uint_as_float(ov[c][1]);
     }
-    const int b = bv / dm.n_q, qi = bv - b * dm.n_q;
-    float M = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < kTop; ++c) M = fmaxf(M, ml[c].x);
-    float num = 0.f, den = 0.f;
-    if (M > -INFINITY) {
-#pragma unroll
-        for (int c = 0; c < kTop; ++c) {
-            const uint32_t keep = c < kSure ? ~0u : (uint32_t)((c - dm.topk) >> 31);
-            const float w = fast_exp2(ml[c].x - M);
-            den += w * __uint_as_float(__float_as_uint(ml[c].y) & keep);
-            num += w * __uint_as_float(__float_as_uint(ov[c]) & keep);
-        }
-    }
-    const float o = den > 0.f ? num / den : 0.f;
-    out.ptr[b * out.sb + qi * out.st + (int64_t)hq * out.sh + cch] = (__bf16)o;
-    if (cch == 0) lse[(int64_t)bv * dm.Hq + hq] = den > 0.f ? (M + fast_log2(den)) * kLn2 : -INFINITY;
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    bf16x2 o;
+    const float inv = 1.f / (den > 0.f ? den : 1.f);
+    o[0] = (__bf16)(den > 0.f ? num.x * inv : 0.f);
+    o[1] = (__bf16)(den > 0.f ? num.y * inv : 0.f);
+    *reinterpret_cast<bf16x2 *>(out.ptr + b * out.sb + qi * out.st + (int64_t)hq * out.sh + 2 * lane) = o;
+    if (lane == 0) lse[row] = den > 0.f ? (M + fast_log2(den)) * kLn2 : -INFINITY;
 }
 
 // ---- host side -------------------------------------------------------------------------------------
@@ -1505,7 +1517,7 @@ static void launch_decode_partial(const Dims &dm, Tensor q, Tensor k, Tensor v, 
 static int launch_decode_merge(const Dims &dm, const float *o_part, const float2 *ml_part, Tensor out, float *lse,
                                hipStream_t stream) {
     timing_begin("decode_merge_kernel", stream);
-    const dim3 grid(dm.Hq, dm.batch * dm.n_q), block(128);
+    const dim3 grid(dm.Hq, dm.n_q, dm.batch), block(64);
     if (dm.topk <= 8) hipLaunchKernelGGL(decode_merge_kernel<8>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
     else if (dm.topk <= 16) hipLaunchKernelGGL(decode_merge_kernel<16>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
     else if (dm.topk <= 32) hipLaunchKernelGGL(decode_merge_kernel<32>, grid, block, 0, stream, dm, o_part, ml_part, out, lse);
