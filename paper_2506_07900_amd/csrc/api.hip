@@ -70,6 +70,7 @@ Dims make_dims(const infllmv2_params *p, int32_t batch, int32_t max_seqlen, int3
     d.scale_log2 = p->softmax_scale * kLog2e;
     d.rho = p->lse_coarse_ratio > 1 ? p->lse_coarse_ratio : 1;
     d.n_q = n_q;
+    d.n_q_inv = n_q > 1 ? (uint32_t)((1ull << 32) / (uint32_t)n_q) + 1u : 0u;
     d.shared_q = 0;
     d.fill = fill;
     return d;

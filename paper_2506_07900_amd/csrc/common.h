@@ -32,6 +32,7 @@ struct Dims {
     float scale_log2;   // softmax_scale * log2(e)
     int32_t rho;        // coarse / fine kernel stride of the approximate log-sum-exp; 1 = exact
     int32_t n_q;        // decode-side kernels: query tokens per sequence (1 = plain decode, n = draft verification)
+    uint32_t n_q_inv;   // floor(2^32 / n_q) + 1: i / n_q = the high word of i * n_q_inv, for n_q > 1 and i < 65536
     int32_t shared_q;   // prefill selection: 1 = one block set per 64-token query block (comparison variant)
     int32_t fill;       // 1 = also clear the rows of sequences shorter than max_seqlen (see internal.h)
 };
@@ -61,6 +62,11 @@ __device__ inline void arguments_arrive(const A &a, const T &...x) {
             const auto &x8, const auto &x9, const auto &x10, const auto &x11) __attribute__((always_inline)) {
         asm volatile("" ::"s"(x0), "s"(x1), "s"(x2), "s"(x3), "s"(x4), "s"(x5), "s"(x6), "s"(x7), "s"(x8), "s"(x9), "s"(x10), "s"(x11));
     }(a, x...);
+}
+
+// A word at a uniform address that nothing in the launch writes: a scalar load, also behind assembly, which the compiler takes to write memory.
+__device__ inline int32_t uniform_load(const int32_t *p) {
+    return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p;
 }
 
 // Number of complete semantic kernels of a sequence of l tokens (p=32, s=16).
@@ -274,6 +280,47 @@ __device__ inline void pick_by_bisection(uint32_t key, uint32_t top, int n, uint
     const uint64_t above = __ballot(key > lo), eq = __ballot(key == lo);      // the keys above lo, and the first of those equal to it
     const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
     chosen = above | __ballot(key == lo && before < n - __popcll(above));
+}
+
+// Sorted 64-bit words, sixteen to a row of lanes, largest first.  A step is a move of both halves across the row, a compare and two selects; nothing goes
+// through LDS, and a wavefront that runs alone needs no barrier.
+template <int kCtrl>
+__device__ inline uint64_t row_move64(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kCtrl, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), kCtrl, 0xf, 0xf, false);
+    return (uint64_t)hi << 32 | lo;
+}
+constexpr int kSwap1 = 0xb1, kSwap2 = 0x4e, kMirror4 = 0x1b, kMirror8 = 0x141, kMirror16 = 0x140, kSwap8 = 0x128;   // lanes i ^ 1, 2, 3, 7, 15, 8
+__device__ inline uint64_t keep_larger(uint64_t x, uint64_t y, bool larger) { return (y > x) == larger ? y : x; }
+__device__ inline uint64_t row_clean(uint64_t x, int lane) {               // two runs of four end to end, one descending, one ascending -> sorted, twice a row
+    x = keep_larger(x, row_move64<kMirror8>(row_move64<kMirror4>(x)), (lane & 4) == 0);
+    x = keep_larger(x, row_move64<kSwap2>(x), (lane & 2) == 0);
+    return keep_larger(x, row_move64<kSwap1>(x), (lane & 1) == 0);
+}
+__device__ inline uint64_t row_sort64(uint64_t x, int lane) {
+    x = keep_larger(x, row_move64<kSwap1>(x), (lane & 1) == 0);
+    x = keep_larger(x, row_move64<kMirror4>(x), (lane & 2) == 0);
+    x = keep_larger(x, row_move64<kSwap1>(x), (lane & 1) == 0);
+    x = keep_larger(x, row_move64<kMirror8>(x), (lane & 4) == 0);
+    x = keep_larger(x, row_move64<kSwap2>(x), (lane & 2) == 0);
+    x = keep_larger(x, row_move64<kSwap1>(x), (lane & 1) == 0);
+    x = keep_larger(x, row_move64<kMirror16>(x), (lane & 8) == 0);
+    return row_clean(x, lane);
+}
+// the sixteen largest of two sorted rows
+__device__ inline uint64_t row_merge64(uint64_t a, uint64_t b, int lane) {
+    uint64_t x = keep_larger(a, row_move64<kMirror16>(b), true);
+    x = keep_larger(x, row_move64<kSwap8>(x), (lane & 8) == 0);
+    return row_clean(x, lane);
+}
+// the sixteen largest of a wavefront's four sorted rows, in every row
+__device__ inline uint64_t rows_merge64(uint64_t x, int lane) {
+    const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    x = row_merge64((uint64_t)h16[0] << 32 | l16[0], (uint64_t)h16[1] << 32 | l16[1], lane);
+    const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    return row_merge64((uint64_t)h32[0] << 32 | l32[0], (uint64_t)h32[1] << 32 | l32[1], lane);
 }
 
 // The running picks of one row, merged with a chunk of kVPL * 64 blocks by one wavefront: lane l brings the keys (0 = not a candidate)

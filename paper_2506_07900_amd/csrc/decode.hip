@@ -36,11 +36,11 @@ __device__ inline int query_row(const Dims &dm, const int32_t *__restrict__ seql
     if (dm.n_q == 1) {
         b = bv;
         qi = 0;
-        return clamp_len(seqlens[b], dm.max_seqlen);
+        return clamp_len(uniform_load(seqlens + b), dm.max_seqlen);
     }
-    b = bv / dm.n_q;
+    b = (int)__umulhi((uint32_t)bv, dm.n_q_inv);
     qi = bv - b * dm.n_q;
-    const int L_all = clamp_len(seqlens[b], dm.max_seqlen);
+    const int L_all = clamp_len(uniform_load(seqlens + b), dm.max_seqlen);
     return L_all < dm.n_q ? 0 : L_all - (dm.n_q - 1 - qi);
 }
 
@@ -560,46 +560,57 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
 // ---- part 2, plain decode: block scores from the logits part 1 kept ---------------------------------
 // (One query per sequence: its logits are a quarter of the bytes of the compressed keys, so reading
 // them back is cheaper than computing them again; with several queries per sequence the balance tips.)
-// grid (n_lists, Hkv, B), 576 threads.  Thread t <= 512 scores kernel 512*bx - 1 + t (one halo kernel to the left);
+// grid (n_lists, Hkv, B), 512 threads.  Thread t scores kernel 512*bx + t, and 16 lanes, a head each, the one before the first;
 // waves 0 and 1 then pool blocks 128*bx + t and leave the list_len best of the 128 as a descending list of pick words:
 // the top-k that follows merges nb/128 short lists, at most one word per thread up to 150K tokens, instead of ranking a
 // row of nb scores -- which each of its topk workgroups per row would do again.
+// Eight wavefronts, so that four workgroups fit a compute unit (with a ninth for the halo kernel, three: 32 sequences
+// of 128K, 1024 workgroups, took two rounds).  kSorted: lists of up to 16, by sorting networks across the lanes instead of by counting.
 constexpr int kMaxParts = 128;                        // partials per head (of >= 128 kernels): contexts up to 262144 tokens
 constexpr int kListBlocks = 128;                      // blocks per list
-__global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int32_t *__restrict__ seqlens,
+constexpr int kScoreThreads = 4 * kListBlocks;
+template <int kG, bool kSorted>
+__global__ __launch_bounds__(kScoreThreads) void decode_scores_z_kernel(Dims dm, const int32_t *__restrict__ seqlens,
                                                              const float *__restrict__ zbuf,
                                                              const float2 *__restrict__ part,
                                                              int32_t n_c_cap, int32_t n_part, int32_t part_kernels,
                                                              uint64_t *__restrict__ lists, int32_t list_len) {
-    __shared__ float lse_h[16];
-    __shared__ float rs[4 * kListBlocks + 4];
+    __shared__ __align__(16) float lse_h[16], halo_e[16];
+    __shared__ float rs[kScoreThreads + 4];
     __shared__ __align__(16) uint64_t words[2][64], best[2][64];
+    arguments_arrive(dm.Hkv, dm.n_init, dm.n_local, dm.topk, dm.max_seqlen, dm.rho, seqlens, zbuf, part, n_c_cap, n_part, part_kernels);
+    arguments_arrive(lists, list_len);
     const int h = blockIdx.y, bv = blockIdx.z;
-    const int tid = threadIdx.x;
-    const int G = dm.G;
-    const int base = blockIdx.x * 4 * kListBlocks;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int base = blockIdx.x * kScoreThreads;
+    const int32_t L_raw = uniform_load(seqlens + bv);
     // Everything this thread reads lies in the workspace at places that do not depend on the sequence
     // length, so the loads go out before the length is known (one memory round trip less on the
     // critical path of the step); what turns out to be past the end is masked afterwards.
-    const int head = min(tid >> 4, G - 1), sub = tid & 15;
+    const float *z_row = zbuf + ((int64_t)bv * dm.Hkv + h) * kG * n_c_cap;
+    const float2 *p_row = part + ((int64_t)bv * dm.Hkv + h) * kG * n_part;
+    const int head = tid >> 4, sub = tid & 15;        // 16 lanes per head merge its partials
     float2 v[kMaxParts / 16];
-    if (tid < 256) {
+    if (tid < 16 * kG) {
 #pragma unroll
-        for (int i = 0; i < kMaxParts / 16; ++i)
-            v[i] = part[(((int64_t)bv * dm.Hkv + h) * G + head) * n_part + min(sub + 16 * i, n_part - 1)];
+        for (int i = 0; i < kMaxParts / 16; ++i) {
+            v[i] = float2{-INFINITY, 0.f};
+            if (16 * i < n_part) v[i] = p_row[head * n_part + min(sub + 16 * i, n_part - 1)];
+        }
     }
-    const int jh = base - 1 + tid;
-    const int jh_c = min(max(jh, 0), n_c_cap - 1);
-    float zz[16];
+    const uint32_t jh_c = min(base + tid, n_c_cap - 1);
+    float zz[kG];
 #pragma unroll
-    for (int gq = 0; gq < 16; ++gq) zz[gq] = zbuf[(((int64_t)bv * dm.Hkv + h) * G + min(gq, G - 1)) * n_c_cap + jh_c];
-    int b, qi;
-    const int L = query_row(dm, seqlens, bv, b, qi);
+    for (int gq = 0; gq < kG; ++gq) zz[gq] = (z_row + (int64_t)gq * n_c_cap)[jh_c];
+    const bool halo = wave == kScoreThreads / 64 - 1 && lane < kG;
+    float z_halo = 0.f;
+    if (halo) z_halo = z_row[lane * n_c_cap + max(base - 1, 0)];
+    const int L = clamp_len(L_raw, dm.max_seqlen);
     const int n_vis = num_kernels(L);
     if (L < 1 || (int)blockIdx.x * kListBlocks > (L - 1) / kBlock) return;   // no block of this chunk exists
     const int np = (n_vis + part_kernels - 1) / part_kernels;   // valid partials
-    // log-sum-exp per head: 16 lanes per head
-    if (tid < 256) {
+    // log-sum-exp per head
+    if (tid < 16 * kG) {
 #pragma unroll
         for (int i = 0; i < kMaxParts / 16; ++i)
             if (sub + 16 * i >= np) v[i] = float2{-INFINITY, 0.f};
@@ -610,26 +621,32 @@ __global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int
         const float mu = m == -INFINITY ? 0.f : m;
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < kMaxParts / 16; ++i) s += v[i].y * fast_exp2(v[i].x - mu);
+        for (int i = 0; i < kMaxParts / 16; ++i)
+            if (16 * i < np) s += v[i].y * fast_exp2(v[i].x - mu);
         s = row_reduce(s, [](float a, float c) { return a + c; });
-        if (sub == 0 && (tid >> 4) < G)   // approximate mode: rho times fewer kernels were summed; 0 when none is visible
-            lse_h[tid >> 4] = dm.rho > 1 ? (m == -INFINITY ? 0.f : m + fast_log2(s) + (float)(31 - __clz(dm.rho)))
-                                         : m + fast_log2(s);
+        // approximate mode: rho times fewer kernels were summed; 0 when none is visible
+        const float exact = m + fast_log2(s), coarse = m == -INFINITY ? 0.f : exact + (float)(31 - __clz(dm.rho));
+        if (sub == 0) lse_h[head] = dm.rho > 1 ? coarse : exact;
     }
     // logits of this thread's kernel, all heads
-    const bool have = tid <= 4 * kListBlocks && jh >= 0 && jh < n_vis;
     __syncthreads();
-    if (tid <= 4 * kListBlocks) {
+    {
         float acc = 0.f;
 #pragma unroll
-        for (int gq = 0; gq < 16; ++gq)
-            if (gq < G) acc += fast_exp2(zz[gq] - lse_h[gq]);
-        rs[tid] = have ? fminf(fmaxf(acc * (1.f / G), kScoreFloor), kScoreCeil) : -INFINITY;
+        for (int gq = 0; gq < kG; ++gq) acc += fast_exp2(zz[gq] - lse_h[gq]);
+        rs[1 + tid] = base + tid < n_vis ? fminf(fmaxf(acc * (1.f / kG), kScoreFloor), kScoreCeil) : -INFINITY;
+        if (halo) {                                   // (the heads are added in the same order)
+            halo_e[lane] = fast_exp2(z_halo - lse_h[lane]);
+            __builtin_amdgcn_wave_barrier();          // same wavefront: LDS keeps the order
+            acc = 0.f;
+#pragma unroll
+            for (int gq = 0; gq < kG; ++gq) acc += halo_e[gq];
+            if (lane == 0) rs[0] = base >= 1 && base - 1 < n_vis ? fminf(fmaxf(acc * (1.f / kG), kScoreFloor), kScoreCeil) : -INFINITY;
+        }
     }
     __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63;
     uint64_t e = 0ull;
-    int rank = 64;
+    uint64_t *list = lists + (((int64_t)bv * dm.Hkv + h) * gridDim.x + blockIdx.x) * list_len;
     if (wave < 2) {
         const int j = blockIdx.x * kListBlocks + tid;     // kernels 4j-1 .. 4j+3 = rs[4*tid .. 4*tid+4]
         float r = rs[4 * tid];
@@ -637,16 +654,31 @@ __global__ __launch_bounds__(576) void decode_scores_z_kernel(Dims dm, const int
         for (int x = 1; x < 5; ++x) r = fmaxf(r, rs[4 * tid + x]);
         const RowRange rr(dm, L);
         e = pick_element(r, j, rr.n_init, rr.jc_max);
-        words[wave][lane] = e;
-        best[wave][lane] = 0ull;
-        __builtin_amdgcn_wave_barrier();                  // same wavefront: LDS keeps the order
-        rank = count_larger(words[wave], 64, e);          // no two words are equal
-        if (rank < list_len) best[wave][rank] = e;
     }
-    __syncthreads();
-    if (wave < 2 && rank < list_len) {
-        rank += count_larger(best[wave ^ 1], (list_len + 3) & ~3, e);
-        if (rank < list_len) lists[(((int64_t)bv * dm.Hkv + h) * gridDim.x + blockIdx.x) * list_len + rank] = e;
+    if constexpr (kSorted) {
+        if (wave < 2) {
+            e = rows_merge64(row_sort64(e, lane), lane);
+            if (wave == 1 && lane < 16) best[1][lane] = e;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            e = row_merge64(e, best[1][lane & 15], lane);
+            if (lane < list_len) list[lane] = e;
+        }
+    } else {
+        int rank = 64;
+        if (wave < 2) {
+            words[wave][lane] = e;
+            best[wave][lane] = 0ull;
+            __builtin_amdgcn_wave_barrier();              // same wavefront: LDS keeps the order
+            rank = count_larger(words[wave], 64, e);      // no two words are equal
+            if (rank < list_len) best[wave][rank] = e;
+        }
+        __syncthreads();
+        if (wave < 2 && rank < list_len) {
+            rank += count_larger(best[wave ^ 1], (list_len + 3) & ~3, e);
+            if (rank < list_len) list[rank] = e;
+        }
     }
 }
 
@@ -826,13 +858,73 @@ __device__ inline int order_row(int *mine, int n_sel, int topk, int32_t *__restr
     return rank;
 }
 
-template <bool kLists, int kVPT>
+// The same for at most 16 picks from at most 16 kSlots (kShare) or 4 kSlots sorted lists: a row of lanes holds a list, rows are merged
+// two at a time without LDS; with kShare the four wavefronts merge a quarter of the lists each and then each other's results.
+// Returns the c-th best word in lane c of every row.  Against counting (32 LDS reads of 16 bytes and 64 compares of 64 bits per
+// wavefront, two barriers): 3200 -> 1600 cycles for 16 lists of 13 on a compute unit of its own.
+constexpr int kMergePicks = 16;
+template <int kSlots, bool kShare>
+struct ListMerge {
+    uint64_t w[kSlots];
+    static __device__ int list(int s) { return ((kShare ? (int)(threadIdx.x >> 6) : 0) * kSlots + s) * 4 + ((int)(threadIdx.x & 63) >> 4); }
+    __device__ ListMerge(const PickInput &in, int64_t row) {
+        const int64_t first = row * in.n_lists * in.list_len + min((int)(threadIdx.x & 15), in.list_len - 1);
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) w[s] = reinterpret_cast<const uint64_t *>(in.found)[first + min(list(s), in.n_lists - 1) * in.list_len];
+    }
+    __device__ uint64_t best(const PickInput &in, int L) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)                  // (lists past the sequence's end were not written)
+            if ((lane & 15) >= in.list_len || list(s) >= in.n_lists || list(s) * in.blocks > (L - 1) / kBlock) w[s] = 0ull;
+        uint64_t x = w[0];
+#pragma unroll
+        for (int s = 1; s < kSlots; ++s) x = row_merge64(x, w[s], lane);
+        x = rows_merge64(x, lane);
+        if constexpr (kShare) {
+            __shared__ uint64_t of_wave[kPickWaves][16];
+            if (lane < 16) of_wave[threadIdx.x >> 6][lane] = x;
+            __syncthreads();
+            x = rows_merge64(of_wave[lane >> 4][lane & 15], lane);
+        }
+        return x;
+    }
+};
+
+// How a row's top-k is found: from its scores (kScores), from sorted lists by counting (kCount) or by merging (kMerge, kMergeShared); kN: elements per
+// thread, or lists per row of lanes.
+enum PickForm { kScores, kCount, kMerge, kMergeShared };
+template <int kForm, int kN>
+struct Picker {
+    std::conditional_t<kForm <= kCount, PickLoad<kForm == kCount, kN>, ListMerge<kN, kForm == kMergeShared>> load;
+    __device__ Picker(const PickInput &in, int64_t row) : load(in, row) {}
+    // the selected blocks of the row, the picked ones first, best first, to this wavefront's `mine`; entry `at` (uniform) is returned.  Every thread calls it.
+    __device__ int pick(const PickInput &in, const RowRange &rr, int L, unsigned char *smem, int topk, int *mine, int at) {
+        if constexpr (kForm <= kCount) {
+            uint64_t el[kN];
+            load.elements(in, rr, L, el);
+            pick_row<kN>(rr, el, PickShared(smem, topk, kN), mine);
+            return __builtin_amdgcn_readfirstlane(mine[min(at, rr.n_sel - 1)]);
+        } else {
+            const int lane = threadIdx.x & 63, n_pick = max(rr.n_pick, 0);
+            int x = 0;
+            if (n_pick > 0) x = (int)~(uint32_t)load.best(in, L);                 // uniform over the workgroup
+            const int f = lane - n_pick;
+            if (f >= 0) x = f < rr.n_init ? f : rr.lo_local + (f - rr.n_init);    // the forced blocks
+            if (lane < rr.n_sel) mine[lane] = x;
+            __builtin_amdgcn_wave_barrier();
+            return __builtin_amdgcn_readlane(x, min(at, rr.n_sel - 1));
+        }
+    }
+};
+
+template <int kForm, int kN>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, const int32_t *__restrict__ seqlens,
                                                                     PickInput in, int32_t *__restrict__ block_idx) {
     extern __shared__ __align__(16) unsigned char pick_smem[];
-    const PickShared sh(pick_smem, dm.topk, kVPT);
+    arguments_arrive(dm.Hkv, dm.topk, dm.n_init, dm.n_local, dm.max_seqlen, dm.n_q, seqlens, in.found, in.n_lists, in.list_len, in.blocks, block_idx);
     const int row = blockIdx.x, bv = row / dm.Hkv, h = row - bv * dm.Hkv;
-    const PickLoad<kLists, kVPT> load(in, row);
+    Picker<kForm, kN> picker(in, row);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     int32_t *o = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
@@ -841,10 +933,8 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, cons
         return;
     }
     const RowRange rr(dm, L);
-    uint64_t el[kVPT];
-    load.elements(in, rr, L, el);
     __shared__ __align__(16) int mine[kPickWaves][64];
-    pick_row<kVPT>(rr, el, sh, mine[threadIdx.x >> 6]);
+    picker.pick(in, rr, L, pick_smem, dm.topk, mine[threadIdx.x >> 6], 0);
     if (threadIdx.x < 64) order_row(mine[0], rr.n_sel, dm.topk, o);
 }
 
@@ -857,12 +947,25 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, cons
 constexpr int kVsPitch = kHeadDim + 4;               // bf16 elements per LDS value row: 4 rows of a transposing load in 4 bank groups
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-// The rows of a block this thread loads, as offsets from the block's first row: value rows tid/16 + 16i (channels
-// 8(tid%16) ..), key row 16 wave + n (channels 32ks + 8g ..).  Worked out before the block is known, so that a uniform
-// base is all that is added afterwards (a lone wavefront spends 0.4 us on the address arithmetic otherwise).
-struct BlockRows {
+// What the fetch of a block does not need the block for: the query's operands, and where the thread's rows lie, value rows tid/16 + 16i (channels
+// 8(tid%16) ..), key row 16 wave + n (channels 32ks + 8g ..).  Worked out, and the queries asked for, before the block is known: a wavefront alone spends 2000
+// cycles on these arguments and products otherwise, and left to itself the compiler moves them to where the block is known.
+struct BlockFetch {
+    int64_t k_head, v_head;                              // uniform: the head's first row
     int64_t v[4], k;
-    __device__ BlockRows(const Tensor &kt, const Tensor &vt, int last) {
+    bf16x8 bq[4];
+    __device__ BlockFetch(const Dims &dm, const Tensor &q, const Tensor &kt, const Tensor &vt, int b, int qi, int h) {
+        const int tid = threadIdx.x, lane = tid & 63;
+        const __bf16 *qr = q.ptr + b * q.sb + qi * q.st + (int64_t)(h * dm.G + min(lane & 15, dm.G - 1)) * q.sh + 8 * (lane >> 4);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
+        k_head = b * kt.sb + h * kt.sh;
+        v_head = b * vt.sb + h * vt.sh;
+        rows(kt, vt, kBlock - 1);
+        asm volatile("" : "+s"(k_head), "+s"(v_head));
+        asm volatile("" : "+v"(k), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+    }
+    __device__ void rows(const Tensor &kt, const Tensor &vt, int last) {                 // the block's rows 0 .. last exist
         const int tid = threadIdx.x, lane = tid & 63;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = (int64_t)min((tid >> 4) + 16 * i, last) * vt.st + 8 * (tid & 15);
@@ -875,7 +978,7 @@ struct BlockRows {
 // the row's ascending list, where the partial result goes; it is called while the block's rows are on their way.
 // kFresh: row fresh_row of the caches (-1: none) is being written by this very launch: it is taken from fresh.k_new / v_new.
 template <bool kFresh, typename Place>
-__device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tensor &k, const Tensor &v, const BlockRows &rows,
+__device__ inline void attend_block(const Dims &dm, const Tensor &k, const Tensor &v, BlockFetch fetch,
                                     int bv, int b, int qi, int h, int L, int blk, const uint64_t *__restrict__ tree_mask,
                                     float *__restrict__ o_part, float2 *__restrict__ ml_part, Place place,
                                     const AppendArgs *fresh = nullptr, int fresh_row = -1) {
@@ -908,21 +1011,18 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &q, const Tenso
     // (rows the query may not see are read, in bounds, and masked)
     const int c8 = tid & 15, vr = tid >> 4;
     uint4 vrow[4];
-    bf16x8 a[4], bq[4];
+    bf16x8 a[4];
+    const bf16x8(&bq)[4] = fetch.bq;
     {
-        const __bf16 *kb = k.ptr + b * k.sb + h * k.sh + (int64_t)key0 * k.st;
-        const __bf16 *vb = v.ptr + b * v.sb + h * v.sh + (int64_t)key0 * v.st;
-        const BlockRows r = key0 + kBlock <= dm.max_seqlen ? rows : BlockRows(k, v, dm.max_seqlen - 1 - key0);
-        const __bf16 *kr = kb + r.k;
+        if (key0 + kBlock > dm.max_seqlen) fetch.rows(k, v, dm.max_seqlen - 1 - key0);
+        const __bf16 *kr = k.ptr + (fetch.k_head + (int64_t)key0 * k.st) + fetch.k;
+        const __bf16 *vb = v.ptr + (fetch.v_head + (int64_t)key0 * v.st);
         if (kFresh && key0 + 16 * wave + n == fresh_row) kr = fresh->k_new.ptr + b * fresh->k_new.sb + h * fresh->k_new.sh + 8 * g;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) a[ks] = load8(kr + 32 * ks);
-        const __bf16 *qr = q.ptr + b * q.sb + qi * q.st + (int64_t)(h * G + min(n, G - 1)) * q.sh + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const __bf16 *vp = vb + r.v[i];
+            const __bf16 *vp = vb + fetch.v[i];
             if (kFresh && key0 + vr + 16 * i == fresh_row) vp = fresh->v_new.ptr + b * fresh->v_new.sb + h * fresh->v_new.sh + 8 * c8;
             vrow[i] = *reinterpret_cast<const uint4 *>(vp);
         }
@@ -1014,8 +1114,8 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     const int blk = block_idx[(((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk + cidx];
-    const BlockRows rows(k, v, kBlock - 1);
-    attend_block<false>(dm, q, k, v, rows, bv, b, qi, h, L, __builtin_amdgcn_readfirstlane(blk), tree_mask, o_part, ml_part,
+    const BlockFetch fetch(dm, q, k, v, b, qi, h);
+    attend_block<false>(dm, k, v, fetch, bv, b, qi, h, L, __builtin_amdgcn_readfirstlane(blk), tree_mask, o_part, ml_part,
                         [cidx] { return cidx; });
 }
 
@@ -1026,7 +1126,7 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
 // entry of the result as it stands, best first; the list's ascending order, which decides where the partial result goes,
 // is worked out while the block's rows are on their way.  Those whose entry is a forced block rank nothing: their rows are on
 // their way while the others rank (32 sequences of 128K: this kernel 12.1 -> 11.7 us, the step 63.6 -> 62.9).
-template <bool kLists, int kVPT>
+template <int kForm, int kN>
 __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims dm, Tensor q, Tensor k, Tensor v,
                                                                             const int32_t *__restrict__ seqlens,
                                                                             PickInput in,
@@ -1035,12 +1135,14 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
                                                                             float *__restrict__ o_part,
                                                                             float2 *__restrict__ ml_part) {
     extern __shared__ __align__(16) unsigned char pick_smem[];
-    const PickShared sh(pick_smem, dm.topk, kVPT);
+    arguments_arrive(dm.Hkv, dm.max_seqlen, dm.n_q, seqlens, in.found, in.n_lists, in.list_len, in.blocks, q.ptr, q.sb, q.sh, q.st);
+    arguments_arrive(dm.Hq, dm.topk, dm.n_init, k.ptr, k.sb, k.sh, k.st, v.ptr, v.sb, v.sh, v.st, tree_mask);
+    arguments_arrive(dm.G, dm.n_local, dm.scale_log2, block_idx, o_part, ml_part);
     const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
-    const PickLoad<kLists, kVPT> load(in, (int64_t)bv * dm.Hkv + h);
-    const BlockRows rows(k, v, kBlock - 1);
+    Picker<kForm, kN> picker(in, (int64_t)bv * dm.Hkv + h);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
+    const BlockFetch fetch(dm, q, k, v, b, qi, h);
     int32_t *orow = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
     __shared__ __align__(16) int mine[kPickWaves][64];
     const int wave = threadIdx.x >> 6;
@@ -1056,14 +1158,12 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
                 at = f < rr.n_init ? f : cidx;
             }
         } else {
-            uint64_t el[kVPT];
-            load.elements(in, rr, L, el);
-            pick_row<kVPT>(rr, el, sh, mine[wave]);
             n_sel = rr.n_sel;
-            if (cidx < n_sel) blk = __builtin_amdgcn_readfirstlane(mine[wave][cidx]);
+            const int mine_at = picker.pick(in, rr, L, pick_smem, dm.topk, mine[wave], cidx);
+            if (cidx < n_sel) blk = mine_at;
         }
     }
-    attend_block<false>(dm, q, k, v, rows, bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
+    attend_block<false>(dm, k, v, fetch, bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
         if (n_sel == 0) return at;
         const int rank = order_row(mine[wave], n_sel, dm.topk, cidx == 0 && wave == 0 ? orow : nullptr);
         return cidx < n_sel ? __builtin_amdgcn_readlane(rank, cidx) : cidx;
@@ -1104,7 +1204,6 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     const bool live = kMode > 0 && L_raw >= 1 && L_raw <= dm.max_seqlen;      // as the stand-alone append: others are skipped
     int32_t *orow = block_idx + ((int64_t)b * dm.Hkv + h) * dm.topk;
     int blk = -1;
-    const BlockRows rows(ap.k, ap.v, kBlock - 1);
     if (live && cidx == 0 && tid < 32) {
         const int c8 = (tid & 15) * 8;
         const Tensor &src = tid < 16 ? ap.k_new : ap.v_new;
@@ -1264,7 +1363,7 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
         if (cidx < rr.n_sel) blk = __builtin_amdgcn_readfirstlane(mine[cidx]);
     }
     if constexpr (kMode == 2)
-        attend_block<true>(dm, q, ap.k, ap.v, rows, b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
+        attend_block<true>(dm, ap.k, ap.v, BlockFetch(dm, q, ap.k, ap.v, b, 0, h), b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
                            live ? L_raw - 1 : -1);
 }
 
@@ -1407,6 +1506,16 @@ static int launch_short(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &a
     return (int)hipGetLastError();
 }
 
+static auto scores_z_kernel(int G, bool sorted) {
+    switch (G) {
+        case 1: return sorted ? decode_scores_z_kernel<1, true> : decode_scores_z_kernel<1, false>;
+        case 2: return sorted ? decode_scores_z_kernel<2, true> : decode_scores_z_kernel<2, false>;
+        case 4: return sorted ? decode_scores_z_kernel<4, true> : decode_scores_z_kernel<4, false>;
+        case 8: return sorted ? decode_scores_z_kernel<8, true> : decode_scores_z_kernel<8, false>;
+        default: return sorted ? decode_scores_z_kernel<16, true> : decode_scores_z_kernel<16, false>;
+    }
+}
+
 int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seqlens,
                          int32_t *block_idx, void *ws, hipStream_t stream, const AppendArgs *append,
                          AttendArgs *attend) {
@@ -1451,8 +1560,8 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     timing_end(stream);
     timing_begin("decode_scores_kernel", stream);
     if (dm.n_q == 1)
-        hipLaunchKernelGGL(decode_scores_z_kernel, dim3(l.n_lists, dm.Hkv, dm.batch), dim3(576), 0, stream,
-                           dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm),
+        hipLaunchKernelGGL(scores_z_kernel(dm.G, l.list_len <= kMergePicks), dim3(l.n_lists, dm.Hkv, dm.batch), dim3(kScoreThreads), 0,
+                           stream, dm, seqlens, zbuf, part_lse, l.n_c_cap, l.n_part, 64 * decode_tiles_per_wave(dm),
                            reinterpret_cast<uint64_t *>(found), l.list_len);
     else
         hipLaunchKernelGGL((l.list_blocks == 64 ? decode_scores_kernel<kVerifyQT, 4> : decode_scores_kernel<kVerifyQT, 2>),
@@ -1467,26 +1576,32 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     if (attend) attend->fused = fuse_units(dm);
     const bool fused = attend && attend->fused;
     timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
-#define INFLLMV2_PICK(LISTS, VPT)                                                                                       \
+#define INFLLMV2_PICK(FORM, N)                                                                                          \
     do {                                                                                                                \
+        const size_t lds = FORM <= kCount ? pick_shared_bytes(dm.topk, N) : 0;                                          \
         if (fused)                                                                                                      \
-            hipLaunchKernelGGL((decode_pick_partial_kernel<LISTS, VPT>), dim3(dm.topk, dm.Hkv, rows),                   \
-                               dim3(kPickThreads), pick_shared_bytes(dm.topk, VPT), stream, dm, q, attend->k,           \
-                               attend->v, seqlens, in, attend->tree_mask, block_idx, attend->o_part, attend->ml_part);  \
+            hipLaunchKernelGGL((decode_pick_partial_kernel<FORM, N>), dim3(dm.topk, dm.Hkv, rows), dim3(kPickThreads),  \
+                               lds, stream, dm, q, attend->k, attend->v, seqlens, in, attend->tree_mask, block_idx,     \
+                               attend->o_part, attend->ml_part);                                                        \
         else                                                                                                            \
-            hipLaunchKernelGGL((decode_pick_kernel<LISTS, VPT>), dim3(rows * dm.Hkv), dim3(kPickThreads),               \
-                               pick_shared_bytes(dm.topk, VPT), stream, dm, seqlens, in, block_idx);                    \
+            hipLaunchKernelGGL((decode_pick_kernel<FORM, N>), dim3(rows * dm.Hkv), dim3(kPickThreads), lds, stream, dm, \
+                               seqlens, in, block_idx);                                                                 \
     } while (0)
-    if (lists) {
-        if (vpt <= 1) INFLLMV2_PICK(true, 1);
-        else if (vpt <= 2) INFLLMV2_PICK(true, 2);
-        else if (vpt <= 4) INFLLMV2_PICK(true, 4);
-        else if (vpt <= 8) INFLLMV2_PICK(true, 8);
-        else INFLLMV2_PICK(true, 16);
+    if (lists && l.list_len <= kMergePicks && l.n_lists <= 32) {
+        if (l.n_lists <= 4) INFLLMV2_PICK(kMerge, 1);
+        else if (l.n_lists <= 8) INFLLMV2_PICK(kMerge, 2);
+        else if (l.n_lists <= 16) INFLLMV2_PICK(kMergeShared, 1);
+        else INFLLMV2_PICK(kMergeShared, 2);
+    } else if (lists) {
+        if (vpt <= 1) INFLLMV2_PICK(kCount, 1);
+        else if (vpt <= 2) INFLLMV2_PICK(kCount, 2);
+        else if (vpt <= 4) INFLLMV2_PICK(kCount, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(kCount, 8);
+        else INFLLMV2_PICK(kCount, 16);
     } else {
-        if (vpt <= 4) INFLLMV2_PICK(false, 4);
-        else if (vpt <= 8) INFLLMV2_PICK(false, 8);
-        else INFLLMV2_PICK(false, 16);
+        if (vpt <= 4) INFLLMV2_PICK(kScores, 4);
+        else if (vpt <= 8) INFLLMV2_PICK(kScores, 8);
+        else INFLLMV2_PICK(kScores, 16);
     }
 #undef INFLLMV2_PICK
     timing_end(stream);
