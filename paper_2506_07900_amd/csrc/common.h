@@ -282,12 +282,12 @@ __device__ inline void pick_by_bisection(uint32_t key, uint32_t top, int n, uint
     chosen = above | __ballot(key == lo && before < n - __popcll(above));
 }
 
-// Sorted 64-bit words, sixteen to a row of lanes, largest first.  A step is a move of both halves across the row, a compare and two selects; nothing goes
-// through LDS, and a wavefront that runs alone needs no barrier.
+// Sorted 64-bit words, sixteen to a row of lanes, largest first.  A step is a move of both halves across the row, a compare and two selects, about 50
+// cycles; nothing goes through LDS, and a wavefront that runs alone needs no barrier.  (Maxima and minima of the words as doubles: the same.)
 template <int kCtrl>
 __device__ inline uint64_t row_move64(uint64_t x) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, kCtrl, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), kCtrl, 0xf, 0xf, false);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, kCtrl, 0xf, 0xf, false);      // (no value for lanes without a source: there are none)
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), kCtrl, 0xf, 0xf, false);
     return (uint64_t)hi << 32 | lo;
 }
 constexpr int kSwap1 = 0xb1, kSwap2 = 0x4e, kMirror4 = 0x1b, kMirror8 = 0x141, kMirror16 = 0x140, kSwap8 = 0x128;   // lanes i ^ 1, 2, 3, 7, 15, 8
@@ -313,14 +313,18 @@ __device__ inline uint64_t row_merge64(uint64_t a, uint64_t b, int lane) {
     x = keep_larger(x, row_move64<kSwap8>(x), (lane & 8) == 0);
     return row_clean(x, lane);
 }
+// the sixteen largest of rows 0 and 1, and of rows 2 and 3, in both
+__device__ inline uint64_t row_pairs_merge64(uint64_t x, int lane) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    return row_merge64((uint64_t)hi[0] << 32 | lo[0], (uint64_t)hi[1] << 32 | lo[1], lane);
+}
 // the sixteen largest of a wavefront's four sorted rows, in every row
 __device__ inline uint64_t rows_merge64(uint64_t x, int lane) {
-    const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
-    const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
-    x = row_merge64((uint64_t)h16[0] << 32 | l16[0], (uint64_t)h16[1] << 32 | l16[1], lane);
-    const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-    const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
-    return row_merge64((uint64_t)h32[0] << 32 | l32[0], (uint64_t)h32[1] << 32 | l32[1], lane);
+    x = row_pairs_merge64(x, lane);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+    return row_merge64((uint64_t)hi[0] << 32 | lo[0], (uint64_t)hi[1] << 32 | lo[1], lane);
 }
 
 // The running picks of one row, merged with a chunk of kVPL * 64 blocks by one wavefront: lane l brings the keys (0 = not a candidate)

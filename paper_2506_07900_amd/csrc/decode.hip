@@ -49,32 +49,43 @@ __device__ inline int query_row(const Dims &dm, const int32_t *__restrict__ seql
 // wave needs the same rows and every workgroup of the launch the same few cache lines, so the
 // workgroup fetches them once into LDS (row pitch 272 bytes: conflict-free 16-byte reads).
 constexpr int kQsPitch = kHeadDim + 8;
-template <int kQT>
-__device__ inline void load_query_operands(const Dims &dm, const Tensor &q, int b, int h, int qi0, uint16_t *qs,
-                                           bf16x8 (&bq)[kQT][4]) {
-    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-    const int G = dm.G;
-    if constexpr (kQT == 1) {
-        const __bf16 *qr = q.ptr + b * q.sb + min(qi0, dm.n_q - 1) * q.st + (int64_t)(h * G + min(n, G - 1)) * q.sh + 8 * g;
+template <int kQT, int kThreads = 256>
+struct QueryOperands {
+    static constexpr int kEach = kQT == 1 ? 1 : kQT * 256 / kThreads;    // 256 threads take a query row's 16 heads x 16 chunks of 16 bytes
+    static_assert(kQT == 1 || kEach * kThreads == kQT * 256, "every thread as many");
+    bf16x8 x[kQT == 1 ? 4 : kEach];
+    __device__ QueryOperands(const Dims &dm, const Tensor &q, int b, int h, int qi0) {      // asked for
+        const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+        const int G = dm.G;
+        if constexpr (kQT == 1) {
+            const __bf16 *qr = q.ptr + (b * q.sb + (int64_t)(h * G) * q.sh) + (min(n, G - 1) * q.sh + 8 * g);   // (one query: n_q = 1)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) bq[0][ks] = load8(qr + 32 * ks);
-    } else {
-        const int row = threadIdx.x >> 4, c16 = threadIdx.x & 15;     // 256 threads: 16 heads x 16 chunks of 16 bytes
-        uint4 x[kQT];
+            for (int ks = 0; ks < 4; ++ks) x[ks] = load8(qr + 32 * ks);
+        } else {
+            const int row = (threadIdx.x >> 4) & 15, c16 = threadIdx.x & 15, t0 = (int)(threadIdx.x >> 8) * kEach;
+            const __bf16 *qr = q.ptr + (b * q.sb + (int64_t)(h * G) * q.sh) + (min(row, G - 1) * q.sh + 8 * c16);
 #pragma unroll
-        for (int t = 0; t < kQT; ++t)
-            x[t] = *reinterpret_cast<const uint4 *>(q.ptr + b * q.sb + min(qi0 + t, dm.n_q - 1) * q.st +
-                                                    (int64_t)(h * G + min(row, G - 1)) * q.sh + 8 * c16);
-#pragma unroll
-        for (int t = 0; t < kQT; ++t) *reinterpret_cast<uint4 *>(&qs[(t * 16 + row) * kQsPitch + 8 * c16]) = x[t];
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < kQT; ++t)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                bq[t][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&qs[(t * 16 + n) * kQsPitch + 32 * ks + 8 * g]));
+            for (int t = 0; t < kEach; ++t) x[t] = load8(qr + min(qi0 + t0 + t, dm.n_q - 1) * q.st);
+        }
     }
-}
+    __device__ void get(uint16_t *qs, bf16x8 (&bq)[kQT][4]) const {       // a barrier inside when kQT > 1
+        const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+        if constexpr (kQT == 1) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bq[0][ks] = x[ks];
+        } else {
+            const int row = (threadIdx.x >> 4) & 15, c16 = threadIdx.x & 15, t0 = (int)(threadIdx.x >> 8) * kEach;
+#pragma unroll
+            for (int t = 0; t < kEach; ++t) *reinterpret_cast<uint4 *>(&qs[((t0 + t) * 16 + row) * kQsPitch + 8 * c16]) = __builtin_bit_cast(uint4, x[t]);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < kQT; ++t)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    bq[t][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&qs[(t * 16 + n) * kQsPitch + 32 * ks + 8 * g]));
+        }
+    }
+};
 
 // Candidates and counts of a query at cache row L - 1 (L >= 1).
 struct RowRange {
@@ -140,10 +151,10 @@ __device__ inline bf16x8 fresh_kernel_row8(const AppendArgs &ap, int b, int h, i
 // ---- part 1: partial (max, sum) of the relevance softmax ---------------------------------------------
 // grid (n_c_cap / (64*kTW), Hkv, B * ceil(n_q/kQT)); wave w owns kernels chunk + 16*kTW*w .. +16*kTW-1.
 // Z^T = CK . Q^T: lane = query head, 4 accumulator entries = 4 consecutive kernels.
-// With kAppend (the one-call steps) the kernel also opens the step: the workgroups of chunk 0
-// copy the new token's key and value rows into the caches (nothing before the attention kernel reads
-// them), and the wave that owns the semantic kernel the new token completes builds its representation
-// itself -- 31 cached rows and the new one, fp64 sum in token order, one rounding, the same bits as
+// With kAppend (the one-call steps) the kernel also opens the step: workgroups behind the chunks copy the new tokens' key and value
+// rows into the caches (nothing before the attention kernel reads them; done by the first chunk's, those held up the launch: 16 drafted
+// tokens at 128K, 12800 of its 13000 cycles), and the wave that owns the semantic kernel the new token completes builds its
+// representation itself -- 31 cached rows and the new one, fp64 sum in token order, one rounding, the same bits as
 // compress_keys_kernel -- uses it, and stores it for the steps to come.  Verification: the same for the n_q new tokens and the up to
 // four kernels they complete, which every workgroup whose chunk holds one builds for itself; the last query tile's stores them.
 // A launch fewer: 16 drafted tokens at 128K 31.5 -> 27.7 us per step, 4 22.4 -> 20.6, 2 x 60K tokens 31.7 -> 27.6.
@@ -153,7 +164,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
                                                              float *__restrict__ zbuf, int32_t n_c_cap,
                                                              float2 *__restrict__ part,
                                                              float2 *__restrict__ part_c, int32_t n_part,
-                                                             AppendArgs ap) {
+                                                             AppendArgs ap, uint32_t n_qt_inv) {
     constexpr int kChunk = 64 * kTW;
     constexpr int kNewKernels = 5;                    // at most, that the new tokens complete (64 drafted tokens: 4)
     __shared__ float2 wpart[kQT][4][16];
@@ -161,39 +172,44 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     __shared__ __align__(16) uint16_t qs[kQT > 1 ? kQT * 16 * kQsPitch : 8];
     __shared__ __align__(16) uint32_t newrow[kAppend ? 64 : 1];
     __shared__ __align__(16) uint16_t newrows[kAppend && kQT > 1 ? kNewKernels * kQsPitch : 8];
+    arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.n_q, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, zbuf, n_c_cap, part);
+    arguments_arrive(q.ptr, q.sb, q.sh, q.st, dm.scale_log2, n_part, dm.rho);
     const int h = blockIdx.y;
     const int n_qt = (dm.n_q + kQT - 1) / kQT;        // query tiles per sequence
-    const int b = kQT == 1 ? blockIdx.z : blockIdx.z / n_qt;   // kQT = 1 is only launched with n_q = 1
+    const int b = kQT == 1 || n_qt == 1 ? blockIdx.z : (int)__umulhi(blockIdx.z, n_qt_inv);   // kQT = 1 is only launched with n_q = 1
     const int qi0 = (blockIdx.z - b * n_qt) * kQT;
-    const int L_all = clamp_len(seqlens[b], dm.max_seqlen);
+    const int32_t L_raw = uniform_load(seqlens + b);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int G = dm.G;
+    __builtin_amdgcn_sched_barrier(0);
+    // (queries and kernels are cold, 3200 cycles away from an idle unit: both are asked for before anything else is worked out)
+    const QueryOperands<kQT> query(dm, q, b, h, qi0);     // heads >= G repeat head G-1: their columns are never used
+    __builtin_amdgcn_sched_barrier(0);
+    const int jw = blockIdx.x * kChunk + wave * 16 * kTW; // first kernel of this wave
+    int64_t ck_wave_at = b * ck.sb + h * ck.sh + (int64_t)jw * ck.st, ck_lane = n * ck.st + 8 * g;   // (worked out while the length is on its way)
+    asm volatile("" : "+s"(ck_wave_at), "+v"(ck_lane));
+    const int L_all = clamp_len(L_raw, dm.max_seqlen);
     bool closes = false;                              // the new token completes semantic kernel n_vis - 1
     int new_from = 0x7fffffff;                        // several tokens: the kernels from here on are completed by them
-    if constexpr (kAppend && kQT > 1) {
-        const int32_t L_raw = seqlens[b];
-        if (L_raw >= dm.n_q && L_raw <= dm.max_seqlen) {              // as the stand-alone append: others are skipped
-            new_from = num_kernels(L_raw - dm.n_q);
-            if (blockIdx.x == 0 && qi0 == 0)
-                for (int i = threadIdx.x; i < 32 * dm.n_q; i += 256) {
-                    const int qi = i >> 5, c8 = (i & 15) * 8;
-                    const Tensor &src = i & 16 ? ap.v_new : ap.k_new;
-                    const Tensor &dst = i & 16 ? ap.v : ap.k;
-                    *reinterpret_cast<uint4 *>(dst.ptr + b * dst.sb + h * dst.sh + (int64_t)(L_raw - dm.n_q + qi) * dst.st + c8) =
-                        *reinterpret_cast<const uint4 *>(src.ptr + b * src.sb + h * src.sh + qi * src.st + c8);
-                }
+    if constexpr (kAppend) {
+        const bool live = L_raw >= dm.n_q && L_raw <= dm.max_seqlen;  // as the stand-alone append: others are skipped
+        if ((int)blockIdx.x >= n_part) {              // copies the rows of eight new tokens into the caches
+            const int qi = ((int)blockIdx.x - n_part) * 8 + (threadIdx.x >> 5), c8 = (threadIdx.x & 15) * 8;
+            if (!live || qi0 > 0 || qi >= dm.n_q) return;
+            const int64_t at = L_raw - dm.n_q + qi;
+            if (threadIdx.x & 16)
+                *reinterpret_cast<uint4 *>(ap.v.ptr + b * ap.v.sb + h * ap.v.sh + at * ap.v.st + c8) =
+                    *reinterpret_cast<const uint4 *>(ap.v_new.ptr + b * ap.v_new.sb + h * ap.v_new.sh + qi * ap.v_new.st + c8);
+            else
+                *reinterpret_cast<uint4 *>(ap.k.ptr + b * ap.k.sb + h * ap.k.sh + at * ap.k.st + c8) =
+                    *reinterpret_cast<const uint4 *>(ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + qi * ap.k_new.st + c8);
+            return;
         }
+        if (kQT > 1 && live) new_from = num_kernels(L_raw - dm.n_q);
+        if (kQT == 1) closes = live && L_raw >= kKernel && (L_raw - kKernel) % kStride == 0;
     }
-    if constexpr (kAppend && kQT == 1) {
-        const int32_t L_raw = seqlens[b];
-        const bool live = L_raw >= 1 && L_raw <= dm.max_seqlen;       // as the stand-alone append: others are skipped
-        if (live && blockIdx.x == 0 && threadIdx.x < 32) {
-            const int c8 = (threadIdx.x & 15) * 8;
-            const Tensor &src = threadIdx.x < 16 ? ap.k_new : ap.v_new;
-            const Tensor &dst = threadIdx.x < 16 ? ap.k : ap.v;
-            *reinterpret_cast<uint4 *>(dst.ptr + b * dst.sb + h * dst.sh + (int64_t)(L_raw - 1) * dst.st + c8) =
-                *reinterpret_cast<const uint4 *>(src.ptr + b * src.sb + h * src.sh + c8);
-        }
-        closes = live && L_raw >= kKernel && (L_raw - kKernel) % kStride == 0;
-    }
+    if (!kAppend && (int)blockIdx.x >= n_part) return;
     int n_vis[kQT], n_vis_max = 0;                    // query slot t sits at L-1: n_c((L-1)+1); 0 = no such row
 #pragma unroll
     for (int t = 0; t < kQT; ++t) {
@@ -201,54 +217,53 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
         n_vis_max = max(n_vis_max, n_vis[t]);
     }
     if ((int)blockIdx.x * kChunk >= n_vis_max) return;    // uniform over the workgroup
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    const int jw = blockIdx.x * kChunk + wave * 16 * kTW; // first kernel of this wave
-    const int G = dm.G;
+    bf16x8 a[kTW][4];
+    // Rows past the last kernel repeat it, and those that this launch completes may or may not be there yet: their scores are masked or their
+    // operands replaced below.
+    const __bf16 *ck_wave = ck.ptr + ck_wave_at;
+    if (jw + 16 * kTW <= n_vis_max) {                 // uniform over the wave
+#pragma unroll
+        for (int i = 0; i < kTW; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a[i][ks] = load8(ck_wave + 16 * i * ck.st + ck_lane + 32 * ks);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kTW; ++i) {
+            const int64_t at = min(16 * i + n, n_vis_max - 1 - jw) * ck.st + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a[i][ks] = load8(ck_wave + at + 32 * ks);
+        }
+    }
     const int build_from = max(new_from, (int)blockIdx.x * kChunk), build_to = min(n_vis_max, (int)(blockIdx.x + 1) * kChunk);
     const bool builds = kAppend && kQT > 1 && build_from < build_to;   // uniform over the workgroup
     if constexpr (kAppend && kQT > 1)
-        if (builds) {                                 // 32 lanes per kernel: new rows from the call's inputs, older ones from the cache
-            const int c = (threadIdx.x & 31) * 4, jh = build_from + (threadIdx.x >> 5), first_new = L_all - dm.n_q;
-            if (jh < build_to) {
-                const __bf16 *kb = ap.k.ptr + b * ap.k.sb + h * ap.k.sh + c, *nb = ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + c;
-                double acc[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = 0.0;
-                uint2 row[kKernel];
-#pragma unroll
-                for (int t = 0; t < kKernel; ++t) {
-                    const int r = jh * kStride + t;
-                    row[t] = *reinterpret_cast<const uint2 *>(r >= first_new ? nb + (int64_t)(r - first_new) * ap.k_new.st : kb + (int64_t)r * ap.k.st);
-                }
+        if (builds) {
+            // A wave per kernel, lane = channels 2*lane, 2*lane + 1; new rows from the call's inputs, older ones from the cache.  Rows' addresses are
+            // scalar.  (A workgroup that builds ends last: with 32 lanes of four channels and addresses per lane it took 14000 cycles, so 9000.)
+            for (int jh = build_from + wave; jh < build_to; jh += 4) {
+                const int t_new = L_all - dm.n_q - jh * kStride;          // rows t_new .. of the kernel are new ones
+                const int64_t old_at = b * ap.k.sb + h * ap.k.sh + (int64_t)jh * kStride * ap.k.st;
+                const int64_t new_at = b * ap.k_new.sb + h * ap.k_new.sh - (int64_t)t_new * ap.k_new.st;
+                uint32_t row[kKernel];
 #pragma unroll
                 for (int t = 0; t < kKernel; ++t) {
-                    acc[0] += (double)__uint_as_float(row[t].x << 16);
-                    acc[1] += (double)__uint_as_float(row[t].x & 0xffff0000u);
-                    acc[2] += (double)__uint_as_float(row[t].y << 16);
-                    acc[3] += (double)__uint_as_float(row[t].y & 0xffff0000u);
+                    const __bf16 *p = t < t_new ? ap.k.ptr + (old_at + t * ap.k.st) : ap.k_new.ptr + (new_at + t * ap.k_new.st);
+                    row[t] = reinterpret_cast<const uint32_t *>(p)[lane];
                 }
-                uint32_t w[4];
+                double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = f64_to_bf16_rne(acc[e] / (double)kKernel);
-                const uint2 x = {w[0] | w[1] << 16, w[2] | w[3] << 16};
-                *reinterpret_cast<uint2 *>(&newrows[(threadIdx.x >> 5) * kQsPitch + c]) = x;
-                if (qi0 + kQT >= dm.n_q)              // the last query tile sees every kernel: it stores them
-                    *reinterpret_cast<uint2 *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh * ck.st + c) = x;
+                for (int t = 0; t < kKernel; ++t) {
+                    s0 += (double)__uint_as_float(row[t] << 16);
+                    s1 += (double)__uint_as_float(row[t] & 0xffff0000u);
+                }
+                const uint32_t x = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) | ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+                *reinterpret_cast<uint32_t *>(&newrows[(jh - build_from) * kQsPitch + 2 * lane]) = x;
+                if (qi0 + kQT >= dm.n_q)                  // the last query tile sees every kernel: it stores them
+                    reinterpret_cast<uint32_t *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh * ck.st)[lane] = x;
             }
         }
-    __builtin_amdgcn_sched_barrier(0);                // (the rows' registers are free again)
-    bf16x8 a[kTW][4], bq[kQT][4];
-#pragma unroll
-    for (int i = 0; i < kTW; ++i) {
-        const __bf16 *ckr = ck.ptr + b * ck.sb + h * ck.sh + (int64_t)(jw + 16 * i + n) * ck.st + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            a[i][ks] = zero8();
-            if (jw + 16 * i + n < (kAppend && kQT > 1 ? min(n_vis_max, new_from) : n_vis_max)) a[i][ks] = load8(ckr + 32 * ks);
-        }
-    }
-    load_query_operands<kQT>(dm, q, b, h, qi0, qs, bq);   // heads >= G repeat head G-1: their columns are never used
+    bf16x8 bq[kQT][4];
+    query.get(qs, bq);
     if constexpr (kAppend && kQT > 1)
         if (builds) {                                 // (a barrier lies between: the query rows went through LDS too)
 #pragma unroll
@@ -265,13 +280,11 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
         const int jh_new = n_vis_max - 1;             // = (L - p) / s when the new token closes a kernel
         if (closes && jh_new >= jw && jh_new < jw + 16 * kTW) {       // uniform over the wave
             // lane = channels 2*lane, 2*lane+1: rows L-32 .. L-2 from the cache, row L-1 from k_new
-            const int L = L_all;
-            const __bf16 *kc = ap.k.ptr + b * ap.k.sb + h * ap.k.sh + 2 * lane;
+            const __bf16 *kc = ap.k.ptr + (b * ap.k.sb + h * ap.k.sh + (int64_t)(L_all - kKernel) * ap.k.st);
             uint32_t rowv[kKernel];
 #pragma unroll
-            for (int t = 0; t < kKernel - 1; ++t)
-                rowv[t] = *reinterpret_cast<const uint32_t *>(kc + (int64_t)(L - kKernel + t) * ap.k.st);
-            rowv[kKernel - 1] = *reinterpret_cast<const uint32_t *>(ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + 2 * lane);
+            for (int t = 0; t < kKernel - 1; ++t) rowv[t] = reinterpret_cast<const uint32_t *>(kc + t * ap.k.st)[lane];
+            rowv[kKernel - 1] = reinterpret_cast<const uint32_t *>(ap.k_new.ptr + (b * ap.k_new.sb + h * ap.k_new.sh))[lane];
             double s0 = 0.0, s1 = 0.0;
 #pragma unroll
             for (int t = 0; t < kKernel; ++t) {
@@ -437,97 +450,125 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 // Z = Q . CK^T: lane = kernel (column), 4 accumulator entries = 4 consecutive heads.  A lane adds its 4
 // heads; the four 16-lane groups leave their sums side by side in LDS and the pooling adds them, so
 // no cross-lane traffic sits between the matrix cores and the scores.
+// Eight wavefronts: a workgroup has a compute unit to itself, and one wavefront per SIMD issues an instruction every other slot.
 template <int kQT, int kTW>
-__global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, Tensor ck,
+__global__ __launch_bounds__(512) void decode_scores_kernel(Dims dm, Tensor q, Tensor ck,
                                                              const int32_t *__restrict__ seqlens,
                                                              const float2 *__restrict__ part, int32_t n_part,
-                                                             void *__restrict__ found, int32_t list_len, int32_t pitch) {
-    constexpr int kChunk = 64 * kTW, kTiles = 4 * kTW + 1;
+                                                             void *__restrict__ found, int32_t list_len, int32_t pitch, uint32_t n_qt_inv) {
+    constexpr int kWaves = 8, kTiles = 4 * kTW + 1, kPerWave = 4 * kTW / kWaves;
+    constexpr int kChunk = 64 * kTW;
     constexpr int kBlocks = 16 * kTW;                 // of a list
-    static_assert(kBlocks <= 64 && kQT * kBlocks <= 256, "a lane per block, a query within a wavefront");
+    static_assert(kBlocks <= 64 && kBlocks % 16 == 0 && kQT * kBlocks <= 256 && kPerWave >= 1, "a lane per block, a query within a wavefront");
     constexpr int kChunk1 = 64 * kVerifyTiles;  // kernels per partial of part 1
-    constexpr int kLanesPerPair = 256 / (16 * kQT);   // lanes that merge the partials of one (query, head)
-    constexpr int kMaxPartsPerLane = 16384 / kChunk1 / kLanesPerPair;   // contexts up to 262144 tokens
+    constexpr int kLanesPerPair = 64 * kWaves / (16 * kQT);   // lanes that merge the partials of one (query, head)
+    static_assert(kLanesPerPair == 8, "half a row of lanes");
+    constexpr int kRound = 4 * 2 * kLanesPerPair;     // partials of a head that are merged at a time: 128K tokens' (of at most 262144 tokens')
     __shared__ __align__(16) float lse_h[kQT][16];
-    __shared__ float rs[kQT][4][kTiles * 16];         // per 16-lane group: head sums of kernels chunk-16 .. chunk+kChunk-1
-    __shared__ __align__(16) uint16_t qs[kQT > 1 ? kQT * 16 * kQsPitch : 8];
+    __shared__ __align__(16) float4 rs[kQT][kTiles * 16];   // head sums of kernels chunk-16 .. chunk+kChunk-1, by 16-lane group
+    __shared__ __align__(16) uint16_t qs[kQT * 16 * kQsPitch];
     __shared__ __align__(16) uint64_t words[kQT][16 * kTW];
+    arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.n_q, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, part, n_part, n_qt_inv);
+    arguments_arrive(q.ptr, q.sb, q.sh, q.st, dm.scale_log2, dm.rho, found, list_len, pitch, dm.topk, dm.n_init, dm.n_local);
     const int h = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int G = dm.G;
     const int n_qt = (dm.n_q + kQT - 1) / kQT;
-    const int b = kQT == 1 ? blockIdx.z : blockIdx.z / n_qt;   // kQT = 1 is only launched with n_q = 1
+    const int b = n_qt == 1 ? blockIdx.z : (int)__umulhi(blockIdx.z, n_qt_inv);
     const int qi0 = (blockIdx.z - b * n_qt) * kQT;
-    const int L_all = clamp_len(seqlens[b], dm.max_seqlen);
+    const int32_t L_raw = uniform_load(seqlens + b);
+    const int first = (int)blockIdx.x * kChunk - 16;  // kernel of rs[.][.][0]
+    const int tile0 = 1 + wave * kPerWave;            // this wave's kernel tiles (tile 0 is the halo, taken by the last wave)
+    int64_t ck_head = b * ck.sb + h * ck.sh, ck_wave_at = ck_head + (int64_t)(first + 16 * tile0) * ck.st, ck_lane = n * ck.st + 8 * g;
+    asm volatile("" : "+s"(ck_wave_at), "+s"(ck_head), "+v"(ck_lane));
+    const int L_all = clamp_len(L_raw, dm.max_seqlen);
     int L_max = 0;
 #pragma unroll
     for (int t = 0; t < kQT; ++t) L_max = max(L_max, row_len(dm, L_all, qi0 + t));
-    if (L_max < 1 || (int)blockIdx.x * 16 * kTW > (L_max - 1) / kBlock) return;    // no block of this chunk exists
+    if (L_max < 1 || (int)blockIdx.x * kBlocks > (L_max - 1) / kBlock) return;    // no block of this chunk exists
     const int n_vis_max = num_kernels(L_max);
-    const int first = (int)blockIdx.x * kChunk - 16;  // kernel of rs[.][.][0]
-    // ---- operand loads: this wave's kernel tiles (tile 0 is the halo, taken by wave 3), the query rows ----
-    bf16x8 aq[kQT][4], bk[kTW + 1][4];
+    // ---- operand loads: rows past the last kernel repeat it, and are left out of the pooling ----
+    bf16x8 aq[kQT][4], bk[kPerWave + 1][4];
+    if (n_vis_max > 0) {                              // uniform over the workgroup
+        const int from = first + 16 * tile0;
+        const __bf16 *ck_wave = ck.ptr + ck_wave_at;
+        const bool all = from + 16 * kPerWave <= n_vis_max;                       // uniform over the wave
 #pragma unroll
-    for (int i = 0; i <= kTW; ++i) {
-        const int tile = i < kTW ? 1 + wave * kTW + i : 0;
-        const int jh = first + 16 * tile + n;
-        const bool have = (i < kTW || wave == 3) && jh >= 0 && jh < n_vis_max;
-        const __bf16 *ckr = ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh * ck.st + 8 * g;
+        for (int i = 0; i < kPerWave; ++i) {
+            const int64_t at = all ? 16 * i * ck.st + ck_lane : min(16 * i + n, n_vis_max - 1 - from) * ck.st + 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            bk[i][ks] = zero8();
-            if (have) bk[i][ks] = load8(ckr + 32 * ks);
+            for (int ks = 0; ks < 4; ++ks) bk[i][ks] = load8(ck_wave + at + 32 * ks);
         }
+        if (wave == kWaves - 1) {
+            const __bf16 *ck_halo = ck.ptr + ck_head + (int64_t)max(min(first + n, n_vis_max - 1), 0) * ck.st + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bk[kPerWave][ks] = load8(ck_halo + 32 * ks);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i <= kPerWave; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) bk[i][ks] = zero8();
     }
-    // ---- log-sum-exp per (query, head): kLanesPerPair lanes each, all loads of a lane issued together ----
+    __builtin_amdgcn_sched_barrier(0);
+    const QueryOperands<kQT, 64 * kWaves> query(dm, q, b, h, qi0);
+    // ---- log-sum-exp per (query, head): kLanesPerPair lanes each, two partials to a load ----
     {
         const int pair = tid / kLanesPerPair, sub = tid % kLanesPerPair;
-        const int t = pair >> 4, head = pair & 15;
-        const int np = (num_kernels(row_len(dm, L_all, qi0 + t)) + kChunk1 - 1) / kChunk1;   // valid partials
-        const int64_t bv = (int64_t)b * dm.n_q + min(qi0 + t, dm.n_q - 1);
+        const int pt = pair >> 4, head = pair & 15;
+        const int64_t bv = (int64_t)b * dm.n_q + min(qi0 + pt, dm.n_q - 1);
         const float2 *pr = part + ((bv * dm.Hkv + h) * G + min(head, G - 1)) * n_part;
-        float2 v[kMaxPartsPerLane];
+        const int np = (num_kernels(row_len(dm, L_all, qi0 + pt)) + kChunk1 - 1) / kChunk1;  // valid partials
+        float M = -INFINITY, S = 0.f;
+        for (int p0 = 0; p0 < n_part; p0 += kRound) {
+            float4 v[4];                              // (n_part is even, a row begins at a multiple of 16 bytes)
 #pragma unroll
-        for (int i = 0; i < kMaxPartsPerLane; ++i) {
-            const int p = sub + kLanesPerPair * i;
-            v[i] = float2{-INFINITY, 0.f};
-            if (p < np) v[i] = pr[p];
+            for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4 *>(pr + min(p0 + 2 * (sub + kLanesPerPair * i), n_part - 2));
+            float m = M;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int p = p0 + 2 * (sub + kLanesPerPair * i);
+                if (p >= np) v[i].x = -INFINITY, v[i].y = 0.f;
+                if (p + 1 >= np) v[i].z = -INFINITY, v[i].w = 0.f;
+                m = fmaxf(m, fmaxf(v[i].x, v[i].z));
+            }
+            const float mu = m == -INFINITY ? 0.f : m;
+            S *= fast_exp2(M - mu);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S += v[i].y * fast_exp2(v[i].x - mu) + v[i].w * fast_exp2(v[i].z - mu);
+            M = m;
         }
-        float m = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < kMaxPartsPerLane; ++i) m = fmaxf(m, v[i].x);
-#pragma unroll
-        for (int o = 1; o < kLanesPerPair; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        float m = M;                                  // over the pair's eight lanes
+        m = fmaxf(m, dpp_rotate<kSwap1>(m));
+        m = fmaxf(m, dpp_rotate<kSwap2>(m));
+        m = fmaxf(m, dpp_rotate<kMirror8>(m));
         const float mu = m == -INFINITY ? 0.f : m;
-        float sm = 0.f;
-#pragma unroll
-        for (int i = 0; i < kMaxPartsPerLane; ++i) sm += v[i].y * fast_exp2(v[i].x - mu);
-#pragma unroll
-        for (int o = 1; o < kLanesPerPair; o <<= 1) sm += __shfl_xor(sm, o);
-        if (sub == 0)      // approximate mode: rho times fewer kernels were summed; 0 when none is visible
-            lse_h[t][head] = dm.rho > 1 ? (m == -INFINITY ? 0.f : m + fast_log2(sm) + (float)(31 - __clz(dm.rho)))
-                                        : m + fast_log2(sm);
+        float sm = S * fast_exp2(M - mu);
+        sm += dpp_rotate<kSwap1>(sm);
+        sm += dpp_rotate<kSwap2>(sm);
+        sm += dpp_rotate<kMirror8>(sm);
+        // approximate mode: rho times fewer kernels were summed; 0 when none is visible
+        const float exact = m + fast_log2(sm), coarse = m == -INFINITY ? 0.f : exact + (float)(31 - __clz(dm.rho));
+        if (sub == 0) lse_h[pt][head] = head >= G ? INFINITY : dm.rho > 1 ? coarse : exact;   // (heads that are not there score 0)
     }
-    load_query_operands<kQT>(dm, q, b, h, qi0, qs, aq);     // (a barrier inside when kQT > 1)
-    __syncthreads();
+    query.get(qs, aq);                                // (a barrier inside)
     // ---- head sums of exp(z - lse) ------------------------------------------------------------------------
 #pragma unroll
     for (int t = 0; t < kQT; ++t) {
         const float4 l4 = *reinterpret_cast<const float4 *>(&lse_h[t][4 * g]);
         const float lh[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-        for (int i = 0; i <= kTW; ++i) {
-            if (i == kTW && wave != 3) break;         // uniform over the wave
-            const int tile = i < kTW ? 1 + wave * kTW + i : 0;
+        for (int i = 0; i <= kPerWave; ++i) {
+            if (i == kPerWave && wave != kWaves - 1) break;   // uniform over the wave
+            const int tile = i < kPerWave ? tile0 + i : 0;
             f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) z = mfma16(aq[t][ks], bk[i][ks], z);
             float acc = 0.f;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (4 * g + r < G) acc += fast_exp2(z[r] * dm.scale_log2 - lh[r]);
-            rs[t][g][16 * tile + n] = acc;
+            for (int r = 0; r < 4; ++r) acc += fast_exp2(z[r] * dm.scale_log2 - lh[r]);
+            reinterpret_cast<float *>(&rs[t][16 * tile + n])[g] = acc;
         }
     }
     __syncthreads();
@@ -540,9 +581,11 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
 #pragma unroll
         for (int x = 0; x < 5; ++x) {
             const int c = 4 * jl + 15 + x, jh = first + c;
-            const float sum = (rs[t][0][c] + rs[t][1][c]) + (rs[t][2][c] + rs[t][3][c]);
-            if (jh >= 0 && jh < n_vis) v = fmaxf(v, fminf(fmaxf(sum * (1.f / G), kScoreFloor), kScoreCeil));
+            const float4 y = rs[t][c];
+            const float sum = (y.x + y.y) + (y.z + y.w);
+            v = fmaxf(v, jh >= 0 && jh < n_vis ? sum : -INFINITY);
         }
+        v = max(first + 4 * jl + 15, 0) < n_vis ? fminf(fmaxf(v * (1.f / G), kScoreFloor), kScoreCeil) : -INFINITY;
         const int64_t row = ((int64_t)b * dm.n_q + qi0 + t) * dm.Hkv + h;
         if (list_len == 0) {
             if (j <= (L - 1) / kBlock) reinterpret_cast<float *>(found)[row * pitch + j] = v;
@@ -550,10 +593,17 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(Dims dm, Tensor q, T
         }
         const RowRange rr(dm, L);
         const uint64_t e = pick_element(v, j, rr.n_init, rr.jc_max);
+        uint64_t *list = reinterpret_cast<uint64_t *>(found) + (row * gridDim.x + blockIdx.x) * list_len;
+        if (list_len <= 16) {                         // by sorting networks, as in plain decode: a query's two or four rows of lanes
+            uint64_t x = row_sort64(e, lane);
+            x = kBlocks == 64 ? rows_merge64(x, lane) : row_pairs_merge64(x, lane);
+            if (jl < list_len) list[jl] = x;
+            return;
+        }
         words[t][jl] = e;
         __builtin_amdgcn_wave_barrier();              // same wavefront: LDS keeps the order
         const int rank = count_larger(words[t], kBlocks, e);   // no two words are equal
-        if (rank < list_len) reinterpret_cast<uint64_t *>(found)[(row * gridDim.x + blockIdx.x) * list_len + rank] = e;
+        if (rank < list_len) list[rank] = e;
     }
 }
 
@@ -1533,14 +1583,19 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     void *found = wsb + l.found;
     const int rows = dm.batch * dm.n_q;                              // <= 65535, checked by the C ABI
     const int n_qt = (dm.n_q + kVerifyQT - 1) / kVerifyQT;
+    const uint32_t n_qt_inv = n_qt > 1 ? (uint32_t)((1ull << 32) / (uint32_t)n_qt) + 1u : 0u;   // i / n_qt, as n_q_inv
     const float2 *part_lse = dm.rho > 1 ? part_c : part;
     timing_begin("decode_logits_kernel", stream);
     const AppendArgs no_append = {q, q, q, q};                       // unused placeholders
     const bool tw4 = decode_tiles_per_wave(dm) == 4;
-    const dim3 grid1(l.n_part, dm.Hkv, dm.batch);
+    // Behind the chunks, workgroups that append; several query tiles per sequence: a multiple of eight, so that all tiles of a chunk run
+    // on one XCD and its kernels come from memory once.
+    int32_t n_wg = l.n_part + (append ? (dm.n_q + 7) / 8 : 0);
+    if (n_qt > 1) n_wg = (n_wg + 7) / 8 * 8;
+    const dim3 grid1(n_wg, dm.Hkv, dm.batch);
 #define INFLLMV2_LOGITS(APPEND, TW, ARG)                                                                        \
     hipLaunchKernelGGL((decode_logits_kernel<1, APPEND, TW>), grid1, dim3(256), 0, stream, dm, q, ck, seqlens, \
-                       zbuf, l.n_c_cap, part, part_c, l.n_part, ARG)
+                       zbuf, l.n_c_cap, part, part_c, l.n_part, ARG, 0u)
     if (dm.n_q == 1 && append) {
         if (tw4) INFLLMV2_LOGITS(true, 4, *append);
         else INFLLMV2_LOGITS(true, 2, *append);
@@ -1548,13 +1603,13 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
         if (tw4) INFLLMV2_LOGITS(false, 4, no_append);
         else INFLLMV2_LOGITS(false, 2, no_append);
     } else {
-        const dim3 grid(l.n_part, dm.Hkv, dm.batch * n_qt);
+        const dim3 grid(n_wg, dm.Hkv, dm.batch * n_qt);
         if (append)
             hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, true, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
-                               nullptr, 0, part, part_c, l.n_part, *append);
+                               nullptr, 0, part, part_c, l.n_part, *append, n_qt_inv);
         else
             hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, false, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
-                               nullptr, 0, part, part_c, l.n_part, no_append);
+                               nullptr, 0, part, part_c, l.n_part, no_append, n_qt_inv);
     }
 #undef INFLLMV2_LOGITS
     timing_end(stream);
@@ -1565,8 +1620,8 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
                            reinterpret_cast<uint64_t *>(found), l.list_len);
     else
         hipLaunchKernelGGL((l.list_blocks == 64 ? decode_scores_kernel<kVerifyQT, 4> : decode_scores_kernel<kVerifyQT, 2>),
-                           dim3(l.n_lists, dm.Hkv, dm.batch * n_qt), dim3(256), 0, stream, dm, q, ck, seqlens, part_lse, l.n_part,
-                           found, l.list_len, l.nb_cap);
+                           dim3(l.n_lists, dm.Hkv, dm.batch * n_qt), dim3(512), 0, stream, dm, q, ck, seqlens, part_lse, l.n_part,
+                           found, l.list_len, l.nb_cap, n_qt_inv);
     timing_end(stream);
     const bool lists = l.list_len > 0;
     const int n_elements = lists ? l.n_lists * l.list_len : (dm.max_seqlen + kBlock - 1) / kBlock;
