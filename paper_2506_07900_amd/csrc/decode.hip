@@ -58,7 +58,7 @@ struct QueryOperands {
         const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
         const int G = dm.G;
         if constexpr (kQT == 1) {
-            const __bf16 *qr = q.ptr + (b * q.sb + (int64_t)(h * G) * q.sh) + (min(n, G - 1) * q.sh + 8 * g);   // (one query: n_q = 1)
+            const __bf16 *qr = q.ptr + (b * q.sb + qi0 * q.st + (int64_t)(h * G) * q.sh) + (min(n, G - 1) * q.sh + 8 * g);
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) x[ks] = load8(qr + 32 * ks);
         } else {
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     const int G = dm.G;
     __builtin_amdgcn_sched_barrier(0);
     // (queries and kernels are cold, 3200 cycles away from an idle unit: both are asked for before anything else is worked out)
-    const QueryOperands<kQT> query(dm, q, b, h, qi0);     // heads >= G repeat head G-1: their columns are never used
+    const QueryOperands<kQT> query(dm, q, b, h, kQT == 1 ? 0 : qi0);      // heads >= G repeat head G-1: their columns are never used
     __builtin_amdgcn_sched_barrier(0);
     const int jw = blockIdx.x * kChunk + wave * 16 * kTW; // first kernel of this wave
     int64_t ck_wave_at = b * ck.sb + h * ck.sh + (int64_t)jw * ck.st, ck_lane = n * ck.st + 8 * g;   // (worked out while the length is on its way)
@@ -997,18 +997,13 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_kernel(Dims dm, cons
 constexpr int kVsPitch = kHeadDim + 4;               // bf16 elements per LDS value row: 4 rows of a transposing load in 4 bank groups
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-// What the fetch of a block does not need the block for: the query's operands, and where the thread's rows lie, value rows tid/16 + 16i (channels
-// 8(tid%16) ..), key row 16 wave + n (channels 32ks + 8g ..).  Worked out, and the queries asked for, before the block is known: a wavefront alone spends 2000
+// What the fetch of a block does not need the block for: where the thread's rows lie, value rows tid/16 + 16i (channels
+// 8(tid%16) ..), key row 16 wave + n (channels 32ks + 8g ..).  Worked out before the block is known: a wavefront alone spends 2000
 // cycles on these arguments and products otherwise, and left to itself the compiler moves them to where the block is known.
 struct BlockFetch {
     int64_t k_head, v_head;                              // uniform: the head's first row
     int64_t v[4], k;
-    bf16x8 bq[4];
-    __device__ BlockFetch(const Dims &dm, const Tensor &q, const Tensor &kt, const Tensor &vt, int b, int qi, int h) {
-        const int tid = threadIdx.x, lane = tid & 63;
-        const __bf16 *qr = q.ptr + b * q.sb + qi * q.st + (int64_t)(h * dm.G + min(lane & 15, dm.G - 1)) * q.sh + 8 * (lane >> 4);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
+    __device__ void set(const Dims &dm, const Tensor &kt, const Tensor &vt, int b, int h) {
         k_head = b * kt.sb + h * kt.sh;
         v_head = b * vt.sb + h * vt.sh;
         rows(kt, vt, kBlock - 1);
@@ -1028,7 +1023,7 @@ struct BlockFetch {
 // the row's ascending list, where the partial result goes; it is called while the block's rows are on their way.
 // kFresh: row fresh_row of the caches (-1: none) is being written by this very launch: it is taken from fresh.k_new / v_new.
 template <bool kFresh, typename Place>
-__device__ inline void attend_block(const Dims &dm, const Tensor &k, const Tensor &v, BlockFetch fetch,
+__device__ inline void attend_block(const Dims &dm, const Tensor &k, const Tensor &v, BlockFetch fetch, const bf16x8 (&bq)[4],
                                     int bv, int b, int qi, int h, int L, int blk, const uint64_t *__restrict__ tree_mask,
                                     float *__restrict__ o_part, float2 *__restrict__ ml_part, Place place,
                                     const AppendArgs *fresh = nullptr, int fresh_row = -1) {
@@ -1062,18 +1057,19 @@ __device__ inline void attend_block(const Dims &dm, const Tensor &k, const Tenso
     const int c8 = tid & 15, vr = tid >> 4;
     uint4 vrow[4];
     bf16x8 a[4];
-    const bf16x8(&bq)[4] = fetch.bq;
     {
         if (key0 + kBlock > dm.max_seqlen) fetch.rows(k, v, dm.max_seqlen - 1 - key0);
         const __bf16 *kr = k.ptr + (fetch.k_head + (int64_t)key0 * k.st) + fetch.k;
         const __bf16 *vb = v.ptr + (fetch.v_head + (int64_t)key0 * v.st);
-        if (kFresh && key0 + 16 * wave + n == fresh_row) kr = fresh->k_new.ptr + b * fresh->k_new.sb + h * fresh->k_new.sh + 8 * g;
+        // (its block is the last: all others' addresses are left alone)
+        const bool fresh_here = kFresh && fresh_row >= key0 && fresh_row < key0 + kBlock;      // uniform
+        if (fresh_here && key0 + 16 * wave + n == fresh_row) kr = fresh->k_new.ptr + b * fresh->k_new.sb + h * fresh->k_new.sh + 8 * g;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) a[ks] = load8(kr + 32 * ks);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const __bf16 *vp = vb + fetch.v[i];
-            if (kFresh && key0 + vr + 16 * i == fresh_row) vp = fresh->v_new.ptr + b * fresh->v_new.sb + h * fresh->v_new.sh + 8 * c8;
+            if (fresh_here && key0 + vr + 16 * i == fresh_row) vp = fresh->v_new.ptr + b * fresh->v_new.sb + h * fresh->v_new.sh + 8 * c8;
             vrow[i] = *reinterpret_cast<const uint4 *>(vp);
         }
     }
@@ -1164,8 +1160,11 @@ __global__ __launch_bounds__(256) void decode_attn_partial_kernel(Dims dm, Tenso
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
     const int blk = block_idx[(((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk + cidx];
-    const BlockFetch fetch(dm, q, k, v, b, qi, h);
-    attend_block<false>(dm, k, v, fetch, bv, b, qi, h, L, __builtin_amdgcn_readfirstlane(blk), tree_mask, o_part, ml_part,
+    bf16x8 bq[1][4];
+    QueryOperands<1>(dm, q, b, h, qi).get(nullptr, bq);
+    BlockFetch fetch;
+    fetch.set(dm, k, v, b, h);
+    attend_block<false>(dm, k, v, fetch, bq[0], bv, b, qi, h, L, __builtin_amdgcn_readfirstlane(blk), tree_mask, o_part, ml_part,
                         [cidx] { return cidx; });
 }
 
@@ -1192,7 +1191,10 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
     Picker<kForm, kN> picker(in, (int64_t)bv * dm.Hkv + h);
     int b, qi;
     const int L = query_row(dm, seqlens, bv, b, qi);
-    const BlockFetch fetch(dm, q, k, v, b, qi, h);
+    bf16x8 bq[1][4];
+    QueryOperands<1>(dm, q, b, h, qi).get(nullptr, bq);
+    BlockFetch fetch;
+    fetch.set(dm, k, v, b, h);
     int32_t *orow = block_idx + (((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
     __shared__ __align__(16) int mine[kPickWaves][64];
     const int wave = threadIdx.x >> 6;
@@ -1213,7 +1215,7 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
             if (cidx < n_sel) blk = mine_at;
         }
     }
-    attend_block<false>(dm, k, v, fetch, bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
+    attend_block<false>(dm, k, v, fetch, bq[0], bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [&] {
         if (n_sel == 0) return at;
         const int rank = order_row(mine[wave], n_sel, dm.topk, cidx == 0 && wave == 0 ? orow : nullptr);
         return cidx < n_sel ? __builtin_amdgcn_readlane(rank, cidx) : cidx;
@@ -1225,12 +1227,12 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
 // in registers, so nothing of the selection has to pass through memory and the step is two launches, this one and the
 // merge, instead of four -- each of which costs 1.3 to 1.9 us between kernels and a round trip to memory before it does
 // anything.  Every one of the k workgroups of a (sequence, key-value head) repeats the selection (128 KB of compressed
-// keys at most, from L2) and attends its own entry of the result; workgroup 0 writes the row and, in a step, the caches.
+// keys at most, from L2) and attends its own entry of the result; workgroup 0 writes the row.
 // In a graph, us per step, four launches -> two: 2K G = 4 13.5 -> 8.3, one sequence of 4000 tokens 16.1 -> 11.5, 8000
 // 16.1 -> 14.4; 32 sequences of 8000, three launches: 25.8 -> 23.9.
 //   mode 0: block list only (infllmv2_select_blocks)       grid (1, Hkv, B)
-//   mode 1: append + block list (steps with many rows)      grid (1, Hkv, B)
-//   mode 2: append + block list + partial attention         grid (topk, Hkv, B)
+//   mode 1: append + block list (steps with many rows)      grid (2, Hkv, B)
+//   mode 2: append + block list + partial attention         grid (topk + 1, Hkv, B)   (the last workgroup appends)
 // Wave w scores kernels 16 kTW w .. +16 kTW - 1, Z = Q . CK^T: lane = kernel, accumulator entries = heads 4g .. 4g+3.
 constexpr int kShortTokens = 8192;
 template <int kTW, int kMode>
@@ -1245,53 +1247,69 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     __shared__ int counts[4][kWords];
     __shared__ int sel[4][64];                            // per wavefront: the selected blocks, ascending
     __shared__ __align__(16) uint32_t newrow[kMode > 0 ? 64 : 4];
+    arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.topk, dm.n_init, dm.n_local, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, block_idx);
+    arguments_arrive(q.ptr, q.sb, q.sh, dm.scale_log2, dm.Hq, o_part, ml_part);
     const int cidx = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int G = dm.G;
-    const int32_t L_raw = __builtin_amdgcn_readfirstlane(seqlens[b]);
+    const int32_t L_raw = uniform_load(seqlens + b);
+    __builtin_amdgcn_sched_barrier(0);
+    const QueryOperands<1> query(dm, q, b, h, 0);
+    const int jw = 16 * kTW * wave;                       // this wave's first kernel
+    int64_t ck_wave_at = b * ck.sb + h * ck.sh + (int64_t)jw * ck.st, ck_lane = n * ck.st + 8 * g;       // (while the length is on its way)
+    asm volatile("" : "+s"(ck_wave_at), "+v"(ck_lane));
+    if (kMode > 0 && cidx == (kMode == 2 ? dm.topk : 1)) {                    // behind the others: copies the new rows into the caches
+        const int c8 = (tid & 15) * 8;
+        if (L_raw < 1 || L_raw > dm.max_seqlen || tid >= 32) return;
+        if (tid < 16)
+            *reinterpret_cast<uint4 *>(ap.k.ptr + b * ap.k.sb + h * ap.k.sh + (int64_t)(L_raw - 1) * ap.k.st + c8) =
+                *reinterpret_cast<const uint4 *>(ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + c8);
+        else
+            *reinterpret_cast<uint4 *>(ap.v.ptr + b * ap.v.sb + h * ap.v.sh + (int64_t)(L_raw - 1) * ap.v.st + c8) =
+                *reinterpret_cast<const uint4 *>(ap.v_new.ptr + b * ap.v_new.sb + h * ap.v_new.sh + c8);
+        return;
+    }
     const int L = clamp_len(L_raw, dm.max_seqlen);
     const bool live = kMode > 0 && L_raw >= 1 && L_raw <= dm.max_seqlen;      // as the stand-alone append: others are skipped
     int32_t *orow = block_idx + ((int64_t)b * dm.Hkv + h) * dm.topk;
-    int blk = -1;
-    if (live && cidx == 0 && tid < 32) {
-        const int c8 = (tid & 15) * 8;
-        const Tensor &src = tid < 16 ? ap.k_new : ap.v_new;
-        const Tensor &dst = tid < 16 ? ap.k : ap.v;
-        *reinterpret_cast<uint4 *>(dst.ptr + b * dst.sb + h * dst.sh + (int64_t)(L_raw - 1) * dst.st + c8) =
-            *reinterpret_cast<const uint4 *>(src.ptr + b * src.sb + h * src.sh + c8);
+    const int n_vis = num_kernels(L);
+    const RowRange rr(dm, max(L, 1));
+    bf16x8 a[kTW][4], bq[1][4];
+    if (n_vis > 0 && rr.n_pick > 0) {                     // (otherwise every block is forced, or there is nothing to score)
+        const __bf16 *ck_wave = ck.ptr + ck_wave_at;
+        const bool all = jw + 16 * kTW <= n_vis;          // uniform over the wave; rows past the last kernel repeat it and are masked below
+#pragma unroll
+        for (int i = 0; i < kTW; ++i) {
+            const int64_t at = all ? 16 * i * ck.st + ck_lane : min(16 * i + n, n_vis - 1 - jw) * ck.st + 8 * g;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a[i][ks] = load8(ck_wave + at + 32 * ks);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kTW; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a[i][ks] = zero8();
     }
+    __builtin_amdgcn_sched_barrier(0);
+    query.get(nullptr, bq);
+    std::conditional_t<kMode == 2, BlockFetch, int> fetch{};
+    if constexpr (kMode == 2) fetch.set(dm, ap.k, ap.v, b, h);
+    int blk = -1;
     if (L < 1) {                                          // uniform over the workgroup
         if (cidx == 0 && tid < dm.topk) orow[tid] = -1;
     } else {
-        const int n_vis = num_kernels(L);
-        const RowRange rr(dm, L);
-        bf16x8 a[kTW][4], bq[4];
-        const int jw = 16 * kTW * wave;
-        if (rr.n_pick > 0) {                              // (otherwise every block is forced: nothing to score)
-            const __bf16 *ckh = ck.ptr + b * ck.sb + h * ck.sh + 8 * g;
-#pragma unroll
-            for (int i = 0; i < kTW; ++i) {               // rows past the last kernel repeat it and are masked below
-                const __bf16 *ckr = ckh + (int64_t)max(min(jw + 16 * i + n, n_vis - 1), 0) * ck.st;
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) a[i][ks] = jw + 16 * i < n_vis ? load8(ckr + 32 * ks) : zero8();
-            }
-            const __bf16 *qr = q.ptr + b * q.sb + (int64_t)(h * G + min(n, G - 1)) * q.sh + 8 * g;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) bq[ks] = load8(qr + 32 * ks);
-        }
         if constexpr (kMode > 0) {
             // the semantic kernel the new token completes: rows L-32 .. L-2 from the cache, row L-1 from k_new, fp64 sum in
             // token order, one rounding (the bits of compress_keys_kernel); lane = channels 2*lane, 2*lane+1
             const int jh_new = n_vis - 1;
             const bool closes = live && L >= kKernel && (L - kKernel) % kStride == 0;
             if (closes && jh_new >= jw && jh_new < jw + 16 * kTW && (rr.n_pick > 0 || cidx == 0)) {   // uniform over the wave
-                const __bf16 *kc = ap.k.ptr + b * ap.k.sb + h * ap.k.sh + 2 * lane;
+                const __bf16 *kc = ap.k.ptr + (b * ap.k.sb + h * ap.k.sh + (int64_t)(L - kKernel) * ap.k.st);
                 uint32_t rowv[kKernel];
 #pragma unroll
-                for (int t = 0; t < kKernel - 1; ++t)
-                    rowv[t] = *reinterpret_cast<const uint32_t *>(kc + (int64_t)(L - kKernel + t) * ap.k.st);
-                rowv[kKernel - 1] = *reinterpret_cast<const uint32_t *>(ap.k_new.ptr + b * ap.k_new.sb + h * ap.k_new.sh + 2 * lane);
+                for (int t = 0; t < kKernel - 1; ++t) rowv[t] = reinterpret_cast<const uint32_t *>(kc + t * ap.k.st)[lane];
+                rowv[kKernel - 1] = reinterpret_cast<const uint32_t *>(ap.k_new.ptr + (b * ap.k_new.sb + h * ap.k_new.sh))[lane];
                 double s0 = 0.0, s1 = 0.0;
 #pragma unroll
                 for (int t = 0; t < kKernel; ++t) {
@@ -1325,7 +1343,7 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
             for (int i = 0; i < kTW; ++i) {
                 f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) z = mfma16(bq[ks], a[i][ks], z);
+                for (int ks = 0; ks < 4; ++ks) z = mfma16(bq[0][ks], a[i][ks], z);
                 const bool vis = jw + 16 * i + n < n_vis;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -1413,7 +1431,7 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
         if (cidx < rr.n_sel) blk = __builtin_amdgcn_readfirstlane(mine[cidx]);
     }
     if constexpr (kMode == 2)
-        attend_block<true>(dm, ap.k, ap.v, BlockFetch(dm, q, ap.k, ap.v, b, 0, h), b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
+        attend_block<true>(dm, ap.k, ap.v, fetch, bq[0], b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
                            live ? L_raw - 1 : -1);
 }
 
@@ -1541,7 +1559,7 @@ static bool fuse_short(const Dims &dm) {
 template <int kMode>
 static int launch_short(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap, const int32_t *seqlens, int32_t *block_idx,
                         float *o_part, float2 *ml_part, hipStream_t stream) {
-    const dim3 grid(kMode == 2 ? dm.topk : 1, dm.Hkv, dm.batch), block(256);
+    const dim3 grid((kMode == 2 ? dm.topk : 1) + (kMode > 0 ? 1 : 0), dm.Hkv, dm.batch), block(256);
     timing_begin("decode_short_kernel", stream);
 #define INFLLMV2_SHORT(TW) \
     hipLaunchKernelGGL((decode_short_kernel<TW, kMode>), grid, block, 0, stream, dm, q, ck, seqlens, ap, block_idx, o_part, ml_part)
