@@ -45,31 +45,39 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(Dims dm, Tensor k, Tensor 
                                                        float *__restrict__ lse) {
     __shared__ __align__(16) __bf16 Ks[kBlock * 136];
     __shared__ __align__(16) __bf16 Vs[kBlock * 136];
+    arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.fill, seqlens, k.ptr, k.sb, k.sh, k.st, kvp, nb_cap);
+    arguments_arrive(v.ptr, v.sb, v.sh, v.st);
     const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    int32_t L = seqlens[b];
+    int32_t L = uniform_load(seqlens + b);
+    const int tid = threadIdx.x, sc = tid & 15, sr = tid >> 4;
+    const __bf16 *kb = k.ptr + (b * k.sb + h * k.sh + (int64_t)j * kBlock * k.st), *vb = v.ptr + (b * v.sb + h * v.sh + (int64_t)j * kBlock * v.st);
     L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
-    const int tid = threadIdx.x;
-    if (dm.fill)                                         // this head's rows of the block's tokens past the end: out = 0, lse = 0
+    auto clear_rows = [&]() {                            // this head's rows of the block's tokens past the end: out = 0, lse = 0
         for (int t = max(j * kBlock, (int)L) + (tid >> 4); t < min((j + 1) * kBlock, dm.max_seqlen); t += 16)
             for (int hq = h * dm.G; hq < (h + 1) * dm.G; ++hq) {
                 *reinterpret_cast<uint4 *>(out.ptr + b * out.sb + (int64_t)t * out.st + (int64_t)hq * out.sh + 8 * (tid & 15)) =
                     uint4{0u, 0u, 0u, 0u};
                 if ((tid & 15) == 0) lse[((int64_t)b * dm.max_seqlen + t) * dm.Hq + hq] = 0.f;
             }
-    if (j * kBlock >= L) return;
-    const int sc = tid & 15, sr = tid >> 4;
-    const __bf16 *kb = k.ptr + b * k.sb + h * k.sh;
-    const __bf16 *vb = v.ptr + b * v.sb + h * v.sh;
+    };
+    const int last = L - 1 - j * kBlock;                 // the block's last row; rows past it repeat it and are stored as zeros
+    if (last < 0) {
+        if (dm.fill) clear_rows();
+        return;
+    }
+    uint4 xk[4], xv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int r = sr + 16 * i, t = j * kBlock + r;
-        uint4 xk = {0u, 0u, 0u, 0u}, xv = {0u, 0u, 0u, 0u};
-        if (t < L) {
-            xk = *reinterpret_cast<const uint4 *>(kb + (int64_t)t * k.st + 8 * sc);
-            xv = *reinterpret_cast<const uint4 *>(vb + (int64_t)t * v.st + 8 * sc);
-        }
-        *reinterpret_cast<uint4 *>(&Ks[r * 136 + 8 * sc]) = xk;
-        *reinterpret_cast<uint4 *>(&Vs[r * 136 + 8 * sc]) = xv;
+        xk[i] = *reinterpret_cast<const uint4 *>(kb + min(sr + 16 * i, last) * k.st + 8 * sc);
+        xv[i] = *reinterpret_cast<const uint4 *>(vb + min(sr + 16 * i, last) * v.st + 8 * sc);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (dm.fill && last < kBlock - 1) clear_rows();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (sr + 16 * i > last) xk[i] = xv[i] = uint4{0u, 0u, 0u, 0u};
+        *reinterpret_cast<uint4 *>(&Ks[(sr + 16 * i) * 136 + 8 * sc]) = xk[i];
+        *reinterpret_cast<uint4 *>(&Vs[(sr + 16 * i) * 136 + 8 * sc]) = xv[i];
     }
     __syncthreads();
     uint4 *dst = kvp + ((((int64_t)b * dm.Hkv + h) * nb_cap + j) * kPackedBlockU4);
@@ -172,21 +180,21 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
                                                             const uint4 *__restrict__ kvp, int32_t nb_cap,
                                                             const int32_t *__restrict__ seqlens,
                                                             const int32_t *__restrict__ block_idx,
-                                                            Tensor out, float *__restrict__ lse,
-                                                            int32_t slots) {
+                                                            Tensor out, float *__restrict__ lse) {
     using C = AttnCfg<kG, kTiles, kSplit>;
     constexpr int kNU = 4, kTPT = C::kTokPerTile, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per wavefront; member bits in one word");
     extern __shared__ __align__(16) unsigned char attn_smem[];
-    // grid: 8 XCDs x slots x (sequence, key-value head); see launch_attn_variant
-    const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
-    const int h = bh % dm.Hkv, b = bh / dm.Hkv;
+    arguments_arrive(dm.Hkv, dm.topk, dm.max_seqlen, seqlens, block_idx, kvp, nb_cap, q.ptr, q.sb, q.sh, q.st, dm.scale_log2);
+    // grid (8 XCDs x slots, key-value heads, sequences); see launch_attn_variant
+    const int xcd = blockIdx.x & 7, sl = blockIdx.x >> 3, h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // Tiles are dealt last first, counted from the sequence's end.  Direct fetches, which are for short buffers, count them from the
     // capacity: their rows of block lists are asked for before the length has arrived (100 tokens 5.9 -> 5.4 us, 250 10.5 -> 9.9).  In
     // longer ones the workgroups of the tiles behind the sequence would all start, and wait for both, before the first real one:
     // 777 tokens in a buffer of 131072, G = 8, 33 us, counted from the capacity 57; in one of their own length, G = 16, 21.6 and 21.5.
-    int32_t L = __builtin_amdgcn_readfirstlane(seqlens[b]);
+    int32_t L = uniform_load(seqlens + b);
+    const __bf16 *q_head = q.ptr + (b * q.sb + (int64_t)(h * kG) * q.sh);     // (while the length is on its way)
     if (!kDirect) L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
     const int last = kDirect ? dm.max_seqlen : L;
     const int tile = (last + C::kTokPerWg - 1) / C::kTokPerWg - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);
@@ -213,28 +221,34 @@ __global__ __launch_bounds__(256, (AttnCfg<kG, kTiles, kSplit>::kWavesPerSimd)) 
     const int tn = n / kG;                               // token of the column inside its tile
     const float c = dm.scale_log2;
 
+    // The queries are asked for before the union is built, and go to LDS behind it.  (Columns of tokens past the end repeat the last one's and are
+    // not written.)
     bf16x8 qf[C::kQLds ? 1 : kTiles][4];
     bf16x8 *ql = reinterpret_cast<bf16x8 *>(attn_smem + C::queries_at(dm.topk)) +                // [tile][ks][lane]
                  (kSplit > 1 ? 0 : wave * kTiles * 4 * 64) + lane;
+    constexpr int kLoad = C::kQLds && kSplit > 1 ? 1 : kTiles;           // the waves that share their tokens load a tile each
+    bf16x8 qx[kLoad][4];
     f32x4 o[kTiles][8];
     float neg_m[kTiles], l_run[kTiles];
 #pragma unroll
-    for (int u = 0; u < kTiles; ++u) {
-        const int tok = t0 + u * kTPT + tn;
-        const __bf16 *qr = q.ptr + b * q.sb + (int64_t)tok * q.st + (int64_t)(h * kG + n % kG) * q.sh + 8 * g;
-        if (!C::kQLds || kSplit == 1 || wave == u) {     // (the waves that share their tokens load a tile each)
+    for (int i = 0; i < kLoad; ++i) {
+        const int u = kLoad < kTiles ? min(wave, kTiles - 1) : i;
+        const __bf16 *qr = q_head + ((int64_t)min(t0 + u * kTPT + tn, (int)L - 1) * q.st + (n % kG) * q.sh + 8 * g);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 x = tok < L ? load8(qr + 32 * ks) : zero8();
-                if constexpr (C::kQLds) ql[(u * 4 + ks) * 64] = x;
-                else qf[u][ks] = x;
-            }
-        }
+        for (int ks = 0; ks < 4; ++ks) qx[i][ks] = load8(qr + 32 * ks);
     }
     const UnionLds ul(attn_smem + (kSplit > 1 ? 0 : wave * UnionLds::bytes(kTok, dm.topk)));
     int cnt = 0;
     if (kSplit == 1 || wave == 0)
         cnt = build_union<kTok>(idx_head, idx_rows, dm.topk, min(kTok, (int)L - t0), b_own, ul, lane);
+#pragma unroll
+    for (int i = 0; i < kLoad; ++i)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            if constexpr (!C::kQLds) qf[i][ks] = qx[i][ks];
+            else if constexpr (kLoad == kTiles) ql[(i * 4 + ks) * 64] = qx[i][ks];
+            else if (wave < kTiles) ql[(wave * 4 + ks) * 64] = qx[i][ks];
+        }
     if constexpr (kSplit > 1) {
         __shared__ int cnt_s;
         if (threadIdx.x == 0) cnt_s = cnt;
@@ -748,15 +762,14 @@ static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, con
     using C = AttnCfg<kG, kTiles, kSplit>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTokPerWg - 1) / C::kTokPerWg;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
-    const int64_t n_wg = (int64_t)slots * 8 * dm.Hkv * dm.batch;
     const size_t lds = C::lds_bytes(dm.topk);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)attn_prefill_kernel<kG, kTiles, kSplit, kDirect>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit, kDirect>), dim3((uint32_t)n_wg), dim3(256), lds, stream,
-                       dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, slots);
+    hipLaunchKernelGGL((attn_prefill_kernel<kG, kTiles, kSplit, kDirect>), dim3(slots * 8, dm.Hkv, dm.batch), dim3(256), lds, stream,
+                       dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse);
     return 0;
 }
 
