@@ -54,6 +54,13 @@ constexpr int kDkdvGroups = 256 * 4;
 constexpr int kShareRows = 32 * kDkdvGroups;
 constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
 constexpr int kMostSteps = 64;
+// A short call, of at most one item per workgroup and few enough bins for one look at all of them (8192 tokens and heads together), has no use for
+// the queues: a workgroup finds its item by its own number and ends with it.  (Drawn from the queues, every workgroup asked all eight for
+// more, one round trip after another.)  Where items are fewer than the compute units, several workgroups take a part of an item's steps each; more
+// parts than that lose to the sums: the chip adds about 270 words per ns, 61 ns per item or part of one (500 tokens, G = 16, 130 items: 32 us in
+// one part, 36 / 74 in three / seven, 13 in seven without the sums).  dk/dv, 2 heads, top-k 16, queues / now, us: G = 16, 150 tokens 39 / 14,
+// 500 47 / 32, 1000 66 / 64; G = 8, 500 42 / 20; G = 1, 500 29 / 12, 1000 33 / 16, 2000 38 / 24.
+constexpr int kPartGroups = 256, kMostParts = 4;
 __host__ __device__ constexpr int least_steps(int G) { return G == 16 ? 8 : 12; }
 __host__ __device__ inline int members_of(int steps, int G) {
     const int m = (steps < least_steps(G) ? least_steps(G) : steps) * 32 / G;
@@ -782,6 +789,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     __shared__ BwdSlot slot0, slot1;
     __shared__ uint4 item_s;
     __shared__ int tries_s, total_s;
+    __shared__ int part_s, parts_s;                       // a short call's workgroup: its part of an item, of how many (0: items from the queues)
     __shared__ __align__(16) uint32_t bins_s[kBins];                  // items in the queue's bins up to this one
     __shared__ BwdBins geo;                               // `bins`, which would hold scalar registers through the walk
     const int tid = threadIdx.x, lane = tid & 63;
@@ -814,11 +822,38 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     };
     if (wave == 0) {
         geo = bins;                                       // by every lane: each reads what it has written itself
-        look_at(0);
+        uint4 it = {0u, 0u, 0u, 0u};
+        int parts = 0, part = 0;
+        if (bins.n <= kSlices) {                          // every bin of every queue in one look
+            const uint32_t n = counters[(lane >> 3) * bins.stride + (lane & 7)], behind = counters[kQueues * bins.stride];
+            const uint32_t incl = (uint32_t)wave_inclusive_sum((int)n), queued = __builtin_amdgcn_readlane(incl, 63);
+            const uint32_t all = queued + __builtin_amdgcn_readfirstlane(behind);
+            if (all <= (uint32_t)kDkdvGroups) {
+                parts = max(1, min(kMostParts, kPartGroups / max((int)all, 1)));
+                // neighbours in the queues' order, which share rows, to one XCD
+                const uint32_t ids = all * (uint32_t)parts, per = ids >> 3, rem = ids & 7u, xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+                if (slot < per + (xcd < rem ? 1u : 0u)) {
+                    const uint32_t id = xcd * per + (xcd < rem ? xcd : rem) + slot, t = id / (uint32_t)parts;
+                    part = (int)(id - t * (uint32_t)parts);
+                    int64_t at = geo.begin(kQueues, 0) + (int64_t)(t - queued);
+                    if (t < queued) {
+                        const int bin = __popcll(__ballot(incl <= t));
+                        at = geo.begin(bin >> 3, bin & 7) + (int64_t)(t - (bin ? __builtin_amdgcn_readlane(incl, bin - 1) : 0u));
+                    }
+                    it = geo.unpack(items[at]);
+                }
+            }
+        }
+        if (parts == 0) look_at(0);
+        if (lane == 0) {
+            item_s = it;
+            parts_s = parts;
+            part_s = part;
+        }
     }
     for (;;) {
         // ---- next item ----------------------------------------------------------------------------------------------
-        if (wave == 0) {
+        if (wave == 0 && parts_s == 0) {
             uint4 it = {0u, 0u, 0u, 0u};
             for (int x = __builtin_amdgcn_readfirstlane(tries_s);;) {   // ends: a queue that is found empty stays empty
                 const uint32_t drawn = __builtin_amdgcn_readfirstlane(ticket), t = drawn & ~kBehind;
@@ -870,7 +905,10 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         }
         __syncthreads();
         const int total = __builtin_amdgcn_readfirstlane(total_s);
-        const int steps = (total + kTPS - 1) / kTPS;
+        const int all_steps = (total + kTPS - 1) / kTPS, parts = __builtin_amdgcn_readfirstlane(parts_s);
+        const int part = __builtin_amdgcn_readfirstlane(part_s);
+        const int from = parts ? all_steps * part / parts : 0, steps = parts ? all_steps * (part + 1) / parts : all_steps;
+        if (from >= steps) return;                        // (more parts than steps)
 
         const __bf16 *s_base = s_ptr + b * s_sb + (int64_t)(h * kG) * s_sh + (int64_t)tok0 * s_st;
         asm volatile("" : "+s"(s_base));
@@ -993,15 +1031,15 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                 dk[i & 3] = mfma32(sf[i >> 2], xb[i & 1], dk[i & 3]);
             }
         };
-        stage(slot0, 0);
-        for (int p = 0;;) {
+        stage(slot0, from);
+        for (int p = from;;) {
             step(slot0, slot1, p);
             if (++p >= steps) break;
             step(slot1, slot0, p);
             if (++p >= steps) break;
         }
         // ---- add to the block's sums: an instruction covers 32 channels of two keys, two cache lines ------------------------
-        if (tid == 0) ticket = draw(tries_s);             // the next item's place, under way meanwhile
+        if (tid == 0 && parts_s == 0) ticket = draw(tries_s);       // the next item's place, under way meanwhile
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int64_t o = ((int64_t)bh * dm.max_seqlen + (int64_t)j * kBlock + 32 * kh + 4 * (ln >> 5)) * kHeadDim + (ln & 31);
@@ -1021,6 +1059,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         if (tok0 >= (j + 1) * kBlock) walk(std::false_type{});
         else walk(std::true_type{});
         __builtin_amdgcn_s_waitcnt(0);                    // the copies past the end have landed: the slots may be filled anew
+        if (parts_s != 0) return;                         // uniform
         __syncthreads();
     }
 }

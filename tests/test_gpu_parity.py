@@ -1087,6 +1087,14 @@ def test_sparse_attn_backward_items_of_large_shares(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
+# Short calls, whose workgroups find their item by number: four parts of an item (more than it has steps: 2), three, two and one; windows of one to
+# eight queues; and just past eight windows, from the queues again.
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([40], 1, 1, 8), ([1], 2, 2, 3), ([260, 65], 16, 1, 8), ([1000, 900, 65, 7], 2, 1, 4),
+                                                 ([1100], 16, 1, 16), ([8000], 1, 1, 8), ([8200], 1, 1, 8)])
+def test_sparse_attn_backward_items_by_number(seqlens, Hq, Hkv, topk):
+    test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
+
+
 # Lists in which all blocks are equally popular, so that their items end at the same tokens: more than a bin holds (47 of 1125 items, 42 of
 # 462, where a bin has three places and a window's tails), the rest from the list behind the queues.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([10000], 2, 1, 16), ([1969, 1969], 6, 3, 3)])
