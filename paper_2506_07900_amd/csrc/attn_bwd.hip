@@ -10,8 +10,8 @@
 // membership words (word of 32 tokens x block) built from the block lists, so both big kernels accumulate
 // in registers:
 //   pack_bwd_kernel     fragment-major copies of every block (K rows, V rows), its tokens' membership bits, its cleared sums
-//   bwd_items_kernel    the members of every block, cut into work items, queued per XCD by the tokens they hold
-//   attn_bwd_dq_kernel  workgroup = 1 to 4 MFMA tiles of 16 (token, head) columns, walks the union of the tokens' block lists:
+//   attn_bwd_dq_kernel  first the members of every block, cut into work items, queued per XCD by the tokens they hold (cut_items); then
+//                       workgroup = 1 to 4 MFMA tiles of 16 (token, head) columns, walks the union of the tokens' block lists:
 //                       D, then S^T = K.Q^T, dP^T = V.dO^T, dQ^T += K^T.dS^T
 //   attn_bwd_dkdv_kernel  workgroup = one item of a block after the other, wavefront = 32 keys x 128 channels:
 //                       S = Q.K^T, dP = dO.V^T, dV += P^T.dO, dK += dS^T.Q over steps of 32 (token, head) rows
@@ -29,7 +29,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBwdBlockU4 = 2 * 16 * 64;              // uint4 per packed block: K rows, V rows (32 KiB)
-// The scatter's work items (see bwd_items_kernel): a block with some of the tokens of a segment of kSegWords words of 32 tokens.  A
+// The scatter's work items (see cut_items): a block with some of the tokens of a segment of kSegWords words of 32 tokens.  A
 // segment has a window per XCD, a window kSlices slices, the XCD's queue a bin per slice (or run of slices).
 constexpr int kSegWords = 256;
 constexpr int kQueues = 8;                            // one per XCD
@@ -48,7 +48,7 @@ constexpr uint32_t kBehind = 1u << 31;                // in a queue's place draw
 // 8.  A share of the capacity instead of the call's tokens leaves most of the chip idle: 777 tokens in a buffer of 2000, top-k 8, 65 us, so
 // 52; in one of 4096, top-k 16, 112 and 54.  So does one that takes all sequences for as long as the item's own: with the cutting, G = 8,
 // 300 + 100 + 900 + 64 tokens 77 us, so 56; G = 16, 1500 + 200 + 800 129 and 100.  From 96 on a share is rounded up to whole words (see
-// bwd_items_kernel): blocks that every token selects are then cut evenly, G = 8, 5000 + 700 tokens, 136 -> 160 members, 129 -> 111 us,
+// cut_items): blocks that every token selects are then cut evenly, G = 8, 5000 + 700 tokens, 136 -> 160 members, 129 -> 111 us,
 // 4096 + 3333, 236 -> 256, 168 -> 162.  Smaller ones grow too much by it: 1500 + 200 + 800, 80 -> 96, 100 -> 112.
 constexpr int kDkdvGroups = 256 * 4;
 constexpr int kShareRows = 32 * kDkdvGroups;
@@ -263,22 +263,35 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(Dims dm, Tensor k, Tensor
 // tokens' q and dout rows, and a block that few tokens
 // select is cut once per 8192 of them: every item costs 32 KiB of K and V and 64 KiB of atomic sums (four times the items: 1190 -> 2210 us
 // for 32K tokens).  Against segments of 2048 tokens, queued as their wavefronts finished: dk/dv 1220 -> 1120 us at 32K tokens, G = 16
-// (segments of 4096: 1100 with the windows' order, 1150 with 2048); this kernel 11.5 -> 9.6 us there and 11.4 -> 6.5 us for
+// (segments of 4096: 1100 with the windows' order, 1150 with 2048); the cutting 11.5 -> 9.6 us there and 11.4 -> 6.5 us for
 // 2 x 4096 tokens (a thread per block walked its words twice, one after the other).  The slices' order instead of the order in which the
 // wavefronts finished inside a window (1024 tokens are 8 MiB of rows, an XCD's L2 holds 4): misses 64 -> 54 million lines, dk/dv by
 // itself the same, the backward call 2410 -> 2350 us at 32K tokens, 10950 -> 10850 at 128K (fewer lines from the far cache: the clock
-// stays higher in dq too).  With windows dealt by their place in the segment, four sequences of 4096 tokens kept half the
+// stays higher in dq too).  Workgroups in front of dq's, which does not need them: as a launch of its own, of 5 to 10 us, 500 tokens, G = 8,
+// the whole backward 46.8 -> 41.8 us, training step of 2 x 4096 453.5 -> 449.6.  With windows dealt by their place in the segment, four sequences of 4096 tokens kept half the
 // queues empty: 1125 -> 1110.
 constexpr int kItemBlocks = 4;
-__global__ __launch_bounds__(256) void bwd_items_kernel(Dims dm, const int32_t *__restrict__ seqlens, const uint32_t *__restrict__ bits,
-                                                         int32_t nb_cap, int32_t n_seg, int64_t rows_per_block, BwdBins bins,
-                                                         uint32_t *__restrict__ counters, uint64_t *__restrict__ items) {
+struct BwdItems {                                         // where they come from and go
+    const uint32_t *bits;
+    uint32_t *counters;
+    uint64_t *items;
+    int64_t rows_per_block;
+    int32_t n_seg, groups;                                // workgroups per sequence and head, a multiple of 8
+    BwdBins bins;
+};
+__device__ __forceinline__ void cut_items(const Dims &dm, const int32_t *__restrict__ seqlens, int32_t nb_cap, const BwdItems &to_cut) {
+    const uint32_t *__restrict__ bits = to_cut.bits;
+    uint32_t *__restrict__ counters = to_cut.counters;
+    uint64_t *__restrict__ items = to_cut.items;
+    int64_t rows_per_block = to_cut.rows_per_block;
+    const int32_t n_seg = to_cut.n_seg;
+    BwdBins bins = to_cut.bins;
     static_assert(kSegWords == 4 * 64 && kWindowWords == 4 * 8 && kSlices == 8, "four words a lane, eight lanes a window, one a slice");
     // (the arguments arrive together, not one round trip after another where each is first used)
     asm volatile("" : "+s"(bins.shift), "+s"(bins.cap), "+s"(bins.tail), "+s"(bins.window), "+s"(bins.size), "+s"(bins.stride),
                  "+s"(bins.block_bits), "+s"(rows_per_block), "+s"(counters), "+s"(items));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int seg = blockIdx.x % n_seg, j0 = (int)(blockIdx.x / n_seg * 4 + wave) * kItemBlocks;
+    const int seg = (int)(blockIdx.x % (uint32_t)n_seg), j0 = (int)(blockIdx.x / (uint32_t)n_seg * 4 + wave) * kItemBlocks;
     const int h = blockIdx.y, b = blockIdx.z;
     const int64_t bh = (int64_t)b * dm.Hkv + h;
     const int L = seq_len(dm, seqlens, b);
@@ -429,17 +442,20 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
                                                               int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                               const int32_t *__restrict__ block_idx,
                                                               const float *__restrict__ lse,
-                                                              float *__restrict__ rowc, Tensor dq, int32_t slots) {
+                                                              float *__restrict__ rowc, Tensor dq, BwdItems to_cut) {
     using C = DqCfg<kG, kTiles>;
     constexpr int kRing = kDqRing, kTPT = C::kTPT, kTok = C::kTok;
     static_assert(64 % kTok == 0 && kTok <= 32, "one own block per workgroup; member bits in one word");
     extern __shared__ __align__(16) unsigned char dq_smem[];
     float2 *row_s = reinterpret_cast<float2 *>(dq_smem + C::kRowBytes + C::kQueryBytes);   // [tile][column]: -lse log2(e), D
     int &cnt_s = *reinterpret_cast<int *>(dq_smem + C::kUnionAt + UnionLds::bytes(kTok, dm.topk));
-    const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x >> 3) % slots, bh = (int)(blockIdx.x >> 3) / slots;
-    const int h = bh % dm.Hkv, b = bh / dm.Hkv;
+    if ((int)blockIdx.x < to_cut.groups) return cut_items(dm, seqlens, nb_cap, to_cut);
+    arguments_arrive(dm.Hkv, dm.Hq, dm.topk, dm.max_seqlen, dm.fill, seqlens, block_idx, q.ptr, q.sb, q.st, q.sh, lse);
+    arguments_arrive(out.ptr, out.sb, out.st, out.sh, dout.ptr, dout.sb, dout.st, dout.sh, dm.scale_log2, kvb, nb_cap, rowc);
+    const int xcd = blockIdx.x & 7, sl = (int)(blockIdx.x - to_cut.groups) >> 3, h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int L = __builtin_amdgcn_readfirstlane(seq_len(dm, seqlens, b));
+    int32_t L = uniform_load(seqlens + b);
+    L = L < 0 ? 0 : (L > dm.max_seqlen ? dm.max_seqlen : L);
     const int n_tiles = (L + kTok - 1) / kTok, tile = n_tiles - 1 - (((sl / kRun) * 8 + xcd) * kRun + sl % kRun);   // (see the forward's launch)
     const int t0 = tile * kTok;
     if (dm.fill) {                                        // rows past the end: this tile's, or those of a tile behind the last
@@ -452,62 +468,72 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
         }
     }
     if (tile < 0) return;                                 // uniform over the workgroup
+    // Lists and rows are asked for before anything waits; the union is built meanwhile, by a wavefront that has no rows of its own to turn where
+    // there is one (2 x 500 tokens: one tile, G = 1, 10.9 -> 7.5 us; two tiles, G = 16, 15.8 -> 14.7).  With several tiles a wavefront brings one to
+    // LDS, with one each keeps it and the first forms D.
+    const int union_wave = C::kLds && kTiles == 4 ? 0 : 3;
     const int32_t *idx_rows = block_idx + (((int64_t)b * dm.Hkv + h) * dm.max_seqlen + t0) * dm.topk;
-    const UnionRows<kTok> idx_head(idx_rows, wave == 0 ? min(kTok, L - t0) * dm.topk : 0, lane);
+    const UnionRows<kTok> idx_head(idx_rows, wave == union_wave ? min(kTok, L - t0) * dm.topk : 0, lane);
     const int b_own = t0 / kBlock;
     const int n = lane & 15, g = lane >> 4;               // MFMA column (token, query head) and 16-lane group
     const int tn = n / kG;
     const float c = dm.scale_log2;
 
-    bf16x8 qf[C::kLds ? 1 : kTiles][4], gf[C::kLds ? 1 : kTiles][4];
+    static_assert(C::kLds || kTiles == 1, "a tile a wavefront, or one for all");
+    bf16x8 qf[1][4], gf[1][4];
     bf16x8 *ql = reinterpret_cast<bf16x8 *>(dq_smem + C::kRowBytes) + lane;   // [q | dout][tile][ks][lane]
     f32x4 acc[kTiles][8];
+    const int own = C::kLds ? wave : 0;                   // tile
+    const bool forms_d = C::kLds ? wave < kTiles : wave == 0;
+    const int tok_d = t0 + own * kTPT + tn, tk = min(tok_d, L - 1);
+    const int row_d = h * kG + n % kG;
+    bf16x8 xo[4];
+    float ls = 0.f;
+    if (!C::kLds || wave < kTiles) {
+        const __bf16 *qr = q.ptr + b * q.sb + (tk * q.st + row_d * q.sh + 8 * g);
+        const __bf16 *gr = dout.ptr + b * dout.sb + (tk * dout.st + row_d * dout.sh + 8 * g);
 #pragma unroll
-    for (int u = 0; u < kTiles; ++u) {
-        const int tok = t0 + u * kTPT + tn, tk = min(tok, L - 1);
-        const int64_t row = (int64_t)(h * kG + n % kG);
-        if (!C::kLds || wave == u) {
-            const __bf16 *qr = q.ptr + b * q.sb + (int64_t)tk * q.st + row * q.sh + 8 * g;
-            const __bf16 *gr = dout.ptr + b * dout.sb + (int64_t)tk * dout.st + row * dout.sh + 8 * g;
-            const __bf16 *orow = out.ptr + b * out.sb + (int64_t)tk * out.st + row * out.sh + 8 * g;
-            float d = 0.f;                                // D = <dout, out> of the row
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 xq = load8(qr + 32 * ks), xg = load8(gr + 32 * ks);
-                if (wave == u) {
-                    const bf16x8 xo = load8(orow + 32 * ks);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) d = __builtin_fmaf((float)xo[e], (float)xg[e], d);
-                }
-                if constexpr (C::kLds) {
-                    ql[(u * 4 + ks) * 64] = xq;
-                    ql[((kTiles + u) * 4 + ks) * 64] = xg;
-                } else {
-                    qf[u][ks] = xq;
-                    gf[u][ks] = xg;
-                }
-            }
-            if (wave == u) {
-                d = xgroup_sum(d);
-                const float ls = lse[((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row];
-                // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
-                const float ne = (ls > -INFINITY && ls < INFINITY) ? -ls * kLog2e : -INFINITY;
-                if (g == 0) {
-                    row_s[u * 16 + n] = float2{tok < L ? ne : -INFINITY, d};
-                    // the same for dk and dv, per (token, key-value head): G exponent offsets, then G times D
-                    float *rec = rowc + (((int64_t)b * dm.max_seqlen + tk) * dm.Hkv + h) * (2 * kG) + n % kG;
-                    if (tok < L) {
-                        rec[0] = ne;
-                        rec[kG] = d;
-                    }
-                }
-            }
+        for (int ks = 0; ks < 4; ++ks) {
+            qf[0][ks] = load8(qr + 32 * ks);
+            gf[0][ks] = load8(gr + 32 * ks);
         }
     }
+    if (forms_d) {
+        const __bf16 *orow = out.ptr + b * out.sb + (tk * out.st + row_d * out.sh + 8 * g);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) xo[ks] = load8(orow + 32 * ks);
+        ls = lse[((int64_t)b * dm.max_seqlen + tk) * dm.Hq + row_d];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const UnionLds ul(dq_smem + C::kUnionAt);
-    if (wave == 0) {
+    if (wave == union_wave) {
         const int x = build_union<kTok>(idx_head, idx_rows, dm.topk, min(kTok, L - t0), b_own, ul, lane);
         if (lane == 0) cnt_s = x;
+    }
+    if (forms_d) {
+        float d = 0.f;                                    // D = <dout, out> of the row
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d = __builtin_fmaf((float)xo[ks][e], (float)gf[0][ks][e], d);
+        if constexpr (C::kLds)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                ql[(own * 4 + ks) * 64] = qf[0][ks];
+                ql[((kTiles + own) * 4 + ks) * 64] = gf[0][ks];
+            }
+        d = xgroup_sum(d);
+        // p = 2^(s*c - lse*log2e); a dead column (no such token, or a row that attended nothing) gets p = 0
+        const float ne = (ls > -INFINITY && ls < INFINITY) ? -ls * kLog2e : -INFINITY;
+        if (g == 0) {
+            row_s[own * 16 + n] = float2{tok_d < L ? ne : -INFINITY, d};
+            // the same for dk and dv, per (token, key-value head): G exponent offsets, then G times D
+            float *rec = rowc + (((int64_t)b * dm.max_seqlen + tk) * dm.Hkv + h) * (2 * kG) + n % kG;
+            if (tok_d < L) {
+                rec[0] = ne;
+                rec[kG] = d;
+            }
+        }
     }
     __syncthreads();
     const int cnt = __builtin_amdgcn_readfirstlane(cnt_s);
@@ -718,7 +744,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(Dims dm, Tensor q, 
 
 template <int kG, int kTiles>
 static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                             const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
+                             const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, const BwdItems &to_cut, hipStream_t stream) {
     using C = DqCfg<kG, kTiles>;
     const int32_t n_tiles = (dm.max_seqlen + C::kTok - 1) / C::kTok;
     const int32_t slots = (n_tiles + 8 * kRun - 1) / (8 * kRun) * kRun;
@@ -728,8 +754,8 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, 
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<kG, kTiles>), dim3((uint32_t)((int64_t)slots * 8 * dm.Hkv * dm.batch)), dim3(256), lds,
-                       stream, dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, slots);
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<kG, kTiles>), dim3(to_cut.groups + slots * 8, dm.Hkv, dm.batch), dim3(256), lds,
+                       stream, dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut);
     return 0;
 }
 
@@ -740,13 +766,13 @@ static int launch_dq_variant(const Dims &dm, Tensor q, Tensor out, Tensor dout, 
 // G = 1 is 16 tokens and four would not fit the 32 member bits.
 template <int kG>
 static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, const uint4 *kvb, int32_t nb_cap, const int32_t *seqlens,
-                           const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, hipStream_t stream) {
+                           const int32_t *block_idx, const float *lse, float *rowc, Tensor dq, const BwdItems &to_cut, hipStream_t stream) {
     const int64_t rows = (int64_t)dm.batch * dm.max_seqlen * dm.Hkv;
     constexpr int kTPT = 16 / kG;
     if constexpr (kG > 1)
-        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
-    return launch_dq_variant<kG, 1>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, stream);
+        if (rows >= (int64_t)512 * 4 * kTPT) return launch_dq_variant<kG, 4>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream);
+    if (rows >= (int64_t)192 * 2 * kTPT) return launch_dq_variant<kG, 2>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream);
+    return launch_dq_variant<kG, 1>(dm, q, out, dout, kvb, nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream);
 }
 
 // ---- dk, dv of one block from the tokens that selected it ------------------------------------------------------
@@ -1119,18 +1145,16 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
     hipLaunchKernelGGL(pack_bwd_kernel, dim3(l.nb_cap, dm.Hkv, dm.batch), dim3(256), 0, stream, dm, k, v, seqlens, kvb,
                        l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, (kQueues + 1) * l.bins.stride, null_row);
     timing_end(stream);
-    timing_begin("bwd_items_kernel", stream);
-    hipLaunchKernelGGL(bwd_items_kernel, dim3((uint32_t)(l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks))), dm.Hkv, dm.batch),
-                       dim3(256), 0, stream, dm, seqlens, bits, l.nb_cap, l.n_seg, rows_per_block(dm), l.bins, counters, items);
-    timing_end(stream);
+    const int32_t groups = l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks));
+    const BwdItems to_cut = {bits, counters, items, rows_per_block(dm), l.n_seg, (groups + 7) & ~7, l.bins};
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {
-        case 1: err = launch_dq_group<1>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
-        case 2: err = launch_dq_group<2>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
-        case 4: err = launch_dq_group<4>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
-        case 8: err = launch_dq_group<8>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
-        case 16: err = launch_dq_group<16>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, stream); break;
+        case 1: err = launch_dq_group<1>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream); break;
+        case 2: err = launch_dq_group<2>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream); break;
+        case 4: err = launch_dq_group<4>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream); break;
+        case 8: err = launch_dq_group<8>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream); break;
+        case 16: err = launch_dq_group<16>(dm, q, out, dout, kvb, l.nb_cap, seqlens, block_idx, lse, rowc, dq, to_cut, stream); break;
     }
     if (err) return err;
     timing_end(stream);
