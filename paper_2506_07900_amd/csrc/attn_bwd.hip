@@ -50,26 +50,32 @@ constexpr uint32_t kBehind = 1u << 31;                // in a queue's place draw
 // 300 + 100 + 900 + 64 tokens 77 us, so 56; G = 16, 1500 + 200 + 800 129 and 100.  From 96 on a share is rounded up to whole words (see
 // cut_items): blocks that every token selects are then cut evenly, G = 8, 5000 + 700 tokens, 136 -> 160 members, 129 -> 111 us,
 // 4096 + 3333, 236 -> 256, 168 -> 162.  Smaller ones grow too much by it: 1500 + 200 + 800, 80 -> 96, 100 -> 112.
-constexpr int kDkdvGroups = 256 * 4;
+constexpr int kDkdvGroups = 256 * 4;                  // of one pair of wavefronts; of two pairs, half as many
 constexpr int kShareRows = 32 * kDkdvGroups;
 constexpr int kMaxMembers = 1024;                     // (an item may exceed its share by a word of 32 but one)
 constexpr int kMostSteps = 64;
-// A short call, of at most one item per workgroup and few enough bins for one look at all of them (8192 tokens and heads together), has no use for
+// A short call, of two pairs and at most one item per workgroup, and few enough bins for one look at all of them (8192 tokens and heads together), has no use for
 // the queues: a workgroup finds its item by its own number and ends with it.  (Drawn from the queues, every workgroup asked all eight for
-// more, one round trip after another.)  Where items are fewer than the compute units, several workgroups take a part of an item's steps each; more
-// parts than that lose to the sums: the chip adds about 270 words per ns, 61 ns per item or part of one (500 tokens, G = 16, 130 items: 32 us in
-// one part, 36 / 74 in three / seven, 13 in seven without the sums).  dk/dv, 2 heads, top-k 16, queues / now, us: G = 16, 150 tokens 39 / 14,
-// 500 47 / 32, 1000 66 / 64; G = 8, 500 42 / 20; G = 1, 500 29 / 12, 1000 33 / 16, 2000 38 / 24.
-constexpr int kPartGroups = 256, kMostParts = 4;
-__host__ __device__ constexpr int least_steps(int G) { return G == 16 ? 8 : 12; }
-__host__ __device__ inline int members_of(int steps, int G) {
-    const int m = (steps < least_steps(G) ? least_steps(G) : steps) * 32 / G;
+// more, one round trip after another.)  Where items are few, two or four workgroups take a part of an item's steps each; more
+// parts than that lose to the sums: the chip adds about 270 words per ns, 61 ns per item or part of one (300 tokens, G = 16, 55 items in 1 / 2 / 3 / 4
+// parts 20.2 / 18.4 / 21.0 / 23.5 us; 700, G = 4, 28.2 / 19.1 / 21.5 in 1 / 2 / 3).  dk/dv, 2 heads, top-k 16, queues / now, us: G = 16, 150 tokens
+// 39 / 14, 500 47 / 25, 1000 65 / 50; G = 8, 500 42 / 20; G = 1, 500 29 / 14, 1000 33 / 16, 2000 38 / 24.
+constexpr int kPartItems = 128;
+// What is left of a call of few steps per workgroup are its sums, all at the same time.  Up to a share of kPairSteps steps an item has two pairs of
+// wavefronts, half its steps each, whose sums meet in LDS before they are added to the block's: half the workgroups, items of twice the share and
+// half the additions.  One pair / two: G = 16, 1000 tokens 65 / 50 us, 2000 97 / 82; G = 8, 1000 37 / 32, 2500 79 / 67; G = 4, 5000
+// 101 / 86; G = 1, 12000 105 / 91; 2 x 4096, G = 8 (64 steps) 185 / 180.  Beyond, two pairs in step wait for each other: 12000, G = 8 261 / 264, 32K, G = 16
+// 1097 / 1180.
+constexpr int kPairSteps = 64;
+__host__ __device__ constexpr int least_steps(int G, int pairs) { return (G == 16 ? 8 : 12) * pairs; }
+__host__ __device__ inline int members_of(int steps, int G, int pairs = 1) {
+    const int m = (steps < least_steps(G, pairs) ? least_steps(G, pairs) : steps) * 32 / G;
     return m > kMaxMembers - 32 ? kMaxMembers - 32 : m;
 }
 __host__ __device__ inline int share_rounds(int share) { return share > kMostSteps ? (share + kMostSteps - 1) / kMostSteps : 1; }
 // steps of a workgroup's share of a call with so many rows (beyond 4096 it is cut into items of kMostSteps either way)
-__host__ __device__ inline int share_steps(int64_t rows) {
-    const int64_t s = (rows + kShareRows - 1) / kShareRows;
+__host__ __device__ inline int share_steps(int64_t rows, int pairs = 1) {
+    const int64_t s = (rows * pairs + kShareRows - 1) / kShareRows;
     return (int)(s < 4096 ? s : 4096);
 }
 // rows of (token, head) per block of 64 tokens
@@ -102,6 +108,7 @@ struct BwdBins {
 struct BwdLayout {
     int32_t nb_cap, words, n_seg;                     // per sequence: blocks, words of 32 tokens, segments of kSegWords words
     int32_t members;                                  // of an item, about: what the bins are laid out for
+    int32_t pairs;                                    // of wavefronts to an item of dk and dv
     BwdBins bins;
     size_t kvb, rowc, bits, acc_dk, acc_dv, counters, items, total; // byte offsets into the workspace
 };
@@ -113,6 +120,7 @@ static BwdLayout bwd_layout(const Dims &dm) {
     l.words = 2 * l.nb_cap;
     l.n_seg = (l.words + kSegWords - 1) / kSegWords;
     const int64_t rows = dm.batch * (int64_t)l.nb_cap * rows_per_block(dm);
+    l.pairs = rows <= (int64_t)kPairSteps * kShareRows ? 2 : 1;
     l.members = members_of((int)(rows / kShareRows < kMostSteps ? rows / kShareRows : kMostSteps), dm.G);
     const size_t nb = (size_t)l.nb_cap, words = (size_t)l.words, windows = BH * ((words + kWindowWords - 1) / kWindowWords);
     const size_t slots = windows ? (windows + kQueues - 1) / kQueues : 1;       // windows of a queue
@@ -294,6 +302,7 @@ struct BwdItems {                                         // where they come fro
     uint64_t *items;
     int64_t rows_per_block;
     int32_t n_seg, groups;                                // workgroups per sequence and head, a multiple of 8
+    int32_t pairs;                                        // of wavefronts to an item
     BwdBins bins;
 };
 __device__ __forceinline__ void cut_items(const Dims &dm, const int32_t *__restrict__ seqlens, int32_t nb_cap, const BwdItems &to_cut) {
@@ -323,7 +332,7 @@ __device__ __forceinline__ void cut_items(const Dims &dm, const int32_t *__restr
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[i][e] = src[(int64_t)min(at + e, w1 - 1) * nb_cap + min(j0 + i, nb_cap - 1)];
     const int64_t rows = (int64_t)__builtin_amdgcn_readfirstlane(blocks.x + blocks.y + blocks.z + blocks.w) * rows_per_block;
-    const int share = share_steps(rows), rounds = share_rounds(share), m = members_of((share + rounds - 1) / rounds, dm.G);
+    const int share = share_steps(rows, to_cut.pairs), rounds = share_rounds(share), m = members_of((share + rounds - 1) / rounds, dm.G, to_cut.pairs);
     const float inv = 1.f / (float)(m >= 96 ? min((m + 31) / 32 * 32, kMaxMembers - 32) : m);
     // Windows are numbered through all sequences and heads of the capacity, eight to the queues' next slices; a sequence's are dealt to the
     // queues round robin by its own length (by the capacity's, short sequences in long buffers meet in one queue: 1000 tokens of 8000,
@@ -793,7 +802,7 @@ static int launch_dq_group(const Dims &dm, Tensor q, Tensor out, Tensor dout, co
 }
 
 // ---- dk, dv of one block from the tokens that selected it ------------------------------------------------------
-// 128 threads, persistent: a workgroup takes items from its XCD's queue, then from the others', until all are empty.  An item's
+// 128 threads, or 256 in two pairs (kPairs), persistent: a workgroup takes items from its XCD's queue, then from the others', until all are empty.  An item's
 // member tokens are expanded from the membership words into a list and walked in steps of 32 rows = (token, head), 32 / G
 // tokens; wave = 32 keys of the block through the whole step, in registers from the scores to the sums (32x32x16 MFMAs):
 //   S[row, key] = Q.K^T and dP = dO.V^T       A = rows from LDS, B = the keys' K and V rows, held in registers
@@ -820,8 +829,8 @@ struct __align__(16) BwdSlot {
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-template <int kG>
-__global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
+template <int kG, int kPairs>
+__global__ __launch_bounds__(128 * kPairs, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q, Tensor dout, const uint4 *__restrict__ kvb,
                                                                 int32_t nb_cap, const int32_t *__restrict__ seqlens,
                                                                 const float *__restrict__ rowc, const float *__restrict__ null_row,
                                                                 const uint32_t *__restrict__ bits, uint32_t *__restrict__ counters,
@@ -829,7 +838,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                                                                 float *__restrict__ acc_dk, float *__restrict__ acc_dv) {
     constexpr int kTPS = 32 / kG;                         // tokens per step
     __shared__ uint16_t list[kMaxMembers];                // the item's member tokens as offsets from its first word's first token
-    __shared__ BwdSlot slot0, slot1;
+    __shared__ BwdSlot slot0s[kPairs], slot1s[kPairs];
     __shared__ uint4 item_s;
     __shared__ int tries_s, total_s;
     __shared__ int part_s, parts_s;                       // a short call's workgroup: its part of an item, of how many (0: items from the queues)
@@ -839,10 +848,11 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     asm volatile("" : "+s"(wave));                        // (a scalar, also after the compiler's own rewriting)
     const int c32 = lane & 31, hf = lane >> 5;
-    const int kh = wave;                                  // key half
+    const int kh = kPairs == 2 ? wave & 1 : wave, pair = kPairs == 2 ? wave >> 1 : 0;     // key half; the pair's part of the steps
+    BwdSlot &slot0 = slot0s[pair], &slot1 = slot1s[pair];
     const float c = dm.scale_log2;
-    const __bf16 *const s_ptr = wave == 0 ? q.ptr : dout.ptr;
-    const int64_t s_sb = wave == 0 ? q.sb : dout.sb, s_sh = wave == 0 ? q.sh : dout.sh, s_st = wave == 0 ? q.st : dout.st;
+    const __bf16 *const s_ptr = kh == 0 ? q.ptr : dout.ptr;
+    const int64_t s_sb = kh == 0 ? q.sb : dout.sb, s_sh = kh == 0 ? q.sh : dout.sh, s_st = kh == 0 ? q.st : dout.st;
     const uint32_t s_head = (uint32_t)(s_sh * 2);         // bytes from head to head
     auto queue_of = [&](int x) __attribute__((always_inline)) { return x < kQueues ? (int)((blockIdx.x + x) % kQueues) : kQueues; };
     auto draw = [&](int x) __attribute__((always_inline)) {
@@ -867,12 +877,12 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
         geo = bins;                                       // by every lane: each reads what it has written itself
         uint4 it = {0u, 0u, 0u, 0u};
         int parts = 0, part = 0;
-        if (bins.n <= kSlices) {                          // every bin of every queue in one look
+        if (kPairs == 2 && bins.n <= kSlices) {                          // every bin of every queue in one look
             const uint32_t n = counters[(lane >> 3) * bins.stride + (lane & 7)], behind = counters[kQueues * bins.stride];
             const uint32_t incl = (uint32_t)wave_inclusive_sum((int)n), queued = __builtin_amdgcn_readlane(incl, 63);
             const uint32_t all = queued + __builtin_amdgcn_readfirstlane(behind);
-            if (all <= (uint32_t)kDkdvGroups) {
-                parts = max(1, min(kMostParts, kPartGroups / max((int)all, 1)));
+            if (all <= (uint32_t)(kDkdvGroups / kPairs)) {
+                parts = all <= kPartItems / 4 ? 4 : all <= kPartItems ? 2 : 1;
                 // neighbours in the queues' order, which share rows, to one XCD
                 const uint32_t ids = all * (uint32_t)parts, per = ids >> 3, rem = ids & 7u, xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
                 if (slot < per + (xcd < rem ? 1u : 0u)) {
@@ -888,7 +898,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
             }
         }
         if (parts == 0) look_at(0);
-        if (lane == 0) {
+        if (kPairs == 2 && lane == 0) {
             item_s = it;
             parts_s = parts;
             part_s = part;
@@ -896,7 +906,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
     }
     for (;;) {
         // ---- next item ----------------------------------------------------------------------------------------------
-        if (wave == 0 && parts_s == 0) {
+        if (wave == 0 && (kPairs == 1 || parts_s == 0)) {
             uint4 it = {0u, 0u, 0u, 0u};
             for (int x = __builtin_amdgcn_readfirstlane(tries_s);;) {   // ends: a queue that is found empty stays empty
                 const uint32_t drawn = __builtin_amdgcn_readfirstlane(ticket), t = drawn & ~kBehind;
@@ -947,11 +957,19 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
             if (lane == 0) total_s = n;
         }
         __syncthreads();
-        const int total = __builtin_amdgcn_readfirstlane(total_s);
-        const int all_steps = (total + kTPS - 1) / kTPS, parts = __builtin_amdgcn_readfirstlane(parts_s);
-        const int part = __builtin_amdgcn_readfirstlane(part_s);
-        const int from = parts ? all_steps * part / parts : 0, steps = parts ? all_steps * (part + 1) / parts : all_steps;
-        if (from >= steps) return;                        // (more parts than steps)
+        int total = __builtin_amdgcn_readfirstlane(total_s), first = 0, last = (total + kTPS - 1) / kTPS;     // members; this pair's steps
+        if constexpr (kPairs == 2) {
+            const int parts = __builtin_amdgcn_readfirstlane(parts_s), part = __builtin_amdgcn_readfirstlane(part_s), steps = last;
+            if (parts) {
+                first = steps * part / parts;
+                last = steps * (part + 1) / parts;
+                if (first >= last) return;                // (more parts than steps)
+            }
+            total = min(total, last * kTPS);              // (the second pair may go a step past them: rows that are not there)
+            const int each = (last - first + 1) / 2;
+            first += pair * each;
+            last = first + each;
+        }
 
         const __bf16 *s_base = s_ptr + b * s_sb + (int64_t)(h * kG) * s_sh + (int64_t)tok0 * s_st;
         asm volatile("" : "+s"(s_base));
@@ -964,7 +982,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
             const uint32_t s_row = ((ln >> 4) % kG) * s_head, s_piece = ((ln & 15) ^ ((ln >> 4) << 2)) << 4;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                auto to = (__attribute__((address_space(3))) void *)&dst.rows[wave][4 * i][0];
+                auto to = (__attribute__((address_space(3))) void *)&dst.rows[kh][4 * i][0];
                 if constexpr (kG >= 4) {
                     const int tok = __builtin_amdgcn_readfirstlane((int)list[min(p * kTPS + 4 * i / kG, total - 1)]);
                     const __amdgpu_buffer_rsrc_t src =
@@ -976,7 +994,7 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, to, 16, 0, 0);
                 }
             }
-            if (wave == 1) {
+            if (kh == 1) {
                 const int at = p * kTPS + (int)(ln & 31) / kG;
                 const uint32_t off = list[min(at, total - 1)] * (uint32_t)(dm.Hkv * 2 * kG * 4) + 4u * ((ln >> 5) * kG + ln % kG);
                 const char *src = at < total ? s_rec + off : reinterpret_cast<const char *>(null_row) + 4u * (16 * (ln >> 5));
@@ -1074,19 +1092,51 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                 dk[i & 3] = mfma32(sf[i >> 2], xb[i & 1], dk[i & 3]);
             }
         };
-        stage(slot0, from);
-        for (int p = from;;) {
+        stage(slot0, first);
+        for (int p = first;;) {
             step(slot0, slot1, p);
-            if (++p >= steps) break;
+            if (++p >= last) break;
             step(slot1, slot0, p);
-            if (++p >= steps) break;
+            if (++p >= last) break;
         }
         // ---- add to the block's sums: an instruction covers 32 channels of two keys, two cache lines ------------------------
-        if (tid == 0 && parts_s == 0) ticket = draw(tries_s);       // the next item's place, under way meanwhile
+        if (tid == 0 && (kPairs == 1 || parts_s == 0)) ticket = draw(tries_s);       // the next item's place, under way meanwhile
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int64_t o = ((int64_t)bh * dm.max_seqlen + (int64_t)j * kBlock + 32 * kh + 4 * (ln >> 5)) * kHeadDim + (ln & 31);
         const int left = L - (j * kBlock + 32 * kh + 4 * (ln >> 5));
+        if constexpr (kPairs == 2) {                      // the first pair adds up dk, the second dv
+            float4 *hand0 = reinterpret_cast<float4 *>(&slot0s[0]), *hand1 = reinterpret_cast<float4 *>(&slot1s[0]);
+            static_assert(sizeof(slot0s) >= 2 * 16 * 64 * sizeof(float4), "a pair's sums of one kind");
+            __builtin_amdgcn_s_waitcnt(0);                // (the copies past the end have landed)
+            __syncthreads();
+            float4 *put = (pair ? hand1 : hand0) + kh * 1024 + ln;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4) {
+                    const f32x16 &x = pair ? dk[ct] : dv[ct];
+                    put[(ct * 4 + v4) * 64] = float4{x[4 * v4], x[4 * v4 + 1], x[4 * v4 + 2], x[4 * v4 + 3]};
+                }
+            __syncthreads();
+            const float4 *get = (pair ? hand0 : hand1) + kh * 1024 + ln;
+            float *to = (pair ? acc_dv : acc_dk) + o;
+#pragma unroll
+            for (int v4 = 0; v4 < 4; ++v4) {
+                float4 y[4];
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) y[ct] = get[(ct * 4 + v4) * 64];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (8 * v4 + r < left) {
+#pragma unroll
+                        for (int ct = 0; ct < 4; ++ct) {
+                            const float z = r == 0 ? y[ct].x : r == 1 ? y[ct].y : r == 2 ? y[ct].z : y[ct].w;
+                            unsafeAtomicAdd(to + (8 * v4 + r) * kHeadDim + 32 * ct, (pair ? dv[ct][4 * v4 + r] : dk[ct][4 * v4 + r]) + z);
+                        }
+                    }
+            }
+        } else {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int key = 8 * (v >> 2) + (v & 3);
@@ -1098,21 +1148,30 @@ __global__ __launch_bounds__(128, 2) void attn_bwd_dkdv_kernel(Dims dm, Tensor q
                 }
             }
         }
+        }
         };
         if (tok0 >= (j + 1) * kBlock) walk(std::false_type{});
         else walk(std::true_type{});
         __builtin_amdgcn_s_waitcnt(0);                    // the copies past the end have landed: the slots may be filled anew
-        if (parts_s != 0) return;                         // uniform
+        if (kPairs == 2 && parts_s != 0) return;          // uniform
         __syncthreads();
     }
+}
+
+template <int kG, int kPairs>
+static void launch_dkdv_pairs(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, const BwdLayout &l, const int32_t *seqlens,
+                        const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint64_t *items,
+                        float *acc_dk, float *acc_dv, hipStream_t stream) {
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<kG, kPairs>), dim3(kDkdvGroups / kPairs), dim3(128 * kPairs), 0, stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc,
+                       null_row, bits, counters, items, l.bins, acc_dk, acc_dv);
 }
 
 template <int kG>
 static void launch_dkdv(const Dims &dm, Tensor q, Tensor dout, const uint4 *kvb, const BwdLayout &l, const int32_t *seqlens,
                         const float *rowc, const float *null_row, const uint32_t *bits, uint32_t *counters, const uint64_t *items,
                         float *acc_dk, float *acc_dv, hipStream_t stream) {
-    hipLaunchKernelGGL(attn_bwd_dkdv_kernel<kG>, dim3(kDkdvGroups), dim3(128), 0, stream, dm, q, dout, kvb, l.nb_cap, seqlens, rowc,
-                       null_row, bits, counters, items, l.bins, acc_dk, acc_dv);
+    if (l.pairs == 2) launch_dkdv_pairs<kG, 2>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream);
+    else launch_dkdv_pairs<kG, 1>(dm, q, dout, kvb, l, seqlens, rowc, null_row, bits, counters, items, acc_dk, acc_dv, stream);
 }
 
 // ---- fp32 accumulators -> bf16 gradients ------------------------------------------------------------------
@@ -1163,7 +1222,7 @@ int launch_attn_bwd(const Dims &dm, Tensor q, Tensor k, Tensor v, Tensor out, Te
                        l.nb_cap, block_idx, bits, acc_dk, acc_dv, counters, (kQueues + 1) * l.bins.stride, null_row);
     timing_end(stream);
     const int32_t groups = l.n_seg * ((l.nb_cap + 4 * kItemBlocks - 1) / (4 * kItemBlocks));
-    const BwdItems to_cut = {bits, counters, items, rows_per_block(dm), l.n_seg, (groups + 7) & ~7, l.bins};
+    const BwdItems to_cut = {bits, counters, items, rows_per_block(dm), l.n_seg, (groups + 7) & ~7, l.pairs, l.bins};
     timing_begin("attn_bwd_dq_kernel", stream);
     int err = (int)hipErrorInvalidValue;
     switch (dm.G) {

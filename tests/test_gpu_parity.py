@@ -1087,11 +1087,17 @@ def test_sparse_attn_backward_items_of_large_shares(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
-# Short calls, whose workgroups find their item by number: four parts of an item (more than it has steps: 2), three, two and one; windows of one to
-# eight queues; and just past eight windows, from the queues again.
+# Short calls, whose workgroups find their item by number: four parts of an item (more than it has steps: 2), two and one, of odd and even numbers
+# of steps (two pairs of wavefronts take half each); windows of one to eight queues; just past eight windows, from the queues again.
 @pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([40], 1, 1, 8), ([1], 2, 2, 3), ([260, 65], 16, 1, 8), ([1000, 900, 65, 7], 2, 1, 4),
-                                                 ([1100], 16, 1, 16), ([8000], 1, 1, 8), ([8200], 1, 1, 8)])
+                                                 ([1100], 16, 1, 16), ([700], 16, 2, 6), ([333], 8, 2, 16), ([8000], 1, 1, 8), ([8200], 1, 1, 8)])
 def test_sparse_attn_backward_items_by_number(seqlens, Hq, Hkv, topk):
+    test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
+
+
+# Either side of the share up to which an item has two pairs of wavefronts (64 steps: 32 blocks x 64 steps of a call's 32768 rows each).
+@pytest.mark.parametrize("seqlens,Hq,Hkv,topk", [([4096], 16, 1, 32), ([4097], 16, 1, 32), ([2048, 2048], 8, 1, 64), ([2049, 64], 8, 1, 64)])
+def test_sparse_attn_backward_pairs(seqlens, Hq, Hkv, topk):
     test_sparse_attn_backward_dispatch(seqlens, Hq, Hkv, topk)
 
 
