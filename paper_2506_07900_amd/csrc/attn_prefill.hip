@@ -781,9 +781,12 @@ static int launch_attn_variant(const Dims &dm, Tensor q, Tensor k, Tensor v, con
 //   32768 1148 -> 755;  G = 1: 777 31 -> 12, 4096 124 -> 38, 32768 1339 -> 534
 // The lines: four tiles, split, from 512 workgroups on (at 390 .. 750 it met two tiles for every G; with three workgroups of two tiles
 // on a compute unit, G = 16, two heads, two / four tiles: 1040 tokens 27.1 / 27.7, 1280 34.4 / 29.8, 1500 42.4 / 35.5; one head, 2100 31.6 / 30.0); two tiles,
-// split, from 192 (at 190 it met one tile, with packed blocks; against direct fetches two tiles come too early there: G = 16, one tile / two, with
-// the packing, 200 tokens x 2 heads 7.2 / 9.5, 280 9.2 / 11.2); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
+// split, from 192 (at 190 it met one tile, with packed blocks), against direct fetches, which save the packing, from 320 for G >= 8 (one tile direct /
+// two tiles packed, both launches, 2 heads: G = 16, 220 tokens 7.6 / 9.3, 300 10.1 / 11.0, 400 13.2 / 12.9; G = 8, 400 10.3 / 11.0, 550
+// 12.5 / 12.8, 700 14.5 / 13.9; smaller groups meet at 192: G = 4, 777 13.5 / 13.5); four tiles on every wave by itself (no merge, no idle wave at the end of a list)
 // only for G = 16 from 1024 workgroups on (smaller groups have longer unions, where the split's balance wins).
+constexpr int kDirectTokens = 896;                       // (see attn_direct; the tiles do not depend on the strides, on which direct fetches do)
+static int64_t two_tile_rows(const Dims &dm) { return (int64_t)(dm.max_seqlen <= kDirectTokens && dm.G >= 8 ? 320 : 192) * 2 * (16 / dm.G); }
 template <int kG>
 static int launch_attn_group(const Dims &dm, Tensor q, Tensor k, Tensor v, bool direct, const uint4 *kvp, int32_t nb_cap, const int32_t *seqlens,
                              const int32_t *block_idx, Tensor out, float *lse, hipStream_t stream) {
@@ -793,7 +796,7 @@ static int launch_attn_group(const Dims &dm, Tensor q, Tensor k, Tensor v, bool 
         if (rows >= (int64_t)1024 * 16) return launch_attn_variant<16, 4, 1>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
     if constexpr (kG > 1)                                // (member bits of at most 32 tokens)
         if (rows >= (int64_t)512 * 4 * kTPT) return launch_attn_variant<kG, 4, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
-    if (rows >= (int64_t)192 * 2 * kTPT) return launch_attn_variant<kG, 2, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
+    if (rows >= two_tile_rows(dm)) return launch_attn_variant<kG, 2, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
     return direct ? launch_attn_variant<kG, 1, 4, true>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream)
                   : launch_attn_variant<kG, 1, 4>(dm, q, k, v, kvp, nb_cap, seqlens, block_idx, out, lse, stream);
 }
@@ -803,9 +806,8 @@ static int launch_attn_group(const Dims &dm, Tensor q, Tensor k, Tensor v, bool 
 // G = 4 8.1 / 6.2; 750 tokens G = 4 13.7 / 12.5, G = 1 11.1 / 10.3; they meet at about 1000 (1 head, G = 4: 11.8 / 12.1; G = 1: 12.6 / 12.2)
 // and at 2000 tokens G = 1 takes 18.9 / 20.0.  Offsets are 32-bit and formed by a 24-bit product, and rows must not overlap
 // (those past the end are told by their offset).
-constexpr int kDirectTokens = 896;
 static bool attn_direct(const Dims &dm, const Tensor &k, const Tensor &v) {
-    if (dm.shared_q || dm.max_seqlen > kDirectTokens || (int64_t)dm.batch * dm.max_seqlen * dm.Hkv >= (int64_t)192 * 2 * (16 / dm.G)) return false;
+    if (dm.shared_q || dm.max_seqlen > kDirectTokens || (int64_t)dm.batch * dm.max_seqlen * dm.Hkv >= two_tile_rows(dm)) return false;
     const int64_t lo = k.st < v.st ? k.st : v.st, hi = k.st < v.st ? v.st : k.st;
     return lo >= kHeadDim && hi < 1 << 19;
 }

@@ -1338,7 +1338,8 @@ def test_decode_step_many_sequences(B):
 # Short prompts read keys and values where they lie: both sides of its lines, padded and interleaved token strides, an end inside a
 # block, sequences of nothing; the same bits whatever the strides.
 @pytest.mark.parametrize("seqlens,Hq,Hkv", [([1], 32, 2), ([64, 0, 17], 16, 1), ([190], 32, 2), ([193], 32, 2), ([383, 100], 8, 2), ([767], 8, 2),
-                                            ([895], 4, 1), ([897], 4, 1), ([896, 1], 1, 1), ([333, 65], 2, 2)])
+                                            ([895], 4, 1), ([897], 4, 1), ([896, 1], 1, 1), ([333, 65], 2, 2), ([319], 32, 2), ([320], 32, 2),
+                                            ([639], 16, 2), ([640, 1], 8, 1)])
 def test_sparse_attn_prefill_direct(seqlens, Hq, Hkv):
     print("case direct", seqlens, Hq, Hkv, flush=True)
     prm, oprm = binding.Params(Hq, Hkv, topk=6), oracle_params(binding.Params(Hq, Hkv, topk=6))
