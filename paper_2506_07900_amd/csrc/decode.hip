@@ -17,7 +17,7 @@
 //                          -> block scores; the logits come from scratch (plain decode) or are
 //                          computed again on the matrix cores (verification)
 //   decode_pick_kernel     two-level top-k of the block scores (sorted lists of 128 blocks, or a row)
-// Caches of up to 8192 tokens: decode_short_kernel does all of this, and the attention, in one workgroup per block.
+// Caches of up to 8192 tokens (verification: 4096): decode_short_kernel does all of this, and the attention, in one workgroup per block.
 // Attention: one workgroup per selected block (split-KV) writes an unnormalised partial
 // (o, max, sum); decode_merge_kernel combines the k partials per query head.  The one-call steps
 // run the top-k inside the attention kernel (decode_pick_partial_kernel): one launch fewer.
@@ -1230,15 +1230,22 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
 // keys at most, from L2) and attends its own entry of the result; workgroup 0 writes the row.
 // In a graph, us per step, four launches -> two: 2K G = 4 13.5 -> 8.3, one sequence of 4000 tokens 16.1 -> 11.5, 8000
 // 16.1 -> 14.4; 32 sequences of 8000, three launches: 25.8 -> 23.9.
-//   mode 0: block list only (infllmv2_select_blocks)       grid (1, Hkv, B)
+//   mode 0: block list only (infllmv2_select_blocks)       grid (1, Hkv, B n_q)
 //   mode 1: append + block list (steps with many rows)      grid (2, Hkv, B)
 //   mode 2: append + block list + partial attention         grid (topk + 1, Hkv, B)   (the last workgroup appends)
+//   mode 3: block list + partial attention (verification)   grid (topk, Hkv, B n_q)
 // Wave w scores kernels 16 kTW w .. +16 kTW - 1, Z = Q . CK^T: lane = kernel, accumulator entries = heads 4g .. 4g+3.
-constexpr int kShortTokens = 8192;
+// Drafted tokens: a launch of its own appends them and builds the semantic kernels they complete, then a row is scored by every workgroup that
+// attends a block of it (mode 3), or by one (mode 0).  Three or four launches instead of four longer ones, us per step in a graph, one
+// sequence: 300 tokens, 4 drafted 14.6 -> 9.6, 900, 16 19.5 -> 15.8, 64 35.4 -> 28.6, 2000, 16 19.8 -> 17.0, 4000, 2 16.9 -> 14.0,
+// 16 20.1 -> 18.7, 64 35.0 -> 30.2; at 8000 tokens they meet (8: 17.9 / 18.3, 16: 20.0 / 21.8).
+constexpr int kShortTokens = 8192, kShortVerify = 4096;
 template <int kTW, int kMode>
 __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Tensor ck, const int32_t *__restrict__ seqlens,
                                                             AppendArgs ap, int32_t *__restrict__ block_idx,
-                                                            float *__restrict__ o_part, float2 *__restrict__ ml_part) {
+                                                            float *__restrict__ o_part, float2 *__restrict__ ml_part,
+                                                            const uint64_t *__restrict__ tree_mask) {
+    constexpr bool kOneRow = kMode == 1 || kMode == 2, kAttends = kMode >= 2;
     constexpr int kKernels = 64 * kTW, kWords = kTW > 4 ? 128 : 64;
     static_assert(16 * kTW <= kWords, "one word per block");
     __shared__ __align__(16) float2 wpart[4][16];
@@ -1246,20 +1253,21 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     __shared__ __align__(16) uint64_t words[kWords];
     __shared__ int counts[4][kWords];
     __shared__ int sel[4][64];                            // per wavefront: the selected blocks, ascending
-    __shared__ __align__(16) uint32_t newrow[kMode > 0 ? 64 : 4];
+    __shared__ __align__(16) uint32_t newrow[kOneRow ? 64 : 4];
     arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.topk, dm.n_init, dm.n_local, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, block_idx);
     arguments_arrive(q.ptr, q.sb, q.sh, dm.scale_log2, dm.Hq, o_part, ml_part);
-    const int cidx = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int G = dm.G;
+    const int b = kOneRow || dm.n_q == 1 ? bv : (int)__umulhi((uint32_t)bv, dm.n_q_inv), qi = kOneRow ? 0 : bv - b * dm.n_q;
     const int32_t L_raw = uniform_load(seqlens + b);
     __builtin_amdgcn_sched_barrier(0);
-    const QueryOperands<1> query(dm, q, b, h, 0);
+    const QueryOperands<1> query(dm, q, b, h, qi);
     const int jw = 16 * kTW * wave;                       // this wave's first kernel
     int64_t ck_wave_at = b * ck.sb + h * ck.sh + (int64_t)jw * ck.st, ck_lane = n * ck.st + 8 * g;       // (while the length is on its way)
     asm volatile("" : "+s"(ck_wave_at), "+v"(ck_lane));
-    if (kMode > 0 && cidx == (kMode == 2 ? dm.topk : 1)) {                    // behind the others: copies the new rows into the caches
+    if (kOneRow && cidx == (kMode == 2 ? dm.topk : 1)) {                    // behind the others: copies the new rows into the caches
         const int c8 = (tid & 15) * 8;
         if (L_raw < 1 || L_raw > dm.max_seqlen || tid >= 32) return;
         if (tid < 16)
@@ -1270,9 +1278,9 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
                 *reinterpret_cast<const uint4 *>(ap.v_new.ptr + b * ap.v_new.sb + h * ap.v_new.sh + c8);
         return;
     }
-    const int L = clamp_len(L_raw, dm.max_seqlen);
-    const bool live = kMode > 0 && L_raw >= 1 && L_raw <= dm.max_seqlen;      // as the stand-alone append: others are skipped
-    int32_t *orow = block_idx + ((int64_t)b * dm.Hkv + h) * dm.topk;
+    const int L = kOneRow ? clamp_len(L_raw, dm.max_seqlen) : row_len(dm, clamp_len(L_raw, dm.max_seqlen), qi);
+    const bool live = kOneRow && L_raw >= 1 && L_raw <= dm.max_seqlen;        // as the stand-alone append: others are skipped
+    int32_t *orow = block_idx + (kOneRow ? (int64_t)b * dm.Hkv + h : ((int64_t)b * dm.Hkv + h) * dm.n_q + qi) * dm.topk;
     const int n_vis = num_kernels(L);
     const RowRange rr(dm, max(L, 1));
     bf16x8 a[kTW][4], bq[1][4];
@@ -1293,13 +1301,13 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     }
     __builtin_amdgcn_sched_barrier(0);
     query.get(nullptr, bq);
-    std::conditional_t<kMode == 2, BlockFetch, int> fetch{};
-    if constexpr (kMode == 2) fetch.set(dm, ap.k, ap.v, b, h);
+    std::conditional_t<kAttends, BlockFetch, int> fetch{};
+    if constexpr (kAttends) fetch.set(dm, ap.k, ap.v, b, h);
     int blk = -1;
     if (L < 1) {                                          // uniform over the workgroup
         if (cidx == 0 && tid < dm.topk) orow[tid] = -1;
     } else {
-        if constexpr (kMode > 0) {
+        if constexpr (kOneRow) {
             // the semantic kernel the new token completes: rows L-32 .. L-2 from the cache, row L-1 from k_new, fp64 sum in
             // token order, one rounding (the bits of compress_keys_kernel); lane = channels 2*lane, 2*lane+1
             const int jh_new = n_vis - 1;
@@ -1433,6 +1441,8 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     if constexpr (kMode == 2)
         attend_block<true>(dm, ap.k, ap.v, fetch, bq[0], b, b, 0, h, L, blk, nullptr, o_part, ml_part, [cidx] { return cidx; }, &ap,
                            live ? L_raw - 1 : -1);
+    if constexpr (kMode == 3)
+        attend_block<false>(dm, ap.k, ap.v, fetch, bq[0], bv, b, qi, h, L, blk, tree_mask, o_part, ml_part, [cidx] { return cidx; });
 }
 
 // ---- attention, part 2: merge the k partials of every query head ---------------------------------
@@ -1534,7 +1544,7 @@ size_t select_decode_ws_bytes(const Dims &dm) {
 }
 
 // One workgroup per row can score it all (see decode_short_kernel); the approximate log-sum-exp keeps the long path.
-static bool short_cache(const Dims &dm) { return dm.n_q == 1 && dm.rho == 1 && dm.max_seqlen <= kShortTokens; }
+static bool short_cache(const Dims &dm) { return dm.rho == 1 && dm.max_seqlen <= (dm.n_q == 1 ? kShortTokens : kShortVerify); }
 // Fused top-k and attention: every workgroup repeats the top-k of its row, which is free while compute units idle and
 // costs throughput once the launch fills the machine.  Measured (us per step, fused / apart): 512 units 35.7 / 37.3 (16 sequences
 // of 128K), 22.4 / 24.2 (of 20K), 31.9 / 33.8 (16 drafted tokens at 128K); 1024 units 56.6 / 58.3, 29.8 / 31.6, 42.3 / 44.0; 1536
@@ -1549,20 +1559,21 @@ static int short_tiles(const Dims &dm) {              // tiles of 16 kernels (16
 // Repeating the whole selection in every attention workgroup beats a launch for it while the workgroups fit the chip a
 // few times over; the more kernels there are to score, the earlier that ends.  Measured (us, fused / apart): 900 tokens
 // 1024 units 16.6 / 18.6, 2048 30.9 / 28.0; 2000 tokens 512 15.1 / 16.7, 1024 19.4 / 19.6 and 16.9 / 16.3; 4000 tokens
-// 256 13.7 / 15.0, 512 17.3 / 17.7 and 16.2 / 15.0; 8000 tokens 256 16.6 / 18.2, 512 21.7 / 20.8.
+// 256 13.7 / 15.0, 512 17.3 / 17.7 and 16.2 / 15.0; 8000 tokens 256 16.6 / 18.2, 512 21.7 / 20.8.  Drafted tokens: 900 tokens 512 units
+// 15.8 / 17.1, 2048 29.4 / 28.6; 2000 tokens 512 17.0 / 17.8, 1024 22.7 / 22.3; 4000 tokens 512 18.7 / 19.2, 2048 38.3 / 30.2.
 static bool fuse_short(const Dims &dm) {
-    const int64_t units = (int64_t)dm.batch * dm.Hkv * dm.topk;
+    const int64_t units = (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk;
     const int t = short_tiles(dm);
-    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? 384 : 256);
+    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? (dm.n_q > 1 ? 512 : 384) : 256);
 }
 
 template <int kMode>
 static int launch_short(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap, const int32_t *seqlens, int32_t *block_idx,
-                        float *o_part, float2 *ml_part, hipStream_t stream) {
-    const dim3 grid((kMode == 2 ? dm.topk : 1) + (kMode > 0 ? 1 : 0), dm.Hkv, dm.batch), block(256);
+                        float *o_part, float2 *ml_part, hipStream_t stream, const uint64_t *tree_mask = nullptr) {
+    const dim3 grid((kMode >= 2 ? dm.topk : 1) + (kMode == 1 || kMode == 2 ? 1 : 0), dm.Hkv, dm.batch * dm.n_q), block(256);
     timing_begin("decode_short_kernel", stream);
 #define INFLLMV2_SHORT(TW) \
-    hipLaunchKernelGGL((decode_short_kernel<TW, kMode>), grid, block, 0, stream, dm, q, ck, seqlens, ap, block_idx, o_part, ml_part)
+    hipLaunchKernelGGL((decode_short_kernel<TW, kMode>), grid, block, 0, stream, dm, q, ck, seqlens, ap, block_idx, o_part, ml_part, tree_mask)
     switch (short_tiles(dm)) {
         case 1: INFLLMV2_SHORT(1); break;
         case 2: INFLLMV2_SHORT(2); break;
@@ -1749,16 +1760,21 @@ int launch_decode_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap
 
 // One verification step for n_q drafted tokens per sequence: append (+ completed semantic kernels),
 // selection per drafted token, tree-masked attention; four launches (one more with the top-k in one of its own, and with the
-// append in one of its own for the approximate log-sum-exp).
+// append in one of its own for the approximate log-sum-exp); three or four up to kShortVerify.
 int launch_verify_step(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &append, const int32_t *seqlens,
                        const uint64_t *tree_mask, int32_t *block_idx, Tensor out, float *lse, void *ws_select,
                        void *ws_attn, hipStream_t stream) {
     if (dm.batch <= 0) return 0;
-    const bool folded = dm.n_q > 1 && dm.rho == 1;        // (a coarse kernel would need rows that other workgroups are storing)
+    const bool brief = short_cache(dm);
+    const bool folded = dm.n_q > 1 && dm.rho == 1 && !brief;     // (a coarse kernel would need rows that other workgroups are storing)
     int err = folded ? 0 : launch_append_kv(dm, append.k_new, append.v_new, append.k, append.v, &ck, seqlens, stream);
     if (err) return err;
     AttendArgs at = {append.k, append.v, tree_mask, false, nullptr, nullptr};
     attn_decode_ws(dm, ws_attn, at.o_part, at.ml_part);
+    if (brief && fuse_short(dm)) {
+        err = launch_short<3>(dm, q, ck, append, seqlens, block_idx, at.o_part, at.ml_part, stream, tree_mask);
+        return err ? err : launch_decode_merge(dm, at.o_part, at.ml_part, out, lse, stream);
+    }
     err = launch_select_decode(dm, q, ck, seqlens, block_idx, ws_select, stream, folded ? &append : nullptr, &at);
     if (err) return err;
     if (!at.fused) launch_decode_partial(dm, q, append.k, append.v, seqlens, block_idx, tree_mask, at.o_part, at.ml_part, stream);
