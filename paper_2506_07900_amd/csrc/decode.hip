@@ -112,8 +112,15 @@ struct RowRange {
 // verification (4 to 64 drafted tokens): under 10 % between them.
 constexpr int kVerifyQT = 4;
 constexpr int kVerifyTiles = 2;                                                          // part 1, verification
-// part 1, plain decode: by batch size
-static inline int decode_tiles_per_wave(const Dims &dm) { return dm.batch >= 4 ? 4 : 2; }
+// Part 1, plain decode: two for up to three sequences; for more, four where workgroups of two tiles are neither few enough for a compute unit each
+// nor enough to fill the chip several times over (two / four tiles, us per step: 4 sequences of 60K, 240 workgroups, 15.1 / 15.8; 8 of 60K, 480,
+// 17.4 / 16.8; 8 of 16K to 128K, 1024 by the capacity, 20.0 / 19.3; 16 of 128K, 2048, 31.6 / 32.0; 32 of 128K, 4096, 56.6 / 58.0, G = 4
+// 38.2 / 40.9).  The scratch holds two sets of partials of `decode_tiles_scratch` tiles each; the exact log-sum-exp needs one, which may be twice as long.
+static inline int decode_tiles_scratch(const Dims &dm) { return dm.batch >= 4 ? 4 : 2; }
+static inline int decode_tiles_per_wave(const Dims &dm) {
+    const int64_t n = (int64_t)dm.batch * dm.Hkv * ((num_kernels(dm.max_seqlen) + 127) / 128);
+    return dm.batch < 4 || (dm.rho == 1 && (n <= 256 || n >= 2048)) ? 2 : 4;
+}
 
 // length of the cache up to and including query token qi of sequence b (0: no such row)
 __device__ inline int row_len(const Dims &dm, int L_all, int qi) {
@@ -1521,7 +1528,7 @@ static DecodeSelLayout decode_sel_layout(const Dims &dm) {
     l.nb_cap = ((dm.max_seqlen + kBlock - 1) / kBlock + 63) / 64 * 64;
     const size_t rows = (size_t)dm.batch * dm.n_q;
     l.z_bytes = dm.n_q == 1 ? align256(rows * dm.Hq * l.n_c_cap * sizeof(float)) : 0;
-    l.part_bytes = align256(rows * dm.Hq * l.n_part * sizeof(float2));
+    l.part_bytes = align256(rows * dm.Hq * (dm.n_q == 1 ? l.n_c_cap / (64 * decode_tiles_scratch(dm)) : l.n_part) * sizeof(float2));
     l.list_blocks = dm.n_q == 1 ? kListBlocks : 16 * verify_tiles2(dm);
     l.n_lists = max(1, (dm.max_seqlen + kBlock * l.list_blocks - 1) / (kBlock * l.list_blocks));
     l.list_len = min(l.list_blocks, max(1, dm.topk - dm.n_init - dm.n_local));

@@ -1338,6 +1338,28 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# Decoding's tiles per workgroup follow sequences x heads x buffer (256 and 2048 workgroups of two tiles): on either side of the lines the first and
+# last of equal sequences (one cache, read with a batch stride of zero) get the lists and outputs that one sequence alone gets.
+@pytest.mark.parametrize("B,T", [(4, 131072), (4, 133000), (28, 17000), (29, 17000), (120, 32800), (121, 32800)])
+def test_decode_tiles_by_workgroups(B, T):
+    print("case decode tiles", B, T, flush=True)
+    Hq, Hkv = 16, 1
+    prm = binding.Params(Hq, Hkv, topk=16)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    k, v = (torch.randn((1, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    q = torch.randn((1, 1, Hq, 128), device="cuda", generator=gen).bfloat16()
+    ck = binding.compress_keys(prm, k, dev_i32([T]), T)
+    n = [T, T - 1000]
+    many = [n[b % 2] for b in range(B)]
+    want = [binding.select_blocks(prm, binding.MODE_DECODE, q, ck, dev_i32([x]), T) for x in n]
+    kb, vb, cb = (x.expand(B, -1, -1, -1) for x in (k, v, ck))
+    got = binding.select_blocks(prm, binding.MODE_DECODE, q.expand(B, -1, -1, -1).contiguous(), cb, dev_i32(many), T)
+    torch.cuda.synchronize()
+    for b in (0, 1, B // 2, B - 2, B - 1):
+        same = len(set(got[b].flatten().tolist()) & set(want[b % 2][0].flatten().tolist()))
+        assert same >= 15, (b, same)                     # (another grouping of the log-sum-exp's sums: a near-tie may fall the other way)
+
+
 # Short prompts read keys and values where they lie: both sides of its lines, padded and interleaved token strides, an end inside a
 # block, sequences of nothing; the same bits whatever the strides.
 @pytest.mark.parametrize("seqlens,Hq,Hkv", [([1], 32, 2), ([64, 0, 17], 16, 1), ([190], 32, 2), ([193], 32, 2), ([383, 100], 8, 2), ([767], 8, 2),
