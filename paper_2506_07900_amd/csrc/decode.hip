@@ -1507,10 +1507,12 @@ __global__ __launch_bounds__(64) void decode_merge_kernel(Dims dm, const float *
 static inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 // Part 2, verification: tiles per wave, and so blocks per list of the top-k: four where that leaves a workgroup for every compute
-// unit.  Measured (us per step at 128K, two / four): 4 drafted tokens 20.5 / 22.1, 16 27.9 / 27.6, 64 62.1 / 59.8.
+// unit, or for every second where lists of 32 blocks would be more than 32 and could not be merged as they are.  Measured (us per step, two / four):
+// 128K, 4 drafted tokens 20.5 / 22.1, 16 27.9 / 27.6, 64 62.1 / 59.8; 120K, 16 (240 workgroups of four) 25.4 / 23.3, 70K, 16 (144) 24.5 / 23.3, 120K,
+// 4 (60) 19.4 / 19.3; 64K, 16 (128) 22.0 / 22.9.
 static int verify_tiles2(const Dims &dm) {
     const int64_t wide = (int64_t)((dm.max_seqlen + 64 * kBlock - 1) / (64 * kBlock)) * dm.Hkv * dm.batch * ((dm.n_q + kVerifyQT - 1) / kVerifyQT);
-    return wide >= 256 ? 4 : 2;
+    return wide >= (dm.max_seqlen > 32 * 32 * kBlock ? 128 : 256) ? 4 : 2;
 }
 
 struct DecodeSelLayout {

@@ -894,10 +894,10 @@ def test_verify_select_and_attn(seqlens, n, Hq, Hkv, topk, kind):
 
 # The two forms in which the scoring workgroups hand on what they found, on either side of their line (lists that fit the scratch of the rows'
 # scores and the second partials, or those scores): 26 | 27 picks beside the forced blocks for lists of 32, 40 | 41 for the lists of 64
-# that a larger call has; G = 16, whose lists always fit.
+# that a larger call has; G = 16, whose lists always fit; either side of 65536 tokens, beyond which half as many workgroups do for the larger lists.
 @pytest.mark.parametrize("seqlens,n,Hq,Hkv,topk", [
     ([4500, 2100], 5, 4, 1, 29), ([4500, 2100], 5, 4, 1, 30), ([4500, 4160], 64, 16, 4, 43), ([4500, 4160], 64, 16, 4, 44),
-    ([8300, 4100], 3, 4, 1, 64), ([8300, 4100], 6, 32, 2, 64)])
+    ([8300, 4100], 3, 4, 1, 64), ([8300, 4100], 6, 32, 2, 64), ([65537], 29, 2, 1, 8), ([65536], 30, 2, 1, 8)])
 def test_verify_selection_lists_and_rows(seqlens, n, Hq, Hkv, topk):
     test_verify_select_and_attn(seqlens, n, Hq, Hkv, topk, "tree")
 
