@@ -300,7 +300,8 @@ int32_t infllmv2_append_kv(const infllmv2_params *prm, const infllmv2_tensor *k_
  * infllmv2_append_kv (with ck) + infllmv2_select_blocks(INFLLMV2_MODE_DECODE) +
  * infllmv2_sparse_attn_decode, with the append folded into the first selection kernel and the top-k
  * into the per-block attention kernel: four launches instead of six (five when batch * Hkv * topk
- * exceeds 1024: the top-k then runs once per row in a launch of its own); with max_seqlen <= 8192 and
+ * exceeds 2048, or 1024 where more than 16 blocks are picked by score: the top-k then runs once per row in a
+ * launch of its own); with max_seqlen <= 8192 and
  * the exact log-sum-exp two, append, selection and partial attention being one kernel (three when
  * batch * Hkv * topk exceeds 1024, 768, 384, 256 for max_seqlen <= 1024, 2048, 4096, 8192).  The same caches, ck,
  * block_idx, out and lse bit for bit.
@@ -343,9 +344,12 @@ int32_t infllmv2_decode_step(const infllmv2_params *prm, const infllmv2_tensor *
  *                               arithmetic as in infllmv2_sparse_attn_decode.
  * infllmv2_verify_step          the three calls in one (ck required), four launches instead of six
  *                               (the top-k is folded into the per-block attention kernel unless
- *                               batch * n_draft * Hkv * topk exceeds 1024, the append into the first
+ *                               batch * n_draft * Hkv * topk exceeds 2048 (1024 where more than 16 blocks are
+ *                               picked by score), the append into the first
  *                               selection kernel unless lse_coarse_ratio > 1 or n_draft == 1: one
- *                               launch more each); the same caches, ck, block_idx, out and lse bit
+ *                               launch more each); with max_seqlen <= 4096 and the exact log-sum-exp three
+ *                               (append; selection and attention; merge), four when that product exceeds 1024, 768, 512 for
+ *                               max_seqlen <= 1024, 2048, 4096; the same caches, ck, block_idx, out and lse bit
  *                               for bit.
  * Workspaces: infllmv2_verify_workspace_bytes(INFLLMV2_OP_SELECT_VERIFY / _ATTN_VERIFY /
  * _VERIFY_STEP, ...) (0 if the arguments are invalid), 256-byte aligned.

@@ -1555,11 +1555,12 @@ size_t select_decode_ws_bytes(const Dims &dm) {
 // One workgroup per row can score it all (see decode_short_kernel); the approximate log-sum-exp keeps the long path.
 static bool short_cache(const Dims &dm) { return dm.rho == 1 && dm.max_seqlen <= (dm.n_q == 1 ? kShortTokens : kShortVerify); }
 // Fused top-k and attention: every workgroup repeats the top-k of its row, which is free while compute units idle and
-// costs throughput once the launch fills the machine.  Measured (us per step, fused / apart): 512 units 35.7 / 37.3 (16 sequences
-// of 128K), 22.4 / 24.2 (of 20K), 31.9 / 33.8 (16 drafted tokens at 128K); 1024 units 56.6 / 58.3, 29.8 / 31.6, 42.3 / 44.0; 1536
-// units 84.7 / 84.9, 37.6 / 37.1, 54.4 / 53.4; 2048 units 110.3 / 110.6, 44.1 / 44.0, 65.0 / 63.3.
-constexpr int64_t kMaxFusedUnits = 1024;              // (row, key-value head, block) workgroups
-static bool fuse_units(const Dims &dm) { return (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk <= kMaxFusedUnits; }
+// costs throughput once the launch fills the machine many times over; merging sorted lists costs less than counting.  Measured (us per step,
+// fused / apart), merged: 1536 units 32.6 / 34.8 (48 sequences of 20K), 2048 37.4 / 39.2 (64), 34.0 / 36.0 and 33.2 / 34.8 (64 and 2 x 32 drafted
+// tokens at 30K); counted: 1024 56.6 / 58.3, 42.3 / 44.0, 1920 31.5 / 30.1 (top-k 48) and 46.3 / 38.5 (30 drafted, top-k 64).
+static bool fuse_units(const Dims &dm, bool merged) {  // by (row, key-value head, block) workgroups
+    return (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk <= (merged ? 2048 : 1024);
+}
 
 static int short_tiles(const Dims &dm) {              // tiles of 16 kernels (16 blocks) per wave
     const int n_blocks = (dm.max_seqlen + kBlock - 1) / kBlock;
@@ -1666,7 +1667,8 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     const int vpt = (n_elements + kPickThreads - 1) / kPickThreads;
     if (vpt > kPickMaxVPT) return (int)hipErrorInvalidValue;         // rejected earlier by the C ABI
     const PickInput in = {found, l.n_lists, l.list_len, (1 << 20) / l.n_lists + 1, l.list_blocks, l.nb_cap};
-    if (attend) attend->fused = fuse_units(dm);
+    const bool merged = lists && l.list_len <= kMergePicks && l.n_lists <= 32;
+    if (attend) attend->fused = fuse_units(dm, merged);
     const bool fused = attend && attend->fused;
     timing_begin(fused ? "decode_pick_partial_kernel" : "decode_pick_kernel", stream);
 #define INFLLMV2_PICK(FORM, N)                                                                                          \
@@ -1680,7 +1682,7 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
             hipLaunchKernelGGL((decode_pick_kernel<FORM, N>), dim3(rows * dm.Hkv), dim3(kPickThreads), lds, stream, dm, \
                                seqlens, in, block_idx);                                                                 \
     } while (0)
-    if (lists && l.list_len <= kMergePicks && l.n_lists <= 32) {
+    if (merged) {
         if (l.n_lists <= 4) INFLLMV2_PICK(kMerge, 1);
         else if (l.n_lists <= 8) INFLLMV2_PICK(kMerge, 2);
         else if (l.n_lists <= 16) INFLLMV2_PICK(kMergeShared, 1);
