@@ -1567,15 +1567,14 @@ static int short_tiles(const Dims &dm) {              // tiles of 16 kernels (16
     return n_blocks <= 16 ? 1 : n_blocks <= 32 ? 2 : n_blocks <= 64 ? 4 : 8;
 }
 // Repeating the whole selection in every attention workgroup beats a launch for it while the workgroups fit the chip a
-// few times over, for caches of more than 2048 tokens only while each has a compute unit to itself.  Measured (us per step, fused / apart): 900 tokens 640
-// units 13.1 / 14.8, 1024 17.2 / 17.4, 2048 25.7 / 24.4; 2000 tokens 384 12.4 / 13.3, 512 14.7 / 13.8 and 14.3 / 12.9 (768, G = 4); 4000 tokens 224
-// 11.0 / 12.6, 256 13.6 / 12.8, 512 17.4 / 15.3; 8000 tokens 224 14.1 / 15.7, 256 18.7 / 15.8.  Drafted tokens, whose units share a cache: 900 tokens 512
+// few times over; the more kernels there are to score, the earlier that ends.  Measured (us, fused / apart): 900 tokens
+// 1024 units 16.6 / 18.6, 2048 30.9 / 28.0; 2000 tokens 512 15.1 / 16.7, 1024 19.4 / 19.6 and 16.9 / 16.3; 4000 tokens
+// 256 13.7 / 15.0, 512 17.3 / 17.7 and 16.2 / 15.0; 8000 tokens 256 16.6 / 18.2, 512 21.7 / 20.8.  Drafted tokens: 900 tokens 512 units
 // 15.8 / 17.1, 2048 29.4 / 28.6; 2000 tokens 512 17.0 / 17.8, 1024 22.7 / 22.3; 4000 tokens 512 18.7 / 19.2, 2048 38.3 / 30.2.
 static bool fuse_short(const Dims &dm) {
     const int64_t units = (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk;
     const int t = short_tiles(dm);
-    if (dm.n_q > 1) return units <= (t == 1 ? 1024 : t == 2 ? 768 : 512);
-    return units <= (t == 1 ? 1024 : t == 2 ? 448 : 240);
+    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? (dm.n_q > 1 ? 512 : 384) : 256);
 }
 
 template <int kMode>
