@@ -303,7 +303,7 @@ int32_t infllmv2_append_kv(const infllmv2_params *prm, const infllmv2_tensor *k_
  * exceeds 2048, or 1024 where more than 16 blocks are picked by score: the top-k then runs once per row in a
  * launch of its own); with max_seqlen <= 8192 and
  * the exact log-sum-exp two, append, selection and partial attention being one kernel (three when
- * batch * Hkv * topk exceeds 1024, 768, 384, 256 for max_seqlen <= 1024, 2048, 4096, 8192).  The same caches, ck,
+ * batch * Hkv * topk exceeds 1024, 768, 512, 256 for max_seqlen <= 1024, 2048, 4096, 8192).  The same caches, ck,
  * block_idx, out and lse bit for bit.
  *   q, out        [batch, 1, Hq, d] bf16;  k_new, v_new  [batch, Hkv, 1, d] bf16
  *   k, v, ck      the caches (updated in place);  seqlens counts the new token

@@ -158,7 +158,7 @@ __device__ inline bf16x8 fresh_kernel_row8(const AppendArgs &ap, int b, int h, i
 // ---- part 1: partial (max, sum) of the relevance softmax ---------------------------------------------
 // grid (n_c_cap / (64*kTW), Hkv, B * ceil(n_q/kQT)); wave w owns kernels chunk + 16*kTW*w .. +16*kTW-1.
 // Z^T = CK . Q^T: lane = query head, 4 accumulator entries = 4 consecutive kernels.
-// With kAppend (the one-call steps) the kernel also opens the step: workgroups behind the chunks copy the new tokens' key and value
+// With kAppend (the one-call steps) the kernel also opens the step: workgroups behind the chunks (of a row, or of all) copy the new tokens' key and value
 // rows into the caches (nothing before the attention kernel reads them; done by the first chunk's, those held up the launch: 16 drafted
 // tokens at 128K, 12800 of its 13000 cycles), and the wave that owns the semantic kernel the new token completes builds its
 // representation itself -- 31 cached rows and the new one, fp64 sum in token order, one rounding, the same bits as
@@ -181,10 +181,17 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     __shared__ __align__(16) uint16_t newrows[kAppend && kQT > 1 ? kNewKernels * kQsPitch : 8];
     arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.n_q, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, zbuf, n_c_cap, part);
     arguments_arrive(q.ptr, q.sb, q.sh, q.st, dm.scale_log2, n_part, dm.rho);
-    const int h = blockIdx.y;
+    int h = blockIdx.y, bz = blockIdx.z, bx = blockIdx.x;
+    if (kQT == 1 && kAppend && bz >= dm.batch) {          // behind all chunks: one appends to each (sequence, key-value head)
+        const int at = ((bz - dm.batch) * dm.Hkv + h) * n_part + bx;
+        if (at >= dm.batch * dm.Hkv) return;
+        bz = at / dm.Hkv;
+        h = at - bz * dm.Hkv;
+        bx = n_part;
+    }
     const int n_qt = (dm.n_q + kQT - 1) / kQT;        // query tiles per sequence
-    const int b = kQT == 1 || n_qt == 1 ? blockIdx.z : (int)__umulhi(blockIdx.z, n_qt_inv);   // kQT = 1 is only launched with n_q = 1
-    const int qi0 = (blockIdx.z - b * n_qt) * kQT;
+    const int b = kQT == 1 || n_qt == 1 ? bz : (int)__umulhi(blockIdx.z, n_qt_inv);   // kQT = 1 is only launched with n_q = 1
+    const int qi0 = kQT == 1 ? 0 : (bz - b * n_qt) * kQT;
     const int32_t L_raw = uniform_load(seqlens + b);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -201,8 +208,8 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     int new_from = 0x7fffffff;                        // several tokens: the kernels from here on are completed by them
     if constexpr (kAppend) {
         const bool live = L_raw >= dm.n_q && L_raw <= dm.max_seqlen;  // as the stand-alone append: others are skipped
-        if ((int)blockIdx.x >= n_part) {              // copies the rows of eight new tokens into the caches
-            const int qi = ((int)blockIdx.x - n_part) * 8 + (threadIdx.x >> 5), c8 = (threadIdx.x & 15) * 8;
+        if (bx >= n_part) {              // copies the rows of eight new tokens into the caches
+            const int qi = (bx - n_part) * 8 + (threadIdx.x >> 5), c8 = (threadIdx.x & 15) * 8;
             if (!live || qi0 > 0 || qi >= dm.n_q) return;
             const int64_t at = L_raw - dm.n_q + qi;
             if (threadIdx.x & 16)
@@ -1239,7 +1246,9 @@ __global__ __launch_bounds__(kPickThreads) void decode_pick_partial_kernel(Dims 
 // 16.1 -> 14.4; 32 sequences of 8000, three launches: 25.8 -> 23.9.
 //   mode 0: block list only (infllmv2_select_blocks)       grid (1, Hkv, B n_q)
 //   mode 1: append + block list (steps with many rows)      grid (2, Hkv, B)
-//   mode 2: append + block list + partial attention         grid (topk + 1, Hkv, B)   (the last workgroup appends)
+//   mode 2: append + block list + partial attention         grid (topk, Hkv, B + ceil(B / topk))
+// (Mode 2 appends in workgroups behind all others, so that these have the compute units first: behind each row's, 240 units and 20 that append
+// took 13.8 us for 5 sequences of 4266, so 12.0; 256 and 32, 8 of 8000, 19.0 and 16.0.)
 //   mode 3: block list + partial attention (verification)   grid (topk, Hkv, B n_q)
 // Wave w scores kernels 16 kTW w .. +16 kTW - 1, Z = Q . CK^T: lane = kernel, accumulator entries = heads 4g .. 4g+3.
 // Drafted tokens: a launch of its own appends them and builds the semantic kernels they complete, then a row is scored by every workgroup that
@@ -1262,8 +1271,15 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     __shared__ int sel[4][64];                            // per wavefront: the selected blocks, ascending
     __shared__ __align__(16) uint32_t newrow[kOneRow ? 64 : 4];
     arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.topk, dm.n_init, dm.n_local, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, block_idx);
-    arguments_arrive(q.ptr, q.sb, q.sh, dm.scale_log2, dm.Hq, o_part, ml_part);
-    const int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
+    arguments_arrive(q.ptr, q.sb, q.sh, dm.scale_log2, dm.Hq, o_part, ml_part, dm.batch);
+    int cidx = blockIdx.x, h = blockIdx.y, bv = blockIdx.z;
+    if (kMode == 2 && bv >= dm.batch) {                   // behind all others: one appends to each (sequence, key-value head)
+        const int at = ((bv - dm.batch) * dm.Hkv + h) * dm.topk + cidx;
+        if (at >= dm.batch * dm.Hkv) return;
+        bv = at / dm.Hkv;
+        h = at - bv * dm.Hkv;
+        cidx = dm.topk;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int G = dm.G;
@@ -1274,7 +1290,7 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
     const int jw = 16 * kTW * wave;                       // this wave's first kernel
     int64_t ck_wave_at = b * ck.sb + h * ck.sh + (int64_t)jw * ck.st, ck_lane = n * ck.st + 8 * g;       // (while the length is on its way)
     asm volatile("" : "+s"(ck_wave_at), "+v"(ck_lane));
-    if (kOneRow && cidx == (kMode == 2 ? dm.topk : 1)) {                    // behind the others: copies the new rows into the caches
+    if (kOneRow && cidx == (kMode == 2 ? dm.topk : 1)) {  // copies the new rows into the caches
         const int c8 = (tid & 15) * 8;
         if (L_raw < 1 || L_raw > dm.max_seqlen || tid >= 32) return;
         if (tid < 16)
@@ -1567,20 +1583,20 @@ static int short_tiles(const Dims &dm) {              // tiles of 16 kernels (16
     return n_blocks <= 16 ? 1 : n_blocks <= 32 ? 2 : n_blocks <= 64 ? 4 : 8;
 }
 // Repeating the whole selection in every attention workgroup beats a launch for it while the workgroups fit the chip a
-// few times over; the more kernels there are to score, the earlier that ends.  Measured (us, fused / apart): 900 tokens
-// 1024 units 16.6 / 18.6, 2048 30.9 / 28.0; 2000 tokens 512 15.1 / 16.7, 1024 19.4 / 19.6 and 16.9 / 16.3; 4000 tokens
-// 256 13.7 / 15.0, 512 17.3 / 17.7 and 16.2 / 15.0; 8000 tokens 256 16.6 / 18.2, 512 21.7 / 20.8.  Drafted tokens: 900 tokens 512 units
-// 15.8 / 17.1, 2048 29.4 / 28.6; 2000 tokens 512 17.0 / 17.8, 1024 22.7 / 22.3; 4000 tokens 512 18.7 / 19.2, 2048 38.3 / 30.2.
+// few times over; the more kernels there are to score, the earlier that ends.  Measured (us per step, fused / apart; a launch more costs an eager
+// caller up to 3 us beside): 900 tokens 768 units 13.4 / 15.5, 2048 25.7 / 24.4; 2000 tokens 512 13.3 / 14.2 and 11.0 / 11.4, 768 15.8 / 16.0 and
+// 13.2 / 12.9; 4000 tokens 256 11.3 / 12.8, 384 14.5 / 14.6, 512 15.2 / 15.2; 8000 tokens 256 14.4 / 15.9, 320 19.3 / 17.1.  Drafted tokens: 900
+// tokens 512 units 15.8 / 17.1, 2048 29.4 / 28.6; 2000 tokens 512 17.0 / 17.8, 1024 22.7 / 22.3; 4000 tokens 512 18.7 / 19.2, 2048 38.3 / 30.2.
 static bool fuse_short(const Dims &dm) {
     const int64_t units = (int64_t)dm.batch * dm.n_q * dm.Hkv * dm.topk;
     const int t = short_tiles(dm);
-    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? (dm.n_q > 1 ? 512 : 384) : 256);
+    return units <= (t == 1 ? 1024 : t == 2 ? 768 : t == 4 ? 512 : 256);
 }
 
 template <int kMode>
 static int launch_short(const Dims &dm, Tensor q, Tensor ck, const AppendArgs &ap, const int32_t *seqlens, int32_t *block_idx,
                         float *o_part, float2 *ml_part, hipStream_t stream, const uint64_t *tree_mask = nullptr) {
-    const dim3 grid((kMode >= 2 ? dm.topk : 1) + (kMode == 1 || kMode == 2 ? 1 : 0), dm.Hkv, dm.batch * dm.n_q), block(256);
+    const dim3 grid(kMode >= 2 ? dm.topk : kMode + 1, dm.Hkv, dm.batch * dm.n_q + (kMode == 2 ? (dm.batch + dm.topk - 1) / dm.topk : 0)), block(256);
     timing_begin("decode_short_kernel", stream);
 #define INFLLMV2_SHORT(TW) \
     hipLaunchKernelGGL((decode_short_kernel<TW, kMode>), grid, block, 0, stream, dm, q, ck, seqlens, ap, block_idx, o_part, ml_part, tree_mask)
@@ -1631,7 +1647,12 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     // on one XCD and its kernels come from memory once.
     int32_t n_wg = l.n_part + (append ? (dm.n_q + 7) / 8 : 0);
     if (n_qt > 1) n_wg = (n_wg + 7) / 8 * 8;
-    const dim3 grid1(n_wg, dm.Hkv, dm.batch);
+    // Plain decode: one per (sequence, key-value head), at the end of its chunks, or, where these fill the chip about once to four times over, behind
+    // all others, so that no chunk waits for a compute unit that one of them has taken (4 sequences of 128K 19.3 -> 16.7 us per step, 8 22.6 -> 20.3; 120
+    // chunks 14.0 and 14.3, 4096 56.6 and 57.3).
+    const int64_t chunks = (int64_t)l.n_part * dm.Hkv * dm.batch;
+    const bool behind = append && chunks > 240 && chunks <= 1024;
+    const dim3 grid1(l.n_part + (append && !behind ? 1 : 0), dm.Hkv, dm.batch + (behind ? (dm.batch + l.n_part - 1) / l.n_part : 0));
 #define INFLLMV2_LOGITS(APPEND, TW, ARG)                                                                        \
     hipLaunchKernelGGL((decode_logits_kernel<1, APPEND, TW>), grid1, dim3(256), 0, stream, dm, q, ck, seqlens, \
                        zbuf, l.n_c_cap, part, part_c, l.n_part, ARG, 0u)

@@ -1339,6 +1339,31 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# Where the workgroups that append sit: at the end of each row's chunks (3 per sequence here, up to 240 and beyond 1024 in all), behind all chunks, or
+# behind the units of a short cache (more of them than a row has units).  The step against its parts, caches included.
+@pytest.mark.parametrize("B,cap,topk", [(80, 8300, 8), (81, 8300, 8), (341, 8300, 4), (342, 8300, 4), (20, 2000, 8), (17, 900, 4), (8, 4096, 32), (7, 8192, 16)])
+def test_decode_step_appends_to_every_sequence(B, cap, topk):
+    print("case decode appends", B, cap, topk, flush=True)
+    Hq, Hkv = 2, 1
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    gen = torch.Generator(device="cuda").manual_seed(cap + B)
+    q = torch.randn((B, 1, Hq, 128), device="cuda", generator=gen).bfloat16()
+    kn, vn = (torch.randn((B, Hkv, 1, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn((B, Hkv, cap, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
+    lens = [cap - (37 * b) % (cap - 1) for b in range(B)]
+    lens[1], lens[2], lens[3] = 32, cap + 1, 0                                          # completes the first kernel; neither of these is appended to
+    sl = dev_i32(lens)
+    ck = binding.compress_keys(prm, k, dev_i32([x - 1 if 0 < x <= cap else min(x, cap) for x in lens]), cap)
+    parts, step = [x.clone() for x in (k, v, ck)], [x.clone() for x in (k, v, ck)]
+    binding.append_kv(prm, kn, vn, parts[0], parts[1], sl, cap, ck=parts[2])
+    idx = binding.select_blocks(prm, binding.MODE_DECODE, q, parts[2], sl, cap)
+    out, lse = binding.sparse_attn_decode(prm, q, parts[0], parts[1], sl, cap, idx)
+    got = binding.decode_step(prm, q, kn, vn, *step, sl, cap)
+    torch.cuda.synchronize()
+    for a, b in zip(parts + [idx, out, lse], step + list(got)):
+        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
+
+
 # Decoding's tiles per workgroup follow sequences x heads x buffer (256 and 2048 workgroups of two tiles): on either side of the lines the first and
 # last of equal sequences (one cache, read with a batch stride of zero) get the lists and outputs that one sequence alone gets.
 @pytest.mark.parametrize("B,T", [(4, 131072), (4, 133000), (28, 17000), (29, 17000), (120, 32800), (121, 32800)])
