@@ -181,17 +181,23 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     __shared__ __align__(16) uint16_t newrows[kAppend && kQT > 1 ? kNewKernels * kQsPitch : 8];
     arguments_arrive(dm.Hkv, dm.G, dm.max_seqlen, dm.n_q, seqlens, ck.ptr, ck.sb, ck.sh, ck.st, zbuf, n_c_cap, part);
     arguments_arrive(q.ptr, q.sb, q.sh, q.st, dm.scale_log2, n_part, dm.rho);
-    int h = blockIdx.y, bz = blockIdx.z, bx = blockIdx.x;
-    if (kQT == 1 && kAppend && bz >= dm.batch) {          // behind all chunks: one appends to each (sequence, key-value head)
-        const int at = ((bz - dm.batch) * dm.Hkv + h) * n_part + bx;
-        if (at >= dm.batch * dm.Hkv) return;
-        bz = at / dm.Hkv;
-        h = at - bz * dm.Hkv;
-        bx = n_part;
+    const int n_qt = kQT == 1 ? 1 : (dm.n_q + kQT - 1) / kQT;            // query tiles per sequence (kQT = 1 is only launched with n_q = 1)
+    int h = blockIdx.y, bx = blockIdx.x, b = blockIdx.z, qi0 = 0;
+    bool appends = kAppend && kQT == 1 && bx >= n_part;
+    if (kAppend && (int)blockIdx.z >= dm.batch * n_qt) {  // behind all chunks: one appends up to eight tokens to a (sequence, key-value head)
+        const int n_app = kQT == 1 ? 1 : (dm.n_q + 7) / 8;
+        const int wide = n_qt > 1 ? (n_part + 7) & ~7 : n_part;          // (the grid's)
+        const int at = (((int)blockIdx.z - dm.batch * n_qt) * dm.Hkv + h) * wide + bx, unit = at / n_app;
+        if (unit >= dm.batch * dm.Hkv) return;
+        b = unit / dm.Hkv;
+        h = unit - b * dm.Hkv;
+        bx = n_part + at - unit * n_app;
+        appends = true;
+    } else if (n_qt > 1) {
+        if (bx >= n_part) return;
+        b = (int)__umulhi(blockIdx.z, n_qt_inv);
+        qi0 = ((int)blockIdx.z - b * n_qt) * kQT;
     }
-    const int n_qt = (dm.n_q + kQT - 1) / kQT;        // query tiles per sequence
-    const int b = kQT == 1 || n_qt == 1 ? bz : (int)__umulhi(blockIdx.z, n_qt_inv);   // kQT = 1 is only launched with n_q = 1
-    const int qi0 = kQT == 1 ? 0 : (bz - b * n_qt) * kQT;
     const int32_t L_raw = uniform_load(seqlens + b);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -208,9 +214,9 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     int new_from = 0x7fffffff;                        // several tokens: the kernels from here on are completed by them
     if constexpr (kAppend) {
         const bool live = L_raw >= dm.n_q && L_raw <= dm.max_seqlen;  // as the stand-alone append: others are skipped
-        if (bx >= n_part) {              // copies the rows of eight new tokens into the caches
+        if (appends) {                                // copies the rows of eight new tokens into the caches
             const int qi = (bx - n_part) * 8 + (threadIdx.x >> 5), c8 = (threadIdx.x & 15) * 8;
-            if (!live || qi0 > 0 || qi >= dm.n_q) return;
+            if (!live || qi >= dm.n_q) return;
             const int64_t at = L_raw - dm.n_q + qi;
             if (threadIdx.x & 16)
                 *reinterpret_cast<uint4 *>(ap.v.ptr + b * ap.v.sb + h * ap.v.sh + at * ap.v.st + c8) =
@@ -1643,16 +1649,15 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     timing_begin("decode_logits_kernel", stream);
     const AppendArgs no_append = {q, q, q, q};                       // unused placeholders
     const bool tw4 = decode_tiles_per_wave(dm) == 4;
-    // Behind the chunks, workgroups that append; several query tiles per sequence: a multiple of eight, so that all tiles of a chunk run
-    // on one XCD and its kernels come from memory once.
-    int32_t n_wg = l.n_part + (append ? (dm.n_q + 7) / 8 : 0);
-    if (n_qt > 1) n_wg = (n_wg + 7) / 8 * 8;
-    // Plain decode: one per (sequence, key-value head), at the end of its chunks, or, where these fill the chip about once to four times over, behind
-    // all others, so that no chunk waits for a compute unit that one of them has taken (4 sequences of 128K 19.3 -> 16.7 us per step, 8 22.6 -> 20.3; 120
-    // chunks 14.0 and 14.3, 4096 56.6 and 57.3).
+    // Workgroups that append.  Plain decode: one per (sequence, key-value head), at the end of its chunks, or, where these fill the chip about once to
+    // four times over, behind all others, so that no chunk waits for a compute unit that one of them has taken (4 sequences of 128K 19.3 -> 16.7 us per
+    // step, 8 22.6 -> 20.3; 120 chunks 14.0 and 14.3, 4096 56.6 and 57.3).  Verification: always behind all.  Several query tiles per
+    // sequence: the chunks are made a multiple of eight, so that all tiles of one run on one XCD and its kernels come from memory once.
     const int64_t chunks = (int64_t)l.n_part * dm.Hkv * dm.batch;
-    const bool behind = append && chunks > 240 && chunks <= 1024;
-    const dim3 grid1(l.n_part + (append && !behind ? 1 : 0), dm.Hkv, dm.batch + (behind ? (dm.batch + l.n_part - 1) / l.n_part : 0));
+    const bool behind = append && (dm.n_q > 1 || (chunks > 240 && chunks <= 1024));
+    const int32_t n_wg = n_qt > 1 ? (l.n_part + 7) / 8 * 8 : l.n_part + (append && !behind ? 1 : 0);
+    const int32_t planes = behind ? (int32_t)(((int64_t)dm.batch * ((dm.n_q + 7) / 8) + n_wg - 1) / n_wg) : 0;
+    const dim3 grid1(n_wg, dm.Hkv, dm.batch * n_qt + planes);
 #define INFLLMV2_LOGITS(APPEND, TW, ARG)                                                                        \
     hipLaunchKernelGGL((decode_logits_kernel<1, APPEND, TW>), grid1, dim3(256), 0, stream, dm, q, ck, seqlens, \
                        zbuf, l.n_c_cap, part, part_c, l.n_part, ARG, 0u)
@@ -1663,12 +1668,11 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
         if (tw4) INFLLMV2_LOGITS(false, 4, no_append);
         else INFLLMV2_LOGITS(false, 2, no_append);
     } else {
-        const dim3 grid(n_wg, dm.Hkv, dm.batch * n_qt);
         if (append)
-            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, true, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
+            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, true, kVerifyTiles>), grid1, dim3(256), 0, stream, dm, q, ck, seqlens,
                                nullptr, 0, part, part_c, l.n_part, *append, n_qt_inv);
         else
-            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, false, kVerifyTiles>), grid, dim3(256), 0, stream, dm, q, ck, seqlens,
+            hipLaunchKernelGGL((decode_logits_kernel<kVerifyQT, false, kVerifyTiles>), grid1, dim3(256), 0, stream, dm, q, ck, seqlens,
                                nullptr, 0, part, part_c, l.n_part, no_append, n_qt_inv);
     }
 #undef INFLLMV2_LOGITS
