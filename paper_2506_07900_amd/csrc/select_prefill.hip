@@ -29,8 +29,6 @@ template <int G> struct SelCfg {
 __device__ inline int n_visible(int i) { return num_kernels(i + 1); }
 
 // A chunk of compressed keys on its way to LDS: asked for one chunk ahead, so that its round trip runs under the chunk at hand.  Rows past
-// the last kernel repeat it; their scores are masked.
-// A chunk of compressed keys on its way to LDS: asked for one chunk ahead, so that its round trip runs under the chunk at hand.  Rows past
 // the last kernel repeat it; their scores are masked.  Both passes, us, two heads: loaded where they are stored and short rows first 8 : 1 heads,
 // 16000 tokens 214, 4 : 1, 12000 84, 1 : 1, 12000 78; longest rows first 170, 77, 67; and a chunk ahead 164, 67, 53.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
