@@ -1517,10 +1517,9 @@ __global__ __launch_bounds__(64) void decode_merge_kernel(Dims dm, const float *
         num.y += wc * __uint_as_float(ov[c][1]);
     }
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16x2 o;
-    const float inv = 1.f / (den > 0.f ? den : 1.f);
-    o[0] = (__bf16)(den > 0.f ? num.x * inv : 0.f);
-    o[1] = (__bf16)(den > 0.f ? num.y * inv : 0.f);
+    bf16x2 o;                                            // (quotients: a reciprocal for both would round once more, and saves under 0.1 us a step)
+    o[0] = (__bf16)(den > 0.f ? num.x / den : 0.f);
+    o[1] = (__bf16)(den > 0.f ? num.y / den : 0.f);
     *reinterpret_cast<bf16x2 *>(out.ptr + b * out.sb + qi * out.st + (int64_t)hq * out.sh + 2 * lane) = o;
     if (lane == 0) lse[row] = den > 0.f ? (M + fast_log2(den)) * kLn2 : -INFINITY;
 }

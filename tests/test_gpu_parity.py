@@ -1339,6 +1339,45 @@ def test_decode_step_many_sequences(B):
         assert out_err(o1[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(l1[b].double().cpu().numpy(), wl[0]) <= 1.0
 
 
+# The merge divides.  With queries of zero every key weighs 1, so an output is the exact mean of integer values: here one that lies halfway between two
+# bf16 numbers, where the quotient rounds to the even one, and a product with the reciprocal, one rounding more, to its neighbour.  One merge kernel per
+# top-k of up to 8, 16, 32 and 64; one to four blocks.
+@pytest.mark.parametrize("L,topk", [(7, 8), (15, 16), (63, 32), (122, 64), (60, 8), (255, 24)])
+def test_decoded_means_are_quotients(L, topk):
+    print("case decoded means", L, topk, flush=True)
+    Hq, Hkv, T = 4, 1, 320
+    prm = binding.Params(Hq, Hkv, topk=topk)
+    f = np.float32
+
+    def bf16(x):
+        return synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(np.asarray(x, f)))
+
+    odd = np.arange(257, 463, 2)                                          # halfway between the even integers that bf16 holds there
+    tells = bf16((odd * L).astype(f) * (f(1) / f(L))) != bf16(odd)
+    mean = np.resize(odd[tells], 128)
+    v = np.zeros((T, 128), np.int64)
+    for c, m in enumerate(mean):                                          # L integers of bf16 with that mean
+        col = np.where(np.arange(L) < L // 2, m - 1, m + 1)
+        if L % 2:                                                         # one odd value, below 256, and what it lacks over the others
+            col[0] = 255
+            more, rest = divmod(int(m * L - col.sum()) // 2, L - 1)
+            col[1:] += 2 * more
+            col[1:1 + rest] += 2
+        assert col.sum() == m * L and (bf16(col) == col).all()
+        v[:L, c] = col
+    vd = torch.from_numpy(v).cuda().bfloat16().reshape(1, Hkv, T, 128)
+    kd = torch.randn((1, Hkv, T, 128), device="cuda").bfloat16()
+    q = torch.zeros((1, 1, Hq, 128), device="cuda", dtype=torch.bfloat16)
+    sl = dev_i32([L])
+    ck = binding.compress_keys(prm, kd, sl, T)
+    want = torch.from_numpy(bf16(mean)).cuda().bfloat16().expand(Hq, 128)  # to nearest, ties to even
+    idx = binding.select_blocks(prm, binding.MODE_DECODE, q, ck, sl, T)
+    out, lse = binding.sparse_attn_decode(prm, q, kd, vd, sl, T, idx)
+    torch.cuda.synchronize()
+    assert torch.equal(out.reshape(Hq, 128), want), int((out.reshape(Hq, 128) != want).sum())
+    assert float((lse - float(np.log(L))).abs().max()) <= 1e-5
+
+
 # Where the workgroups that append sit: at the end of each row's chunks (3 per sequence here, up to 240 and beyond 1024 in all), behind all chunks, or
 # behind the units of a short cache (more of them than a row has units).  The step against its parts, caches included.
 @pytest.mark.parametrize("B,cap,topk", [(80, 8300, 8), (81, 8300, 8), (341, 8300, 4), (342, 8300, 4), (20, 2000, 8), (17, 900, 4), (8, 4096, 32), (7, 8192, 16)])
