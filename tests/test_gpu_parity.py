@@ -933,17 +933,18 @@ def test_verify_append_writes_rows_and_completed_kernels():
 
 # One call against its parts, bit for bit: new kernels on either side of a workgroup's 128, caches no longer than the draft, a length
 # beyond the cache, both widths of the scoring workgroups; buffers (three longer than the longest) of up to 4096 tokens, whose rows one kernel
-# scores, on either side of the workgroups up to which it attends as well; longer ones on either side of those up to which every workgroup ranks.
+# scores, on either side of the workgroups up to which it attends as well; longer ones on either side of those up to which every workgroup ranks, fewer
+# beyond 131072 tokens, whose lists are more than are merged.
 @pytest.mark.parametrize("seqlens,n,Hq,Hkv,topk,rho", [
     ([2080, 2079, 2096, 4128, 31], 33, 32, 2, 16, 1), ([2081, 2, 33, 1], 2, 4, 1, 6, 1), ([4200, 64, 95, 63, 9999], 64, 16, 2, 64, 1),
     ([3000, 2090], 16, 16, 1, 24, 2), ([1021], 32, 32, 2, 16, 1), ([1021], 33, 8, 2, 16, 1), ([4093], 16, 32, 2, 16, 1),
     ([4093, 20], 17, 2, 1, 32, 1), ([4094], 16, 32, 2, 16, 1), ([5000], 64, 8, 2, 16, 1), ([5000], 64, 8, 2, 17, 1), ([5000], 42, 4, 1, 24, 1),
-    ([5000], 43, 4, 1, 24, 1)])
+    ([5000], 43, 4, 1, 24, 1), ([131069], 64, 4, 1, 17, 1), ([131070], 64, 4, 1, 16, 1), ([131070], 64, 4, 1, 17, 1)])
 def test_verify_step_equals_its_parts(seqlens, n, Hq, Hkv, topk, rho):
     print("case verify step", seqlens, n, Hq, Hkv, topk, rho, flush=True)
     prm = binding.Params(Hq, Hkv, topk=topk, lse_coarse_ratio=rho)
     gen = torch.Generator(device="cuda").manual_seed(12)
-    B, T = len(seqlens), max(x for x in seqlens if x < 9000) + 3
+    B, T = len(seqlens), max(x for x in seqlens if x != 9999) + 3
     q = torch.randn((B, n, Hq, 128), device="cuda", generator=gen).bfloat16()
     kn, vn = (torch.randn((B, Hkv, n, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
     k, v = (torch.randn((B, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
@@ -1304,16 +1305,16 @@ def test_sparse_attn_prefill_shared(seqlens, Hq, Hkv, topk, planted):
         assert bool((out[b, l:] == 0).all())
 
 
-@pytest.mark.parametrize("B", [4, 17])
-def test_decode_step_many_sequences(B):
-    # the decode selection covers more kernels per workgroup from 4 sequences on: one step on a ragged
-    # batch, every sequence against the oracle (lengths include steps that complete a kernel)
+@pytest.mark.parametrize("B,first", [(4, 4128), (17, 4128), (4, 8240), (17, 8240)])
+def test_decode_step_many_sequences(B, first):
+    # one step on a ragged batch, every sequence against the oracle (lengths include steps that complete a kernel); one kernel scores a row of up to
+    # 8192 tokens; beyond, the selection has kernels of its own
     Hq, Hkv, topk = 32, 2, 8
     prm = binding.Params(Hq, Hkv, topk=topk)
     oprm = oracle_params(prm)
     rng = np.random.default_rng(77)
     lens = [int(rng.integers(40, 5000)) for _ in range(B)]
-    lens[0], lens[1], lens[2] = 4128, 48, 1025                              # 4128 and 48 complete a kernel
+    lens[0], lens[1], lens[2] = first, 48, 1025                             # 4128, 8240 and 48 complete a kernel
     q, k, v, T = make_batch(97, lens, Hq, Hkv, n_planted=3)
     q1 = np.stack([q[b, l - 1] for b, l in enumerate(lens)])[:, None]
     kn = np.stack([k[b, :, l - 1] for b, l in enumerate(lens)])[:, :, None]
@@ -1403,26 +1404,105 @@ def test_decode_step_appends_to_every_sequence(B, cap, topk):
         assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
 
 
-# Decoding's tiles per workgroup follow sequences x heads x buffer (256 and 2048 workgroups of two tiles): on either side of the lines the first and
-# last of equal sequences (one cache, read with a batch stride of zero) get the lists and outputs that one sequence alone gets.
+def without_partial(q, ck, L, p, topk):
+    """Block list of a decoding query whose log-sum-exps lack the p-th 128 kernels (p < 0: none).  q [Hq, d], ck [n_c, d] in 64 bits, one key-value
+    head, 1 + 2 blocks forced."""
+    z = q @ ck.T * q.shape[1] ** -0.5
+    counted = np.where(np.arange(len(ck)) // 128 == p, -np.inf, z)
+    m = counted.max(1, keepdims=True)
+    r = np.exp(z - m - np.log(np.exp(counted - m).sum(1, keepdims=True))).mean(0)
+    n = (L - 1) // 64 + 1
+    r = np.concatenate([[-np.inf], r, np.full(4 * n + 4 - len(r), -np.inf)])                # block j: kernels 4j - 1 .. 4j + 3
+    score = np.array([r[4 * j:4 * j + 5].max() for j in range(n)])
+    picks = sorted(range(1, n - 2), key=lambda j: (-score[j], j))[:topk - 3]
+    return np.array(sorted([0, n - 2, n - 1] + picks), np.int32)[None, None]
+
+
+def rows_that_tell_partials(T, lens, Hq=16, topk=16, d=128):
+    """A cache of T tokens, one key-value head, and four queries at its rows lens[i] - 1 whose picks move if a partial of their log-sum-exps is lost or
+    counted for another head.  Half of a row's picks are blocks that two of its heads each put nearly all their weight on, in eight of the partials of
+    128 kernels, the first, the last and those around the middle among them; which the others are follows from the heads' log-sum-exps.
+    -> k, v [1, T, d], queries [4][Hq, d] as bits, what the oracle selects [4]."""
+    oprm = ref.Params(Hq, 1, topk=topk)
+    rng = np.random.default_rng(T)
+    n_part = (ref.num_kernels(T, 32, 16) + 127) // 128
+    u = rng.standard_normal((n_part, d)).astype(np.float32)
+    u *= d ** 0.5 / np.linalg.norm(u, axis=1, keepdims=True)
+    k = rng.standard_normal((T, d), dtype=np.float32) * np.exp(rng.standard_normal((T, 1), dtype=np.float32))
+    for p in range(n_part):                               # a block of keys along u[p] within the kernels of every partial
+        at = 2048 * p + (64 * (4 + 7 * p % 24) if 2048 * (p + 1) <= T - 1000 else 0)
+        k[at:at + 64] = (u[p] + 0.1 * rng.standard_normal((64, d), dtype=np.float32))[:T - at]
+    k = synth.f32_to_bf16_bits(k)[None]
+    v = synth.f32_to_bf16_bits(rng.standard_normal((1, T, d), dtype=np.float32))
+    qs, want, lost = [], [], 0
+    for b, L in enumerate(lens):
+        _, ck = ref.compress_keys(np.ascontiguousarray(k[:, :L]), oprm)
+        n = (ck.shape[1] + 127) // 128
+        parts = [(i * n // 8 + (0, 3, 5, n - 1 - 7 * n // 8)[b]) % n for i in range(8)]
+        q = rng.standard_normal((Hq, d), dtype=np.float32)
+        for h in range(Hq):
+            q[h] += (8 + 6 * (5 * h % 16) / 15) * d ** -0.5 * u[parts[h % 8]]
+        qs.append(synth.f32_to_bf16_bits(q))
+        want.append(ref.select_blocks(qs[b][None], ck, np.array([L - 1], np.int32), oprm, want_scores=True))
+        q64, ck64 = (synth.bf16_bits_to_f32(x).astype(np.float64) for x in (qs[b], ck[0]))
+        assert not compare_selection(without_partial(q64, ck64, L, -1, topk), *want[b])[3]
+        lost += sum(len(compare_selection(without_partial(q64, ck64, L, p, topk), *want[b])[3]) for p in parts)
+    assert lost >= 24, "the inputs do not tell whether a partial is missing"     # of 32, by more than a near-tie
+    return k, v, qs, want
+
+
+# Decoding's tiles per workgroup follow sequences x heads x buffer (256 and 2048 workgroups of two tiles), and with them what a log-sum-exp is added
+# up from: partials of 128 or of 256 kernels.  On either side of both lines, steps against the oracle.
 @pytest.mark.parametrize("B,T", [(4, 131072), (4, 133000), (28, 17000), (29, 17000), (120, 32800), (121, 32800)])
 def test_decode_tiles_by_workgroups(B, T):
     print("case decode tiles", B, T, flush=True)
-    Hq, Hkv = 16, 1
-    prm = binding.Params(Hq, Hkv, topk=16)
-    gen = torch.Generator(device="cuda").manual_seed(T)
-    k, v = (torch.randn((1, Hkv, T, 128), device="cuda", generator=gen).bfloat16() for _ in range(2))
-    q = torch.randn((1, 1, Hq, 128), device="cuda", generator=gen).bfloat16()
-    ck = binding.compress_keys(prm, k, dev_i32([T]), T)
-    n = [T, T - 1000]
-    many = [n[b % 2] for b in range(B)]
-    want = [binding.select_blocks(prm, binding.MODE_DECODE, q, ck, dev_i32([x]), T) for x in n]
-    kb, vb, cb = (x.expand(B, -1, -1, -1) for x in (k, v, ck))
-    got = binding.select_blocks(prm, binding.MODE_DECODE, q.expand(B, -1, -1, -1).contiguous(), cb, dev_i32(many), T)
+    prm = binding.Params(16, 1, topk=16)
+    lens = [T, T - 1000, T - 1000, T]
+    k, v, qs, want = rows_that_tell_partials(T, lens)
+    kd, vd = (to_dev(x).expand(B, 1, T, 128).contiguous() for x in (k, v))
+    of = [b % 4 for b in range(B)]
+    qd, sl = to_dev(np.stack(qs))[of][:, None], dev_i32([lens[b] for b in of])
+    kn, vn = (to_dev(np.stack([x[:, L - 1:L] for L in lens]))[of] for x in (k, v))
+    for b in range(B):
+        kd[b, :, lens[of[b]] - 1:] = 0                    # (the step appends the last row; what lies behind it is not looked at)
+        vd[b, :, lens[of[b]] - 1:] = 0
+    ck = binding.compress_keys(prm, kd, sl - 1, T)
+    idx, out, lse = binding.decode_step(prm, qd, kn, vn, kd, vd, ck, sl, T)
+    alone = binding.select_blocks(prm, binding.MODE_DECODE, qd, ck, sl, T)
     torch.cuda.synchronize()
-    for b in (0, 1, B // 2, B - 2, B - 1):
-        same = len(set(got[b].flatten().tolist()) & set(want[b % 2][0].flatten().tolist()))
-        assert same >= 15, (b, same)                     # (another grouping of the log-sum-exp's sums: a near-tie may fall the other way)
+    assert torch.equal(alone, idx)
+    for b in range(4, B):                                 # equal sequences, equal results
+        assert torch.equal(idx[b], idx[of[b]]) and torch.equal(lse[b], lse[of[b]]), b
+        assert torch.equal(out[b].view(torch.int16), out[of[b]].view(torch.int16)), b
+    near = 0
+    for b, L in enumerate(lens):
+        got = idx[b].cpu().numpy()
+        _, _, nt, hard = compare_selection(got, *want[b])
+        assert not hard, (b, hard)
+        near += nt
+        wo, wl = ref.sparse_attn(qs[b][None], np.ascontiguousarray(k[:, :L]), np.ascontiguousarray(v[:, :L]), np.array([L - 1], np.int32), got,
+                                 oracle_params(prm))
+        assert out_err(out[b].double().cpu().numpy(), wo) <= 1.0 and lse_err(lse[b].double().cpu().numpy(), wl[0]) <= 1.0, b
+    assert near <= 1
+
+
+# Verification merges 64 partials of a log-sum-exp at a time: 8192 kernels, one more, and as many as a buffer may have.
+@pytest.mark.parametrize("T", [131088, 131104, 262144])
+def test_verify_selection_partials(T):
+    print("case verify partials", T, flush=True)
+    prm = binding.Params(16, 1, topk=16)
+    lens = [T - 3, T - 2, T - 1, T]
+    k, v, qs, want = rows_that_tell_partials(T, lens)
+    kd, sl = to_dev(k)[None], dev_i32([T])
+    ck = binding.compress_keys(prm, kd, sl, T)
+    idx = binding.select_blocks_verify(prm, to_dev(np.stack(qs))[None], ck, sl, T)
+    torch.cuda.synchronize()
+    near = 0
+    for t in range(4):
+        _, _, nt, hard = compare_selection(idx[0, :, t:t + 1].cpu().numpy(), *want[t])
+        assert not hard, (t, hard)
+        near += nt
+    assert near <= 1
 
 
 # Short prompts read keys and values where they lie: both sides of its lines, padded and interleaved token strides, an end inside a
