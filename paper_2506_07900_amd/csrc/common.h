@@ -94,6 +94,18 @@ __device__ inline uint16_t f64_to_bf16_rne(double x) {
     return (uint16_t)(r >> 16);
 }
 
+// Two channels of a semantic kernel from their 32 rows, a bf16 pair each: the sum runs in fp64 in token order, exact for bf16 inputs, and is rounded
+// once.  Wherever a kernel is built, by compress_keys or by the step whose token completes it, these are its bits.
+__device__ __forceinline__ uint32_t kernel_mean(const uint32_t (&row)[kKernel]) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int t = 0; t < kKernel; ++t) {
+        s0 += (double)__uint_as_float(row[t] << 16);
+        s1 += (double)__uint_as_float(row[t] & 0xffff0000u);
+    }
+    return (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) | ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+}
+
 // 16x16x32 bf16 MFMA, D = A*B + C.
 //   A is 16(M) x 32(K): lane l holds row l%16, k = 8*(l/16) .. 8*(l/16)+7
 //   B is 32(K) x 16(N): lane l holds column l%16, same k range

@@ -30,13 +30,7 @@ __global__ __launch_bounds__(64 * kCompressWaves) void compress_keys_kernel(Dims
             uint32_t x[kKernel];
 #pragma unroll
             for (int t = 0; t < kKernel; ++t) x[t] = reinterpret_cast<const uint32_t *>(rows + t * k.st)[lane];
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-            for (int t = 0; t < kKernel; ++t) {
-                s0 += (double)__uint_as_float(x[t] << 16);
-                s1 += (double)__uint_as_float(x[t] & 0xffff0000u);
-            }
-            w = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) | ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+            w = kernel_mean(x);
         }
         reinterpret_cast<uint32_t *>(ck.ptr + (ck_head + (int64_t)jh * ck.st))[lane] = w;
     }
