@@ -270,13 +270,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
                     const __bf16 *p = t < t_new ? ap.k.ptr + (old_at + t * ap.k.st) : ap.k_new.ptr + (new_at + t * ap.k_new.st);
                     row[t] = reinterpret_cast<const uint32_t *>(p)[lane];
                 }
-                double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-                for (int t = 0; t < kKernel; ++t) {
-                    s0 += (double)__uint_as_float(row[t] << 16);
-                    s1 += (double)__uint_as_float(row[t] & 0xffff0000u);
-                }
-                const uint32_t x = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) | ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+                const uint32_t x = kernel_mean(row);
                 *reinterpret_cast<uint32_t *>(&newrows[(jh - build_from) * kQsPitch + 2 * lane]) = x;
                 if (qi0 + kQT >= dm.n_q)                  // the last query tile sees every kernel: it stores them
                     reinterpret_cast<uint32_t *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh * ck.st)[lane] = x;
@@ -305,14 +299,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 #pragma unroll
             for (int t = 0; t < kKernel - 1; ++t) rowv[t] = reinterpret_cast<const uint32_t *>(kc + t * ap.k.st)[lane];
             rowv[kKernel - 1] = reinterpret_cast<const uint32_t *>(ap.k_new.ptr + (b * ap.k_new.sb + h * ap.k_new.sh))[lane];
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-            for (int t = 0; t < kKernel; ++t) {
-                s0 += (double)__uint_as_float(rowv[t] << 16);
-                s1 += (double)__uint_as_float(rowv[t] & 0xffff0000u);
-            }
-            const uint32_t packed = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) |
-                                    ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+            const uint32_t packed = kernel_mean(rowv);
             newrow[lane] = packed;
             *reinterpret_cast<uint32_t *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh_new * ck.st + 2 * lane) = packed;
             // same wavefront wrote newrow: LDS keeps the order.  The lanes whose operand row it is take it from there.
@@ -1337,8 +1324,8 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
         if (cidx == 0 && tid < dm.topk) orow[tid] = -1;
     } else {
         if constexpr (kOneRow) {
-            // the semantic kernel the new token completes: rows L-32 .. L-2 from the cache, row L-1 from k_new, fp64 sum in
-            // token order, one rounding (the bits of compress_keys_kernel); lane = channels 2*lane, 2*lane+1
+            // the semantic kernel the new token completes: rows L-32 .. L-2 from the cache, row L-1 from k_new; lane = channels
+            // 2*lane, 2*lane+1
             const int jh_new = n_vis - 1;
             const bool closes = live && L >= kKernel && (L - kKernel) % kStride == 0;
             if (closes && jh_new >= jw && jh_new < jw + 16 * kTW && (rr.n_pick > 0 || cidx == 0)) {   // uniform over the wave
@@ -1347,14 +1334,7 @@ __global__ __launch_bounds__(256) void decode_short_kernel(Dims dm, Tensor q, Te
 #pragma unroll
                 for (int t = 0; t < kKernel - 1; ++t) rowv[t] = reinterpret_cast<const uint32_t *>(kc + t * ap.k.st)[lane];
                 rowv[kKernel - 1] = reinterpret_cast<const uint32_t *>(ap.k_new.ptr + (b * ap.k_new.sb + h * ap.k_new.sh))[lane];
-                double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-                for (int t = 0; t < kKernel; ++t) {
-                    s0 += (double)__uint_as_float(rowv[t] << 16);
-                    s1 += (double)__uint_as_float(rowv[t] & 0xffff0000u);
-                }
-                const uint32_t packed = (uint32_t)f64_to_bf16_rne(s0 / (double)kKernel) |
-                                        ((uint32_t)f64_to_bf16_rne(s1 / (double)kKernel) << 16);
+                const uint32_t packed = kernel_mean(rowv);
                 newrow[lane] = packed;
                 if (cidx == 0) *reinterpret_cast<uint32_t *>(ck.ptr + b * ck.sb + h * ck.sh + (int64_t)jh_new * ck.st + 2 * lane) = packed;
                 __builtin_amdgcn_wave_barrier();          // same wavefront: LDS keeps the order
