@@ -345,12 +345,14 @@ int32_t infllmv2_decode_step(const infllmv2_params *prm, const infllmv2_tensor *
  * infllmv2_verify_step          the three calls in one (ck required), four launches instead of six
  *                               (the top-k is folded into the per-block attention kernel unless
  *                               batch * n_draft * Hkv * topk exceeds 2048 (1024 where more than 16 blocks are
- *                               picked by score), the append into the first
- *                               selection kernel unless lse_coarse_ratio > 1 or n_draft == 1: one
- *                               launch more each); with max_seqlen <= 4096 and the exact log-sum-exp three
- *                               (append; selection and attention; merge), four when that product exceeds 1024, 768, 512 for
- *                               max_seqlen <= 1024, 2048, 4096; the same caches, ck, block_idx, out and lse bit
- *                               for bit.
+ *                               picked by score, with max_seqlen > 131072, and above 65536 where
+ *                               ceil(max_seqlen / 4096) * batch * Hkv * ceil(n_draft / 4) is less than 128),
+ *                               the append into the first selection kernel unless lse_coarse_ratio > 1
+ *                               or n_draft == 1: one launch more each); with max_seqlen <= 4096 (n_draft == 1:
+ *                               8192) and the exact log-sum-exp three (append; selection and attention;
+ *                               merge), four when that product exceeds 1024, 768, 512, 256 for
+ *                               max_seqlen <= 1024, 2048, 4096, 8192; the same caches, ck, block_idx, out
+ *                               and lse bit for bit.
  * Workspaces: infllmv2_verify_workspace_bytes(INFLLMV2_OP_SELECT_VERIFY / _ATTN_VERIFY /
  * _VERIFY_STEP, ...) (0 if the arguments are invalid), 256-byte aligned.
  */

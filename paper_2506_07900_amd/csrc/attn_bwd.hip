@@ -58,14 +58,15 @@ constexpr int kMostSteps = 64;
 // the queues: a workgroup finds its item by its own number and ends with it.  (Drawn from the queues, every workgroup asked all eight for
 // more, one round trip after another.)  Where items are few, two or four workgroups take a part of an item's steps each; more
 // parts than that lose to the sums: the chip adds about 270 words per ns, 61 ns per item or part of one (300 tokens, G = 16, 55 items in 1 / 2 / 3 / 4
-// parts 20.2 / 18.4 / 21.0 / 23.5 us; 700, G = 4, 28.2 / 19.1 / 21.5 in 1 / 2 / 3).  dk/dv, 2 heads, top-k 16, queues / now, us: G = 16, 150 tokens
-// 39 / 14, 500 47 / 25, 1000 65 / 50; G = 8, 500 42 / 20; G = 1, 500 29 / 14, 1000 33 / 16, 2000 38 / 24.
+// parts 20.2 / 18.4 / 21.0 / 23.5 us; 700, G = 4, 28.2 / 19.1 / 21.5 in 1 / 2 / 3).  dk/dv, 2 heads, top-k 16, one pair each, queues / by number, us:
+// G = 16, 150 tokens 39 / 14, 500 45 / 31, 1000 65 / 64; G = 8, 500 41 / 20, 1000 47 / 36; G = 1, 500 29 / 13, 1000 34 / 17, 2000 36 / 25.
 constexpr int kPartItems = 128;
 // What is left of a call of few steps per workgroup are its sums, all at the same time.  Up to a share of kPairSteps steps an item has two pairs of
 // wavefronts, half its steps each, whose sums meet in LDS before they are added to the block's: half the workgroups, items of twice the share and
-// half the additions.  One pair / two: G = 16, 1000 tokens 65 / 50 us, 2000 97 / 82; G = 8, 1000 37 / 32, 2500 79 / 67; G = 4, 5000
-// 101 / 86; G = 1, 12000 105 / 91; 2 x 4096, G = 8 (64 steps) 185 / 180.  Beyond, two pairs in step wait for each other: 12000, G = 8 261 / 264, 32K, G = 16
-// 1097 / 1180.
+// half the additions.  One pair / two, both by number where that fits: G = 16, 500 tokens 31 / 25 us, 1000 64 / 50, 2000 101 / 81; G = 8, 500 20 / 18, 1000
+// 36 / 31, 2500 76 / 64; G = 4, 5000 95 / 79; G = 1, 12000 108 / 87; 2 x 4096, G = 8 (64 steps) 185 / 180.  Short calls of G = 1 lose a little (300
+// tokens 11.2 / 12.9, 800 15.7 / 17.0, 2000 24.6 / 26.4, 4000 35.0 / 35.9); they have two all the same, for the one kernel that finds items by number.
+// Beyond, two pairs in step wait for each other: 12000, G = 8 261 / 264, 32K, G = 16 1097 / 1180.
 constexpr int kPairSteps = 64;
 __host__ __device__ constexpr int least_steps(int G, int pairs) { return (G == 16 ? 8 : 12) * pairs; }
 __host__ __device__ inline int members_of(int steps, int G, int pairs = 1) {

@@ -106,10 +106,9 @@ struct RowRange {
 // covers kTW tiles of 16 kernels per wave, one of part 2 verify_tiles2 (plus one halo tile).  More
 // tiles per wave mean fewer workgroups and fewer log-sum-exp partials for part 2 to merge (every
 // workgroup of part 2 reads all partials of its heads); fewer tiles spread a lone step over more compute
-// units.  Measured at 128K context, plain decode, 1 / 2 / 4 tiles: 21.6 / 21.1 / 21.6 us per step for
-// one sequence, 27.2 / 26.8 / 25.8 us for the ragged batch of 8, 73 / 62 / 61 us for 32 sequences (eight
-// tiles: 63 us);
-// verification (4 to 64 drafted tokens): under 10 % between them.
+// units.  Measured at 128K context, plain decode in a graph, 2 / 4 tiles: 14.2 / 15.0 us per step for
+// one sequence, 14.5 / 15.4 for two, 16.6 / 16.1 for three, 20.7 / 19.9 for the ragged batch of 8, 49.9 / 50.9 for 32;
+// one sequence of 32K 13.5 / 14.5.
 constexpr int kVerifyQT = 4;
 constexpr int kVerifyTiles = 2;                                                          // part 1, verification
 // Part 1, plain decode: two for up to three sequences; for more, four where workgroups of two tiles are neither few enough for a compute unit each
@@ -447,7 +446,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
 }
 
 // ---- part 2, several queries per sequence: block scores ----------------------------------------------
-// grid (n_lists, Hkv, B * ceil(n_q/kQT)), 256 threads (every block has a workgroup, also a
+// grid (n_lists, Hkv, B * ceil(n_q/kQT)), 512 threads (every block has a workgroup, also a
 // last one too short to hold a complete kernel).  Workgroup bx pools blocks
 // 16*kTW*bx .. +16*kTW-1 of kQT consecutive query tokens; block j needs kernels 4j-1 .. 4j+3, so the
 // workgroup scores 4*kTW+1 tiles of 16 kernels starting one tile before its chunk (of that halo tile
@@ -1556,7 +1555,8 @@ size_t select_decode_ws_bytes(const Dims &dm) {
 // One workgroup per row can score it all (see decode_short_kernel); the approximate log-sum-exp keeps the long path.
 static bool short_cache(const Dims &dm) { return dm.rho == 1 && dm.max_seqlen <= (dm.n_q == 1 ? kShortTokens : kShortVerify); }
 // Fused top-k and attention: every workgroup repeats the top-k of its row, which is free while compute units idle and
-// costs throughput once the launch fills the machine many times over; merging sorted lists costs less than counting.  Measured (us per step,
+// costs throughput once the launch fills the machine many times over; merging sorted lists (up to 32 of up to 16 words: any context in plain decode,
+// in verification up to 131072 tokens, or 65536 where its lists are of 32 blocks) costs less than counting.  Measured (us per step,
 // fused / apart), merged: 1536 units 32.6 / 34.8 (48 sequences of 20K), 2048 37.4 / 39.2 (64), 34.0 / 36.0 and 33.2 / 34.8 (64 and 2 x 32 drafted
 // tokens at 30K); counted: 1024 56.6 / 58.3, 42.3 / 44.0, 1920 31.5 / 30.1 (top-k 48) and 46.3 / 38.5 (30 drafted, top-k 64).
 static bool fuse_units(const Dims &dm, bool merged) {  // by (row, key-value head, block) workgroups
