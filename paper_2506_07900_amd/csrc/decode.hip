@@ -121,6 +121,17 @@ static inline int decode_tiles_per_wave(const Dims &dm) {
     return dm.batch < 4 || (dm.rho == 1 && (n <= 256 || n >= 2048)) ? 2 : 4;
 }
 
+// Part 1, verification: how many columns the grid has for a row's chunks.  A multiple of eight runs all query tiles of a chunk on one XCD, so that its
+// kernels come from memory once; the columns that are added are empty, and the XCDs without them have up to twice the others' work.  It pays for
+// few tiles per chunk, and while these do not fill the chip.  us, chunks' number / a multiple: 8 tiles per chunk (16 drafted, 2 heads), 10 chunks 6.2 / 5.8, 50
+// 7.3 / 6.8, 90 9.1 / 8.3, 106 9.8 / 10.0; 16 tiles, 18 chunks 7.2 / 6.7, 42 8.6 / 8.4, 50 9.6 / 9.8, 58 10.1 / 11.5; 24 tiles, 10 chunks 6.2 / 7.1, 30 8.6 / 10.0,
+// 58 12.9 / 14.3; 96 tiles (3 sequences, 32 drafted, 4 heads), 10 chunks 10.3 / 13.5; 128 tiles, 26 chunks 19.9 / 27.0.
+__host__ __device__ inline int verify_columns(const Dims &dm, int n_qt, int n_part) {
+    const int wide = (n_part + 7) & ~7;
+    const int64_t tiles = (int64_t)dm.Hkv * dm.batch * n_qt;
+    return n_qt > 1 && tiles <= 16 && tiles * wide <= 768 ? wide : n_part;
+}
+
 // length of the cache up to and including query token qi of sequence b (0: no such row)
 __device__ inline int row_len(const Dims &dm, int L_all, int qi) {
     return (L_all < dm.n_q || qi >= dm.n_q) ? 0 : L_all - (dm.n_q - 1 - qi);
@@ -185,7 +196,7 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(Dims dm, Tensor q, T
     bool appends = kAppend && kQT == 1 && bx >= n_part;
     if (kAppend && (int)blockIdx.z >= dm.batch * n_qt) {  // behind all chunks: one appends up to eight tokens to a (sequence, key-value head)
         const int n_app = kQT == 1 ? 1 : (dm.n_q + 7) / 8;
-        const int wide = n_qt > 1 ? (n_part + 7) & ~7 : n_part;          // (the grid's)
+        const int wide = verify_columns(dm, n_qt, n_part);               // (the grid's)
         const int at = (((int)blockIdx.z - dm.batch * n_qt) * dm.Hkv + h) * wide + bx, unit = at / n_app;
         if (unit >= dm.batch * dm.Hkv) return;
         b = unit / dm.Hkv;
@@ -1630,11 +1641,10 @@ int launch_select_decode(const Dims &dm, Tensor q, Tensor ck, const int32_t *seq
     const bool tw4 = decode_tiles_per_wave(dm) == 4;
     // Workgroups that append.  Plain decode: one per (sequence, key-value head), at the end of its chunks, or, where these fill the chip about once to
     // four times over, behind all others, so that no chunk waits for a compute unit that one of them has taken (4 sequences of 128K 19.3 -> 16.7 us per
-    // step, 8 22.6 -> 20.3; 120 chunks 14.0 and 14.3, 4096 56.6 and 57.3).  Verification: always behind all.  Several query tiles per
-    // sequence: the chunks are made a multiple of eight, so that all tiles of one run on one XCD and its kernels come from memory once.
+    // step, 8 22.6 -> 20.3; 120 chunks 14.0 and 14.3, 4096 56.6 and 57.3).  Verification: always behind all.
     const int64_t chunks = (int64_t)l.n_part * dm.Hkv * dm.batch;
     const bool behind = append && (dm.n_q > 1 || (chunks > 240 && chunks <= 1024));
-    const int32_t n_wg = n_qt > 1 ? (l.n_part + 7) / 8 * 8 : l.n_part + (append && !behind ? 1 : 0);
+    const int32_t n_wg = verify_columns(dm, n_qt, l.n_part) + (append && !behind ? 1 : 0);
     const int32_t planes = behind ? (int32_t)(((int64_t)dm.batch * ((dm.n_q + 7) / 8) + n_wg - 1) / n_wg) : 0;
     const dim3 grid1(n_wg, dm.Hkv, dm.batch * n_qt + planes);
 #define INFLLMV2_LOGITS(APPEND, TW, ARG)                                                                        \

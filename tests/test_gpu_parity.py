@@ -934,12 +934,14 @@ def test_verify_append_writes_rows_and_completed_kernels():
 # One call against its parts, bit for bit: new kernels on either side of a workgroup's 128, caches no longer than the draft, a length
 # beyond the cache, both widths of the scoring workgroups; buffers (three longer than the longest) of up to 4096 tokens, whose rows one kernel
 # scores, on either side of the workgroups up to which it attends as well; longer ones on either side of those up to which every workgroup ranks, fewer
-# beyond 131072 tokens, whose lists are more than are merged.
+# beyond 131072 tokens, whose lists are more than are merged; chunks of kernels in columns of their number and of a multiple of eight, up to 16 tiles of
+# four drafted tokens and beyond, and up to 768 workgroups.
 @pytest.mark.parametrize("seqlens,n,Hq,Hkv,topk,rho", [
     ([2080, 2079, 2096, 4128, 31], 33, 32, 2, 16, 1), ([2081, 2, 33, 1], 2, 4, 1, 6, 1), ([4200, 64, 95, 63, 9999], 64, 16, 2, 64, 1),
     ([3000, 2090], 16, 16, 1, 24, 2), ([1021], 32, 32, 2, 16, 1), ([1021], 33, 8, 2, 16, 1), ([4093], 16, 32, 2, 16, 1),
     ([4093, 20], 17, 2, 1, 32, 1), ([4094], 16, 32, 2, 16, 1), ([5000], 64, 8, 2, 16, 1), ([5000], 64, 8, 2, 17, 1), ([5000], 42, 4, 1, 24, 1),
-    ([5000], 43, 4, 1, 24, 1), ([131069], 64, 4, 1, 17, 1), ([131070], 64, 4, 1, 16, 1), ([131070], 64, 4, 1, 17, 1)])
+    ([5000], 43, 4, 1, 24, 1), ([131069], 64, 4, 1, 17, 1), ([131070], 64, 4, 1, 16, 1), ([131070], 64, 4, 1, 17, 1),
+    ([20000], 32, 4, 2, 8, 1), ([20000, 19990], 20, 4, 2, 8, 1), ([98000], 32, 2, 2, 8, 1), ([100000], 32, 2, 2, 8, 1)])
 def test_verify_step_equals_its_parts(seqlens, n, Hq, Hkv, topk, rho):
     print("case verify step", seqlens, n, Hq, Hkv, topk, rho, flush=True)
     prm = binding.Params(Hq, Hkv, topk=topk, lse_coarse_ratio=rho)
